@@ -84,9 +84,13 @@ static void* op_params(Op& op) {
   }
 }
 
-static hipError_t launch_op(Op& op, hipStream_t s) {
+// done != NULL: the event completes with the kernel.  It is attached to the dispatch itself: an
+// event recorded behind the kernel is a packet of its own in the queue (3.8 us per record between
+// back-to-back kernels, against 1.5 us for the attached one) and its waiters see it 2.5 us later.
+static hipError_t launch_op(Op& op, hipStream_t s, hipEvent_t done) {
   const KernelDesc d = op_desc(op);
   void* args[1] = {op_params(op)};
+  if (done) return hipExtLaunchKernel(d.func, d.grid, d.block, args, d.shmem, s, nullptr, done, 0);
   return hipLaunchKernel(d.func, d.grid, d.block, args, d.shmem, s);
 }
 
@@ -122,12 +126,14 @@ struct Slot {
   std::vector<Op> post;    // stage 3
   std::vector<Op> overlay; // stage 4: one launch, blockIdx.y = stream of the batch
   hipEvent_t ev_pre = nullptr, ev_infer = nullptr, ev_post = nullptr, ev_overlay = nullptr;
+  // the event that says the frame has left the last stage: ev_overlay, or, for a member of a
+  // group, the first member's (one overlay launch serves them all)
+  hipEvent_t ev_done = nullptr;
   // Consecutive frames rotate over the lanes (activation sets + streams) and overlap;
   // the recurrent cell is the only thing that chains them: its gate convolution (op wait_idx)
-  // waits for the previous frame's state update, whose kernel (op record_idx) is followed by a
-  // record of ev_state.  -1: the network has no recurrent state.
-  int lane = 0, wait_idx = -1, record_idx = -1;
-  hipEvent_t ev_state = nullptr;
+  // waits for the previous frame's state update, the last kernel of stage 2 (ev_infer).
+  // -1: the network has no recurrent state.
+  int lane = 0, wait_idx = -1;
   // stages 1-3 as one HIP graph (kernel nodes chained in order, event-record nodes at the
   // stage boundaries); only the frame pointer of the first node changes from frame to frame
   hipGraph_t graph = nullptr;
@@ -188,6 +194,7 @@ struct hs_app {
   uint64_t n_submitted = 0, n_completed = 0, n_delivered = 0;
   std::mutex mu;
   std::condition_variable cv_work, cv_done;
+  std::atomic<uint64_t> completed_pub{0};   // n_completed for waiters that spin without the lock
   std::thread completer;
   bool stop = false;
   std::string completer_error;
@@ -977,7 +984,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     }
     s.lane = i % lanes;
     s.infer = lane_b[s.lane]->ops;
-    if (b.stateful) { s.wait_idx = b.lstm_conv_op; s.record_idx = b.logits_op; }
+    if (b.stateful) s.wait_idx = b.lstm_conv_op;
     if (s.infer[b.first_conv_op].fam == F_STEM) s.infer[b.first_conv_op].stem.in = s.d_netin;
     else s.infer[b.first_conv_op].conv.in = s.d_netin;
     Op& lo = s.infer[b.logits_op];
@@ -1042,7 +1049,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     HS_HIP(hipEventCreate(&s.ev_infer));
     HS_HIP(hipEventCreate(&s.ev_post));
     HS_HIP(hipEventCreate(&s.ev_overlay));
-    HS_HIP(hipEventCreate(&s.ev_state));
+    s.ev_done = s.ev_overlay;
   }
   return HS_OK;
 }
@@ -1058,12 +1065,12 @@ static void completer_main(hs_app* app) {
       if (app->n_completed >= app->n_submitted) return;   // stop requested and nothing pending
       s = &app->slots[app->n_completed % app->depth];
     }
-    hipError_t e = hipEventSynchronize(s->ev_overlay);
+    hipError_t e = hipEventSynchronize(s->ev_done);
     const uint64_t t_done = now_ns();
     float ms_pre = 0, ms_inf = 0, ms_post = 0;
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_overlay);
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_overlay);
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_post, s->ev_overlay);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_done);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_done);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_post, s->ev_done);
     auto back = [&](float ms) {
       const double ns = (double)ms * 1e6;
       return t_done - (uint64_t)std::max(0.0, ns);
@@ -1084,6 +1091,7 @@ static void completer_main(hs_app* app) {
         app->completer_error = hipGetErrorString(e);
       s->state = SLOT_DONE;
       app->n_completed++;
+      app->completed_pub.store(app->n_completed, std::memory_order_release);
     }
     app->cv_done.notify_all();
   }
@@ -1156,9 +1164,11 @@ static void collect_timing(hs_app* app) {
   app->timed.clear();
 }
 
-static hs_status run_ops(hs_app* app, std::vector<Op>& ops, hipStream_t st, size_t first = 0,
-                         size_t last = (size_t)-1) {
-  for (size_t i = first; i < std::min(last, ops.size()); ++i) {
+// done: event that completes with the last of the launched ops.
+static hs_status run_ops(hs_app* app, std::vector<Op>& ops, hipStream_t st, hipEvent_t done,
+                         size_t first = 0, size_t last = (size_t)-1) {
+  last = std::min(last, ops.size());
+  for (size_t i = first; i < last; ++i) {
     Op& op = ops[i];
     if (app->timing) {
       TimedLaunch t{op.fam, op.flops, op.bytes, nullptr, nullptr};
@@ -1171,9 +1181,10 @@ static hs_status run_ops(hs_app* app, std::vector<Op>& ops, hipStream_t st, size
       HS_HIP(hipExtLaunchKernel(d.func, d.grid, d.block, args, d.shmem, st, t.e0, t.e1, 0));
       app->timed.push_back(t);
     } else {
-      HS_HIP(launch_op(op, st));
+      HS_HIP(launch_op(op, st, i + 1 == last ? done : nullptr));
     }
   }
+  if (app->timing && done) HS_HIP(hipEventRecord(done, st));   // the dispatch carries e1 already
   return HS_OK;
 }
 
@@ -1193,7 +1204,7 @@ static hipKernelNodeParams node_params(Op& op, void** args) {
 
 // Stages 1-3 of one queue slot as a linear HIP graph: resize, [event], network kernels,
 // [event], postprocess.  Built once; per frame only the resize node's source pointer changes.
-// wait_ev: the previous slot's ev_state (the frame before this slot's frame ran there).
+// wait_ev: the previous slot's ev_infer (the frame before this slot's frame ran there).
 static hs_status build_slot_graph(Slot& s, hipEvent_t wait_ev) {
   HS_HIP(hipGraphCreate(&s.graph, 0));
   hipGraphNode_t prev = nullptr;
@@ -1222,7 +1233,6 @@ static hs_status build_slot_graph(Slot& s, hipEvent_t wait_ev) {
       prev = n;
     }
     HS_HIP(add_kernel(s.infer[j], nullptr));
-    if ((int)j == s.record_idx) HS_HIP(add_event(s.ev_state));
   }
   HS_HIP(add_event(s.ev_infer));
   for (Op& op : s.post) HS_HIP(add_kernel(op, nullptr));
@@ -1390,7 +1400,7 @@ hs_status hs_create_app(hs_ctx* ctx, const hs_app_desc* desc, hs_app** out) {
   for (size_t i = 0; st == HS_OK && i < app->slots.size(); ++i) {
     const size_t n_slots = app->slots.size();
     st = build_slot_graph(app->slots[i],
-                          n_slots > 1 ? app->slots[(i + n_slots - 1) % n_slots].ev_state : nullptr);
+                          n_slots > 1 ? app->slots[(i + n_slots - 1) % n_slots].ev_infer : nullptr);
   }
   if (st == HS_OK) st = make_streams(app, nullptr, nullptr, 0);
   if (st != HS_OK) {
@@ -1401,7 +1411,6 @@ hs_status hs_create_app(hs_ctx* ctx, const hs_app_desc* desc, hs_app** out) {
       if (s.ev_infer) (void)hipEventDestroy(s.ev_infer);
       if (s.ev_post) (void)hipEventDestroy(s.ev_post);
       if (s.ev_overlay) (void)hipEventDestroy(s.ev_overlay);
-      if (s.ev_state) (void)hipEventDestroy(s.ev_state);
     }
     destroy_streams(app);
     if (app->pinned) (void)hipHostFree(app->pinned);
@@ -1439,7 +1448,6 @@ hs_status hs_destroy_app(hs_app* app) {
     (void)hipEventDestroy(s.ev_infer);
     (void)hipEventDestroy(s.ev_post);
     (void)hipEventDestroy(s.ev_overlay);
-    (void)hipEventDestroy(s.ev_state);
   }
   destroy_streams(app);
   if (app->pinned) (void)hipHostFree(app->pinned);
@@ -1670,34 +1678,31 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   app->lane_last_stream[s->lane] = lane_stream;
   // the caller's producer (another stream) may still be writing the frames
   if (frames_ready) HS_HIP(hipStreamWaitEvent(lane_stream, frames_ready, 0));
-  if (app->launch_mode == HS_LAUNCH_GRAPH && !app->timing && !static_scratch) {
+  const bool graph = app->launch_mode == HS_LAUNCH_GRAPH && !app->timing && !static_scratch;
+  if (graph) {
     void* args[1];
     hipKernelNodeParams kp = node_params(s->pre[0], args);
     HS_HIP(hipGraphExecKernelNodeSetParams(s->graph_exec, s->resize_nodes[0], &kp));
     HS_HIP(hipGraphLaunch(s->graph_exec, lane_stream));
   } else {
-    st = run_ops(app, s->pre, lane_stream);
+    st = run_ops(app, s->pre, lane_stream, s->ev_pre);
     if (st != HS_OK) return st;
-    HS_HIP(hipEventRecord(s->ev_pre, lane_stream));
-    if (s->wait_idx >= 0) {
+    if (s->wait_idx >= 0 && app->depth > 1) {
       // the recurrent cell waits for the previous frame's state update (other lane)
       Slot& before = app->slots[(size_t)((s - app->slots.data()) + app->depth - 1) % app->depth];
-      st = run_ops(app, infer, lane_stream, 0, (size_t)s->wait_idx);
+      st = run_ops(app, infer, lane_stream, nullptr, 0, (size_t)s->wait_idx);
       if (st != HS_OK) return st;
-      if (app->depth > 1) HS_HIP(hipStreamWaitEvent(lane_stream, before.ev_state, 0));
-      st = run_ops(app, infer, lane_stream, (size_t)s->wait_idx, (size_t)s->record_idx + 1);
-      if (st != HS_OK) return st;
-      HS_HIP(hipEventRecord(s->ev_state, lane_stream));
-      st = run_ops(app, infer, lane_stream, (size_t)s->record_idx + 1);
+      HS_HIP(hipStreamWaitEvent(lane_stream, before.ev_infer, 0));
+      st = run_ops(app, infer, lane_stream, s->ev_infer, (size_t)s->wait_idx);
     } else {
-      st = run_ops(app, infer, lane_stream);
+      st = run_ops(app, infer, lane_stream, s->ev_infer);
     }
     if (st != HS_OK) return st;
-    HS_HIP(hipEventRecord(s->ev_infer, lane_stream));
-    st = run_ops(app, s->post, lane_stream);
+    st = run_ops(app, s->post, lane_stream, s->ev_post);
     if (st != HS_OK) return st;
   }
-  HS_HIP(hipEventRecord(s->ev_post, lane_stream));
+  if (graph) HS_HIP(hipEventRecord(s->ev_post, lane_stream));
+  s->ev_done = s->ev_overlay;
   if (!own_overlay) {
     *slot_out = s;
     *stream_out = lane_stream;
@@ -1705,9 +1710,8 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   }
   hipStream_t ov_stream = app->s_overlay ? app->s_overlay : lane_stream;
   if (ov_stream != lane_stream) HS_HIP(hipStreamWaitEvent(ov_stream, s->ev_post, 0));
-  st = run_ops(app, s->overlay, ov_stream);
+  st = run_ops(app, s->overlay, ov_stream, s->ev_overlay);
   if (st != HS_OK) return st;
-  HS_HIP(hipEventRecord(s->ev_overlay, ov_stream));
   finish_submit(app, s);
   return HS_OK;
 }
@@ -1797,11 +1801,41 @@ hs_status hs_poll_batch(hs_app* app, hs_result* out) {
   return deliver_locked(app, out);
 }
 
+// Spins until the application has completed more than n_delivered frames, at most as long as a
+// frame takes in practice (1 ms) and never past `deadline_ns` (now_ns clock); the caller then takes
+// the lock and sleeps if need be.  A thread that sleeps on the condition variable sees a finished
+// frame 7 us (one frame in flight) to 14 us (after 0.6 ms of sleep, its core idle) late.
+static void spin_for_completion(hs_app* app, uint64_t n_delivered, uint64_t deadline_ns) {
+  static const bool enough_cores = std::thread::hardware_concurrency() >= 4;
+  if (!enough_cores) return;
+  const uint64_t until = std::min<uint64_t>(now_ns() + 1000000ull, deadline_ns);
+  do {
+    for (int i = 0; i < 32; ++i) {
+      if (app->completed_pub.load(std::memory_order_acquire) > n_delivered) return;
+      __builtin_ia32_pause();
+    }
+  } while (now_ns() < until);
+}
+
+static uint64_t deadline_after(uint64_t timeout_ns) {
+  const uint64_t t = now_ns();
+  return timeout_ns > UINT64_MAX - t ? UINT64_MAX : t + timeout_ns;
+}
+
 hs_status hs_wait_batch(hs_app* app, hs_result* out, uint64_t timeout_ns) {
   if (!app || !out) { set_error("hs_wait_batch: NULL argument"); return HS_E_INVAL; }
   if (refuse_grouped(app, "hs_wait_batch") != HS_OK) return HS_E_STATE;
+  uint64_t delivered, in_flight;
+  {
+    std::lock_guard<std::mutex> lk(app->mu);
+    delivered = app->n_delivered;
+    in_flight = app->n_submitted - app->n_completed;
+  }
+  const uint64_t deadline_ns = deadline_after(timeout_ns);
+  if (in_flight) spin_for_completion(app, delivered, deadline_ns);
   std::unique_lock<std::mutex> lk(app->mu);
-  const bool ok = app->cv_done.wait_for(lk, std::chrono::nanoseconds(timeout_ns), [&] {
+  const uint64_t now = now_ns(), left = deadline_ns > now ? deadline_ns - now : 0;
+  const bool ok = app->cv_done.wait_for(lk, std::chrono::nanoseconds(left), [&] {
     return app->n_delivered < app->n_completed;
   });
   if (!ok) {
@@ -1977,10 +2011,8 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   auto overlay_all = [&]() -> hs_status {
     for (size_t i = 0; i < n; ++i)
       if (tail[i] != ov_stream) HS_HIP(hipStreamWaitEvent(ov_stream, slot[i]->ev_post, 0));
-    const hs_status st = run_ops(a0, group->overlay, ov_stream);
-    if (st != HS_OK) return st;
-    for (size_t i = 0; i < n; ++i) HS_HIP(hipEventRecord(slot[i]->ev_overlay, ov_stream));
-    return HS_OK;
+    for (size_t i = 1; i < n; ++i) slot[i]->ev_done = slot[0]->ev_overlay;
+    return run_ops(a0, group->overlay, ov_stream, slot[0]->ev_overlay);
   };
   const hs_status st = overlay_all();
   if (st != HS_OK) return fail_all(st);
@@ -2015,8 +2047,15 @@ hs_status hs_poll_group(hs_group* group, hs_result* out) {
 hs_status hs_wait_group(hs_group* group, hs_result* out, uint64_t timeout_ns) {
   if (!group || !out) { set_error("hs_wait_group: NULL argument"); return HS_E_INVAL; }
   const auto deadline = std::chrono::steady_clock::now() + std::chrono::nanoseconds(timeout_ns);
+  const uint64_t deadline_ns = deadline_after(timeout_ns);
   for (hs_app* a : group->members) {
     std::unique_lock<std::mutex> lk(a->mu);
+    if (a->n_delivered >= a->n_completed && a->n_completed < a->n_submitted) {
+      const uint64_t delivered = a->n_delivered;
+      lk.unlock();
+      spin_for_completion(a, delivered, deadline_ns);
+      lk.lock();
+    }
     if (!a->cv_done.wait_until(lk, deadline, [&] { return a->n_delivered < a->n_completed; })) {
       set_error("hs_wait_group: timed out");
       return HS_E_NOT_READY;
