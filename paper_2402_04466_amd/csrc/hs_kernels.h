@@ -46,48 +46,47 @@ KernelDesc describe(const ResizeParams& p);
 // (q % chunks_per_tap) * KC of input pixel (stride*oy + ky - pad, stride*ox + kx - pad).
 // Out-of-range pixels read as zero.  First layers (3 input channels) use a padded
 // 4-channel image and "row taps": kw = 1, a chunk spans several adjacent pixels.
+enum ConvVariant {
+  CONV_GENERIC,   // tile of 64 consecutive pixels x 64 channels, any shape (k_conv_mfma)
+  CONV_C64_WALK,  // 3x3/1 layers with 64 input channels on large grids: tile 8 x 16, resident weights,
+                  // a workgroup walks tiles_per_wg tiles (k_conv3x3_c64_walk)
+  CONV_BLOCK64,   // a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU between,
+                  // shortcut from the input, ReLU) in one launch (k_block64_fused): wt = first,
+                  // wt2 = second convolution, res = in
+  CONV_DIRA,      // 3x3/1 layers with >= 2 Cin chunks: tile 8 x 16 pixels x 64 channels, weights read
+                  // as MFMA fragments straight from wt_frag (k_conv3x3_dira)
+  CONV_S2_DIRA,   // 3x3/2 layers (+ fused 1x1/2 projection) on large grids: tile 8 x 8 x 128, weights
+                  // from wt_frag / wt2_frag, tile walking, no residual (k_conv3x3s2_dira)
+  CONV_KW         // 3x3 layers of either stride (+ fused projection) on small and middle grids, K
+                  // splits inside the workgroup, weights from wt_frag / wt2_frag (k_conv3x3_kw)
+};
 struct ConvParams {
   const f16* in;
   const f16* wt;        // packed [cout_pad][ktot], ktot = nchunks*KC, zero rows above cout
-  const f16* wt_frag;   // variant 6: the same weights in MFMA fragment order,
-                        // [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane r + 32 h
-                        // holding k = 16 * step + 8 * h .. + 7 of channel 32 * group + r
+  const f16* wt_frag;   // the same weights in MFMA fragment order (the variants that read it have no
+                        // wt): [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
+                        // r + 32 h holding k = 16 * step + 8 * h .. + 7 of channel 32 * group + r
   int hin, win, cin_pitch;
   int hout, wout, m;    // m = batch*hout*wout output pixels (images stacked along m)
   int batch, img_m;     // images per launch, pixels per image (hout*wout)
   int cout, cout_pad;   // cout_pad: multiple of the block's N tile
   int kc;               // 16, 32 or 64
   int depth;            // prefetch depth in chunks: 4, or 8 (kc == 64 only)
-  int variant;          // 0: generic tile of 64 consecutive pixels (k_conv_mfma)
-                        // 1, 2, 3: 3x3/1 layers with a shared input patch (k_conv3x3_halo),
-                        //    needs cin % 64 == 0; spatial tile 8 x 8 (1) or 8 x 16 (2, 3);
-                        //    3 keeps one patch buffer and three weight stages, so that three
-                        //    workgroups fit a CU (grids well beyond two workgroups per CU)
-                        // 4: 3x3/2 pad-1 layers the same way (8 x 8 tile, patch stored as four
-                        //    parity planes), optionally with the block's 1x1/2 projection of
-                        //    the same input fused in (wt2 != NULL)
-                        // 5: a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU
-                        //    between, shortcut from the input, ReLU) in one launch
-                        //    (k_block64_fused): wt = first, wt2 = second convolution, res = in
-                        // 6: 3x3/1 layers with >= 2 Cin chunks on grids of >= 1.5 workgroups per CU:
-                        //    8 x 16 tile as variant 2, weights read as MFMA fragments straight
-                        //    from wt_frag into registers, no weight tile in LDS (k_conv3x3_dira)
-                        // 7: 3x3/2 layers (+ fused 1x1/2 projection) on such grids, weights from
-                        //    wt_frag / wt2_frag, fp16 outputs with cout % 64 == 0 or split-K
-                        //    partials, no residual (k_conv3x3s2_dira)
-  int tiles_x;          // variant 1..5: spatial tiles per output row
+  int variant;          // ConvVariant
+  int kw_splits, kw_cgroups, kw_groups;   // CONV_KW: K splits and groups of 32 channels (their
+                        // product: wavefronts per workgroup), groups of 4 x 8 pixels per tile
+  int tiles_x;          // spatial variants: tiles per output row
   int ntaps, kw, chunks_per_tap, nchunks, ktot;
   int stride, pad;
-  // split-K: blockIdx.z handles chunks [z*chunks_per_split, ...)
+  // K splits as workgroups (CONV_GENERIC; CONV_KW has its splits inside a workgroup and nsplit 1):
+  // split z handles chunks [z*chunks_per_split, ...)
   int nsplit, chunks_per_split;
-  int tiles_m, tiles_n; // 64x64 output tiles; the grid is 8 * tiles_per_xcd workgroups
-  int tiles_per_wg;     // variant 1..4: consecutive spatial tiles one workgroup walks (>= 1);
+  int tiles_m, tiles_n; // spatial x channel tiles; the grid is 8 * tiles_per_xcd workgroups
+  int tiles_per_wg;     // consecutive spatial tiles one workgroup walks (>= 1);
                         // workgroups = ceil(tiles_m / tiles_per_wg) * tiles_n * nsplit
   int tiles_per_xcd;    // ceil(workgroups / 8)
-  int n_block;          // variant 1..4: channel tiles per block of the tile order (divides tiles_n;
+  int n_block;          // channel tiles per block of the tile order (divides tiles_n;
                         // 1: spatial tile fastest, tiles_n: channel tile fastest)
-  int frag_ok;          // host planning hint: the layer may use the fragment-weight kernels
-                        // (fp16 output of whole 64-channel tiles or split-K partials, no residual)
   int use_partial;      // 1: store fp32 partial sums for a reduction kernel, no epilogue here
   float* partial;       // [nsplit][m][cout_pad] fp32
   // fused epilogue (use_partial == 0)
@@ -97,12 +96,13 @@ struct ConvParams {
   int res_pitch;
   int relu;
   float* out_f32;       // if set: planar fp32 out_f32[n*m_total + m] instead of `out`
-  // variant 4 only: fused 1x1 stride-2 projection of the same input (no residual, no ReLU)
-  const f16* wt2;       // packed [cout_pad][cin], or NULL
-  const f16* wt2_frag;  // variant 7: the projection in MFMA fragment order,
-                        // [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves], or NULL
+  const f16* wt2;       // CONV_BLOCK64: second convolution
+  // stride 2: fused 1x1 stride-2 projection of the same input (no residual, no ReLU), or NULL:
+  // [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
+  const f16* wt2_frag;
   f16* out2; int out2_pitch;
-  float* partial2;      // [nsplit][m][cout_pad] fp32 when use_partial
+  // weights of the layer that runs next, for the kernels that prefetch them: 128-byte lines (0: none)
+  const void* next_wt; int next_lines;
 };
 KernelDesc describe(const ConvParams& p);
 
@@ -110,8 +110,6 @@ KernelDesc describe(const ConvParams& p);
 struct SplitKEpilogueParams {
   const float* partial; int nsplit; int m; int cout; int cout_pad;
   f16* out; int out_pitch; const f16* res; int res_pitch; int relu; float* out_f32; int img_m;
-  // optional second tensor reduced in the same launch (fused projection): plain fp16 store
-  const float* partial2; f16* out2; int out2_pitch;
 };
 KernelDesc describe(const SplitKEpilogueParams& p);
 

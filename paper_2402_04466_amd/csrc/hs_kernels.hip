@@ -473,333 +473,20 @@ __global__ __launch_bounds__(256) void k_conv_mfma(ConvParams p) {
 #undef HS_LOAD_CHUNK
 
 // =============================================================================================
-// Stage 2, 3x3 stride-1 pad-1 layers (13 of the 21 convolutions, 85 % of the flops): the same
-// implicit GEMM, but the workgroup's output tile is a SPATIAL block (8 rows x 8*MT columns),
-// so that the nine taps read one shared (8+2) x (8*MT+2) input patch.  Per 64-channel chunk
-// of Cin the patch goes to LDS once and serves all nine taps; only the weight tile (64 x 64
-// halves per tap) is streamed per tap.  Global traffic per tap drops from 16 KB to
-// 8 KB + patch/9 -- these layers are bound by bytes fetched per workgroup, not by MFMA rate.
-// Pipeline: WS weight stages in registers (stage = tap % WS, a literal): while a tap is
-// computed, the weights of the step WS taps ahead are being fetched -- with WS == 9 a whole
-// chunk of weights is in flight, which suits grids of at most two workgroups per CU; the next
-// chunk's patch is prefetched during the first taps of the current one and, with a single patch
-// buffer (PB == 1), handed to LDS behind one extra barrier per chunk.  PB == 1 with WS == 3 is
-// the lean form: 45 KB of LDS and under 170 registers, three workgroups per CU.  The nine steps
-// of a chunk are written out, loads are unconditional and branch-free.
-// Wavefront (wm, wn): pixel rows 4*wm .. 4*wm+3 (MT groups of 4 x 8 pixels), channels
-// 32*wn .. +31.  chunks_per_split / nchunks count Cin chunks here (split-K over Cin).
+// Stage 2, 3x3 layers (all of the big network's convolutions but the stem): the same implicit GEMM,
+// but a workgroup's output tile is a SPATIAL block, so that the nine taps read one shared input
+// patch in LDS.  Patch pixels are padded to 144 bytes and patch rows to 128 mod 256 bytes: the 16
+// lanes of one ds_read_b128 pass (two rows of 8 pixels) then fall into 16 different 16-byte bank
+// groups.  Every output accumulates chunk by chunk (64 input channels), tap by tap, four K-steps
+// of 16 per tap, whichever of the stride-1 kernels computes it: their results are bit-identical.
+//
+// Tile order of all of them: workgroup id mod 8 selects the XCD, and each XCD (own L2) takes a run
+// of consecutive tiles.  Tiles are ordered in blocks of n_block channel tiles; inside a block the
+// channel tile varies fastest, then the spatial tile.  n_block == 1: the workgroups of one L2 share
+// a weight slice and every L2 that holds a channel tile fetches the input; n_block == tiles_n: they
+// share input patches and every L2 fetches all the weights.  The host picks the block size that
+// brings the fewest bytes into the eight L2s.
 // =============================================================================================
-template <int MT, int PB, int WS, int STRIDE, bool PERSIST, int OCC>
-__global__ __launch_bounds__(256, OCC) void k_conv3x3_halo(ConvParams p) {
-  constexpr int KC = 64, TH = 8, TW = 8 * MT;
-  constexpr int IPH = STRIDE * TH + 3 - STRIDE, IPW = STRIDE * TW + 3 - STRIDE;   // input patch
-  constexpr int NPL = STRIDE * STRIDE;                 // parity planes the patch is stored as
-  constexpr int PLH = STRIDE == 1 ? IPH : TH + 1, PLW = STRIDE == 1 ? IPW : TW + 1;
-  constexpr int NPIX = IPH * IPW;
-  constexpr int PITCH = KC + 8;
-  constexpr int BN = 64;                     // output channels per workgroup
-  constexpr int WL = BN / 32;                // weight vectors per thread and tap
-  // Plane rows are padded so that consecutive rows start 128 bytes apart modulo 256: the 16
-  // lanes of one ds_read_b128 pass (two rows of 8 pixels, 144-byte pixel pitch) then fall into
-  // 16 different 16-byte bank groups.
-  constexpr int RP = (PLW * PITCH * 2 + ((128 - (PLW * PITCH * 2) % 256 + 256) % 256)) / 2;
-  static_assert((RP * 2) % 256 == 128, "plane row pitch must be 128 mod 256 bytes");
-  constexpr int PV = NPIX * 8;               // 16-byte vectors in a patch
-  constexpr int PL = (PV + 255) / 256;       // patch vectors per thread (4, 6 or 10)
-  constexpr int PT = (PL + 8) / 9;           // of which fetched per tap
-  static_assert(PT <= 2, "patch prefetch is spread over the nine taps");
-  static_assert(WS == 9 || WS == 3, "weight stages: a divisor of nine");
-  static_assert(STRIDE == 1 || (MT == 1 && PB == 1), "stride 2: 8 x 8 tile, one patch buffer");
-  __shared__ __align__(16) f16 s_patch[PB][NPL * PLH * RP];
-  __shared__ __align__(16) f16 s_w[2][BN * PITCH];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  // A workgroup owns tiles_per_wg consecutive spatial tiles of one channel tile (and K split)
-  // and walks them in one software pipeline: the next tile's patch is prefetched during the
-  // last chunk of the current one, so the cold start is paid once per workgroup.
-  const int groups_m = (p.tiles_m + p.tiles_per_wg - 1) / p.tiles_per_wg;
-  if (tile >= groups_m * p.tiles_n * p.nsplit) return;
-  // Tile order inside a K split: blocks of n_block channel tiles; inside a block the channel
-  // tile varies fastest, then the spatial tile.  n_block == 1: the workgroups of one L2 share
-  // a weight slice and every L2 that holds a channel tile fetches the input; n_block ==
-  // tiles_n: they share input patches and every L2 fetches all the weights.  The host picks
-  // the block size that brings the fewest bytes into the eight L2s.
-  const int within = tile % (groups_m * p.tiles_n);
-  const int blk = groups_m * p.n_block, in_blk = within % blk;
-  const int tm_begin = (in_blk / p.n_block) * p.tiles_per_wg;
-  const int tm_end = PERSIST ? min(p.tiles_m, tm_begin + p.tiles_per_wg) : tm_begin + 1;
-  const int tile_n = (within / blk) * p.n_block + in_blk % p.n_block;
-  const int split = tile / (groups_m * p.tiles_n);
-  const int tiles_img = p.tiles_m / p.batch;            // spatial tiles per image
-  const int n0 = tile_n * BN;
-  const int cc_begin = split * p.chunks_per_split;
-  const int cc_end = min(p.chunks_per_tap, cc_begin + p.chunks_per_split);
-  const bool has_proj = STRIDE == 2 && p.wt2 != nullptr;
-  // A layer with a single Cin chunk uses the same nine weight tiles for every tile a workgroup
-  // walks: with all nine held in the register stages they are fetched once per workgroup
-  // instead of once per tile (at 12 frames per launch the stage-1 layers otherwise pull four
-  // times more weight bytes than activation bytes from L2).
-  const bool keep_w = PERSIST && WS == 9 && p.chunks_per_tap == 1;
-
-  // loop-invariant loader state
-  const f16* l_wbase[WL];
-  const f16* l_w2base[WL];
-  int l_wlds[WL];
-#pragma unroll
-  for (int i = 0; i < WL; ++i) {
-    const int v = tid + 256 * i, row = v >> 3, kv = v & 7;
-    l_wbase[i] = p.wt + (size_t)(n0 + row) * p.ktot + kv * 8;
-    l_w2base[i] = has_proj ? p.wt2 + (size_t)(n0 + row) * (p.chunks_per_tap * KC) + kv * 8 : p.wt;
-    l_wlds[i] = row * PITCH + kv * 8;
-  }
-  // patch loader: the LDS slot of every vector is fixed, its source depends on the tile.
-  // l_pyx packs the vector's pixel inside the patch; a source is kept as an offset in halves
-  // from p.in (below 2^31 by construction of the plan), negative when the pixel is padding.
-  int l_plds[PL], l_pyx[PL];
-#pragma unroll
-  for (int i = 0; i < PL; ++i) {
-    const int v = tid + 256 * i;
-    const int pix = min(v >> 3, NPIX - 1), kv = v & 7;
-    const int py = pix / IPW, px = pix - py * IPW;
-    l_pyx[i] = py | (px << 8);
-    // stride 2: pixel (py, px) goes to parity plane (py & 1, px & 1) at (py / 2, px / 2), so
-    // that the lanes of a tap read neighbouring plane pixels, as for stride 1.  -1: no such vector
-    l_plds[i] = v >= PV ? -1
-                : STRIDE == 1 ? py * RP + px * PITCH + kv * 8
-                              : (((py & 1) * 2 + (px & 1)) * PLH + (py >> 1)) * RP +
-                                    (px >> 1) * PITCH + kv * 8;
-  }
-  // source offsets of spatial tile TM_ (also its image and origin)
-#define HS_TILE_SETUP(TM_, POFF_, IMG_, Y0_, X0_)                                              \
-  {                                                                                            \
-    IMG_ = (TM_) / tiles_img;                                                                  \
-    const int ts_ = (TM_) - IMG_ * tiles_img;                                                  \
-    const int ty_ = ts_ / p.tiles_x;                                                           \
-    Y0_ = ty_ * TH;                                                                            \
-    X0_ = (ts_ - ty_ * p.tiles_x) * TW;                                                        \
-    _Pragma("unroll") for (int i = 0; i < PL; ++i) {                                           \
-      const int iy_ = STRIDE * Y0_ + (l_pyx[i] & 0xff) - 1;                                    \
-      const int ix_ = STRIDE * X0_ + (l_pyx[i] >> 8) - 1;                                      \
-      const bool inb_ = l_plds[i] >= 0 && iy_ >= 0 && iy_ < p.hin && ix_ >= 0 && ix_ < p.win;  \
-      POFF_[i] = inb_ ? ((IMG_ * p.hin + iy_) * p.win + ix_) * p.cin_pitch + (tid & 7) * 8 : -1; \
-    }                                                                                          \
-  }
-  int l_poff[PL], l_poff_n[PL];
-  int img, y0, x0, img_n, y0_n, x0_n;
-  HS_TILE_SETUP(tm_begin, l_poff, img, y0, x0)
-
-  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  floatx16 acc[MT], acc2 = zero16;
-#pragma unroll
-  for (int g = 0; g < MT; ++g) acc[g] = zero16;
-
-  const int wm = wave & 1, wn = wave >> 1;
-  // fragment bases: weights row (32*wn + r); pixel (4*wm + r/8, r%8) of column group g
-  const int fw_off = (wn * 32 + r) * PITCH + h * 8;
-  const int fp_off = (4 * wm + (r >> 3)) * RP + (r & 7) * PITCH + h * 8;
-
-  u32x4 st_w[WS][WL];
-  u32x4 st_w2[WL];
-  u32x4 st_p[PL];
-#define HS_LOAD_W(S_, CC_, TAP_)                                                               \
-  {                                                                                            \
-    const long off_ = ((long)(TAP_) * p.chunks_per_tap + (CC_)) * KC;                          \
-    _Pragma("unroll") for (int i = 0; i < WL; ++i)                                             \
-      st_w[S_][i] = *reinterpret_cast<const u32x4*>(l_wbase[i] + off_);                        \
-  }
-#define HS_LOAD_W2(CC_)                                                                        \
-  _Pragma("unroll") for (int i = 0; i < WL; ++i)                                               \
-    st_w2[i] = *reinterpret_cast<const u32x4*>(l_w2base[i] + (long)(CC_) * KC);
-#define HS_LOAD_P(I_, CC_, POFF_)                                                              \
-  st_p[I_] = *reinterpret_cast<const u32x4*>(p.in + (POFF_[I_] >= 0 ? POFF_[I_] + (CC_) * KC : 0));
-  // offset of tap (ky, kx) inside the patch, relative to the wavefront's first pixel
-#define HS_TAP_OFF(KY_, KX_)                                                                   \
-  (STRIDE == 1 ? (KY_) * RP + (KX_) * PITCH                                                    \
-               : ((((KY_) & 1) * 2 + ((KX_) & 1)) * PLH + ((KY_) >> 1)) * RP + ((KX_) >> 1) * PITCH)
-
-  // One tap of chunk cc of the current tile.  TAP_ and LAST_ are literals: every register index
-  // and every refill decision is resolved at compile time.  Weight stage TAP_ % WS is handed to
-  // LDS and refilled with the weights of the step WS taps ahead; CCN_, PBASE_N_, PINB_N_ name
-  // the item after this chunk (next chunk of this tile, or first chunk of the next tile).
-#define HS_TAP(TAP_, LAST_, CCN_, POFF_N_)                                                     \
-  {                                                                                            \
-    _Pragma("unroll") for (int i = 0; i < WL; ++i)                                             \
-      *reinterpret_cast<u32x4*>(&s_w[buf][l_wlds[i]]) = st_w[(TAP_) % WS][i];                  \
-    if ((TAP_) == 0) {                                                                         \
-      if (PB == 1) __syncthreads(); /* every wave is done with the previous chunk's patch */   \
-      const u32x4 zero_ = {0u, 0u, 0u, 0u};                                                    \
-      _Pragma("unroll") for (int i = 0; i < PL; ++i)                                           \
-        if (l_plds[i] >= 0)                                                                    \
-          *reinterpret_cast<u32x4*>(&s_patch[pb][l_plds[i]]) = l_poff[i] >= 0 ? st_p[i] : zero_; \
-    }                                                                                          \
-    __syncthreads();                                                                           \
-    if ((!(LAST_) || (TAP_) + WS < 9) && !keep_w)                                              \
-      HS_LOAD_W((TAP_) % WS, ((TAP_) + WS >= 9 ? (CCN_) : cc), ((TAP_) + WS) % 9)              \
-    if (!(LAST_)) {                                                                            \
-      _Pragma("unroll") for (int i = PT * (TAP_); i < PT * (TAP_) + PT; ++i)                   \
-        if (i < PL) { HS_LOAD_P(i < PL ? i : 0, CCN_, POFF_N_) }                               \
-    }                                                                                          \
-    const f16* fw_ = &s_w[buf][fw_off];                                                        \
-    const f16* fp_ = &s_patch[pb][fp_off + HS_TAP_OFF((TAP_) / 3, (TAP_) % 3)];                \
-    _Pragma("unroll") for (int ks = 0; ks < KC / 16; ++ks) {                                   \
-      const half8 a_ = *reinterpret_cast<const half8*>(fw_ + ks * 16);                         \
-      _Pragma("unroll") for (int g = 0; g < MT; ++g) {                                         \
-        const half8 b_ = *reinterpret_cast<const half8*>(fp_ + g * 8 * PITCH + ks * 16);       \
-        acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_, b_, acc[g], 0, 0, 0);              \
-      }                                                                                        \
-    }                                                                                          \
-    buf ^= 1;                                                                                  \
-  }
-  // Tenth step of a stride-2 chunk: the 1x1 stride-2 projection of the same input reads exactly
-  // the centre tap's pixels, so it rides along with its own weights and accumulator.
-#define HS_PROJ(LAST_, CCN_)                                                                   \
-  if (has_proj) {                                                                              \
-    _Pragma("unroll") for (int i = 0; i < WL; ++i)                                             \
-      *reinterpret_cast<u32x4*>(&s_w[buf][l_wlds[i]]) = st_w2[i];                              \
-    __syncthreads();                                                                           \
-    if (!(LAST_)) { HS_LOAD_W2(CCN_) }                                                         \
-    const f16* fw_ = &s_w[buf][fw_off];                                                        \
-    const f16* fp_ = &s_patch[pb][fp_off + HS_TAP_OFF(1, 1)];                                  \
-    _Pragma("unroll") for (int ks = 0; ks < KC / 16; ++ks) {                                   \
-      const half8 a_ = *reinterpret_cast<const half8*>(fw_ + ks * 16);                         \
-      const half8 b_ = *reinterpret_cast<const half8*>(fp_ + ks * 16);                         \
-      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_, b_, acc2, 0, 0, 0);                    \
-    }                                                                                          \
-    buf ^= 1;                                                                                  \
-  }
-#define HS_CHUNK(LAST_, CCN_, PO_N_)                                                           \
-  HS_TAP(0, LAST_, CCN_, PO_N_) HS_TAP(1, LAST_, CCN_, PO_N_) HS_TAP(2, LAST_, CCN_, PO_N_)    \
-  HS_TAP(3, LAST_, CCN_, PO_N_) HS_TAP(4, LAST_, CCN_, PO_N_) HS_TAP(5, LAST_, CCN_, PO_N_)    \
-  HS_TAP(6, LAST_, CCN_, PO_N_) HS_TAP(7, LAST_, CCN_, PO_N_) HS_TAP(8, LAST_, CCN_, PO_N_)    \
-  if (STRIDE == 2) { HS_PROJ(LAST_, CCN_) }
-
-  const int wm_rows = 4 * wm + (r >> 3);
-  const int n_base = n0 + wn * 32 + h * 4;
-  // The residual of a block's second convolution is fetched while the tile's last chunk is
-  // still being computed, not between the last MFMA and the store (one full memory latency
-  // at the end of every such launch otherwise).  Loads are unconditional, from clamped addresses.
-  const bool res_here = p.res != nullptr && !p.use_partial;
-  // fp16 output with whole 64-channel tiles: 16-byte stores after a lane exchange (store_octets);
-  // not in the tile-walking stride-2 instantiation, which has no registers to spare for it
-  const bool wide_out =
-      !(STRIDE == 2 && PERSIST) && !p.use_partial && p.out_f32 == nullptr && (p.cout & 63) == 0;
-  half4 res_pre[MT][4];
-#define HS_RES_PREFETCH()                                                                      \
-  if (res_here) {                                                                              \
-    const int oy_ = min(y0 + wm_rows, p.hout - 1);                                             \
-    _Pragma("unroll") for (int g = 0; g < MT; ++g) {                                           \
-      const int ox_ = min(x0 + 8 * g + (r & 7), p.wout - 1);                                   \
-      const f16* rp_ = p.res + (size_t)(img * p.img_m + oy_ * p.wout + ox_) * p.res_pitch;     \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i)                                            \
-        res_pre[g][i] = *reinterpret_cast<const half4*>(rp_ + min(n_base + 8 * i, p.cout - 4)); \
-    }                                                                                          \
-  }
-  // Stores the finished tile (image img, origin y0, x0) and clears the accumulators.
-  // Accumulator quad i of group g: channels n_base + 8*i .. +3 of pixel (oy, ox_g).
-#define HS_STORE_TILE()                                                                        \
-  {                                                                                            \
-    const int oy = y0 + wm_rows;                                                               \
-    _Pragma("unroll") for (int g = 0; g < MT; ++g) {                                           \
-      const int ox = x0 + 8 * g + (r & 7);                                                     \
-      if (oy < p.hout && ox < p.wout) {                                                        \
-        const int m = img * p.img_m + oy * p.wout + ox;                                        \
-        if (p.use_partial) {                                                                   \
-          float* dst = p.partial + ((size_t)split * p.m + m) * p.cout_pad + n_base;            \
-          _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
-            *reinterpret_cast<float4*>(dst + 8 * i) = make_float4(                             \
-                acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);       \
-        } else if (!wide_out) {                                                                \
-          _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                      \
-            const int n = n_base + 8 * i;                                                      \
-            if (n < p.cout) {                                                                  \
-              float v[4] = {acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2],               \
-                            acc[g][4 * i + 3]};                                                \
-              if (res_here) {                                                                  \
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) v[j] += (float)res_pre[g][i][j]; \
-              }                                                                                \
-              store_quad<false>(p, m, n, v);                                                   \
-            }                                                                                  \
-          }                                                                                    \
-        }                                                                                      \
-      }                                                                                        \
-      if (wide_out)   /* every lane takes part in the exchange */                              \
-        store_octets(p, oy < p.hout && ox < p.wout, img * p.img_m + oy * p.wout + ox,          \
-                     n0 + wn * 32, h, acc[g], res_pre[g], res_here);                           \
-      acc[g] = zero16;                                                                         \
-    }                                                                                          \
-    if (has_proj) { /* projection output: no residual, no ReLU */                              \
-      const int ox = x0 + (r & 7);                                                             \
-      if (oy < p.hout && ox < p.wout) {                                                        \
-        const int m = img * p.img_m + oy * p.wout + ox;                                        \
-        if (p.use_partial) {                                                                   \
-          float* dst = p.partial2 + ((size_t)split * p.m + m) * p.cout_pad + n_base;           \
-          _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
-            *reinterpret_cast<float4*>(dst + 8 * i) = make_float4(                             \
-                acc2[4 * i], acc2[4 * i + 1], acc2[4 * i + 2], acc2[4 * i + 3]);               \
-        } else {                                                                               \
-          _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                      \
-            const int n = n_base + 8 * i;                                                      \
-            if (n < p.cout) {                                                                  \
-              half4 o;                                                                         \
-              _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = (f16)acc2[4 * i + j];       \
-              *reinterpret_cast<half4*>(p.out2 + (size_t)m * p.out2_pitch + n) = o;            \
-            }                                                                                  \
-          }                                                                                    \
-        }                                                                                      \
-      }                                                                                        \
-      acc2 = zero16;                                                                           \
-    }                                                                                          \
-  }
-
-  int buf = 0, pb = 0;
-  int cc = cc_begin;
-#pragma unroll
-  for (int i = 0; i < PL; ++i) HS_LOAD_P(i, cc, l_poff)
-  HS_LOAD_W(0, cc, 0) HS_LOAD_W(1, cc, 1) HS_LOAD_W(2, cc, 2)
-  if (WS == 9) {
-    HS_LOAD_W(3 % WS, cc, 3) HS_LOAD_W(4 % WS, cc, 4) HS_LOAD_W(5 % WS, cc, 5)
-    HS_LOAD_W(6 % WS, cc, 6) HS_LOAD_W(7 % WS, cc, 7) HS_LOAD_W(8 % WS, cc, 8)
-  }
-  if (STRIDE == 2) { HS_LOAD_W2(cc) }
-  // Items = (tile, chunk) pairs in order; `_n` state describes the item after the current one.
-  const int n_items = (tm_end - tm_begin) * (cc_end - cc_begin);
-  int tm = tm_begin;
-#pragma unroll
-  for (int i = 0; i < PL; ++i) l_poff_n[i] = l_poff[i];
-  img_n = img; y0_n = y0; x0_n = x0;
-  for (int item = 0; item + 1 < n_items; ++item) {
-    const bool cross = PERSIST && cc + 1 == cc_end;    // the next item starts a new tile
-    const int cc_nx = cross ? cc_begin : cc + 1;
-    if (cross) {
-      HS_TILE_SETUP(tm + 1, l_poff_n, img_n, y0_n, x0_n)
-      HS_RES_PREFETCH()
-    }
-    HS_CHUNK(false, cc_nx, l_poff_n)
-    if (PB == 2) pb ^= 1;
-    if (cross) {
-      HS_STORE_TILE()
-#pragma unroll
-      for (int i = 0; i < PL; ++i) l_poff[i] = l_poff_n[i];
-      img = img_n; y0 = y0_n; x0 = x0_n;
-      ++tm;
-    }
-    cc = cc_nx;
-  }
-  HS_RES_PREFETCH()
-  HS_CHUNK(true, cc, l_poff)
-  HS_STORE_TILE()
-#undef HS_RES_PREFETCH
-#undef HS_STORE_TILE
-#undef HS_CHUNK
-#undef HS_PROJ
-#undef HS_TAP
-#undef HS_TAP_OFF
-#undef HS_LOAD_P
-#undef HS_LOAD_W2
-#undef HS_LOAD_W
-#undef HS_TILE_SETUP
-}
 
 // =============================================================================================
 // 3x3 stride-1 layers with 64 input channels (one Cin chunk) on grids several times the device:
@@ -807,9 +494,7 @@ __global__ __launch_bounds__(256, OCC) void k_conv3x3_halo(ConvParams p) {
 // tiles, so they are made resident once -- taps 0..2 in LDS, taps 3..8 as MFMA fragments in
 // registers (all nine in LDS would leave one workgroup per CU, all nine in registers none of
 // the registers).  A tile then costs one patch hand-over (two barriers) and 72 MFMAs per
-// wavefront with no weight traffic and no barrier between the taps.  Same tile, wavefront
-// layout and accumulation order (tap-major, four K-steps of 16 per tap) as
-// k_conv3x3_halo<2, 1, 9, 1, true, *>: results are bit-identical.
+// wavefront with no weight traffic and no barrier between the taps.
 // =============================================================================================
 __global__ __launch_bounds__(256, 2) void k_conv3x3_c64_walk(ConvParams p) {
   constexpr int TH = 8, TW = 16, IPH = TH + 2, IPW = TW + 2, NPIX = IPH * IPW;
@@ -827,7 +512,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_c64_walk(ConvParams p) {
   const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
   const int groups_m = (p.tiles_m + p.tiles_per_wg - 1) / p.tiles_per_wg;
   if (tile >= groups_m * p.tiles_n) return;
-  const int blk = groups_m * p.n_block, in_blk = tile % blk;       // tile order: see k_conv3x3_halo
+  const int blk = groups_m * p.n_block, in_blk = tile % blk;       // tile order: see above
   const int tm_begin = (in_blk / p.n_block) * p.tiles_per_wg;
   const int tm_end = min(p.tiles_m, tm_begin + p.tiles_per_wg);
   const int n0 = ((tile / blk) * p.n_block + in_blk % p.n_block) * 64;
@@ -903,7 +588,6 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_c64_walk(ConvParams p) {
   }
 
   const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int n_base = n0 + wn * 32 + h * 4;
   for (int tm = tm_begin; tm < tm_end; ++tm) {
     const int img = f_img, y0 = f_y0, x0 = f_x0;
     if (tm != tm_begin) __syncthreads();      // every wavefront is done with the previous patch
@@ -974,7 +658,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_c64_walk(ConvParams p) {
 // Phase B is the tile loop body of k_conv3x3_c64_walk on that patch.  The 18 weight tiles
 // stream through nine register stages and a double-buffered LDS tile, one barrier per tap;
 // every output accumulates tap-major with four K-steps of 16 per tap, as in the unfused
-// kernels: results are bit-identical to two k_conv3x3_halo launches.
+// kernels: results are bit-identical to two launches of those.
 // p.wt / p.wt2: packed weights of conv_a / conv_b; p.res = p.in (the shortcut).
 // =============================================================================================
 __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
@@ -1129,13 +813,12 @@ __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
 }
 
 // =============================================================================================
-// 3x3 stride-1 pad-1 layers with several Cin chunks on grids of at least 1.5 workgroups per CU
-// (stages 2-4 and the ConvLSTM gates from a few frames per launch on).  Same 8 x 16 spatial
-// tile, wavefront layout and accumulation order as k_conv3x3_halo<2, ...> -- bit-identical
-// results -- but the weights never touch LDS: they are packed on the host in MFMA fragment
+// 3x3 stride-1 pad-1 layers with several Cin chunks on grids of more than one round of workgroups
+// (stages 2-4 and the ConvLSTM gates from a few frames per launch on).  8 x 16 spatial tile x 64
+// channels.  The weights never touch LDS: they are packed on the host in MFMA fragment
 // order (one 1 KB block of 64 lanes x 16 bytes per 32 channels, tap and K-step of 16) and every
 // wavefront loads its "A" fragments straight into registers, three taps ahead.  On those grids
-// the layers are paced by LDS throughput (a tap step of the LDS-staged kernel moves 48 KB of
+// the layers are paced by LDS throughput (a tap step with the weights staged in LDS moves 48 KB of
 // fragment reads and 10 KB of writes per workgroup; writes run at under half the rate of
 // reads): without the weight tile the LDS carries the pixel fragments only (32 KB of reads per
 // tap step), the per-tap barrier disappears (one barrier per Cin chunk, for the patch), and
@@ -1158,16 +841,13 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
   const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (tile >= p.tiles_m * p.tiles_n * p.nsplit) return;
-  const int within = tile % (p.tiles_m * p.tiles_n);              // tile order: see k_conv3x3_halo
-  const int blk = p.tiles_m * p.n_block, in_blk = within % blk;
+  if (tile >= p.tiles_m * p.tiles_n) return;
+  const int blk = p.tiles_m * p.n_block, in_blk = tile % blk;       // tile order: see above
   const int tm = in_blk / p.n_block;
-  const int tile_n = (within / blk) * p.n_block + in_blk % p.n_block;
-  const int split = tile / (p.tiles_m * p.tiles_n);
+  const int tile_n = (tile / blk) * p.n_block + in_blk % p.n_block;
   const int tiles_img = p.tiles_m / p.batch;
   const int n0 = tile_n * 64;
-  const int cc_begin = split * p.chunks_per_split;
-  const int cc_end = min(p.chunks_per_tap, cc_begin + p.chunks_per_split);
+  const int cc_end = p.chunks_per_tap;
   const int img = tm / tiles_img, ts = tm - img * tiles_img, ty = ts / p.tiles_x;
   const int y0 = ty * TH, x0 = (ts - ty * p.tiles_x) * TW;
   const int wm = wave & 1, wn = wave >> 1;
@@ -1194,8 +874,8 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
 
   // ---- weight fragments: this wavefront's 32 channels, one 1 KB block per (chunk, tap, K-step)
   const u32x4* wf = reinterpret_cast<const u32x4*>(p.wt_frag) +
-                    ((size_t)(n0 / 32 + wn) * p.chunks_per_tap + cc_begin) * (9 * 4 * 64) + lane;
-  const u32x4* const wf_last = wf + (size_t)((cc_end - cc_begin) * 9 - 1) * (4 * 64);
+                    (size_t)(n0 / 32 + wn) * p.chunks_per_tap * (9 * 4 * 64) + lane;
+  const u32x4* const wf_last = wf + (size_t)(cc_end * 9 - 1) * (4 * 64);
   u32x4 fa[3][4];
 #define HS_LOAD_A(S_)                                                                          \
   {                                                                                            \
@@ -1245,7 +925,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
   static_assert(BD == 3, "HS_CHUNK primes three K-steps");
 
   // ---- prologue: first patch into buffer 0, first three taps of weights into the stages
-  int cc = cc_begin, pb = 0;
+  int cc = 0, pb = 0;
   {
     u32x4 first[PL];
 #pragma unroll
@@ -1268,11 +948,9 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
     __syncthreads();      // the next patch is complete, and every wavefront is done with this one
     pb ^= 1;
   }
-  // residual of the block's second convolution: fetched while the last chunk is computed
-  // (with whole 64-channel tiles of fp16 output as two 16-byte pieces per pixel, see
-  // res_octets_to_quads; otherwise as the four quads the accumulators are laid out in)
+  // Residual of the block's second convolution: fetched while the last chunk is computed, as two
+  // 16-byte pieces per pixel (res_octets_to_quads)
   const bool res_here = p.res != nullptr && !p.use_partial;
-  const bool wide_out = !p.use_partial && p.out_f32 == nullptr && (p.cout & 63) == 0;
   half4 res_pre[2][4];
   u32x4 res_raw[2][2];
   if (res_here) {
@@ -1280,15 +958,9 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int ox_c = min(x0 + 8 * g + (r & 7), p.wout - 1);
-      const f16* rp = p.res + (size_t)(img * p.img_m + oy_c * p.wout + ox_c) * p.res_pitch;
-      if (wide_out) {
-        res_raw[g][0] = *reinterpret_cast<const u32x4*>(rp + n0 + wn * 32 + h * 8);
-        res_raw[g][1] = *reinterpret_cast<const u32x4*>(rp + n0 + wn * 32 + h * 8 + 16);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          res_pre[g][i] = *reinterpret_cast<const half4*>(rp + min(n_base + 8 * i, p.cout - 4));
-      }
+      const f16* rp = p.res + (size_t)(img * p.img_m + oy_c * p.wout + ox_c) * p.res_pitch + n0 + wn * 32 + h * 8;
+      res_raw[g][0] = *reinterpret_cast<const u32x4*>(rp);
+      res_raw[g][1] = *reinterpret_cast<const u32x4*>(rp + 16);
     }
   }
   HS_CHUNK(true)
@@ -1299,30 +971,15 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
     const int ox = x0 + 8 * g + (r & 7);
     const bool valid = oy < p.hout && ox < p.wout;
     const int m = img * p.img_m + oy * p.wout + ox;
-    if (wide_out) {                       // every lane takes part in the exchanges
+    if (!p.use_partial) {                 // every lane takes part in the exchanges
       if (res_here) res_octets_to_quads(res_raw[g], res_pre[g]);
       store_octets(p, valid, m, n0 + wn * 32, h, acc[g], res_pre[g], res_here);
     } else if (valid) {
-      if (p.use_partial) {
-        float* dst = p.partial + ((size_t)split * p.m + m) * p.cout_pad + n_base;
+      float* dst = p.partial + (size_t)m * p.cout_pad + n_base;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          *reinterpret_cast<float4*>(dst + 8 * i) =
-              make_float4(acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int n = n_base + 8 * i;
-          if (n < p.cout) {
-            float v[4] = {acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]};
-            if (res_here) {
-#pragma unroll
-              for (int j = 0; j < 4; ++j) v[j] += (float)res_pre[g][i][j];
-            }
-            store_quad<false>(p, m, n, v);
-          }
-        }
-      }
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(dst + 8 * i) =
+            make_float4(acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);
     }
   }
 #undef HS_CHUNK
@@ -1358,8 +1015,8 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
 //     first patch and weights are fetched during the last taps of the current tile), so the
 //     short K loops of the 64-channel layer do not pay a cold start per tile.
 // Per output the K order is chunk, half chunk, tap, K-step: within a chunk the two halves are
-// summed one after the other, not interleaved tap by tap as in k_conv3x3_halo<1, 1, 3, 2, ...>;
-// results agree with that kernel to fp32 rounding, not bit for bit.
+// summed one after the other, not interleaved tap by tap as in k_conv3x3_kw<2, ...>; results
+// agree with that kernel to fp32 rounding, not bit for bit.
 // =============================================================================================
 __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
   constexpr int TH = 8, TW = 8, IPW = 2 * TW + 1, NPIX = IPW * IPW;   // 17 x 17 input pixels
@@ -1371,18 +1028,14 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
   const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
   const int groups_m = (p.tiles_m + p.tiles_per_wg - 1) / p.tiles_per_wg;
-  if (tile >= groups_m * p.tiles_n * p.nsplit) return;
-  const int within = tile % (groups_m * p.tiles_n);               // tile order: see k_conv3x3_halo
-  const int blk = groups_m * p.n_block, in_blk = within % blk;
+  if (tile >= groups_m * p.tiles_n) return;
+  const int blk = groups_m * p.n_block, in_blk = tile % blk;       // tile order: see above
   const int tm_begin = (in_blk / p.n_block) * p.tiles_per_wg;
   const int tm_end = min(p.tiles_m, tm_begin + p.tiles_per_wg);
-  const int tile_n = (within / blk) * p.n_block + in_blk % p.n_block;
-  const int split = tile / (groups_m * p.tiles_n);
+  const int tile_n = (tile / blk) * p.n_block + in_blk % p.n_block;
   const int tiles_img = p.tiles_m / p.batch;
   const int n0 = tile_n * 128;
-  const int cc_begin = split * p.chunks_per_split;
-  const int cc_end = min(p.chunks_per_tap, cc_begin + p.chunks_per_split);
-  const int n_halves = 2 * (cc_end - cc_begin);                   // items per tile
+  const int n_halves = 2 * p.chunks_per_tap;                      // items per tile
   const int n_items = (tm_end - tm_begin) * n_halves;
   const bool has_proj = p.wt2_frag != nullptr;
 
@@ -1442,9 +1095,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
   const u32x4* const wp0 = has_proj ? reinterpret_cast<const u32x4*>(p.wt2_frag) +
                                           (size_t)(n0 / 32 + wave) * p.chunks_per_tap * (4 * 64) + lane
                                     : wf0;
-  // half chunk HF_ (0 .. n_halves - 1) of the K range: chunk cc_begin + HF_ / 2, K-steps 2 * (HF_ & 1) ..
-#define HS_WBASE(HF_) (wf0 + ((size_t)(cc_begin + ((HF_) >> 1)) * 36 + 2 * ((HF_) & 1)) * 64)
-#define HS_PBASE(HF_) (wp0 + ((size_t)(cc_begin + ((HF_) >> 1)) * 4 + 2 * ((HF_) & 1)) * 64)
+  // half chunk HF_ (0 .. n_halves - 1): chunk HF_ / 2, K-steps 2 * (HF_ & 1) ..
+#define HS_WBASE(HF_) (wf0 + ((size_t)((HF_) >> 1) * 36 + 2 * ((HF_) & 1)) * 64)
+#define HS_PBASE(HF_) (wp0 + ((size_t)((HF_) >> 1) * 4 + 2 * ((HF_) & 1)) * 64)
   u32x4 fa[3][2], fp2[2];
 #define HS_LOAD_A(S_, BASE_, T_)                                                               \
   {                                                                                            \
@@ -1498,10 +1151,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
   int pb = 0;
   {
     u32x4 first[PL];
-    const int ch0 = cc_begin * 64;
 #pragma unroll
     for (int i = 0; i < PL; ++i)
-      first[i] = *reinterpret_cast<const u32x4*>(p.in + (l_poff[i] >= 0 ? l_poff[i] + ch0 : 0));
+      first[i] = *reinterpret_cast<const u32x4*>(p.in + (l_poff[i] >= 0 ? l_poff[i] : 0));
     const u32x4* w0 = HS_WBASE(0);
     HS_LOAD_A(0, w0, 0) HS_LOAD_A(1, w0, 1) HS_LOAD_A(2, w0, 2)
 #pragma unroll
@@ -1513,7 +1165,6 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
   }
   __syncthreads();
 
-  const int n_base = n0 + wave * 32 + h * 4;
   int tm = tm_begin, hf = 0;
   for (int item = 0; item < n_items; ++item) {
     // the item after this one: next half chunk of the tile, or the first of the next tile
@@ -1522,7 +1173,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
     const int hf_n = more ? (cross ? 0 : hf + 1) : hf;
     const int s_img = img, s_y0 = y0, s_x0 = x0;      // this item's tile (for the store below)
     if (more && cross) HS_TILE_SETUP(tm + 1, img, y0, x0)   // l_poff now describes the next tile
-    const int ch_n = (cc_begin + (hf_n >> 1)) * 64 + (hf_n & 1) * 32;
+    const int ch_n = (hf_n >> 1) * 64 + (hf_n & 1) * 32;
     const u32x4* const w_cur = HS_WBASE(hf);
     const u32x4* const w_nxt = HS_WBASE(hf_n);
     if (has_proj) {
@@ -1535,36 +1186,18 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
     HS_KSTEP(7) HS_KSTEP(8) HS_KSTEP(9) HS_KSTEP(10) HS_KSTEP(11) HS_KSTEP(12) HS_KSTEP(13)
     HS_KSTEP(14) HS_KSTEP(15) HS_KSTEP(16) HS_KSTEP(17) HS_KSTEP(18) HS_KSTEP(19)
     if (cross) {
-      // ---- the tile is complete: accumulator quad i of group g = channels n_base + 8*i .. +3 of
-      // pixel (4*g + r/8, r%8) of the tile
+      // ---- the tile is complete: group g = pixel (4*g + r/8, r%8) of the tile
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
         const int oy = s_y0 + 4 * g + oy_l, ox = s_x0 + ox_l;
         const bool valid = oy < p.hout && ox < p.wout;
         const int m = s_img * p.img_m + oy * p.wout + ox;
-        if (p.use_partial) {
-          if (valid) {
-            float* dst = p.partial + ((size_t)split * p.m + m) * p.cout_pad + n_base;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              *reinterpret_cast<float4*>(dst + 8 * i) = make_float4(
-                  acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);
-            if (has_proj) {
-              float* dst2 = p.partial2 + ((size_t)split * p.m + m) * p.cout_pad + n_base;
-#pragma unroll
-              for (int i = 0; i < 4; ++i)
-                *reinterpret_cast<float4*>(dst2 + 8 * i) = make_float4(
-                    acc2[g][4 * i], acc2[g][4 * i + 1], acc2[g][4 * i + 2], acc2[g][4 * i + 3]);
-            }
-          }
-        } else {
-          // fp16 outputs with whole 128-channel tiles (the host selects this kernel only then)
-          const half4 none[4] = {};
-          store_octets(p, valid, m, n0 + wave * 32, h, acc[g], none, false);
-          if (has_proj)                            // projection: no residual, no ReLU
-            store_octets_to(p.out2, p.out2_pitch, false, valid, m, n0 + wave * 32, h, acc2[g], none,
-                            false);
-        }
+        // fp16 outputs with whole 128-channel tiles (the host selects this kernel only then)
+        const half4 none[4] = {};
+        store_octets(p, valid, m, n0 + wave * 32, h, acc[g], none, false);
+        if (has_proj)                            // projection: no residual, no ReLU
+          store_octets_to(p.out2, p.out2_pitch, false, valid, m, n0 + wave * 32, h, acc2[g], none,
+                          false);
       }
       acc[0] = acc[1] = zero16;
       acc2[0] = acc2[1] = zero16;
@@ -1585,27 +1218,292 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
 #undef HS_TILE_SETUP
 }
 
-constexpr int OCC3 = 2, OCC4 = 2;   // waves per SIMD the tile-walking instantiations are built for
+// =============================================================================================
+// 3x3 pad-1 layers (stride 1, and stride 2 with the block's 1x1 stride-2 projection riding along)
+// on SMALL grids: one or a few frames per launch.  There a layer is a launch, one memory round trip
+// and a K loop whose operands have to get into the few CUs at work; what bounds it is those
+// latencies and the 64 bytes per clock a CU takes in, not the matrix rate.  So the K splits live
+// in ONE workgroup (as workgroups of their own they need a second launch to add the partial
+// sums), the tile is small so that the grid covers the device, and every wavefront streams its
+// operands deep ahead without a barrier per tap:
+//   - wavefront (split, cg) computes 32 * PG pixels (PG groups of 4 x 8) x 32 channels over the Cin
+//     chunks of its split; its weight fragments come straight from memory (fragment order,
+//     p.wt_frag) through a ring of FR register sets, so up to FR KB per wavefront are in flight;
+//   - the CW wavefronts of a split (channel groups) share the input patch of the chunk in LDS;
+//     with CW == 1 the patch is the wavefront's own and the K loop has no barrier at all;
+//   - the partial tiles of the NS splits are added through LDS in split order.
+// Per output: chunk, tap, K-step within a split, then the splits in order.  With one split (the
+// larger of these grids) stride-1 results are bit-identical to k_conv3x3_dira's.
+// Stride 2: the patch is stored as four parity planes (pixel (py, px) in plane (py & 1, px & 1) at
+// (py / 2, px / 2)), so that a tap's lanes read neighbouring pixels, and the 1x1 stride-2 projection,
+// which reads exactly the centre tap's pixels, is a tenth tap with its own accumulators.
+// Ring depth FR, measured over maps of 5 x 9 to 60 x 107 pixels and 1 to 16 frames per launch: 12 for
+// PG == 1 (36 is 5 to 7 % slower: fewer workgroups per CU), 18 for PG == 2 (12: equal), 12 at stride 2
+// (18 spills: 10 to 30 % slower).
+// Against the kernels they replace (weights staged through LDS, K splits as workgroups of their own
+// and a launch to add them), 1080p frame: 256-channel layers 8.6 + 3.3 -> 7.2 us, 512-channel layers
+// 8.9 + 3.7 -> 7.5 us; of those 1.8 us are launch and set-up, 0.8 us the first operands' latency, 2 us the
+// weight stream (288 KB per CU), 1.7 us the sum over the splits and the store.
+// =============================================================================================
+// Touches this workgroup's share of the next layer's weights (one 4-byte load per 128-byte line),
+// so that they are on their way into the last-level cache when that layer starts: streamed from
+// HBM by the layer itself, every ring of fragments in flight costs a full memory latency.  Called
+// behind the K loop; the loads complete during the epilogue (the value is consumed at its end).
+__device__ __forceinline__ uint32_t prefetch_next(const ConvParams& p, int block, int n_blocks) {
+  uint32_t x = 0;
+  for (int i = block * (int)blockDim.x + (int)threadIdx.x; i < p.next_lines; i += n_blocks * (int)blockDim.x)
+    x ^= *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(p.next_wt) + (size_t)i * 128);
+  return x;
+}
+
+template <int STRIDE, int PG, int CW, int NW, int FR>
+__global__ __launch_bounds__(64 * NW, 2) void k_conv3x3_kw(ConvParams p) {
+  constexpr int NS = NW / CW;
+  constexpr int TH = 4 * PG, TW = 8;
+  constexpr int IPH = STRIDE * TH + 3 - STRIDE, IPW = STRIDE * TW + 3 - STRIDE, NPIX = IPH * IPW;
+  constexpr int PLH = STRIDE == 1 ? IPH : TH + 1, PLW = STRIDE == 1 ? IPW : TW + 1;
+  constexpr int PITCH = 64 + 8;
+  constexpr int RP = (PLW * PITCH * 2 + ((128 - (PLW * PITCH * 2) % 256 + 256) % 256)) / 2;
+  static_assert((RP * 2) % 256 == 128, "plane row pitch must be 128 mod 256 bytes");
+  constexpr int PATCH = STRIDE * STRIDE * PLH * RP;         // halves per split
+  constexpr int PV = NPIX * 8, PL = (PV + 64 * CW - 1) / (64 * CW);   // 16-byte vectors, per lane
+  constexpr int NG = STRIDE == 2 ? 2 * PG : PG;             // accumulator groups (projection: PG more)
+  constexpr int RED = 8 * 34;                               // float4s per group of partial sums
+  constexpr int BYTES = NS * PATCH * 2 > NW * NG * RED * 16 ? NS * PATCH * 2 : NW * NG * RED * 16;
+  static_assert(36 % FR == 0, "the fragment ring must divide a chunk's 36 K-steps");
+  __shared__ __align__(16) unsigned char s_raw[BYTES];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
+  const int split = wave / CW, cg = wave % CW;
+  const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
+  if (tile >= p.tiles_m * p.tiles_n) return;
+  const int blk = p.tiles_m * p.n_block, in_blk = tile % blk;     // tile order: see above
+  const int tm = in_blk / p.n_block;
+  const int n_tile = ((tile / blk) * p.n_block + in_blk % p.n_block) * (32 * CW);
+  const int tiles_img = p.tiles_m / p.batch;
+  const int img = tm / tiles_img, ts = tm - img * tiles_img, ty = ts / p.tiles_x;
+  const int y0 = ty * TH, x0 = (ts - ty * p.tiles_x) * TW;
+  const int n0 = n_tile + 32 * cg;                                // this wavefront's channels
+  const int cc_begin = split * p.chunks_per_split;
+  const int cc_end = min(p.chunks_per_tap, cc_begin + p.chunks_per_split);
+  const bool has_proj = STRIDE == 2 && p.wt2_frag != nullptr;
+
+  // ---- patch loader: the CW wavefronts of a split fetch its patch together
+  f16* const s_patch = reinterpret_cast<f16*>(s_raw) + split * PATCH;
+  int l_plds[PL], l_poff[PL];
+#pragma unroll
+  for (int i = 0; i < PL; ++i) {
+    const int vec = cg * 64 + lane + 64 * CW * i, pix = min(vec >> 3, NPIX - 1), v = vec & 7;
+    const int py = pix / IPW, px = pix - py * IPW;
+    l_plds[i] = vec >= PV ? -1
+                : STRIDE == 1 ? py * RP + px * PITCH + v * 8
+                              : (((py & 1) * 2 + (px & 1)) * PLH + (py >> 1)) * RP + (px >> 1) * PITCH + v * 8;
+    const int iy = STRIDE * y0 + py - 1, ix = STRIDE * x0 + px - 1;
+    const bool inb = vec < PV && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
+    l_poff[i] = inb ? ((img * p.hin + iy) * p.win + ix) * p.cin_pitch + v * 8 : -1;
+  }
+  u32x4 st_p[PL];
+#define HS_LOAD_PATCH(CC_)                                                                     \
+  _Pragma("unroll") for (int i = 0; i < PL; ++i)                                               \
+    st_p[i] = *reinterpret_cast<const u32x4*>(p.in + (l_poff[i] >= 0 ? l_poff[i] + (CC_) * 64 : 0));
+#define HS_SYNC_PATCH()                                                                        \
+  if (CW > 1) __syncthreads();                                                                 \
+  else {                                                                                       \
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                     \
+    __builtin_amdgcn_wave_barrier();                                                           \
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                     \
+  }
+#define HS_HAND_PATCH()                                                                        \
+  {                                                                                            \
+    const u32x4 zero_ = {0u, 0u, 0u, 0u};                                                      \
+    _Pragma("unroll") for (int i = 0; i < PL; ++i)                                             \
+      if (l_plds[i] >= 0)                                                                      \
+        *reinterpret_cast<u32x4*>(&s_patch[l_plds[i]]) = l_poff[i] >= 0 ? st_p[i] : zero_;     \
+    HS_SYNC_PATCH()                                                                            \
+  }
+
+  // ---- weight fragments of this wavefront: 36 blocks of 64 lanes x 16 bytes per chunk (tap-major,
+  // four K-steps per tap), four per chunk for the projection
+  const u32x4* wf = reinterpret_cast<const u32x4*>(p.wt_frag) +
+                    ((size_t)(n0 / 32) * p.chunks_per_tap + cc_begin) * (36 * 64) + lane;
+  const u32x4* wp = has_proj ? reinterpret_cast<const u32x4*>(p.wt2_frag) +
+                                   ((size_t)(n0 / 32) * p.chunks_per_tap + cc_begin) * (4 * 64) + lane
+                             : wf;
+  u32x4 fa[FR], fp2[4];
+
+  const int fp_off = (r >> 3) * RP + (r & 7) * PITCH + h * 8;
+  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  floatx16 acc[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) acc[g] = zero16;
+
+  // K-step Q_ (literal) of a chunk: tap Q_ / 4 (9: the projection, on the centre tap's pixels), K-step
+  // Q_ % 4.  Pixel fragments are read BD steps ahead through a ring.  LAST_: no chunk follows.
+  constexpr int BD = 3, QN = STRIDE == 2 ? 40 : 36;
+  half8 bf[BD + 1][PG];
+#define HS_TAPQ(Q_) ((Q_) / 4 == 9 ? 4 : (Q_) / 4)
+#define HS_READ_B(Q_)                                                                          \
+  {                                                                                            \
+    const int ky_ = HS_TAPQ(Q_) / 3, kx_ = HS_TAPQ(Q_) % 3;                                    \
+    const int toff_ = STRIDE == 1 ? ky_ * RP + kx_ * PITCH                                     \
+                                  : (((ky_ & 1) * 2 + (kx_ & 1)) * PLH + (ky_ >> 1)) * RP + (kx_ >> 1) * PITCH; \
+    _Pragma("unroll") for (int g = 0; g < PG; ++g)                                             \
+      bf[(Q_) % (BD + 1)][g] = *reinterpret_cast<const half8*>(                                \
+          &s_patch[fp_off + toff_ + 4 * g * RP + ((Q_) % 4) * 16]);                            \
+  }
+#define HS_CHUNK(LAST_)                                                                        \
+  {                                                                                            \
+    HS_READ_B(0) HS_READ_B(1) HS_READ_B(2)                                                     \
+    _Pragma("unroll") for (int q = 0; q < 36; ++q) {                                           \
+      if (q + BD < QN) HS_READ_B(q + BD)                                                       \
+      const half8 a_ = __builtin_bit_cast(half8, fa[q % FR]);                                  \
+      _Pragma("unroll") for (int g = 0; g < PG; ++g)                                           \
+        acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_, bf[q % (BD + 1)][g], acc[g], 0, 0, 0); \
+      if (!(LAST_) || q + FR < 36) fa[q % FR] = wf[(q + FR) * 64];                             \
+      __builtin_amdgcn_sched_barrier(0);                                                       \
+    }                                                                                          \
+    wf += 36 * 64;                                                                             \
+    if (STRIDE == 2 && has_proj) {                                                             \
+      wp += 4 * 64;                                                                            \
+      _Pragma("unroll") for (int q = 36; q < 40; ++q) {                                        \
+        if (q + BD < QN) HS_READ_B(q + BD)                                                     \
+        const half8 a_ = __builtin_bit_cast(half8, fp2[q % 4]);                                \
+        _Pragma("unroll") for (int g = 0; g < PG; ++g)                                         \
+          acc[NG - PG + g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(                           \
+              a_, bf[q % (BD + 1)][g], acc[NG - PG + g], 0, 0, 0);                             \
+        if (!(LAST_)) fp2[q % 4] = wp[(q % 4) * 64];                                           \
+      }                                                                                        \
+    }                                                                                          \
+  }
+
+  HS_LOAD_PATCH(cc_begin)
+#pragma unroll
+  for (int q = 0; q < FR; ++q) fa[q] = wf[q * 64];
+  if (STRIDE == 2) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) fp2[q] = wp[q * 64];
+  }
+  // the residual of the outputs this thread will finish: channel quad t % (8 * CW) of pixel t / (8 * CW)
+  constexpr int ITEMS = PG * 256 * CW / (64 * NW) + (PG * 256 * CW % (64 * NW) != 0 ? 1 : 0);
+  half4 res[ITEMS];
+  int o_m[ITEMS];                    // output pixel, -1: outside the image or no such item
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int t = tid + 64 * NW * k, px = t / (8 * CW);
+    const int oy = y0 + (px >> 3), ox = x0 + (px & 7);
+    o_m[k] = px < 32 * PG && oy < p.hout && ox < p.wout ? img * p.img_m + oy * p.wout + ox : -1;
+    if (p.res)
+      res[k] = *reinterpret_cast<const half4*>(p.res + (size_t)max(o_m[k], 0) * p.res_pitch + n_tile +
+                                               (t % (8 * CW)) * 4);
+  }
+  HS_HAND_PATCH()
+  // every wavefront goes through chunks_per_split rounds (the barriers are for all of them); the
+  // last split may own fewer chunks
+  int cc = cc_begin;
+  for (int it = 1; it < p.chunks_per_split; ++it) {
+    if (cc + 1 < cc_end) {
+      HS_LOAD_PATCH(cc + 1)
+      HS_CHUNK(false)
+    } else if (cc < cc_end) {
+      HS_CHUNK(true)
+    }
+    if (CW > 1) __syncthreads();     // all readers of the patch are done
+    HS_HAND_PATCH()
+    ++cc;
+  }
+  if (cc < cc_end) HS_CHUNK(true)
+#undef HS_CHUNK
+#undef HS_READ_B
+#undef HS_TAPQ
+#undef HS_HAND_PATCH
+#undef HS_SYNC_PATCH
+#undef HS_LOAD_PATCH
+
+  // ---- add the partial tiles: accumulator quad i of group g of lane (r, h) = channels 8 * i + 4 * h ..
+  // +3 (quad 2 * i + h) of pixel 32 * g + r.  34 float4s per quad row: reads and writes conflict free
+  float4* const s_red = reinterpret_cast<float4*>(s_raw);
+  const uint32_t touched = prefetch_next(p, tile, p.tiles_m * p.tiles_n);
+  __syncthreads();                   // every wavefront is done with its patch
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      s_red[(wave * NG + g) * RED + (2 * i + h) * 34 + r] =
+          make_float4(acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (o_m[k] < 0) continue;
+    const int t = tid + 64 * NW * k, px = t / (8 * CW), c4 = t % (8 * CW), n = n_tile + 4 * c4;
+    const float4* src = s_red + ((c4 >> 3) * NG + (px >> 5)) * RED + (c4 & 7) * 34 + (px & 31);
+    float4 a = src[0];
+#pragma unroll
+    for (int w = 1; w < NS; ++w) {
+      const float4 b = src[w * CW * NG * RED];
+      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    if (p.use_partial) {
+      *reinterpret_cast<float4*>(p.partial + (size_t)o_m[k] * p.cout_pad + n) = a;
+    } else {
+      float v[4] = {a.x, a.y, a.z, a.w};
+      half4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (p.res) v[j] += (float)res[k][j];
+        if (p.relu) v[j] = fmaxf(v[j], 0.0f);
+        o[j] = (f16)v[j];
+      }
+      *reinterpret_cast<half4*>(p.out + (size_t)o_m[k] * p.out_pitch + n) = o;
+    }
+    if (has_proj) {                  // projection output: no residual, no ReLU
+      const float4* src2 = src + PG * RED;
+      float4 b = src2[0];
+#pragma unroll
+      for (int w = 1; w < NS; ++w) {
+        const float4 d = src2[w * CW * NG * RED];
+        b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
+      }
+      half4 o2;
+      o2[0] = (f16)b.x; o2[1] = (f16)b.y; o2[2] = (f16)b.z; o2[3] = (f16)b.w;
+      *reinterpret_cast<half4*>(p.out2 + (size_t)o_m[k] * p.out2_pitch + n) = o2;
+    }
+  }
+  asm volatile("" ::"v"(touched));
+}
+
+// The instantiations the host's rules ask for (see Builder::plan_kw).
+static const void* kw_kernel_of(const ConvParams& p) {
+  const int key = p.stride * 1000 + p.kw_groups * 100 + p.kw_cgroups * 10 + p.kw_splits;
+  switch (key) {
+    case 1141: return (const void*)k_conv3x3_kw<1, 1, 4, 4, 12>;
+    case 1121: return (const void*)k_conv3x3_kw<1, 1, 2, 2, 12>;
+    case 1122: return (const void*)k_conv3x3_kw<1, 1, 2, 4, 12>;
+    case 1112: return (const void*)k_conv3x3_kw<1, 1, 1, 2, 12>;
+    case 1113: return (const void*)k_conv3x3_kw<1, 1, 1, 3, 12>;
+    case 1114: return (const void*)k_conv3x3_kw<1, 1, 1, 4, 12>;
+    case 1116: return (const void*)k_conv3x3_kw<1, 1, 1, 6, 12>;
+    case 1241: return (const void*)k_conv3x3_kw<1, 2, 4, 4, 18>;
+    case 1222: return (const void*)k_conv3x3_kw<1, 2, 2, 4, 18>;
+    case 2141: return (const void*)k_conv3x3_kw<2, 1, 4, 4, 12>;
+    case 2121: return (const void*)k_conv3x3_kw<2, 1, 2, 2, 12>;
+    case 2122: return (const void*)k_conv3x3_kw<2, 1, 2, 4, 12>;
+    case 2114: return (const void*)k_conv3x3_kw<2, 1, 1, 4, 12>;
+    default: return nullptr;
+  }
+}
+
 KernelDesc describe(const ConvParams& p) {
   // 1-D grid, padded to a multiple of 8 so that every XCD owns tiles_per_xcd consecutive tiles
   const dim3 grid(8u * (unsigned)p.tiles_per_xcd);
-  const bool walk = p.tiles_per_wg > 1;
-  if (p.variant == 5) return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
-  if (p.variant == 6) return KernelDesc{(const void*)k_conv3x3_dira, grid, dim3(256), 0};
-  if (p.variant == 7) return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
-  if (p.variant == 1) return KernelDesc{(const void*)k_conv3x3_halo<1, 2, 9, 1, false, 1>, grid, dim3(256), 0};
-  if (p.variant == 2) return KernelDesc{(const void*)k_conv3x3_halo<2, 2, 9, 1, false, 1>, grid, dim3(256), 0};
-  if (p.variant == 3 && walk && p.chunks_per_tap == 1 && !p.use_partial && p.nsplit == 1 &&
-      !p.out_f32 && p.cout % 64 == 0)
-    return KernelDesc{(const void*)k_conv3x3_c64_walk, grid, dim3(256), 0};
-  if (p.variant == 3 && walk && p.chunks_per_tap == 1)
-    return KernelDesc{(const void*)k_conv3x3_halo<2, 1, 9, 1, true, OCC3>, grid, dim3(256), 0};
-  if (p.variant == 3)
-    return KernelDesc{walk ? (const void*)k_conv3x3_halo<2, 1, 3, 1, true, OCC3>
-                           : (const void*)k_conv3x3_halo<2, 1, 3, 1, false, 1>, grid, dim3(256), 0};
-  if (p.variant == 4)
-    return KernelDesc{walk ? (const void*)k_conv3x3_halo<1, 1, 3, 2, true, OCC4>
-                           : (const void*)k_conv3x3_halo<1, 1, 3, 2, false, 1>, grid, dim3(256), 0};
+  switch (p.variant) {
+    case CONV_C64_WALK: return KernelDesc{(const void*)k_conv3x3_c64_walk, grid, dim3(256), 0};
+    case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
+    case CONV_DIRA: return KernelDesc{(const void*)k_conv3x3_dira, grid, dim3(256), 0};
+    case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
+    case CONV_KW:
+      return KernelDesc{kw_kernel_of(p), grid, dim3(64u * (unsigned)(p.kw_splits * p.kw_cgroups)), 0};
+    default: break;
+  }
   const void* f = p.kc == 16   ? (const void*)k_conv_mfma<16, 4>
                   : p.kc == 32 ? (const void*)k_conv_mfma<32, 4>
                   : p.depth == 8 ? (const void*)k_conv_mfma<64, 8>
@@ -1646,17 +1544,6 @@ __global__ __launch_bounds__(256) void k_splitk_epilogue(SplitKEpilogueParams p)
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[j] = (f16)v[j];
     *reinterpret_cast<half4*>(p.out + (size_t)m * p.out_pitch + n) = o;
-  }
-  if (p.partial2) {
-    float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int sidx = 0; sidx < p.nsplit; ++sidx) {
-      const float4 v2 = *reinterpret_cast<const float4*>(
-          p.partial2 + ((size_t)sidx * p.m + m) * p.cout_pad + n);
-      b.x += v2.x; b.y += v2.y; b.z += v2.z; b.w += v2.w;
-    }
-    half4 o2;
-    o2[0] = (f16)b.x; o2[1] = (f16)b.y; o2[2] = (f16)b.z; o2[3] = (f16)b.w;
-    *reinterpret_cast<half4*>(p.out2 + (size_t)m * p.out2_pitch + n) = o2;
   }
 }
 

@@ -10,6 +10,7 @@
 #include <cmath>
 #include <condition_variable>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -241,41 +242,59 @@ struct hs_group {
 namespace hs {
 
 // ---- weight packing ----------------------------------------------------------------------------
-// Generic layer: packed[n][(ky*k + kx)*cin + c] = w[n][c][ky][kx]; rows cout..cout_pad-1 zero.
-static void pack_generic(const float* w, int cout, int cin, int k, int cout_pad, f16* dst) {
-  const size_t ktot = (size_t)k * k * cin;
-  std::memset(dst, 0, (size_t)cout_pad * ktot * sizeof(f16));
-  for (int n = 0; n < cout; ++n)
-    for (int c = 0; c < cin; ++c)
-      for (int ky = 0; ky < k; ++ky)
-        for (int kx = 0; kx < k; ++kx)
-          dst[(size_t)n * ktot + (size_t)(ky * k + kx) * cin + c] =
-              (f16)w[(((size_t)n * cin + c) * k + ky) * k + kx];
+// The blob is converted to fp16 once, then every layer is rearranged by tasks of 32 output channels
+// that run on a few host threads (create time: 18 M weights; converting and scattering them one by
+// one took 130 ms).
+#if !defined(__HIP_DEVICE_COMPILE__) && (defined(__x86_64__) || defined(__i386__))
+__attribute__((target("f16c"))) static void to_half_f16c(const float* src, f16* dst, size_t n) {
+  for (size_t i = 0; i < n; ++i) dst[i] = (f16)src[i];
+}
+static bool has_f16c() { return __builtin_cpu_supports("f16c"); }
+#else
+static void to_half_f16c(const float*, f16*, size_t) {}
+static bool has_f16c() { return false; }
+#endif
+static void to_half(const float* src, f16* dst, size_t n) {
+  if (has_f16c()) return to_half_f16c(src, dst, n);
+  for (size_t i = 0; i < n; ++i) dst[i] = (f16)src[i];
 }
 
-// The same layer in MFMA fragment order for the kernel that reads its weight operand straight
-// from memory (3x3, cin % 64 == 0): dst[(((g*chunks + cc)*9 + tap)*4 + ks)*64 + lane][j] =
-// w[32*g + r][64*cc + 16*ks + 8*h + j][tap], lane = r + 32*h; channels above cout are zero.
-// ntaps = 9 (3x3) or 1 (the 1x1 projection fused into a stride-2 layer).
-static void pack_frag(const float* w, int cout, int cin, int ntaps, int cout_pad, f16* dst) {
+// Generic layer: packed[n][(ky*k + kx)*cin + c] = w[n][c][ky][kx] for rows n0 .. n1-1 (rows from cout on
+// are zero); taps = k * k.
+static void pack_generic(const f16* w, int cout, int cin, int taps, int n0, int n1, f16* dst) {
+  const size_t ktot = (size_t)taps * cin;
+  for (int n = n0; n < n1; ++n) {
+    f16* row = dst + (size_t)n * ktot;
+    if (n >= cout) { std::memset((void*)row, 0, ktot * sizeof(f16)); continue; }
+    const f16* src = w + (size_t)n * ktot;
+    for (int t = 0; t < taps; ++t)
+      for (int c = 0; c < cin; ++c) row[(size_t)t * cin + c] = src[(size_t)c * taps + t];
+  }
+}
+
+// The same layer in MFMA fragment order for the kernels that read their weight operand straight
+// from memory (3x3, cin % 64 == 0), channel group g = rows 32*g .. +31: dst[(((g*chunks + cc)*taps +
+// tap)*4 + ks)*64 + lane][j] = w[32*g + r][64*cc + 16*ks + 8*h + j][tap], lane = r + 32*h; channels above
+// cout are zero.  taps = 9 (3x3) or 1 (the 1x1 projection fused into a stride-2 layer).
+static void pack_frag(const f16* w, int cout, int cin, int taps, int g, f16* dst) {
   const int chunks = cin / 64;
-  std::memset(dst, 0, (size_t)cout_pad * ntaps * cin * sizeof(f16));
-  for (int n = 0; n < cout; ++n) {
-    const int g = n / 32, r = n % 32;
-    for (int c = 0; c < cin; ++c) {
-      const int cc = c / 64, ks = (c % 64) / 16, h = (c % 16) / 8, j = c % 8;
-      for (int tap = 0; tap < ntaps; ++tap) {
-        const size_t block = (((size_t)g * chunks + cc) * ntaps + tap) * 4 + ks;
-        dst[(block * 64 + (size_t)(r + 32 * h)) * 8 + j] =
-            (f16)w[((size_t)n * cin + c) * ntaps + tap];
+  f16* out = dst + (size_t)g * chunks * taps * 4 * 512;
+  for (int cc = 0; cc < chunks; ++cc)
+    for (int r = 0; r < 32; ++r) {
+      const int n = 32 * g + r;
+      for (int oct = 0; oct < 8; ++oct) {               // channels 64*cc + 8*oct .. +7: ks = oct / 2, h = oct % 2
+        const f16* src = w + ((size_t)std::min(n, cout - 1) * cin + 64 * cc + 8 * oct) * taps;
+        for (int tap = 0; tap < taps; ++tap) {
+          f16* o = out + (((size_t)cc * taps + tap) * 4 + oct / 2) * 512 + (size_t)(r + 32 * (oct % 2)) * 8;
+          for (int j = 0; j < 8; ++j) o[j] = n < cout ? src[(size_t)j * taps + tap] : (f16)0.0f;
+        }
       }
     }
-  }
 }
 
 // First layer on the padded 4-channel image: one chunk per kernel row, covering chunk_px
 // adjacent pixels of 4 channels; packed[n][ky][px][ch] = w[n][ch][ky][px] (px < k, ch < 3).
-static void pack_rowtap(const float* w, int cout, int k, int chunk_px, int cout_pad, f16* dst) {
+static void pack_rowtap(const f16* w, int cout, int k, int chunk_px, int cout_pad, f16* dst) {
   const size_t ktot = (size_t)k * chunk_px * 4;
   std::memset(dst, 0, (size_t)cout_pad * ktot * sizeof(f16));
   for (int n = 0; n < cout; ++n)
@@ -283,13 +302,13 @@ static void pack_rowtap(const float* w, int cout, int k, int chunk_px, int cout_
       for (int ky = 0; ky < k; ++ky)
         for (int px = 0; px < k; ++px)
           dst[(size_t)n * ktot + ((size_t)ky * chunk_px + px) * 4 + ch] =
-              (f16)w[(((size_t)n * 3 + ch) * k + ky) * k + px];
+              w[(((size_t)n * 3 + ch) * k + ky) * k + px];
 }
 
 // The 7x7 stem's weights in MFMA fragment order for k_stem_pool: block ((wn * 7 + ky) * 2 + s) of
 // 64 lanes x 8 halves; lane (h, r) holds channel 32 * wn + r, k = ky * 32 + s * 16 + h * 8 .. + 7 of
 // the row-tap layout (k = (ky * 8 + px) * 4 + ch, zero where px == 7 or ch == 3).
-static void pack_stem_frag(const float* w, f16* dst) {
+static void pack_stem_frag(const f16* w, f16* dst) {
   std::vector<f16> rows((size_t)64 * 224);
   pack_rowtap(w, 64, 7, 8, 64, rows.data());
   for (int wn = 0; wn < 2; ++wn)
@@ -316,6 +335,8 @@ struct Builder {
   bool pack;                      // pack weights on the host (create only)
   bool carve_acts;                // hand out activation storage (second walk)
   std::vector<f16> host_w;        // packed weights staged on the host
+  std::vector<f16> half_blob;     // the blob in fp16 (pack only)
+  std::vector<std::function<void()>> pack_tasks;   // run by run_pack() once host_w has its size
   f16* d_w = nullptr;             // device weights base
   size_t w_halves = 0;            // packed weights consumed so far
   const float* blob;
@@ -341,74 +362,153 @@ struct Builder {
   size_t reserve_w(size_t n) {
     const size_t off = w_halves;
     w_halves = round_up_sz(off + n, 128);
-    if (pack) host_w.resize(w_halves);
     return off;
+  }
+
+  // Packing tasks of a layer whose weights start at blob offset `at`, into region `off`.
+  void pack_generic_at(size_t at, int cout, int cin, int taps, int cout_pad, size_t off) {
+    if (!pack) return;
+    for (int n = 0; n < cout_pad; n += 32)
+      pack_tasks.push_back([=] {
+        pack_generic(half_blob.data() + at, cout, cin, taps, n, std::min(n + 32, cout_pad), host_w.data() + off);
+      });
+  }
+  void pack_frag_at(size_t at, int cout, int cin, int taps, int cout_pad, size_t off) {
+    if (!pack) return;
+    for (int g = 0; g < cout_pad / 32; ++g)
+      pack_tasks.push_back([=] { pack_frag(half_blob.data() + at, cout, cin, taps, g, host_w.data() + off); });
+  }
+  // Converts the blob and runs the packing tasks, on up to eight host threads.
+  void run_pack() {
+    host_w.assign(w_halves, (f16)0.0f);
+    half_blob.resize(d.weight_floats);
+    std::vector<std::function<void()>> convert;
+    constexpr size_t kPiece = (size_t)1 << 20;
+    for (size_t i = 0; i < d.weight_floats; i += kPiece)
+      convert.push_back([=] { to_half(blob + i, half_blob.data() + i, std::min(kPiece, d.weight_floats - i)); });
+    run_tasks(convert);
+    run_tasks(pack_tasks);
+    pack_tasks.clear();
+    half_blob = std::vector<f16>();
+  }
+  static void run_tasks(const std::vector<std::function<void()>>& tasks) {
+    std::atomic<size_t> next{0};
+    auto work = [&] {
+      for (size_t i = next++; i < tasks.size(); i = next++) tasks[i]();
+    };
+    // (a thread costs about as much as one task: few tasks run on the caller's)
+    const size_t n = tasks.size() < 16 ? 1 : std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency()));
+    std::vector<std::thread> threads;
+    struct Join {
+      std::vector<std::thread>& t;
+      ~Join() { for (std::thread& x : t) x.join(); }
+    } join{threads};
+    for (size_t i = 1; i < n; ++i) threads.emplace_back(work);
+    work();
+  }
+
+  // CONV_KW with ns K splits, cw channel groups and pg pixel groups per workgroup.
+  static void plan_kw(ConvParams& c, int ns, int cw, int pg) {
+    c.variant = CONV_KW;
+    c.kw_splits = ns; c.kw_cgroups = cw; c.kw_groups = pg;
+    c.tiles_x = (c.wout + 7) / 8;
+    c.tiles_m = c.batch * ((c.hout + 4 * pg - 1) / (4 * pg)) * c.tiles_x;
+    c.tiles_n = c.cout / (32 * cw);
+    c.chunks_per_split = (c.chunks_per_tap + ns - 1) / ns;
   }
 
   // Picks the kernel variant, the tile grid and the split along K.
   static void choose_split(ConvParams& c) {
     // the shared-patch kernels address the input with 32-bit offsets (in halves)
     const bool fits32 = (double)c.batch * c.hin * c.win * c.cin_pitch < 2147483648.0;
-    const bool halo = c.ntaps == 9 && c.kw == 3 && c.stride == 1 && c.pad == 1 && c.kc == 64 && fits32;
-    const bool halo2 = c.ntaps == 9 && c.kw == 3 && c.stride == 2 && c.pad == 1 && c.kc == 64 && fits32;
-    if (halo2) {
-      c.variant = 4;
-      c.tiles_x = (c.wout + 7) / 8;
-      c.tiles_m = c.batch * ((c.hout + 7) / 8) * c.tiles_x;
-      c.tiles_n = c.cout_pad / 64;
-      const int tiles = c.tiles_m * c.tiles_n;
-      // from 1.5 workgroups per CU on: weights as fragments from memory, half-chunk patches
-      // (channel tiles of 128 there: the patch, the heavy operand at stride 2, serves them all)
-      if (tiles >= 768 && c.frag_ok && c.cout % 128 == 0) {
-        c.variant = 7;
-        c.tiles_n = c.cout_pad / 128;
+    const bool s3x3 = c.ntaps == 9 && c.kw == 3 && c.pad == 1 && c.kc == 64 && c.cout % 128 == 0 && fits32;
+    c.nsplit = 1;
+    c.tiles_per_wg = 1;
+    c.depth = 4;
+    // workgroups of a CONV_KW grid
+    auto wgs = [&](int cw, int pg) {
+      return c.batch * ((c.hout + 4 * pg - 1) / (4 * pg)) * ((c.wout + 7) / 8) * (c.cout / (32 * cw));
+    };
+    auto tiles = [&](int tw) {          // tiles of 8 rows x tw columns x 64 channels
+      return c.batch * ((c.hout + 7) / 8) * ((c.wout + tw - 1) / tw) * (c.cout / 64);
+    };
+    // K splits: the count is part of the result (fp32 sums are not associative), so it depends on
+    // the shape alone and not on the kernel: as many as bring 256 tiles of 8 x 8 pixels x 64 channels,
+    // in whole chunks (stride 1: at least two per split)
+    auto k_splits = [&](int n_tiles, int most) {
+      const int ns = n_tiles >= 192 ? 1 : std::max(1, std::min((256 + n_tiles - 1) / n_tiles, most));
+      const int per = (c.chunks_per_tap + ns - 1) / ns;
+      return (c.chunks_per_tap + per - 1) / per;
+    };
+    constexpr int kRound = 256;         // one workgroup per CU
+    if (s3x3 && c.stride == 2) {
+      if (tiles(8) >= 768) {
+        // from 1.5 workgroups of 8 x 8 x 128 per CU on: the patch, the heavy operand at stride 2, serves
+        // 128 channels.  Two workgroups per CU are resident: beyond two rounds, walk in one.  (The
+        // line also marks a change of the K order, and so of the results' last bits.)
+        c.variant = CONV_S2_DIRA;
+        c.tiles_x = (c.wout + 7) / 8;
+        c.tiles_m = c.batch * ((c.hout + 7) / 8) * c.tiles_x;
+        c.tiles_n = c.cout / 128;
+        const int n = c.tiles_m * c.tiles_n;
+        if (n > 1024) c.tiles_per_wg = (n + 511) / 512;
+      } else {
+        // one split: two channel groups per workgroup while that is one round, else four (the patch
+        // serves twice the channels)
+        const int ns = k_splits(tiles(8), c.chunks_per_tap);
+        plan_kw(c, ns, ns == 1 ? (wgs(2, 1) <= kRound ? 2 : 4) : ns == 2 ? 2 : 1, 1);
       }
-      const int units = c.chunks_per_tap;
-      int ns = 1;
-      if (tiles < 192) ns = std::max(1, std::min((256 + tiles - 1) / tiles, units));
-      c.chunks_per_split = (units + ns - 1) / ns;
-      c.nsplit = (units + c.chunks_per_split - 1) / c.chunks_per_split;
-    } else if (halo) {
-      // spatial tiles of 8 x 16 pixels when that still yields enough workgroups, else 8 x 8;
-      // grids of more than two workgroups per CU take the leaner 8 x 16 kernel (three per CU)
-      const int ty = (c.hout + 7) / 8;
-      const int wide = c.batch * ty * ((c.wout + 15) / 16) * (c.cout_pad / 64);
-      c.variant = wide > 512 ? 3 : wide >= 192 ? 2 : 1;
-      // from 1.5 workgroups per CU on, layers with several Cin chunks are paced by LDS
-      // throughput: the variant that keeps the weights out of LDS takes them
-      if (wide >= 384 && c.chunks_per_tap >= 2) c.variant = 6;
-      const int tw = c.variant == 1 ? 8 : 16;
-      c.tiles_x = (c.wout + tw - 1) / tw;
-      c.tiles_m = c.batch * ty * c.tiles_x;
-      c.tiles_n = c.cout_pad / 64;
-      const int tiles = c.tiles_m * c.tiles_n;
-      const int units = c.chunks_per_tap;        // split over Cin chunks
-      int ns = 1;
-      if (tiles < 192) ns = std::max(1, std::min((256 + tiles - 1) / tiles, units / 2));
-      c.chunks_per_split = (units + ns - 1) / ns;
-      c.nsplit = (units + c.chunks_per_split - 1) / c.chunks_per_split;
+    } else if (s3x3 && c.stride == 1 && c.chunks_per_tap >= 2) {
+      const int wide = tiles(16);
+      const int ns = k_splits(wide < 192 ? tiles(8) : wide, c.chunks_per_tap / 2);
+      // Measured over maps of 5 x 9 to 60 x 107 pixels and 1 to 16 frames per launch: the smallest
+      // workgroup whose grid is one round wins (a round costs what its workgroup costs, and a
+      // workgroup's time is its weight stream: 128 channels x 32 pixels take 0.62 to 0.9 of the time of
+      // 128 x 64); beyond one round the 64-pixel tiles, which feed two MFMAs per weight fragment.
+      // Two wavefronts per workgroup only in one round: a second such workgroup on a CU shares
+      // the first one's SIMDs.
+      if (ns == 1) {
+        auto rounds = [](int n) { return (n + kRound - 1) / kRound; };
+        const int big = wgs(4, 2);
+        if (wgs(2, 1) <= kRound) plan_kw(c, 1, 2, 1);
+        else if (wgs(4, 1) <= kRound) plan_kw(c, 1, 4, 1);
+        else if (5 * rounds(wgs(4, 1)) < 7 * std::min(rounds(big), rounds(wide)) && c.chunks_per_tap >= 8)
+          plan_kw(c, 1, 4, 1);
+        else if (rounds(big) < rounds(wide) || (rounds(big) == rounds(wide) && (big < wide || rounds(big) == 1)))
+          plan_kw(c, 1, 4, 2);
+        else {
+          // 8 x 16-pixel tiles, where they waste no more pixels on the map's edges
+          c.variant = CONV_DIRA;
+          c.tiles_x = (c.wout + 15) / 16;
+          c.tiles_m = c.batch * ((c.hout + 7) / 8) * c.tiles_x;
+          c.tiles_n = c.cout / 64;
+        }
+      } else if (ns == 2) {
+        if (wgs(1, 1) <= kRound) plan_kw(c, 2, 1, 1);
+        else plan_kw(c, 2, 2, wgs(2, 1) <= kRound ? 1 : 2);
+      } else {
+        plan_kw(c, ns, 1, 1);
+      }
+    } else if (c.ntaps == 9 && c.kw == 3 && c.stride == 1 && c.pad == 1 && c.kc == 64 && c.cout == 64 &&
+               c.chunks_per_tap == 1 && fits32 && tiles(16) > 1536) {
+      // several times what the device holds at once: each workgroup walks consecutive tiles, so that
+      // the whole grid is resident at two per CU (smaller grids run the block in one launch)
+      c.variant = CONV_C64_WALK;
+      c.tiles_x = (c.wout + 15) / 16;
+      c.tiles_m = tiles(16);
+      c.tiles_n = 1;
+      c.tiles_per_wg = (c.tiles_m + 511) / 512;
     } else {
-      c.variant = 0;
+      c.variant = CONV_GENERIC;
       c.tiles_x = 0;
       c.tiles_m = (c.m + 63) / 64;
       c.tiles_n = c.cout_pad / 64;
-      const int tiles = c.tiles_m * c.tiles_n;
+      const int n = c.tiles_m * c.tiles_n;
       int ns = 1;
-      if (tiles < 192) ns = std::max(1, std::min((320 + tiles - 1) / tiles, c.nchunks / 4));
+      if (n < 192) ns = std::max(1, std::min((320 + n - 1) / n, c.nchunks / 4));
       c.chunks_per_split = (c.nchunks + ns - 1) / ns;
       c.nsplit = (c.nchunks + c.chunks_per_split - 1) / c.chunks_per_split;
-    }
-    c.depth = (c.kc == 64 && c.chunks_per_split >= 12) ? 8 : 4;
-    // grids several times what the device holds at once (768 workgroups): each workgroup walks
-    // consecutive spatial tiles, sized so that the whole grid is resident at two per CU
-    c.tiles_per_wg = 1;
-    if (c.variant == 3 || c.variant == 4) {
-      const int wgs = c.tiles_m * c.tiles_n * c.nsplit;
-      if (wgs > 1536) c.tiles_per_wg = (wgs + 511) / 512;
-    }
-    if (c.variant == 7) {   // two workgroups per CU are resident: beyond two rounds, walk in one
-      const int wgs = c.tiles_m * c.tiles_n * c.nsplit;
-      if (wgs > 1024) c.tiles_per_wg = (wgs + 511) / 512;
+      if (c.kc == 64 && c.chunks_per_split >= 12) c.depth = 8;
     }
     const int groups_m = (c.tiles_m + c.tiles_per_wg - 1) / c.tiles_per_wg;
     c.tiles_per_xcd = (groups_m * c.tiles_n * c.nsplit + 7) / 8;
@@ -416,25 +516,22 @@ struct Builder {
     // block size, count what the eight L2s fetch (each its own spatial groups' input slices and
     // its own channel tiles' weight slices, once) and keep the cheapest.
     c.n_block = 1;
-    if (((c.variant >= 1 && c.variant <= 4) || c.variant == 6 || c.variant == 7) && c.tiles_n > 1) {
-      const double in_unit = 2.0 * c.batch * c.hin * c.win * (c.chunks_per_tap * 64.0) /
-                             ((double)groups_m * c.nsplit);
-      const double w_unit = 2.0 * c.cout_pad * c.ktot / ((double)c.tiles_n * c.nsplit);
-      const int per_split = groups_m * c.tiles_n, total = per_split * c.nsplit;
+    if (c.variant != CONV_GENERIC && c.tiles_n > 1) {
+      const double in_unit = 2.0 * c.batch * c.hin * c.win * (c.chunks_per_tap * 64.0) / (double)groups_m;
+      const double w_unit = 2.0 * c.cout_pad * c.ktot / (double)c.tiles_n;
+      const int total = groups_m * c.tiles_n;
       double best = 0;
       for (int nb = 1; nb <= c.tiles_n; nb *= 2) {
         if (c.tiles_n % nb) continue;
         double bytes = 0;
-        std::vector<char> seen_in((size_t)groups_m * c.nsplit), seen_w((size_t)c.tiles_n * c.nsplit);
+        std::vector<char> seen_in((size_t)groups_m), seen_w((size_t)c.tiles_n);
         for (int x = 0; x < 8; ++x) {
           std::fill(seen_in.begin(), seen_in.end(), 0);
           std::fill(seen_w.begin(), seen_w.end(), 0);
           for (int t = x * c.tiles_per_xcd; t < std::min(total, (x + 1) * c.tiles_per_xcd); ++t) {
-            const int split = t / per_split, within = t % per_split;
-            const int blk = groups_m * nb, in_blk = within % blk;
-            const int gm = in_blk / nb, tn = (within / blk) * nb + in_blk % nb;
-            char& si = seen_in[(size_t)split * groups_m + gm];
-            char& sw = seen_w[(size_t)split * c.tiles_n + tn];
+            const int blk = groups_m * nb, in_blk = t % blk;
+            char& si = seen_in[(size_t)(in_blk / nb)];
+            char& sw = seen_w[(size_t)((t / blk) * nb + in_blk % nb)];
             if (!si) { si = 1; bytes += in_unit; }
             if (!sw) { sw = 1; bytes += w_unit; }
           }
@@ -447,34 +544,28 @@ struct Builder {
   // Appends the convolution and, when it is split along K, its reduction kernel.
   // keep_partial: leave the partial sums in the scratch buffer for a later kernel (ConvLSTM).
   // Returns the index of the convolution op.
-  // w2_off / out2: packed weights and output of a 1x1 stride-2 projection fused into a 3x3
-  // stride-2 layer (out2 == NULL: none).
+  // wf_off: the weights' offset in fragment order, for the variants that read them so (w_off then
+  // is none).  wf2_off / out2: fragment-ordered weights and output of a 1x1 stride-2 projection
+  // fused into a 3x3 stride-2 layer (out2 == NULL: none).
+  static constexpr size_t kNoWeights = (size_t)-1;
   int add_conv(ConvParams c, size_t w_off, const Tensor* res, const Tensor* out, bool relu,
-               bool want_f32, bool keep_partial, double flops, size_t w2_off = 0,
-               const Tensor* out2 = nullptr, size_t wf_off = (size_t)-1,
-               size_t wf2_off = (size_t)-1) {
+               bool want_f32, bool keep_partial, double flops, size_t wf_off = kNoWeights,
+               size_t wf2_off = kNoWeights, const Tensor* out2 = nullptr) {
     Op op;
     op.fam = F_CONV;
     op.flops = flops;
-    c.wt = d_w ? d_w + w_off : nullptr;
-    c.wt_frag = (d_w && wf_off != (size_t)-1) ? d_w + wf_off : nullptr;
+    auto at = [&](size_t off) { return d_w && off != kNoWeights ? d_w + off : nullptr; };
+    c.wt = at(w_off); c.wt_frag = at(wf_off); c.wt2 = nullptr; c.wt2_frag = at(wf2_off);
     choose_split(c);
     const bool partial = c.nsplit > 1 || keep_partial;
     c.use_partial = partial ? 1 : 0;
     c.partial = nullptr;   // patched when the scratch buffer is carved
     c.out = nullptr; c.out_pitch = 0; c.res = nullptr; c.res_pitch = 0; c.relu = 0;
     c.out_f32 = nullptr;
-    c.wt2 = nullptr; c.out2 = nullptr; c.out2_pitch = 0; c.partial2 = nullptr;
-    const bool fused = out2 != nullptr && (c.variant == 4 || c.variant == 7);
-    c.wt2_frag = nullptr;
-    if (fused) {
-      c.wt2 = d_w ? d_w + w2_off : nullptr;
-      c.wt2_frag = (d_w && wf2_off != (size_t)-1) ? d_w + wf2_off : nullptr;
-      if (!partial) { c.out2 = out2->p; c.out2_pitch = out2->pitch; }
-    }
+    c.out2 = nullptr; c.out2_pitch = 0;
+    if (out2) { c.out2 = out2->p; c.out2_pitch = out2->pitch; }
     if (partial) {
-      partial_floats =
-          std::max(partial_floats, (size_t)(fused ? 2 : 1) * c.nsplit * c.m * c.cout_pad);
+      partial_floats = std::max(partial_floats, (size_t)c.nsplit * c.m * c.cout_pad);
     } else {
       if (out) { c.out = out->p; c.out_pitch = out->pitch; }
       if (res) { c.res = res->p; c.res_pitch = res->pitch; }
@@ -496,11 +587,6 @@ struct Builder {
       s.relu = relu ? 1 : 0;
       s.out_f32 = nullptr;
       s.img_m = c.img_m;
-      s.partial2 = nullptr; s.out2 = nullptr; s.out2_pitch = 0;
-      if (fused) {
-        s.out2 = out2->p; s.out2_pitch = out2->pitch;   // partial2 patched with the scratch
-        e.bytes *= 2.0;
-      }
       ops.push_back(e);
       if (want_f32) logits_op = (int)ops.size() - 1;
     }
@@ -525,42 +611,31 @@ struct Builder {
     g.ntaps = k * k; g.kw = k; g.chunks_per_tap = cin / g.kc;
     g.nchunks = g.ntaps * g.chunks_per_tap; g.ktot = g.nchunks * g.kc;
     g.stride = stride; g.pad = pad;
-    g.frag_ok = (res == nullptr && !want_f32) ? 1 : 0;
-    const size_t w_off = reserve_w((size_t)g.cout_pad * g.ktot);
-    if (pack) pack_generic(blob + blob_at, cout, cin, k, g.cout_pad, host_w.data() + w_off);
     out->h = g.hout; out->w = g.wout; out->c = cout;
-    const bool fuse = proj_out && k == 3 && stride == 2 && pad == 1 && g.kc == 64 &&
-                      (double)g.batch * g.hin * g.win * g.cin_pitch < 2147483648.0;
-    if (proj_fused) *proj_fused = fuse;
-    if (!fuse) {
-      // the kernel variant is a function of the shapes alone: layers that will read their
-      // weights as MFMA fragments get a second, fragment-ordered copy
-      size_t wf_off = (size_t)-1;
-      ConvParams probe = g;
-      choose_split(probe);
-      if (probe.variant == 6 || probe.variant == 7) {
-        wf_off = reserve_w((size_t)g.cout_pad * g.ktot);
-        if (pack) pack_frag(blob + blob_at, cout, cin, 9, g.cout_pad, host_w.data() + wf_off);
-      }
-      return add_conv(g, w_off, res, out, relu, want_f32, keep_partial,
-                      2.0 * g.m * (double)cout * cin * k * k, 0, nullptr, wf_off);
-    }
-    const size_t w2_off = reserve_w((size_t)g.cout_pad * cin);
-    if (pack) pack_generic(blob + proj_at, cout, cin, 1, g.cout_pad, host_w.data() + w2_off);
-    proj_out->h = g.hout; proj_out->w = g.wout; proj_out->c = cout;
-    size_t wf_off = (size_t)-1, wf2_off = (size_t)-1;
+    // The kernel variant is a function of the shapes alone: layers that read their weights as MFMA
+    // fragments are packed in that order, the others row by row.
     ConvParams probe = g;
     choose_split(probe);
-    if (probe.variant == 7) {   // fragment-ordered copies of the 3x3 weights and of the projection
-      wf_off = reserve_w((size_t)g.cout_pad * g.ktot);
+    const bool frag = probe.variant == CONV_DIRA || probe.variant == CONV_S2_DIRA || probe.variant == CONV_KW;
+    size_t w_off = kNoWeights, wf_off = kNoWeights, wf2_off = kNoWeights;
+    const size_t n_w = (size_t)g.cout_pad * g.ktot;
+    if (frag) {
+      wf_off = reserve_w(n_w);
+      pack_frag_at(blob_at, cout, cin, 9, g.cout_pad, wf_off);
+    } else {
+      w_off = reserve_w(n_w);
+      pack_generic_at(blob_at, cout, cin, k * k, g.cout_pad, w_off);
+    }
+    const bool fuse = proj_out && frag && stride == 2;
+    if (proj_fused) *proj_fused = fuse;
+    if (fuse) {
+      proj_out->h = g.hout; proj_out->w = g.wout; proj_out->c = cout;
       wf2_off = reserve_w((size_t)g.cout_pad * cin);
-      if (pack) {
-        pack_frag(blob + blob_at, cout, cin, 9, g.cout_pad, host_w.data() + wf_off);
-        pack_frag(blob + proj_at, cout, cin, 1, g.cout_pad, host_w.data() + wf2_off);
-      }
+      pack_frag_at(proj_at, cout, cin, 1, g.cout_pad, wf2_off);
     }
     return add_conv(g, w_off, res, out, relu, want_f32, keep_partial,
-                    2.0 * g.m * (double)cout * cin * (k * k + 1), w2_off, proj_out, wf_off, wf2_off);
+                    2.0 * g.m * (double)cout * cin * (k * k + (fuse ? 1 : 0)), wf_off, wf2_off,
+                    fuse ? proj_out : nullptr);
   }
 
   // A 64 -> 64 -> 64 channel BasicBlock without projection as ONE launch (k_block64_fused):
@@ -583,11 +658,11 @@ struct Builder {
     g.ntaps = 9; g.kw = 3; g.chunks_per_tap = 1; g.nchunks = 9; g.ktot = 576;
     g.stride = 1; g.pad = 1;
     const size_t wa_off = reserve_w((size_t)64 * 576);
-    if (pack) pack_generic(blob + at_a, 64, 64, 3, 64, host_w.data() + wa_off);
+    pack_generic_at(at_a, 64, 64, 9, 64, wa_off);
     const size_t wb_off = reserve_w((size_t)64 * 576);
-    if (pack) pack_generic(blob + at_b, 64, 64, 3, 64, host_w.data() + wb_off);
+    pack_generic_at(at_b, 64, 64, 9, 64, wb_off);
     out->h = g.hout; out->w = g.wout; out->c = 64;
-    g.variant = 5;
+    g.variant = CONV_BLOCK64;
     g.tiles_x = (g.wout + 15) / 16;
     g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
     g.tiles_n = 1; g.nsplit = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
@@ -620,7 +695,10 @@ struct Builder {
     g.ntaps = k; g.kw = 1; g.chunks_per_tap = 1; g.nchunks = k; g.ktot = k * g.kc;
     g.stride = 2; g.pad = 0;
     const size_t w_off = reserve_w((size_t)g.cout_pad * g.ktot);
-    if (pack) pack_rowtap(blob + blob_at, cout, k, chunk_px, g.cout_pad, host_w.data() + w_off);
+    if (pack)
+      pack_tasks.push_back([=] {
+        pack_rowtap(half_blob.data() + blob_at, cout, k, chunk_px, g.cout_pad, host_w.data() + w_off);
+      });
     out->h = g.hout; out->w = g.wout; out->c = cout;
     first_conv_op =
         add_conv(g, w_off, nullptr, out, true, false, false, 2.0 * g.m * (double)cout * 3 * k * k);
@@ -660,7 +738,7 @@ struct Builder {
       // stem convolution and max-pool in one kernel; weights packed as MFMA fragments of row
       // taps of 8 pixels
       const size_t w_off = reserve_w((size_t)64 * 224);
-      if (pack) pack_stem_frag(blob + at, host_w.data() + w_off);
+      if (pack) pack_tasks.push_back([=] { pack_stem_frag(half_blob.data() + at, host_w.data() + w_off); });
       Op op;
       op.fam = F_STEM;
       StemPoolParams& sp = op.stem;
@@ -730,7 +808,7 @@ struct Builder {
     // head weights: 8 x 256 fp16, plain [k][c]; the head runs inside the ConvLSTM epilogue
     const size_t w_off = reserve_w(2048);
     if (pack)
-      for (int i = 0; i < 2048; ++i) host_w[w_off + i] = (f16)blob[at + i];
+      pack_tasks.push_back([=] { std::copy_n(half_blob.data() + at, 2048, host_w.data() + w_off); });
     at += 2048;
     {
       Op op;
@@ -750,6 +828,19 @@ struct Builder {
 
   void walk(int ph, int pw) {
     if (d.net == HS_NET_TINY4) walk_tiny(ph, pw); else walk_resnet(ph, pw);
+    // With several frames per launch every layer prefetches the next one's fragment-ordered weights:
+    // a pass then touches more than the last-level cache holds and finds the weights in HBM (four
+    // frames 641 x 361: 363 -> 337 us, sixteen frames 416 x 240: 375 -> 358).  The 36 MB of a one-frame
+    // application stay cached, and the prefetch would only cost (168 -> 172 us).
+    ConvParams* prev = nullptr;
+    for (Op& op : ops) {
+      if (op.fam != F_CONV) continue;
+      if (prev && op.conv.wt_frag && d.batch > 1) {
+        prev->next_wt = op.conv.wt_frag;
+        prev->next_lines = (int)((size_t)op.conv.cout_pad * op.conv.ktot * sizeof(f16) / 128);
+      }
+      prev = &op.conv;
+    }
   }
 };
 
@@ -844,17 +935,8 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     float* d_partial = bb.carve.take<float>(bb.partial_floats);
     bb.d_partial = d_partial;
     for (Op& op : bb.ops) {
-      if (op.fam == F_CONV && op.conv.use_partial) {
-        op.conv.partial = d_partial;
-        if (op.conv.wt2)
-          op.conv.partial2 = d_partial + (size_t)op.conv.nsplit * op.conv.m * op.conv.cout_pad;
-      }
-      if (op.fam == F_SPLITK) {
-        op.splitk.partial = d_partial;
-        if (op.splitk.out2)
-          op.splitk.partial2 =
-              d_partial + (size_t)op.splitk.nsplit * op.splitk.m * op.splitk.cout_pad;
-      }
+      if (op.fam == F_CONV && op.conv.use_partial) op.conv.partial = d_partial;
+      if (op.fam == F_SPLITK) op.splitk.partial = d_partial;
       if (op.fam == F_LSTM) op.lstm.partial = d_partial;
     }
   };
@@ -920,6 +1002,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
   app->x_ch = 512;
 
   // upload weights and tables, zero the recurrent state and the padded borders
+  b.run_pack();
   HS_HIP(hipMemcpy(b.d_w, b.host_w.data(), b.host_w.size() * sizeof(f16), hipMemcpyHostToDevice));
   {
     float lut32[256];
@@ -1002,8 +1085,8 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       };
       s.infer_static = s.infer;
       for (Op& op : s.infer_static) {
-        if (op.fam == F_CONV) { move(op.conv.partial); move(op.conv.partial2); }
-        if (op.fam == F_SPLITK) { move(op.splitk.partial); move(op.splitk.partial2); }
+        if (op.fam == F_CONV) move(op.conv.partial);
+        if (op.fam == F_SPLITK) move(op.splitk.partial);
         if (op.fam == F_LSTM) move(op.lstm.partial);
       }
     }

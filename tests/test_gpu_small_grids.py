@@ -1,0 +1,56 @@
+"""The convolution kernels of small and middle grids (k_conv3x3_kw): every instantiation the host's
+rules choose, at maps smaller than one tile, one tile plus a remainder, and several ragged
+tiles, against the CPU oracle.  The recurrent cell is checked alone on the GPU's own inputs."""
+import numpy as np
+import pytest
+
+import oracle
+import synth_inputs as si
+from gpu_common import TOL_CELL, TOL_STATE_RMS, check_frame, make_oracles, rel_err, rms_rel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nw,nh,batch", [
+    (96, 64, 1),      # maps of 8 x 12, 4 x 6 and 2 x 3 pixels: less than a tile; 1, 2, 4 and 6 K splits
+    (130, 66, 6),     # three K splits (the last one shorter), grids beyond one round of workgroups
+    (130, 66, 16),    # one split, two and four channel groups per workgroup, both strides
+    (288, 160, 5),    # two splits with 8 x 8-pixel tiles
+    (288, 160, 12),   # one split with 8 x 8-pixel tiles, maps of 20 x 36, 10 x 18 and 5 x 9
+])
+def test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch):
+    from paper_2402_04466_amd.harness import AppStream
+    fw, fh, frames = 320, 180, 2
+    blob = si.he_normal_blob(si.RESNET18_CONVLSTM_LAYERS, 8)
+    w16 = [w.astype(np.float16).astype(np.float32)
+           for w in oracle.split_blob(blob, oracle.ResNet18ConvLSTMNet.shapes())[-2:]]
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_RESNET18_CONVLSTM, frame_w=fw, frame_h=fh, net_w=nw, net_h=nh,
+                  blob=blob, palette=si.DEFAULT_PALETTE, queue_depth=2, batch=batch)
+    try:
+        host = {j: list(si.tool_scene_frames(frames, fh, fw, 70 + j)) for j in range(batch)}
+        sampled = sorted({0, batch - 1})
+        oracles = {j: make_oracles("resnet18_convlstm", blob, nw, nh, True, si.DEFAULT_PALETTE)[0]
+                   for j in sampled}
+        prev = {}
+        for t in range(frames):
+            print(f"[small-grid] {nw}x{nh} batch {batch} frame {t}", flush=True)
+            d_in = [s.upload_frame(host[j][t]) for j in range(batch)]
+            d_out = [s.new_output() for _ in range(batch)]
+            assert s.submit_batch(d_in, d_out, t) == hs.HS_OK
+            rs = s.wait_batch()
+            for j in sampled:
+                g, o = s.fetch(rs[j], d_out[j]), oracles[j].process(host[j][t])
+                check_frame(g, host[j][t], o, None, threshold=0.5, alpha=0.5,
+                            palette=si.DEFAULT_PALETTE, fp32_input=False,
+                            tag=f"small-grid/{nw}x{nh}x{batch}/stream{j}/frame{t}")
+                h, c = s.state(rs[j], stream=j)
+                h0, c0 = prev.get(j, (np.zeros_like(h), np.zeros_like(c)))
+                oh, oc = oracle.convlstm_step(s.features(rs[j], stream=j), h0, c0, w16[0])
+                head = oracle.conv2d(h, w16[1], 1, 0)
+                assert max(rel_err(h, oh), rel_err(c, oc), rel_err(g["logits"], head)) <= TOL_CELL
+                assert rms_rel(h, o["h"]) <= TOL_STATE_RMS and rms_rel(c, o["c"]) <= TOL_STATE_RMS
+                prev[j] = (h, c)
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
