@@ -119,8 +119,10 @@ typedef struct {
  * t_enqueued_ns is when hs_submit_frame had handed all work to the GPU queues (host
  * launch cost = t_enqueued_ns - t_submit_ns).
  * The three intermediate stamps are t_overlay_done_ns minus the GPU-event time between
- * that stage's end and the overlay's end.  End-to-end latency = t_overlay_done_ns -
- * t_submit_ns (Section II-C).
+ * that stage's end and the overlay's end.  (Recurrent network without the annotation layer:
+ * stage 3's per-cell outputs are written by stage 2's last kernel and its channel maxima are
+ * found beside the overlay, in one launch; stage 3 then ends with the per-cell outputs.)
+ * End-to-end latency = t_overlay_done_ns - t_submit_ns (Section II-C).
  *
  * Device pointers alias the queue slot the frame was given inside the application's
  * workspace and stay valid until queue_depth further frames have been submitted to the

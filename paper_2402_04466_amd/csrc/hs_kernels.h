@@ -121,6 +121,8 @@ struct LstmEpilogueParams {
   const float* partial; int nsplit; int m; int hid;
   float* c; f16* h_out; int h_pitch;
   const f16* w_head; float* logits; int img_m;
+  // stage 3's per-cell outputs (see PostParams), from the same logits
+  float theta; float* heat; uint8_t* mask; uint8_t* kmap;
 };
 KernelDesc describe(const LstmEpilogueParams& p);
 
@@ -148,7 +150,8 @@ struct PostRecord {           // written by the kernel into pinned host memory
 struct PostParams {
   const float* logits; int n;    // [8][n]
   float theta;                   // logit threshold
-  float* heat; uint8_t* mask;    // [8][n]
+  float* heat; uint8_t* mask;    // [8][n]; NULL: only the maxima are wanted (the per-cell outputs
+                                 // have been written with the logits)
   PostRecord* rec;               // host-visible
   int batch;                     // images: logits/heat/mask are [batch][8][n], rec[batch]
   uint8_t* kmap;                 // [batch][n]: lowest channel with mask set, 0xff if none
@@ -171,6 +174,9 @@ struct OverlayLayer {
   const int* marks;                  // anchors written by the postprocess kernel, NULL: none
   int arm, half, scale;              // marker arm / half thickness, pixels per glyph cell
   float rcp_scale;                   // 1/scale
+  // stage 3's channel maxima of this layer's network, found in the overlay's launch: logits
+  // [batch][8][hm*wm] and the records [batch] (NULL: a launch of their own has found them)
+  const float* logits; PostRecord* rec; float theta;
   uint64_t glyph[9];                 // bit (5*row + col) of glyph g, col 0 = leftmost
 };
 struct OverlayParams {
@@ -178,6 +184,8 @@ struct OverlayParams {
   int batch; size_t pitch; int wf, hf;
   float rcp_gpr, rcp_hf, rcp_wf;     // 1/ceil(wf/16), 1/hf, 1/wf (ceil(wf/16)*hf below 2^31)
   int n_layers;                      // layers drawn in order, each over the one before
+  int n_max;                         // workgroups per image ahead of the drawing ones: 8 * n_layers
+                                     // when some layer has a rec, else 0
   OverlayLayer layer[kMaxLayers];
 };
 KernelDesc describe(const OverlayParams& p);

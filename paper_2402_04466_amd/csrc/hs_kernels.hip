@@ -178,6 +178,8 @@ KernelDesc describe(const ResizeParams& p) {
 // reduction kernels below sum them in split order and run the epilogue.
 // =============================================================================================
 __device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + __expf(-x)); }
+// stage 3's heat value of a logit
+__device__ __forceinline__ float heat_of(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 // residual add, ReLU and store of 4 consecutive output channels n..n+3 of pixel m
 template <bool LOAD_RES = true>
@@ -1558,6 +1560,8 @@ KernelDesc describe(const SplitKEpilogueParams& p) {
 // eight logits of the pixel are the workgroup-wide sums of w[k][j] * h[j] over the stored
 // (fp16) h: a wavefront butterfly, then the four wavefront sums in order.
 // logits: planar per image, logits[(image*8 + k)*img_m + pixel in image].
+// The eight threads that hold a pixel's logits also finish the part of stage 3 that needs no other
+// pixel: heat map, mask and the overlay's channel map.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_lstm_epilogue(LstmEpilogueParams p) {
   __shared__ float s_part[4][8];
@@ -1609,7 +1613,13 @@ __global__ __launch_bounds__(256) void k_lstm_epilogue(LstmEpilogueParams p) {
   if (j < 8) {
     const float sum = ((s_part[0][j] + s_part[1][j]) + s_part[2][j]) + s_part[3][j];
     const int img = m / p.img_m, ml = m - img * p.img_m;
-    p.logits[((size_t)img * 8 + j) * p.img_m + ml] = sum;
+    const size_t at = ((size_t)img * 8 + j) * p.img_m + ml;
+    p.logits[at] = sum;
+    p.heat[at] = heat_of(sum);
+    const bool set = sum > p.theta;
+    p.mask[at] = set ? 1 : 0;
+    const uint32_t set_channels = (uint32_t)__ballot(set) & 0xffu;
+    if (j == 0) p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
   }
 }
 
@@ -1752,41 +1762,33 @@ KernelDesc describe(const StemPoolParams& p) {
 }
 
 // =============================================================================================
-// Stage 3: one workgroup per tool channel (plus one for the overlay's channel map).  Every lane keeps (best value, lowest index);
-// wavefront butterfly reduction, then one more across the 4 wavefronts through LDS.
-// The integer outputs are decided on the logits with exact comparisons.
+// Stage 3.  Per channel: maximum, its lowest index, presence -- one workgroup per tool channel;
+// every lane keeps (best value, lowest index), a wavefront butterfly, then one more across the 4
+// wavefronts through LDS.  The integer outputs are decided on the logits with exact comparisons.
+// Per cell (heat, mask, lowest set channel): in the kernel that computes the logits where that is
+// the ConvLSTM epilogue, else here.  Where nothing else waits for the maxima, their workgroups ride
+// along in the overlay's launch (k_overlay) instead of a launch of their own.
 // =============================================================================================
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);
 }
 
-__global__ __launch_bounds__(256) void k_postprocess(PostParams p) {
+// Maximum of channel k of one image (logits L[0 .. n-1]) into the host-visible record; every thread of
+// a 256-thread workgroup.  CELLS: also the heat and mask values on the way.  marks: see PostParams.
+template <bool CELLS>
+__device__ __forceinline__ void channel_maximum(const float* L, int n, float theta, int k, PostRecord* rec,
+                                                float* heat, uint8_t* mask, int* mk, const PostParams* p) {
   __shared__ float s_v[4];
   __shared__ int s_i[4];
-  const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const size_t img_off = (size_t)blockIdx.y * 8 * p.n;   // image blockIdx.y of the batch
-  if (k == 8) {
-    // ninth workgroup: per cell the lowest channel whose mask is set (what the overlay draws),
-    // decided on the logits with the same comparison as the masks
-    for (int i = tid; i < p.n; i += 256) {
-      uint8_t lowest = 0xff;
-#pragma unroll
-      for (int c = 7; c >= 0; --c)
-        if (p.logits[img_off + (size_t)c * p.n + i] > p.theta) lowest = (uint8_t)c;
-      p.kmap[(size_t)blockIdx.y * p.n + i] = lowest;
-    }
-    return;
-  }
-  float* const heat = p.heat + img_off;
-  uint8_t* const mask = p.mask + img_off;
-  PostRecord* const rec = p.rec + blockIdx.y;
-  const float* L = p.logits + img_off + (size_t)k * p.n;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float bv = -INFINITY;
   int bi = 0x7fffffff;
-  for (int i = tid; i < p.n; i += 256) {
+  for (int i = tid; i < n; i += 256) {
     const float x = L[i];
-    heat[(size_t)k * p.n + i] = 1.0f / (1.0f + expf(-x));
-    mask[(size_t)k * p.n + i] = x > p.theta ? 1 : 0;
+    if (CELLS) {
+      heat[i] = heat_of(x);
+      mask[i] = x > theta ? 1 : 0;
+    }
     if (better(x, i, bv, bi)) { bv = x; bi = i; }
   }
 #pragma unroll
@@ -1801,15 +1803,14 @@ __global__ __launch_bounds__(256) void k_postprocess(PostParams p) {
     for (int w = 1; w < 4; ++w)
       if (better(s_v[w], s_i[w], bv, bi)) { bv = s_v[w]; bi = s_i[w]; }
     rec->argmax_idx[k] = bi;
-    rec->peak[k] = 1.0f / (1.0f + expf(-bv));
-    rec->present[k] = bv > p.theta ? 1 : 0;
-    if (p.marks) {
+    rec->peak[k] = heat_of(bv);
+    rec->present[k] = bv > theta ? 1 : 0;
+    if (mk) {
       // anchor of the annotation layer: centre of the argmax cell's footprint in the frame
-      int* mk = p.marks + ((size_t)blockIdx.y * 8 + k) * 2;
-      if (bv > p.theta) {
-        const int ay = bi / p.wm, ax = bi - ay * p.wm;
-        mk[0] = ((2 * ax + 1) * p.wf) / (2 * p.wm);
-        mk[1] = ((2 * ay + 1) * p.hf) / (2 * p.hm);
+      if (bv > theta) {
+        const int ay = bi / p->wm, ax = bi - ay * p->wm;
+        mk[0] = ((2 * ax + 1) * p->wf) / (2 * p->wm);
+        mk[1] = ((2 * ay + 1) * p->hf) / (2 * p->hm);
       } else {
         mk[0] = -1;
         mk[1] = -1;
@@ -1818,8 +1819,32 @@ __global__ __launch_bounds__(256) void k_postprocess(PostParams p) {
   }
 }
 
+__global__ __launch_bounds__(256) void k_postprocess(PostParams p) {
+  const int k = blockIdx.x, tid = threadIdx.x;
+  const size_t img_off = (size_t)blockIdx.y * 8 * p.n;   // image blockIdx.y of the batch
+  if (k == 8) {
+    // ninth workgroup: per cell the lowest channel whose mask is set (what the overlay draws),
+    // decided on the logits with the same comparison as the masks
+    for (int i = tid; i < p.n; i += 256) {
+      uint8_t lowest = 0xff;
+#pragma unroll
+      for (int c = 7; c >= 0; --c)
+        if (p.logits[img_off + (size_t)c * p.n + i] > p.theta) lowest = (uint8_t)c;
+      p.kmap[(size_t)blockIdx.y * p.n + i] = lowest;
+    }
+    return;
+  }
+  const size_t ch_off = img_off + (size_t)k * p.n;
+  int* const mk = p.marks ? p.marks + ((size_t)blockIdx.y * 8 + k) * 2 : nullptr;
+  if (p.heat)
+    channel_maximum<true>(p.logits + ch_off, p.n, p.theta, k, p.rec + blockIdx.y, p.heat + ch_off,
+                          p.mask + ch_off, mk, &p);
+  else
+    channel_maximum<false>(p.logits + ch_off, p.n, p.theta, k, p.rec + blockIdx.y, nullptr, nullptr, mk, &p);
+}
+
 KernelDesc describe(const PostParams& p) {
-  return KernelDesc{(const void*)k_postprocess, dim3(9, p.batch), dim3(256), 0};
+  return KernelDesc{(const void*)k_postprocess, dim3(p.heat ? 9 : 8, p.batch), dim3(256), 0};
 }
 
 // =============================================================================================
@@ -1827,9 +1852,14 @@ KernelDesc describe(const PostParams& p) {
 // accesses) of one frame row; groups are numbered row-major over the frame, 256 per workgroup,
 // so there is no per-row prologue and no barrier.  A group spans at most two cells of the
 // channel map when a cell is at least 16 pixels wide: both are fetched up front together with
-// the pixels (a third cell, on tiny frames, is fetched on demand).  Where the frame rows are
-// contiguous, a wavefront moves its 3072 bytes as fully coalesced 16-byte vectors and regroups
-// them through LDS, instead of every lane touching its own 48-byte span.
+// the pixels (a third cell, on tiny frames, is fetched on demand).  A wavefront moves the 192
+// vectors of its 64 groups as consecutive 16-byte accesses and regroups them through LDS, instead
+// of every lane touching its own 48-byte span.  The last group of a row may hang over the row's
+// end: vectors that start beyond the pitch are not fetched, and of a vector that holds the end of
+// the pixels only their bytes are stored, so the padding between rows stays what it was.  (Those
+// groups used to go pixel by pixel: one such lane held up its wavefront for 45 byte loads, 54 us
+// instead of 11 for four 1279 x 719 frames with annotations.)
+// The first n_max workgroups of an image find stage 3's channel maxima (see channel_maximum).
 // =============================================================================================
 // One layer of stage 4 applied to a group of 16 pixels held in registers (w[0..11], word j starts
 // with channel j mod 3): blend of the layer's channel map, then its annotations.
@@ -1873,7 +1903,7 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
   // fields, (256 - a) * byte + (a * colour + 128) never exceeds 65408, so no field carries into
   // its neighbour.  The field pair is below 2^24 and the factor at most 256: 24-bit multiplies
   // (full rate; the 32-bit ones run at a quarter of it) are exact.
-  const int mx_last = (int)udiv_est((uint32_t)((X0 + 15) * L.wm), (uint32_t)p.wf, p.rcp_wf);
+  const int mx_last = (int)udiv_est((uint32_t)(min(X0 + 15, p.wf - 1) * L.wm), (uint32_t)p.wf, p.rcp_wf);
   const bool one_cell = mx_last == mx0 || (mx_last == mx0 + 1 && k1 == k0);
   if (one_cell) {
     if (k0 != 0xff) {
@@ -1923,7 +1953,7 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
     int rem = X0 * L.wm - mx0 * p.wf;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const uint8_t k = mx == mx0 ? k0 : (mx == mx0 + 1 ? k1 : krow[mx]);
+      const uint8_t k = mx == mx0 ? k0 : (mx == mx0 + 1 ? k1 : krow[min(mx, L.wm - 1)]);
       if (k != 0xff) {
         const uint32_t col = overlay_colour(L, k);
 #pragma unroll
@@ -1941,16 +1971,26 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
   }
   if (L.marks) {
     // annotation layer: a tool's drawing lies in one box; only groups that meet a box look
-    // closer, pixel by pixel, tools in increasing order (later tools paint over earlier ones)
+    // closer, pixel by pixel, tools in increasing order (later tools paint over earlier ones).
+    // The eight anchors are fetched together and tested first: one memory latency, and a wavefront
+    // visits only the tools that some lane meets.
     const int* mk = L.marks + (size_t)by * 16;
     const int lab_w = 11 * L.scale, lab_h = 7 * L.scale;
-#pragma unroll 1
+    uint32_t met = 0;
+#pragma unroll
     for (int k = 0; k < 8; ++k) {
       const int cx = mk[2 * k], cy = mk[2 * k + 1];
-      if (cx < 0) continue;
       const int ox = cx + L.arm + 2, oy = cy - lab_h - 2;          // label origin
-      if (Y < min(cy - L.arm, oy) || Y > cy + L.arm || X0 + 15 < cx - L.arm || X0 >= ox + lab_w)
-        continue;
+      const bool in = cx >= 0 && Y >= min(cy - L.arm, oy) && Y <= cy + L.arm && X0 + 15 >= cx - L.arm &&
+                      X0 < ox + lab_w;
+      met |= in ? 1u << k : 0u;
+    }
+#pragma unroll 1
+    for (int k = 0; k < 8; ++k) {
+      if (!__any((int)((met >> k) & 1u))) continue;
+      if (!((met >> k) & 1u)) continue;
+      const int cx = mk[2 * k], cy = mk[2 * k + 1];
+      const int ox = cx + L.arm + 2, oy = cy - lab_h - 2;
       const uint32_t col = L.pal[k];
       // what this row paints, as pixel intervals around cx and a bit per label pixel
       const int dy = abs(Y - cy);
@@ -1986,115 +2026,90 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
   }
 }
 
-// The same layer applied to one pixel (x[0..2]) of a ragged row tail.
-__device__ __forceinline__ void overlay_layer_pixel(const OverlayParams& p, const OverlayLayer& L,
-                                                    uint32_t (&x)[3], int Y, int X, int by) {
-  const int my = (int)udiv_est((uint32_t)(Y * L.hm), (uint32_t)p.hf, p.rcp_hf);
-  const int mx = (int)udiv_est((uint32_t)(X * L.wm), (uint32_t)p.wf, p.rcp_wf);
-  const uint8_t k = L.kmap[((size_t)by * L.hm + my) * L.wm + mx];
-  int paint = -1;                          // tool whose marker or label covers this pixel
-  if (L.marks) {
-    const int* mk = L.marks + (size_t)by * 16;
-    for (int t = 0; t < 8; ++t) {
-      const int cx = mk[2 * t], cy = mk[2 * t + 1];
-      if (cx < 0) continue;
-      const int dx = abs(X - cx), dy = abs(Y - cy);
-      bool hit = (dx <= L.arm && dy <= L.half) || (dy <= L.arm && dx <= L.half);
-      const int lx = X - (cx + L.arm + 2), ly = Y - (cy - 7 * L.scale - 2);
-      if (lx >= 0 && lx < 11 * L.scale && ly >= 0 && ly < 7 * L.scale) {
-        const int cell = lx / L.scale, gy = ly / L.scale;
-        const int gi = cell >= 6 ? 1 : 0, gx = cell - 6 * gi;
-        if (gx < 5) hit = hit || ((L.glyph[gi ? 1 + t : 0] >> (5 * gy + gx)) & 1ull);
-      }
-      if (hit) paint = t;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (k != 0xff) {
-      const uint32_t pc = (overlay_colour(L, k) >> (8 * c)) & 0xffu;
-      x[c] = mad24((uint32_t)L.a, pc, mad24((uint32_t)(256 - L.a), x[c], 128u)) >> 8;
-    }
-    if (paint >= 0) x[c] = (overlay_colour(L, (uint32_t)paint) >> (8 * c)) & 0xffu;
-  }
-}
-
 // LAYERS == false: exactly one layer (every single-network application).  LAYERS == true: the
 // n_layers layers of a multi-network application are applied in order, each on the result of
 // the one before, while the pixels sit in registers (one read and one write of the frame).
 template <bool LAYERS>
 __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   __shared__ u32x4 s_x[4][192];
-  const int gpr = (p.wf + 15) >> 4;                              // groups per row
-  const int g = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g_wave = g - lane;                                   // first group of the wavefront
-  // rows of whole groups butt against each other and the wavefront is full (uniform per wavefront)
-  const bool coalesced =
-      (p.wf & 15) == 0 && p.pitch == (size_t)48 * gpr && g_wave + 64 <= gpr * p.hf;
-  if (g >= gpr * p.hf) return;
-  // all quotients by float estimate + exact fix-up (operands < 2^31, quotients < 2^22)
-  const int Y = (int)udiv_est((uint32_t)g, (uint32_t)gpr, p.rcp_gpr), X0 = (g - Y * gpr) * 16;
-  const uint8_t* srow = p.src[blockIdx.y] + (size_t)Y * p.pitch;
-  uint8_t* drow = p.dst[blockIdx.y] + (size_t)Y * p.pitch;
-  const int npx = min(16, p.wf - X0);
+  const int by = (int)blockIdx.y;                                // image of the batch
   const int nl = LAYERS ? p.n_layers : 1;
-  if (npx == 16) {
-    // the first layer's map bytes are requested before the pixels, so the two fetches overlap
-    const OverlayCells first = overlay_cells(p, p.layer[0], Y, X0, (int)blockIdx.y);
-    u32x4 v[3];
-    if (coalesced) {
-      // the wavefront's 64 groups are 3072 contiguous bytes: fetch them as 3 x 64 consecutive
-      // 16-byte vectors and regroup through LDS (own region per wavefront, no workgroup barrier)
-      const u32x4* s4 = reinterpret_cast<const u32x4*>(p.src[blockIdx.y] + (size_t)g_wave * 48);
-      const u32x4 t0 = s4[lane], t1 = s4[64 + lane], t2 = s4[128 + lane];
-      s_x[wave][lane] = t0; s_x[wave][64 + lane] = t1; s_x[wave][128 + lane] = t2;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      v[0] = s_x[wave][3 * lane]; v[1] = s_x[wave][3 * lane + 1]; v[2] = s_x[wave][3 * lane + 2];
-    } else {
-      const u32x4* s4 = reinterpret_cast<const u32x4*>(srow + (size_t)X0 * 3);
-      v[0] = s4[0]; v[1] = s4[1]; v[2] = s4[2];
-    }
-    uint32_t w[12];
+  if ((int)blockIdx.x < p.n_max) {                               // eight workgroups per layer
+    const OverlayLayer& L = p.layer[LAYERS ? blockIdx.x >> 3 : 0];
+    const int k = (int)(blockIdx.x & 7u), n = L.wm * L.hm;
+    if (L.rec)
+      channel_maximum<false>(L.logits + ((size_t)by * 8 + k) * n, n, L.theta, k, L.rec + by, nullptr, nullptr,
+                             nullptr, nullptr);
+    return;
+  }
+  const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;          // groups per row, of the frame
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g_wave = ((int)blockIdx.x - p.n_max) * 256 + wave * 64;   // first group of the wavefront
+  if (g_wave >= total) return;
+  const uint8_t* const src = p.src[by];
+  uint8_t* const dst = p.dst[by];
+  // rows of whole groups that butt against each other: the frame is one run of vectors
+  const bool flat = (p.wf & 15) == 0 && p.pitch == (size_t)48 * gpr;
+  // all quotients by float estimate + exact fix-up (operands < 2^31, quotients < 2^22)
+  const int g = min(g_wave + lane, total - 1);
+  const int Y = (int)udiv_est((uint32_t)g, (uint32_t)gpr, p.rcp_gpr), X0 = (g - Y * gpr) * 16;
+  // the first layer's map bytes are requested before the pixels, so the two fetches overlap
+  const OverlayCells first = overlay_cells(p, p.layer[0], Y, X0, by);
+  // vector 64 * j + lane of the wavefront: byte offset in the frame, and how many of its bytes are pixels
+  size_t v_off[3];
+  int v_bytes[3];
+  u32x4 t[3];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) w[i] = v[i >> 2][i & 3];
-    overlay_layer_group(p, p.layer[0], first, w, Y, X0, (int)blockIdx.y);
-    if (LAYERS) {
+  for (int j = 0; j < 3; ++j) {
+    const int v = 64 * j + lane;
+    const uint32_t gi = ((uint32_t)v * 171u) >> 9;               // v / 3 for v < 192
+    const int gv = g_wave + (int)gi;
+    if (flat) {
+      const bool in = gv < total;
+      v_off[j] = (size_t)(in ? g_wave * 3 + v : g_wave * 3) * 16;
+      v_bytes[j] = in ? 16 : 0;
+    } else {
+      const int yv = (int)udiv_est((uint32_t)min(gv, total - 1), (uint32_t)gpr, p.rcp_gpr);
+      const int in_row = (min(gv, total - 1) - yv * gpr) * 48 + (v - 3 * (int)gi) * 16;
+      v_bytes[j] = gv < total ? max(0, min(16, 3 * p.wf - in_row)) : 0;
+      v_off[j] = (size_t)yv * p.pitch + (v_bytes[j] > 0 ? in_row : 0);
+    }
+    t[j] = *reinterpret_cast<const u32x4*>(src + v_off[j]);
+  }
+  s_x[wave][lane] = t[0]; s_x[wave][64 + lane] = t[1]; s_x[wave][128 + lane] = t[2];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  uint32_t w[12];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const u32x4 v = s_x[wave][3 * lane + j];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[4 * j + i] = v[i];
+  }
+  overlay_layer_group(p, p.layer[0], first, w, Y, X0, by);
+  if (LAYERS) {
 #pragma unroll 1
-      for (int l = 1; l < nl; ++l)
-        overlay_layer_group(p, p.layer[l], overlay_cells(p, p.layer[l], Y, X0, (int)blockIdx.y), w,
-                            Y, X0, (int)blockIdx.y);
-    }
-    if (coalesced) {
+    for (int l = 1; l < nl; ++l)
+      overlay_layer_group(p, p.layer[l], overlay_cells(p, p.layer[l], Y, X0, by), w, Y, X0, by);
+  }
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        u32x4 o = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-        s_x[wave][3 * lane + j] = o;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      u32x4* d4 = reinterpret_cast<u32x4*>(p.dst[blockIdx.y] + (size_t)g_wave * 48);
-      d4[lane] = s_x[wave][lane];
-      d4[64 + lane] = s_x[wave][64 + lane];
-      d4[128 + lane] = s_x[wave][128 + lane];
-    } else {
-      u32x4* d4 = reinterpret_cast<u32x4*>(drow + (size_t)X0 * 3);
+  for (int j = 0; j < 3; ++j) {
+    const u32x4 o = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
+    s_x[wave][3 * lane + j] = o;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        u32x4 o = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-        d4[j] = o;
-      }
-    }
-  } else {
-    for (int i = 0; i < npx; ++i) {
-      const int X = X0 + i;
-      uint32_t x[3];
-      for (int c = 0; c < 3; ++c) x[c] = srow[(size_t)X * 3 + c];
-      for (int l = 0; l < nl; ++l) overlay_layer_pixel(p, p.layer[l], x, Y, X, (int)blockIdx.y);
-      for (int c = 0; c < 3; ++c) drow[(size_t)X * 3 + c] = (uint8_t)x[c];
+  for (int j = 0; j < 3; ++j) {
+    const u32x4 o = s_x[wave][64 * j + lane];
+    if (v_bytes[j] == 16) {
+      *reinterpret_cast<u32x4*>(dst + v_off[j]) = o;
+    } else if (v_bytes[j] > 0) {                                 // the end of a row inside this vector
+#pragma unroll
+      for (int i = 0; i < 15; ++i)
+        if (i < v_bytes[j]) dst[v_off[j] + i] = (uint8_t)(o[i >> 2] >> (8 * (i & 3)));
     }
   }
 }
@@ -2102,7 +2117,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
 KernelDesc describe(const OverlayParams& p) {
   const unsigned groups = (unsigned)(((p.wf + 15) >> 4) * p.hf);
   const void* f = p.n_layers > 1 ? (const void*)k_overlay<true> : (const void*)k_overlay<false>;
-  return KernelDesc{f, dim3((groups + 255) / 256, p.batch), dim3(256), 0};
+  return KernelDesc{f, dim3((groups + 255) / 256 + (unsigned)p.n_max, p.batch), dim3(256), 0};
 }
 
 // ---------------------------------------------------------------------------------------------

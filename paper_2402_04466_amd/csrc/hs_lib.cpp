@@ -127,6 +127,8 @@ struct Slot {
   std::vector<Op> post;    // stage 3
   std::vector<Op> overlay; // stage 4: one launch, blockIdx.y = stream of the batch
   hipEvent_t ev_pre = nullptr, ev_infer = nullptr, ev_post = nullptr, ev_overlay = nullptr;
+  // the event behind stage 3 (ev_infer where stage 3 has no launch of its own)
+  hipEvent_t ev_stage3 = nullptr;
   // the event that says the frame has left the last stage: ev_overlay, or, for a member of a
   // group, the first member's (one overlay launch serves them all)
   hipEvent_t ev_done = nullptr;
@@ -815,7 +817,8 @@ struct Builder {
       op.fam = F_LSTM;
       op.lstm = LstmEpilogueParams{nullptr, ops[lstm_conv].conv.nsplit, mf, 256, cstate,
                                    concat ? concat + 512 : nullptr, 768,
-                                   d_w ? d_w + w_off : nullptr, nullptr, hf * wf};
+                                   d_w ? d_w + w_off : nullptr, nullptr, hf * wf, 0.0f, nullptr, nullptr,
+                                   nullptr};
       op.bytes = (double)ops[lstm_conv].conv.nsplit * mf * 1024 * 4.0 + (double)mf * 256 * 10.0;
       op.flops = 2.0 * mf * 8 * 256;
       ops.push_back(op);
@@ -1073,7 +1076,15 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     Op& lo = s.infer[b.logits_op];
     if (lo.fam == F_CONV) lo.conv.out_f32 = s.d_logits;
     else if (lo.fam == F_SPLITK) lo.splitk.out_f32 = s.d_logits;
-    else lo.lstm.logits = s.d_logits;
+    else {
+      lo.lstm.logits = s.d_logits;
+      lo.lstm.theta = (float)theta_d;
+      lo.lstm.heat = s.d_heat; lo.lstm.mask = s.d_mask; lo.lstm.kmap = sb[i].kmap;
+    }
+    // Stage 3 behind the ConvLSTM epilogue is the channel maxima alone.  Only the annotation layer
+    // waits for them; without it they are found in the overlay's launch (one launch, 4 us, less).
+    const bool cells_done = lo.fam == F_LSTM;
+    const bool maxima_with_overlay = cells_done && !d->annotate;
     app->partial_bytes = b.partial_floats * sizeof(float);
     if (app->partial_bytes <= app->ctx->static_scratch_bytes && app->ctx->d_static_scratch) {
       // the same launches with every split-K pointer moved from the lane's scratch in the
@@ -1090,12 +1101,13 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
         if (op.fam == F_LSTM) move(op.lstm.partial);
       }
     }
-    {
+    if (!maxima_with_overlay) {
       Op p;
       p.fam = F_POST;
-      p.post = PostParams{s.d_logits, (int)n_map, (float)theta_d, s.d_heat, s.d_mask, s.rec, B,
+      p.post = PostParams{s.d_logits, (int)n_map, (float)theta_d, cells_done ? nullptr : s.d_heat,
+                          cells_done ? nullptr : s.d_mask, s.rec, B,
                           sb[i].kmap, sb[i].marks, mw, mh, d->frame_w, d->frame_h};
-      p.bytes = B * 8.0 * n_map * (4 + 4 + 1);
+      p.bytes = B * 8.0 * n_map * (4 + (cells_done ? 0 : 4 + 1));
       s.post.push_back(p);
     }
     {
@@ -1110,6 +1122,10 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       op.n_layers = 1;
       OverlayLayer& L = op.layer[0];
       L.kmap = sb[i].kmap; L.wm = mw; L.hm = mh;
+      if (maxima_with_overlay) {
+        L.logits = s.d_logits; L.rec = s.rec; L.theta = (float)theta_d;
+        op.n_max = 8;
+      }
       L.rcp_wm = 1.0f / (float)mw;
       L.a = a_q8;
       L.marks = sb[i].marks;
@@ -1133,6 +1149,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     HS_HIP(hipEventCreate(&s.ev_post));
     HS_HIP(hipEventCreate(&s.ev_overlay));
     s.ev_done = s.ev_overlay;
+    s.ev_stage3 = s.ev_post;
   }
   return HS_OK;
 }
@@ -1153,7 +1170,7 @@ static void completer_main(hs_app* app) {
     float ms_pre = 0, ms_inf = 0, ms_post = 0;
     if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_done);
     if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_done);
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_post, s->ev_done);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_stage3, s->ev_done);
     auto back = [&](float ms) {
       const double ns = (double)ms * 1e6;
       return t_done - (uint64_t)std::max(0.0, ns);
@@ -1657,7 +1674,7 @@ static void finish_submit(hs_app* app, Slot* s) {
 
 // Enqueues stages 1-3 of one batch and, with own_overlay, stage 4 as well.  Without it the
 // caller draws the overlay (a group), records s->ev_overlay and calls finish_submit; *slot_out
-// and *stream_out then name the slot taken and the stream whose tail is the ev_post record.
+// and *stream_out then name the slot taken and the stream whose tail is ev_stage3.
 static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* const* d_frames,
                                 uint8_t* const* d_overlay_outs, uint64_t frame_id,
                                 uint64_t t_submit, bool own_overlay, Slot** slot_out,
@@ -1756,7 +1773,7 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
       app->depth >= app->lanes) {
     Slot& same_lane =
         app->slots[(size_t)((s - app->slots.data()) + app->depth - app->lanes) % app->depth];
-    HS_HIP(hipStreamWaitEvent(lane_stream, same_lane.ev_post, 0));
+    HS_HIP(hipStreamWaitEvent(lane_stream, same_lane.ev_stage3, 0));
   }
   app->lane_last_stream[s->lane] = lane_stream;
   // the caller's producer (another stream) may still be writing the frames
@@ -1781,10 +1798,11 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
       st = run_ops(app, infer, lane_stream, s->ev_infer);
     }
     if (st != HS_OK) return st;
-    st = run_ops(app, s->post, lane_stream, s->ev_post);
+    if (!s->post.empty()) st = run_ops(app, s->post, lane_stream, s->ev_post);
     if (st != HS_OK) return st;
   }
   if (graph) HS_HIP(hipEventRecord(s->ev_post, lane_stream));
+  s->ev_stage3 = !graph && s->post.empty() ? s->ev_infer : s->ev_post;
   s->ev_done = s->ev_overlay;
   if (!own_overlay) {
     *slot_out = s;
@@ -1792,7 +1810,7 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
     return HS_OK;
   }
   hipStream_t ov_stream = app->s_overlay ? app->s_overlay : lane_stream;
-  if (ov_stream != lane_stream) HS_HIP(hipStreamWaitEvent(ov_stream, s->ev_post, 0));
+  if (ov_stream != lane_stream) HS_HIP(hipStreamWaitEvent(ov_stream, s->ev_stage3, 0));
   st = run_ops(app, s->overlay, ov_stream, s->ev_overlay);
   if (st != HS_OK) return st;
   finish_submit(app, s);
@@ -2085,7 +2103,11 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
     return st;
   };
   if (st0 != HS_OK) { set_error("%s", err0.c_str()); return fail_all(st0); }
-  for (size_t i = 0; i < n; ++i) op.layer[i] = slot[i]->overlay[0].overlay.layer[0];
+  op.n_max = 0;
+  for (size_t i = 0; i < n; ++i) {
+    op.layer[i] = slot[i]->overlay[0].overlay.layer[0];
+    if (op.layer[i].rec) op.n_max = 8 * (int)n;
+  }
   op.src[0] = d_frame;
   op.dst[0] = d_overlay_out;
   // one launch draws every member's layer, on member 0's overlay stream, after all stage 3s
@@ -2093,7 +2115,7 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   hipStream_t ov_stream = a0->s_overlay ? a0->s_overlay : tail[0];
   auto overlay_all = [&]() -> hs_status {
     for (size_t i = 0; i < n; ++i)
-      if (tail[i] != ov_stream) HS_HIP(hipStreamWaitEvent(ov_stream, slot[i]->ev_post, 0));
+      if (tail[i] != ov_stream) HS_HIP(hipStreamWaitEvent(ov_stream, slot[i]->ev_stage3, 0));
     for (size_t i = 1; i < n; ++i) slot[i]->ev_done = slot[0]->ev_overlay;
     return run_ops(a0, group->overlay, ov_stream, slot[0]->ev_overlay);
   };

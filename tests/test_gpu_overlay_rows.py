@@ -1,0 +1,56 @@
+"""Stage 4 where a frame row does not end on a group of 16 pixels: rows shorter than a group, one
+pixel short of and past a group's end, wavefronts that cross row ends, rows with padding behind
+them.  Bit-exact against the oracle's overlay of the GPU's own mask (and its annotations); the
+output's padding bytes stay untouched."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("fw,fh,extra_pitch,net,annotate", [
+    (1, 1, 0, "tiny4", False),
+    (15, 9, 0, "tiny4", True),
+    (16, 70, 16, "tiny4", False),
+    (17, 5, 32, "tiny4", False),
+    (335, 33, 0, "tiny4", True),
+    (337, 200, 48, "resnet18_convlstm", False),
+    (1279, 31, 0, "resnet18_convlstm", True),
+])
+def test_overlay_row_ends(hs, fw, fh, extra_pitch, net, annotate):
+    from paper_2402_04466_amd.harness import AppStream
+    tiny = net == "tiny4"
+    pitch = (3 * fw + 15) // 16 * 16 + extra_pitch
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4 if tiny else hs.HS_NET_RESNET18_CONVLSTM, frame_w=fw,
+                  frame_h=fh, net_w=96 if not tiny else 40, net_h=64 if not tiny else 24,
+                  blob=si.he_normal_blob(si.TINY4_LAYERS if tiny else si.RESNET18_CONVLSTM_LAYERS, 11),
+                  palette=si.DEFAULT_PALETTE, frame_pitch=pitch, alpha=0.37,
+                  glyphs=si.DEFAULT_GLYPHS if annotate else None, marker_arm=5, marker_half=1,
+                  glyph_scale=1)
+    try:
+        for i, f in enumerate(si.uniform_frames(2, fh, fw, 12)):
+            print(f"[overlay-rows] {fw}x{fh} pitch {pitch} {net} frame {i}", flush=True)
+            d_in, d_out = s.upload_frame(f), s.new_output()
+            d_out.fill_(0xA5)
+            torch.cuda.synchronize()
+            assert s.submit(d_in, d_out, i) == hs.HS_OK
+            g = s.fetch(s.wait(), d_out)
+            want = oracle.overlay(f, g["mask"], si.DEFAULT_PALETTE, 0.37)
+            if annotate:
+                want = oracle.annotate(want, g["argmax_idx"], g["present"], g["mask"].shape[2],
+                                       g["mask"].shape[1], si.DEFAULT_PALETTE, si.DEFAULT_GLYPHS, 5, 1, 1)
+            assert np.array_equal(g["overlay"], want)
+            p = oracle.postprocess(g["logits"], 0.5)
+            for key in ("mask", "argmax_idx", "present"):
+                assert np.array_equal(g[key], p[key]), key
+            assert np.abs(g["heat"] - p["heat"]).max() <= 1e-6
+            assert np.abs(g["peak"] - p["peak"]).max() <= 1e-6
+            assert bool((d_out[:, 3 * fw:] == 0xA5).all()), "row padding was written"
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
