@@ -47,7 +47,8 @@ KernelDesc describe(const ResizeParams& p);
 // Out-of-range pixels read as zero.  First layers (3 input channels) use a padded
 // 4-channel image and "row taps": kw = 1, a chunk spans several adjacent pixels.
 enum ConvVariant {
-  CONV_GENERIC,   // tile of 64 consecutive pixels x 64 channels, any shape (k_conv_mfma)
+  CONV_DIRECT,    // <= 32 output channels, one chunk of 16 or 32 halves per tap, <= 9 taps: no LDS tiles,
+                  // K splits inside the workgroup (k_conv_direct); wt_frag: [chunk][K-step][lane][8]
   CONV_C64_WALK,  // 3x3/1 layers with 64 input channels on large grids: tile 8 x 16, resident weights,
                   // a workgroup walks tiles_per_wg tiles (k_conv3x3_c64_walk)
   CONV_BLOCK64,   // a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU between,
@@ -71,31 +72,30 @@ struct ConvParams {
   int batch, img_m;     // images per launch, pixels per image (hout*wout)
   int cout, cout_pad;   // cout_pad: multiple of the block's N tile
   int kc;               // 16, 32 or 64
-  int depth;            // prefetch depth in chunks: 4, or 8 (kc == 64 only)
   int variant;          // ConvVariant
-  int kw_splits, kw_cgroups, kw_groups;   // CONV_KW: K splits and groups of 32 channels (their
+  int kw_splits, kw_cgroups, kw_groups;   // CONV_KW, CONV_DIRECT: K splits; groups of 32 channels (their
                         // product: wavefronts per workgroup), groups of 4 x 8 pixels per tile
   int tiles_x;          // spatial variants: tiles per output row
   int ntaps, kw, chunks_per_tap, nchunks, ktot;
   int stride, pad;
-  // K splits as workgroups (CONV_GENERIC; CONV_KW has its splits inside a workgroup and nsplit 1):
-  // split z handles chunks [z*chunks_per_split, ...)
-  int nsplit, chunks_per_split;
+  int chunks_per_split; // K split z handles chunks [z*chunks_per_split, ...)
   int tiles_m, tiles_n; // spatial x channel tiles; the grid is 8 * tiles_per_xcd workgroups
   int tiles_per_wg;     // consecutive spatial tiles one workgroup walks (>= 1);
-                        // workgroups = ceil(tiles_m / tiles_per_wg) * tiles_n * nsplit
+                        // workgroups = ceil(tiles_m / tiles_per_wg) * tiles_n
   int tiles_per_xcd;    // ceil(workgroups / 8)
   int n_block;          // channel tiles per block of the tile order (divides tiles_n;
                         // 1: spatial tile fastest, tiles_n: channel tile fastest)
-  int use_partial;      // 1: store fp32 partial sums for a reduction kernel, no epilogue here
-  float* partial;       // [nsplit][m][cout_pad] fp32
+  int use_partial;      // 1: store the fp32 sums for the ConvLSTM epilogue, no epilogue here
+  float* partial;       // [m][cout_pad] fp32
   // fused epilogue (use_partial == 0)
   f16* out;             // out[m*out_pitch + n]
   int out_pitch;
   const f16* res;       // optional residual, res[m*res_pitch + n]
   int res_pitch;
   int relu;
-  float* out_f32;       // if set: planar fp32 out_f32[n*m_total + m] instead of `out`
+  float* out_f32;       // if set: the logits, planar fp32 out_f32[(image*8 + n)*img_m + pixel], instead of
+                        // `out`; with them stage 3's per-cell outputs (see PostParams)
+  float theta; float* heat; uint8_t* mask; uint8_t* kmap;
   const f16* wt2;       // CONV_BLOCK64: second convolution
   // stride 2: fused 1x1 stride-2 projection of the same input (no residual, no ReLU), or NULL:
   // [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
@@ -106,19 +106,12 @@ struct ConvParams {
 };
 KernelDesc describe(const ConvParams& p);
 
-// Sum split-K partials in split order, add residual, ReLU, store fp16 (or planar fp32).
-struct SplitKEpilogueParams {
-  const float* partial; int nsplit; int m; int cout; int cout_pad;
-  f16* out; int out_pitch; const f16* res; int res_pitch; int relu; float* out_f32; int img_m;
-};
-KernelDesc describe(const SplitKEpilogueParams& p);
-
 // ConvLSTM gate non-linearities and state update from the gate pre-activations, plus the 1x1
-// head on the new h.  partial: [nsplit][m][4*hid], channels ordered i, f, g, o (hid each);
+// head on the new h.  partial: [m][4*hid], channels ordered i, f, g, o (hid each);
 // hid must be 256.  c: fp32 [m][hid] updated in place; h: fp16 written to h_out[m*h_pitch + j];
 // logits[(image*8 + k)*img_m + pixel] = sum_j w_head[k][j] * h[pixel][j] (fp16 weights).
 struct LstmEpilogueParams {
-  const float* partial; int nsplit; int m; int hid;
+  const float* partial; int m; int hid;
   float* c; f16* h_out; int h_pitch;
   const f16* w_head; float* logits; int img_m;
   // stage 3's per-cell outputs (see PostParams), from the same logits
@@ -147,14 +140,14 @@ struct PostRecord {           // written by the kernel into pinned host memory
   float peak[8];
   uint8_t present[8];
 };
+// Stage 3.  Per cell (written by the kernel that computes the logits): heat = sigmoid(logit), mask =
+// logit > theta, both [batch][8][n], and kmap [batch][n] = the lowest channel whose mask is set, 0xff
+// if none (what the overlay draws).  Per channel (here, or in the overlay's launch): PostRecord.
 struct PostParams {
-  const float* logits; int n;    // [8][n]
+  const float* logits; int n;    // [batch][8][n]
   float theta;                   // logit threshold
-  float* heat; uint8_t* mask;    // [8][n]; NULL: only the maxima are wanted (the per-cell outputs
-                                 // have been written with the logits)
-  PostRecord* rec;               // host-visible
-  int batch;                     // images: logits/heat/mask are [batch][8][n], rec[batch]
-  uint8_t* kmap;                 // [batch][n]: lowest channel with mask set, 0xff if none
+  PostRecord* rec;               // [batch], host-visible
+  int batch;
   // anchors of the annotation layer: marks[(image*8 + k)*2 + {0,1}] = frame position (cx, cy) of
   // the centre of tool k's argmax cell, cx = -1 when the tool is absent; NULL: not wanted
   int* marks;

@@ -164,51 +164,17 @@ KernelDesc describe(const ResizeParams& p) {
 }
 
 // =============================================================================================
-// Stage 2: implicit-GEMM convolution.  A workgroup (4 wavefronts) owns a 64-pixel x 64-channel
-// output tile; each wavefront owns a 32x32 quarter and accumulates it with
-// v_mfma_f32_32x32x16_f16.  The MFMA "A" operand is the weight tile and the "B" operand the
-// pixel tile, so a lane ends up holding 4 consecutive output channels of one pixel per
-// accumulator quad -> 8-byte fp16 stores into the pixel-major output.
-//
-// Latency hiding: at batch 1 a grid is only 1-2 workgroups per CU, so the K loop keeps DEPTH
-// chunks of global loads in flight in registers (the loads of chunk q+DEPTH are issued right
-// after chunk q has been handed to LDS); LDS is double buffered, one barrier per chunk.
-//
-// Split-K: blockIdx.z owns a contiguous range of chunks and stores fp32 partial sums; the
-// reduction kernels below sum them in split order and run the epilogue.
+// Stage 2: implicit-GEMM convolution on v_mfma_f32_32x32x16_f16.  The MFMA "A" operand is the weight
+// tile and the "B" operand the pixel tile, so a lane ends up holding 4 consecutive output channels
+// of one pixel per accumulator quad of the pixel-major output.
 // =============================================================================================
 __device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + __expf(-x)); }
 // stage 3's heat value of a logit
 __device__ __forceinline__ float heat_of(float x) { return 1.0f / (1.0f + expf(-x)); }
 
-// residual add, ReLU and store of 4 consecutive output channels n..n+3 of pixel m
-template <bool LOAD_RES = true>
-__device__ __forceinline__ void store_quad(const ConvParams& p, int m, int n, float v[4]) {
-  if (LOAD_RES && p.res) {
-    const half4 r = *reinterpret_cast<const half4*>(p.res + (size_t)m * p.res_pitch + n);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += (float)r[j];
-  }
-  if (p.relu) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.0f);
-  }
-  if (p.out_f32) {
-    // planar per image: out_f32[(image * cout + channel) * img_m + pixel in image]
-    const int b = m / p.img_m, ml = m - b * p.img_m;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) p.out_f32[((size_t)b * p.cout + n + j) * p.img_m + ml] = v[j];
-  } else {
-    half4 o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = (f16)v[j];
-    *reinterpret_cast<half4*>(p.out + (size_t)m * p.out_pitch + n) = o;
-  }
-}
-
 // Epilogue of the 32 channels of one pixel that a lane pair (r, r + 32) holds as accumulator
 // quads: lane half h has channels cbase + 4h + 8i .. +3 in acc[4i .. 4i+3], i = 0..3.  Residual,
-// ReLU and rounding to fp16 as in store_quad; then the two lanes swap one quad of every pair
+// ReLU and rounding to fp16; then the two lanes swap one quad of every pair
 // (v_permlane32_swap: lanes 32..63 of the first operand <-> lanes 0..31 of the second), so that
 // each holds 8 consecutive channels per pair and stores 16 bytes at a time instead of 8.
 // For fp16 outputs whose channel count is a multiple of 32.  Every lane of the wavefront must
@@ -277,206 +243,112 @@ __device__ __forceinline__ void res_octets_to_quads(const u32x4 (&o)[2], half4 (
   for (int i = 0; i < 4; ++i) res[i] = __builtin_bit_cast(half4, make_uint2(q[i][0], q[i][1]));
 }
 
-template <int KC, int DEPTH>
-__global__ __launch_bounds__(256) void k_conv_mfma(ConvParams p) {
-  constexpr int BM = 64, BN = 64;
-  constexpr int PITCH = KC + 8;            // halves; +16 bytes keeps ds_read_b128 conflict-free
-  constexpr int VPR = KC / 8;              // 16-byte vectors per tile row
-  constexpr int NV = BM * VPR;             // vectors per tile (pixel tile and weight tile alike)
-  constexpr int NP = (NV + 255) / 256;     // vectors per thread
-  __shared__ __align__(16) f16 s_x[2][BM * PITCH];
-  __shared__ __align__(16) f16 s_w[2][BN * PITCH];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // XCD-aware tile order.  Workgroups are dealt round-robin to the 8 XCDs (workgroup id % 8),
-  // each with its own L2.  Tile t = (id % 8) * tiles_per_xcd + id / 8 gives every XCD a run of
-  // consecutive tiles (pixel tile fastest, then channel tile, then K split): the workgroups
-  // that share a weight slice, and neighbouring pixel tiles, meet in the same L2.
+// =============================================================================================
+// The small network's layers: at most 32 output channels, 16 or 32 input channels (or four
+// 4-channel pixels of the first layer) per tap, at most nine taps.  A layer is one launch and one
+// memory round trip: a wavefront owns 32 consecutive pixels x 32 channels of one K split, gathers
+// every tap's pixel vectors and weight fragments (wt_frag) straight from memory, all before its
+// first MFMA, and the two wavefronts of a split pair meet in LDS.  (Tiles of 64 pixels x 64 channels
+// staged through LDS computed two to eight times the channels there are, and split K over workgroups
+// whose sums a further launch added: 128 x 128 input, 38 us of launches per frame -> 25.)
+// Per output: chunks in order within a split, then the splits in order.
+// The layer that computes the logits also finishes stage 3's per-cell outputs (see PostParams).
+// KSTEPS: MFMA K-steps of 16 per chunk.  NS: K splits, 1 or 2.
+// =============================================================================================
+template <int KSTEPS, int NS>
+__global__ __launch_bounds__(256) void k_conv_direct(ConvParams p) {
+  constexpr int MAXC = NS == 2 ? 5 : 9;                // chunks of a split
+  constexpr int TILES = 4 / NS;                        // pixel tiles per workgroup
+  __shared__ float4 s_part[NS == 2 ? TILES : 1][4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, h = lane >> 5;
+  const int split = wave % NS, pt = wave / NS;
   const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (tile >= p.tiles_m * p.tiles_n * p.nsplit) return;
-  const int tile_m = tile % p.tiles_m;
-  const int tile_n = (tile / p.tiles_m) % p.tiles_n;
-  const int split = tile / (p.tiles_m * p.tiles_n);
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int q_begin = split * p.chunks_per_split;
-  const int q_end = min(p.nchunks, q_begin + p.chunks_per_split);
+  const int m = (tile * TILES + pt) * 32 + r;
+  const bool valid = m < p.m;
+  const int mc = min(m, p.m - 1), img = mc / p.img_m, ml = mc - img * p.img_m;
+  const int oy = ml / p.wout, ox = ml - oy * p.wout;
+  const int iy0 = oy * p.stride - p.pad, ix0 = ox * p.stride - p.pad;
+  const int q0 = split * p.chunks_per_split, q1 = min(p.nchunks, q0 + p.chunks_per_split);
+  const f16* const base = p.in + (((long)img * p.hin + iy0) * p.win + ix0) * p.cin_pitch + h * 8;
+  const u32x4* const wf = reinterpret_cast<const u32x4*>(p.wt_frag) + lane;
 
-  // Per-thread loader state, fixed over the K loop: for every 16-byte vector this thread
-  // fetches, the address of tap (0,0) / channel 0 of its pixel, the address of its weight
-  // row, and one validity bit per tap (zero padding, ragged last tile).  Per chunk only a
-  // wave-uniform offset is added, so the inner loop carries almost no address arithmetic.
-  const f16* l_abase[NP];
-  const f16* l_wbase[NP];
-  uint32_t l_tapmask[NP];
-  int l_lds[NP];
-  bool l_act[NP];
+  u32x4 xb[MAXC][KSTEPS], wa[MAXC][KSTEPS];
 #pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int v = tid + i * 256;
-    l_act[i] = v < NV;
-    const int row = (v / VPR) % BM;      // threads beyond the tile re-load a valid row, unused
-    const int kv = v % VPR;
-    const int m = m0 + row;
-    const int img = m / p.img_m, ml = m - img * p.img_m;   // image of the batch, pixel in it
-    const int oy = ml / p.wout, ox = ml - oy * p.wout;
-    const int iy0 = oy * p.stride - p.pad, ix0 = ox * p.stride - p.pad;
-    uint32_t mask = 0;
-    for (int t = 0; t < p.ntaps; ++t) {
-      const int ky = t / p.kw, kx = t - ky * p.kw;
-      const int iy = iy0 + ky, ix = ix0 + kx;
-      if (m < p.m && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win) mask |= 1u << t;
+  for (int c = 0; c < MAXC; ++c) {
+    const int q = min(q0 + c, q1 - 1), ky = q / p.kw, kx = q - ky * p.kw;
+    const int iy = iy0 + ky, ix = ix0 + kx;
+    const bool inb = iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
+    const f16* src = inb ? base + ((long)ky * p.win + kx) * p.cin_pitch : p.in;
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      wa[c][ks] = wf[(q * KSTEPS + ks) * 64];
+      const u32x4 v = *reinterpret_cast<const u32x4*>(src + ks * 16);
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      xb[c][ks] = inb ? v : zero;
     }
-    l_tapmask[i] = mask;
-    l_abase[i] = p.in + (((long)img * p.hin + iy0) * p.win + ix0) * p.cin_pitch + kv * 8;
-    l_wbase[i] = p.wt + (size_t)(n0 + row) * p.ktot + kv * 8;
-    l_lds[i] = row * PITCH + kv * 8;
   }
-  const f16* const a_safe = p.in;         // any valid address: out-of-range taps read it, unused
-
-  // Loads are unconditional (out-of-range taps read a valid dummy address and are zeroed
-  // when handed to LDS): with no branch around a load the compiler can count outstanding
-  // loads exactly and waits only for the oldest stage.  Stage registers are indexed with
-  // compile-time constants only (macro, fully unrolled) so that they stay in VGPRs.
-  // Chunks are fetched strictly in order; (ld_q, ld_tap, ld_cc, ld_ky, ld_kx) is the next one
-  // and stops advancing at the last chunk of this workgroup's range.
-  u32x4 st_x[DEPTH][NP], st_w[DEPTH][NP];
-  uint32_t st_inb[DEPTH];
-  int ld_q = q_begin;
-  int ld_tap = q_begin / p.chunks_per_tap;
-  int ld_cc = q_begin - ld_tap * p.chunks_per_tap;
-  int ld_ky = ld_tap / p.kw, ld_kx = ld_tap - ld_ky * p.kw;
-#define HS_LOAD_CHUNK(D_)                                                                      \
-  {                                                                                            \
-    const long a_off_ = ((long)ld_ky * p.win + ld_kx) * p.cin_pitch + ld_cc * KC;              \
-    const long w_off_ = (long)ld_q * KC;                                                       \
-    uint32_t mask_ = 0;                                                                        \
-    _Pragma("unroll") for (int i = 0; i < NP; ++i) {                                           \
-      const bool inb_ = (l_tapmask[i] >> ld_tap) & 1u;                                         \
-      mask_ |= (inb_ ? 1u : 0u) << i;                                                          \
-      const f16* a_ = inb_ ? l_abase[i] + a_off_ : a_safe;                                     \
-      st_x[D_][i] = *reinterpret_cast<const u32x4*>(a_);                                       \
-      st_w[D_][i] = *reinterpret_cast<const u32x4*>(l_wbase[i] + w_off_);                      \
-    }                                                                                          \
-    st_inb[D_] = mask_;                                                                        \
-    const bool adv_ = ld_q + 1 < q_end;                                                        \
-    const bool wrap_c_ = ld_cc + 1 == p.chunks_per_tap;                                        \
-    const bool wrap_x_ = wrap_c_ && (ld_kx + 1 == p.kw);                                       \
-    ld_q += adv_ ? 1 : 0;                                                                      \
-    ld_cc = !adv_ ? ld_cc : (wrap_c_ ? 0 : ld_cc + 1);                                         \
-    ld_tap += (adv_ && wrap_c_) ? 1 : 0;                                                       \
-    ld_ky += (adv_ && wrap_x_) ? 1 : 0;                                                        \
-    ld_kx = !(adv_ && wrap_c_) ? ld_kx : (wrap_x_ ? 0 : ld_kx + 1);                            \
-  }
-
   floatx16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-
-  const int wm = wave & 1, wn = wave >> 1;
-  const int fx_off = (wm * 32 + (lane & 31)) * PITCH + (lane >> 5) * 8;
-  const int fw_off = (wn * 32 + (lane & 31)) * PITCH + (lane >> 5) * 8;
-
-  static_assert(DEPTH == 4 || DEPTH == 8, "the pipeline below is written out for 4 or 8 stages");
-  // Prologue: fill all four stages.  Chunk indices are clamped instead of guarded so that
-  // there is no branch around a load (a short K range re-loads its last chunk, unused).
-  HS_LOAD_CHUNK(0)
-  HS_LOAD_CHUNK(1)
-  HS_LOAD_CHUNK(2)
-  HS_LOAD_CHUNK(3)
-  if constexpr (DEPTH > 4) {
-    HS_LOAD_CHUNK(4)
-    HS_LOAD_CHUNK(5)
-    HS_LOAD_CHUNK(6)
-    HS_LOAD_CHUNK(7)
-  }
-
-  // One pipeline step for stage D_ (a literal, so every register index is a constant):
-  // hand chunk q to LDS, barrier, refill the stage with chunk q + DEPTH, MFMAs on chunk q.
-  // REFILL_ is the refill condition: `true` in the steady-state loop (branch-free body, so
-  // the wait before the LDS hand-over is for the oldest stage only), a test in the tail.
-#define HS_STEP(D_, REFILL_)                                                                   \
-  {                                                                                            \
-    const int q = qb + (D_);                                                                   \
-    (void)q;                                                                                   \
-    _Pragma("unroll") for (int i = 0; i < NP; ++i) {                                           \
-      if constexpr (NV % 256 != 0) { if (!l_act[i]) continue; }                                \
-      const u32x4 zero = {0u, 0u, 0u, 0u};                                                     \
-      *reinterpret_cast<u32x4*>(&s_x[buf][l_lds[i]]) =                                         \
-          ((st_inb[D_] >> i) & 1u) ? st_x[D_][i] : zero;                                       \
-      *reinterpret_cast<u32x4*>(&s_w[buf][l_lds[i]]) = st_w[D_][i];                            \
-    }                                                                                          \
-    __syncthreads();                                                                           \
-    if (REFILL_) HS_LOAD_CHUNK(D_)                                                  \
-    const f16* fx = &s_x[buf][fx_off];                                                         \
-    const f16* fw = &s_w[buf][fw_off];                                                         \
-    _Pragma("unroll") for (int ks = 0; ks < KC / 16; ++ks) {                                   \
-      const half8 a = *reinterpret_cast<const half8*>(fw + ks * 16);                           \
-      const half8 b = *reinterpret_cast<const half8*>(fx + ks * 16);                           \
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc, 0, 0, 0);                        \
-    }                                                                                          \
-    buf ^= 1;                                                                                  \
-  }
-
-  int buf = 0;
-  int qb = q_begin;
-  for (; qb + 2 * DEPTH <= q_end; qb += DEPTH) {   // steady state: every refill is in range
-    HS_STEP(0, true)
-    HS_STEP(1, true)
-    HS_STEP(2, true)
-    HS_STEP(3, true)
-    if constexpr (DEPTH > 4) {
-      HS_STEP(4, true)
-      HS_STEP(5, true)
-      HS_STEP(6, true)
-      HS_STEP(7, true)
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c)
+    if (c < q1 - q0) {
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, wa[c][ks]),
+                                                    __builtin_bit_cast(half8, xb[c][ks]), acc, 0, 0, 0);
     }
-  }
-  for (; qb < q_end; qb += DEPTH) {                // tail: at most 2*DEPTH - 1 chunks
-    if (qb + 0 < q_end) HS_STEP(0, q + DEPTH < q_end)
-    if (qb + 1 < q_end) HS_STEP(1, q + DEPTH < q_end)
-    if (qb + 2 < q_end) HS_STEP(2, q + DEPTH < q_end)
-    if (qb + 3 < q_end) HS_STEP(3, q + DEPTH < q_end)
-    if constexpr (DEPTH > 4) {
-      if (qb + 4 < q_end) HS_STEP(4, q + DEPTH < q_end)
-      if (qb + 5 < q_end) HS_STEP(5, q + DEPTH < q_end)
-      if (qb + 6 < q_end) HS_STEP(6, q + DEPTH < q_end)
-      if (qb + 7 < q_end) HS_STEP(7, q + DEPTH < q_end)
+  if (NS == 2) {
+    if (split == 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        s_part[pt][i][lane] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
     }
-  }
-#undef HS_STEP
-
-  // accumulator register 4*i + j holds channel n_base + 8*i + j of pixel m
-  const int m = m0 + wm * 32 + (lane & 31);
-  const int n_base = n0 + wn * 32 + (lane >> 5) * 4;
-  if (!p.use_partial) {
-    if (m >= p.m) return;
+    __syncthreads();
+    if (split == 1) return;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int n = n_base + 8 * i;
+      const float4 b = s_part[pt][i][lane];
+      const float v[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[4 * i + j] = (0.0f + acc[4 * i + j]) + v[j];
+    }
+  }
+  // accumulator quad i: channels 8 * i + 4 * h .. + 3 of pixel m
+  if (p.out_f32 == nullptr) {
+    if (!valid) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int n = 8 * i + 4 * h;
       if (n >= p.cout) continue;
-      float v[4] = {acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]};
-      store_quad(p, m, n, v);
+      half4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = (f16)(p.relu ? fmaxf(acc[4 * i + j], 0.0f) : acc[4 * i + j]);
+      *reinterpret_cast<half4*>(p.out + (size_t)m * p.out_pitch + n) = o;
     }
     return;
   }
-
-  // ---- split-K: store fp32 partial sums; a separate kernel reduces them.  (Reducing inside
-  // this kernel would need a device-wide release per workgroup, which on a multi-XCD part
-  // means a full L2 write-back each time -- measured 3x slower than the extra launch.)
-  if (m < p.m) {
-    float* dst = p.partial + ((size_t)split * p.m + m) * p.cout_pad + n_base;
+  // logits: eight channels, planar per image; lane half h holds four of a pixel's
+  uint32_t set_channels = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<float4*>(dst + 8 * i) =
-          make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+  for (int j = 0; j < 4; ++j) {
+    const float x = acc[j];
+    const bool set = x > p.theta;
+    set_channels |= set ? 1u << (4 * h + j) : 0u;
+    if (valid) {
+      const size_t at = ((size_t)img * 8 + 4 * h + j) * p.img_m + ml;
+      p.out_f32[at] = x;
+      p.heat[at] = heat_of(x);
+      p.mask[at] = set ? 1 : 0;
+    }
   }
+  set_channels |= (uint32_t)__shfl_xor((int)set_channels, 32, 64);
+  if (valid && h == 0) p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
 }
 
-#undef HS_LOAD_CHUNK
-
 // =============================================================================================
-// Stage 2, 3x3 layers (all of the big network's convolutions but the stem): the same implicit GEMM,
-// but a workgroup's output tile is a SPATIAL block, so that the nine taps read one shared input
+// Stage 2, 3x3 layers (all of the big network's convolutions but the stem): a workgroup's output
+// tile is a SPATIAL block, so that the nine taps read one shared input
 // patch in LDS.  Patch pixels are padded to 144 bytes and patch rows to 128 mod 256 bytes: the 16
 // lanes of one ds_read_b128 pass (two rows of 8 pixels) then fall into 16 different 16-byte bank
 // groups.  Every output accumulates chunk by chunk (64 input channels), tap by tap, four K-steps
@@ -1259,7 +1131,7 @@ __device__ __forceinline__ uint32_t prefetch_next(const ConvParams& p, int block
 }
 
 template <int STRIDE, int PG, int CW, int NW, int FR>
-__global__ __launch_bounds__(64 * NW, 2) void k_conv3x3_kw(ConvParams p) {
+__global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k_conv3x3_kw(ConvParams p) {
   constexpr int NS = NW / CW;
   constexpr int TH = 4 * PG, TW = 8;
   constexpr int IPH = STRIDE * TH + 3 - STRIDE, IPW = STRIDE * TW + 3 - STRIDE, NPIX = IPH * IPW;
@@ -1498,60 +1370,19 @@ KernelDesc describe(const ConvParams& p) {
   // 1-D grid, padded to a multiple of 8 so that every XCD owns tiles_per_xcd consecutive tiles
   const dim3 grid(8u * (unsigned)p.tiles_per_xcd);
   switch (p.variant) {
+    case CONV_DIRECT: {
+      const void* f = p.kc == 16 ? (p.kw_splits == 2 ? (const void*)k_conv_direct<1, 2> : (const void*)k_conv_direct<1, 1>)
+                                 : (p.kw_splits == 2 ? (const void*)k_conv_direct<2, 2> : (const void*)k_conv_direct<2, 1>);
+      return KernelDesc{f, grid, dim3(256), 0};
+    }
     case CONV_C64_WALK: return KernelDesc{(const void*)k_conv3x3_c64_walk, grid, dim3(256), 0};
     case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
     case CONV_DIRA: return KernelDesc{(const void*)k_conv3x3_dira, grid, dim3(256), 0};
     case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
     case CONV_KW:
       return KernelDesc{kw_kernel_of(p), grid, dim3(64u * (unsigned)(p.kw_splits * p.kw_cgroups)), 0};
-    default: break;
+    default: return KernelDesc{nullptr, grid, dim3(256), 0};
   }
-  const void* f = p.kc == 16   ? (const void*)k_conv_mfma<16, 4>
-                  : p.kc == 32 ? (const void*)k_conv_mfma<32, 4>
-                  : p.depth == 8 ? (const void*)k_conv_mfma<64, 8>
-                               : (const void*)k_conv_mfma<64, 4>;
-  return KernelDesc{f, grid, dim3(256), 0};
-}
-
-// ---------------------------------------------------------------------------------------------
-// Split-K epilogue: one thread per (pixel, 4 channels).
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_splitk_epilogue(SplitKEpilogueParams p) {
-  const int quads = p.cout >> 2;
-  const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (size_t)p.m * quads) return;
-  const int m = (int)(t / quads), n = (int)(t - (size_t)m * quads) * 4;
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sidx = 0; sidx < p.nsplit; ++sidx) {
-    const float4 v =
-        *reinterpret_cast<const float4*>(p.partial + ((size_t)sidx * p.m + m) * p.cout_pad + n);
-    a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-  }
-  float v[4] = {a.x, a.y, a.z, a.w};
-  if (p.res) {
-    const half4 r = *reinterpret_cast<const half4*>(p.res + (size_t)m * p.res_pitch + n);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += (float)r[j];
-  }
-  if (p.relu) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.0f);
-  }
-  if (p.out_f32) {
-    const int b = m / p.img_m, ml = m - b * p.img_m;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) p.out_f32[((size_t)b * p.cout + n + j) * p.img_m + ml] = v[j];
-  } else {
-    half4 o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = (f16)v[j];
-    *reinterpret_cast<half4*>(p.out + (size_t)m * p.out_pitch + n) = o;
-  }
-}
-
-KernelDesc describe(const SplitKEpilogueParams& p) {
-  const size_t n = (size_t)p.m * (p.cout >> 2);
-  return KernelDesc{(const void*)k_splitk_epilogue, dim3((unsigned)((n + 255) / 256)), dim3(256), 0};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1569,11 +1400,9 @@ __global__ __launch_bounds__(256) void k_lstm_epilogue(LstmEpilogueParams p) {
   const size_t t = (size_t)m * p.hid + j;
   const int n4 = 4 * p.hid;
   float g[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int sidx = 0; sidx < p.nsplit; ++sidx) {
-    const float* row = p.partial + ((size_t)sidx * p.m + m) * n4;
+  const float* row = p.partial + (size_t)m * n4;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) g[k] += row[k * p.hid + j];
-  }
+  for (int k = 0; k < 4; ++k) g[k] += row[k * p.hid + j];
   const float gi = sigmoid_f(g[0]), gf = sigmoid_f(g[1]), gg = tanhf(g[2]), go = sigmoid_f(g[3]);
   const float c_new = gf * p.c[t] + gi * gg;
   p.c[t] = c_new;
@@ -1762,33 +1591,27 @@ KernelDesc describe(const StemPoolParams& p) {
 }
 
 // =============================================================================================
-// Stage 3.  Per channel: maximum, its lowest index, presence -- one workgroup per tool channel;
+// Stage 3's channel maxima: maximum, its lowest index, presence -- one workgroup per tool channel;
 // every lane keeps (best value, lowest index), a wavefront butterfly, then one more across the 4
 // wavefronts through LDS.  The integer outputs are decided on the logits with exact comparisons.
-// Per cell (heat, mask, lowest set channel): in the kernel that computes the logits where that is
-// the ConvLSTM epilogue, else here.  Where nothing else waits for the maxima, their workgroups ride
-// along in the overlay's launch (k_overlay) instead of a launch of their own.
+// Where nothing else waits for the maxima, their workgroups ride along in the overlay's launch
+// (k_overlay) instead of a launch of their own.
 // =============================================================================================
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);
 }
 
 // Maximum of channel k of one image (logits L[0 .. n-1]) into the host-visible record; every thread of
-// a 256-thread workgroup.  CELLS: also the heat and mask values on the way.  marks: see PostParams.
-template <bool CELLS>
+// a 256-thread workgroup.  Thread 0 returns it in bv, bi.
 __device__ __forceinline__ void channel_maximum(const float* L, int n, float theta, int k, PostRecord* rec,
-                                                float* heat, uint8_t* mask, int* mk, const PostParams* p) {
+                                                float& bv, int& bi) {
   __shared__ float s_v[4];
   __shared__ int s_i[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float bv = -INFINITY;
-  int bi = 0x7fffffff;
+  bv = -INFINITY;
+  bi = 0x7fffffff;
   for (int i = tid; i < n; i += 256) {
     const float x = L[i];
-    if (CELLS) {
-      heat[i] = heat_of(x);
-      mask[i] = x > theta ? 1 : 0;
-    }
     if (better(x, i, bv, bi)) { bv = x; bi = i; }
   }
 #pragma unroll
@@ -1805,46 +1628,25 @@ __device__ __forceinline__ void channel_maximum(const float* L, int n, float the
     rec->argmax_idx[k] = bi;
     rec->peak[k] = heat_of(bv);
     rec->present[k] = bv > theta ? 1 : 0;
-    if (mk) {
-      // anchor of the annotation layer: centre of the argmax cell's footprint in the frame
-      if (bv > theta) {
-        const int ay = bi / p->wm, ax = bi - ay * p->wm;
-        mk[0] = ((2 * ax + 1) * p->wf) / (2 * p->wm);
-        mk[1] = ((2 * ay + 1) * p->hf) / (2 * p->hm);
-      } else {
-        mk[0] = -1;
-        mk[1] = -1;
-      }
-    }
   }
 }
 
 __global__ __launch_bounds__(256) void k_postprocess(PostParams p) {
-  const int k = blockIdx.x, tid = threadIdx.x;
-  const size_t img_off = (size_t)blockIdx.y * 8 * p.n;   // image blockIdx.y of the batch
-  if (k == 8) {
-    // ninth workgroup: per cell the lowest channel whose mask is set (what the overlay draws),
-    // decided on the logits with the same comparison as the masks
-    for (int i = tid; i < p.n; i += 256) {
-      uint8_t lowest = 0xff;
-#pragma unroll
-      for (int c = 7; c >= 0; --c)
-        if (p.logits[img_off + (size_t)c * p.n + i] > p.theta) lowest = (uint8_t)c;
-      p.kmap[(size_t)blockIdx.y * p.n + i] = lowest;
-    }
-    return;
+  const int k = blockIdx.x, img = blockIdx.y;
+  float bv;
+  int bi;
+  channel_maximum(p.logits + ((size_t)img * 8 + k) * p.n, p.n, p.theta, k, p.rec + img, bv, bi);
+  if (threadIdx.x == 0 && p.marks) {
+    // anchor of the annotation layer: centre of the argmax cell's footprint in the frame
+    int* const mk = p.marks + ((size_t)img * 8 + k) * 2;
+    const int ay = bi / p.wm, ax = bi - ay * p.wm;
+    mk[0] = bv > p.theta ? ((2 * ax + 1) * p.wf) / (2 * p.wm) : -1;
+    mk[1] = bv > p.theta ? ((2 * ay + 1) * p.hf) / (2 * p.hm) : -1;
   }
-  const size_t ch_off = img_off + (size_t)k * p.n;
-  int* const mk = p.marks ? p.marks + ((size_t)blockIdx.y * 8 + k) * 2 : nullptr;
-  if (p.heat)
-    channel_maximum<true>(p.logits + ch_off, p.n, p.theta, k, p.rec + blockIdx.y, p.heat + ch_off,
-                          p.mask + ch_off, mk, &p);
-  else
-    channel_maximum<false>(p.logits + ch_off, p.n, p.theta, k, p.rec + blockIdx.y, nullptr, nullptr, mk, &p);
 }
 
 KernelDesc describe(const PostParams& p) {
-  return KernelDesc{(const void*)k_postprocess, dim3(p.heat ? 9 : 8, p.batch), dim3(256), 0};
+  return KernelDesc{(const void*)k_postprocess, dim3(8, p.batch), dim3(256), 0};
 }
 
 // =============================================================================================
@@ -2037,9 +1839,9 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   if ((int)blockIdx.x < p.n_max) {                               // eight workgroups per layer
     const OverlayLayer& L = p.layer[LAYERS ? blockIdx.x >> 3 : 0];
     const int k = (int)(blockIdx.x & 7u), n = L.wm * L.hm;
-    if (L.rec)
-      channel_maximum<false>(L.logits + ((size_t)by * 8 + k) * n, n, L.theta, k, L.rec + by, nullptr, nullptr,
-                             nullptr, nullptr);
+    float bv;
+    int bi;
+    if (L.rec) channel_maximum(L.logits + ((size_t)by * 8 + k) * n, n, L.theta, k, L.rec + by, bv, bi);
     return;
   }
   const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;          // groups per row, of the frame

@@ -45,16 +45,15 @@ static inline uint64_t now_ns() {
   } while (0)
 
 // ---- kernel families (for timing) ----------------------------------------------------------
-enum Family { F_RESIZE, F_CONV, F_SPLITK, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_COUNT };
-static const char* kFamilyName[F_COUNT] = {"resize_norm", "conv_mfma", "splitk_epilogue",
-                                           "lstm_head", "stem_pool_mfma", "postprocess", "overlay"};
+enum Family { F_RESIZE, F_CONV, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_COUNT };
+static const char* kFamilyName[F_COUNT] = {"resize_norm", "conv_mfma", "lstm_head",
+                                           "stem_pool_mfma", "postprocess", "overlay"};
 
 struct Op {
   Family fam;
   double flops = 0, bytes = 0;
   ResizeParams resize;
   ConvParams conv;
-  SplitKEpilogueParams splitk;
   LstmEpilogueParams lstm;
   StemPoolParams stem;
   PostParams post;
@@ -65,7 +64,6 @@ static KernelDesc op_desc(const Op& op) {
   switch (op.fam) {
     case F_RESIZE: return describe(op.resize);
     case F_CONV: return describe(op.conv);
-    case F_SPLITK: return describe(op.splitk);
     case F_LSTM: return describe(op.lstm);
     case F_STEM: return describe(op.stem);
     case F_POST: return describe(op.post);
@@ -77,7 +75,6 @@ static void* op_params(Op& op) {
   switch (op.fam) {
     case F_RESIZE: return &op.resize;
     case F_CONV: return &op.conv;
-    case F_SPLITK: return &op.splitk;
     case F_LSTM: return &op.lstm;
     case F_STEM: return &op.stem;
     case F_POST: return &op.post;
@@ -124,7 +121,8 @@ struct Slot {
   std::vector<Op> infer;   // stage 2: the network over the whole batch
   std::vector<Op> infer_static;   // the same with the split-K scratch in the library's fixed
                                   // device array (empty when the scratch needed exceeds it)
-  std::vector<Op> post;    // stage 3
+  std::vector<Op> post;    // stage 3: the channel maxima
+  bool maxima_with_overlay = false;   // they may ride in the overlay's launch instead
   std::vector<Op> overlay; // stage 4: one launch, blockIdx.y = stream of the batch
   hipEvent_t ev_pre = nullptr, ev_infer = nullptr, ev_post = nullptr, ev_overlay = nullptr;
   // the event behind stage 3 (ev_infer where stage 3 has no launch of its own)
@@ -306,6 +304,20 @@ static void pack_frag(const f16* w, int cout, int cin, int taps, int g, f16* dst
     }
 }
 
+// A layer of the small network in fragment order: dst[(q*ksteps + ks)*64 + lane][j] = weight of
+// channel r (zero from cout on) at k = 16*ks + 8*h + j of chunk q, lane = r + 32*h.  `rows`: the packed
+// rows [cout][nchunks * kc].
+static void pack_direct(const f16* rows, int cout, int nchunks, int kc, f16* dst) {
+  for (int q = 0; q < nchunks; ++q)
+    for (int ks = 0; ks < kc / 16; ++ks)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int r = lane & 31, h = lane >> 5;
+        f16* out = dst + ((size_t)(q * (kc / 16) + ks) * 64 + lane) * 8;
+        for (int j = 0; j < 8; ++j)
+          out[j] = r < cout ? rows[(size_t)r * nchunks * kc + (size_t)q * kc + 16 * ks + 8 * h + j] : (f16)0.0f;
+      }
+}
+
 // First layer on the padded 4-channel image: one chunk per kernel row, covering chunk_px
 // adjacent pixels of 4 channels; packed[n][ky][px][ch] = w[n][ch][ky][px] (px < k, ch < 3).
 static void pack_rowtap(const f16* w, int cout, int k, int chunk_px, int cout_pad, f16* dst) {
@@ -436,9 +448,7 @@ struct Builder {
     // the shared-patch kernels address the input with 32-bit offsets (in halves)
     const bool fits32 = (double)c.batch * c.hin * c.win * c.cin_pitch < 2147483648.0;
     const bool s3x3 = c.ntaps == 9 && c.kw == 3 && c.pad == 1 && c.kc == 64 && c.cout % 128 == 0 && fits32;
-    c.nsplit = 1;
     c.tiles_per_wg = 1;
-    c.depth = 4;
     // workgroups of a CONV_KW grid
     auto wgs = [&](int cw, int pg) {
       return c.batch * ((c.hout + 4 * pg - 1) / (4 * pg)) * ((c.wout + 7) / 8) * (c.cout / (32 * cw));
@@ -512,25 +522,25 @@ struct Builder {
       c.tiles_m = tiles(16);
       c.tiles_n = 1;
       c.tiles_per_wg = (c.tiles_m + 511) / 512;
-    } else {
-      c.variant = CONV_GENERIC;
-      c.tiles_x = 0;
-      c.tiles_m = (c.m + 63) / 64;
-      c.tiles_n = c.cout_pad / 64;
-      const int n = c.tiles_m * c.tiles_n;
-      int ns = 1;
-      if (n < 192) ns = std::max(1, std::min((320 + n - 1) / n, c.nchunks / 4));
+    } else if (c.cout <= 32 && c.kc <= 32 && c.chunks_per_tap == 1 && c.ntaps <= 9) {
+      // two K splits, of at most five taps each, while tiles of 64 pixels would be fewer than 192
+      c.variant = CONV_DIRECT;
+      const int ns = (c.m + 63) / 64 < 192 && c.nchunks >= 8 ? 2 : 1;
+      c.kw_splits = ns;
       c.chunks_per_split = (c.nchunks + ns - 1) / ns;
-      c.nsplit = (c.nchunks + c.chunks_per_split - 1) / c.chunks_per_split;
-      if (c.kc == 64 && c.chunks_per_split >= 12) c.depth = 8;
+      c.tiles_x = 0;
+      c.tiles_m = ((c.m + 31) / 32 + 4 / ns - 1) / (4 / ns);
+      c.tiles_n = 1;
+    } else {
+      throw std::logic_error("no convolution kernel for a layer of this network");
     }
     const int groups_m = (c.tiles_m + c.tiles_per_wg - 1) / c.tiles_per_wg;
-    c.tiles_per_xcd = (groups_m * c.tiles_n * c.nsplit + 7) / 8;
+    c.tiles_per_xcd = (groups_m * c.tiles_n + 7) / 8;
     // Tile order: every XCD (own L2) takes a run of tiles_per_xcd consecutive tiles.  For every
     // block size, count what the eight L2s fetch (each its own spatial groups' input slices and
     // its own channel tiles' weight slices, once) and keep the cheapest.
     c.n_block = 1;
-    if (c.variant != CONV_GENERIC && c.tiles_n > 1) {
+    if (c.tiles_n > 1) {
       const double in_unit = 2.0 * c.batch * c.hin * c.win * (c.chunks_per_tap * 64.0) / (double)groups_m;
       const double w_unit = 2.0 * c.cout_pad * c.ktot / (double)c.tiles_n;
       const int total = groups_m * c.tiles_n;
@@ -555,7 +565,7 @@ struct Builder {
     }
   }
 
-  // Appends the convolution and, when it is split along K, its reduction kernel.
+  // Appends the convolution.
   // keep_partial: leave the partial sums in the scratch buffer for a later kernel (ConvLSTM).
   // Returns the index of the convolution op.
   // wf_off: the weights' offset in fragment order, for the variants that read them so (w_off then
@@ -571,15 +581,14 @@ struct Builder {
     auto at = [&](size_t off) { return d_w && off != kNoWeights ? d_w + off : nullptr; };
     c.wt = at(w_off); c.wt_frag = at(wf_off); c.wt2 = nullptr; c.wt2_frag = at(wf2_off);
     choose_split(c);
-    const bool partial = c.nsplit > 1 || keep_partial;
-    c.use_partial = partial ? 1 : 0;
+    c.use_partial = keep_partial ? 1 : 0;
     c.partial = nullptr;   // patched when the scratch buffer is carved
     c.out = nullptr; c.out_pitch = 0; c.res = nullptr; c.res_pitch = 0; c.relu = 0;
-    c.out_f32 = nullptr;
+    c.out_f32 = nullptr;   // the slot's, for the layer that writes the logits
     c.out2 = nullptr; c.out2_pitch = 0;
     if (out2) { c.out2 = out2->p; c.out2_pitch = out2->pitch; }
-    if (partial) {
-      partial_floats = std::max(partial_floats, (size_t)c.nsplit * c.m * c.cout_pad);
+    if (keep_partial) {
+      partial_floats = std::max(partial_floats, (size_t)c.m * c.cout_pad);
     } else {
       if (out) { c.out = out->p; c.out_pitch = out->pitch; }
       if (res) { c.res = res->p; c.res_pitch = res->pitch; }
@@ -587,24 +596,8 @@ struct Builder {
     }
     op.conv = c;
     ops.push_back(op);
-    const int conv_idx = (int)ops.size() - 1;
-    if (want_f32 && !partial) logits_op = conv_idx;
-    if (partial && !keep_partial) {
-      Op e;
-      e.fam = F_SPLITK;
-      e.bytes = (double)c.nsplit * c.m * c.cout * 4.0 + (double)c.m * c.cout * 2.0;
-      SplitKEpilogueParams& s = e.splitk;
-      s.partial = nullptr;
-      s.nsplit = c.nsplit; s.m = c.m; s.cout = c.cout; s.cout_pad = c.cout_pad;
-      s.out = out ? out->p : nullptr; s.out_pitch = out ? out->pitch : 0;
-      s.res = res ? res->p : nullptr; s.res_pitch = res ? res->pitch : 0;
-      s.relu = relu ? 1 : 0;
-      s.out_f32 = nullptr;
-      s.img_m = c.img_m;
-      ops.push_back(e);
-      if (want_f32) logits_op = (int)ops.size() - 1;
-    }
-    return conv_idx;
+    if (want_f32) logits_op = (int)ops.size() - 1;
+    return (int)ops.size() - 1;
   }
 
   // Generic convolution on a pixel-major tensor; weights are the next cout*cin*k*k floats of the
@@ -633,7 +626,15 @@ struct Builder {
     const bool frag = probe.variant == CONV_DIRA || probe.variant == CONV_S2_DIRA || probe.variant == CONV_KW;
     size_t w_off = kNoWeights, wf_off = kNoWeights, wf2_off = kNoWeights;
     const size_t n_w = (size_t)g.cout_pad * g.ktot;
-    if (frag) {
+    if (probe.variant == CONV_DIRECT) {
+      wf_off = reserve_w((size_t)32 * g.ktot);
+      if (pack)
+        pack_tasks.push_back([=] {
+          std::vector<f16> rows((size_t)cout * g.ktot);
+          pack_generic(half_blob.data() + blob_at, cout, cin, k * k, 0, cout, rows.data());
+          pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
+        });
+    } else if (frag) {
       wf_off = reserve_w(n_w);
       pack_frag_at(blob_at, cout, cin, 9, g.cout_pad, wf_off);
     } else {
@@ -679,8 +680,7 @@ struct Builder {
     g.variant = CONV_BLOCK64;
     g.tiles_x = (g.wout + 15) / 16;
     g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
-    g.tiles_n = 1; g.nsplit = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
-    g.depth = 4;
+    g.tiles_n = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
     g.tiles_per_xcd = (g.tiles_m + 7) / 8;
     g.wt = d_w ? d_w + wa_off : nullptr;
     g.wt2 = d_w ? d_w + wb_off : nullptr;
@@ -708,14 +708,16 @@ struct Builder {
     g.kc = chunk_px * 4;
     g.ntaps = k; g.kw = 1; g.chunks_per_tap = 1; g.nchunks = k; g.ktot = k * g.kc;
     g.stride = 2; g.pad = 0;
-    const size_t w_off = reserve_w((size_t)g.cout_pad * g.ktot);
+    const size_t wf_off = reserve_w((size_t)32 * g.ktot);
     if (pack)
       pack_tasks.push_back([=] {
-        pack_rowtap(half_blob.data() + blob_at, cout, k, chunk_px, g.cout_pad, host_w.data() + w_off);
+        std::vector<f16> rows((size_t)cout * g.ktot);
+        pack_rowtap(half_blob.data() + blob_at, cout, k, chunk_px, cout, rows.data());
+        pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
       });
     out->h = g.hout; out->w = g.wout; out->c = cout;
-    first_conv_op =
-        add_conv(g, w_off, nullptr, out, true, false, false, 2.0 * g.m * (double)cout * 3 * k * k);
+    first_conv_op = add_conv(g, kNoWeights, nullptr, out, true, false, false,
+                             2.0 * g.m * (double)cout * 3 * k * k, wf_off);
   }
 
   void walk_tiny(int ph, int pw) {
@@ -827,11 +829,11 @@ struct Builder {
     {
       Op op;
       op.fam = F_LSTM;
-      op.lstm = LstmEpilogueParams{nullptr, ops[lstm_conv].conv.nsplit, mf, 256, cstate,
+      op.lstm = LstmEpilogueParams{nullptr, mf, 256, cstate,
                                    concat ? concat + 512 : nullptr, 768,
                                    d_w ? d_w + w_off : nullptr, nullptr, hf * wf, 0.0f, nullptr, nullptr,
                                    nullptr};
-      op.bytes = (double)ops[lstm_conv].conv.nsplit * mf * 1024 * 4.0 + (double)mf * 256 * 10.0;
+      op.bytes = (double)mf * 1024 * 4.0 + (double)mf * 256 * 10.0;
       op.flops = 2.0 * mf * 8 * 256;
       ops.push_back(op);
       logits_op = (int)ops.size() - 1;
@@ -951,7 +953,6 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     bb.d_partial = d_partial;
     for (Op& op : bb.ops) {
       if (op.fam == F_CONV && op.conv.use_partial) op.conv.partial = d_partial;
-      if (op.fam == F_SPLITK) op.splitk.partial = d_partial;
       if (op.fam == F_LSTM) op.lstm.partial = d_partial;
     }
   };
@@ -1086,17 +1087,13 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     if (s.infer[b.first_conv_op].fam == F_STEM) s.infer[b.first_conv_op].stem.in = s.d_netin;
     else s.infer[b.first_conv_op].conv.in = s.d_netin;
     Op& lo = s.infer[b.logits_op];
-    if (lo.fam == F_CONV) lo.conv.out_f32 = s.d_logits;
-    else if (lo.fam == F_SPLITK) lo.splitk.out_f32 = s.d_logits;
-    else {
-      lo.lstm.logits = s.d_logits;
-      lo.lstm.theta = (float)theta_d;
+    if (lo.fam == F_CONV) {
+      lo.conv.out_f32 = s.d_logits; lo.conv.theta = (float)theta_d;
+      lo.conv.heat = s.d_heat; lo.conv.mask = s.d_mask; lo.conv.kmap = sb[i].kmap;
+    } else {
+      lo.lstm.logits = s.d_logits; lo.lstm.theta = (float)theta_d;
       lo.lstm.heat = s.d_heat; lo.lstm.mask = s.d_mask; lo.lstm.kmap = sb[i].kmap;
     }
-    // Stage 3 behind the ConvLSTM epilogue is the channel maxima alone.  Only the annotation layer
-    // waits for them; without it they are found in the overlay's launch (one launch, 4 us, less).
-    const bool cells_done = lo.fam == F_LSTM;
-    const bool maxima_with_overlay = cells_done && !d->annotate;
     app->partial_bytes = b.partial_floats * sizeof(float);
     if (app->partial_bytes <= app->ctx->static_scratch_bytes && app->ctx->d_static_scratch) {
       // the same launches with every split-K pointer moved from the lane's scratch in the
@@ -1109,18 +1106,20 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       s.infer_static = s.infer;
       for (Op& op : s.infer_static) {
         if (op.fam == F_CONV) move(op.conv.partial);
-        if (op.fam == F_SPLITK) move(op.splitk.partial);
         if (op.fam == F_LSTM) move(op.lstm.partial);
       }
     }
-    if (!maxima_with_overlay) {
+    {
+      // Stage 3 behind the kernel that writes the logits (and, with them, the per-cell outputs) is the
+      // channel maxima alone.  Only the annotation layer waits for them; without it they are found
+      // in the overlay's launch, one launch (4 us) less, unless the kernels are being timed.
       Op p;
       p.fam = F_POST;
-      p.post = PostParams{s.d_logits, (int)n_map, (float)theta_d, cells_done ? nullptr : s.d_heat,
-                          cells_done ? nullptr : s.d_mask, s.rec, B,
-                          sb[i].kmap, sb[i].marks, mw, mh, d->frame_w, d->frame_h};
-      p.bytes = B * 8.0 * n_map * (4 + (cells_done ? 0 : 4 + 1));
+      p.post = PostParams{s.d_logits, (int)n_map, (float)theta_d, s.rec, B, sb[i].marks, mw, mh,
+                          d->frame_w, d->frame_h};
+      p.bytes = B * 8.0 * n_map * 4;
       s.post.push_back(p);
+      s.maxima_with_overlay = !d->annotate;
     }
     {
       Op o;
@@ -1134,10 +1133,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       op.n_layers = 1;
       OverlayLayer& L = op.layer[0];
       L.kmap = sb[i].kmap; L.wm = mw; L.hm = mh;
-      if (maxima_with_overlay) {
-        L.logits = s.d_logits; L.rec = s.rec; L.theta = (float)theta_d;
-        op.n_max = 8;
-      }
+      L.logits = s.d_logits; L.theta = (float)theta_d;   // rec and n_max: per frame
       L.rcp_wm = 1.0f / (float)mw;
       L.a = a_q8;
       L.marks = sb[i].marks;
@@ -1354,7 +1350,8 @@ static hs_status build_slot_graph(Slot& s, hipEvent_t wait_ev) {
     HS_HIP(add_kernel(s.infer[j], nullptr));
   }
   HS_HIP(add_event(s.ev_infer));
-  for (Op& op : s.post) HS_HIP(add_kernel(op, nullptr));
+  if (!s.maxima_with_overlay)
+    for (Op& op : s.post) HS_HIP(add_kernel(op, nullptr));
   HS_HIP(hipGraphInstantiate(&s.graph_exec, s.graph, nullptr, nullptr, 0));
   return HS_OK;
 }
@@ -1801,6 +1798,10 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   // activation buffers).
   app->last_stream = idle ? app->home_lane : (app->last_stream + 1) % app->lanes;
   hipStream_t lane_stream = app->s_lane[app->last_stream];
+  const bool graph = app->launch_mode == HS_LAUNCH_GRAPH && !app->timing && !static_scratch;
+  const bool maxima_here = s->maxima_with_overlay && !app->timing;
+  s->overlay[0].overlay.layer[0].rec = maxima_here ? s->rec : nullptr;
+  s->overlay[0].overlay.n_max = maxima_here ? 8 : 0;
   if (!idle && app->lane_last_stream[s->lane] && app->lane_last_stream[s->lane] != lane_stream &&
       app->depth >= app->lanes) {
     Slot& same_lane =
@@ -1810,7 +1811,6 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   app->lane_last_stream[s->lane] = lane_stream;
   // the caller's producer (another stream) may still be writing the frames
   if (frames_ready) HS_HIP(hipStreamWaitEvent(lane_stream, frames_ready, 0));
-  const bool graph = app->launch_mode == HS_LAUNCH_GRAPH && !app->timing && !static_scratch;
   if (graph) {
     void* args[1];
     hipKernelNodeParams kp = node_params(s->pre[0], args);
@@ -1830,11 +1830,11 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
       st = run_ops(app, infer, lane_stream, s->ev_infer);
     }
     if (st != HS_OK) return st;
-    if (!s->post.empty()) st = run_ops(app, s->post, lane_stream, s->ev_post);
+    if (!maxima_here) st = run_ops(app, s->post, lane_stream, s->ev_post);
     if (st != HS_OK) return st;
   }
   if (graph) HS_HIP(hipEventRecord(s->ev_post, lane_stream));
-  s->ev_stage3 = !graph && s->post.empty() ? s->ev_infer : s->ev_post;
+  s->ev_stage3 = !graph && maxima_here ? s->ev_infer : s->ev_post;
   s->ev_done = s->ev_overlay;
   if (!own_overlay) {
     *slot_out = s;

@@ -1,7 +1,7 @@
-"""The convolution kernels of small and middle grids (k_conv3x3_kw): every instantiation the host's
-rules choose, at maps smaller than one tile, one tile plus a remainder, and several ragged
-tiles, against the CPU oracle.  The recurrent cell is checked alone on the GPU's own inputs."""
-import numpy as np
+"""The convolution kernels of small and middle grids: every instantiation of k_conv3x3_kw the
+host's rules choose, at maps smaller than one tile, one tile plus a remainder, and several ragged
+tiles, and k_conv_direct (the small network), against the CPU oracle.  The recurrent cell is checked
+alone on the GPU's own inputs."""
 import pytest
 
 import oracle
@@ -51,6 +51,33 @@ def test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch):
                 assert max(rel_err(h, oh), rel_err(c, oc), rel_err(g["logits"], head)) <= TOL_CELL
                 assert rms_rel(h, o["h"]) <= TOL_STATE_RMS and rms_rel(c, o["c"]) <= TOL_STATE_RMS
                 prev[j] = (h, c)
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("nw,nh,batch", [
+    (8, 8, 1),        # a 2 x 2 map: one pixel tile, mostly beyond the layer's end
+    (33, 17, 3),      # ragged maps, images that end inside a pixel tile, two K splits
+    (250, 190, 5),    # first layers without a split, the last ones at the line between one and two
+])
+def test_small_network_layers_match_the_oracle(hs, nw, nh, batch):
+    from paper_2402_04466_amd.harness import AppStream
+    fw, fh = 64, 48
+    blob = si.he_normal_blob(si.TINY4_LAYERS, 9)
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=fw, frame_h=fh, net_w=nw, net_h=nh, blob=blob,
+                  palette=si.DEFAULT_PALETTE, queue_depth=2, batch=batch)
+    try:
+        host = [si.uniform_frames(1, fh, fw, 90 + j)[0] for j in range(batch)]
+        print(f"[small-network] {nw}x{nh} batch {batch}", flush=True)
+        d_in, d_out = [s.upload_frame(f) for f in host], [s.new_output() for _ in host]
+        assert s.submit_batch(d_in, d_out, 0) == hs.HS_OK
+        for j, r in enumerate(s.wait_batch()):
+            o32, o16 = make_oracles("tiny4", blob, nw, nh, True, si.DEFAULT_PALETTE)
+            check_frame(s.fetch(r, d_out[j]), host[j], o32.process(host[j]), o16.process(host[j]),
+                        threshold=0.5, alpha=0.5, palette=si.DEFAULT_PALETTE, fp32_input=False,
+                        tag=f"small-network/{nw}x{nh}/stream{j}")
     finally:
         s.close()
         hs.hs_shutdown(ctx)
