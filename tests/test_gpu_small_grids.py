@@ -2,6 +2,7 @@
 host's rules choose, at maps smaller than one tile, one tile plus a remainder, and several ragged
 tiles, and k_conv_direct (the small network), against the CPU oracle.  The recurrent cell is checked
 alone on the GPU's own inputs."""
+import numpy as np
 import pytest
 
 import oracle
