@@ -49,11 +49,9 @@ KernelDesc describe(const ResizeParams& p);
 enum ConvVariant {
   CONV_DIRECT,    // <= 32 output channels, one chunk of 16 or 32 halves per tap, <= 9 taps: no LDS tiles,
                   // K splits inside the workgroup (k_conv_direct); wt_frag: [chunk][K-step][lane][8]
-  CONV_C64_WALK,  // 3x3/1 layers with 64 input channels on large grids: tile 8 x 16, resident weights,
-                  // a workgroup walks tiles_per_wg tiles (k_conv3x3_c64_walk)
   CONV_BLOCK64,   // a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU between,
-                  // shortcut from the input, ReLU) in one launch (k_block64_fused): wt = first,
-                  // wt2 = second convolution, res = in
+                  // shortcut from the input, ReLU) in one launch (k_block64_fused): wt_frag = first,
+                  // wt2_frag = second convolution, res = in
   CONV_DIRA,      // 3x3/1 layers with >= 2 Cin chunks: tile 8 x 16 pixels x 64 channels, weights read
                   // as MFMA fragments straight from wt_frag (k_conv3x3_dira)
   CONV_S2_DIRA,   // 3x3/2 layers (+ fused 1x1/2 projection) on large grids: tile 8 x 8 x 128, weights
@@ -63,9 +61,7 @@ enum ConvVariant {
 };
 struct ConvParams {
   const f16* in;
-  const f16* wt;        // packed [cout_pad][ktot], ktot = nchunks*KC, zero rows above cout
-  const f16* wt_frag;   // the same weights in MFMA fragment order (the variants that read it have no
-                        // wt): [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
+  const f16* wt_frag;   // weights in MFMA fragment order: [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
                         // r + 32 h holding k = 16 * step + 8 * h .. + 7 of channel 32 * group + r
   int hin, win, cin_pitch;
   int hout, wout, m;    // m = batch*hout*wout output pixels (images stacked along m)
@@ -96,9 +92,8 @@ struct ConvParams {
   float* out_f32;       // if set: the logits, planar fp32 out_f32[(image*8 + n)*img_m + pixel], instead of
                         // `out`; with them stage 3's per-cell outputs (see PostParams)
   float theta; float* heat; uint8_t* mask; uint8_t* kmap;
-  const f16* wt2;       // CONV_BLOCK64: second convolution
-  // stride 2: fused 1x1 stride-2 projection of the same input (no residual, no ReLU), or NULL:
-  // [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
+  // CONV_BLOCK64: the second convolution's weights.  Stride 2: fused 1x1 stride-2 projection of the
+  // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
   const f16* wt2_frag;
   f16* out2; int out2_pitch;
   // weights of the layer that runs next, for the kernels that prefetch them: 128-byte lines (0: none)

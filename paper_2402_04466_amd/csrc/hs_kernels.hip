@@ -363,179 +363,31 @@ __global__ __launch_bounds__(256) void k_conv_direct(ConvParams p) {
 // =============================================================================================
 
 // =============================================================================================
-// 3x3 stride-1 layers with 64 input channels (one Cin chunk) on grids several times the device:
-// the nine weight tiles of a workgroup's channel tile never change while it walks its spatial
-// tiles, so they are made resident once -- taps 0..2 in LDS, taps 3..8 as MFMA fragments in
-// registers (all nine in LDS would leave one workgroup per CU, all nine in registers none of
-// the registers).  A tile then costs one patch hand-over (two barriers) and 72 MFMAs per
-// wavefront with no weight traffic and no barrier between the taps.
-// =============================================================================================
-__global__ __launch_bounds__(256, 2) void k_conv3x3_c64_walk(ConvParams p) {
-  constexpr int TH = 8, TW = 16, IPH = TH + 2, IPW = TW + 2, NPIX = IPH * IPW;
-  constexpr int PITCH = 64 + 8;
-  constexpr int RP = (IPW * PITCH * 2 + ((128 - (IPW * PITCH * 2) % 256 + 256) % 256)) / 2;
-  static_assert((RP * 2) % 256 == 128, "plane row pitch must be 128 mod 256 bytes");
-  constexpr int PV = NPIX * 8, PL = (PV + 255) / 256;
-  constexpr int LT = 3;                       // taps whose weights stay in LDS (the rest: registers)
-  constexpr int WT = 64 * PITCH;              // halves of one weight tile in LDS
-  static_assert(IPH * RP >= 2 * WT, "the patch buffer stages two weight tiles in the prologue");
-  __shared__ __align__(16) f16 s_patch[IPH * RP];
-  __shared__ __align__(16) f16 s_wk[LT * WT];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  const int groups_m = (p.tiles_m + p.tiles_per_wg - 1) / p.tiles_per_wg;
-  if (tile >= groups_m * p.tiles_n) return;
-  const int blk = groups_m * p.n_block, in_blk = tile % blk;       // tile order: see above
-  const int tm_begin = (in_blk / p.n_block) * p.tiles_per_wg;
-  const int tm_end = min(p.tiles_m, tm_begin + p.tiles_per_wg);
-  const int n0 = ((tile / blk) * p.n_block + in_blk % p.n_block) * 64;
-  const int tiles_img = p.tiles_m / p.batch;
-  const int wm = wave & 1, wn = wave >> 1;
-  const int fw_off = (wn * 32 + r) * PITCH + h * 8;
-  const int fp_off = (4 * wm + (r >> 3)) * RP + (r & 7) * PITCH + h * 8;
-
-  // ---- patch loader: LDS slot and pixel of every vector are fixed, the source depends on the tile
-  int l_plds[PL], l_pyx[PL];
-#pragma unroll
-  for (int i = 0; i < PL; ++i) {
-    const int v = tid + 256 * i;
-    const int pix = min(v >> 3, NPIX - 1), py = pix / IPW, px = pix - py * IPW;
-    l_pyx[i] = py | (px << 8);
-    l_plds[i] = v >= PV ? -1 : py * RP + px * PITCH + (v & 7) * 8;
-  }
-  u32x4 st_p[PL];
-  uint32_t st_inb = 0;          // bit i: vector i of the fetched patch lies inside the image
-  int f_img = 0, f_y0 = 0, f_x0 = 0;   // image and origin of the tile whose patch is in st_p
-#define HS_FETCH_PATCH(TM_)                                                                    \
-  {                                                                                            \
-    f_img = (TM_) / tiles_img;                                                                 \
-    const int ts_ = (TM_) - f_img * tiles_img, ty_ = ts_ / p.tiles_x;                          \
-    f_y0 = ty_ * TH;                                                                           \
-    f_x0 = (ts_ - ty_ * p.tiles_x) * TW;                                                       \
-    st_inb = 0;                                                                                \
-    _Pragma("unroll") for (int i = 0; i < PL; ++i) {                                           \
-      const int iy_ = f_y0 + (l_pyx[i] & 0xff) - 1, ix_ = f_x0 + (l_pyx[i] >> 8) - 1;          \
-      const bool in_ = l_plds[i] >= 0 && iy_ >= 0 && iy_ < p.hin && ix_ >= 0 && ix_ < p.win;   \
-      st_inb |= (in_ ? 1u : 0u) << i;                                                          \
-      const int off_ = in_ ? ((f_img * p.hin + iy_) * p.win + ix_) * p.cin_pitch + (tid & 7) * 8 : 0; \
-      st_p[i] = *reinterpret_cast<const u32x4*>(p.in + off_);                                  \
-    }                                                                                          \
-  }
-  HS_FETCH_PATCH(tm_begin)
-
-  // ---- weights: taps 0..2 into their LDS tiles; taps 3..8, two at a time, through the (still
-  // unused) patch buffer into fragment registers
-  half8 a_keep[9 - LT][4];
-  {
-    const int row0 = tid >> 3, kv = tid & 7;        // this thread's vectors: rows row0, row0 + 32
-    const f16* w0 = p.wt + (size_t)(n0 + row0) * p.ktot + kv * 8;
-    const f16* w1 = w0 + (size_t)32 * p.ktot;
-    const int l0 = row0 * PITCH + kv * 8, l1 = l0 + 32 * PITCH;
-    u32x4 sw[9][2];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      sw[t][0] = *reinterpret_cast<const u32x4*>(w0 + t * 64);
-      sw[t][1] = *reinterpret_cast<const u32x4*>(w1 + t * 64);
-    }
-#pragma unroll
-    for (int t = 0; t < LT; ++t) {
-      *reinterpret_cast<u32x4*>(&s_wk[t * WT + l0]) = sw[t][0];
-      *reinterpret_cast<u32x4*>(&s_wk[t * WT + l1]) = sw[t][1];
-    }
-#pragma unroll
-    for (int pair = 0; pair < (9 - LT) / 2; ++pair) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        *reinterpret_cast<u32x4*>(&s_patch[j * WT + l0]) = sw[LT + 2 * pair + j][0];
-        *reinterpret_cast<u32x4*>(&s_patch[j * WT + l1]) = sw[LT + 2 * pair + j][1];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          a_keep[2 * pair + j][ks] =
-              *reinterpret_cast<const half8*>(&s_patch[j * WT + fw_off + ks * 16]);
-      __syncthreads();
-    }
-  }
-
-  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int tm = tm_begin; tm < tm_end; ++tm) {
-    const int img = f_img, y0 = f_y0, x0 = f_x0;
-    if (tm != tm_begin) __syncthreads();      // every wavefront is done with the previous patch
-#pragma unroll
-    for (int i = 0; i < PL; ++i) {
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      if (l_plds[i] >= 0)
-        *reinterpret_cast<u32x4*>(&s_patch[l_plds[i]]) = ((st_inb >> i) & 1u) ? st_p[i] : zero;
-    }
-    __syncthreads();
-    if (tm + 1 < tm_end) HS_FETCH_PATCH(tm + 1)
-    // residual of this tile: fetched now, used after the MFMAs (clamped addresses, unconditional)
-    const int oy = y0 + 4 * wm + (r >> 3);
-    u32x4 res_raw[2][2];      // two 16-byte pieces per pixel (res_octets_to_quads)
-    if (p.res) {
-      const int oy_c = min(oy, p.hout - 1);
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const int ox_c = min(x0 + 8 * g + (r & 7), p.wout - 1);
-        const f16* rp = p.res + (size_t)(img * p.img_m + oy_c * p.wout + ox_c) * p.res_pitch +
-                        n0 + wn * 32 + h * 8;
-        res_raw[g][0] = *reinterpret_cast<const u32x4*>(rp);
-        res_raw[g][1] = *reinterpret_cast<const u32x4*>(rp + 16);
-      }
-    }
-
-    floatx16 acc[2] = {zero16, zero16};
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const f16* fp = &s_patch[fp_off + (tap / 3) * RP + (tap % 3) * PITCH];
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const half8 a = tap < LT ? *reinterpret_cast<const half8*>(&s_wk[tap * WT + fw_off + ks * 16])
-                                 : a_keep[tap < LT ? 0 : tap - LT][ks];
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          const half8 b = *reinterpret_cast<const half8*>(fp + g * 8 * PITCH + ks * 16);
-          acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc[g], 0, 0, 0);
-        }
-      }
-    }
-
-    // fp16 output with a multiple of 64 channels (the host selects this kernel only then)
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const int ox = x0 + 8 * g + (r & 7);
-      half4 res_q[4] = {};
-      if (p.res) res_octets_to_quads(res_raw[g], res_q);
-      store_octets(p, oy < p.hout && ox < p.wout, img * p.img_m + oy * p.wout + ox, n0 + wn * 32, h,
-                   acc[g], res_q, p.res != nullptr);
-    }
-  }
-#undef HS_FETCH_PATCH
-}
-
-// =============================================================================================
 // A whole 64-channel BasicBlock in one launch: out = ReLU(conv_b(ReLU(conv_a(x))) + x), both
 // convolutions 3x3 stride 1 pad 1, 64 -> 64 channels (one workgroup owns every channel of its
-// tile, so the intermediate tensor need not leave the CU).  For small grids (one frame, a few
-// frames): there a layer is a kernel boundary, a cold start and nine dependent steps, and the
-// block costs one of each of the first two instead of two.
+// tile, so the intermediate tensor need not leave the CU).  On small grids that saves a kernel
+// boundary and a cold start, on large ones the intermediate's trip through memory (80 MB per block
+// at twelve 854x480 frames).
 //
 // Output tile 8 x 16.  conv_b needs the intermediate on 10 x 18 pixels, conv_a therefore the
 // input on 12 x 20.  Phase A: the 180 intermediate pixels in row-major order form six groups of
 // 32 (the last 12 lanes idle); wavefront (wm, wn) computes groups wm, wm + 2, wm + 4 for
-// channels 32*wn .. +31 and writes them -- ReLU, rounded to fp16 exactly as the unfused layer
-// stores them, zero outside the image (conv_b's padding) -- into LDS over the input patch.
-// Phase B is the tile loop body of k_conv3x3_c64_walk on that patch.  The 18 weight tiles
-// stream through nine register stages and a double-buffered LDS tile, one barrier per tap;
-// every output accumulates tap-major with four K-steps of 16 per tap, as in the unfused
-// kernels: results are bit-identical to two launches of those.
-// p.wt / p.wt2: packed weights of conv_a / conv_b; p.res = p.in (the shortcut).
+// channels 32*wn .. +31 and writes them -- ReLU, rounded to fp16 exactly as a layer of its own
+// would store them, zero outside the image (conv_b's padding) -- into LDS over the input patch.
+// Phase B: conv_b on that patch, wavefront (wm, wn) rows 4*wm .. +3.
+// The 72 weight fragments of a wavefront stream from memory through one ring of FR register sets
+// that runs on from conv_a into conv_b: no weight tile in LDS, and three barriers in all.  (Staged
+// through LDS tap by tap they cost 18 barriers and a fragment read per K-step: one 854x480 frame
+// 11.3 -> 9.4 us, four 641x361 20.6 -> 18.1, sixteen 416x240 29.2 -> 24.5; twelve 854x480 frames as
+// two launches with the weights resident in LDS and registers 61.4 -> 58.9, which was the last
+// grid where two launches had been the faster form.)
+// FR and BD are the largest that leave three workgroups per CU (154 registers): with BD = 3 and two
+// workgroups 64 us at twelve frames; FR = 9 is equal, FR = 18 (two workgroups) 64.
+// Every output accumulates tap-major with four K-steps of 16 per tap, as in the other stride-1
+// kernels.
+// p.wt_frag / p.wt2_frag: weights of conv_a / conv_b in fragment order; p.res = p.in (the shortcut).
 // =============================================================================================
-__global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
+__global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
   constexpr int TH = 8, TW = 16, YH = TH + 2, YW = TW + 2, XH = TH + 4, XW = TW + 4;
   constexpr int PITCH = 64 + 8;
   constexpr int RPY = (YW * PITCH * 2 + ((128 - (YW * PITCH * 2) % 256 + 256) % 256)) / 2;
@@ -544,9 +396,8 @@ __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
   static_assert(XH * RPX >= YH * RPY, "the intermediate patch is written over the input patch");
   constexpr int NPY = YH * YW;                         // 180 intermediate pixels
   constexpr int XV = XH * XW * 8, XL = (XV + 255) / 256;   // input patch vectors, per thread
-  constexpr int WT = 64 * PITCH;
+  constexpr int FR = 12, BD = 2;        // weight fragments and pixel K-steps in flight
   __shared__ __align__(16) f16 s_xy[XH * RPX];
-  __shared__ __align__(16) f16 s_w[2 * WT];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
   const int tm = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
@@ -569,19 +420,12 @@ __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
     const int off = in ? ((img * p.hin + iy) * p.win + ix) * p.cin_pitch + (tid & 7) * 8 : 0;
     st_x[i] = *reinterpret_cast<const u32x4*>(p.in + off);
   }
-  // ---- weights: stage t holds tap t of conv_a, later tap t of conv_b
-  const int w_row = tid >> 3, w_kv = tid & 7;
-  const f16* wa0 = p.wt + (size_t)w_row * p.ktot + w_kv * 8;
-  const f16* wa1 = wa0 + (size_t)32 * p.ktot;
-  const f16* wb0 = p.wt2 + (size_t)w_row * p.ktot + w_kv * 8;
-  const f16* wb1 = wb0 + (size_t)32 * p.ktot;
-  const int wl0 = w_row * PITCH + w_kv * 8, wl1 = wl0 + 32 * PITCH;
-  u32x4 st_w[9][2];
+  // ---- weight fragments of this wavefront's 32 channels: 36 of conv_a, then 36 of conv_b
+  const u32x4* const wa = reinterpret_cast<const u32x4*>(p.wt_frag) + wn * (36 * 64) + lane;
+  const u32x4* const wb = reinterpret_cast<const u32x4*>(p.wt2_frag) + wn * (36 * 64) + lane;
+  u32x4 fa[FR];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    st_w[t][0] = *reinterpret_cast<const u32x4*>(wa0 + t * 64);
-    st_w[t][1] = *reinterpret_cast<const u32x4*>(wa1 + t * 64);
-  }
+  for (int q = 0; q < FR; ++q) fa[q] = wa[q * 64];
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int v = tid + 256 * i;
@@ -594,7 +438,6 @@ __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
   }
 
   const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int fw_off = (wn * 32 + r) * PITCH + h * 8;
 
   // ---- phase A: intermediate pixel q = 32*(wm + 2k) + r of the 10 x 18 patch, k = 0..2
   int a_py[3], a_px[3], a_off[3];
@@ -606,25 +449,26 @@ __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
     a_off[k] = a_py[k] * RPX + a_px[k] * PITCH + h * 8;
   }
   floatx16 acc_a[3] = {zero16, zero16, zero16};
+  half8 bf[BD + 1][3];
+  // K-step Q_ of a convolution: tap Q_ / 4, K-step Q_ % 4 of it
+#define HS_READ_A(Q_)                                                                          \
+  _Pragma("unroll") for (int k = 0; k < 3; ++k)                                                \
+    bf[(Q_) % (BD + 1)][k] = *reinterpret_cast<const half8*>(                                  \
+        &s_xy[a_off[k] + ((Q_) / 12) * RPX + (((Q_) / 4) % 3) * PITCH + ((Q_) % 4) * 16]);
+  __syncthreads();
 #pragma unroll
-  for (int tap = 0; tap < 9; ++tap) {
-    f16* sw = &s_w[(tap & 1) * WT];
-    *reinterpret_cast<u32x4*>(&sw[wl0]) = st_w[tap][0];
-    *reinterpret_cast<u32x4*>(&sw[wl1]) = st_w[tap][1];
-    __syncthreads();
-    st_w[tap][0] = *reinterpret_cast<const u32x4*>(wb0 + tap * 64);
-    st_w[tap][1] = *reinterpret_cast<const u32x4*>(wb1 + tap * 64);
-    const int toff = (tap / 3) * RPX + (tap % 3) * PITCH;
+  for (int q = 0; q < BD; ++q) HS_READ_A(q)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const half8 a = *reinterpret_cast<const half8*>(&sw[fw_off + ks * 16]);
+  for (int q = 0; q < 36; ++q) {
+    if (q + BD < 36) HS_READ_A(q + BD)
+    const half8 a = __builtin_bit_cast(half8, fa[q % FR]);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const half8 b = *reinterpret_cast<const half8*>(&s_xy[a_off[k] + toff + ks * 16]);
-        acc_a[k] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc_a[k], 0, 0, 0);
-      }
-    }
+    for (int k = 0; k < 3; ++k)
+      acc_a[k] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bf[q % (BD + 1)][k], acc_a[k], 0, 0, 0);
+    fa[q % FR] = q + FR < 36 ? wa[(q + FR) * 64] : wb[(q + FR - 36) * 64];
+    __builtin_amdgcn_sched_barrier(0);
   }
+#undef HS_READ_A
   __syncthreads();          // every wavefront is done with the input patch
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -643,46 +487,49 @@ __global__ __launch_bounds__(256, 2) void k_block64_fused(ConvParams p) {
     }
   }
 
-  // ---- residual of this tile (the block's input), fetched now, used after phase B
+  // ---- residual of this tile (the block's input), fetched now, used after phase B: two 16-byte
+  // pieces per pixel (res_octets_to_quads)
   const int oy = y0 + 4 * wm + (r >> 3);
-  const int n_base = wn * 32 + h * 4;
-  half4 res_pre[2][4];
+  u32x4 res_raw[2][2];
   {
     const int oy_c = min(oy, p.hout - 1);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int ox_c = min(x0 + 8 * g + (r & 7), p.wout - 1);
-      const f16* rp = p.res + (size_t)(img * p.img_m + oy_c * p.wout + ox_c) * p.res_pitch;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) res_pre[g][i] = *reinterpret_cast<const half4*>(rp + n_base + 8 * i);
+      const f16* rp = p.res + (size_t)(img * p.img_m + oy_c * p.wout + ox_c) * p.res_pitch + wn * 32 + h * 8;
+      res_raw[g][0] = *reinterpret_cast<const u32x4*>(rp);
+      res_raw[g][1] = *reinterpret_cast<const u32x4*>(rp + 16);
     }
   }
+  __syncthreads();          // the intermediate patch is complete
 
-  // ---- phase B: conv_b on the intermediate patch (the first barrier below also publishes it)
+  // ---- phase B: conv_b on the intermediate patch
   const int fp_off = (4 * wm + (r >> 3)) * RPY + (r & 7) * PITCH + h * 8;
   floatx16 acc_b[2] = {zero16, zero16};
+#define HS_READ_B(Q_)                                                                          \
+  _Pragma("unroll") for (int g = 0; g < 2; ++g)                                                \
+    bf[(Q_) % (BD + 1)][g] = *reinterpret_cast<const half8*>(                                  \
+        &s_xy[fp_off + ((Q_) / 12) * RPY + (((Q_) / 4) % 3) * PITCH + g * 8 * PITCH + ((Q_) % 4) * 16]);
 #pragma unroll
-  for (int tap = 0; tap < 9; ++tap) {
-    f16* sw = &s_w[((tap + 1) & 1) * WT];       // continues the alternation of phase A (taps 9..17)
-    *reinterpret_cast<u32x4*>(&sw[wl0]) = st_w[tap][0];
-    *reinterpret_cast<u32x4*>(&sw[wl1]) = st_w[tap][1];
-    __syncthreads();
-    const f16* fp = &s_xy[fp_off + (tap / 3) * RPY + (tap % 3) * PITCH];
+  for (int q = 0; q < BD; ++q) HS_READ_B(q)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const half8 a = *reinterpret_cast<const half8*>(&sw[fw_off + ks * 16]);
+  for (int q = 0; q < 36; ++q) {
+    if (q + BD < 36) HS_READ_B(q + BD)
+    const half8 a = __builtin_bit_cast(half8, fa[q % FR]);
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const half8 b = *reinterpret_cast<const half8*>(fp + g * 8 * PITCH + ks * 16);
-        acc_b[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc_b[g], 0, 0, 0);
-      }
-    }
+    for (int g = 0; g < 2; ++g)
+      acc_b[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bf[q % (BD + 1)][g], acc_b[g], 0, 0, 0);
+    if (q + FR < 36) fa[q % FR] = wb[(q + FR) * 64];
+    __builtin_amdgcn_sched_barrier(0);
   }
+#undef HS_READ_B
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
     const int ox = x0 + 8 * g + (r & 7);
+    half4 res_q[4];
+    res_octets_to_quads(res_raw[g], res_q);
     store_octets(p, oy < p.hout && ox < p.wout, img * p.img_m + oy * p.wout + ox, wn * 32, h,
-                 acc_b[g], res_pre[g], true);
+                 acc_b[g], res_q, true);
   }
 }
 
@@ -1375,7 +1222,6 @@ KernelDesc describe(const ConvParams& p) {
                                  : (p.kw_splits == 2 ? (const void*)k_conv_direct<2, 2> : (const void*)k_conv_direct<2, 1>);
       return KernelDesc{f, grid, dim3(256), 0};
     }
-    case CONV_C64_WALK: return KernelDesc{(const void*)k_conv3x3_c64_walk, grid, dim3(256), 0};
     case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
     case CONV_DIRA: return KernelDesc{(const void*)k_conv3x3_dira, grid, dim3(256), 0};
     case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};

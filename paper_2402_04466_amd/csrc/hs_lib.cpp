@@ -392,13 +392,6 @@ struct Builder {
   }
 
   // Packing tasks of a layer whose weights start at blob offset `at`, into region `off`.
-  void pack_generic_at(size_t at, int cout, int cin, int taps, int cout_pad, size_t off) {
-    if (!pack) return;
-    for (int n = 0; n < cout_pad; n += 32)
-      pack_tasks.push_back([=] {
-        pack_generic(half_blob.data() + at, cout, cin, taps, n, std::min(n + 32, cout_pad), host_w.data() + off);
-      });
-  }
   void pack_frag_at(size_t at, int cout, int cin, int taps, int cout_pad, size_t off) {
     if (!pack) return;
     for (int g = 0; g < cout_pad / 32; ++g)
@@ -513,15 +506,6 @@ struct Builder {
       } else {
         plan_kw(c, ns, 1, 1);
       }
-    } else if (c.ntaps == 9 && c.kw == 3 && c.stride == 1 && c.pad == 1 && c.kc == 64 && c.cout == 64 &&
-               c.chunks_per_tap == 1 && fits32 && tiles(16) > 1536) {
-      // several times what the device holds at once: each workgroup walks consecutive tiles, so that
-      // the whole grid is resident at two per CU (smaller grids run the block in one launch)
-      c.variant = CONV_C64_WALK;
-      c.tiles_x = (c.wout + 15) / 16;
-      c.tiles_m = tiles(16);
-      c.tiles_n = 1;
-      c.tiles_per_wg = (c.tiles_m + 511) / 512;
     } else if (c.cout <= 32 && c.kc <= 32 && c.chunks_per_tap == 1 && c.ntaps <= 9) {
       // two K splits, of at most five taps each, while tiles of 64 pixels would be fewer than 192
       c.variant = CONV_DIRECT;
@@ -568,18 +552,16 @@ struct Builder {
   // Appends the convolution.
   // keep_partial: leave the partial sums in the scratch buffer for a later kernel (ConvLSTM).
   // Returns the index of the convolution op.
-  // wf_off: the weights' offset in fragment order, for the variants that read them so (w_off then
-  // is none).  wf2_off / out2: fragment-ordered weights and output of a 1x1 stride-2 projection
+  // wf_off: offset of the weights in fragment order (none: the caller sets them).  wf2_off / out2: fragment-ordered weights and output of a 1x1 stride-2 projection
   // fused into a 3x3 stride-2 layer (out2 == NULL: none).
   static constexpr size_t kNoWeights = (size_t)-1;
-  int add_conv(ConvParams c, size_t w_off, const Tensor* res, const Tensor* out, bool relu,
-               bool want_f32, bool keep_partial, double flops, size_t wf_off = kNoWeights,
-               size_t wf2_off = kNoWeights, const Tensor* out2 = nullptr) {
+  int add_conv(ConvParams c, size_t wf_off, const Tensor* res, const Tensor* out, bool relu,
+               bool want_f32, bool keep_partial, double flops, size_t wf2_off = kNoWeights, const Tensor* out2 = nullptr) {
     Op op;
     op.fam = F_CONV;
     op.flops = flops;
     auto at = [&](size_t off) { return d_w && off != kNoWeights ? d_w + off : nullptr; };
-    c.wt = at(w_off); c.wt_frag = at(wf_off); c.wt2 = nullptr; c.wt2_frag = at(wf2_off);
+    c.wt_frag = at(wf_off); c.wt2_frag = at(wf2_off);
     choose_split(c);
     c.use_partial = keep_partial ? 1 : 0;
     c.partial = nullptr;   // patched when the scratch buffer is carved
@@ -603,10 +585,10 @@ struct Builder {
   // Generic convolution on a pixel-major tensor; weights are the next cout*cin*k*k floats of the
   // blob starting at blob_at. Fills out->h/w/c.
   // proj_at / proj_out: blob offset and output of the block's 1x1 stride-2 projection, fused into
-  // this 3x3 stride-2 layer when the layer qualifies (returns through *proj_fused whether it was).
+  // this 3x3 stride-2 layer (none: NULL).
   int conv_layer(const Tensor& in, size_t blob_at, int cout, int k, int stride, int pad, bool relu,
                  const Tensor* res, Tensor* out, bool want_f32, bool keep_partial,
-                 size_t proj_at = 0, Tensor* proj_out = nullptr, bool* proj_fused = nullptr) {
+                 size_t proj_at = 0, Tensor* proj_out = nullptr) {
     const int cin = in.c;
     ConvParams g;
     std::memset(&g, 0, sizeof(g));
@@ -619,50 +601,33 @@ struct Builder {
     g.nchunks = g.ntaps * g.chunks_per_tap; g.ktot = g.nchunks * g.kc;
     g.stride = stride; g.pad = pad;
     out->h = g.hout; out->w = g.wout; out->c = cout;
-    // The kernel variant is a function of the shapes alone: layers that read their weights as MFMA
-    // fragments are packed in that order, the others row by row.
+    // The kernel variant is a function of the shapes alone.
     ConvParams probe = g;
     choose_split(probe);
-    const bool frag = probe.variant == CONV_DIRA || probe.variant == CONV_S2_DIRA || probe.variant == CONV_KW;
-    size_t w_off = kNoWeights, wf_off = kNoWeights, wf2_off = kNoWeights;
-    const size_t n_w = (size_t)g.cout_pad * g.ktot;
-    if (probe.variant == CONV_DIRECT) {
-      wf_off = reserve_w((size_t)32 * g.ktot);
-      if (pack)
-        pack_tasks.push_back([=] {
-          std::vector<f16> rows((size_t)cout * g.ktot);
-          pack_generic(half_blob.data() + blob_at, cout, cin, k * k, 0, cout, rows.data());
-          pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
-        });
-    } else if (frag) {
-      wf_off = reserve_w(n_w);
+    const bool direct = probe.variant == CONV_DIRECT, fuse = proj_out != nullptr;
+    const size_t wf_off = reserve_w(direct ? (size_t)32 * g.ktot : (size_t)g.cout_pad * g.ktot);
+    size_t wf2_off = kNoWeights;
+    if (!direct) {
       pack_frag_at(blob_at, cout, cin, 9, g.cout_pad, wf_off);
-    } else {
-      w_off = reserve_w(n_w);
-      pack_generic_at(blob_at, cout, cin, k * k, g.cout_pad, w_off);
+    } else if (pack) {
+      pack_tasks.push_back([=] {
+        std::vector<f16> rows((size_t)cout * g.ktot);
+        pack_generic(half_blob.data() + blob_at, cout, cin, k * k, 0, cout, rows.data());
+        pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
+      });
     }
-    const bool fuse = proj_out && frag && stride == 2;
-    if (proj_fused) *proj_fused = fuse;
     if (fuse) {
       proj_out->h = g.hout; proj_out->w = g.wout; proj_out->c = cout;
       wf2_off = reserve_w((size_t)g.cout_pad * cin);
       pack_frag_at(proj_at, cout, cin, 1, g.cout_pad, wf2_off);
     }
-    return add_conv(g, w_off, res, out, relu, want_f32, keep_partial,
-                    2.0 * g.m * (double)cout * cin * (k * k + (fuse ? 1 : 0)), wf_off, wf2_off,
+    return add_conv(g, wf_off, res, out, relu, want_f32, keep_partial,
+                    2.0 * g.m * (double)cout * cin * (k * k + (fuse ? 1 : 0)), wf2_off,
                     fuse ? proj_out : nullptr);
   }
 
   // A 64 -> 64 -> 64 channel BasicBlock without projection as ONE launch (k_block64_fused):
-  // out = ReLU(conv_b(ReLU(conv_a(in))) + in).  For grids up to the size from which the layers
-  // walk their tiles (measured: 3-9 % more frames per second at 1 to 6 frames per launch, even
-  // from 8 on, where the tile-walking kernel with resident weights takes over).
-  // Weights are reserved in blob order (conv a, conv b), as by two conv_layer calls.
-  static bool block64_fits(const hs_app_desc& d, const Tensor& in) {
-    const long tiles = (long)d.batch * ((in.h + 7) / 8) * ((in.w + 15) / 16);
-    return in.c == 64 && tiles <= 1536 &&
-           (double)d.batch * in.h * in.w * in.pitch < 2147483648.0;
-  }
+  // out = ReLU(conv_b(ReLU(conv_a(in))) + in).  Weights are reserved in blob order (conv a, conv b).
   void block64_layer(const Tensor& in, size_t at_a, size_t at_b, Tensor* out) {
     ConvParams g;
     std::memset(&g, 0, sizeof(g));
@@ -673,17 +638,17 @@ struct Builder {
     g.ntaps = 9; g.kw = 3; g.chunks_per_tap = 1; g.nchunks = 9; g.ktot = 576;
     g.stride = 1; g.pad = 1;
     const size_t wa_off = reserve_w((size_t)64 * 576);
-    pack_generic_at(at_a, 64, 64, 9, 64, wa_off);
+    pack_frag_at(at_a, 64, 64, 9, 64, wa_off);
     const size_t wb_off = reserve_w((size_t)64 * 576);
-    pack_generic_at(at_b, 64, 64, 9, 64, wb_off);
+    pack_frag_at(at_b, 64, 64, 9, 64, wb_off);
     out->h = g.hout; out->w = g.wout; out->c = 64;
     g.variant = CONV_BLOCK64;
     g.tiles_x = (g.wout + 15) / 16;
     g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
     g.tiles_n = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
     g.tiles_per_xcd = (g.tiles_m + 7) / 8;
-    g.wt = d_w ? d_w + wa_off : nullptr;
-    g.wt2 = d_w ? d_w + wb_off : nullptr;
+    g.wt_frag = d_w ? d_w + wa_off : nullptr;
+    g.wt2_frag = d_w ? d_w + wb_off : nullptr;
     g.out = out->p; g.out_pitch = out->pitch;
     g.res = in.p; g.res_pitch = in.pitch;
     g.relu = 1;
@@ -716,8 +681,7 @@ struct Builder {
         pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
       });
     out->h = g.hout; out->w = g.wout; out->c = cout;
-    first_conv_op = add_conv(g, kNoWeights, nullptr, out, true, false, false,
-                             2.0 * g.m * (double)cout * 3 * k * k, wf_off);
+    first_conv_op = add_conv(g, wf_off, nullptr, out, true, false, false, 2.0 * g.m * (double)cout * 3 * k * k);
   }
 
   void walk_tiny(int ph, int pw) {
@@ -794,11 +758,9 @@ struct Builder {
         if (proj) {
           // the projection reads the centre-tap pixels of conv a: one kernel computes both
           sc.pitch = width;
-          bool fused = false;
-          conv_layer(a, at_a, width, 3, 2, 1, true, nullptr, &t, false, false, at_p, &sc, &fused);
-          if (!fused) conv_layer(a, at_p, width, 1, 2, 0, false, nullptr, &sc, false, false);
+          conv_layer(a, at_a, width, 3, 2, 1, true, nullptr, &t, false, false, at_p, &sc);
           shortcut = &sc;
-        } else if (width == 64 && block64_fits(d, a)) {
+        } else if (width == 64) {
           // the whole block in one launch; the intermediate tensor t is never written
           o.pitch = width;
           block64_layer(a, at_a, at_b, &o);
