@@ -10,12 +10,14 @@
 #include <cmath>
 #include <condition_variable>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <memory>
 #include <mutex>
 #include <new>
 #include <stdexcept>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <pthread.h>
 #include <sched.h>
@@ -412,18 +414,28 @@ struct Builder {
   }
   static void run_tasks(const std::vector<std::function<void()>>& tasks) {
     std::atomic<size_t> next{0};
+    std::mutex mu;
+    std::exception_ptr failed;           // a task's exception reaches the caller, not the thread's end
     auto work = [&] {
-      for (size_t i = next++; i < tasks.size(); i = next++) tasks[i]();
+      try {
+        for (size_t i = next++; i < tasks.size(); i = next++) tasks[i]();
+      } catch (...) {
+        std::lock_guard<std::mutex> lk(mu);
+        failed = std::current_exception();
+      }
     };
     // (a thread costs about as much as one task: few tasks run on the caller's)
     const size_t n = tasks.size() < 16 ? 1 : std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency()));
     std::vector<std::thread> threads;
-    struct Join {
-      std::vector<std::thread>& t;
-      ~Join() { for (std::thread& x : t) x.join(); }
-    } join{threads};
-    for (size_t i = 1; i < n; ++i) threads.emplace_back(work);
+    threads.reserve(n);
+    try {
+      for (size_t i = 1; i < n; ++i) threads.emplace_back(work);
+    } catch (const std::system_error&) {
+      // no more threads to be had: those that there are do the work
+    }
     work();
+    for (std::thread& x : threads) x.join();
+    if (failed) std::rethrow_exception(failed);
   }
 
   // CONV_KW with ns K splits, cw channel groups and pg pixel groups per workgroup.
