@@ -575,6 +575,7 @@ struct Builder {
     auto at = [&](size_t off) { return d_w && off != kNoWeights ? d_w + off : nullptr; };
     c.wt_frag = at(wf_off); c.wt2_frag = at(wf2_off);
     choose_split(c);
+    if (!describe(c).func) throw std::logic_error("no instantiation of the planned convolution kernel");
     c.use_partial = keep_partial ? 1 : 0;
     c.partial = nullptr;   // patched when the scratch buffer is carved
     c.out = nullptr; c.out_pitch = 0; c.res = nullptr; c.res_pitch = 0; c.relu = 0;

@@ -229,3 +229,16 @@ def test_seeded_inputs_hash_to_the_recorded_values():
     want = [l.rstrip("\n") for l in open(os.path.join(ROOT, "tests", "golden", "input_hashes.txt"))
             if not l.startswith("#")]
     assert list(mod.lines()) == want
+
+
+def test_every_accepted_size_has_a_kernel_for_every_layer():
+    """The plan of a size names the kernels its layers run on (grid rules, K splits, tile shapes):
+    none may be missing, from the smallest network input to the largest the boundary accepts."""
+    sizes = [(8, 8), (8, 2000), (2000, 8), (33, 17), (96, 64), (130, 66), (192, 108), (250, 190), (288, 160),
+             (416, 240), (511, 257), (641, 361), (854, 480), (1280, 720), (1450, 1440)]
+    sizes += [(w, w * 9 // 16) for w in range(64, 900, 23)]
+    for net in (hs.HS_NET_RESNET18_CONVLSTM, hs.HS_NET_TINY4):
+        for w, h in sizes:
+            for batch in (1, 2, 3, 4, 5, 7, 8, 11, 12, 16):
+                assert hs.hs_query_workspace(_desc(frame_w=640, frame_h=360, frame_pitch=1920, net_w=w, net_h=h,
+                                                   net=net, batch=batch)) > 0, (net, w, h, batch)
