@@ -172,6 +172,27 @@ __device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + __ex
 // stage 3's heat value of a logit
 __device__ __forceinline__ float heat_of(float x) { return 1.0f / (1.0f + expf(-x)); }
 
+// Pairs q[i] = fp16 channels cbase + 8i + 4h .. +3 of the lane's pixel: the exchange and the store.
+__device__ __forceinline__ void store_quads_to(f16* out, int pitch, bool valid, int m, int cbase, int h,
+                                               uint32_t (&q)[4][2]) {
+#pragma unroll
+  for (int pr = 0; pr < 2; ++pr)
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const auto sw = __builtin_amdgcn_permlane32_swap(q[2 * pr][w], q[2 * pr + 1][w], false, false);
+      q[2 * pr][w] = sw[0];
+      q[2 * pr + 1][w] = sw[1];
+    }
+  if (valid) {
+    f16* dst = out + (size_t)m * pitch + cbase + h * 8;
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+      const u32x4 o = {q[2 * pr][0], q[2 * pr][1], q[2 * pr + 1][0], q[2 * pr + 1][1]};
+      *reinterpret_cast<u32x4*>(dst + 16 * pr) = o;
+    }
+  }
+}
+
 // Epilogue of the 32 channels of one pixel that a lane pair (r, r + 32) holds as accumulator
 // quads: lane half h has channels cbase + 4h + 8i .. +3 in acc[4i .. 4i+3], i = 0..3.  Residual,
 // ReLU and rounding to fp16; then the two lanes swap one quad of every pair
@@ -191,33 +212,15 @@ __device__ __forceinline__ void store_octets_to(f16* out, int pitch, bool relu, 
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] += (float)res[i][j];
     }
-    if (relu) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.0f);
-    }
     half4 o;
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[j] = (f16)v[j];
+    if (relu) o = __builtin_elementwise_max(o, half4{});   // ReLU and rounding commute: two values at once
     const uint2 w = __builtin_bit_cast(uint2, o);
     q[i][0] = w.x;
     q[i][1] = w.y;
   }
-#pragma unroll
-  for (int pr = 0; pr < 2; ++pr)
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      const auto sw = __builtin_amdgcn_permlane32_swap(q[2 * pr][w], q[2 * pr + 1][w], false, false);
-      q[2 * pr][w] = sw[0];
-      q[2 * pr + 1][w] = sw[1];
-    }
-  if (valid) {
-    f16* dst = out + (size_t)m * pitch + cbase + h * 8;
-#pragma unroll
-    for (int pr = 0; pr < 2; ++pr) {
-      const u32x4 o = {q[2 * pr][0], q[2 * pr][1], q[2 * pr + 1][0], q[2 * pr + 1][1]};
-      *reinterpret_cast<u32x4*>(dst + 16 * pr) = o;
-    }
-  }
+  store_quads_to(out, pitch, valid, m, cbase, h, q);
 }
 __device__ __forceinline__ void store_octets(const ConvParams& p, bool valid, int m, int cbase,
                                              int h, const floatx16& acc, const half4 (&res)[4],
@@ -481,7 +484,8 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
       for (int i = 0; i < 4; ++i) {
         half4 o;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = inside ? (f16)fmaxf(acc_a[k][4 * i + j], 0.0f) : (f16)0.0f;
+        for (int j = 0; j < 4; ++j) o[j] = (f16)acc_a[k][4 * i + j];
+        o = inside ? __builtin_elementwise_max(o, half4{}) : half4{};
         *reinterpret_cast<half4*>(dst + 8 * i) = o;
       }
     }
@@ -1316,14 +1320,19 @@ KernelDesc describe(const LstmEpilogueParams& p) {
 // straight from the patch, no im2col copy.
 // Wavefront (wm, wn): convolution rows 8*wm .. 8*wm+8 (row 8 is computed by both halves, it
 // feeds pooled rows 3 and 4), channels 32*wn .. +31: nine accumulators.  Pooling: maximum over
-// three accumulators (rows), then over lanes r, r+1, r+2 (columns, two DPP wavefront shifts),
-// ReLU last; even lanes store.
-// Rounding to fp16 after the maximum equals the maximum of the rounded values.
+// three accumulators (rows), then over lanes r, r+1, r+2 (columns, two DPP wavefront shifts), on
+// rounded and clamped values; even lanes store.
+// Twelve 854x480 frames, whole pass: 710 -> 699 us against the same pooling in 32-bit floats.
 // =============================================================================================
 // value of lane + 1 (DPP whole-wavefront shift; lane 63 keeps its own)
-__device__ __forceinline__ float lane_plus_1(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x130,
-                                                    0xf, 0xf, false));
+__device__ __forceinline__ uint32_t lane_plus_1(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x130, 0xf, 0xf, false);
+}
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+typedef f16 half2v __attribute__((ext_vector_type(2)));
+// larger of each half of two pairs of non-negative fp16 numbers
+__device__ __forceinline__ uint32_t max_pairs(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, a), __builtin_bit_cast(i16x2, b)));
 }
 
 __global__ __launch_bounds__(256, 2) void k_stem_pool(StemPoolParams p) {
@@ -1397,38 +1406,51 @@ __global__ __launch_bounds__(256, 2) void k_stem_pool(StemPoolParams p) {
     }
   }
 
-  // ---- pool, ReLU.  max and ReLU commute, so ReLU comes last; a pooling window always holds
-  // its centre row (convolution row 2 * py exists whenever pooled row py does), rows outside the
-  // convolution output are skipped (the same for the whole wavefront), columns outside it count
-  // as 0, which cannot change ReLU(max).  Then the lane pair (r, r + 32) exchanges quads and
-  // stores 16 bytes per lane (store_octets_to); every lane takes part in the exchange.
+  // ---- ReLU, pool.  Rounding to fp16, ReLU and the maximum commute, so the accumulators are rounded
+  // and clamped first, two values per instruction; ReLU also turns a NaN into 0, and what is left
+  // is ordered like its bits, so the maxima are 16-bit integer ones (a float maximum costs a second
+  // instruction per operand to quieten a NaN that the compiler cannot rule out: of the 850 vector
+  // instructions of this part in 32-bit floats 370 are left).  A pooling window always holds its centre row
+  // (convolution row 2 * py exists whenever pooled row py does), rows outside the convolution
+  // output are skipped (the same for the whole wavefront), columns outside it count as 0, which
+  // cannot change the maximum.  Then the lane pair (r, r + 32) exchanges quads and stores 16 bytes
+  // per lane (store_quads_to); every lane takes part in the exchange.
   const int cx = cx0 + r;
-  const bool col_ok = cx >= 0 && cx < p.wc;
+  const uint32_t col_mask = cx >= 0 && cx < p.wc ? 0xffffffffu : 0u;
   const int q = q0 + (r >> 1);
   const bool writer = (r & 1) == 0 && r <= 28 && q < p.wp;
+  i16x2 y[9][8];
+#pragma unroll
+  for (int j = 0; j < 9; ++j)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const half2v t = {(f16)acc[j][2 * i], (f16)acc[j][2 * i + 1]}, zero = {(f16)0.0f, (f16)0.0f};
+      y[j][i] = __builtin_bit_cast(i16x2, __builtin_elementwise_max(t, zero));
+    }
 #pragma unroll
   for (int pl = 0; pl < 4; ++pl) {
     const int py = p0 + 4 * wm + pl;
     const int cy_top = cy0 + 8 * wm + 2 * pl;             // rows cy_top, cy_top + 1 (centre), cy_top + 2
     const bool top_ok = cy_top >= 0, bot_ok = cy_top + 2 < p.hc;
-    floatx16 v = acc[2 * pl + 1];
+    i16x2 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = y[2 * pl + 1][i];
     if (top_ok) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = fmaxf(v[i], acc[2 * pl][i]);
+      for (int i = 0; i < 8; ++i) v[i] = __builtin_elementwise_max(v[i], y[2 * pl][i]);
     }
     if (bot_ok) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = fmaxf(v[i], acc[2 * pl + 2][i]);
+      for (int i = 0; i < 8; ++i) v[i] = __builtin_elementwise_max(v[i], y[2 * pl + 2][i]);
     }
+    uint32_t o[4][2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float m = col_ok ? v[i] : 0.0f;
-      const float m2 = fmaxf(m, lane_plus_1(m));       // columns r, r+1
-      v[i] = fmaxf(fmaxf(m2, lane_plus_1(m2)), 0.0f);  // columns r .. r+2, ReLU
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t m = __builtin_bit_cast(uint32_t, v[i]) & col_mask;
+      const uint32_t m2 = max_pairs(m, lane_plus_1(m));        // columns r, r+1
+      o[i >> 1][i & 1] = max_pairs(m2, lane_plus_1(m2));       // columns r .. r+2
     }
-    const half4 none[4] = {};
-    store_octets_to(p.out, 64, false, writer && py < p.hp, (img * p.hp + py) * p.wp + q, 32 * wn, h, v,
-                    none, false);
+    store_quads_to(p.out, 64, writer && py < p.hp, (img * p.hp + py) * p.wp + q, 32 * wn, h, o);
   }
 }
 
