@@ -121,7 +121,7 @@ constexpr int kMaxLanes = 2;
 struct Slot {
   std::vector<Op> pre;     // stage 1: one launch, blockIdx.y = stream of the batch
   std::vector<Op> infer;   // stage 2: the network over the whole batch
-  std::vector<Op> infer_static;   // the same with the split-K scratch in the library's fixed
+  std::vector<Op> infer_static;   // the same with the gate scratch in the library's fixed
                                   // device array (empty when the scratch needed exceeds it)
   std::vector<Op> post;    // stage 3: the channel maxima
   bool maxima_with_overlay = false;   // they may ride in the overlay's launch instead
@@ -221,7 +221,7 @@ struct hs_app {
   uint64_t acc_n[F_COUNT] = {0};
   void* pinned = nullptr;
   hs_group* group = nullptr;   // set while the application is a member of a multi-network group
-  size_t partial_bytes = 0;    // split-K scratch one frame needs
+  size_t partial_bytes = 0;    // gate scratch (pre-activations, fp32) one frame needs
 };
 
 // A multi-network application: the members run stages 1-3 on the same frame side by side, one
@@ -356,7 +356,7 @@ static inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 static inline size_t round_up_sz(size_t v, size_t m) { return (v + m - 1) / m * m; }
 
 // Walks the layers of a network in blob order.  Used twice: a sizing walk (no pointers, no
-// packing) that yields the packed-weight and split-K scratch sizes, then the real walk.
+// packing) that yields the packed-weight and gate scratch sizes, then the real walk.
 struct Builder {
   const hs_app_desc& d;
   Carver carve;
@@ -370,7 +370,7 @@ struct Builder {
   const float* blob;
   size_t blob_off = 0;
   size_t partial_floats = 0;
-  float* d_partial = nullptr;     // split-K scratch of this lane inside the workspace
+  float* d_partial = nullptr;     // gate scratch of this lane inside the workspace
   std::vector<Op> ops;            // stage-2 ops; slot-dependent pointers are patched per slot
   int first_conv_op = -1;         // op whose conv.in is the slot's padded net input
   int logits_op = -1;             // op that writes the slot's logits
@@ -564,8 +564,8 @@ struct Builder {
   // Appends the convolution.
   // keep_partial: leave the partial sums in the scratch buffer for a later kernel (ConvLSTM).
   // Returns the index of the convolution op.
-  // wf_off: offset of the weights in fragment order (none: the caller sets them).  wf2_off / out2: fragment-ordered weights and output of a 1x1 stride-2 projection
-  // fused into a 3x3 stride-2 layer (out2 == NULL: none).
+  // wf_off: offset of the weights in fragment order.  wf2_off / out2: fragment-ordered weights and
+  // output of a 1x1 stride-2 projection fused into a 3x3 stride-2 layer (out2 == NULL: none).
   static constexpr size_t kNoWeights = (size_t)-1;
   int add_conv(ConvParams c, size_t wf_off, const Tensor* res, const Tensor* out, bool relu,
                bool want_f32, bool keep_partial, double flops, size_t wf2_off = kNoWeights, const Tensor* out2 = nullptr) {
@@ -919,7 +919,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     return HS_E_INVAL;
   }
 
-  // real walk: workspace = [weights][activations, state][split-K scratch][tables][slots]
+  // real walk: workspace = [weights][activations, state][gate scratch][tables][slots]
   Builder b(*d, create ? d->d_workspace : nullptr, create, true);
   b.d_w = b.carve.take<f16>(sizing.w_halves);
   b.walk(ph, pw);
@@ -1071,7 +1071,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     }
     app->partial_bytes = b.partial_floats * sizeof(float);
     if (app->partial_bytes <= app->ctx->static_scratch_bytes && app->ctx->d_static_scratch) {
-      // the same launches with every split-K pointer moved from the lane's scratch in the
+      // the same launches with every scratch pointer moved from the lane's scratch in the
       // workspace to the same offset inside the library's fixed array
       float* const from = lane_b[s.lane]->d_partial;
       float* const to = (float*)app->ctx->d_static_scratch;
