@@ -111,6 +111,7 @@ struct Carver {
 struct Tensor {
   f16* p = nullptr;
   int h = 0, w = 0, c = 0, pitch = 0;
+  size_t cap = 0;   // halves its buffer holds (known in a sizing walk too, where p is NULL)
 };
 
 enum SlotState { SLOT_FREE = 0, SLOT_INFLIGHT = 1, SLOT_DONE = 2 };
@@ -386,6 +387,18 @@ struct Builder {
   template <typename T>
   T* acts(size_t count) { return carve_acts ? carve.take<T>(count) : nullptr; }
 
+  // A buffer for activations.
+  Tensor act(size_t halves) {
+    Tensor t;
+    t.p = acts<f16>(halves);
+    t.cap = halves;
+    return t;
+  }
+  // A plan whose layer writes past its output's buffer is refused here, on the host.
+  static void check_room(const Tensor& t, int pixels) {
+    if ((size_t)pixels * t.pitch > t.cap) throw std::logic_error("a layer's output exceeds its buffer");
+  }
+
   // Reserve room for n packed halves; returns the offset. Regions start 256-byte aligned.
   size_t reserve_w(size_t n) {
     const size_t off = w_halves;
@@ -614,6 +627,7 @@ struct Builder {
     g.nchunks = g.ntaps * g.chunks_per_tap; g.ktot = g.nchunks * g.kc;
     g.stride = stride; g.pad = pad;
     out->h = g.hout; out->w = g.wout; out->c = cout;
+    if (!want_f32 && !keep_partial) check_room(*out, g.m);
     // The kernel variant is a function of the shapes alone.
     ConvParams probe = g;
     choose_split(probe);
@@ -631,6 +645,7 @@ struct Builder {
     }
     if (fuse) {
       proj_out->h = g.hout; proj_out->w = g.wout; proj_out->c = cout;
+      check_room(*proj_out, g.m);
       wf2_off = reserve_w((size_t)g.cout_pad * cin);
       pack_frag_at(proj_at, cout, cin, 1, g.cout_pad, wf2_off);
     }
@@ -655,6 +670,7 @@ struct Builder {
     const size_t wb_off = reserve_w((size_t)64 * 576);
     pack_frag_at(at_b, 64, 64, 9, 64, wb_off);
     out->h = g.hout; out->w = g.wout; out->c = 64;
+    check_room(*out, g.m);
     g.variant = CONV_BLOCK64;
     g.tiles_x = (g.wout + 15) / 16;
     g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
@@ -694,17 +710,16 @@ struct Builder {
         pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
       });
     out->h = g.hout; out->w = g.wout; out->c = cout;
+    check_room(*out, g.m);
     first_conv_op = add_conv(g, wf_off, nullptr, out, true, false, false, 2.0 * g.m * (double)cout * 3 * k * k);
   }
 
   void walk_tiny(int ph, int pw) {
     const int h1 = conv_out(d.net_h, 3, 2, 1), w1 = conv_out(d.net_w, 3, 2, 1);
     const int h2 = conv_out(h1, 3, 2, 1), w2 = conv_out(w1, 3, 2, 1);
-    Tensor t1, t2, t3, lg;
     const size_t nb = (size_t)d.batch;
-    t1.p = acts<f16>(nb * h1 * w1 * 16); t1.pitch = 16;
-    t2.p = acts<f16>(nb * h2 * w2 * 32); t2.pitch = 32;
-    t3.p = acts<f16>(nb * h2 * w2 * 32); t3.pitch = 32;
+    Tensor t1 = act(nb * h1 * w1 * 16), t2 = act(nb * h2 * w2 * 32), t3 = act(nb * h2 * w2 * 32), lg;
+    t1.pitch = 16; t2.pitch = 32; t3.pitch = 32;
     size_t at = 0;
     first_layer(at, ph, pw, 16, 3, &t1);                                 at += 16 * 3 * 9;
     conv_layer(t1, at, 32, 3, 2, 1, true, nullptr, &t2, false, false);   at += 32 * 16 * 9;
@@ -717,13 +732,21 @@ struct Builder {
   void walk_resnet(int ph, int pw) {
     const int hs_ = conv_out(d.net_h, 7, 2, 3), ws_ = conv_out(d.net_w, 7, 2, 3);
     const int hp = conv_out(hs_, 3, 2, 1), wp = conv_out(ws_, 3, 2, 1);
+    const int widths[4] = {64, 128, 256, 512};
     int hf = hp, wf = wp;
-    for (int i = 0; i < 3; ++i) { hf = conv_out(hf, 3, 2, 1); wf = conv_out(wf, 3, 2, 1); }
+    // The four buffers rotate through all stages.  A stage halves the map and doubles the width: the first
+    // stage is the largest but on maps of a few pixels, whose halves round up.
+    size_t act_img = (size_t)hp * wp * 64;
+    for (int s = 1; s < 4; ++s) {
+      hf = conv_out(hf, 3, 2, 1); wf = conv_out(wf, 3, 2, 1);
+      act_img = std::max(act_img, (size_t)hf * wf * widths[s]);
+    }
     const size_t nb = (size_t)d.batch;
     const int mf = (int)nb * hf * wf;                    // feature-map pixels over the batch
     Tensor buf[4];
-    for (int i = 0; i < 4; ++i) buf[i].p = acts<f16>(nb * hp * wp * 64);
-    f16* concat = acts<f16>((size_t)mf * 768);
+    for (Tensor& t : buf) t = act(nb * act_img);
+    const Tensor concat_buf = act((size_t)mf * 768);
+    f16* const concat = concat_buf.p;
     float* cstate = acts<float>((size_t)mf * 256);
 
     size_t at = 0;
@@ -751,7 +774,7 @@ struct Builder {
     at += 64 * 3 * 49;
     int cur = 0;
     buf[0].h = hp; buf[0].w = wp; buf[0].c = 64; buf[0].pitch = 64;
-    const int widths[4] = {64, 128, 256, 512};
+    check_room(buf[0], (int)nb * hp * wp);
     int cin = 64;
     for (int s = 0; s < 4; ++s) {
       for (int blk = 0; blk < 2; ++blk) {
@@ -784,7 +807,8 @@ struct Builder {
           conv_layer(a, at_a, width, 3, 1, 1, true, nullptr, &t, false, false);
         }
         const bool last = s == 3 && blk == 1;
-        if (last) { o.p = concat; o.pitch = 768; } else { o.pitch = width; }
+        if (last) o = concat_buf;
+        o.pitch = last ? 768 : width;
         conv_layer(t, at_b, width, 3, 1, 1, true, shortcut, &o, false, false);
         cur = (cur + 3) % 4;
         cin = width;

@@ -242,3 +242,25 @@ def test_every_accepted_size_has_a_kernel_for_every_layer():
             for batch in (1, 2, 3, 4, 5, 7, 8, 11, 12, 16):
                 assert hs.hs_query_workspace(_desc(frame_w=640, frame_h=360, frame_pitch=1920, net_w=w, net_h=h,
                                                    net=net, batch=batch)) > 0, (net, w, h, batch)
+
+
+def test_workspace_holds_the_output_of_every_layer():
+    """Every image of a batch adds at least the tensors its layers write: on maps of a few pixels a
+    later stage of the backbone (half the map, twice the channels, sizes rounded up) is larger than
+    the first one, and the four buffers that rotate through the stages have to hold it."""
+    def half(n):
+        return (n + 1) // 2
+
+    for w, h in ((8, 8), (8, 12), (12, 8), (16, 9), (17, 17), (33, 17), (96, 64)):
+        mh, mw, stages = half(half(h)), half(half(w)), []
+        for width in (64, 128, 256, 512):
+            if width > 64:
+                mh, mw = half(mh), half(mw)
+            stages.append(mh * mw * width)
+        image = 4 * 2 * max(stages)                     # rotating buffers, fp16
+        image += mh * mw * (768 * 2 + 256 * 4 + 1024 * 4)   # [x_t ; h], c, gate pre-activations
+        image += h * w * 8 + mh * mw * 8 * (4 + 4 + 1) + mh * mw   # net input, logits, heat, mask, map
+        one, many = (hs.hs_query_workspace(_desc(frame_w=64, frame_h=48, frame_pitch=192, net_w=w, net_h=h,
+                                                 queue_depth=1, batch=b)) for b in (1, 16))
+        # every region starts on a multiple of 256 bytes: 14 regions of the one-image plan may end short
+        assert many - one >= 15 * image - 14 * 256, (w, h, many - one, 15 * image)

@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nw,nh,batch", [
+    (8, 8, 1),        # the smallest input: maps of 2 x 2 and 1 x 1 pixels, the last stage's the largest tensor
+    (8, 8, 3),        # the same, several images in every tensor
     (96, 64, 1),      # maps of 8 x 12, 4 x 6 and 2 x 3 pixels: less than a tile; 1, 2, 4 and 6 K splits
     (130, 66, 6),     # three K splits (the last one shorter), grids beyond one round of workgroups
     (130, 66, 16),    # one split, two and four channel groups per workgroup, both strides
