@@ -1647,12 +1647,15 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
     // visits only the tools that some lane meets.
     const int* mk = L.marks + (size_t)by * 16;
     const int lab_w = 11 * L.scale, lab_h = 7 * L.scale;
+    // the cross-hair's bars are 2 * arm + 1 long and 2 * half + 1 thick; either may be the larger.  The
+    // label reaches further to the right than a bar (13 pixels past arm at least, half is at most 8)
+    const int ext = max(L.arm, L.half);
     uint32_t met = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const int cx = mk[2 * k], cy = mk[2 * k + 1];
       const int ox = cx + L.arm + 2, oy = cy - lab_h - 2;          // label origin
-      const bool in = cx >= 0 && Y >= min(cy - L.arm, oy) && Y <= cy + L.arm && X0 + 15 >= cx - L.arm &&
+      const bool in = cx >= 0 && Y >= min(cy - ext, oy) && Y <= cy + ext && X0 + 15 >= cx - ext &&
                       X0 < ox + lab_w;
       met |= in ? 1u << k : 0u;
     }
@@ -1665,7 +1668,8 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
       const uint32_t col = L.pal[k];
       // what this row paints, as pixel intervals around cx and a bit per label pixel
       const int dy = abs(Y - cy);
-      const int reach = dy <= L.half ? L.arm : (dy <= L.arm ? L.half : -1);   // |X - cx| <= reach
+      // |X - cx| <= reach: the wider of the two bars where the row meets both
+      const int reach = max(dy <= L.half ? L.arm : -1, dy <= L.arm ? L.half : -1);
       uint64_t lab_lo = 0, lab_hi = 0;       // label pixels lx = 0..63 and 64..87 of this row
       if (Y >= oy && Y < oy + lab_h) {
         const int gy = (int)udiv_est((uint32_t)(Y - oy), (uint32_t)L.scale, L.rcp_scale);

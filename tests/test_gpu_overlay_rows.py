@@ -54,3 +54,35 @@ def test_overlay_row_ends(hs, fw, fh, extra_pitch, net, annotate):
     finally:
         s.close()
         hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("arm,half,scale", [
+    (0, 0, 1),      # a single pixel and its label
+    (0, 3, 1),      # bars thicker than long: the vertical bar is the wider one
+    (3, 8, 2),
+    (4, 4, 1),
+    (64, 8, 8),     # the largest
+])
+def test_marker_shapes(hs, arm, half, scale):
+    """Cross-hair and label of every accepted shape, bit-exact against the oracle's, in rows that end
+    inside a group of 16 pixels."""
+    from paper_2402_04466_amd.harness import AppStream
+    fw, fh = 335, 201
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=fw, frame_h=fh, net_w=40, net_h=24,
+                  blob=si.he_normal_blob(si.TINY4_LAYERS, 11), palette=si.DEFAULT_PALETTE, alpha=0.37,
+                  glyphs=si.DEFAULT_GLYPHS, marker_arm=arm, marker_half=half, glyph_scale=scale)
+    try:
+        for i, f in enumerate(si.uniform_frames(2, fh, fw, 13)):
+            print(f"[marker-shapes] arm {arm} half {half} scale {scale} frame {i}", flush=True)
+            d_in, d_out = s.upload_frame(f), s.new_output()
+            assert s.submit(d_in, d_out, i) == hs.HS_OK
+            g = s.fetch(s.wait(), d_out)
+            assert g["present"].any()
+            want = oracle.annotate(oracle.overlay(f, g["mask"], si.DEFAULT_PALETTE, 0.37), g["argmax_idx"],
+                                   g["present"], g["mask"].shape[2], g["mask"].shape[1], si.DEFAULT_PALETTE,
+                                   si.DEFAULT_GLYPHS, arm, half, scale)
+            assert np.array_equal(g["overlay"], want)
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
