@@ -17,7 +17,6 @@
 #include <new>
 #include <stdexcept>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <pthread.h>
 #include <sched.h>
@@ -443,8 +442,9 @@ struct Builder {
     threads.reserve(n);
     try {
       for (size_t i = 1; i < n; ++i) threads.emplace_back(work);
-    } catch (const std::system_error&) {
-      // no more threads to be had: those that there are do the work
+    } catch (...) {
+      // no more threads to be had (system_error), or no memory for one's state (bad_alloc): those that
+      // there are do the work
     }
     work();
     for (std::thread& x : threads) x.join();

@@ -1,0 +1,68 @@
+// Host code of the library against the stand-in runtime: `host_double_main <check>` exits 0 when the
+// check holds, prints what does not and exits 1 otherwise.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <string>
+#include <vector>
+
+#include "fake_hip.h"
+#include "hs.h"
+
+#define CHECK(cond)                                                                \
+  do {                                                                             \
+    if (!(cond)) {                                                                 \
+      printf("line %d: %s does not hold (%s)\n", __LINE__, #cond, hs_last_error()); \
+      exit(1);                                                                     \
+    }                                                                              \
+  } while (0)
+
+struct Program {   // what a program has in hand before it creates an application
+  hs_ctx* ctx = nullptr;
+  hs_app_desc d;
+  std::vector<float> weights;
+  void* workspace = nullptr;
+  std::vector<uint8_t> frame, out;
+  explicit Program(int net) : frame(64 * 48 * 3 + 16), out(64 * 48 * 3 + 16) {
+    CHECK(hs_init(0, &ctx) == HS_OK);
+    memset(&d, 0, sizeof(d));
+    d.frame_w = 64; d.frame_h = 48; d.frame_pitch = 192;
+    d.net_w = 40; d.net_h = 24; d.net = net;
+    d.mean = 0.5f; d.std = 0.25f; d.threshold = 0.5f; d.alpha = 0.5f;
+    d.queue_depth = 2; d.batch = 1; d.glyph_scale = 1;
+    size_t need = 0;
+    CHECK(hs_query_workspace(&d, &need) == HS_OK);
+    workspace = aligned_alloc(256, (need + 255) / 256 * 256);
+    d.d_workspace = workspace; d.workspace_bytes = need;
+    weights.assign(net == HS_NET_TINY4 ? 16 * 27 + 32 * 144 + 32 * 288 + 8 * 288 : 18246848, 0.01f);
+    d.weights = weights.data(); d.weight_floats = weights.size();
+  }
+  const uint8_t* src() { return (const uint8_t*)(((uintptr_t)frame.data() + 15) & ~(uintptr_t)15); }
+  uint8_t* dst() { return (uint8_t*)(((uintptr_t)out.data() + 15) & ~(uintptr_t)15); }
+  ~Program() {
+    CHECK(hs_shutdown(ctx) == HS_OK);
+    free(workspace);
+  }
+};
+
+// A packing thread whose own state cannot be allocated, or that the system refuses to start: the
+// threads that there are do the work.
+static void packing_threads() {
+  Program p(HS_NET_RESNET18_CONVLSTM);
+  hs_app* app = nullptr;
+  fake::fail_block_after_thread_start = true;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  CHECK(hs_destroy_app(app) == HS_OK);
+  fake::reset_failures();
+  fake::threads_until_failure = 2;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  CHECK(hs_destroy_app(app) == HS_OK);
+}
+
+int main(int argc, char** argv) {
+  const std::string check = argc > 1 ? argv[1] : "";
+  if (check == "packing_threads") packing_threads();
+  else { printf("no check named '%s'\n", check.c_str()); return 2; }
+  return 0;
+}

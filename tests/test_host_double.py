@@ -1,0 +1,31 @@
+"""Host code of the library (csrc/hs_host.cpp, hs_lib.cpp, hs_driver.cpp) compiled against a stand-in
+for the HIP runtime (tests/host_double), on the CPU: what happens when memory or threads run out, and
+how the waiting calls wait.  Every check runs in a process of its own."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2402_04466_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "host_double")
+
+
+@pytest.fixture(scope="session")
+def host_double(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host_double") / "host_double")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
+    src = [os.path.join(build.CSRC, f) for f in ("hs_host.cpp", "hs_lib.cpp", "hs_driver.cpp")]
+    src += [os.path.join(HERE, f) for f in ("fake_hip.cpp", "host_double_main.cpp")]
+    subprocess.run([os.path.join(rocm, "llvm", "bin", "clang++"), "-std=c++17", "-O2", "-w",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"), "-I",
+                    os.path.join(ROOT, "include"), "-I", build.CSRC, *src, "-o", exe, "-lpthread", "-ldl"],
+                   check=True)
+    return exe
+
+
+@pytest.mark.parametrize("check", ["packing_threads"])
+def test_host_code(host_double, check):
+    r = subprocess.run([host_double, check], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stdout[-500:], r.stderr[-500:])
