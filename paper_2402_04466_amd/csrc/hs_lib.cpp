@@ -1278,6 +1278,36 @@ static void collect_timing(hs_app* app) {
   app->timed.clear();
 }
 
+// Waits for the application's frames and gives back everything it holds; one that is only half made
+// holds less.
+static void release_app(hs_app* app) {
+  (void)hipSetDevice(app->ctx->device);
+  {
+    std::lock_guard<std::mutex> lk(app->mu);
+    app->stop = true;
+  }
+  app->cv_work.notify_all();
+  if (app->completer.joinable()) app->completer.join();   // drains pending frames first
+  for (int l = 0; l < kMaxLanes; ++l)
+    if (app->s_lane[l]) (void)hipStreamSynchronize(app->s_lane[l]);
+  if (app->s_overlay) (void)hipStreamSynchronize(app->s_overlay);
+  collect_timing(app);
+  for (Slot& s : app->slots) {
+    if (s.graph_exec) (void)hipGraphExecDestroy(s.graph_exec);
+    if (s.graph) (void)hipGraphDestroy(s.graph);
+    for (hipEvent_t ev : {s.ev_pre, s.ev_infer, s.ev_post, s.ev_overlay})
+      if (ev) (void)hipEventDestroy(ev);
+  }
+  destroy_streams(app);
+  if (app->pinned) (void)hipHostFree(app->pinned);
+  {
+    std::lock_guard<std::mutex> lk(app->ctx->mu);
+    auto& v = app->ctx->apps;
+    v.erase(std::remove(v.begin(), v.end(), app), v.end());
+  }
+  delete app;
+}
+
 // done: event that completes with the last of the launched ops.
 static hs_status run_ops(hs_app* app, std::vector<Op>& ops, hipStream_t st, hipEvent_t done,
                          size_t first = 0, size_t last = (size_t)-1) {
@@ -1514,41 +1544,28 @@ hs_status hs_create_app(hs_ctx* ctx, const hs_app_desc* desc, hs_app** out) {
     return HS_E_INVAL;
   }
   HS_HIP(hipSetDevice(ctx->device));
-  hs_app* app = new (std::nothrow) hs_app();
-  if (!app) { set_error("hs_create_app: out of host memory"); return HS_E_NOMEM; }
+  // whatever ends this call early, an exception included, gives back what has been made so far
+  std::unique_ptr<hs_app, void (*)(hs_app*)> app(new hs_app(), release_app);
   app->ctx = ctx;
   app->desc = *desc;
   app->desc.weights = nullptr;   // not retained
   app->depth = desc->queue_depth;
   size_t need = 0;
-  st = build_plan(desc, app, &need);
+  st = build_plan(desc, app.get(), &need);
   for (size_t i = 0; st == HS_OK && i < app->slots.size(); ++i) {
     const size_t n_slots = app->slots.size();
     st = build_slot_graph(app->slots[i],
                           n_slots > 1 ? app->slots[(i + n_slots - 1) % n_slots].ev_infer : nullptr);
   }
-  if (st == HS_OK) st = make_streams(app, nullptr, nullptr, 0);
-  if (st != HS_OK) {
-    for (Slot& s : app->slots) {
-      if (s.graph_exec) (void)hipGraphExecDestroy(s.graph_exec);
-      if (s.graph) (void)hipGraphDestroy(s.graph);
-      if (s.ev_pre) (void)hipEventDestroy(s.ev_pre);
-      if (s.ev_infer) (void)hipEventDestroy(s.ev_infer);
-      if (s.ev_post) (void)hipEventDestroy(s.ev_post);
-      if (s.ev_overlay) (void)hipEventDestroy(s.ev_overlay);
-    }
-    destroy_streams(app);
-    if (app->pinned) (void)hipHostFree(app->pinned);
-    delete app;
-    return st;
-  }
-  app->completer = std::thread(completer_main, app);
+  if (st == HS_OK) st = make_streams(app.get(), nullptr, nullptr, 0);
+  if (st != HS_OK) return st;
+  app->completer = std::thread(completer_main, app.get());
   {
     std::lock_guard<std::mutex> lk(ctx->mu);
+    ctx->apps.push_back(app.get());
     app->home_lane = (int)(ctx->n_created++ / 2 % (unsigned)app->lanes);
-    ctx->apps.push_back(app);
   }
-  *out = app;
+  *out = app.release();
   return HS_OK;
   });
 }
@@ -1556,33 +1573,7 @@ hs_status hs_create_app(hs_ctx* ctx, const hs_app_desc* desc, hs_app** out) {
 hs_status hs_destroy_app(hs_app* app) {
   if (!app) { set_error("hs_destroy_app: NULL"); return HS_E_INVAL; }
   if (app->group) { set_error("hs_destroy_app: destroy the application's group first"); return HS_E_STATE; }
-  (void)hipSetDevice(app->ctx->device);
-  {
-    std::lock_guard<std::mutex> lk(app->mu);
-    app->stop = true;
-  }
-  app->cv_work.notify_all();
-  if (app->completer.joinable()) app->completer.join();   // drains pending frames first
-  for (int l = 0; l < kMaxLanes; ++l)
-    if (app->s_lane[l]) (void)hipStreamSynchronize(app->s_lane[l]);
-  if (app->s_overlay) (void)hipStreamSynchronize(app->s_overlay);
-  collect_timing(app);
-  for (Slot& s : app->slots) {
-    if (s.graph_exec) (void)hipGraphExecDestroy(s.graph_exec);
-    if (s.graph) (void)hipGraphDestroy(s.graph);
-    (void)hipEventDestroy(s.ev_pre);
-    (void)hipEventDestroy(s.ev_infer);
-    (void)hipEventDestroy(s.ev_post);
-    (void)hipEventDestroy(s.ev_overlay);
-  }
-  destroy_streams(app);
-  if (app->pinned) (void)hipHostFree(app->pinned);
-  {
-    std::lock_guard<std::mutex> lk(app->ctx->mu);
-    auto& v = app->ctx->apps;
-    v.erase(std::remove(v.begin(), v.end(), app), v.end());
-  }
-  delete app;
+  release_app(app);
   return HS_OK;
 }
 

@@ -60,9 +60,36 @@ static void packing_threads() {
   CHECK(hs_destroy_app(app) == HS_OK);
 }
 
+// Every allocation of a create call fails once, then every thread start: an error code, and nothing
+// of the half-made application is left.
+static void create_failures() {
+  for (int threads = 0; threads < 2; ++threads) {
+    Program p(HS_NET_TINY4);
+    const long objects = fake::live_objects, blocks = fake::live_blocks;
+    for (long n = 0;; ++n) {
+      hs_app* app = nullptr;
+      (threads ? fake::threads_until_failure : fake::blocks_until_failure) = n;
+      const hs_status st = hs_create_app(p.ctx, &p.d, &app);
+      const bool reached = (threads ? fake::threads_until_failure : fake::blocks_until_failure) < 0;
+      fake::reset_failures();
+      if (!reached) {               // the call needs no more than n
+        CHECK(st == HS_OK && n > 0);
+        CHECK(hs_destroy_app(app) == HS_OK);
+        break;
+      }
+      CHECK(st == HS_E_NOMEM || st == HS_E_DEVICE);
+      CHECK(app == nullptr);
+      CHECK(fake::live_objects == objects);
+      // (the context's list of applications may have grown its storage)
+      CHECK(fake::live_blocks <= blocks + 1);
+    }
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
+  else if (check == "create_failures") create_failures();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
