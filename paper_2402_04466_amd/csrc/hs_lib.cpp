@@ -964,7 +964,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
   std::vector<std::unique_ptr<Builder>> extra;
   std::vector<Builder*> lane_b{&b};
   for (int l = 1; l < lanes; ++l) {
-    extra.emplace_back(new Builder(*d, create ? d->d_workspace : nullptr, false, true));
+    extra.push_back(std::make_unique<Builder>(*d, create ? d->d_workspace : nullptr, false, true));
     Builder& bl = *extra.back();
     bl.carve.off = lane_b.back()->carve.off;
     bl.d_w = b.d_w;
