@@ -244,6 +244,15 @@ struct GroupWorker {
   std::string error;
   Slot* slot = nullptr;
   hipStream_t tail = nullptr;
+
+  ~GroupWorker() {   // ends the thread, once its job is done
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      stop = true;
+    }
+    cv.notify_all();
+    if (th.joinable()) th.join();
+  }
 };
 
 struct hs_group {
@@ -2033,8 +2042,7 @@ hs_status hs_create_group(hs_ctx* ctx, hs_app* const* members, int n_members, hs
       return HS_E_STATE;
     }
   }
-  hs_group* g = new (std::nothrow) hs_group();
-  if (!g) { set_error("hs_create_group: out of host memory"); return HS_E_NOMEM; }
+  std::unique_ptr<hs_group> g(new hs_group());
   g->ctx = ctx;
   g->members.assign(members, members + n_members);
   // the frame-level fields of the overlay launch come from member 0; layers are set per frame
@@ -2045,13 +2053,13 @@ hs_status hs_create_group(hs_ctx* ctx, hs_app* const* members, int n_members, hs
   o.bytes = 6.0 * members[0]->desc.frame_w * members[0]->desc.frame_h + map_bytes;
   g->overlay.push_back(o);
   for (int i = 1; i < n_members; ++i) {
-    g->workers.emplace_back(new GroupWorker());
+    g->workers.push_back(std::make_unique<GroupWorker>());
     GroupWorker* w = g->workers.back().get();
     w->app = members[i];
     w->th = std::thread(group_worker_main, w, ctx->device);
   }
-  for (hs_app* a : g->members) a->group = g;
-  *out = g;
+  for (hs_app* a : g->members) a->group = g.get();
+  *out = g.release();
   return HS_OK;
   });
 }
@@ -2062,14 +2070,7 @@ hs_status hs_destroy_group(hs_group* group) {
     std::unique_lock<std::mutex> lk(a->mu);
     a->cv_done.wait(lk, [&] { return a->n_completed == a->n_submitted; });
   }
-  for (auto& w : group->workers) {
-    {
-      std::lock_guard<std::mutex> lk(w->mu);
-      w->stop = true;
-    }
-    w->cv.notify_all();
-    w->th.join();
-  }
+  group->workers.clear();              // ends their threads
   for (hs_app* a : group->members) a->group = nullptr;
   delete group;
   return HS_OK;

@@ -19,7 +19,7 @@
 #include "hs_kernels.h"
 
 namespace fake {
-std::atomic<long> live_objects{0}, live_blocks{0};
+std::atomic<long> live_objects{0}, live_blocks{0}, live_threads{0};
 std::atomic<long> event_wait_ns{0};
 std::atomic<long> blocks_until_failure{-1}, threads_until_failure{-1};
 std::atomic<bool> fail_block_after_thread_start{false};
@@ -56,11 +56,22 @@ void operator delete(void* p, size_t) noexcept { give_block(p); }
 void operator delete[](void* p, size_t) noexcept { give_block(p); }
 void operator delete(void* p, const std::nothrow_t&) noexcept { give_block(p); }
 
+struct Start { void* (*f)(void*); void* x; };
+static void* counted(void* p) {
+  const Start s = *(Start*)p;
+  free(p);
+  void* r = s.f(s.x);
+  --live_threads;
+  return r;
+}
 extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* x) {
   using Fn = int (*)(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*);
   static Fn real = (Fn)dlsym(RTLD_NEXT, "pthread_create");
   if (threads_until_failure >= 0 && threads_until_failure.fetch_sub(1) == 0) return EAGAIN;
-  const int rc = real(t, a, f, x);
+  Start* s = (Start*)malloc(sizeof(Start));
+  *s = Start{f, x};
+  ++live_threads;
+  const int rc = real(t, a, counted, s);
   if (rc == 0 && fail_block_after_thread_start.exchange(false)) fail_next_block = true;
   return rc;
 }

@@ -87,10 +87,39 @@ static void create_failures() {
   }
 }
 
+// The same for a group of three: no thread and no memory of it is left, and its members are free.
+static void group_failures() {
+  Program p(HS_NET_TINY4);
+  Program p2(HS_NET_TINY4), p3(HS_NET_TINY4);
+  hs_app* m[3];
+  CHECK(hs_create_app(p.ctx, &p.d, &m[0]) == HS_OK);
+  CHECK(hs_create_app(p.ctx, &p2.d, &m[1]) == HS_OK);
+  CHECK(hs_create_app(p.ctx, &p3.d, &m[2]) == HS_OK);
+  const long blocks = fake::live_blocks, running = fake::live_threads;
+  for (int threads = 0; threads < 2; ++threads)
+    for (long n = 0;; ++n) {
+      hs_group* g = nullptr;
+      (threads ? fake::threads_until_failure : fake::blocks_until_failure) = n;
+      const hs_status st = hs_create_group(p.ctx, m, 3, &g);
+      const bool reached = (threads ? fake::threads_until_failure : fake::blocks_until_failure) < 0;
+      fake::reset_failures();
+      if (!reached) {
+        CHECK(st == HS_OK && n > 0);
+        CHECK(hs_destroy_group(g) == HS_OK);
+        break;
+      }
+      CHECK(st == HS_E_NOMEM || st == HS_E_DEVICE);
+      CHECK(fake::live_blocks == blocks);
+      CHECK(fake::live_threads == running);
+    }
+  for (hs_app* a : m) CHECK(hs_destroy_app(a) == HS_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
   else if (check == "create_failures") create_failures();
+  else if (check == "group_failures") group_failures();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
