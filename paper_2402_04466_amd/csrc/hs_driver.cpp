@@ -333,8 +333,18 @@ extern "C" hs_status hs_run_feeds(const hs_feed* feeds, int n_feeds, double fps,
       w.period = fps > 0.0 ? (uint64_t)(1e9 / fps) : 0;
     }
     const uint64_t t_begin = now_ns();
-    for (int i = 0; i < n_feeds; ++i) threads.emplace_back(worker_main, &workers[(size_t)i]);
+    threads.reserve((size_t)n_feeds);
+    std::string not_started;     // a source whose thread cannot be had; those that run are seen to their end
+    try {
+      for (int i = 0; i < n_feeds; ++i) threads.emplace_back(worker_main, &workers[(size_t)i]);
+    } catch (const std::exception& e) {
+      not_started = e.what();
+    }
     for (std::thread& t : threads) t.join();
+    if (threads.size() < (size_t)n_feeds) {
+      set_error("hs_run_feeds: no thread for feed %zu: %s", threads.size(), not_started.c_str());
+      return HS_E_NOMEM;
+    }
     if (elapsed_s) *elapsed_s = (double)(now_ns() - t_begin) * 1e-9;
     hs_status st = HS_OK;
     for (int i = 0; i < n_feeds; ++i) {

@@ -115,11 +115,43 @@ static void group_failures() {
   for (hs_app* a : m) CHECK(hs_destroy_app(a) == HS_OK);
 }
 
+// A source whose thread cannot be started: the sources that run are seen to their end, the call
+// reports it, and the applications can be used and destroyed.
+static void feed_failures() {
+  Program p(HS_NET_TINY4), p2(HS_NET_TINY4), p3(HS_NET_TINY4);
+  Program* all[3] = {&p, &p2, &p3};
+  hs_feed feeds[3];
+  memset(feeds, 0, sizeof(feeds));
+  const uint8_t* src[3];
+  uint8_t* dst[3];
+  hs_result out[3][4];
+  hs_result* results[3];
+  for (int i = 0; i < 3; ++i) {
+    CHECK(hs_create_app(p.ctx, &all[i]->d, &feeds[i].app) == HS_OK);
+    src[i] = all[i]->src(); dst[i] = all[i]->dst();
+    feeds[i].d_frames = &src[i]; feeds[i].d_outs = &dst[i];
+    feeds[i].n_frames = feeds[i].n_outs = feeds[i].batch = feeds[i].results_per_frame = 1;
+    feeds[i].cpu = -1;
+    results[i] = out[i];
+  }
+  for (long n = 0; n < 3; ++n) {
+    fake::threads_until_failure = n;
+    CHECK(hs_run_feeds(feeds, 3, 0.0, 4, results, nullptr, nullptr, nullptr) == HS_E_NOMEM);
+    fake::reset_failures();
+  }
+  fake::fail_block_after_thread_start = true;
+  CHECK(hs_run_feeds(feeds, 3, 0.0, 4, results, nullptr, nullptr, nullptr) == HS_E_NOMEM);
+  fake::reset_failures();
+  CHECK(hs_run_feeds(feeds, 3, 0.0, 4, results, nullptr, nullptr, nullptr) == HS_OK);
+  for (hs_feed& f : feeds) CHECK(hs_destroy_app(f.app) == HS_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
   else if (check == "create_failures") create_failures();
   else if (check == "group_failures") group_failures();
+  else if (check == "feed_failures") feed_failures();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
