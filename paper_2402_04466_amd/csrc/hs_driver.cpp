@@ -17,7 +17,6 @@
 #include <deque>
 #include <mutex>
 #include <new>
-#include <string>
 #include <thread>
 #include <vector>
 
@@ -228,7 +227,7 @@ struct Worker {
   uint64_t t0 = 0, period = 0;    // period 0: back to back
   int dropped = 0;
   hs_status status = HS_OK;
-  std::string error;
+  hs::Message error;
 };
 
 hs_status feed_submit(const hs_feed* f, int k) {
@@ -262,7 +261,7 @@ void worker_main(Worker* w) {
   int got = 0;   // frames whose results have been collected, in order
   auto fail = [&](hs_status st) {
     w->status = st;
-    w->error = hs_last_error();
+    w->error.set(hs_last_error());
   };
   auto slot = [&](int i) { return w->results + (size_t)i * w->per_frame; };
   for (int k = 0; k < w->n_frames; ++k) {
@@ -334,15 +333,15 @@ extern "C" hs_status hs_run_feeds(const hs_feed* feeds, int n_feeds, double fps,
     }
     const uint64_t t_begin = now_ns();
     threads.reserve((size_t)n_feeds);
-    std::string not_started;     // a source whose thread cannot be had; those that run are seen to their end
+    hs::Message not_started;     // a source whose thread cannot be had; those that run are seen to their end
     try {
       for (int i = 0; i < n_feeds; ++i) threads.emplace_back(worker_main, &workers[(size_t)i]);
     } catch (const std::exception& e) {
-      not_started = e.what();
+      not_started.set(e.what());
     }
     for (std::thread& t : threads) t.join();
     if (threads.size() < (size_t)n_feeds) {
-      set_error("hs_run_feeds: no thread for feed %zu: %s", threads.size(), not_started.c_str());
+      set_error("hs_run_feeds: no thread for feed %zu: %s", threads.size(), not_started.text);
       return HS_E_NOMEM;
     }
     if (elapsed_s) *elapsed_s = (double)(now_ns() - t_begin) * 1e-9;
@@ -351,7 +350,7 @@ extern "C" hs_status hs_run_feeds(const hs_feed* feeds, int n_feeds, double fps,
       if (dropped) dropped[i] = workers[(size_t)i].dropped;
       if (st == HS_OK && workers[(size_t)i].status != HS_OK) {
         st = workers[(size_t)i].status;
-        set_error("hs_run_feeds: feed %d: %s", i, workers[(size_t)i].error.c_str());
+        set_error("hs_run_feeds: feed %d: %s", i, workers[(size_t)i].error.text);
       }
     }
     return st;

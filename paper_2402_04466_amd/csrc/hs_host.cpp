@@ -95,6 +95,7 @@ hs_status hs_admission_check(const uint32_t* claimed_by_others, const uint32_t* 
 
 hs_status hs_latency_metrics_compute(const double* lat, size_t n, int trim,
                                      hs_latency_metrics* out) {
+  return hs::guarded("latency metrics", [&]() -> hs_status {
   if (!lat || !out) {
     hs::set_error("latency metrics: NULL argument");
     return HS_E_INVAL;
@@ -121,9 +122,11 @@ hs_status hs_latency_metrics_compute(const double* lat, size_t n, int trim,
   out->tail = s.back() - hs::percentile_sorted(s, 95.0);
   out->flatness = hs::percentile_sorted(s, 90.0) - hs::percentile_sorted(s, 10.0);
   return HS_OK;
+  });
 }
 
 hs_status hs_mann_whitney_u(const double* a, size_t na, const double* b, size_t nb, hs_mwu* out) {
+  return hs::guarded("mann-whitney", [&]() -> hs_status {
   if (!a || !b || !out || na == 0 || nb == 0) {
     hs::set_error("mann-whitney: NULL or empty sample");
     return HS_E_INVAL;
@@ -158,6 +161,7 @@ hs_status hs_mann_whitney_u(const double* a, size_t na, const double* b, size_t 
   out->z = z;
   out->significant = std::fabs(z) > 1.96 ? 1 : 0;
   return HS_OK;
+  });
 }
 
 }  // extern "C"

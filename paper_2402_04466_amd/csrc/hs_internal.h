@@ -2,6 +2,10 @@
 #pragma once
 
 #include <stdint.h>
+#include <stdio.h>
+
+#include <exception>
+#include <new>
 
 #include "hs.h"
 
@@ -18,6 +22,28 @@ int xcd_count(int device_cus);
 // another application; HS_E_INVAL for bad arguments or a mask without a CU on every XCD.
 hs_status admission_check(const uint32_t* claimed, const uint32_t* req_a, const uint32_t* req_b,
                           int n_words, int device_cus);
+
+// An error text that can be kept where no memory is to be had.
+struct Message {
+  char text[512] = "";
+  bool empty() const { return text[0] == 0; }
+  void set(const char* a, const char* b = "", const char* c = "") { snprintf(text, sizeof(text), "%s%s%s", a, b, c); }
+};
+
+// No C++ exception may cross the C boundary: calls that allocate host memory or start threads
+// run inside this guard.
+template <class F>
+hs_status guarded(const char* fn, F&& body) {
+  try {
+    return body();
+  } catch (const std::bad_alloc&) {
+    set_error("%s: out of host memory", fn);
+    return HS_E_NOMEM;
+  } catch (const std::exception& e) {
+    set_error("%s: %s", fn, e.what());
+    return HS_E_DEVICE;
+  }
+}
 
 }  // namespace hs
 

@@ -16,7 +16,6 @@
 #include <mutex>
 #include <new>
 #include <stdexcept>
-#include <string>
 #include <thread>
 #include <pthread.h>
 #include <sched.h>
@@ -212,7 +211,7 @@ struct hs_app {
   std::atomic<uint64_t> completed_pub{0};   // n_completed for waiters that spin without the lock
   std::thread completer;
   bool stop = false;
-  std::string completer_error;
+  Message completer_error;
   int launch_mode = HS_LAUNCH_EAGER;
   // kernel timing
   bool timing = false;
@@ -241,7 +240,7 @@ struct GroupWorker {
   uint64_t frame_id = 0, t_submit = 0;
   // its outcome
   hs_status status = HS_OK;
-  std::string error;
+  Message error;
   Slot* slot = nullptr;
   hipStream_t tail = nullptr;
 
@@ -1204,7 +1203,7 @@ static void completer_main(hs_app* app) {
     {
       std::lock_guard<std::mutex> lk(app->mu);
       if (e != hipSuccess && app->completer_error.empty())
-        app->completer_error = hipGetErrorString(e);
+        app->completer_error.set(hipGetErrorString(e));
       s->state = SLOT_DONE;
       app->n_completed++;
       app->completed_pub.store(app->n_completed, std::memory_order_release);
@@ -1275,14 +1274,14 @@ static bool frames_in_flight(hs_app* app) {
 static void collect_timing(hs_app* app) {
   for (TimedLaunch& t : app->timed) {
     float ms = 0;
-    if (hipEventSynchronize(t.e1) == hipSuccess && hipEventElapsedTime(&ms, t.e0, t.e1) == hipSuccess) {
+    if (t.e1 && hipEventSynchronize(t.e1) == hipSuccess && hipEventElapsedTime(&ms, t.e0, t.e1) == hipSuccess) {
       app->acc_ms[t.fam] += ms;
       app->acc_flops[t.fam] += t.flops;
       app->acc_bytes[t.fam] += t.bytes;
       app->acc_n[t.fam] += 1;
     }
-    (void)hipEventDestroy(t.e0);
-    (void)hipEventDestroy(t.e1);
+    if (t.e0) (void)hipEventDestroy(t.e0);
+    if (t.e1) (void)hipEventDestroy(t.e1);
   }
   app->timed.clear();
 }
@@ -1324,7 +1323,8 @@ static hs_status run_ops(hs_app* app, std::vector<Op>& ops, hipStream_t st, hipE
   for (size_t i = first; i < last; ++i) {
     Op& op = ops[i];
     if (app->timing) {
-      TimedLaunch t{op.fam, op.flops, op.bytes, nullptr, nullptr};
+      app->timed.push_back(TimedLaunch{op.fam, op.flops, op.bytes, nullptr, nullptr});
+      TimedLaunch& t = app->timed.back();
       HS_HIP(hipEventCreate(&t.e0));
       HS_HIP(hipEventCreate(&t.e1));
       // events attached to the dispatch itself: elapsed = the kernel's own begin -> end
@@ -1332,7 +1332,6 @@ static hs_status run_ops(hs_app* app, std::vector<Op>& ops, hipStream_t st, hipE
       const KernelDesc d = op_desc(op);
       void* args[1] = {op_params(op)};
       HS_HIP(hipExtLaunchKernel(d.func, d.grid, d.block, args, d.shmem, st, t.e0, t.e1, 0));
-      app->timed.push_back(t);
     } else {
       HS_HIP(launch_op(op, st, i + 1 == last ? done : nullptr));
     }
@@ -1397,31 +1396,13 @@ static hs_status build_slot_graph(Slot& s, hipEvent_t wait_ev) {
 }  // namespace hs
 
 // ================================================================================================
-// No C++ exception may cross the C boundary: calls that allocate host memory or start threads
-// run inside this guard.
-template <class F>
-static hs_status guarded(const char* fn, F&& body) {
-  try {
-    return body();
-  } catch (const std::bad_alloc&) {
-    hs::set_error("%s: out of host memory", fn);
-    return HS_E_NOMEM;
-  } catch (const std::exception& e) {
-    hs::set_error("%s: %s", fn, e.what());
-    return HS_E_DEVICE;
-  }
-}
-
-extern "C" {
-
-}  // extern "C"
-
 int hs_internal_app_batch(const hs_app* app) { return app->batch; }
 int hs_internal_app_grouped(const hs_app* app) { return app->group != nullptr; }
 
 extern "C" {
 
 hs_status hs_init(int device, hs_ctx** out) {
+  return guarded("hs_init", [&]() -> hs_status {
   if (!out) { set_error("hs_init: NULL out"); return HS_E_INVAL; }
   *out = nullptr;
   int n = 0;
@@ -1459,6 +1440,7 @@ hs_status hs_init(int device, hs_ctx** out) {
   }
   *out = c;
   return HS_OK;
+  });
 }
 
 hs_status hs_shutdown(hs_ctx* ctx) {
@@ -1608,6 +1590,7 @@ hs_status hs_reset_state(hs_app* app) {
 }
 
 hs_status hs_get_state(hs_app* app, int stream, float* h_out, float* c_out) {
+  return guarded("hs_get_state", [&]() -> hs_status {
   if (!app) { set_error("hs_get_state: NULL"); return HS_E_INVAL; }
   if (!app->stateful) { set_error("hs_get_state: network has no recurrent state"); return HS_E_INVAL; }
   if (stream < 0 || stream >= app->batch) { set_error("hs_get_state: no stream %d", stream); return HS_E_INVAL; }
@@ -1633,9 +1616,11 @@ hs_status hs_get_state(hs_app* app, int stream, float* h_out, float* c_out) {
         h_out[(size_t)j * n + m] = (float)tmp[m * app->concat_pitch + app->x_ch + j];
   }
   return HS_OK;
+  });
 }
 
 hs_status hs_get_features(hs_app* app, int stream, float* x_out) {
+  return guarded("hs_get_features", [&]() -> hs_status {
   if (!app || !x_out) { set_error("hs_get_features: NULL"); return HS_E_INVAL; }
   if (!app->stateful) { set_error("hs_get_features: network has no recurrent cell"); return HS_E_INVAL; }
   if (stream < 0 || stream >= app->batch) { set_error("hs_get_features: no stream %d", stream); return HS_E_INVAL; }
@@ -1650,6 +1635,7 @@ hs_status hs_get_features(hs_app* app, int stream, float* x_out) {
     for (int j = 0; j < app->x_ch; ++j)
       x_out[(size_t)j * n + m] = (float)tmp[m * app->concat_pitch + j];
   return HS_OK;
+  });
 }
 
 hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
@@ -1713,8 +1699,7 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
 static void poison(hs_app* app, const char* what) {
   std::lock_guard<std::mutex> lk(app->mu);
   if (app->completer_error.empty())
-    app->completer_error = std::string("a submit failed after work had been enqueued (") + what +
-                           "); destroy the application";
+    app->completer_error.set("a submit failed after work had been enqueued (", what, "); destroy the application");
 }
 
 static hs_status submit_stages(hs_app* app, const uint8_t* const* d_frames,
@@ -1737,7 +1722,7 @@ static hs_status submit_stages(hs_app* app, const uint8_t* const* d_frames,
   {
     std::lock_guard<std::mutex> lk(app->mu);
     if (!app->completer_error.empty()) {
-      set_error("device error in an earlier frame: %s", app->completer_error.c_str());
+      set_error("device error in an earlier frame: %s", app->completer_error.text);
       return HS_E_DEVICE;
     }
     if (app->n_submitted - app->n_delivered >= (uint64_t)app->depth) {
@@ -1752,9 +1737,10 @@ static hs_status submit_stages(hs_app* app, const uint8_t* const* d_frames,
       return HS_E_STATE;
     }
   }
-  const hs_status st = enqueue_stages(app, s, idle, d_frames, d_overlay_outs, frame_id, t_submit,
-                                      own_overlay, slot_out, stream_out, frames_ready,
-                                      static_scratch);
+  const hs_status st = guarded("hs_submit_batch", [&] {    // timed launches are noted in a list that grows
+    return enqueue_stages(app, s, idle, d_frames, d_overlay_outs, frame_id, t_submit, own_overlay,
+                          slot_out, stream_out, frames_ready, static_scratch);
+  });
   if (st != HS_OK) poison(app, hs_last_error());
   return st;
 }
@@ -1916,7 +1902,7 @@ static hs_status deliver_locked(hs_app* app, hs_result* out) {
   s.state = SLOT_FREE;
   app->n_delivered++;
   if (!app->completer_error.empty()) {
-    set_error("device error: %s", app->completer_error.c_str());
+    set_error("device error: %s", app->completer_error.text);
     return HS_E_DEVICE;
   }
   return HS_OK;
@@ -2010,7 +1996,7 @@ static void group_worker_main(GroupWorker* w, int device) {
     {
       std::lock_guard<std::mutex> lk(w->mu);
       w->status = st;
-      if (st != HS_OK) w->error = hs_last_error();
+      if (st != HS_OK) w->error.set(hs_last_error());
       w->done = true;
     }
     w->cv.notify_all();
@@ -2086,7 +2072,7 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
     hs_app* a = group->members[i];
     std::lock_guard<std::mutex> lk(a->mu);
     if (!a->completer_error.empty()) {
-      set_error("device error in an earlier frame: %s", a->completer_error.c_str());
+      set_error("device error in an earlier frame: %s", a->completer_error.text);
       return HS_E_DEVICE;
     }
     if (a->n_submitted - a->n_delivered >= (uint64_t)a->depth) {
@@ -2109,7 +2095,8 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   }
   hs_status st0 = submit_stages(group->members[0], &d_frame, &d_overlay_out, frame_id, t_submit,
                                 false, &slot[0], &tail[0]);
-  std::string err0 = st0 != HS_OK ? hs_last_error() : "";
+  Message err0;
+  if (st0 != HS_OK) err0.set(hs_last_error());
   for (size_t i = 1; i < n; ++i) {   // always collect every worker, also after a failure
     GroupWorker* w = group->workers[i - 1].get();
     std::unique_lock<std::mutex> lk(w->mu);
@@ -2120,12 +2107,13 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   // From here on a failure leaves some members a frame ahead of the others (their cells have
   // been updated by a frame that will never be delivered): the whole group is poisoned.
   auto fail_all = [&](hs_status st) {
-    const std::string why = hs_last_error();
-    for (hs_app* a : group->members) poison(a, why.c_str());
-    set_error("%s", why.c_str());
+    Message why;
+    why.set(hs_last_error());
+    for (hs_app* a : group->members) poison(a, why.text);
+    set_error("%s", why.text);
     return st;
   };
-  if (st0 != HS_OK) { set_error("%s", err0.c_str()); return fail_all(st0); }
+  if (st0 != HS_OK) { set_error("%s", err0.text); return fail_all(st0); }
   op.n_max = 0;
   for (size_t i = 0; i < n; ++i) {
     op.layer[i] = slot[i]->overlay[0].overlay.layer[0];
@@ -2142,7 +2130,7 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
     for (size_t i = 1; i < n; ++i) slot[i]->ev_done = slot[0]->ev_overlay;
     return run_ops(a0, group->overlay, ov_stream, slot[0]->ev_overlay);
   };
-  const hs_status st = overlay_all();
+  const hs_status st = guarded("hs_submit_group", overlay_all);
   if (st != HS_OK) return fail_all(st);
   for (size_t i = 0; i < n; ++i) finish_submit(group->members[i], slot[i]);
   return HS_OK;

@@ -146,12 +146,51 @@ static void feed_failures() {
   for (hs_feed& f : feeds) CHECK(hs_destroy_app(f.app) == HS_OK);
 }
 
+// Every other call that allocates: a refused allocation is an error code.  A submit that fails after
+// work has been handed over leaves an application that says so.
+static void call_failures() {
+  hs_ctx* ctx = nullptr;
+  fake::blocks_until_failure = 0;
+  CHECK(hs_init(0, &ctx) == HS_E_NOMEM && ctx == nullptr);
+  fake::reset_failures();
+  const double x[3] = {1, 2, 3};
+  hs_latency_metrics lm;
+  hs_mwu u;
+  fake::blocks_until_failure = 0;
+  CHECK(hs_latency_metrics_compute(x, 3, 0, &lm) == HS_E_NOMEM);
+  fake::blocks_until_failure = 0;
+  CHECK(hs_mann_whitney_u(x, 3, x, 3, &u) == HS_E_NOMEM);
+  fake::reset_failures();
+
+  Program p(HS_NET_RESNET18_CONVLSTM), p2(HS_NET_TINY4);
+  hs_app *a = nullptr, *b = nullptr;
+  hs_result r[2];
+  CHECK(hs_create_app(p.ctx, &p.d, &a) == HS_OK && hs_create_app(p.ctx, &p2.d, &b) == HS_OK);
+  CHECK(hs_submit_frame(a, p.src(), p.dst(), 0) == HS_OK && hs_wait_result(a, r, 1000000000) == HS_OK);
+  std::vector<float> map((size_t)512 * r->map_w * r->map_h);
+  fake::blocks_until_failure = 0;
+  CHECK(hs_get_features(a, 0, map.data()) == HS_E_NOMEM);
+  fake::blocks_until_failure = 0;
+  CHECK(hs_get_state(a, 0, map.data(), nullptr) == HS_E_NOMEM);
+  fake::blocks_until_failure = 0;
+  CHECK(hs_get_state(a, 0, nullptr, map.data()) == HS_E_NOMEM);
+  fake::reset_failures();
+  CHECK(hs_set_kernel_timing(b, 1) == HS_OK);
+  fake::blocks_until_failure = 1;
+  CHECK(hs_submit_frame(b, p2.src(), p2.dst(), 0) == HS_E_NOMEM);
+  fake::reset_failures();
+  CHECK(hs_submit_frame(b, p2.src(), p2.dst(), 1) == HS_E_DEVICE);
+  CHECK(strstr(hs_last_error(), "destroy the application"));
+  CHECK(hs_destroy_app(b) == HS_OK && hs_destroy_app(a) == HS_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
   else if (check == "create_failures") create_failures();
   else if (check == "group_failures") group_failures();
   else if (check == "feed_failures") feed_failures();
+  else if (check == "call_failures") call_failures();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
