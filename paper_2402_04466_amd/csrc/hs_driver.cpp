@@ -15,6 +15,7 @@
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <list>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -47,27 +48,40 @@ struct hs_mux {
   // per submitted batch, in submit order: what to restore in its results
   struct Rec { std::vector<uint64_t> ids, t_submit; };
   std::deque<Rec> in_flight;
-  // finished batches not yet collected by every stream, oldest first
+  // finished batches not yet collected by every stream, oldest first, and room for further ones: a
+  // batch is delivered into room that is there already, so that filing it cannot fail
   struct Done { std::vector<hs_result> r; std::vector<char> taken; int n_taken = 0; };
-  std::deque<Done> done;
+  std::list<Done> done, room;
   bool draining = false;   // a thread is blocked in hs_wait_batch on behalf of all
-  std::vector<hs_result> tmp;
 };
 
-// Files the batch the application has just delivered into m->tmp (mux lock held).
-static void mux_file(hs_mux* m) {
-  hs_mux::Done d;
-  d.r = m->tmp;
-  d.taken.assign((size_t)m->batch, 0);
+// Room for one batch (mux lock held).
+static std::list<hs_mux::Done> mux_room(hs_mux* m) {
+  std::list<hs_mux::Done> one;
+  if (m->room.empty()) {
+    one.emplace_back();
+    one.front().r.resize((size_t)m->batch);
+    one.front().taken.resize((size_t)m->batch);
+  } else {
+    one.splice(one.end(), m->room, m->room.begin());
+  }
+  std::fill(one.front().taken.begin(), one.front().taken.end(), 0);
+  one.front().n_taken = 0;
+  return one;
+}
+
+// Files the batch the application has just delivered into `one` (mux lock held).
+static void mux_file(hs_mux* m, std::list<hs_mux::Done>& one) {
   if (!m->in_flight.empty()) {
     const hs_mux::Rec& rec = m->in_flight.front();
     for (int j = 0; j < m->batch; ++j) {
-      d.r[(size_t)j].frame_id = rec.ids[(size_t)j];
-      d.r[(size_t)j].t_submit_ns = rec.t_submit[(size_t)j];   // the stream's own arrival
+      hs_result& r = one.front().r[(size_t)j];
+      r.frame_id = rec.ids[(size_t)j];
+      r.t_submit_ns = rec.t_submit[(size_t)j];   // the stream's own arrival
     }
     m->in_flight.pop_front();
   }
-  m->done.push_back(std::move(d));
+  m->done.splice(m->done.end(), one);
 }
 
 // Oldest finished result of `stream`, if any (mux lock held).
@@ -78,7 +92,8 @@ static bool mux_take(hs_mux* m, int stream, hs_result* out) {
     out->t_observed_ns = now_ns();
     d.taken[(size_t)stream] = 1;
     ++d.n_taken;
-    while (!m->done.empty() && m->done.front().n_taken == m->batch) m->done.pop_front();
+    while (!m->done.empty() && m->done.front().n_taken == m->batch)
+      m->room.splice(m->room.end(), m->done, m->done.begin());
     return true;
   }
   return false;
@@ -107,7 +122,6 @@ extern "C" hs_status hs_create_mux(hs_app* app, int batch, hs_mux** out) {
     m->ids.assign((size_t)batch, 0);
     m->t_submit.assign((size_t)batch, 0);
     m->have.assign((size_t)batch, 0);
-    m->tmp.resize((size_t)batch);
     *out = m;
     return HS_OK;
   } catch (const std::exception& e) {
@@ -144,10 +158,14 @@ extern "C" hs_status hs_mux_submit(hs_mux* m, int stream, const uint8_t* d_frame
       ++m->n_have;
       return HS_OK;
     }
-    // the last frame of the batch: hand the batch to the application
-    const hs_status st = hs_submit_batch(m->app, m->frames.data(), m->outs.data(), m->n_batches);
-    if (st != HS_OK) return st;   // this frame was not taken; the others keep waiting
+    // the last frame of the batch: hand the batch to the application.  It is noted first: once it has
+    // been handed over nothing may fail
     m->in_flight.push_back(hs_mux::Rec{m->ids, m->t_submit});
+    const hs_status st = hs_submit_batch(m->app, m->frames.data(), m->outs.data(), m->n_batches);
+    if (st != HS_OK) {   // this frame was not taken; the others keep waiting
+      m->in_flight.pop_back();
+      return st;
+    }
     ++m->n_batches;
     std::fill(m->have.begin(), m->have.end(), 0);
     m->n_have = 0;
@@ -166,10 +184,12 @@ extern "C" hs_status hs_mux_poll(hs_mux* m, int stream, hs_result* out) {
     for (;;) {
       if (mux_take(m, stream, out)) return HS_OK;
       if (m->draining) break;   // another thread is fetching: it will file what it gets
-      const hs_status st = hs_poll_batch(m->app, m->tmp.data());
+      auto one = mux_room(m);
+      const hs_status st = hs_poll_batch(m->app, one.front().r.data());
+      if (st == HS_OK) { mux_file(m, one); continue; }
+      m->room.splice(m->room.end(), one);
       if (st == HS_E_NOT_READY) break;
-      if (st != HS_OK) return st;
-      mux_file(m);
+      return st;
     }
     set_error("hs_mux_poll: no finished frame for stream %d", stream);
     return HS_E_NOT_READY;
@@ -196,19 +216,19 @@ extern "C" hs_status hs_mux_wait(hs_mux* m, int stream, hs_result* out, uint64_t
       }
       // fetch the next finished batch on behalf of every stream; one thread at a time talks to
       // the application, so batches are filed in the order they are delivered
-      hs_status st = hs_poll_batch(m->app, m->tmp.data());
+      auto one = mux_room(m);
+      hs_status st = hs_poll_batch(m->app, one.front().r.data());
       if (st == HS_E_NOT_READY) {
         m->draining = true;
         lk.unlock();
-        std::vector<hs_result> got((size_t)m->batch);
-        st = hs_wait_batch(m->app, got.data(), (uint64_t)std::min<int64_t>(left, 20000000));
+        st = hs_wait_batch(m->app, one.front().r.data(), (uint64_t)std::min<int64_t>(left, 20000000));
         lk.lock();
         m->draining = false;
-        if (st == HS_OK) m->tmp = got;
         m->cv.notify_all();
       }
-      if (st == HS_OK) mux_file(m);
-      else if (st != HS_E_NOT_READY) return st;
+      if (st == HS_OK) mux_file(m, one);
+      else m->room.splice(m->room.end(), one);
+      if (st != HS_OK && st != HS_E_NOT_READY) return st;
     }
   } catch (const std::exception& e) {
     set_error("hs_mux_wait: %s", e.what());

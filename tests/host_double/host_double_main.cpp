@@ -184,6 +184,53 @@ static void call_failures() {
   CHECK(hs_destroy_app(b) == HS_OK && hs_destroy_app(a) == HS_OK);
 }
 
+// A mux whose allocations are refused, one after the other: a frame that is not taken can be handed
+// over again, a result that cannot be fetched is still there at the next call, and every stream gets
+// its own ids, in order.
+static void mux_failures() {
+  Program p(HS_NET_TINY4);
+  p.d.batch = 2;
+  size_t need = 0;
+  CHECK(hs_query_workspace(&p.d, &need) == HS_OK);
+  void* workspace = aligned_alloc(256, (need + 255) / 256 * 256);
+  p.d.d_workspace = workspace; p.d.workspace_bytes = need;
+  hs_app* app = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  fake::event_wait_ns = 200000;
+  for (int waiting = 0; waiting < 2; ++waiting)
+    for (long n = 0; n < 40; ++n) {
+      hs_mux* mux = nullptr;
+      CHECK(hs_create_mux(app, 2, &mux) == HS_OK);
+      hs_result r;
+      bool refused = false;
+      // calls f until it no longer lacks memory; its n-th allocation over the frames is refused
+      auto insist = [&](auto f) {
+        hs_status st;
+        while ((st = f()) == HS_E_NOMEM) { CHECK(!refused); refused = true; }
+        return st;
+      };
+      fake::blocks_until_failure = n;
+      for (uint64_t k = 0; k < 3; ++k) {
+        CHECK(insist([&] { return hs_mux_submit(mux, 0, p.src(), p.dst(), 100 + k); }) == HS_OK);
+        CHECK(insist([&] { return hs_mux_submit(mux, 1, p.src(), p.dst(), 200 + k); }) == HS_OK);
+        for (int stream = 0; stream < 2; ++stream) {
+          hs_status st;
+          do {
+            st = insist([&] {
+              return waiting ? hs_mux_wait(mux, stream, &r, 1000000000) : hs_mux_poll(mux, stream, &r);
+            });
+          } while (!waiting && st == HS_E_NOT_READY);
+          CHECK(st == HS_OK && r.frame_id == (stream ? 200 : 100) + k);
+        }
+      }
+      fake::reset_failures();
+      CHECK(hs_destroy_mux(mux) == HS_OK);
+    }
+  fake::event_wait_ns = 0;
+  CHECK(hs_destroy_app(app) == HS_OK);
+  free(workspace);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -191,6 +238,7 @@ int main(int argc, char** argv) {
   else if (check == "group_failures") group_failures();
   else if (check == "feed_failures") feed_failures();
   else if (check == "call_failures") call_failures();
+  else if (check == "mux_failures") mux_failures();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
