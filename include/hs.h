@@ -269,8 +269,10 @@ hs_status hs_submit_frame_static_scratch(hs_app* app, const uint8_t* d_frame,
 /* Deliver the oldest finished, not yet delivered frame (submit order). Non-blocking:
  * HS_E_NOT_READY if none has finished. Frees that frame's queue slot. */
 hs_status hs_poll_result(hs_app* app, hs_result* out);
-/* As hs_poll_result, but sleeps until a frame has finished or timeout_ns elapsed
- * (HS_E_NOT_READY on time-out). */
+/* As hs_poll_result, but waits until a frame has finished or timeout_ns elapsed
+ * (HS_E_NOT_READY on time-out).  While a frame is in flight a thread that may run on four cores or
+ * more first spins for up to 1 ms, offering its core to other threads; then, and otherwise, it sleeps.
+ * The same holds for the other hs_wait_* calls. */
 hs_status hs_wait_result(hs_app* app, hs_result* out, uint64_t timeout_ns);
 
 /* Batched applications (desc.batch = B > 1): one frame of each of the B streams per call.

@@ -1,8 +1,10 @@
 // Host code of the library against the stand-in runtime: `host_double_main <check>` exits 0 when the
 // check holds, prints what does not and exits 1 otherwise.
+#include <sched.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <time.h>
 
 #include <string>
 #include <vector>
@@ -231,6 +233,47 @@ static void mux_failures() {
   free(workspace);
 }
 
+// A thread confined to one core sleeps in hs_wait_* and hs_wait_group: the completion thread may be
+// pinned to that core.
+static void pinned_wait() {
+  Program p(HS_NET_TINY4);
+  hs_app* app = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  cpu_set_t all, one;
+  CHECK(sched_getaffinity(0, sizeof(all), &all) == 0);
+  int cpu = 0;
+  while (!CPU_ISSET(cpu, &all)) ++cpu;
+  CPU_ZERO(&one);
+  CPU_SET(cpu, &one);
+  CHECK(sched_setaffinity(0, sizeof(one), &one) == 0);
+  fake::event_wait_ns = 900000;
+  auto clock_ns = [](clockid_t c) {
+    timespec t;
+    clock_gettime(c, &t);
+    return t.tv_sec * 1000000000ll + t.tv_nsec;
+  };
+  hs_group* group = nullptr;
+  for (int grouped = 0; grouped < 2; ++grouped) {
+    if (grouped) CHECK(hs_create_group(p.ctx, &app, 1, &group) == HS_OK);
+    const long long wall = clock_ns(CLOCK_MONOTONIC), busy = clock_ns(CLOCK_THREAD_CPUTIME_ID);
+    hs_result r;
+    for (uint64_t k = 0; k < 40; ++k) {
+      if (grouped) {
+        CHECK(hs_submit_group(group, p.src(), p.dst(), k) == HS_OK);
+        CHECK(hs_wait_group(group, &r, 1000000000) == HS_OK);
+      } else {
+        CHECK(hs_submit_frame(app, p.src(), p.dst(), k) == HS_OK);
+        CHECK(hs_wait_result(app, &r, 1000000000) == HS_OK);
+      }
+    }
+    // 36 ms of waiting at least
+    CHECK(4 * (clock_ns(CLOCK_THREAD_CPUTIME_ID) - busy) < clock_ns(CLOCK_MONOTONIC) - wall);
+  }
+  fake::event_wait_ns = 0;
+  CHECK(hs_destroy_group(group) == HS_OK);
+  CHECK(hs_destroy_app(app) == HS_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -239,6 +282,7 @@ int main(int argc, char** argv) {
   else if (check == "feed_failures") feed_failures();
   else if (check == "call_failures") call_failures();
   else if (check == "mux_failures") mux_failures();
+  else if (check == "pinned_wait") pinned_wait();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
