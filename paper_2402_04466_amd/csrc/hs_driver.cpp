@@ -24,11 +24,7 @@
 #include "hs.h"
 #include "hs_internal.h"
 
-static inline uint64_t now_ns() {
-  timespec ts;
-  clock_gettime(CLOCK_MONOTONIC, &ts);
-  return (uint64_t)ts.tv_sec * 1000000000ull + (uint64_t)ts.tv_nsec;
-}
+using hs::now_ns;
 
 // ---- per-stream front of a batched application --------------------------------------------------
 // The streams of the batch hand over their frames one by one, each with its own arrival stamp;
@@ -203,12 +199,11 @@ extern "C" hs_status hs_mux_wait(hs_mux* m, int stream, hs_result* out, uint64_t
   using hs::set_error;
   if (!m || !out || stream < 0 || stream >= m->batch) { set_error("hs_mux_wait: bad argument"); return HS_E_INVAL; }
   try {
-    const auto deadline = std::chrono::steady_clock::now() + std::chrono::nanoseconds(timeout_ns);
+    const uint64_t deadline = hs::deadline_after(timeout_ns);
     std::unique_lock<std::mutex> lk(m->mu);
     for (;;) {
       if (mux_take(m, stream, out)) return HS_OK;
-      const auto left = std::chrono::duration_cast<std::chrono::nanoseconds>(
-                            deadline - std::chrono::steady_clock::now()).count();
+      const int64_t left = (int64_t)deadline - (int64_t)now_ns();
       if (left <= 0) { set_error("hs_mux_wait: timed out"); return HS_E_NOT_READY; }
       if (m->draining) {   // another thread is fetching the next batch for everybody
         m->cv.wait_for(lk, std::chrono::nanoseconds(std::min<int64_t>(left, 20000000)));

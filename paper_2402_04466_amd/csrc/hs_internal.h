@@ -3,6 +3,10 @@
 
 #include <stdint.h>
 #include <stdio.h>
+#include <time.h>
+
+#include <algorithm>
+#include <chrono>
 
 #include <exception>
 #include <new>
@@ -22,6 +26,20 @@ int xcd_count(int device_cus);
 // another application; HS_E_INVAL for bad arguments or a mask without a CU on every XCD.
 hs_status admission_check(const uint32_t* claimed, const uint32_t* req_a, const uint32_t* req_b,
                           int n_words, int device_cus);
+
+inline uint64_t now_ns() {
+  timespec ts;
+  clock_gettime(CLOCK_MONOTONIC, &ts);
+  return (uint64_t)ts.tv_sec * 1000000000ull + (uint64_t)ts.tv_nsec;
+}
+// A deadline on that clock, which is the steady_clock's, and as its time point.  Neither a time-out nor
+// a deadline beyond the clock's range (UINT64_MAX: wait for good) wraps around.
+inline uint64_t deadline_after(uint64_t timeout_ns) {
+  return now_ns() + std::min<uint64_t>(timeout_ns, (uint64_t)INT64_MAX / 2);
+}
+inline std::chrono::steady_clock::time_point clock_time(uint64_t t_ns) {
+  return std::chrono::steady_clock::time_point(std::chrono::nanoseconds((int64_t)t_ns));
+}
 
 // An error text that can be kept where no memory is to be had.
 struct Message {

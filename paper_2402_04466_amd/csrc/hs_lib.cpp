@@ -29,12 +29,6 @@
 
 namespace hs {
 
-static inline uint64_t now_ns() {
-  timespec ts;
-  clock_gettime(CLOCK_MONOTONIC, &ts);
-  return (uint64_t)ts.tv_sec * 1000000000ull + (uint64_t)ts.tv_nsec;
-}
-
 #define HS_HIP(call)                                                                   \
   do {                                                                                 \
     hipError_t e_ = (call);                                                            \
@@ -1945,11 +1939,6 @@ static void spin_for_completion(hs_app* app, uint64_t n_delivered, uint64_t dead
   } while (now < until);
 }
 
-static uint64_t deadline_after(uint64_t timeout_ns) {
-  const uint64_t t = now_ns();
-  return timeout_ns > UINT64_MAX - t ? UINT64_MAX : t + timeout_ns;
-}
-
 hs_status hs_wait_batch(hs_app* app, hs_result* out, uint64_t timeout_ns) {
   if (!app || !out) { set_error("hs_wait_batch: NULL argument"); return HS_E_INVAL; }
   if (refuse_grouped(app, "hs_wait_batch") != HS_OK) return HS_E_STATE;
@@ -1962,8 +1951,7 @@ hs_status hs_wait_batch(hs_app* app, hs_result* out, uint64_t timeout_ns) {
   const uint64_t deadline_ns = deadline_after(timeout_ns);
   if (in_flight) spin_for_completion(app, delivered, deadline_ns);
   std::unique_lock<std::mutex> lk(app->mu);
-  const uint64_t now = now_ns(), left = deadline_ns > now ? deadline_ns - now : 0;
-  const bool ok = app->cv_done.wait_for(lk, std::chrono::nanoseconds(left), [&] {
+  const bool ok = app->cv_done.wait_until(lk, clock_time(deadline_ns), [&] {
     return app->n_delivered < app->n_completed;
   });
   if (!ok) {
@@ -2172,7 +2160,6 @@ hs_status hs_poll_group(hs_group* group, hs_result* out) {
 
 hs_status hs_wait_group(hs_group* group, hs_result* out, uint64_t timeout_ns) {
   if (!group || !out) { set_error("hs_wait_group: NULL argument"); return HS_E_INVAL; }
-  const auto deadline = std::chrono::steady_clock::now() + std::chrono::nanoseconds(timeout_ns);
   const uint64_t deadline_ns = deadline_after(timeout_ns);
   for (hs_app* a : group->members) {
     std::unique_lock<std::mutex> lk(a->mu);
@@ -2182,7 +2169,7 @@ hs_status hs_wait_group(hs_group* group, hs_result* out, uint64_t timeout_ns) {
       spin_for_completion(a, delivered, deadline_ns);
       lk.lock();
     }
-    if (!a->cv_done.wait_until(lk, deadline, [&] { return a->n_delivered < a->n_completed; })) {
+    if (!a->cv_done.wait_until(lk, clock_time(deadline_ns), [&] { return a->n_delivered < a->n_completed; })) {
       set_error("hs_wait_group: timed out");
       return HS_E_NOT_READY;
     }

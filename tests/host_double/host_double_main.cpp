@@ -274,6 +274,33 @@ static void pinned_wait() {
   CHECK(hs_destroy_app(app) == HS_OK);
 }
 
+// A time-out as long as its type allows is no time-out of the past.
+static void endless_wait() {
+  Program p(HS_NET_TINY4);
+  hs_app* app = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  fake::event_wait_ns = 5000000;
+  hs_result r;
+  for (uint64_t timeout : {UINT64_MAX, UINT64_MAX / 2, UINT64_MAX / 2 + 1}) {
+    CHECK(hs_submit_frame(app, p.src(), p.dst(), 1) == HS_OK);
+    CHECK(hs_wait_result(app, &r, timeout) == HS_OK);
+    hs_mux* mux = nullptr;
+    CHECK(hs_create_mux(app, 1, &mux) == HS_OK);
+    CHECK(hs_mux_submit(mux, 0, p.src(), p.dst(), 1) == HS_OK);
+    CHECK(hs_mux_wait(mux, 0, &r, timeout) == HS_OK);
+    CHECK(hs_destroy_mux(mux) == HS_OK);
+    hs_group* group = nullptr;
+    CHECK(hs_create_group(p.ctx, &app, 1, &group) == HS_OK);
+    CHECK(hs_submit_group(group, p.src(), p.dst(), 1) == HS_OK);
+    CHECK(hs_wait_group(group, &r, timeout) == HS_OK);
+    CHECK(hs_destroy_group(group) == HS_OK);
+  }
+  CHECK(hs_wait_result(app, &r, 1000000) == HS_E_NOT_READY);
+  CHECK(hs_wait_result(app, &r, 0) == HS_E_NOT_READY);
+  fake::event_wait_ns = 0;
+  CHECK(hs_destroy_app(app) == HS_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -283,6 +310,7 @@ int main(int argc, char** argv) {
   else if (check == "call_failures") call_failures();
   else if (check == "mux_failures") mux_failures();
   else if (check == "pinned_wait") pinned_wait();
+  else if (check == "endless_wait") endless_wait();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
