@@ -119,9 +119,10 @@ typedef struct {
  * t_enqueued_ns is when hs_submit_frame had handed all work to the GPU queues (host
  * launch cost = t_enqueued_ns - t_submit_ns).
  * The three intermediate stamps are t_overlay_done_ns minus the GPU-event time between
- * that stage's end and the overlay's end.  (Recurrent network without the annotation layer:
- * stage 3's per-cell outputs are written by stage 2's last kernel and its channel maxima are
- * found beside the overlay, in one launch; stage 3 then ends with the per-cell outputs.)
+ * that stage's end and the overlay's end.  Stage 3's per-cell outputs (heat, mask) are written by
+ * stage 2's last kernel; stage 3 ends when its channel maxima (argmax, present, peak) have been
+ * found.  Without the annotation layer that is done by the first workgroups of the overlay's
+ * launch, beside the drawing ones, and they stamp their end themselves (within 1 us).
  * End-to-end latency = t_overlay_done_ns - t_submit_ns (Section II-C).
  *
  * Device pointers alias the queue slot the frame was given inside the application's
@@ -372,6 +373,8 @@ hs_status hs_set_cpu_affinity(hs_app* app, int cpu);
 /* enable != 0: bracket every kernel launch of this application with HIP events on the
  * launching stream and accumulate elapsed time per kernel family (adds event overhead;
  * meant for roofline measurements, off by default). Switching resets the accumulators.
+ * While it is on, stage 3's channel maxima have a launch of their own ("postprocess"), so that
+ * they and the overlay are timed apart; otherwise only the annotation layer makes it one.
  * HS_E_STATE while frames are in flight. */
 hs_status hs_set_kernel_timing(hs_app* app, int enable);
 /* Copy up to max_entries accumulated entries; *n_entries receives the count available.

@@ -91,7 +91,7 @@ struct ConvParams {
   int relu;
   float* out_f32;       // if set: the logits, planar fp32 out_f32[(image*8 + n)*img_m + pixel], instead of
                         // `out`; with them stage 3's per-cell outputs (see PostParams)
-  float theta; float* heat; uint8_t* mask; uint8_t* kmap;
+  float theta; float* heat; uint8_t* mask; uint8_t* kmap; uint64_t* t_end;
   // CONV_BLOCK64: the second convolution's weights.  Stride 2: fused 1x1 stride-2 projection of the
   // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
   const f16* wt2_frag;
@@ -110,7 +110,7 @@ struct LstmEpilogueParams {
   float* c; f16* h_out; int h_pitch;
   const f16* w_head; float* logits; int img_m;
   // stage 3's per-cell outputs (see PostParams), from the same logits
-  float theta; float* heat; uint8_t* mask; uint8_t* kmap;
+  float theta; float* heat; uint8_t* mask; uint8_t* kmap; uint64_t* t_end;
 };
 KernelDesc describe(const LstmEpilogueParams& p);
 
@@ -134,10 +134,14 @@ struct PostRecord {           // written by the kernel into pinned host memory
   int32_t argmax_idx[8];
   float peak[8];
   uint8_t present[8];
+  // found in the overlay's launch: ticks of the device's constant-rate clock from the end of stage 2
+  // (see PostParams) until then
+  int32_t ticks[8];
 };
 // Stage 3.  Per cell (written by the kernel that computes the logits): heat = sigmoid(logit), mask =
 // logit > theta, both [batch][8][n], and kmap [batch][n] = the lowest channel whose mask is set, 0xff
 // if none (what the overlay draws).  Per channel (here, or in the overlay's launch): PostRecord.
+// t_end: when that kernel's last workgroup ended, on the device's constant-rate clock (one for all XCDs).
 struct PostParams {
   const float* logits; int n;    // [batch][8][n]
   float theta;                   // logit threshold
@@ -164,7 +168,7 @@ struct OverlayLayer {
   float rcp_scale;                   // 1/scale
   // stage 3's channel maxima of this layer's network, found in the overlay's launch: logits
   // [batch][8][hm*wm] and the records [batch] (NULL: a launch of their own has found them)
-  const float* logits; PostRecord* rec; float theta;
+  const float* logits; PostRecord* rec; float theta; const uint64_t* t_stage2;
   uint64_t glyph[9];                 // bit (5*row + col) of glyph g, col 0 = leftmost
 };
 struct OverlayParams {

@@ -347,6 +347,7 @@ __global__ __launch_bounds__(256) void k_conv_direct(ConvParams p) {
   }
   set_channels |= (uint32_t)__shfl_xor((int)set_channels, 32, 64);
   if (valid && h == 0) p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
+  if (m == p.m - 1 && h == 0) *p.t_end = wall_clock64();
 }
 
 // =============================================================================================
@@ -1298,7 +1299,10 @@ __global__ __launch_bounds__(256) void k_lstm_epilogue(LstmEpilogueParams p) {
     const bool set = sum > p.theta;
     p.mask[at] = set ? 1 : 0;
     const uint32_t set_channels = (uint32_t)__ballot(set) & 0xffu;
-    if (j == 0) p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
+    if (j == 0) {
+      p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
+      if (m == p.m - 1) *p.t_end = wall_clock64();
+    }
   }
 }
 
@@ -1712,9 +1716,12 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   if ((int)blockIdx.x < p.n_max) {                               // eight workgroups per layer
     const OverlayLayer& L = p.layer[LAYERS ? blockIdx.x >> 3 : 0];
     const int k = (int)(blockIdx.x & 7u), n = L.wm * L.hm;
+    if (!L.rec) return;
+    const uint64_t t_stage2 = *L.t_stage2;
     float bv;
     int bi;
-    if (L.rec) channel_maximum(L.logits + ((size_t)by * 8 + k) * n, n, L.theta, k, L.rec + by, bv, bi);
+    channel_maximum(L.logits + ((size_t)by * 8 + k) * n, n, L.theta, k, L.rec + by, bv, bi);
+    if (threadIdx.x == 0) L.rec[by].ticks[k] = (int32_t)(wall_clock64() - t_stage2);
     return;
   }
   const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;          // groups per row, of the frame

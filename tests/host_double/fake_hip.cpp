@@ -96,6 +96,7 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   p->multiProcessorCount = 256;
   return hipSuccess;
 }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 100000; return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "fake"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
