@@ -46,6 +46,7 @@ static const char* kFamilyName[F_COUNT] = {"resize_norm", "conv_mfma", "lstm_hea
 struct Op {
   Family fam;
   double flops = 0, bytes = 0;
+  size_t wt_halves = 0;    // F_CONV: what conv.wt_frag holds
   ResizeParams resize;
   ConvParams conv;
   LstmEpilogueParams lstm;
@@ -637,7 +638,7 @@ struct Builder {
     ConvParams probe = g;
     choose_split(probe);
     const bool direct = probe.variant == CONV_DIRECT, fuse = proj_out != nullptr;
-    const size_t wf_off = reserve_w(direct ? (size_t)32 * g.ktot : (size_t)g.cout_pad * g.ktot);
+    const size_t wf_halves = (size_t)(direct ? 32 : g.cout_pad) * g.ktot, wf_off = reserve_w(wf_halves);
     size_t wf2_off = kNoWeights;
     if (!direct) {
       pack_frag_at(blob_at, cout, cin, 9, g.cout_pad, wf_off);
@@ -654,9 +655,11 @@ struct Builder {
       wf2_off = reserve_w((size_t)g.cout_pad * cin);
       pack_frag_at(proj_at, cout, cin, 1, g.cout_pad, wf2_off);
     }
-    return add_conv(g, wf_off, res, out, relu, want_f32, keep_partial,
-                    2.0 * g.m * (double)cout * cin * (k * k + (fuse ? 1 : 0)), wf2_off,
-                    fuse ? proj_out : nullptr);
+    const int idx = add_conv(g, wf_off, res, out, relu, want_f32, keep_partial,
+                             2.0 * g.m * (double)cout * cin * (k * k + (fuse ? 1 : 0)), wf2_off,
+                             fuse ? proj_out : nullptr);
+    ops[(size_t)idx].wt_halves = wf_halves;
+    return idx;
   }
 
   // A 64 -> 64 -> 64 channel BasicBlock without projection as ONE launch (k_block64_fused):
@@ -689,6 +692,7 @@ struct Builder {
     Op op;
     op.fam = F_CONV;
     op.flops = 2.0 * (2.0 * g.m * 64.0 * 64.0 * 9.0);
+    op.wt_halves = (size_t)64 * 576;
     op.conv = g;
     ops.push_back(op);
   }
@@ -707,7 +711,7 @@ struct Builder {
     g.kc = chunk_px * 4;
     g.ntaps = k; g.kw = 1; g.chunks_per_tap = 1; g.nchunks = k; g.ktot = k * g.kc;
     g.stride = 2; g.pad = 0;
-    const size_t wf_off = reserve_w((size_t)32 * g.ktot);
+    const size_t wf_halves = (size_t)32 * g.ktot, wf_off = reserve_w(wf_halves);
     if (pack)
       pack_tasks.push_back([=] {
         std::vector<f16> rows((size_t)cout * g.ktot);
@@ -717,6 +721,7 @@ struct Builder {
     out->h = g.hout; out->w = g.wout; out->c = cout;
     check_room(*out, g.m);
     first_conv_op = add_conv(g, wf_off, nullptr, out, true, false, false, 2.0 * g.m * (double)cout * 3 * k * k);
+    ops[(size_t)first_conv_op].wt_halves = wf_halves;
   }
 
   void walk_tiny(int ph, int pw) {
@@ -849,16 +854,16 @@ struct Builder {
 
   void walk(int ph, int pw) {
     if (d.net == HS_NET_TINY4) walk_tiny(ph, pw); else walk_resnet(ph, pw);
-    // With several frames per launch every layer prefetches the next one's fragment-ordered weights:
-    // a pass then touches more than the last-level cache holds and finds the weights in HBM (four
+    // With several frames per launch the layers that k_conv3x3_kw computes prefetch the next layer's
+    // weights (not its projection's): a pass then touches more than the last-level cache holds and finds the weights in HBM (four
     // frames 641 x 361: 363 -> 337 us, sixteen frames 416 x 240: 375 -> 358).  The 36 MB of a one-frame
     // application stay cached, and the prefetch would only cost (168 -> 172 us).
     ConvParams* prev = nullptr;
     for (Op& op : ops) {
       if (op.fam != F_CONV) continue;
-      if (prev && op.conv.wt_frag && d.batch > 1) {
+      if (prev && prev->variant == CONV_KW && op.conv.wt_frag && d.batch > 1) {
         prev->next_wt = op.conv.wt_frag;
-        prev->next_lines = (int)((size_t)op.conv.cout_pad * op.conv.ktot * sizeof(f16) / 128);
+        prev->next_lines = (int)(op.wt_halves * sizeof(f16) / 128);
       }
       prev = &op.conv;
     }

@@ -24,6 +24,8 @@ std::atomic<long> event_wait_ns{0};
 std::atomic<long> blocks_until_failure{-1}, threads_until_failure{-1};
 std::atomic<bool> fail_block_after_thread_start{false};
 static thread_local bool fail_next_block = false;
+hs::ConvParams conv_launches[kMaxConvLaunches];
+std::atomic<int> n_conv_launches{0};
 void reset_failures() {
   blocks_until_failure = threads_until_failure = -1;
   fail_block_after_thread_start = false;
@@ -152,7 +154,10 @@ namespace hs {
 static int some_kernel;
 static KernelDesc some() { return KernelDesc{&some_kernel, dim3(1), dim3(64), 0}; }
 KernelDesc describe(const ResizeParams&) { return some(); }
-KernelDesc describe(const ConvParams&) { return some(); }
+KernelDesc describe(const ConvParams& p) {
+  if (p.wt_frag && fake::n_conv_launches < fake::kMaxConvLaunches) fake::conv_launches[fake::n_conv_launches++] = p;
+  return some();
+}
 KernelDesc describe(const LstmEpilogueParams&) { return some(); }
 KernelDesc describe(const StemPoolParams&) { return some(); }
 KernelDesc describe(const PostParams&) { return some(); }

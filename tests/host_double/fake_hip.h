@@ -1,6 +1,9 @@
 // What a test can set and read of the stand-in (fake_hip.cpp).
 #pragma once
 #include <atomic>
+
+#include "hs_kernels.h"
+
 namespace fake {
 extern std::atomic<long> live_objects;     // events, streams, graphs, pinned blocks
 extern std::atomic<long> live_blocks;      // operator new
@@ -8,5 +11,9 @@ extern std::atomic<long> live_threads;     // started and not ended
 extern std::atomic<long> event_wait_ns;    // how long hipEventSynchronize sleeps
 extern std::atomic<long> blocks_until_failure, threads_until_failure;   // that many succeed, one fails; -1: never
 extern std::atomic<bool> fail_block_after_thread_start;   // the thread's starter fails to allocate once, right after
+// the convolutions described so far with their weights in place: planned, or launched
+constexpr int kMaxConvLaunches = 128;
+extern hs::ConvParams conv_launches[kMaxConvLaunches];
+extern std::atomic<int> n_conv_launches;
 void reset_failures();
 }  // namespace fake

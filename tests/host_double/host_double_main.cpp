@@ -26,13 +26,13 @@ struct Program {   // what a program has in hand before it creates an applicatio
   std::vector<float> weights;
   void* workspace = nullptr;
   std::vector<uint8_t> frame, out;
-  explicit Program(int net) : frame(64 * 48 * 3 + 16), out(64 * 48 * 3 + 16) {
+  explicit Program(int net, int batch = 1) : frame(64 * 48 * 3 + 16), out(64 * 48 * 3 + 16) {
     CHECK(hs_init(0, &ctx) == HS_OK);
     memset(&d, 0, sizeof(d));
     d.frame_w = 64; d.frame_h = 48; d.frame_pitch = 192;
     d.net_w = 40; d.net_h = 24; d.net = net;
     d.mean = 0.5f; d.std = 0.25f; d.threshold = 0.5f; d.alpha = 0.5f;
-    d.queue_depth = 2; d.batch = 1; d.glyph_scale = 1;
+    d.queue_depth = 2; d.batch = batch; d.glyph_scale = 1;
     size_t need = 0;
     CHECK(hs_query_workspace(&d, &need) == HS_OK);
     workspace = aligned_alloc(256, (need + 255) / 256 * 256);
@@ -301,6 +301,36 @@ static void endless_wait() {
   CHECK(hs_destroy_app(app) == HS_OK);
 }
 
+// A kernel is told to prefetch the next layer's weights only if it does so (k_conv3x3_kw), and then
+// exactly those that the layer has.
+static void prefetched_weights() {
+  for (int net : {(int)HS_NET_TINY4, (int)HS_NET_RESNET18_CONVLSTM}) {
+    Program p(net, 2);
+    hs_app* app = nullptr;
+    CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+    fake::n_conv_launches = 0;
+    const uint8_t* src[2] = {p.src(), p.src()};
+    uint8_t* dst[2] = {p.dst(), p.dst()};
+    hs_result r[2];
+    CHECK(hs_submit_batch(app, src, dst, 1) == HS_OK && hs_wait_batch(app, r, 1000000000) == HS_OK);
+    const int n = fake::n_conv_launches;
+    CHECK(n > 0 && n < fake::kMaxConvLaunches);
+    int told = 0;
+    for (int i = 0; i < n; ++i) {
+      const hs::ConvParams& a = fake::conv_launches[i];
+      if (a.next_lines == 0) continue;
+      ++told;
+      CHECK(a.variant == hs::CONV_KW && i + 1 < n);
+      const hs::ConvParams& b = fake::conv_launches[i + 1];
+      CHECK(a.next_wt == b.wt_frag);
+      CHECK((size_t)a.next_lines * 128 ==
+            (size_t)(b.variant == hs::CONV_DIRECT ? 32 : b.cout_pad) * b.ktot * sizeof(hs::f16));
+    }
+    CHECK((told > 0) == (net != HS_NET_TINY4));
+    CHECK(hs_destroy_app(app) == HS_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -311,6 +341,7 @@ int main(int argc, char** argv) {
   else if (check == "mux_failures") mux_failures();
   else if (check == "pinned_wait") pinned_wait();
   else if (check == "endless_wait") endless_wait();
+  else if (check == "prefetched_weights") prefetched_weights();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
