@@ -279,13 +279,11 @@ static void to_half(const float* src, f16* dst, size_t n) {
   for (size_t i = 0; i < n; ++i) dst[i] = (f16)src[i];
 }
 
-// Generic layer: packed[n][(ky*k + kx)*cin + c] = w[n][c][ky][kx] for rows n0 .. n1-1 (rows from cout on
-// are zero); taps = k * k.
-static void pack_generic(const f16* w, int cout, int cin, int taps, int n0, int n1, f16* dst) {
+// Generic layer: packed[n][(ky*k + kx)*cin + c] = w[n][c][ky][kx], taps = k * k.
+static void pack_generic(const f16* w, int cout, int cin, int taps, f16* dst) {
   const size_t ktot = (size_t)taps * cin;
-  for (int n = n0; n < n1; ++n) {
+  for (int n = 0; n < cout; ++n) {
     f16* row = dst + (size_t)n * ktot;
-    if (n >= cout) { std::memset((void*)row, 0, ktot * sizeof(f16)); continue; }
     const f16* src = w + (size_t)n * ktot;
     for (int t = 0; t < taps; ++t)
       for (int c = 0; c < cin; ++c) row[(size_t)t * cin + c] = src[(size_t)c * taps + t];
@@ -645,7 +643,7 @@ struct Builder {
     } else if (pack) {
       pack_tasks.push_back([=] {
         std::vector<f16> rows((size_t)cout * g.ktot);
-        pack_generic(half_blob.data() + blob_at, cout, cin, k * k, 0, cout, rows.data());
+        pack_generic(half_blob.data() + blob_at, cout, cin, k * k, rows.data());
         pack_direct(rows.data(), cout, g.nchunks, g.kc, host_w.data() + wf_off);
       });
     }
