@@ -252,10 +252,11 @@ hs_status hs_submit_frame(hs_app* app, const uint8_t* d_frame, uint8_t* d_overla
  * allocator while they run: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, same results bit for bit, same status codes; the call
  * allocates nothing, neither on the device nor (on its success path) on the host.  The one
- * scratch buffer of the hot path, the fp32 partial sums of the convolutions that are split
- * along K, is taken from a fixed 8 MiB device array inside the library (one copy per GPU, held
- * until the process ends) instead of the application's workspace; kernels are always launched
- * one by one (never as a HIP graph).  The 1920x1080 -> 854x480 network needs 6.6 MB of it.
+ * scratch buffer of the hot path, the fp32 gate pre-activations of the recurrent cell (1024 per
+ * cell of the map, 4096 bytes), is taken from a fixed 8 MiB device array inside the library (one
+ * copy per GPU, held until the process ends) instead of the application's workspace; kernels are
+ * always launched one by one (never as a HIP graph).  It serves maps of up to 2048 cells; the
+ * 1920x1080 -> 854x480 network's 15 x 27 take 1.66 MB of it.
  *   HS_E_NOMEM  a frame of this application needs more scratch than the array holds
  *               (hs_last_error() names both sizes); nothing is enqueued
  *   HS_E_STATE  batched or grouped application, kernel timing switched on, or a frame of this

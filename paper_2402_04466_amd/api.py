@@ -310,7 +310,7 @@ def hs_submit_frame(app: int, d_frame: int, d_overlay_out: int, frame_id: int) -
 
 
 def hs_submit_frame_static_scratch(app: int, d_frame: int, d_overlay_out: int, frame_id: int) -> int:
-    """hs_submit_frame with the split-K scratch in the library's fixed device array (no
+    """hs_submit_frame with the gate scratch in the library's fixed device array (no
     allocation).  Returns HS_OK or HS_E_QUEUE_FULL; raises on any other status."""
     return _check(load().hs_submit_frame_static_scratch(app, d_frame, d_overlay_out, frame_id),
                   soft=(HS_E_QUEUE_FULL,))

@@ -96,7 +96,7 @@ struct ConvParams {
   // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
   const f16* wt2_frag;
   f16* out2; int out2_pitch;
-  // weights of the layer that runs next, for the kernels that prefetch them: 128-byte lines (0: none)
+  // CONV_KW: weights of the layer that runs next, to be prefetched, in 128-byte lines (0: none)
   const void* next_wt; int next_lines;
 };
 KernelDesc describe(const ConvParams& p);

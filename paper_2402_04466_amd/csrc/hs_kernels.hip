@@ -1803,7 +1803,7 @@ KernelDesc describe(const OverlayParams& p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Split-K scratch for callers that cannot allocate.  In host code the array's name is only a
+// Gate scratch for callers that cannot allocate.  In host code the array's name is only a
 // handle for hipGetSymbolAddress: every GPU holds its own copy at its own address, looked up
 // once per device (with that device current) and used as an ordinary device pointer from then
 // on -- the kernels receive it in their parameter blocks like the workspace scratch it replaces.

@@ -1901,7 +1901,7 @@ hs_status hs_submit_frame_static_scratch(hs_app* app, const uint8_t* d_frame,
   }
   if (app->slots[0].infer_static.empty()) {
     set_error("hs_submit_frame_static_scratch: a frame of this application needs %zu bytes of "
-              "split-K scratch, the library's fixed array holds %zu", app->partial_bytes,
+              "scratch for the gate pre-activations, the library's fixed array holds %zu", app->partial_bytes,
               app->ctx->static_scratch_bytes);
     return HS_E_NOMEM;
   }

@@ -165,7 +165,7 @@ def _desc(**over):
 
 def test_workspace_query_and_validation():
     big = hs.hs_query_workspace(_desc())
-    # fp16 weights 36.5 MB + stem output 13.1 MB + 4 activation buffers + split-K scratch ...
+    # fp16 weights 36.5 MB + stem output 13.1 MB + 4 activation buffers + gate scratch ...
     assert 60e6 < big < 120e6
     assert hs.hs_query_workspace(_desc(queue_depth=4)) > big
     small = hs.hs_query_workspace(_desc(frame_w=320, frame_h=240, net_w=128, net_h=128,

@@ -1,5 +1,5 @@
 """hs_submit_frame_static_scratch (the entry point for callers that cannot allocate: its
-split-K scratch is a fixed device array inside the library) against hs_submit_frame, through
+gate scratch is a fixed device array inside the library) against hs_submit_frame, through
 the C ABI: every output of every stage must be the same, bit for bit, on two calls in a row,
 the second on a smaller input that leaves most of the array holding the first call's values."""
 import numpy as np
@@ -81,7 +81,7 @@ def test_static_scratch_submit_matches_workspace_submit_twice_in_a_row(hs):
 
 
 def test_static_scratch_submit_refuses_what_it_cannot_serve(hs):
-    """Batched applications and applications whose split-K scratch exceeds the fixed array are
+    """Batched applications and applications whose gate scratch exceeds the fixed array are
     refused with a clear status; nothing is enqueued."""
     from paper_2402_04466_amd.harness import AppStream
     ctx = hs.hs_init(0)
