@@ -121,8 +121,9 @@ typedef struct {
  * The three intermediate stamps are t_overlay_done_ns minus the GPU-event time between
  * that stage's end and the overlay's end.  Stage 3's per-cell outputs (heat, mask) are written by
  * stage 2's last kernel; stage 3 ends when its channel maxima (argmax, present, peak) have been
- * found.  Without the annotation layer that is done by the first workgroups of the overlay's
- * launch, beside the drawing ones, and they stamp their end themselves (within 1 us).
+ * found.  Without the annotation layer that is done by the first workgroups of each image in the
+ * overlay's launch, beside the drawing ones, and they stamp their end themselves (within 1 us);
+ * for a batch, whose last image is drawn last, stage 3 then ends shortly before the overlay.
  * End-to-end latency = t_overlay_done_ns - t_submit_ns (Section II-C).
  *
  * Device pointers alias the queue slot the frame was given inside the application's

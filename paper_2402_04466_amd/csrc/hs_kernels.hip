@@ -967,9 +967,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
 // PG == 1 (36 is 5 to 7 % slower: fewer workgroups per CU), 18 for PG == 2 (12: equal), 12 at stride 2
 // (18 spills: 10 to 30 % slower).
 // Against the kernels they replace (weights staged through LDS, K splits as workgroups of their own
-// and a launch to add them), 1080p frame: 256-channel layers 8.6 + 3.3 -> 7.2 us, 512-channel layers
-// 8.9 + 3.7 -> 7.5 us; of those 1.8 us are launch and set-up, 0.8 us the first operands' latency, 2 us the
-// weight stream (288 KB per CU), 1.7 us the sum over the splits and the store.
+// and a launch to add them), one 1080p frame, medians of kernel traces: 256-channel layers 9.0 + 3.5 -> 7.7
+// to 8.2 us, 512-channel layers 9.1 + 3.9 -> 7.8 to 8.4 us; of those 1.8 us are launch and set-up, 0.8 us the
+// first operands' latency, 2 us the weight stream (288 KB per CU), 1.7 us the sum over the splits and the store.
 // =============================================================================================
 // Touches this workgroup's share of the next layer's weights (one 4-byte load per 128-byte line),
 // so that they are on their way into the last-level cache when that layer starts: streamed from

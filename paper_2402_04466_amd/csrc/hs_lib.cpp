@@ -108,8 +108,9 @@ struct Tensor {
 };
 
 enum SlotState { SLOT_FREE = 0, SLOT_INFLIGHT = 1, SLOT_DONE = 2 };
-// Two lanes: with more frames in flight the submitting host thread (one graph launch per frame,
-// about 75 us) is the limit, not the GPU (four lanes were measured: no gain).
+// Two lanes: with more frames in flight the submitting host thread is the limit, not the GPU.  A 1080p frame
+// back to back takes 106 us, of which the host spends 80 handing over its 19 launches.  (Four lanes were
+// measured with one graph launch per frame, about 75 us: no gain.)
 constexpr int kMaxLanes = 2;
 
 struct Slot {
@@ -486,7 +487,9 @@ struct Builder {
       const int per = (c.chunks_per_tap + ns - 1) / ns;
       return (c.chunks_per_tap + per - 1) / per;
     };
-    constexpr int kRound = 256;         // one workgroup per CU
+    // A round: one workgroup for every CU.  It measures the work of the busiest CU, for all forms alike, and not
+    // what is resident at once (k_conv3x3_dira: three workgroups per CU, k_conv3x3_kw: two of 64 pixels).
+    constexpr int kRound = 256;
     if (s3x3 && c.stride == 2) {
       if (tiles(8) >= 768) {
         // from 1.5 workgroups of 8 x 8 x 128 per CU on: the patch, the heavy operand at stride 2, serves
@@ -509,8 +512,10 @@ struct Builder {
       const int ns = k_splits(wide < 192 ? tiles(8) : wide, c.chunks_per_tap / 2);
       // Measured over maps of 5 x 9 to 60 x 107 pixels and 1 to 16 frames per launch: the smallest
       // workgroup whose grid is one round wins (a round costs what its workgroup costs, and a
-      // workgroup's time is its weight stream: 128 channels x 32 pixels take 0.62 to 0.9 of the time of
-      // 128 x 64); beyond one round the 64-pixel tiles, which feed two MFMAs per weight fragment.
+      // workgroup's time is its weight stream: 128 channels x 32 pixels take 0.79 to 0.94 of the time of
+      // 128 x 64); beyond one round the 64-pixel tiles, which feed two MFMAs per weight fragment (256
+      // channels, four 1080p frames: 14.2 us, 128 x 32 pixels 16.7).  There the form taken is within 12 % of
+      // the best one, which from three frames on is often k_conv3x3_dira (13.3 us).
       // Two wavefronts per workgroup only in one round: a second such workgroup on a CU shares
       // the first one's SIMDs.
       if (ns == 1) {
@@ -853,8 +858,8 @@ struct Builder {
   void walk(int ph, int pw) {
     if (d.net == HS_NET_TINY4) walk_tiny(ph, pw); else walk_resnet(ph, pw);
     // With several frames per launch the layers that k_conv3x3_kw computes prefetch the next layer's
-    // weights (not its projection's): a pass then touches more than the last-level cache holds and finds the weights in HBM (four
-    // frames 641 x 361: 363 -> 337 us, sixteen frames 416 x 240: 375 -> 358).  The 36 MB of a one-frame
+    // weights (not its projection's): a pass then touches more than the last-level cache holds and finds
+    // the weights in HBM (four frames 641 x 361: 363 -> 337 us, sixteen frames 416 x 240: 375 -> 358).  The 36 MB of a one-frame
     // application stay cached, and the prefetch would only cost (168 -> 172 us).
     ConvParams* prev = nullptr;
     for (Op& op : ops) {
