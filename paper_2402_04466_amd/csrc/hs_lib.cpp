@@ -1971,14 +1971,15 @@ static void spin_for_completion(hs_app* app, uint64_t n_delivered, uint64_t dead
 hs_status hs_wait_batch(hs_app* app, hs_result* out, uint64_t timeout_ns) {
   if (!app || !out) { set_error("hs_wait_batch: NULL argument"); return HS_E_INVAL; }
   if (refuse_grouped(app, "hs_wait_batch") != HS_OK) return HS_E_STATE;
-  uint64_t delivered, in_flight;
+  uint64_t delivered;
+  bool running;            // nothing to deliver yet, and a frame in flight
   {
     std::lock_guard<std::mutex> lk(app->mu);
     delivered = app->n_delivered;
-    in_flight = app->n_submitted - app->n_completed;
+    running = app->n_delivered >= app->n_completed && app->n_completed < app->n_submitted;
   }
   const uint64_t deadline_ns = deadline_after(timeout_ns);
-  if (in_flight) spin_for_completion(app, delivered, deadline_ns);
+  if (running) spin_for_completion(app, delivered, deadline_ns);
   std::unique_lock<std::mutex> lk(app->mu);
   const bool ok = app->cv_done.wait_until(lk, clock_time(deadline_ns), [&] {
     return app->n_delivered < app->n_completed;

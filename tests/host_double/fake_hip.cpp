@@ -9,6 +9,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <pthread.h>
+#include <sched.h>
 #include <stdlib.h>
 #include <string.h>
 #include <time.h>
@@ -21,6 +22,7 @@
 namespace fake {
 std::atomic<long> live_objects{0}, live_blocks{0}, live_threads{0};
 std::atomic<long> event_wait_ns{0};
+std::atomic<long> mask_queries{0};
 std::atomic<long> blocks_until_failure{-1}, threads_until_failure{-1};
 std::atomic<bool> fail_block_after_thread_start{false};
 static thread_local bool fail_next_block = false;
@@ -66,6 +68,13 @@ static void* counted(void* p) {
   --live_threads;
   return r;
 }
+extern "C" int sched_getaffinity(pid_t pid, size_t size, cpu_set_t* set) noexcept {
+  using Fn = int (*)(pid_t, size_t, cpu_set_t*);
+  static Fn real = (Fn)dlsym(RTLD_NEXT, "sched_getaffinity");
+  ++fake::mask_queries;
+  return real(pid, size, set);
+}
+
 extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* x) {
   using Fn = int (*)(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*);
   static Fn real = (Fn)dlsym(RTLD_NEXT, "pthread_create");

@@ -9,6 +9,7 @@ extern std::atomic<long> live_objects;     // events, streams, graphs, pinned bl
 extern std::atomic<long> live_blocks;      // operator new
 extern std::atomic<long> live_threads;     // started and not ended
 extern std::atomic<long> event_wait_ns;    // how long hipEventSynchronize sleeps
+extern std::atomic<long> mask_queries;     // calls of sched_getaffinity
 extern std::atomic<long> blocks_until_failure, threads_until_failure;   // that many succeed, one fails; -1: never
 extern std::atomic<bool> fail_block_after_thread_start;   // the thread's starter fails to allocate once, right after
 // the convolutions described so far with their weights in place: planned, or launched

@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <time.h>
+#include <unistd.h>
 
 #include <string>
 #include <vector>
@@ -274,6 +275,27 @@ static void pinned_wait() {
   CHECK(hs_destroy_app(app) == HS_OK);
 }
 
+// A result that is there already is delivered without a system call, a later frame in flight or not.
+static void ready_result() {
+  Program p(HS_NET_TINY4);
+  hs_app* app = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  hs_result r;
+  for (uint64_t k = 0; k < 5; ++k) {
+    fake::event_wait_ns = 0;
+    CHECK(hs_submit_frame(app, p.src(), p.dst(), 2 * k) == HS_OK);
+    usleep(50000);                       // its completion has been noted
+    fake::event_wait_ns = 50000000;
+    CHECK(hs_submit_frame(app, p.src(), p.dst(), 2 * k + 1) == HS_OK);
+    const long queries = fake::mask_queries;
+    CHECK(hs_wait_result(app, &r, 1000000000) == HS_OK && r.frame_id == 2 * k);
+    CHECK(fake::mask_queries == queries);
+    CHECK(hs_wait_result(app, &r, 1000000000) == HS_OK && r.frame_id == 2 * k + 1);
+  }
+  fake::event_wait_ns = 0;
+  CHECK(hs_destroy_app(app) == HS_OK);
+}
+
 // A time-out as long as its type allows is no time-out of the past.
 static void endless_wait() {
   Program p(HS_NET_TINY4);
@@ -340,6 +362,7 @@ int main(int argc, char** argv) {
   else if (check == "call_failures") call_failures();
   else if (check == "mux_failures") mux_failures();
   else if (check == "pinned_wait") pinned_wait();
+  else if (check == "ready_result") ready_result();
   else if (check == "endless_wait") endless_wait();
   else if (check == "prefetched_weights") prefetched_weights();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
