@@ -122,8 +122,10 @@ typedef struct {
  * that stage's end and the overlay's end.  Stage 3's per-cell outputs (heat, mask) are written by
  * stage 2's last kernel; stage 3 ends when its channel maxima (argmax, present, peak) have been
  * found.  Without the annotation layer that is done by the first workgroups of each image in the
- * overlay's launch, beside the drawing ones, and they stamp their end themselves (within 1 us);
- * for a batch, whose last image is drawn last, stage 3 then ends shortly before the overlay.
+ * overlay's launch, beside the drawing ones, and they stamp their end themselves (within 1 us; a
+ * few with graph launch, where the event behind stage 2 is a packet of its own).  Stage 3 of a batch,
+ * whose last image is drawn last, then ends shortly before the overlay, and that of a group's member
+ * includes the wait for the other members' networks.
  * End-to-end latency = t_overlay_done_ns - t_submit_ns (Section II-C).
  *
  * Device pointers alias the queue slot the frame was given inside the application's
