@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "hs_run.h"
+
 namespace hs {
 
 typedef _Float16 f16;
@@ -52,13 +54,21 @@ enum ConvVariant {
   CONV_BLOCK64,   // a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU between,
                   // shortcut from the input, ReLU) in one launch (k_block64_fused): wt_frag = first,
                   // wt2_frag = second convolution, res = in
-  CONV_DIRA,      // 3x3/1 layers with >= 2 Cin chunks: tile 8 x 16 pixels x 64 channels, weights read
-                  // as MFMA fragments straight from wt_frag (k_conv3x3_dira)
   CONV_S2_DIRA,   // 3x3/2 layers (+ fused 1x1/2 projection) on large grids: tile 8 x 8 x 128, weights
                   // from wt_frag / wt2_frag, tile walking, no residual (k_conv3x3s2_dira)
-  CONV_KW         // 3x3 layers of either stride (+ fused projection) on small and middle grids, K
-                  // splits inside the workgroup, weights from wt_frag / wt2_frag (k_conv3x3_kw)
+  CONV_KW         // 3x3 layers with the K splits inside the workgroup, weights from wt_frag / wt2_frag.  Stride 1, an
+                  // even number of Cin chunks: tiles of consecutive pixels (k_conv3x3_run).  Stride 2 (+ fused
+                  // projection) on small and middle grids: tiles of 4 x 8 pixels (k_conv3x3s2_kw)
 };
+// The forms of k_conv3x3_run: channels and pixels of a tile, loading passes over a patch (32 pixels each), bytes of a patch
+// buffer; cost of a tile in us where its CU works on several, fixed and per Cin chunk (see Builder::choose_run).
+struct RunForm { int ch, px, passes, lds; double cost, chunk_cost; };
+constexpr RunForm kRunForms[] = {
+    {32, 32, 3, 16384, 0.35, 0.47}, {32, 64, 4, 24576, 0.55, 0.57},  {64, 64, 4, 24576, 0.75, 1.03},
+    {64, 96, 6, 26624, 1.3, 1.29},  {64, 128, 7, 36864, 1.9, 1.62}, {64, 160, 8, 40960, 2.3, 2.22},
+    {32, 32, 7, 44032, 0.35, 0.47},   // patches of maps a few pixels wide or high, which hold mostly border
+};
+constexpr int kRunFormCount = 7, kRunFormAnyMap = 6;
 struct ConvParams {
   const f16* in;
   const f16* wt_frag;   // weights in MFMA fragment order: [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
@@ -69,8 +79,8 @@ struct ConvParams {
   int cout, cout_pad;   // cout_pad: multiple of the block's N tile
   int kc;               // 16, 32 or 64
   int variant;          // ConvVariant
-  int kw_splits, kw_cgroups, kw_groups;   // CONV_KW, CONV_DIRECT: K splits; groups of 32 channels (their
-                        // product: wavefronts per workgroup), groups of 4 x 8 pixels per tile
+  int kw_splits, kw_cgroups;   // k_conv3x3s2_kw, CONV_DIRECT: K splits; groups of 32 channels (their product:
+                        // wavefronts per workgroup)
   int tiles_x;          // spatial variants: tiles per output row
   int ntaps, kw, chunks_per_tap, nchunks, ktot;
   int stride, pad;
@@ -96,6 +106,13 @@ struct ConvParams {
   // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
   const f16* wt2_frag;
   f16* out2; int out2_pitch;
+  // k_conv3x3_run: form (kRunForms), tiles; bytes of the input and of the weights; log2 of n_block, reciprocal of
+  // tiles_m * n_block (run_div31)
+  int run_form;
+  RunGeometry run;
+  uint32_t run_in_bytes, run_w_bytes;
+  int run_nb_shift;
+  uint32_t run_by_blk;
   // CONV_KW: weights of the layer that runs next, to be prefetched, in 128-byte lines (0: none)
   const void* next_wt; int next_lines;
 };

@@ -21,6 +21,17 @@ __device__ __forceinline__ uint32_t udiv_est(uint32_t num, uint32_t d, float rcp
   return q;
 }
 
+// A buffer of `bytes` bytes (below 2^31) for loads with a scalar and a per-lane offset: no address arithmetic per
+// load, and a lane whose offset lies behind the buffer reads zeros (kOutside: always).
+typedef __amdgpu_buffer_rsrc_t BufferRsrc;
+constexpr int kOutside = (int)0x80000000u;
+__device__ __forceinline__ BufferRsrc buffer_of(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
+}
+__device__ __forceinline__ u32x4 load16(BufferRsrc buf, int lane_offset, int offset) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, lane_offset, offset, 0));
+}
+
 // =============================================================================================
 // Stage 1: one workgroup per output row.  The two source rows the row needs are staged in
 // LDS with 16-byte loads; every output pixel is the exact integer 4-tap sum, rounded once.
@@ -246,6 +257,52 @@ __device__ __forceinline__ void res_octets_to_quads(const u32x4 (&o)[2], half4 (
   for (int i = 0; i < 4; ++i) res[i] = __builtin_bit_cast(half4, make_uint2(q[i][0], q[i][1]));
 }
 
+// The same for one half of them, 16 channels from cbase on: v0 = channels cbase + 4h .. + 3, v1 = 8 further;
+// res: the lane's 16 bytes of the residual (channels cbase + 8h .. + 7).  m < 0: nothing is stored.
+__device__ __forceinline__ void store_half(const ConvParams& p, int m, int cbase, int h, const float4& v0,
+                                           const float4& v1, const u32x4& res) {
+  float v[2][4] = {{v0.x, v0.y, v0.z, v0.w}, {v1.x, v1.y, v1.z, v1.w}};
+  if (p.res) {
+    const auto s0 = __builtin_amdgcn_permlane32_swap(res[0], res[2], false, false);
+    const auto s1 = __builtin_amdgcn_permlane32_swap(res[1], res[3], false, false);
+    const half4 r0 = __builtin_bit_cast(half4, make_uint2(s0[0], s1[0]));
+    const half4 r1 = __builtin_bit_cast(half4, make_uint2(s0[1], s1[1]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[0][j] += (float)r0[j];
+      v[1][j] += (float)r1[j];
+    }
+  }
+  uint2 w[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    half4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = (f16)v[i][j];
+    if (p.relu) o = __builtin_elementwise_max(o, half4{});
+    w[i] = __builtin_bit_cast(uint2, o);
+  }
+  const auto s0 = __builtin_amdgcn_permlane32_swap(w[0].x, w[1].x, false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(w[0].y, w[1].y, false, false);
+  if (m >= 0) {
+    const u32x4 o = {s0[0], s1[0], s0[1], s1[1]};
+    *reinterpret_cast<u32x4*>(p.out + (size_t)m * p.out_pitch + cbase + 8 * h) = o;
+  }
+}
+// And for one quad, channels cbase + 4h .. + 3; res: the lane's 8 bytes of the residual.
+__device__ __forceinline__ void store_quad(const ConvParams& p, int m, int cbase, int h, const float4& v0, const u32x4& res) {
+  float v[4] = {v0.x, v0.y, v0.z, v0.w};
+  const half4 rq = __builtin_bit_cast(half4, make_uint2(res[0], res[1]));
+  half4 o;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (p.res) v[j] += (float)rq[j];
+    o[j] = (f16)v[j];
+  }
+  if (p.relu) o = __builtin_elementwise_max(o, half4{});
+  if (m >= 0) *reinterpret_cast<half4*>(p.out + (size_t)m * p.out_pitch + cbase + 4 * h) = o;
+}
+
 // =============================================================================================
 // The small network's layers: at most 32 output channels, 16 or 32 input channels (or four
 // 4-channel pixels of the first layer) per tap, at most nine taps.  A layer is one launch and one
@@ -352,11 +409,10 @@ __global__ __launch_bounds__(256) void k_conv_direct(ConvParams p) {
 
 // =============================================================================================
 // Stage 2, 3x3 layers (all of the big network's convolutions but the stem): a workgroup's output
-// tile is a SPATIAL block, so that the nine taps read one shared input
-// patch in LDS.  Patch pixels are padded to 144 bytes and patch rows to 128 mod 256 bytes: the 16
-// lanes of one ds_read_b128 pass (two rows of 8 pixels) then fall into 16 different 16-byte bank
-// groups.  Every output accumulates chunk by chunk (64 input channels), tap by tap, four K-steps
-// of 16 per tap, whichever of the stride-1 kernels computes it: their results are bit-identical.
+// tile is a SPATIAL block or a run of pixels, so that the nine taps read one shared input
+// patch in LDS.  Patch pixels are padded to 144 bytes: the 16
+// lanes of one ds_read_b128 pass then fall into 16 different 16-byte bank
+// groups (two rows of 8 pixels: with patch rows of 128 mod 256 bytes).
 //
 // Tile order of all of them: workgroup id mod 8 selects the XCD, and each XCD (own L2) takes a run
 // of consecutive tiles.  Tiles are ordered in blocks of n_block channel tiles; inside a block the
@@ -539,187 +595,8 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
 }
 
 // =============================================================================================
-// 3x3 stride-1 pad-1 layers with several Cin chunks on grids of more than one round of workgroups
-// (stages 2-4 and the ConvLSTM gates from a few frames per launch on).  8 x 16 spatial tile x 64
-// channels.  The weights never touch LDS: they are packed on the host in MFMA fragment
-// order (one 1 KB block of 64 lanes x 16 bytes per 32 channels, tap and K-step of 16) and every
-// wavefront loads its "A" fragments straight into registers, three taps ahead.  On those grids
-// the layers are paced by LDS throughput (a tap step with the weights staged in LDS moves 48 KB of
-// fragment reads and 10 KB of writes per workgroup; writes run at under half the rate of
-// reads): without the weight tile the LDS carries the pixel fragments only (32 KB of reads per
-// tap step), the per-tap barrier disappears (one barrier per Cin chunk, for the patch), and
-// the weight bytes come through the vector memory path, which has room (16 KB per tap step
-// and workgroup; the two wavefronts that share a channel half fetch the same lines).
-// The input patch is double buffered: chunk c+1 streams into the other buffer during the
-// taps of chunk c, at most four vectors per thread in flight.
-// p.wt_frag: [cout_pad / 32][Cin chunk][tap][K-step][lane][8 halves]; a workgroup's K range is
-// one contiguous run per channel half, walked by a pointer that advances 4 KB per tap.
-// =============================================================================================
-__global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
-  constexpr int KC = 64, TH = 8, TW = 16, IPH = TH + 2, IPW = TW + 2, NPIX = IPH * IPW;
-  constexpr int PITCH = KC + 8;
-  constexpr int RP = (IPW * PITCH * 2 + ((128 - (IPW * PITCH * 2) % 256 + 256) % 256)) / 2;
-  static_assert((RP * 2) % 256 == 128, "plane row pitch must be 128 mod 256 bytes");
-  constexpr int PV = NPIX * 8;               // 16-byte vectors in a patch
-  constexpr int PL = (PV + 255) / 256;       // patch vectors per thread
-  static_assert(PL == 6, "the patch pipeline below is written out for six vectors per thread");
-  __shared__ __align__(16) f16 s_patch[2][IPH * RP];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (tile >= p.tiles_m * p.tiles_n) return;
-  const int blk = p.tiles_m * p.n_block, in_blk = tile % blk;       // tile order: see above
-  const int tm = in_blk / p.n_block;
-  const int tile_n = (tile / blk) * p.n_block + in_blk % p.n_block;
-  const int tiles_img = p.tiles_m / p.batch;
-  const int n0 = tile_n * 64;
-  const int cc_end = p.chunks_per_tap;
-  const int img = tm / tiles_img, ts = tm - img * tiles_img, ty = ts / p.tiles_x;
-  const int y0 = ty * TH, x0 = (ts - ty * p.tiles_x) * TW;
-  const int wm = wave & 1, wn = wave >> 1;
-
-  // ---- patch loader: LDS slot and source offset (in halves from p.in, -1: padding) per vector
-  int l_plds[PL], l_poff[PL];
-#pragma unroll
-  for (int i = 0; i < PL; ++i) {
-    const int v = tid + 256 * i;
-    const int pix = min(v >> 3, NPIX - 1), py = pix / IPW, px = pix - py * IPW;
-    l_plds[i] = v >= PV ? -1 : py * RP + px * PITCH + (v & 7) * 8;
-    const int iy = y0 + py - 1, ix = x0 + px - 1;
-    const bool inb = v < PV && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
-    l_poff[i] = inb ? ((img * p.hin + iy) * p.win + ix) * p.cin_pitch + (tid & 7) * 8 : -1;
-  }
-#define HS_LOAD_P(I_, CC_) \
-  st_p[(I_) & 3] = *reinterpret_cast<const u32x4*>(p.in + (l_poff[I_] >= 0 ? l_poff[I_] + (CC_) * KC : 0));
-#define HS_HAND_P(I_, PB_)                                                                     \
-  if (l_plds[I_] >= 0) {                                                                       \
-    const u32x4 zero_ = {0u, 0u, 0u, 0u};                                                      \
-    *reinterpret_cast<u32x4*>(&s_patch[PB_][l_plds[I_]]) = l_poff[I_] >= 0 ? st_p[(I_) & 3] : zero_; \
-  }
-  u32x4 st_p[4];
-
-  // ---- weight fragments: this wavefront's 32 channels, one 1 KB block per (chunk, tap, K-step)
-  const u32x4* wf = reinterpret_cast<const u32x4*>(p.wt_frag) +
-                    (size_t)(n0 / 32 + wn) * p.chunks_per_tap * (9 * 4 * 64) + lane;
-  const u32x4* const wf_last = wf + (size_t)(cc_end * 9 - 1) * (4 * 64);
-  u32x4 fa[3][4];
-#define HS_LOAD_A(S_)                                                                          \
-  {                                                                                            \
-    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) fa[S_][ks] = wf[ks * 64];                 \
-    wf = wf + 4 * 64 <= wf_last ? wf + 4 * 64 : wf_last;   /* the last steps re-read the last tap */ \
-  }
-
-  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  floatx16 acc[2] = {zero16, zero16};
-  const int fp_off = (4 * wm + (r >> 3)) * RP + (r & 7) * PITCH + h * 8;
-
-  // A chunk is 36 K-steps of 16 (tap-major, four per tap); Q_ and LAST_ are literals.  Weight
-  // stage (Q_ / 4) % 3 holds the tap's fragments and is refilled, behind their last use, with
-  // those of the step three taps ahead.  Pixel fragments are read from LDS BD K-steps before
-  // the MFMAs that use them (a ring of BD + 1 register sets), so that an LDS round trip hides
-  // behind 2 * BD MFMAs of this wavefront; only the first BD steps of a chunk, behind its
-  // barrier, wait for theirs.  Vector i of the next chunk's patch is fetched at tap i and
-  // handed to the other buffer at tap i + 3.
-  constexpr int BD = 3;
-  half8 bf[BD + 1][2];
-#define HS_READ_B(Q_)                                                                          \
-  {                                                                                            \
-    const f16* fp_ = &s_patch[pb][fp_off + ((Q_) / 12) * RP + (((Q_) / 4) % 3) * PITCH + ((Q_) % 4) * 16]; \
-    _Pragma("unroll") for (int g = 0; g < 2; ++g)                                              \
-      bf[(Q_) % (BD + 1)][g] = *reinterpret_cast<const half8*>(fp_ + g * 8 * PITCH);           \
-  }
-#define HS_KSTEP(Q_, LAST_)                                                                    \
-  {                                                                                            \
-    if ((Q_) + BD < 36) HS_READ_B((Q_) + BD)                                                   \
-    if ((Q_) % 4 == 0) {                                                                       \
-      if (!(LAST_) && (Q_) / 4 >= 3) HS_HAND_P((Q_) / 4 - 3, pb ^ 1)                           \
-      if (!(LAST_) && (Q_) / 4 < PL) HS_LOAD_P((Q_) / 4, cc + 1)                               \
-    }                                                                                          \
-    const half8 a_ = __builtin_bit_cast(half8, fa[((Q_) / 4) % 3][(Q_) % 4]);                  \
-    _Pragma("unroll") for (int g = 0; g < 2; ++g)                                              \
-      acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_, bf[(Q_) % (BD + 1)][g], acc[g], 0, 0, 0); \
-    if ((Q_) % 4 == 3) HS_LOAD_A(((Q_) / 4) % 3)                                               \
-    __builtin_amdgcn_sched_barrier(0);                                                         \
-  }
-#define HS_TAP(T_, LAST_)                                                                      \
-  HS_KSTEP(4 * (T_), LAST_) HS_KSTEP(4 * (T_) + 1, LAST_) HS_KSTEP(4 * (T_) + 2, LAST_)        \
-  HS_KSTEP(4 * (T_) + 3, LAST_)
-#define HS_CHUNK(LAST_)                                                                        \
-  HS_READ_B(0) HS_READ_B(1) HS_READ_B(2)                                                       \
-  HS_TAP(0, LAST_) HS_TAP(1, LAST_) HS_TAP(2, LAST_) HS_TAP(3, LAST_) HS_TAP(4, LAST_)         \
-  HS_TAP(5, LAST_) HS_TAP(6, LAST_) HS_TAP(7, LAST_) HS_TAP(8, LAST_)
-  static_assert(BD == 3, "HS_CHUNK primes three K-steps");
-
-  // ---- prologue: first patch into buffer 0, first three taps of weights into the stages
-  int cc = 0, pb = 0;
-  {
-    u32x4 first[PL];
-#pragma unroll
-    for (int i = 0; i < PL; ++i)
-      first[i] = *reinterpret_cast<const u32x4*>(p.in + (l_poff[i] >= 0 ? l_poff[i] + cc * KC : 0));
-    HS_LOAD_A(0) HS_LOAD_A(1) HS_LOAD_A(2)
-#pragma unroll
-    for (int i = 0; i < PL; ++i)
-      if (l_plds[i] >= 0) {
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4*>(&s_patch[0][l_plds[i]]) = l_poff[i] >= 0 ? first[i] : zero;
-      }
-  }
-  __syncthreads();
-
-  const int oy = y0 + 4 * wm + (r >> 3);
-  const int n_base = n0 + wn * 32 + h * 4;
-  for (; cc + 1 < cc_end; ++cc) {
-    HS_CHUNK(false)
-    __syncthreads();      // the next patch is complete, and every wavefront is done with this one
-    pb ^= 1;
-  }
-  // Residual of the block's second convolution: fetched while the last chunk is computed, as two
-  // 16-byte pieces per pixel (res_octets_to_quads)
-  const bool res_here = p.res != nullptr && !p.use_partial;
-  half4 res_pre[2][4];
-  u32x4 res_raw[2][2];
-  if (res_here) {
-    const int oy_c = min(oy, p.hout - 1);
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const int ox_c = min(x0 + 8 * g + (r & 7), p.wout - 1);
-      const f16* rp = p.res + (size_t)(img * p.img_m + oy_c * p.wout + ox_c) * p.res_pitch + n0 + wn * 32 + h * 8;
-      res_raw[g][0] = *reinterpret_cast<const u32x4*>(rp);
-      res_raw[g][1] = *reinterpret_cast<const u32x4*>(rp + 16);
-    }
-  }
-  HS_CHUNK(true)
-
-  // ---- epilogue: accumulator quad i of group g = channels n_base + 8*i .. +3 of pixel (oy, ox_g)
-#pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    const int ox = x0 + 8 * g + (r & 7);
-    const bool valid = oy < p.hout && ox < p.wout;
-    const int m = img * p.img_m + oy * p.wout + ox;
-    if (!p.use_partial) {                 // every lane takes part in the exchanges
-      if (res_here) res_octets_to_quads(res_raw[g], res_pre[g]);
-      store_octets(p, valid, m, n0 + wn * 32, h, acc[g], res_pre[g], res_here);
-    } else if (valid) {
-      float* dst = p.partial + (size_t)m * p.cout_pad + n_base;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        *reinterpret_cast<float4*>(dst + 8 * i) =
-            make_float4(acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);
-    }
-  }
-#undef HS_CHUNK
-#undef HS_TAP
-#undef HS_KSTEP
-#undef HS_READ_B
-#undef HS_LOAD_A
-#undef HS_HAND_P
-#undef HS_LOAD_P
-}
-
-// =============================================================================================
 // 3x3 stride-2 pad-1 layers (with the block's 1x1 stride-2 projection riding along) on grids of
-// at least 1.5 workgroups per CU: the stride-2 counterpart of k_conv3x3_dira.  Output tile 8 x 8
+// at least 1.5 workgroups per CU.  Output tile 8 x 8
 // pixels x 128 channels; wavefront w = all 64 pixels (two groups of four rows), channels
 // 32*w .. +31: a weight fragment is fetched by one wavefront only and serves two MFMAs, and
 // the patch -- the heavy operand of a stride-2 tile -- serves 128 channels.
@@ -741,7 +618,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3x3_dira(ConvParams p) {
 //     first patch and weights are fetched during the last taps of the current tile), so the
 //     short K loops of the 64-channel layer do not pay a cold start per tile.
 // Per output the K order is chunk, half chunk, tap, K-step: within a chunk the two halves are
-// summed one after the other, not interleaved tap by tap as in k_conv3x3_kw<2, ...>; results
+// summed one after the other, not interleaved tap by tap as in k_conv3x3s2_kw; results
 // agree with that kernel to fp32 rounding, not bit for bit.
 // =============================================================================================
 __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
@@ -945,31 +822,24 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
 }
 
 // =============================================================================================
-// 3x3 pad-1 layers (stride 1, and stride 2 with the block's 1x1 stride-2 projection riding along)
+// 3x3 stride-2 pad-1 layers with the block's 1x1 stride-2 projection riding along
 // on SMALL grids: one or a few frames per launch.  There a layer is a launch, one memory round trip
 // and a K loop whose operands have to get into the few CUs at work; what bounds it is those
 // latencies and the 64 bytes per clock a CU takes in, not the matrix rate.  So the K splits live
 // in ONE workgroup (as workgroups of their own they need a second launch to add the partial
 // sums), the tile is small so that the grid covers the device, and every wavefront streams its
 // operands deep ahead without a barrier per tap:
-//   - wavefront (split, cg) computes 32 * PG pixels (PG groups of 4 x 8) x 32 channels over the Cin
+//   - wavefront (split, cg) computes 4 x 8 pixels x 32 channels over the Cin
 //     chunks of its split; its weight fragments come straight from memory (fragment order,
-//     p.wt_frag) through a ring of FR register sets, so up to FR KB per wavefront are in flight;
+//     p.wt_frag) through a ring of 12 register sets (18 spill: 10 to 30 % slower), so up to 12 KB per wavefront
+//     are in flight;
 //   - the CW wavefronts of a split (channel groups) share the input patch of the chunk in LDS;
 //     with CW == 1 the patch is the wavefront's own and the K loop has no barrier at all;
 //   - the partial tiles of the NS splits are added through LDS in split order.
-// Per output: chunk, tap, K-step within a split, then the splits in order.  With one split (the
-// larger of these grids) stride-1 results are bit-identical to k_conv3x3_dira's.
-// Stride 2: the patch is stored as four parity planes (pixel (py, px) in plane (py & 1, px & 1) at
+// Per output: chunk, tap, K-step within a split, then the splits in order.
+// The patch is stored as four parity planes (pixel (py, px) in plane (py & 1, px & 1) at
 // (py / 2, px / 2)), so that a tap's lanes read neighbouring pixels, and the 1x1 stride-2 projection,
 // which reads exactly the centre tap's pixels, is a tenth tap with its own accumulators.
-// Ring depth FR, measured over maps of 5 x 9 to 60 x 107 pixels and 1 to 16 frames per launch: 12 for
-// PG == 1 (36 is 5 to 7 % slower: fewer workgroups per CU), 18 for PG == 2 (12: equal), 12 at stride 2
-// (18 spills: 10 to 30 % slower).
-// Against the kernels they replace (weights staged through LDS, K splits as workgroups of their own
-// and a launch to add them), one 1080p frame, medians of kernel traces: 256-channel layers 9.0 + 3.5 -> 7.7
-// to 8.2 us, 512-channel layers 9.1 + 3.9 -> 7.8 to 8.4 us; of those 1.8 us are launch and set-up, 0.8 us the
-// first operands' latency, 2 us the weight stream (288 KB per CU), 1.7 us the sum over the splits and the store.
 // =============================================================================================
 // Touches this workgroup's share of the next layer's weights (one 4-byte load per 128-byte line),
 // so that they are on their way into the last-level cache when that layer starts: streamed from
@@ -982,20 +852,20 @@ __device__ __forceinline__ uint32_t prefetch_next(const ConvParams& p, int block
   return x;
 }
 
-template <int STRIDE, int PG, int CW, int NW, int FR>
-__global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k_conv3x3_kw(ConvParams p) {
-  constexpr int NS = NW / CW;
-  constexpr int TH = 4 * PG, TW = 8;
-  constexpr int IPH = STRIDE * TH + 3 - STRIDE, IPW = STRIDE * TW + 3 - STRIDE, NPIX = IPH * IPW;
-  constexpr int PLH = STRIDE == 1 ? IPH : TH + 1, PLW = STRIDE == 1 ? IPW : TW + 1;
+template <int CW, int NW>
+__global__ __launch_bounds__(64 * NW, NW / CW > 2 ? 1 : 2) void k_conv3x3s2_kw(ConvParams p) {
+  constexpr int NS = NW / CW, FR = 12;
+  constexpr int TH = 4, TW = 8;
+  constexpr int IPH = 2 * TH + 1, IPW = 2 * TW + 1, NPIX = IPH * IPW;
+  constexpr int PLH = TH + 1, PLW = TW + 1;
   constexpr int PITCH = 64 + 8;
   constexpr int RP = (PLW * PITCH * 2 + ((128 - (PLW * PITCH * 2) % 256 + 256) % 256)) / 2;
   static_assert((RP * 2) % 256 == 128, "plane row pitch must be 128 mod 256 bytes");
-  constexpr int PATCH = STRIDE * STRIDE * PLH * RP;         // halves per split
+  constexpr int PATCH = 4 * PLH * RP;                       // halves per split
   constexpr int PV = NPIX * 8, PL = (PV + 64 * CW - 1) / (64 * CW);   // 16-byte vectors, per lane
-  constexpr int NG = STRIDE == 2 ? 2 * PG : PG;             // accumulator groups (projection: PG more)
   constexpr int RED = 8 * 34;                               // float4s per group of partial sums
-  constexpr int BYTES = NS * PATCH * 2 > NW * NG * RED * 16 ? NS * PATCH * 2 : NW * NG * RED * 16;
+  // accumulators: the layer's, the projection's
+  constexpr int BYTES = NS * PATCH * 2 > NW * 2 * RED * 16 ? NS * PATCH * 2 : NW * 2 * RED * 16;
   static_assert(36 % FR == 0, "the fragment ring must divide a chunk's 36 K-steps");
   __shared__ __align__(16) unsigned char s_raw[BYTES];
 
@@ -1012,7 +882,7 @@ __global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k
   const int n0 = n_tile + 32 * cg;                                // this wavefront's channels
   const int cc_begin = split * p.chunks_per_split;
   const int cc_end = min(p.chunks_per_tap, cc_begin + p.chunks_per_split);
-  const bool has_proj = STRIDE == 2 && p.wt2_frag != nullptr;
+  const bool has_proj = p.wt2_frag != nullptr;
 
   // ---- patch loader: the CW wavefronts of a split fetch its patch together
   f16* const s_patch = reinterpret_cast<f16*>(s_raw) + split * PATCH;
@@ -1022,9 +892,8 @@ __global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k
     const int vec = cg * 64 + lane + 64 * CW * i, pix = min(vec >> 3, NPIX - 1), v = vec & 7;
     const int py = pix / IPW, px = pix - py * IPW;
     l_plds[i] = vec >= PV ? -1
-                : STRIDE == 1 ? py * RP + px * PITCH + v * 8
-                              : (((py & 1) * 2 + (px & 1)) * PLH + (py >> 1)) * RP + (px >> 1) * PITCH + v * 8;
-    const int iy = STRIDE * y0 + py - 1, ix = STRIDE * x0 + px - 1;
+                         : (((py & 1) * 2 + (px & 1)) * PLH + (py >> 1)) * RP + (px >> 1) * PITCH + v * 8;
+    const int iy = 2 * y0 + py - 1, ix = 2 * x0 + px - 1;
     const bool inb = vec < PV && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
     l_poff[i] = inb ? ((img * p.hin + iy) * p.win + ix) * p.cin_pitch + v * 8 : -1;
   }
@@ -1059,44 +928,36 @@ __global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k
 
   const int fp_off = (r >> 3) * RP + (r & 7) * PITCH + h * 8;
   const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  floatx16 acc[NG];
-#pragma unroll
-  for (int g = 0; g < NG; ++g) acc[g] = zero16;
+  floatx16 acc = zero16, acc2 = zero16;
 
   // K-step Q_ (literal) of a chunk: tap Q_ / 4 (9: the projection, on the centre tap's pixels), K-step
   // Q_ % 4.  Pixel fragments are read BD steps ahead through a ring.  LAST_: no chunk follows.
-  constexpr int BD = 3, QN = STRIDE == 2 ? 40 : 36;
-  half8 bf[BD + 1][PG];
+  constexpr int BD = 3, QN = 40;
+  half8 bf[BD + 1];
 #define HS_TAPQ(Q_) ((Q_) / 4 == 9 ? 4 : (Q_) / 4)
 #define HS_READ_B(Q_)                                                                          \
   {                                                                                            \
     const int ky_ = HS_TAPQ(Q_) / 3, kx_ = HS_TAPQ(Q_) % 3;                                    \
-    const int toff_ = STRIDE == 1 ? ky_ * RP + kx_ * PITCH                                     \
-                                  : (((ky_ & 1) * 2 + (kx_ & 1)) * PLH + (ky_ >> 1)) * RP + (kx_ >> 1) * PITCH; \
-    _Pragma("unroll") for (int g = 0; g < PG; ++g)                                             \
-      bf[(Q_) % (BD + 1)][g] = *reinterpret_cast<const half8*>(                                \
-          &s_patch[fp_off + toff_ + 4 * g * RP + ((Q_) % 4) * 16]);                            \
+    const int toff_ = (((ky_ & 1) * 2 + (kx_ & 1)) * PLH + (ky_ >> 1)) * RP + (kx_ >> 1) * PITCH; \
+    bf[(Q_) % (BD + 1)] = *reinterpret_cast<const half8*>(&s_patch[fp_off + toff_ + ((Q_) % 4) * 16]); \
   }
 #define HS_CHUNK(LAST_)                                                                        \
   {                                                                                            \
     HS_READ_B(0) HS_READ_B(1) HS_READ_B(2)                                                     \
     _Pragma("unroll") for (int q = 0; q < 36; ++q) {                                           \
       if (q + BD < QN) HS_READ_B(q + BD)                                                       \
-      const half8 a_ = __builtin_bit_cast(half8, fa[q % FR]);                                  \
-      _Pragma("unroll") for (int g = 0; g < PG; ++g)                                           \
-        acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_, bf[q % (BD + 1)][g], acc[g], 0, 0, 0); \
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, fa[q % FR]),      \
+                                                   bf[q % (BD + 1)], acc, 0, 0, 0);            \
       if (!(LAST_) || q + FR < 36) fa[q % FR] = wf[(q + FR) * 64];                             \
       __builtin_amdgcn_sched_barrier(0);                                                       \
     }                                                                                          \
     wf += 36 * 64;                                                                             \
-    if (STRIDE == 2 && has_proj) {                                                             \
+    if (has_proj) {                                                                            \
       wp += 4 * 64;                                                                            \
       _Pragma("unroll") for (int q = 36; q < 40; ++q) {                                        \
         if (q + BD < QN) HS_READ_B(q + BD)                                                     \
-        const half8 a_ = __builtin_bit_cast(half8, fp2[q % 4]);                                \
-        _Pragma("unroll") for (int g = 0; g < PG; ++g)                                         \
-          acc[NG - PG + g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(                           \
-              a_, bf[q % (BD + 1)][g], acc[NG - PG + g], 0, 0, 0);                             \
+        acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, fp2[q % 4]),   \
+                                                      bf[q % (BD + 1)], acc2, 0, 0, 0);        \
         if (!(LAST_)) fp2[q % 4] = wp[(q % 4) * 64];                                           \
       }                                                                                        \
     }                                                                                          \
@@ -1105,22 +966,16 @@ __global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k
   HS_LOAD_PATCH(cc_begin)
 #pragma unroll
   for (int q = 0; q < FR; ++q) fa[q] = wf[q * 64];
-  if (STRIDE == 2) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) fp2[q] = wp[q * 64];
-  }
-  // the residual of the outputs this thread will finish: channel quad t % (8 * CW) of pixel t / (8 * CW)
-  constexpr int ITEMS = PG * 256 * CW / (64 * NW) + (PG * 256 * CW % (64 * NW) != 0 ? 1 : 0);
-  half4 res[ITEMS];
+  for (int q = 0; q < 4; ++q) fp2[q] = wp[q * 64];
+  // the outputs this thread will finish: channel quad t % (8 * CW) of pixel t / (8 * CW)
+  constexpr int ITEMS = (256 * CW + 64 * NW - 1) / (64 * NW);
   int o_m[ITEMS];                    // output pixel, -1: outside the image or no such item
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const int t = tid + 64 * NW * k, px = t / (8 * CW);
+    const int px = (tid + 64 * NW * k) / (8 * CW);
     const int oy = y0 + (px >> 3), ox = x0 + (px & 7);
-    o_m[k] = px < 32 * PG && oy < p.hout && ox < p.wout ? img * p.img_m + oy * p.wout + ox : -1;
-    if (p.res)
-      res[k] = *reinterpret_cast<const half4*>(p.res + (size_t)max(o_m[k], 0) * p.res_pitch + n_tile +
-                                               (t % (8 * CW)) * 4);
+    o_m[k] = px < 32 && oy < p.hout && ox < p.wout ? img * p.img_m + oy * p.wout + ox : -1;
   }
   HS_HAND_PATCH()
   // every wavefront goes through chunks_per_split rounds (the barriers are for all of them); the
@@ -1145,75 +1000,309 @@ __global__ __launch_bounds__(64 * NW, STRIDE == 2 && NW / CW > 2 ? 1 : 2) void k
 #undef HS_SYNC_PATCH
 #undef HS_LOAD_PATCH
 
-  // ---- add the partial tiles: accumulator quad i of group g of lane (r, h) = channels 8 * i + 4 * h ..
-  // +3 (quad 2 * i + h) of pixel 32 * g + r.  34 float4s per quad row: reads and writes conflict free
+  // ---- add the partial tiles: accumulator quad i of lane (r, h) = channels 8 * i + 4 * h .. +3 (quad 2 * i + h) of
+  // pixel r.  34 float4s per quad row: reads and writes conflict free
   float4* const s_red = reinterpret_cast<float4*>(s_raw);
   const uint32_t touched = prefetch_next(p, tile, p.tiles_m * p.tiles_n);
   __syncthreads();                   // every wavefront is done with its patch
 #pragma unroll
-  for (int g = 0; g < NG; ++g)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      s_red[(wave * NG + g) * RED + (2 * i + h) * 34 + r] =
-          make_float4(acc[g][4 * i], acc[g][4 * i + 1], acc[g][4 * i + 2], acc[g][4 * i + 3]);
+  for (int i = 0; i < 4; ++i) {
+    float4* const dst = s_red + wave * 2 * RED + (2 * i + h) * 34 + r;
+    dst[0] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+    dst[RED] = make_float4(acc2[4 * i], acc2[4 * i + 1], acc2[4 * i + 2], acc2[4 * i + 3]);
+  }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
     if (o_m[k] < 0) continue;
     const int t = tid + 64 * NW * k, px = t / (8 * CW), c4 = t % (8 * CW), n = n_tile + 4 * c4;
-    const float4* src = s_red + ((c4 >> 3) * NG + (px >> 5)) * RED + (c4 & 7) * 34 + (px & 31);
-    float4 a = src[0];
-#pragma unroll
-    for (int w = 1; w < NS; ++w) {
-      const float4 b = src[w * CW * NG * RED];
-      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    }
-    if (p.use_partial) {
-      *reinterpret_cast<float4*>(p.partial + (size_t)o_m[k] * p.cout_pad + n) = a;
-    } else {
-      float v[4] = {a.x, a.y, a.z, a.w};
-      half4 o;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (p.res) v[j] += (float)res[k][j];
-        if (p.relu) v[j] = fmaxf(v[j], 0.0f);
-        o[j] = (f16)v[j];
-      }
-      *reinterpret_cast<half4*>(p.out + (size_t)o_m[k] * p.out_pitch + n) = o;
-    }
-    if (has_proj) {                  // projection output: no residual, no ReLU
-      const float4* src2 = src + PG * RED;
-      float4 b = src2[0];
+    const float4* src = s_red + (c4 >> 3) * 2 * RED + (c4 & 7) * 34 + px;
+    auto sum = [&](const float4* at) {
+      float4 a = at[0];
 #pragma unroll
       for (int w = 1; w < NS; ++w) {
-        const float4 d = src2[w * CW * NG * RED];
-        b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
+        const float4 b = at[w * CW * 2 * RED];
+        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
       }
-      half4 o2;
-      o2[0] = (f16)b.x; o2[1] = (f16)b.y; o2[2] = (f16)b.z; o2[3] = (f16)b.w;
+      return a;
+    };
+    const float4 a = sum(src);
+    half4 o = {(f16)a.x, (f16)a.y, (f16)a.z, (f16)a.w};
+    if (p.relu) o = __builtin_elementwise_max(o, half4{});
+    *reinterpret_cast<half4*>(p.out + (size_t)o_m[k] * p.out_pitch + n) = o;
+    if (has_proj) {                  // projection output: no ReLU
+      const float4 b = sum(src + RED);
+      const half4 o2 = {(f16)b.x, (f16)b.y, (f16)b.z, (f16)b.w};
       *reinterpret_cast<half4*>(p.out2 + (size_t)o_m[k] * p.out2_pitch + n) = o2;
     }
   }
   asm volatile("" ::"v"(touched));
 }
 
+// =============================================================================================
+// 3x3 stride-1 pad-1 layers with several Cin chunks (stages 2-4 and the ConvLSTM gates), at every size.
+// A tile is 32 * CW channels x a RUN of 32 * PG consecutive pixels: the map is cut into strips of run_w columns, and
+// the pixels of all strips of all images of the launch, row by row, are one list that the runs are cut from.  So no
+// tile but the last is partly empty, whatever the map (tiles of 8 x 16 pixels are to 79 % full on a 27 x 15 map), and
+// the host can pick the tile whose count fills the CUs (Builder::choose_run).
+//   - The patch under a run, the border columns and a row of zeros between the images included, goes through LDS one
+//     chunk of 64 input channels at a time, double buffered: a chunk's loads are issued two chunks ahead, one barrier
+//     per chunk.  Rows are padded so that the pixel behind a row's last one lies in the bank group it would lie in
+//     without the border pixels between them: the lanes of a run never meet (gates, twelve 854 x 480 frames, without:
+//     a fifth of the cycles).
+//   - The KS K splits are wavefronts of the workgroup: of the four K-steps of every tap a wavefront takes 4 / KS.  Each
+//     weight fragment is fetched by one wavefront only, straight from memory through a ring of FR register sets, and
+//     serves PG MFMAs: what bounds these layers is the 64 bytes per clock a CU takes in, and with the splits inside the
+//     tile a tile's weights come in once (two wavefronts that share a channel group fetch them twice).
+//   - All loads have scalar offsets into buffers of known size: no address arithmetic in the loop, and padding reads
+//     as zeros (flat pointers and selects instead: 4 to 10 % of a launch).
+//   - The partial sums meet in LDS and are added in pairs, PASSES times a part of them; every wavefront finishes its share
+//     of the channels.
+// Per output and K split: chunk, tap, K-step; then the splits in pairs.
+// PL: 16-byte vectors of a patch per thread; LDS: bytes of a patch buffer (128 of them taken by vectors beyond the
+// patch); FR, BD: weight and pixel fragments in flight; OCC: workgroups per CU.  The values are the fastest of those
+// tried on eleven sizes from 192 x 110 x 1 to 854 x 480 x 12 frames.  (A wavefront with 64 channels x 64 to 160 pixels
+// and four K splits moves the fewest bytes, but its registers leave one workgroup per CU or too few fragments in
+// flight: 2 to 10 % slower.)
+// Against the kernels it replaced (8 x 16-pixel tiles x 64 channels, or 32 to 64-pixel tiles with the K splits
+// chunk by chunk), mean us per layer of 128 / 256 / 512 channels and gates: one 288 x 160 frame 6.4 / 6.3 / 7.0 / 8.9
+// -> 4.5 / 5.1 / 6.6 / 8.3, one 854 x 480 frame 7.5 / 7.5 / 7.4 / 15.2 -> 6.2 / 6.2 / 6.9 / 11.2, four 641 x 361
+// frames 12.7 / 12.5 / 16.4 / 27.0 -> 8.5 / 8.5 / 9.6 / 17.5, sixteen 416 x 240 frames 15.1 / 14.5 / 18.7 / 31.5 ->
+// 12.9 / 12.0 / 12.2 / 27.2, twelve 854 x 480 frames 32.7 / 32.4 / 35.1 / 81 -> 29.6 / 25.8 / 26.3 / 62.
+// =============================================================================================
+template <int PG, int KS, int CW, int FR, int BD, int PL, int LDS, int OCC>
+__global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p) {
+  constexpr int NW = KS * CW, C = 32 * CW, PITCH = kRunPitch;
+  constexpr int KK = 4 / KS, SPC = 9 * KK;        // K-steps of a tap, of a chunk, that a wavefront takes
+  static_assert(2 * SPC % FR == 0, "the fragment ring must divide the K-steps of two chunks");
+  // accumulators are finished in pieces of 16 channels x 32 pixels (QU = 2 quads per lane), or 8 where there are fewer
+  // such pieces than K splits
+  constexpr int QU = 2 * PG < KS ? 1 : 2, UNITS = 4 / QU * PG, UB = QU * 1024;
+  // partial sums that meet in LDS at a time, and passes over them
+  constexpr int UP = KS == 1 || UNITS * NW * UB <= 2 * LDS || UNITS * NW * UB <= 65536 ? UNITS : KS, PASSES = UNITS / UP, UN = UP / KS;
+  static_assert(UNITS % UP == 0 && UP % KS == 0, "every K split finishes the same number of pieces");
+  constexpr int RED = KS == 1 ? 0 : (PASSES > 1 ? 2 : 1) * UP * NW * UB, SHM = RED > 2 * LDS ? RED : 2 * LDS;
+  __shared__ __align__(16) unsigned char s_raw[SHM];
+  f16* const s_patch = reinterpret_cast<f16*>(s_raw);
+
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wave % KS, cw = wave / KS;
+  const uint32_t tile = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
+  if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
+  const uint32_t nb = (uint32_t)p.n_block;                         // a power of two; tile order: see above
+  const uint32_t t_blk = run_div31(tile, p.run_by_blk), in_blk = tile - t_blk * (uint32_t)p.tiles_m * nb;
+  const int n0 = (int)(t_blk * nb + (in_blk & (nb - 1))) * C;
+  const RunOrigin org = run_origin(p.run, in_blk >> p.run_nb_shift);
+  const int rw = p.run.strip_w + 2, rp = run_row_pitch(p.run.strip_w);   // patch pixels, LDS halves per row
+
+  // ---- patch loader: pixel (tid + threads * i) / 8 of the patch: source offset in bytes (padding: reads as
+  // zeros), LDS slot (beyond the patch: 128 bytes that nothing reads)
+  int l_poff[PL], l_lds[PL];
+  {
+    const uint32_t pix = (uint32_t)tid >> 3;
+    uint32_t prow = run_div23(pix, p.run.by23_row), pcol = pix - prow * (uint32_t)rw;
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+      int m;
+      const bool fits = prow < (uint32_t)p.run.rows, in = run_patch_pixel(p.run, org, prow, pcol, m) && fits;
+      l_poff[i] = in ? (m * p.cin_pitch + (tid & 7) * 8) * 2 : kOutside;
+      l_lds[i] = fits ? (int)prow * rp + (int)pcol * PITCH + (tid & 7) * 8 : LDS / 2 - 64 + (tid & 7) * 8;
+      prow += (uint32_t)p.run.step_q;
+      pcol += (uint32_t)p.run.step_r;
+      if (pcol >= (uint32_t)rw) { pcol -= (uint32_t)rw; ++prow; }
+    }
+  }
+  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes);
+  u32x4 st_p[PL];
+#define HS_LOAD_P(I_, CC_) st_p[I_] = load16(in_buf, l_poff[I_], (CC_) * 128);
+#define HS_HAND_P(V_, I_, B_) *reinterpret_cast<u32x4*>(&s_patch[(B_) * (LDS / 2) + l_lds[I_]]) = (V_);
+
+  // ---- prologue: loads of the first patch (and the second), of the weight ring, in the order of the loop below,
+  // whose waits count the loads issued since
+  const int n_cc = p.chunks_per_tap;                               // even
+  u32x4 first[PL];
+#pragma unroll
+  for (int i = 0; i < PL; ++i)
+    first[i] = load16(in_buf, l_poff[i], 0);
+#pragma unroll
+  for (int i = 0; i < PL; ++i) HS_LOAD_P(i, 1)
+  int wf = ((n0 / 32 + cw) * n_cc * 36 + ks * KK) * 1024;          // bytes from wt_frag on
+  // K-step S_ (literal, counted from an even chunk) of this wavefront
+#define HS_WOFF(S_) ((((S_) / SPC) * 36 + (((S_) % SPC) / KK) * 4 + (S_) % KK) * 1024)
+  u32x4 fa[FR];
+#pragma unroll
+  for (int s = 0; s < FR; ++s) fa[s] = load16(w_buf, lane * 16, wf + HS_WOFF(s));
+  // ---- pixels of this wavefront: LDS offset of a pixel's first tap, output pixel (-1: none)
+  auto pixel = [&](int g, int& lds, int& m) {
+    uint32_t row, col;
+    run_pixel(p.run, org, 32 * g + r, row, col, m);
+    lds = (int)row * rp + (int)col * PITCH + h * 8 + ks * KK * 16;
+  };
+  int fpo[PG], o_m[PG];
+#pragma unroll
+  for (int g = 0; g < PG; ++g) pixel(g, fpo[g], o_m[g]);
+#pragma unroll
+  for (int i = 0; i < PL; ++i) HS_HAND_P(first[i], i, 0)
+  __syncthreads();
+
+  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  floatx16 acc[PG];
+#pragma unroll
+  for (int g = 0; g < PG; ++g) acc[g] = zero16;
+  // Pixel fragment F_ = K-step * PG + group of a chunk, read BD fragments ahead of its MFMAs
+  half8 bf[BD + 1];
+#define HS_READ_B(U_, F_)                                                                      \
+  bf[(F_) % (BD + 1)] = *reinterpret_cast<const half8*>(                                       \
+      &s_patch[(U_) * (LDS / 2) + fpo[(F_) % PG] + ((F_) / PG / KK / 3) * rp +                 \
+               (((F_) / PG / KK) % 3) * PITCH + (((F_) / PG) % KK) * 16]);
+  // Chunk cc + U_ (U_ literal: its parity).  The next chunk's patch, fetched a chunk ago, goes to the other buffer
+  // spread over the K-steps, and its registers are refilled with the chunk behind that.
+#define HS_CHUNK(U_, LAST_)                                                                    \
+  {                                                                                            \
+    _Pragma("unroll") for (int f = 0; f < BD; ++f) HS_READ_B(U_, f)                            \
+    _Pragma("unroll") for (int s = 0; s < SPC; ++s) {                                          \
+      _Pragma("unroll") for (int i = 0; i < PL; ++i)                                           \
+        if ((2 * i + 1) * SPC / (2 * PL) == s && (!(LAST_) || (U_) == 0)) {                    \
+          HS_HAND_P(st_p[i], i, 1 - (U_))                                                      \
+          if (!(LAST_)) HS_LOAD_P(i, min(cc + (U_) + 2, n_cc - 1))                             \
+        }                                                                                      \
+      _Pragma("unroll") for (int g = 0; g < PG; ++g) {                                         \
+        if (s * PG + g + BD < SPC * PG) HS_READ_B(U_, s * PG + g + BD)                         \
+        acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(                                       \
+            __builtin_bit_cast(half8, fa[((U_) * SPC + s) % FR]), bf[(s * PG + g) % (BD + 1)], acc[g], 0, 0, 0); \
+        if (PG > 2) __builtin_amdgcn_sched_barrier(0);                                         \
+      }                                                                                        \
+      if (!(LAST_) || (U_) * SPC + s + FR < 2 * SPC)                                           \
+        fa[((U_) * SPC + s) % FR] = load16(w_buf, lane * 16, wf + HS_WOFF((U_) * SPC + s + FR)); \
+      __builtin_amdgcn_sched_barrier(0);                                                       \
+    }                                                                                          \
+  }
+  int cc = 0;
+  for (; cc + 2 < n_cc; cc += 2) {
+    HS_CHUNK(0, false)
+    __syncthreads();
+    HS_CHUNK(1, false)
+    __syncthreads();
+    wf += 72 * 1024;
+  }
+  // residual of the pieces this wavefront finishes (without one: any address, so that the loads are
+  // unconditional), fetched behind the last chunks
+  u32x4 res_raw[PASSES][UN];
+  {
+    const f16* const rsp = p.res ? p.res + n0 + cw * 32 + 4 * QU * h : p.in;
+    const int pitch = p.res ? p.res_pitch : 0;
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps)
+#pragma unroll
+      for (int k = 0; k < UN; ++k) {
+        const int q = (ps * UP + ks * UN + k) * QU;
+        int lds, m;
+        pixel(q / 4, lds, m);
+        const f16* const at = rsp + (size_t)max(m, 0) * pitch + (p.res ? 8 * (q % 4) : 0);
+        if (QU == 2) {
+          res_raw[ps][k] = *reinterpret_cast<const u32x4*>(at);
+        } else {
+          const uint2 v = *reinterpret_cast<const uint2*>(at);
+          res_raw[ps][k] = {v.x, v.y, 0u, 0u};
+        }
+      }
+  }
+  HS_CHUNK(0, true)
+  __syncthreads();
+  HS_CHUNK(1, true)
+#undef HS_CHUNK
+#undef HS_READ_B
+#undef HS_WOFF
+#undef HS_HAND_P
+#undef HS_LOAD_P
+
+  const uint32_t touched = prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n);
+  if (KS > 1) __syncthreads();       // every wavefront is done with the patches
+#pragma unroll
+  for (int ps = 0; ps < PASSES; ++ps) {
+    // (the passes take the two halves of the LDS in turn: the barrier of one pass orders the next one's writes
+    // behind the reads of the one before)
+    float4* const s_red = reinterpret_cast<float4*>(s_raw) + (PASSES > 1 ? (ps & 1) * UP * NW * (UB / 16) : 0) +
+                          (size_t)(wave / KS) * KS * UP * (UB / 16) + lane;
+    if (KS > 1) {
+#pragma unroll
+      for (int u = 0; u < UP; ++u)
+        if (u / UN != ks) {
+          const int q = (ps * UP + u) * QU;                        // first quad of the piece
+          const floatx16& a = acc[q / 4];
+#pragma unroll
+          for (int j = 0; j < QU; ++j) {
+            const int o = 4 * (q % 4 + j);
+            s_red[(ks * UP + u) * (UB / 16) + 64 * j] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
+          }
+        }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < UP; ++u)
+      if (u / UN == ks) {
+        const int q = (ps * UP + u) * QU;
+        const floatx16& a = acc[q / 4];
+        float4 v[2];
+#pragma unroll
+        for (int j = 0; j < QU; ++j) {
+          const int o = 4 * (q % 4 + j);
+          float4 b[KS];
+#pragma unroll
+          for (int k = 0; k < KS; ++k) {
+            b[k] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
+            if (k != ks) b[k] = s_red[(k * UP + u) * (UB / 16) + 64 * j];
+          }
+#pragma unroll
+          for (int d = KS / 2; d >= 1; d /= 2)                     // in pairs
+#pragma unroll
+            for (int k = 0; k < d; ++k) {
+              b[k].x += b[k + d].x; b[k].y += b[k + d].y; b[k].z += b[k + d].z; b[k].w += b[k + d].w;
+            }
+          v[j] = b[0];
+        }
+        const int cbase = n0 + cw * 32 + 8 * (q % 4), m = o_m[q / 4];
+        if (p.use_partial) {
+          if (m >= 0) {
+            float* dst = p.partial + (size_t)m * p.cout_pad + cbase + 4 * h;
+#pragma unroll
+            for (int j = 0; j < QU; ++j) *reinterpret_cast<float4*>(dst + 8 * j) = v[j];
+          }
+        } else if (QU == 2) {
+          store_half(p, m, cbase, h, v[0], v[1], res_raw[ps][u % UN]);
+        } else {
+          store_quad(p, m, cbase, h, v[0], res_raw[ps][u % UN]);
+        }
+      }
+  }
+  asm volatile("" ::"v"(touched));
+}
+// The instantiations of k_conv3x3_run: see kRunForms.
+static const void* run_kernel_of(int form) {
+  switch (form) {
+    case 0: return (const void*)k_conv3x3_run<1, 4, 1, 9, 8, 3, 16384, 3>;
+    case 1: return (const void*)k_conv3x3_run<2, 4, 1, 9, 6, 4, 24576, 3>;
+    case 2: return (const void*)k_conv3x3_run<2, 2, 2, 9, 8, 4, 24576, 3>;
+    case 3: return (const void*)k_conv3x3_run<3, 2, 2, 9, 4, 6, 26624, 3>;
+    case 4: return (const void*)k_conv3x3_run<4, 2, 2, 9, 5, 7, 36864, 2>;
+    case 5: return (const void*)k_conv3x3_run<5, 2, 2, 12, 5, 8, 40960, 2>;
+    case 6: return (const void*)k_conv3x3_run<1, 4, 1, 9, 8, 7, 44032, 1>;
+    default: return nullptr;
+  }
+}
+static_assert(kRunForms[0].passes == 3 && kRunForms[0].lds == 16384 && kRunForms[1].passes == 4 && kRunForms[1].lds == 24576 &&
+              kRunForms[2].passes == 4 && kRunForms[2].lds == 24576 && kRunForms[3].passes == 6 && kRunForms[3].lds == 26624 &&
+              kRunForms[4].passes == 7 && kRunForms[4].lds == 36864 && kRunForms[5].passes == 8 && kRunForms[5].lds == 40960 &&
+              kRunForms[6].passes == 7 && kRunForms[6].lds == 44032, "the host plans for the kernels' patch buffers");
+
 // The instantiations the host's rules ask for (see Builder::plan_kw).
 static const void* kw_kernel_of(const ConvParams& p) {
-  const int key = p.stride * 1000 + p.kw_groups * 100 + p.kw_cgroups * 10 + p.kw_splits;
-  switch (key) {
-    case 1141: return (const void*)k_conv3x3_kw<1, 1, 4, 4, 12>;
-    case 1121: return (const void*)k_conv3x3_kw<1, 1, 2, 2, 12>;
-    case 1122: return (const void*)k_conv3x3_kw<1, 1, 2, 4, 12>;
-    case 1112: return (const void*)k_conv3x3_kw<1, 1, 1, 2, 12>;
-    case 1113: return (const void*)k_conv3x3_kw<1, 1, 1, 3, 12>;
-    case 1114: return (const void*)k_conv3x3_kw<1, 1, 1, 4, 12>;
-    case 1116: return (const void*)k_conv3x3_kw<1, 1, 1, 6, 12>;
-    case 1241: return (const void*)k_conv3x3_kw<1, 2, 4, 4, 18>;
-    case 1222: return (const void*)k_conv3x3_kw<1, 2, 2, 4, 18>;
-    case 2141: return (const void*)k_conv3x3_kw<2, 1, 4, 4, 12>;
-    case 2121: return (const void*)k_conv3x3_kw<2, 1, 2, 2, 12>;
-    case 2122: return (const void*)k_conv3x3_kw<2, 1, 2, 4, 12>;
-    case 2114: return (const void*)k_conv3x3_kw<2, 1, 1, 4, 12>;
+  switch (p.kw_cgroups * 10 + p.kw_splits) {
+    case 41: return (const void*)k_conv3x3s2_kw<4, 4>;
+    case 21: return (const void*)k_conv3x3s2_kw<2, 2>;
+    case 22: return (const void*)k_conv3x3s2_kw<2, 4>;
+    case 14: return (const void*)k_conv3x3s2_kw<1, 4>;
     default: return nullptr;
   }
 }
@@ -1228,9 +1317,9 @@ KernelDesc describe(const ConvParams& p) {
       return KernelDesc{f, grid, dim3(256), 0};
     }
     case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
-    case CONV_DIRA: return KernelDesc{(const void*)k_conv3x3_dira, grid, dim3(256), 0};
     case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
     case CONV_KW:
+      if (p.stride == 1) return KernelDesc{run_kernel_of(p.run_form), grid, dim3(256), 0};
       return KernelDesc{kw_kernel_of(p), grid, dim3(64u * (unsigned)(p.kw_splits * p.kw_cgroups)), 0};
     default: return KernelDesc{nullptr, grid, dim3(256), 0};
   }

@@ -456,14 +456,48 @@ struct Builder {
     if (failed) std::rethrow_exception(failed);
   }
 
-  // CONV_KW with ns K splits, cw channel groups and pg pixel groups per workgroup.
-  static void plan_kw(ConvParams& c, int ns, int cw, int pg) {
+  // k_conv3x3s2_kw with ns K splits and cw channel groups per workgroup.
+  static void plan_kw(ConvParams& c, int ns, int cw) {
     c.variant = CONV_KW;
-    c.kw_splits = ns; c.kw_cgroups = cw; c.kw_groups = pg;
+    c.kw_splits = ns; c.kw_cgroups = cw;
     c.tiles_x = (c.wout + 7) / 8;
-    c.tiles_m = c.batch * ((c.hout + 4 * pg - 1) / (4 * pg)) * c.tiles_x;
+    c.tiles_m = c.batch * ((c.hout + 3) / 4) * c.tiles_x;
     c.tiles_n = c.cout / (32 * cw);
     c.chunks_per_split = (c.chunks_per_tap + ns - 1) / ns;
+  }
+
+  // k_conv3x3_run with a form of kRunForms.  False: the layer is out of the form's range.
+  static bool plan_run(ConvParams& c, int form) {
+    const RunForm& f = kRunForms[form];
+    const double in_bytes = 2.0 * c.batch * c.hin * c.win * c.cin_pitch, w_bytes = 2.0 * c.cout_pad * c.ktot;
+    if (c.chunks_per_tap % 2 != 0 || c.cout % f.ch != 0 || in_bytes >= 2147483648.0 || w_bytes >= 2147483648.0) return false;
+    c.variant = CONV_KW;
+    c.run_form = form;
+    c.run_in_bytes = (uint32_t)in_bytes; c.run_w_bytes = (uint32_t)w_bytes;
+    c.tiles_m = run_plan(c.hout, c.wout, c.batch, f.px, f.passes, f.lds, c.run);
+    c.tiles_n = c.cout / f.ch;
+    return c.tiles_m > 0 && (double)c.tiles_m * c.tiles_n * c.tiles_m * c.tiles_n < 2147483648.0;   // run_div31
+  }
+
+  // The form of k_conv3x3_run for a layer.  A tile's time is a fixed part and one per Cin chunk (kRunForms, fitted to
+  // twelve 854 x 480 frames, where every CU works on several tiles); the launch lasts as long as its busiest CU, which
+  // has ceil(tiles / 256) of them.  A CU with a single tile hides nothing of its latencies behind another one: 1 us
+  // more.  Over eleven sizes from one 192 x 110 to twelve 854 x 480 frames the form with the smallest sum is the fastest
+  // one or within 8 % of it (four 641 x 361 frames, 512 channels: 9.6 us, the other forms 11.7 to 19.7).
+  static void choose_run(ConvParams& c) {
+    constexpr int kRound = 256;
+    double best = 0;
+    int form = -1;
+    for (int i = 0; i < kRunFormCount; ++i) {
+      if (i == kRunFormAnyMap && form >= 0) break;
+      ConvParams t = c;
+      if (!plan_run(t, i)) continue;
+      const int rounds = (t.tiles_m * t.tiles_n + kRound - 1) / kRound;
+      const double cost = rounds * (kRunForms[i].cost + kRunForms[i].chunk_cost * c.chunks_per_tap) + (rounds == 1 ? 1.0 : 0.0);
+      if (form < 0 || cost < best) { best = cost; form = i; }
+    }
+    if (form < 0) throw std::logic_error("no tile form for a layer of this network");
+    plan_run(c, form);
   }
 
   // Picks the kernel variant, the tile grid and the split along K.
@@ -472,26 +506,22 @@ struct Builder {
     const bool fits32 = (double)c.batch * c.hin * c.win * c.cin_pitch < 2147483648.0;
     const bool s3x3 = c.ntaps == 9 && c.kw == 3 && c.pad == 1 && c.kc == 64 && c.cout % 128 == 0 && fits32;
     c.tiles_per_wg = 1;
-    // workgroups of a CONV_KW grid
-    auto wgs = [&](int cw, int pg) {
-      return c.batch * ((c.hout + 4 * pg - 1) / (4 * pg)) * ((c.wout + 7) / 8) * (c.cout / (32 * cw));
+    // workgroups of a k_conv3x3s2_kw grid
+    auto wgs = [&](int cw) {
+      return c.batch * ((c.hout + 3) / 4) * ((c.wout + 7) / 8) * (c.cout / (32 * cw));
     };
-    auto tiles = [&](int tw) {          // tiles of 8 rows x tw columns x 64 channels
-      return c.batch * ((c.hout + 7) / 8) * ((c.wout + tw - 1) / tw) * (c.cout / 64);
-    };
+    const int tiles = c.batch * ((c.hout + 7) / 8) * ((c.wout + 7) / 8) * (c.cout / 64);   // of 8 x 8 pixels x 64 channels
     // K splits: the count is part of the result (fp32 sums are not associative), so it depends on
     // the shape alone and not on the kernel: as many as bring 256 tiles of 8 x 8 pixels x 64 channels,
-    // in whole chunks (stride 1: at least two per split)
-    auto k_splits = [&](int n_tiles, int most) {
-      const int ns = n_tiles >= 192 ? 1 : std::max(1, std::min((256 + n_tiles - 1) / n_tiles, most));
+    // in whole chunks
+    auto k_splits = [&] {
+      const int ns = tiles >= 192 ? 1 : std::max(1, std::min((256 + tiles - 1) / tiles, c.chunks_per_tap));
       const int per = (c.chunks_per_tap + ns - 1) / ns;
       return (c.chunks_per_tap + per - 1) / per;
     };
-    // A round: one workgroup for every CU.  It measures the work of the busiest CU, for all forms alike, and not
-    // what is resident at once (k_conv3x3_dira: three workgroups per CU, k_conv3x3_kw: two of 64 pixels).
-    constexpr int kRound = 256;
+    constexpr int kRound = 256;         // one workgroup for every CU
     if (s3x3 && c.stride == 2) {
-      if (tiles(8) >= 768) {
+      if (tiles >= 768) {
         // from 1.5 workgroups of 8 x 8 x 128 per CU on: the patch, the heavy operand at stride 2, serves
         // 128 channels.  Two workgroups per CU are resident: beyond two rounds, walk in one.  (The
         // line also marks a change of the K order, and so of the results' last bits.)
@@ -504,42 +534,11 @@ struct Builder {
       } else {
         // one split: two channel groups per workgroup while that is one round, else four (the patch
         // serves twice the channels)
-        const int ns = k_splits(tiles(8), c.chunks_per_tap);
-        plan_kw(c, ns, ns == 1 ? (wgs(2, 1) <= kRound ? 2 : 4) : ns == 2 ? 2 : 1, 1);
+        const int ns = k_splits();
+        plan_kw(c, ns, ns == 1 ? (wgs(2) <= kRound ? 2 : 4) : ns == 2 ? 2 : 1);
       }
     } else if (s3x3 && c.stride == 1 && c.chunks_per_tap >= 2) {
-      const int wide = tiles(16);
-      const int ns = k_splits(wide < 192 ? tiles(8) : wide, c.chunks_per_tap / 2);
-      // Measured over maps of 5 x 9 to 60 x 107 pixels and 1 to 16 frames per launch: the smallest
-      // workgroup whose grid is one round wins (a round costs what its workgroup costs, and a
-      // workgroup's time is its weight stream: 128 channels x 32 pixels take 0.79 to 0.94 of the time of
-      // 128 x 64); beyond one round the 64-pixel tiles, which feed two MFMAs per weight fragment (256
-      // channels, four 1080p frames: 14.2 us, 128 x 32 pixels 16.7).  There the form taken is within 12 % of
-      // the best one, which from three frames on is often k_conv3x3_dira (13.3 us).
-      // Two wavefronts per workgroup only in one round: a second such workgroup on a CU shares
-      // the first one's SIMDs.
-      if (ns == 1) {
-        auto rounds = [](int n) { return (n + kRound - 1) / kRound; };
-        const int big = wgs(4, 2);
-        if (wgs(2, 1) <= kRound) plan_kw(c, 1, 2, 1);
-        else if (wgs(4, 1) <= kRound) plan_kw(c, 1, 4, 1);
-        else if (5 * rounds(wgs(4, 1)) < 7 * std::min(rounds(big), rounds(wide)) && c.chunks_per_tap >= 8)
-          plan_kw(c, 1, 4, 1);
-        else if (rounds(big) < rounds(wide) || (rounds(big) == rounds(wide) && (big < wide || rounds(big) == 1)))
-          plan_kw(c, 1, 4, 2);
-        else {
-          // 8 x 16-pixel tiles, where they waste no more pixels on the map's edges
-          c.variant = CONV_DIRA;
-          c.tiles_x = (c.wout + 15) / 16;
-          c.tiles_m = c.batch * ((c.hout + 7) / 8) * c.tiles_x;
-          c.tiles_n = c.cout / 64;
-        }
-      } else if (ns == 2) {
-        if (wgs(1, 1) <= kRound) plan_kw(c, 2, 1, 1);
-        else plan_kw(c, 2, 2, wgs(2, 1) <= kRound ? 1 : 2);
-      } else {
-        plan_kw(c, ns, 1, 1);
-      }
+      choose_run(c);
     } else if (c.cout <= 32 && c.kc <= 32 && c.chunks_per_tap == 1 && c.ntaps <= 9) {
       // two K splits, of at most five taps each, while tiles of 64 pixels would be fewer than 192
       c.variant = CONV_DIRECT;
@@ -580,6 +579,12 @@ struct Builder {
         }
         if (nb == 1 || bytes < 0.9 * best) { best = bytes; c.n_block = nb; }
       }
+    }
+    if (c.variant == CONV_KW && c.stride == 1) {
+      c.run_nb_shift = 0;
+      while ((1 << c.run_nb_shift) < c.n_block) ++c.run_nb_shift;
+      const uint64_t blk = (uint64_t)c.tiles_m * c.n_block;
+      c.run_by_blk = (uint32_t)((((uint64_t)1 << 31) + blk - 1) / blk);
     }
   }
 
@@ -857,7 +862,7 @@ struct Builder {
 
   void walk(int ph, int pw) {
     if (d.net == HS_NET_TINY4) walk_tiny(ph, pw); else walk_resnet(ph, pw);
-    // With several frames per launch the layers that k_conv3x3_kw computes prefetch the next layer's
+    // With several frames per launch the layers that k_conv3x3_run and k_conv3x3s2_kw compute prefetch the next layer's
     // weights (not its projection's): a pass then touches more than the last-level cache holds and finds
     // the weights in HBM (four frames 641 x 361: 363 -> 337 us, sixteen frames 416 x 240: 375 -> 358).  The 36 MB of a one-frame
     // application stay cached, and the prefetch would only cost (168 -> 172 us).

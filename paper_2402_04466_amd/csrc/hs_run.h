@@ -1,0 +1,119 @@
+// Geometry of k_conv3x3_run's tiles (see there): runs of consecutive pixels of strips of all images of a launch, and the
+// patch under a run.  One definition for the kernel and for the host, which plans with it.
+#pragma once
+
+#include <stdint.h>
+
+#include <hip/hip_runtime.h>
+
+namespace hs {
+
+constexpr int kRunPitch = 64 + 8;        // LDS halves per patch pixel: 64 channels, padded against bank conflicts
+
+// Of a layer with stride 1: maps of h x w pixels, `batch` images.
+struct RunGeometry {
+  int px;               // pixels per tile
+  int h, w, batch;
+  int strip_w;          // columns per strip
+  int rows;             // patch rows at most, the rows of zeros between images included
+  int step_q, step_r;   // quotient and remainder of the patch pixels per loading pass (32) by a patch row's length
+  // reciprocals: ceil(2^31 / d) for quotients of scalars, ceil(2^23 / d) for those of lanes
+  uint32_t by_strip_w, by_h, by_batch;
+  uint32_t by23_strip_w, by23_row, by23_h, by23_h1, by23_batch;
+};
+
+// LDS halves per patch row.  The pixel behind a row's last one lies in the bank group it would lie in without the two
+// border pixels between them (9 x 16 bytes per pixel, 16 bank groups).
+constexpr __host__ __device__ __forceinline__ int run_row_pitch(int strip_w) { return kRunPitch * strip_w + 256; }
+
+__host__ __device__ __forceinline__ uint32_t run_mul24(uint32_t a, uint32_t b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  // written as an instruction because the compiler turns __umul24 back into a 32-bit multiply, at a quarter of the
+  // rate, when it knows one factor to be small
+  uint32_t r;
+  asm("v_mul_u32_u24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+#else
+  return (a & 0xffffffu) * (b & 0xffffffu);
+#endif
+}
+__host__ __device__ __forceinline__ uint32_t run_div31(uint32_t n, uint32_t by) {   // n * d below 2^31
+#ifdef __HIP_DEVICE_COMPILE__
+  return __umulhi(n << 1, by);
+#else
+  return (uint32_t)(((uint64_t)(n << 1) * by) >> 32);
+#endif
+}
+__host__ __device__ __forceinline__ uint32_t run_div23(uint32_t n, uint32_t by) {   // n * d below 2^23
+  return run_mul24(n, by) >> 23;
+}
+
+// Where tile `tile` starts: row `y` of column `img` (image) of strip `strip`, `rem` pixels into the row.
+struct RunOrigin {
+  uint32_t rem, y, strip, img;
+};
+__host__ __device__ __forceinline__ RunOrigin run_origin(const RunGeometry& g, uint32_t tile) {
+  const uint32_t q = tile * (uint32_t)g.px, row = run_div31(q, g.by_strip_w), v = run_div31(row, g.by_h);
+  RunOrigin o;
+  o.rem = q - row * (uint32_t)g.strip_w;
+  o.y = row - v * (uint32_t)g.h;
+  o.strip = run_div31(v, g.by_batch);
+  o.img = v - o.strip * (uint32_t)g.batch;
+  return o;
+}
+
+// Patch pixel (row, col): true if it is a pixel of the map, at index m of the launch's pixels; else it is a zero (border,
+// or the row between two images, or beyond the last strip, which starts at column w or later).
+__host__ __device__ __forceinline__ bool run_patch_pixel(const RunGeometry& g, const RunOrigin& o, uint32_t row, uint32_t col,
+                                                         int& m) {
+  const uint32_t e = o.y + row;          // 0: a row of zeros, then an image's rows, then the next image
+  const uint32_t k = run_div23(e, g.by23_h1), f = e - k * (uint32_t)(g.h + 1);
+  const uint32_t ds = run_div23(o.img + k, g.by23_batch), img = o.img + k - ds * (uint32_t)g.batch;
+  const int x = (int)((o.strip + ds) * (uint32_t)g.strip_w + col) - 1;
+  m = ((int)(img * (uint32_t)g.h + f) - 1) * g.w + x;
+  return f != 0 && x >= 0 && x < g.w;
+}
+
+// Pixel i of the tile: its index m among the launch's pixels, -1 if there is none; (row, col): the patch pixel of its
+// first tap.
+__host__ __device__ __forceinline__ void run_pixel(const RunGeometry& g, const RunOrigin& o, uint32_t i, uint32_t& row,
+                                                   uint32_t& col, int& m) {
+  const uint32_t n = o.rem + i, d = run_div23(n, g.by23_strip_w);
+  const uint32_t k = run_div23(o.y + d, g.by23_h), y = o.y + d - k * (uint32_t)g.h;
+  const uint32_t ds = run_div23(o.img + k, g.by23_batch), img = o.img + k - ds * (uint32_t)g.batch;
+  col = n - d * (uint32_t)g.strip_w;
+  row = d + k;
+  const uint32_t x = (o.strip + ds) * (uint32_t)g.strip_w + col;
+  m = x < (uint32_t)g.w ? (int)((img * (uint32_t)g.h + y) * (uint32_t)g.w + x) : -1;
+}
+
+// Plans runs of px pixels with patches of at most 32 * passes pixels and lds bytes: the strips as wide as gives the fewest
+// tiles and then the smallest patch.  Returns the number of tiles, 0 if no strip width fits.
+inline int run_plan(int h, int w, int batch, int px, int passes, int lds, RunGeometry& g) {
+  const int64_t rows = (int64_t)batch * h;
+  if (h > 2500 || rows * (w + 64) >= (int64_t)1 << 23) return 0;
+  int best_tiles = 0, best_px = 0;
+  for (int sw = 1; sw <= w && sw <= 64; ++sw) {
+    const int64_t strips = (w + sw - 1) / sw, tiles = (rows * strips * sw + px - 1) / px;
+    // rows under a run that starts anywhere in its first one, images that begin inside it
+    const int d = (px % sw == 0 ? px - 1 : px + sw - 2) / sw, k = (d + h - 1) / h, n_rows = d + k + 3;
+    const int n_px = n_rows * (sw + 2);
+    if (n_px > 32 * passes || n_rows * run_row_pitch(sw) * 2 + 128 > lds) continue;
+    if (tiles * px * sw >= (int64_t)1 << 31 || (rows * strips + px) * h >= (int64_t)1 << 31) continue;
+    if (!best_tiles || tiles < best_tiles || (tiles == best_tiles && n_px < best_px)) {
+      best_tiles = (int)tiles; best_px = n_px;
+      g.strip_w = sw; g.rows = n_rows;
+    }
+  }
+  if (!best_tiles) return 0;
+  g.px = px; g.h = h; g.w = w; g.batch = batch;
+  const int row = g.strip_w + 2;
+  g.step_q = 32 / row; g.step_r = 32 % row;
+  auto by = [](int bits, int d) { return (uint32_t)((((uint64_t)1 << bits) + (uint64_t)d - 1) / (uint64_t)d); };
+  g.by_strip_w = by(31, g.strip_w); g.by_h = by(31, h); g.by_batch = by(31, batch);
+  g.by23_strip_w = by(23, g.strip_w); g.by23_row = by(23, row);
+  g.by23_h = by(23, h); g.by23_h1 = by(23, h + 1); g.by23_batch = by(23, batch);
+  return best_tiles;
+}
+
+}  // namespace hs

@@ -60,6 +60,16 @@ def test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch):
 
 
 @pytest.mark.parametrize("nw,nh,batch", [
+    (40, 520, 2),     # maps of 2 x 17 pixels and wider: strips of a few columns, tiles over several images
+    (300, 170, 16),   # tiles of 32 and 64 channels x 64 pixels, of 64 x 96
+    (430, 250, 16),   # tiles of 64 channels x 128 pixels
+    (860, 500, 11),   # tiles of 64 channels x 160 pixels, maps no multiple of any strip
+])
+def test_tiles_of_consecutive_pixels_match_the_oracle(hs, nw, nh, batch):
+    test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch)
+
+
+@pytest.mark.parametrize("nw,nh,batch", [
     (8, 8, 1),        # a 2 x 2 map: one pixel tile, mostly beyond the layer's end
     (33, 17, 3),      # ragged maps, images that end inside a pixel tile, two K splits
     (250, 190, 5),    # first layers without a split, the last ones at the line between one and two

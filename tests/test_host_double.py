@@ -31,3 +31,13 @@ def host_double(tmp_path_factory):
 def test_host_code(host_double, check):
     r = subprocess.run([host_double, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (r.returncode, r.stdout[-500:], r.stderr[-500:])
+
+
+def test_tiles_of_consecutive_pixels(tmp_path):
+    exe = str(tmp_path / "run_geometry")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
+    subprocess.run([os.path.join(rocm, "llvm", "bin", "clang++"), "-std=c++17", "-O2", "-w",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"), "-I", build.CSRC,
+                    os.path.join(HERE, "run_geometry_main.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-500:]
