@@ -51,6 +51,8 @@ KernelDesc describe(const ResizeParams& p);
 enum ConvVariant {
   CONV_DIRECT,    // <= 32 output channels, one chunk of 16 or 32 halves per tap, <= 9 taps: no LDS tiles,
                   // K splits inside the workgroup (k_conv_direct); wt_frag: [chunk][K-step][lane][8]
+  CONV_TINY_NET,  // the whole small network in one launch (k_tiny_net): hin, win the padded image, hout, wout the logits'
+                  // map, mid_h, mid_w the first layer's; wt_frag: the four layers' weights as for CONV_DIRECT
   CONV_BLOCK64,   // a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU between,
                   // shortcut from the input, ReLU) in one launch (k_block64_fused): wt_frag = first,
                   // wt2_frag = second convolution, res = in
@@ -74,6 +76,7 @@ struct ConvParams {
   const f16* wt_frag;   // weights in MFMA fragment order: [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
                         // r + 32 h holding k = 16 * step + 8 * h .. + 7 of channel 32 * group + r
   int hin, win, cin_pitch;
+  int mid_h, mid_w;     // CONV_TINY_NET
   int hout, wout, m;    // m = batch*hout*wout output pixels (images stacked along m)
   int batch, img_m;     // images per launch, pixels per image (hout*wout)
   int cout, cout_pad;   // cout_pad: multiple of the block's N tile

@@ -303,6 +303,28 @@ __device__ __forceinline__ void store_quad(const ConvParams& p, int m, int cbase
   if (m >= 0) *reinterpret_cast<half4*>(p.out + (size_t)m * p.out_pitch + cbase + 4 * h) = o;
 }
 
+// The small network's last layer: logits of pixel ml of an image, eight channels, planar per image, and stage 3's per-cell
+// outputs (see PostParams).  Lane half h holds four of a pixel's channels; every lane of the wavefront must call it.
+__device__ __forceinline__ void store_logits(const ConvParams& p, bool valid, int img, int ml, int h, const floatx16& acc) {
+  uint32_t set_channels = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float x = acc[j];
+    const bool set = x > p.theta;
+    set_channels |= set ? 1u << (4 * h + j) : 0u;
+    if (valid) {
+      const size_t at = ((size_t)img * 8 + 4 * h + j) * p.img_m + ml;
+      p.out_f32[at] = x;
+      p.heat[at] = heat_of(x);
+      p.mask[at] = set ? 1 : 0;
+    }
+  }
+  set_channels |= (uint32_t)__shfl_xor((int)set_channels, 32, 64);
+  const int m = img * p.img_m + ml;
+  if (valid && h == 0) p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
+  if (valid && m == p.m - 1 && h == 0) *p.t_end = wall_clock64();
+}
+
 // =============================================================================================
 // The small network's layers: at most 32 output channels, 16 or 32 input channels (or four
 // 4-channel pixels of the first layer) per tap, at most nine taps.  A layer is one launch and one
@@ -388,23 +410,120 @@ __global__ __launch_bounds__(256) void k_conv_direct(ConvParams p) {
     }
     return;
   }
-  // logits: eight channels, planar per image; lane half h holds four of a pixel's
-  uint32_t set_channels = 0;
+  store_logits(p, valid, img, ml, h, acc);
+}
+
+// =============================================================================================
+// The whole small network in one launch: a workgroup takes 8 x 8 logits through all four layers.  The layers' halos
+// (10 x 10, 12 x 12 and 25 x 25 pixels of the layers before) are computed again by the neighbouring workgroups -- up to
+// 2.4 times the products, of which there are few -- and the intermediate tensors stay in LDS: as launches of their own
+// the layers take 3.7 to 5.9 us each for one 128 x 128 input, almost all of it launch, memory round trip and set-up.
+// Eight wavefronts of 32 pixels x 32 channels (20 such groups in the first layer, then 5, 4 and 2).  The first layer's
+// pixels come straight from the 4-channel image (see k_conv_direct), all layers' weights straight from memory, asked for
+// before the first product by the wavefronts that need them.  LDS pixels are padded to 48 and 80 bytes against bank
+// conflicts.  Sums as in k_conv_direct with two K splits (first layer: one).
+// p.wt_frag: the four layers' weights in k_conv_direct's order, one after the other.
+// =============================================================================================
+__global__ __launch_bounds__(512, 2) void k_tiny_net(ConvParams p) {
+  constexpr int N1 = 25, N2 = 12, N3 = 10, N4 = 8;                 // pixels per side of the layers' tiles
+  constexpr int P1 = 24, P2 = 40;                                  // halves per LDS pixel of 16 and 32 channels
+  constexpr int W2 = 3 * 1024, W3 = W2 + 9 * 1024, W4 = W3 + 18 * 1024, W_BYTES = W4 + 18 * 1024;
+  __shared__ __align__(16) f16 s1[N1 * N1 * P1], s2[N2 * N2 * P2], s3[N3 * N3 * P2];
+
+  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int x0 = N4 * (int)blockIdx.x, y0 = N4 * (int)blockIdx.y, img = (int)blockIdx.z;
+  const BufferRsrc in_buf = buffer_of(p.in, (uint32_t)(p.batch * p.hin * p.win * 8)), w_buf = buffer_of(p.wt_frag, W_BYTES);
+  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // ---- operands: first layer's pixels (groups wave, wave + 8, wave + 16), then the weights
+  u32x4 xb[3][3], w1[3], w2[9], w34[18];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float x = acc[j];
-    const bool set = x > p.theta;
-    set_channels |= set ? 1u << (4 * h + j) : 0u;
-    if (valid) {
-      const size_t at = ((size_t)img * 8 + 4 * h + j) * p.img_m + ml;
-      p.out_f32[at] = x;
-      p.heat[at] = heat_of(x);
-      p.mask[at] = set ? 1 : 0;
+  for (int i = 0; i < 3; ++i) {
+    const int q = 32 * (wave + 8 * i) + r, ry = q / N1, rx = q - ry * N1, y = 2 * y0 - 5 + ry, x = 2 * x0 - 5 + rx;
+    const bool in = q < N1 * N1 && y >= 0 && y < p.mid_h && x >= 0 && x < p.mid_w;
+    const int off = in ? ((img * p.hin + 2 * y) * p.win + 2 * x + 2 * h) * 8 : kOutside;
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky) xb[i][ky] = load16(in_buf, off, ky * p.win * 8);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) w1[q] = load16(w_buf, lane * 16, q * 1024);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) w2[q] = load16(w_buf, lane * 16, W2 + q * 1024);
+  // wavefronts 0-3 compute the third layer, 4 and 5 the last one
+#pragma unroll
+  for (int q = 0; q < 18; ++q) w34[q] = load16(w_buf, lane * 16, (wave < 4 ? W3 : W4) + q * 1024);
+
+  // ---- first layer: 3 -> 16 channels, stride 2.  Zero outside the layer's map, the next layer's padding
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (wave + 8 * i >= (N1 * N1 + 31) / 32) break;
+    floatx16 acc = zero16;
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, w1[ky]), __builtin_bit_cast(half8, xb[i][ky]),
+                                                  acc, 0, 0, 0);
+    const int q = 32 * (wave + 8 * i) + r;
+    if (q < N1 * N1) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {                                // (out of the map the pixels were zeros, and so is acc)
+        half4 o = {(f16)acc[4 * j], (f16)acc[4 * j + 1], (f16)acc[4 * j + 2], (f16)acc[4 * j + 3]};
+        *reinterpret_cast<half4*>(&s1[q * P1 + 8 * j + 4 * h]) = __builtin_elementwise_max(o, half4{});
+      }
     }
   }
-  set_channels |= (uint32_t)__shfl_xor((int)set_channels, 32, 64);
-  if (valid && h == 0) p.kmap[m] = set_channels ? (uint8_t)__builtin_ctz(set_channels) : 0xff;
-  if (m == p.m - 1 && h == 0) *p.t_end = wall_clock64();
+  __syncthreads();
+  // One group of a further layer: pixel `at` (LDS halves of its first tap, channel 8 * h) of a source with `row` pixels per
+  // row and PITCH_ halves per pixel, KS_ K-steps per tap; taps 0-4 and 5-8 are summed apart
+#define HS_LAYER(ACC_, SRC_, AT_, ROW_, PITCH_, KS_, W_)                                       \
+  floatx16 ACC_ = zero16;                                                                      \
+  {                                                                                            \
+    floatx16 acc_b = zero16;                                                                   \
+    _Pragma("unroll") for (int t = 0; t < 9; ++t)                                              \
+      _Pragma("unroll") for (int k = 0; k < KS_; ++k) {                                        \
+        const half8 b_ = *reinterpret_cast<const half8*>(&SRC_[(AT_) + ((t / 3) * ROW_ + t % 3) * PITCH_ + 16 * k]); \
+        floatx16& a_ = t < 5 ? ACC_ : acc_b;                                                   \
+        a_ = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, W_[t * KS_ + k]), b_, a_, 0, 0, 0); \
+      }                                                                                        \
+    _Pragma("unroll") for (int i = 0; i < 16; ++i) ACC_[i] = (0.0f + ACC_[i]) + acc_b[i];      \
+  }
+  // ---- second layer: 16 -> 32 channels, stride 2
+  if (wave < (N2 * N2 + 31) / 32) {
+    const int q = 32 * wave + r, qc = min(q, N2 * N2 - 1), ry = qc / N2, rx = qc - ry * N2;
+    HS_LAYER(acc, s1, (2 * ry * N1 + 2 * rx) * P1 + 8 * h, N1, P1, 1, w2)
+    const int y = y0 - 2 + ry, x = x0 - 2 + rx;
+    const bool in = y >= 0 && y < p.hout && x >= 0 && x < p.wout;
+    if (q < N2 * N2) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        half4 o = {(f16)acc[4 * j], (f16)acc[4 * j + 1], (f16)acc[4 * j + 2], (f16)acc[4 * j + 3]};
+        *reinterpret_cast<half4*>(&s2[q * P2 + 8 * j + 4 * h]) = in ? __builtin_elementwise_max(o, half4{}) : half4{};
+      }
+    }
+  }
+  __syncthreads();
+  // ---- third layer: 32 -> 32 channels
+  if (wave < 4) {
+    const int q = 32 * wave + r, qc = min(q, N3 * N3 - 1), ry = qc / N3, rx = qc - ry * N3;
+    HS_LAYER(acc, s2, (ry * N2 + rx) * P2 + 8 * h, N2, P2, 2, w34)
+    const int y = y0 - 1 + ry, x = x0 - 1 + rx;
+    const bool in = y >= 0 && y < p.hout && x >= 0 && x < p.wout;
+    if (q < N3 * N3) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        half4 o = {(f16)acc[4 * j], (f16)acc[4 * j + 1], (f16)acc[4 * j + 2], (f16)acc[4 * j + 3]};
+        *reinterpret_cast<half4*>(&s3[q * P2 + 8 * j + 4 * h]) = in ? __builtin_elementwise_max(o, half4{}) : half4{};
+      }
+    }
+  }
+  __syncthreads();
+  // ---- last layer: 32 -> 8 channels, the logits, and stage 3's per-cell outputs
+  if (wave == 4 || wave == 5) {
+    const int q = 32 * (wave - 4) + r, ry = q / N4, rx = q % N4, y = y0 + ry, x = x0 + rx;
+    HS_LAYER(acc, s3, (ry * N3 + rx) * P2 + 8 * h, N3, P2, 2, w34)
+    store_logits(p, y < p.hout && x < p.wout, img, y * p.wout + x, h, acc);
+  }
+#undef HS_LAYER
 }
 
 // =============================================================================================
@@ -1316,6 +1435,9 @@ KernelDesc describe(const ConvParams& p) {
                                  : (p.kw_splits == 2 ? (const void*)k_conv_direct<2, 2> : (const void*)k_conv_direct<2, 1>);
       return KernelDesc{f, grid, dim3(256), 0};
     }
+    case CONV_TINY_NET:
+      return KernelDesc{(const void*)k_tiny_net, dim3((unsigned)(p.wout + 7) / 8, (unsigned)(p.hout + 7) / 8, (unsigned)p.batch),
+                        dim3(512), 0};
     case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
     case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
     case CONV_KW:

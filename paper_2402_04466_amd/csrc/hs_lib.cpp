@@ -116,6 +116,7 @@ constexpr int kMaxLanes = 2;
 struct Slot {
   std::vector<Op> pre;     // stage 1: one launch, blockIdx.y = stream of the batch
   std::vector<Op> infer;   // stage 2: the network over the whole batch
+  std::vector<Op> infer_layers;   // the small network layer by layer, while kernels are being timed
   std::vector<Op> infer_static;   // the same with the gate scratch in the library's fixed
                                   // device array (empty when the scratch needed exceeds it)
   std::vector<Op> post;    // stage 3: the channel maxima
@@ -377,6 +378,7 @@ struct Builder {
   size_t partial_floats = 0;
   float* d_partial = nullptr;     // gate scratch of this lane inside the workspace
   std::vector<Op> ops;            // stage-2 ops; slot-dependent pointers are patched per slot
+  std::vector<Op> layer_ops;      // the small network: its layers as launches of their own
   int first_conv_op = -1;         // op whose conv.in is the slot's padded net input
   int logits_op = -1;             // op that writes the slot's logits
   int lstm_conv_op = -1;          // gate convolution of the recurrent cell (-1: none)
@@ -745,6 +747,29 @@ struct Builder {
     conv_layer(t3, at, 8, 3, 1, 1, false, nullptr, &lg, true, false);    at += 8 * 32 * 9;
     blob_off = at;
     map_h = lg.h; map_w = lg.w; stateful = false;
+    // One launch for all layers, but the layers one after the other while kernels are being timed, and where there are
+    // many tiles: the halos that k_tiny_net computes again then cost more than the launches and tensors it saves
+    // (network's launches in us, layers -> one: one 128 x 128 frame 16.8 -> 6.8, eight 320 x 320 28.2 -> 23.5, sixteen, 1600
+    // tiles, 43.7 -> 39.1, sixteen 640 x 640, 6400 tiles, 113 -> 131).
+    if (d.batch * ((map_h + 7) / 8) * ((map_w + 7) / 8) > 2048) return;
+    layer_ops = ops;
+    Op net;
+    net.fam = F_CONV;
+    net.conv = layer_ops[0].conv;
+    const ConvParams& last = layer_ops[3].conv;
+    net.conv.variant = CONV_TINY_NET;
+    net.conv.mid_h = h1; net.conv.mid_w = w1;
+    net.conv.hout = last.hout; net.conv.wout = last.wout;
+    net.conv.m = last.m; net.conv.img_m = last.img_m;
+    for (const Op& op : layer_ops) { net.flops += op.flops; net.wt_halves += op.wt_halves; }
+    // k_tiny_net takes the four layers' weights as one run
+    size_t end = 0;
+    for (const Op& op : layer_ops) {
+      if (d_w && op.conv.wt_frag != d_w + end) throw std::logic_error("the small network's weights are not one run");
+      end += op.wt_halves;
+    }
+    ops = {net};
+    first_conv_op = logits_op = 0;
   }
 
   void walk_resnet(int ph, int pw) {
@@ -1101,18 +1126,22 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     }
     s.lane = i % lanes;
     s.infer = lane_b[s.lane]->ops;
+    s.infer_layers = lane_b[s.lane]->layer_ops;
     if (b.stateful) s.wait_idx = b.lstm_conv_op;
     if (s.infer[b.first_conv_op].fam == F_STEM) s.infer[b.first_conv_op].stem.in = s.d_netin;
     else s.infer[b.first_conv_op].conv.in = s.d_netin;
+    auto bind_logits = [&](auto& w, float*& logits) {
+      logits = s.d_logits;
+      w.theta = (float)theta_d;
+      w.heat = s.d_heat; w.mask = s.d_mask; w.kmap = sb[i].kmap;
+      w.t_end = sb[i].t_stage2;
+    };
     Op& lo = s.infer[b.logits_op];
-    if (lo.fam == F_CONV) {
-      lo.conv.out_f32 = s.d_logits; lo.conv.theta = (float)theta_d;
-      lo.conv.heat = s.d_heat; lo.conv.mask = s.d_mask; lo.conv.kmap = sb[i].kmap;
-      lo.conv.t_end = sb[i].t_stage2;
-    } else {
-      lo.lstm.logits = s.d_logits; lo.lstm.theta = (float)theta_d;
-      lo.lstm.heat = s.d_heat; lo.lstm.mask = s.d_mask; lo.lstm.kmap = sb[i].kmap;
-      lo.lstm.t_end = sb[i].t_stage2;
+    if (lo.fam == F_CONV) bind_logits(lo.conv, lo.conv.out_f32);
+    else bind_logits(lo.lstm, lo.lstm.logits);
+    if (!s.infer_layers.empty()) {
+      s.infer_layers.front().conv.in = s.d_netin;
+      bind_logits(s.infer_layers.back().conv, s.infer_layers.back().conv.out_f32);
     }
     app->partial_bytes = b.partial_floats * sizeof(float);
     if (app->partial_bytes <= app->ctx->static_scratch_bytes && app->ctx->d_static_scratch) {
@@ -1778,7 +1807,8 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
                                 hipStream_t* stream_out, hipEvent_t frames_ready,
                                 bool static_scratch) {
   HS_HIP(hipSetDevice(app->ctx->device));
-  std::vector<Op>& infer = static_scratch ? s->infer_static : s->infer;
+  std::vector<Op>& infer = static_scratch ? s->infer_static
+                           : app->timing && !s->infer_layers.empty() ? s->infer_layers : s->infer;
   const int B = app->batch;
   const size_t n_map = (size_t)app->map_w * app->map_h;
   const size_t netin_img = (size_t)app->netin_h * app->netin_w * 4;

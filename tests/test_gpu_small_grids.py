@@ -94,3 +94,55 @@ def test_small_network_layers_match_the_oracle(hs, nw, nh, batch):
     finally:
         s.close()
         hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("nw,nh,batch", [
+    (8, 8, 1),        # one tile, mostly beyond the map
+    (33, 17, 3),      # 9 x 5 logits: tiles of one column and of five rows
+    (130, 122, 2),    # several ragged tiles
+])
+def test_small_network_in_one_launch_equals_its_layers(hs, nw, nh, batch):
+    from paper_2402_04466_amd.harness import AppStream
+    fw, fh = 64, 48
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=fw, frame_h=fh, net_w=nw, net_h=nh,
+                  blob=si.he_normal_blob(si.TINY4_LAYERS, 10), palette=si.DEFAULT_PALETTE, queue_depth=2, batch=batch)
+    try:
+        print(f"[small-network] one launch against layers {nw}x{nh} batch {batch}", flush=True)
+        host = [si.uniform_frames(1, fh, fw, 40 + j)[0] for j in range(batch)]
+        d_in = [s.upload_frame(f) for f in host]
+        got = []
+        for timed in (False, True):          # layer by layer while kernels are being timed
+            hs.hs_set_kernel_timing(s.app, timed)
+            d_out = [s.new_output() for _ in host]
+            assert s.submit_batch(d_in, d_out, 0) == hs.HS_OK
+            got.append([s.fetch(r, o) for r, o in zip(s.wait_batch(), d_out)])
+        for a, b in zip(*got):
+            for key in ("logits", "heat", "mask", "overlay"):
+                assert np.array_equal(a[key], b[key]), key
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
+
+
+def test_small_network_of_many_tiles_matches_the_oracle(hs):
+    from paper_2402_04466_amd.harness import AppStream
+    nw, nh, batch, fw, fh = 522, 402, 16, 64, 48       # 131 x 101 logits: 17 x 13 x 16 tiles
+    blob = si.he_normal_blob(si.TINY4_LAYERS, 11)
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=fw, frame_h=fh, net_w=nw, net_h=nh, blob=blob,
+                  palette=si.DEFAULT_PALETTE, queue_depth=2, batch=batch)
+    try:
+        print(f"[small-network] {nw}x{nh} batch {batch}", flush=True)
+        host = [si.uniform_frames(1, fh, fw, 60 + j)[0] for j in range(batch)]
+        d_in, d_out = [s.upload_frame(f) for f in host], [s.new_output() for _ in host]
+        assert s.submit_batch(d_in, d_out, 0) == hs.HS_OK
+        rs = s.wait_batch()
+        for j in (0, batch - 1):
+            o32, o16 = make_oracles("tiny4", blob, nw, nh, True, si.DEFAULT_PALETTE)
+            check_frame(s.fetch(rs[j], d_out[j]), host[j], o32.process(host[j]), o16.process(host[j]),
+                        threshold=0.5, alpha=0.5, palette=si.DEFAULT_PALETTE, fp32_input=False,
+                        tag=f"small-network/{nw}x{nh}/stream{j}")
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
