@@ -56,14 +56,14 @@ enum ConvVariant {
   CONV_BLOCK64,   // a whole 64 -> 64 -> 64 channel block (two 3x3/1 convolutions, ReLU between,
                   // shortcut from the input, ReLU) in one launch (k_block64_fused): wt_frag = first,
                   // wt2_frag = second convolution, res = in
-  CONV_S2_DIRA,   // 3x3/2 layers (+ fused 1x1/2 projection) on large grids: tile 8 x 8 x 128, weights
+  CONV_S2_DIRA,   // 3x3/2 layers (+ fused 1x1/2 projection) of one Cin chunk on large grids: tile 8 x 8 x 128, weights
                   // from wt_frag / wt2_frag, tile walking, no residual (k_conv3x3s2_dira)
-  CONV_KW         // 3x3 layers with the K splits inside the workgroup, weights from wt_frag / wt2_frag.  Stride 1, an
-                  // even number of Cin chunks: tiles of consecutive pixels (k_conv3x3_run).  Stride 2 (+ fused
-                  // projection) on small and middle grids: tiles of 4 x 8 pixels (k_conv3x3s2_kw)
+  CONV_KW         // 3x3 layers with the K splits inside the workgroup, tiles of consecutive pixels, weights from wt_frag /
+                  // wt2_frag.  Stride 1, an even number of Cin chunks: k_conv3x3_run.  Stride 2 (+ fused projection):
+                  // k_conv3x3s2_run
 };
 // The forms of k_conv3x3_run: channels and pixels of a tile, loading passes over a patch (32 pixels each), bytes of a patch
-// buffer; cost of a tile in us where its CU works on several, fixed and per Cin chunk (see Builder::choose_run).
+// buffer; cost of a tile in us where its CU works on several, fixed and per Cin chunk (see Builder::choose_form).
 struct RunForm { int ch, px, passes, lds; double cost, chunk_cost; };
 constexpr RunForm kRunForms[] = {
     {32, 32, 3, 16384, 0.35, 0.47}, {32, 64, 4, 24576, 0.55, 0.57},  {64, 64, 4, 24576, 0.75, 1.03},
@@ -71,6 +71,14 @@ constexpr RunForm kRunForms[] = {
     {32, 32, 7, 44032, 0.35, 0.47},   // patches of maps a few pixels wide or high, which hold mostly border
 };
 constexpr int kRunFormCount = 7, kRunFormAnyMap = 6;
+// And of k_conv3x3s2_run: patch pixels per loading pass, 16-byte LDS units per patch pixel besides.
+struct Run2Form { int ch, px, passes, lds, step, units; double cost, chunk_cost; };
+constexpr Run2Form kRun2Forms[] = {
+    {32, 32, 6, 28672, 32, 9, 1.2, 0.53}, {64, 32, 3, 16384, 64, 5, 0.4, 1.3}, {64, 64, 5, 28672, 64, 5, 1.4, 1.62},
+    {64, 96, 8, 40960, 64, 5, 2.4, 2.0},
+    {32, 32, 8, 40960, 32, 9, 1.2, 0.53},   // maps a few pixels wide or high
+};
+constexpr int kRun2FormCount = 5, kRun2FormAnyMap = 4;
 struct ConvParams {
   const f16* in;
   const f16* wt_frag;   // weights in MFMA fragment order: [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
@@ -82,8 +90,7 @@ struct ConvParams {
   int cout, cout_pad;   // cout_pad: multiple of the block's N tile
   int kc;               // 16, 32 or 64
   int variant;          // ConvVariant
-  int kw_splits, kw_cgroups;   // k_conv3x3s2_kw, CONV_DIRECT: K splits; groups of 32 channels (their product:
-                        // wavefronts per workgroup)
+  int kw_splits;        // CONV_DIRECT: K splits
   int tiles_x;          // spatial variants: tiles per output row
   int ntaps, kw, chunks_per_tap, nchunks, ktot;
   int stride, pad;
@@ -109,7 +116,7 @@ struct ConvParams {
   // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
   const f16* wt2_frag;
   f16* out2; int out2_pitch;
-  // k_conv3x3_run: form (kRunForms), tiles; bytes of the input and of the weights; log2 of n_block, reciprocal of
+  // CONV_KW: form (kRunForms, kRun2Forms), tiles; bytes of the input and of the weights; log2 of n_block, reciprocal of
   // tiles_m * n_block (run_div31)
   int run_form;
   RunGeometry run;

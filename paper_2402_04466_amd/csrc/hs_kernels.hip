@@ -259,10 +259,10 @@ __device__ __forceinline__ void res_octets_to_quads(const u32x4 (&o)[2], half4 (
 
 // The same for one half of them, 16 channels from cbase on: v0 = channels cbase + 4h .. + 3, v1 = 8 further;
 // res: the lane's 16 bytes of the residual (channels cbase + 8h .. + 7).  m < 0: nothing is stored.
-__device__ __forceinline__ void store_half(const ConvParams& p, int m, int cbase, int h, const float4& v0,
-                                           const float4& v1, const u32x4& res) {
+__device__ __forceinline__ void store_half(f16* out, int pitch, bool relu, int m, int cbase, int h, const float4& v0,
+                                           const float4& v1, const u32x4& res, bool has_res) {
   float v[2][4] = {{v0.x, v0.y, v0.z, v0.w}, {v1.x, v1.y, v1.z, v1.w}};
-  if (p.res) {
+  if (has_res) {
     const auto s0 = __builtin_amdgcn_permlane32_swap(res[0], res[2], false, false);
     const auto s1 = __builtin_amdgcn_permlane32_swap(res[1], res[3], false, false);
     const half4 r0 = __builtin_bit_cast(half4, make_uint2(s0[0], s1[0]));
@@ -279,14 +279,14 @@ __device__ __forceinline__ void store_half(const ConvParams& p, int m, int cbase
     half4 o;
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[j] = (f16)v[i][j];
-    if (p.relu) o = __builtin_elementwise_max(o, half4{});
+    if (relu) o = __builtin_elementwise_max(o, half4{});
     w[i] = __builtin_bit_cast(uint2, o);
   }
   const auto s0 = __builtin_amdgcn_permlane32_swap(w[0].x, w[1].x, false, false);
   const auto s1 = __builtin_amdgcn_permlane32_swap(w[0].y, w[1].y, false, false);
   if (m >= 0) {
     const u32x4 o = {s0[0], s1[0], s0[1], s1[1]};
-    *reinterpret_cast<u32x4*>(p.out + (size_t)m * p.out_pitch + cbase + 8 * h) = o;
+    *reinterpret_cast<u32x4*>(out + (size_t)m * pitch + cbase + 8 * h) = o;
   }
 }
 // And for one quad, channels cbase + 4h .. + 3; res: the lane's 8 bytes of the residual.
@@ -714,8 +714,8 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
 }
 
 // =============================================================================================
-// 3x3 stride-2 pad-1 layers (with the block's 1x1 stride-2 projection riding along) on grids of
-// at least 1.5 workgroups per CU.  Output tile 8 x 8
+// 3x3 stride-2 pad-1 layers (with the block's 1x1 stride-2 projection riding along) of one Cin chunk
+// on grids beyond two rounds of workgroups (the others: k_conv3x3s2_run).  Output tile 8 x 8
 // pixels x 128 channels; wavefront w = all 64 pixels (two groups of four rows), channels
 // 32*w .. +31: a weight fragment is fetched by one wavefront only and serves two MFMAs, and
 // the patch -- the heavy operand of a stride-2 tile -- serves 128 channels.
@@ -736,9 +736,7 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
 //   - a workgroup walks tiles_per_wg consecutive spatial tiles in one pipeline (the next tile's
 //     first patch and weights are fetched during the last taps of the current tile), so the
 //     short K loops of the 64-channel layer do not pay a cold start per tile.
-// Per output the K order is chunk, half chunk, tap, K-step: within a chunk the two halves are
-// summed one after the other, not interleaved tap by tap as in k_conv3x3s2_kw; results
-// agree with that kernel to fp32 rounding, not bit for bit.
+// Per output the K order is chunk, half chunk, tap, K-step.
 // =============================================================================================
 __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
   constexpr int TH = 8, TW = 8, IPW = 2 * TW + 1, NPIX = IPW * IPW;   // 17 x 17 input pixels
@@ -940,26 +938,6 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
 #undef HS_TILE_SETUP
 }
 
-// =============================================================================================
-// 3x3 stride-2 pad-1 layers with the block's 1x1 stride-2 projection riding along
-// on SMALL grids: one or a few frames per launch.  There a layer is a launch, one memory round trip
-// and a K loop whose operands have to get into the few CUs at work; what bounds it is those
-// latencies and the 64 bytes per clock a CU takes in, not the matrix rate.  So the K splits live
-// in ONE workgroup (as workgroups of their own they need a second launch to add the partial
-// sums), the tile is small so that the grid covers the device, and every wavefront streams its
-// operands deep ahead without a barrier per tap:
-//   - wavefront (split, cg) computes 4 x 8 pixels x 32 channels over the Cin
-//     chunks of its split; its weight fragments come straight from memory (fragment order,
-//     p.wt_frag) through a ring of 12 register sets (18 spill: 10 to 30 % slower), so up to 12 KB per wavefront
-//     are in flight;
-//   - the CW wavefronts of a split (channel groups) share the input patch of the chunk in LDS;
-//     with CW == 1 the patch is the wavefront's own and the K loop has no barrier at all;
-//   - the partial tiles of the NS splits are added through LDS in split order.
-// Per output: chunk, tap, K-step within a split, then the splits in order.
-// The patch is stored as four parity planes (pixel (py, px) in plane (py & 1, px & 1) at
-// (py / 2, px / 2)), so that a tap's lanes read neighbouring pixels, and the 1x1 stride-2 projection,
-// which reads exactly the centre tap's pixels, is a tenth tap with its own accumulators.
-// =============================================================================================
 // Touches this workgroup's share of the next layer's weights (one 4-byte load per 128-byte line),
 // so that they are on their way into the last-level cache when that layer starts: streamed from
 // HBM by the layer itself, every ring of fragments in flight costs a full memory latency.  Called
@@ -971,199 +949,12 @@ __device__ __forceinline__ uint32_t prefetch_next(const ConvParams& p, int block
   return x;
 }
 
-template <int CW, int NW>
-__global__ __launch_bounds__(64 * NW, NW / CW > 2 ? 1 : 2) void k_conv3x3s2_kw(ConvParams p) {
-  constexpr int NS = NW / CW, FR = 12;
-  constexpr int TH = 4, TW = 8;
-  constexpr int IPH = 2 * TH + 1, IPW = 2 * TW + 1, NPIX = IPH * IPW;
-  constexpr int PLH = TH + 1, PLW = TW + 1;
-  constexpr int PITCH = 64 + 8;
-  constexpr int RP = (PLW * PITCH * 2 + ((128 - (PLW * PITCH * 2) % 256 + 256) % 256)) / 2;
-  static_assert((RP * 2) % 256 == 128, "plane row pitch must be 128 mod 256 bytes");
-  constexpr int PATCH = 4 * PLH * RP;                       // halves per split
-  constexpr int PV = NPIX * 8, PL = (PV + 64 * CW - 1) / (64 * CW);   // 16-byte vectors, per lane
-  constexpr int RED = 8 * 34;                               // float4s per group of partial sums
-  // accumulators: the layer's, the projection's
-  constexpr int BYTES = NS * PATCH * 2 > NW * 2 * RED * 16 ? NS * PATCH * 2 : NW * 2 * RED * 16;
-  static_assert(36 % FR == 0, "the fragment ring must divide a chunk's 36 K-steps");
-  __shared__ __align__(16) unsigned char s_raw[BYTES];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  const int split = wave / CW, cg = wave % CW;
-  const int tile = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (tile >= p.tiles_m * p.tiles_n) return;
-  const int blk = p.tiles_m * p.n_block, in_blk = tile % blk;     // tile order: see above
-  const int tm = in_blk / p.n_block;
-  const int n_tile = ((tile / blk) * p.n_block + in_blk % p.n_block) * (32 * CW);
-  const int tiles_img = p.tiles_m / p.batch;
-  const int img = tm / tiles_img, ts = tm - img * tiles_img, ty = ts / p.tiles_x;
-  const int y0 = ty * TH, x0 = (ts - ty * p.tiles_x) * TW;
-  const int n0 = n_tile + 32 * cg;                                // this wavefront's channels
-  const int cc_begin = split * p.chunks_per_split;
-  const int cc_end = min(p.chunks_per_tap, cc_begin + p.chunks_per_split);
-  const bool has_proj = p.wt2_frag != nullptr;
-
-  // ---- patch loader: the CW wavefronts of a split fetch its patch together
-  f16* const s_patch = reinterpret_cast<f16*>(s_raw) + split * PATCH;
-  int l_plds[PL], l_poff[PL];
-#pragma unroll
-  for (int i = 0; i < PL; ++i) {
-    const int vec = cg * 64 + lane + 64 * CW * i, pix = min(vec >> 3, NPIX - 1), v = vec & 7;
-    const int py = pix / IPW, px = pix - py * IPW;
-    l_plds[i] = vec >= PV ? -1
-                         : (((py & 1) * 2 + (px & 1)) * PLH + (py >> 1)) * RP + (px >> 1) * PITCH + v * 8;
-    const int iy = 2 * y0 + py - 1, ix = 2 * x0 + px - 1;
-    const bool inb = vec < PV && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
-    l_poff[i] = inb ? ((img * p.hin + iy) * p.win + ix) * p.cin_pitch + v * 8 : -1;
-  }
-  u32x4 st_p[PL];
-#define HS_LOAD_PATCH(CC_)                                                                     \
-  _Pragma("unroll") for (int i = 0; i < PL; ++i)                                               \
-    st_p[i] = *reinterpret_cast<const u32x4*>(p.in + (l_poff[i] >= 0 ? l_poff[i] + (CC_) * 64 : 0));
-#define HS_SYNC_PATCH()                                                                        \
-  if (CW > 1) __syncthreads();                                                                 \
-  else {                                                                                       \
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                     \
-    __builtin_amdgcn_wave_barrier();                                                           \
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                     \
-  }
-#define HS_HAND_PATCH()                                                                        \
-  {                                                                                            \
-    const u32x4 zero_ = {0u, 0u, 0u, 0u};                                                      \
-    _Pragma("unroll") for (int i = 0; i < PL; ++i)                                             \
-      if (l_plds[i] >= 0)                                                                      \
-        *reinterpret_cast<u32x4*>(&s_patch[l_plds[i]]) = l_poff[i] >= 0 ? st_p[i] : zero_;     \
-    HS_SYNC_PATCH()                                                                            \
-  }
-
-  // ---- weight fragments of this wavefront: 36 blocks of 64 lanes x 16 bytes per chunk (tap-major,
-  // four K-steps per tap), four per chunk for the projection
-  const u32x4* wf = reinterpret_cast<const u32x4*>(p.wt_frag) +
-                    ((size_t)(n0 / 32) * p.chunks_per_tap + cc_begin) * (36 * 64) + lane;
-  const u32x4* wp = has_proj ? reinterpret_cast<const u32x4*>(p.wt2_frag) +
-                                   ((size_t)(n0 / 32) * p.chunks_per_tap + cc_begin) * (4 * 64) + lane
-                             : wf;
-  u32x4 fa[FR], fp2[4];
-
-  const int fp_off = (r >> 3) * RP + (r & 7) * PITCH + h * 8;
-  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  floatx16 acc = zero16, acc2 = zero16;
-
-  // K-step Q_ (literal) of a chunk: tap Q_ / 4 (9: the projection, on the centre tap's pixels), K-step
-  // Q_ % 4.  Pixel fragments are read BD steps ahead through a ring.  LAST_: no chunk follows.
-  constexpr int BD = 3, QN = 40;
-  half8 bf[BD + 1];
-#define HS_TAPQ(Q_) ((Q_) / 4 == 9 ? 4 : (Q_) / 4)
-#define HS_READ_B(Q_)                                                                          \
-  {                                                                                            \
-    const int ky_ = HS_TAPQ(Q_) / 3, kx_ = HS_TAPQ(Q_) % 3;                                    \
-    const int toff_ = (((ky_ & 1) * 2 + (kx_ & 1)) * PLH + (ky_ >> 1)) * RP + (kx_ >> 1) * PITCH; \
-    bf[(Q_) % (BD + 1)] = *reinterpret_cast<const half8*>(&s_patch[fp_off + toff_ + ((Q_) % 4) * 16]); \
-  }
-#define HS_CHUNK(LAST_)                                                                        \
-  {                                                                                            \
-    HS_READ_B(0) HS_READ_B(1) HS_READ_B(2)                                                     \
-    _Pragma("unroll") for (int q = 0; q < 36; ++q) {                                           \
-      if (q + BD < QN) HS_READ_B(q + BD)                                                       \
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, fa[q % FR]),      \
-                                                   bf[q % (BD + 1)], acc, 0, 0, 0);            \
-      if (!(LAST_) || q + FR < 36) fa[q % FR] = wf[(q + FR) * 64];                             \
-      __builtin_amdgcn_sched_barrier(0);                                                       \
-    }                                                                                          \
-    wf += 36 * 64;                                                                             \
-    if (has_proj) {                                                                            \
-      wp += 4 * 64;                                                                            \
-      _Pragma("unroll") for (int q = 36; q < 40; ++q) {                                        \
-        if (q + BD < QN) HS_READ_B(q + BD)                                                     \
-        acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, fp2[q % 4]),   \
-                                                      bf[q % (BD + 1)], acc2, 0, 0, 0);        \
-        if (!(LAST_)) fp2[q % 4] = wp[(q % 4) * 64];                                           \
-      }                                                                                        \
-    }                                                                                          \
-  }
-
-  HS_LOAD_PATCH(cc_begin)
-#pragma unroll
-  for (int q = 0; q < FR; ++q) fa[q] = wf[q * 64];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) fp2[q] = wp[q * 64];
-  // the outputs this thread will finish: channel quad t % (8 * CW) of pixel t / (8 * CW)
-  constexpr int ITEMS = (256 * CW + 64 * NW - 1) / (64 * NW);
-  int o_m[ITEMS];                    // output pixel, -1: outside the image or no such item
-#pragma unroll
-  for (int k = 0; k < ITEMS; ++k) {
-    const int px = (tid + 64 * NW * k) / (8 * CW);
-    const int oy = y0 + (px >> 3), ox = x0 + (px & 7);
-    o_m[k] = px < 32 && oy < p.hout && ox < p.wout ? img * p.img_m + oy * p.wout + ox : -1;
-  }
-  HS_HAND_PATCH()
-  // every wavefront goes through chunks_per_split rounds (the barriers are for all of them); the
-  // last split may own fewer chunks
-  int cc = cc_begin;
-  for (int it = 1; it < p.chunks_per_split; ++it) {
-    if (cc + 1 < cc_end) {
-      HS_LOAD_PATCH(cc + 1)
-      HS_CHUNK(false)
-    } else if (cc < cc_end) {
-      HS_CHUNK(true)
-    }
-    if (CW > 1) __syncthreads();     // all readers of the patch are done
-    HS_HAND_PATCH()
-    ++cc;
-  }
-  if (cc < cc_end) HS_CHUNK(true)
-#undef HS_CHUNK
-#undef HS_READ_B
-#undef HS_TAPQ
-#undef HS_HAND_PATCH
-#undef HS_SYNC_PATCH
-#undef HS_LOAD_PATCH
-
-  // ---- add the partial tiles: accumulator quad i of lane (r, h) = channels 8 * i + 4 * h .. +3 (quad 2 * i + h) of
-  // pixel r.  34 float4s per quad row: reads and writes conflict free
-  float4* const s_red = reinterpret_cast<float4*>(s_raw);
-  const uint32_t touched = prefetch_next(p, tile, p.tiles_m * p.tiles_n);
-  __syncthreads();                   // every wavefront is done with its patch
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float4* const dst = s_red + wave * 2 * RED + (2 * i + h) * 34 + r;
-    dst[0] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
-    dst[RED] = make_float4(acc2[4 * i], acc2[4 * i + 1], acc2[4 * i + 2], acc2[4 * i + 3]);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < ITEMS; ++k) {
-    if (o_m[k] < 0) continue;
-    const int t = tid + 64 * NW * k, px = t / (8 * CW), c4 = t % (8 * CW), n = n_tile + 4 * c4;
-    const float4* src = s_red + (c4 >> 3) * 2 * RED + (c4 & 7) * 34 + px;
-    auto sum = [&](const float4* at) {
-      float4 a = at[0];
-#pragma unroll
-      for (int w = 1; w < NS; ++w) {
-        const float4 b = at[w * CW * 2 * RED];
-        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-      }
-      return a;
-    };
-    const float4 a = sum(src);
-    half4 o = {(f16)a.x, (f16)a.y, (f16)a.z, (f16)a.w};
-    if (p.relu) o = __builtin_elementwise_max(o, half4{});
-    *reinterpret_cast<half4*>(p.out + (size_t)o_m[k] * p.out_pitch + n) = o;
-    if (has_proj) {                  // projection output: no ReLU
-      const float4 b = sum(src + RED);
-      const half4 o2 = {(f16)b.x, (f16)b.y, (f16)b.z, (f16)b.w};
-      *reinterpret_cast<half4*>(p.out2 + (size_t)o_m[k] * p.out2_pitch + n) = o2;
-    }
-  }
-  asm volatile("" ::"v"(touched));
-}
-
 // =============================================================================================
 // 3x3 stride-1 pad-1 layers with several Cin chunks (stages 2-4 and the ConvLSTM gates), at every size.
 // A tile is 32 * CW channels x a RUN of 32 * PG consecutive pixels: the map is cut into strips of run_w columns, and
 // the pixels of all strips of all images of the launch, row by row, are one list that the runs are cut from.  So no
 // tile but the last is partly empty, whatever the map (tiles of 8 x 16 pixels are to 79 % full on a 27 x 15 map), and
-// the host can pick the tile whose count fills the CUs (Builder::choose_run).
+// the host can pick the tile whose count fills the CUs (Builder::choose_form).
 //   - The patch under a run, the border columns and a row of zeros between the images included, goes through LDS one
 //     chunk of 64 input channels at a time, double buffered: a chunk's loads are issued two chunks ahead, one barrier
 //     per chunk.  Rows are padded so that the pixel behind a row's last one lies in the bank group it would lie in
@@ -1389,13 +1180,208 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
             for (int j = 0; j < QU; ++j) *reinterpret_cast<float4*>(dst + 8 * j) = v[j];
           }
         } else if (QU == 2) {
-          store_half(p, m, cbase, h, v[0], v[1], res_raw[ps][u % UN]);
+          store_half(p.out, p.out_pitch, p.relu != 0, m, cbase, h, v[0], v[1], res_raw[ps][u % UN], p.res != nullptr);
         } else {
           store_quad(p, m, cbase, h, v[0], res_raw[ps][u % UN]);
         }
       }
   }
   asm volatile("" ::"v"(touched));
+}
+// =============================================================================================
+// 3x3 stride-2 pad-1 layers with the block's 1x1 stride-2 projection riding along: k_conv3x3_run's tiles, K splits and
+// loads.  What differs:
+//   - An output pixel needs four input pixels.  A patch row holds its even pixels first, then the odd ones, so that the
+//     lanes of a tap read neighbours; rows are padded so that the next output row (two patch rows further) goes on in the
+//     next bank group.
+//   - The K loop goes by items of 16 * KS input channels (a chunk, or half of one): every wavefront takes one K-step per
+//     tap and item, and one of the projection's, whose pixels are the centre tap's and whose sums are accumulators of
+//     their own.  The 64-channel layer's single chunk is one item of four K splits or two of two.
+// Per output and K split: item, tap; then the splits in pairs.
+// Against the kernels it replaced (4 x 8-pixel tiles with the splits chunk by chunk; 8 x 8 x 128 tiles on large grids), us
+// for the layers of 128 / 256 / 512 channels: one 288 x 160 frame 6.0 / 6.7 / 7.8 -> 4.5 / 5.3 / 6.5, one 854 x 480 frame 8.0
+// / 8.0 / 8.4 -> 6.9 / 6.6 / 6.9, four 641 x 361 frames 15.9 / 12.3 / 12.9 -> 12.0 / 8.7 / 12.6, sixteen 416 x 240 frames
+// 17.7 / 13.9 / 14.0 -> 15.1 / 12.3 / 12.1, twelve 854 x 480 frames 30.9 / 27.6 / 28.8 -> (k_conv3x3s2_dira) / 26.9 / 24.8.
+// =============================================================================================
+template <int PG, int KS, int CW, int BD, int PL, int LDS, int OCC>
+__global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams p) {
+  constexpr int NW = KS * CW, C = 32 * CW, VP = 2 * KS, U = VP + 1, PITCH = 8 * U;   // 16-byte vectors, LDS units per pixel
+  constexpr int UNITS = 4 * PG;                                    // pieces of 16 channels x 32 pixels, the projection's too
+  constexpr int UP = UNITS * NW * 2048 <= 2 * LDS || UNITS * NW * 2048 <= 65536 ? UNITS : UNITS / 2, PASSES = UNITS / UP, UN = UP / KS;
+  static_assert(UP % KS == 0, "every K split finishes the same number of pieces");
+  constexpr int RED = UP * NW * 2048, SHM = RED > 2 * LDS ? RED : 2 * LDS;
+  __shared__ __align__(16) unsigned char s_raw[SHM];
+  f16* const s_patch = reinterpret_cast<f16*>(s_raw);
+
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wave % KS, cw = wave / KS;
+  const uint32_t tile = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
+  if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
+  const uint32_t nb = (uint32_t)p.n_block;                         // a power of two; tile order: see above
+  const uint32_t t_blk = run_div31(tile, p.run_by_blk), in_blk = tile - t_blk * (uint32_t)p.tiles_m * nb;
+  const int n0 = (int)(t_blk * nb + (in_blk & (nb - 1))) * C;
+  const RunOrigin org = run_origin(p.run, in_blk >> p.run_nb_shift);
+  const int rw = 2 * p.run.strip_w + 1, rp = p.run.pitch2, odd = (p.run.strip_w + 1) * PITCH;   // odd: offset of a row's odd pixels
+
+  // ---- patch loader, as in k_conv3x3_run
+  int l_poff[PL], l_lds[PL];
+  {
+    const uint32_t pix = (uint32_t)tid / VP;
+    const int v = (tid % VP) * 8;
+    uint32_t prow = run_div23(pix, p.run.by23_row), pcol = pix - prow * (uint32_t)rw;
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+      int m;
+      const bool fits = prow < (uint32_t)p.run.rows, in = run2_patch_pixel(p.run, org, prow, pcol, m) && fits;
+      l_poff[i] = in ? (m * p.cin_pitch + v) * 2 : kOutside;
+      l_lds[i] = fits ? (int)prow * rp + (int)(pcol >> 1) * PITCH + (pcol & 1u ? odd : 0) + v : LDS / 2 - 64 + v;
+      prow += (uint32_t)p.run.step_q;
+      pcol += (uint32_t)p.run.step_r;
+      if (pcol >= (uint32_t)rw) { pcol -= (uint32_t)rw; ++prow; }
+    }
+  }
+  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes),
+                   w2_buf = buffer_of(p.wt2_frag, p.run_w_bytes / 9);
+  u32x4 st_p[PL];
+#define HS_LOAD_P(I_, IT_) st_p[I_] = load16(in_buf, l_poff[I_], (IT_) * (VP * 16));
+#define HS_HAND_P(V_, I_, B_) *reinterpret_cast<u32x4*>(&s_patch[(B_) * (LDS / 2) + l_lds[I_]]) = (V_);
+
+  // An item is VP * 8 input channels: a chunk, or half of one.  Its K-steps are the KS splits': a wavefront takes one per
+  // tap, and one for the projection (on the centre tap's pixels).  n_it items, in pairs; a single one comes second.
+  const int n_it = p.chunks_per_tap * (4 / KS), single = n_it & 1;
+  constexpr int WI = KS == 4 ? 36 * 1024 : 2 * 1024, WI2 = KS == 4 ? 4 * 1024 : 2 * 1024;   // bytes from item to item of a pair
+  constexpr int WP = 36 * 1024 * KS / 2, WP2 = 4 * 1024 * KS / 2;                           // and from pair to pair
+  int wf = (n0 / 32 + cw) * p.chunks_per_tap * 36 * 1024 + ks * 1024 - single * WI;
+  int wf2 = (n0 / 32 + cw) * p.chunks_per_tap * 4 * 1024 + ks * 1024 - single * WI2;
+  u32x4 first[PL];
+#pragma unroll
+  for (int i = 0; i < PL; ++i) first[i] = load16(in_buf, l_poff[i], 0);
+#pragma unroll
+  for (int i = 0; i < PL; ++i) HS_LOAD_P(i, min(1, n_it - 1))
+  u32x4 fa[9], fb;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) fa[t] = load16(w_buf, lane * 16, wf + single * WI + t * 4096);
+  fb = load16(w2_buf, lane * 16, wf2 + single * WI2);
+  int fpo[PG], o_m[PG];
+#pragma unroll
+  for (int g = 0; g < PG; ++g) {
+    uint32_t row, col;
+    run2_pixel(p.run, org, 32 * g + r, row, col, o_m[g]);
+    fpo[g] = (int)row * rp + (int)col * PITCH + h * 8 + ks * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < PL; ++i) HS_HAND_P(first[i], i, single)
+  __syncthreads();
+
+  const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  floatx16 acc[2][PG];                                             // the layer's, the projection's
+#pragma unroll
+  for (int g = 0; g < PG; ++g) acc[0][g] = acc[1][g] = zero16;
+  // Pixel fragment F_ = K-step * PG + group of an item; K-step 4 is the centre tap, which the projection shares
+  half8 bf[BD + 1];
+#define HS_READ_B(U_, F_)                                                                      \
+  bf[(F_) % (BD + 1)] = *reinterpret_cast<const half8*>(                                       \
+      &s_patch[(U_) * (LDS / 2) + fpo[(F_) % PG] + ((F_) / PG / 3) * rp + (((F_) / PG) % 3 == 1 ? odd : ((F_) / PG) % 3 / 2 * PITCH)]);
+#define HS_ITEM(U_, LAST_)                                                                     \
+  {                                                                                            \
+    _Pragma("unroll") for (int f = 0; f < BD; ++f) HS_READ_B(U_, f)                            \
+    _Pragma("unroll") for (int s = 0; s < 9; ++s) {                                            \
+      _Pragma("unroll") for (int i = 0; i < PL; ++i)                                           \
+        if ((2 * i + 1) * 9 / (2 * PL) == s && (!(LAST_) || (U_) == 0)) {                      \
+          HS_HAND_P(st_p[i], i, 1 - (U_))                                                      \
+          if (!(LAST_)) HS_LOAD_P(i, min(it + (U_) + 2, n_it - 1))                             \
+        }                                                                                      \
+      _Pragma("unroll") for (int g = 0; g < PG; ++g) {                                         \
+        if (s * PG + g + BD < 9 * PG) HS_READ_B(U_, s * PG + g + BD)                           \
+        const half8 b_ = bf[(s * PG + g) % (BD + 1)];                                          \
+        acc[0][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, fa[s]), b_, acc[0][g], 0, 0, 0); \
+        if (s == 4) acc[1][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, fb), b_, acc[1][g], 0, 0, 0); \
+        if (PG > 2) __builtin_amdgcn_sched_barrier(0);                                         \
+      }                                                                                        \
+      if (!(LAST_) || (U_) == 0) {                                                             \
+        fa[s] = load16(w_buf, lane * 16, wf + ((U_) == 0 ? WI : WP) + s * 4096);               \
+        if (s == 4) fb = load16(w2_buf, lane * 16, wf2 + ((U_) == 0 ? WI2 : WP2));             \
+      }                                                                                        \
+      __builtin_amdgcn_sched_barrier(0);                                                       \
+    }                                                                                          \
+  }
+  int it = 0;
+  for (; it + 2 < n_it; it += 2) {
+    HS_ITEM(0, false)
+    __syncthreads();
+    HS_ITEM(1, false)
+    __syncthreads();
+    wf += WP;
+    wf2 += WP2;
+  }
+  if (!single) {
+    HS_ITEM(0, true)
+    __syncthreads();
+  }
+  HS_ITEM(1, true)
+#undef HS_ITEM
+#undef HS_READ_B
+#undef HS_HAND_P
+#undef HS_LOAD_P
+
+  const uint32_t touched = prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n);
+  float4* const s_red = reinterpret_cast<float4*>(s_raw) + wave / KS * KS * UP * 128 + lane;
+#pragma unroll
+  for (int ps = 0; ps < PASSES; ++ps) {
+    __syncthreads();                 // every wavefront is done with the patches, or with the sums of the pass before
+#pragma unroll
+    for (int u = 0; u < UP; ++u)
+      if (u / UN != ks) {
+        const floatx16& a = acc[(ps * UP + u) / (2 * PG)][(ps * UP + u) / 2 % PG];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int o = 8 * (u & 1) + 4 * j;
+          s_red[(ks * UP + u) * 128 + 64 * j] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
+        }
+      }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < UP; ++u)
+      if (u / UN == ks) {
+        const int w = (ps * UP + u) / (2 * PG), g = (ps * UP + u) / 2 % PG;
+        const floatx16& a = acc[w][g];
+        float4 v[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int o = 8 * (u & 1) + 4 * j;
+          float4 b[KS];
+#pragma unroll
+          for (int k = 0; k < KS; ++k) {
+            b[k] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
+            if (k != ks) b[k] = s_red[(k * UP + u) * 128 + 64 * j];
+          }
+#pragma unroll
+          for (int d = KS / 2; d >= 1; d /= 2)                     // in pairs
+#pragma unroll
+            for (int k = 0; k < d; ++k) {
+              b[k].x += b[k + d].x; b[k].y += b[k + d].y; b[k].z += b[k + d].z; b[k].w += b[k + d].w;
+            }
+          v[j] = b[0];
+        }
+        const int cbase = n0 + cw * 32 + 16 * (u & 1);
+        const u32x4 none = {0u, 0u, 0u, 0u};
+        if (w == 0) store_half(p.out, p.out_pitch, p.relu != 0, o_m[g], cbase, h, v[0], v[1], none, false);
+        else store_half(p.out2, p.out2_pitch, false, o_m[g], cbase, h, v[0], v[1], none, false);   // no ReLU
+      }
+  }
+  asm volatile("" ::"v"(touched));
+}
+// The instantiations of k_conv3x3s2_run: see kRun2Forms.
+static const void* run2_kernel_of(int form) {
+  switch (form) {
+    case 0: return (const void*)k_conv3x3s2_run<1, 4, 1, 5, 6, 28672, 2>;
+    case 1: return (const void*)k_conv3x3s2_run<1, 2, 2, 5, 3, 16384, 3>;
+    case 2: return (const void*)k_conv3x3s2_run<2, 2, 2, 5, 5, 28672, 2>;
+    case 3: return (const void*)k_conv3x3s2_run<3, 2, 2, 5, 8, 40960, 2>;
+    case 4: return (const void*)k_conv3x3s2_run<1, 4, 1, 5, 8, 40960, 1>;
+    default: return nullptr;
+  }
 }
 // The instantiations of k_conv3x3_run: see kRunForms.
 static const void* run_kernel_of(int form) {
@@ -1415,17 +1401,6 @@ static_assert(kRunForms[0].passes == 3 && kRunForms[0].lds == 16384 && kRunForms
               kRunForms[4].passes == 7 && kRunForms[4].lds == 36864 && kRunForms[5].passes == 8 && kRunForms[5].lds == 40960 &&
               kRunForms[6].passes == 7 && kRunForms[6].lds == 44032, "the host plans for the kernels' patch buffers");
 
-// The instantiations the host's rules ask for (see Builder::plan_kw).
-static const void* kw_kernel_of(const ConvParams& p) {
-  switch (p.kw_cgroups * 10 + p.kw_splits) {
-    case 41: return (const void*)k_conv3x3s2_kw<4, 4>;
-    case 21: return (const void*)k_conv3x3s2_kw<2, 2>;
-    case 22: return (const void*)k_conv3x3s2_kw<2, 4>;
-    case 14: return (const void*)k_conv3x3s2_kw<1, 4>;
-    default: return nullptr;
-  }
-}
-
 KernelDesc describe(const ConvParams& p) {
   // 1-D grid, padded to a multiple of 8 so that every XCD owns tiles_per_xcd consecutive tiles
   const dim3 grid(8u * (unsigned)p.tiles_per_xcd);
@@ -1441,8 +1416,7 @@ KernelDesc describe(const ConvParams& p) {
     case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
     case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
     case CONV_KW:
-      if (p.stride == 1) return KernelDesc{run_kernel_of(p.run_form), grid, dim3(256), 0};
-      return KernelDesc{kw_kernel_of(p), grid, dim3(64u * (unsigned)(p.kw_splits * p.kw_cgroups)), 0};
+      return KernelDesc{p.stride == 1 ? run_kernel_of(p.run_form) : run2_kernel_of(p.run_form), grid, dim3(256), 0};
     default: return KernelDesc{nullptr, grid, dim3(256), 0};
   }
 }

@@ -458,16 +458,6 @@ struct Builder {
     if (failed) std::rethrow_exception(failed);
   }
 
-  // k_conv3x3s2_kw with ns K splits and cw channel groups per workgroup.
-  static void plan_kw(ConvParams& c, int ns, int cw) {
-    c.variant = CONV_KW;
-    c.kw_splits = ns; c.kw_cgroups = cw;
-    c.tiles_x = (c.wout + 7) / 8;
-    c.tiles_m = c.batch * ((c.hout + 3) / 4) * c.tiles_x;
-    c.tiles_n = c.cout / (32 * cw);
-    c.chunks_per_split = (c.chunks_per_tap + ns - 1) / ns;
-  }
-
   // k_conv3x3_run with a form of kRunForms.  False: the layer is out of the form's range.
   static bool plan_run(ConvParams& c, int form) {
     const RunForm& f = kRunForms[form];
@@ -481,25 +471,40 @@ struct Builder {
     return c.tiles_m > 0 && (double)c.tiles_m * c.tiles_n * c.tiles_m * c.tiles_n < 2147483648.0;   // run_div31
   }
 
-  // The form of k_conv3x3_run for a layer.  A tile's time is a fixed part and one per Cin chunk (kRunForms, fitted to
-  // twelve 854 x 480 frames, where every CU works on several tiles); the launch lasts as long as its busiest CU, which
-  // has ceil(tiles / 256) of them.  A CU with a single tile hides nothing of its latencies behind another one: 1 us
-  // more.  Over eleven sizes from one 192 x 110 to twelve 854 x 480 frames the form with the smallest sum is the fastest
-  // one or within 8 % of it (four 641 x 361 frames, 512 channels: 9.6 us, the other forms 11.7 to 19.7).
-  static void choose_run(ConvParams& c) {
+  // k_conv3x3s2_run with a form of kRun2Forms.
+  static bool plan_run2(ConvParams& c, int form) {
+    const Run2Form& f = kRun2Forms[form];
+    const double in_bytes = 2.0 * c.batch * c.hin * c.win * c.cin_pitch, w_bytes = 2.0 * c.cout_pad * c.ktot;
+    if (c.cout % f.ch != 0 || in_bytes >= 2147483648.0 || w_bytes >= 2147483648.0) return false;
+    c.variant = CONV_KW;
+    c.run_form = form;
+    c.run_in_bytes = (uint32_t)in_bytes; c.run_w_bytes = (uint32_t)w_bytes;
+    c.tiles_m = run2_plan(c.hin, c.win, c.batch, f.px, f.passes, f.lds, f.step, f.units, c.run);
+    c.tiles_n = c.cout / f.ch;
+    return c.tiles_m > 0 && (double)c.tiles_m * c.tiles_n * c.tiles_m * c.tiles_n < 2147483648.0;   // run_div31
+  }
+
+  // The form of k_conv3x3_run or k_conv3x3s2_run for a layer.  A tile's time is a fixed part and one per Cin chunk
+  // (kRunForms, kRun2Forms, fitted to twelve 854 x 480 frames, where every CU works on several tiles); the launch lasts as
+  // long as its busiest CU, which has ceil(tiles / 256) of them.  A CU with a single tile hides nothing of its latencies
+  // behind another one: 1 us more.  Over eleven sizes from one 192 x 110 to twelve 854 x 480 frames the form with the
+  // smallest sum is the fastest one or within 8 % of it (four 641 x 361 frames, 512 channels at stride 1: 9.6 us, the other
+  // forms 11.7 to 19.7).
+  template <class Form, class Plan>
+  static void choose_form(ConvParams& c, const Form* forms, int n_forms, int any_map, Plan plan) {
     constexpr int kRound = 256;
     double best = 0;
     int form = -1;
-    for (int i = 0; i < kRunFormCount; ++i) {
-      if (i == kRunFormAnyMap && form >= 0) break;
+    for (int i = 0; i < n_forms; ++i) {
+      if (i == any_map && form >= 0) break;
       ConvParams t = c;
-      if (!plan_run(t, i)) continue;
+      if (!plan(t, i)) continue;
       const int rounds = (t.tiles_m * t.tiles_n + kRound - 1) / kRound;
-      const double cost = rounds * (kRunForms[i].cost + kRunForms[i].chunk_cost * c.chunks_per_tap) + (rounds == 1 ? 1.0 : 0.0);
+      const double cost = rounds * (forms[i].cost + forms[i].chunk_cost * c.chunks_per_tap) + (rounds == 1 ? 1.0 : 0.0);
       if (form < 0 || cost < best) { best = cost; form = i; }
     }
     if (form < 0) throw std::logic_error("no tile form for a layer of this network");
-    plan_run(c, form);
+    plan(c, form);
   }
 
   // Picks the kernel variant, the tile grid and the split along K.
@@ -508,39 +513,22 @@ struct Builder {
     const bool fits32 = (double)c.batch * c.hin * c.win * c.cin_pitch < 2147483648.0;
     const bool s3x3 = c.ntaps == 9 && c.kw == 3 && c.pad == 1 && c.kc == 64 && c.cout % 128 == 0 && fits32;
     c.tiles_per_wg = 1;
-    // workgroups of a k_conv3x3s2_kw grid
-    auto wgs = [&](int cw) {
-      return c.batch * ((c.hout + 3) / 4) * ((c.wout + 7) / 8) * (c.cout / (32 * cw));
-    };
-    const int tiles = c.batch * ((c.hout + 7) / 8) * ((c.wout + 7) / 8) * (c.cout / 64);   // of 8 x 8 pixels x 64 channels
-    // K splits: the count is part of the result (fp32 sums are not associative), so it depends on
-    // the shape alone and not on the kernel: as many as bring 256 tiles of 8 x 8 pixels x 64 channels,
-    // in whole chunks
-    auto k_splits = [&] {
-      const int ns = tiles >= 192 ? 1 : std::max(1, std::min((256 + tiles - 1) / tiles, c.chunks_per_tap));
-      const int per = (c.chunks_per_tap + ns - 1) / ns;
-      return (c.chunks_per_tap + per - 1) / per;
-    };
-    constexpr int kRound = 256;         // one workgroup for every CU
     if (s3x3 && c.stride == 2) {
-      if (tiles >= 768) {
-        // from 1.5 workgroups of 8 x 8 x 128 per CU on: the patch, the heavy operand at stride 2, serves
-        // 128 channels.  Two workgroups per CU are resident: beyond two rounds, walk in one.  (The
-        // line also marks a change of the K order, and so of the results' last bits.)
+      const int n = c.batch * ((c.hout + 7) / 8) * ((c.wout + 7) / 8) * (c.cout / 128);   // tiles of 8 x 8 x 128
+      if (c.chunks_per_tap == 1 && n > 1024) {
+        // One chunk, more tiles than two rounds of workgroups: k_conv3x3s2_dira walks them, the next tile's patch fetched
+        // during the current one's products (two workgroups per CU are resident, so walk in one round).  Twelve 854 x 480
+        // frames (1344 tiles) 30.9 us, k_conv3x3s2_run 33.8; sixteen 416 x 240 frames (448 tiles) 17.7, 15.1.
         c.variant = CONV_S2_DIRA;
         c.tiles_x = (c.wout + 7) / 8;
         c.tiles_m = c.batch * ((c.hout + 7) / 8) * c.tiles_x;
         c.tiles_n = c.cout / 128;
-        const int n = c.tiles_m * c.tiles_n;
-        if (n > 1024) c.tiles_per_wg = (n + 511) / 512;
+        c.tiles_per_wg = (n + 511) / 512;
       } else {
-        // one split: two channel groups per workgroup while that is one round, else four (the patch
-        // serves twice the channels)
-        const int ns = k_splits();
-        plan_kw(c, ns, ns == 1 ? (wgs(2) <= kRound ? 2 : 4) : ns == 2 ? 2 : 1);
+        choose_form(c, kRun2Forms, kRun2FormCount, kRun2FormAnyMap, plan_run2);
       }
     } else if (s3x3 && c.stride == 1 && c.chunks_per_tap >= 2) {
-      choose_run(c);
+      choose_form(c, kRunForms, kRunFormCount, kRunFormAnyMap, plan_run);
     } else if (c.cout <= 32 && c.kc <= 32 && c.chunks_per_tap == 1 && c.ntaps <= 9) {
       // two K splits, of at most five taps each, while tiles of 64 pixels would be fewer than 192
       c.variant = CONV_DIRECT;
@@ -582,7 +570,7 @@ struct Builder {
         if (nb == 1 || bytes < 0.9 * best) { best = bytes; c.n_block = nb; }
       }
     }
-    if (c.variant == CONV_KW && c.stride == 1) {
+    if (c.variant == CONV_KW) {
       c.run_nb_shift = 0;
       while ((1 << c.run_nb_shift) < c.n_block) ++c.run_nb_shift;
       const uint64_t blk = (uint64_t)c.tiles_m * c.n_block;
@@ -887,7 +875,7 @@ struct Builder {
 
   void walk(int ph, int pw) {
     if (d.net == HS_NET_TINY4) walk_tiny(ph, pw); else walk_resnet(ph, pw);
-    // With several frames per launch the layers that k_conv3x3_run and k_conv3x3s2_kw compute prefetch the next layer's
+    // With several frames per launch the layers that k_conv3x3_run and k_conv3x3s2_run compute prefetch the next layer's
     // weights (not its projection's): a pass then touches more than the last-level cache holds and finds
     // the weights in HBM (four frames 641 x 361: 363 -> 337 us, sixteen frames 416 x 240: 375 -> 358).  The 36 MB of a one-frame
     // application stay cached, and the prefetch would only cost (168 -> 172 us).

@@ -1,5 +1,5 @@
-// Geometry of k_conv3x3_run's tiles (see there): runs of consecutive pixels of strips of all images of a launch, and the
-// patch under a run.  One definition for the kernel and for the host, which plans with it.
+// Geometry of the tiles of k_conv3x3_run and k_conv3x3s2_run (see there): runs of consecutive pixels of strips of all
+// images of a launch, and the patch under a run.  One definition for the kernels and for the host, which plans with it.
 #pragma once
 
 #include <stdint.h>
@@ -10,15 +10,17 @@ namespace hs {
 
 constexpr int kRunPitch = 64 + 8;        // LDS halves per patch pixel: 64 channels, padded against bank conflicts
 
-// Of a layer with stride 1: maps of h x w pixels, `batch` images.
+// Of a layer: output maps of h x w pixels, input maps of hin x win (stride 1: the same), `batch` images.
 struct RunGeometry {
   int px;               // pixels per tile
   int h, w, batch;
+  int hin, win;
   int strip_w;          // columns per strip
   int rows;             // patch rows at most, the rows of zeros between images included
-  int step_q, step_r;   // quotient and remainder of the patch pixels per loading pass (32) by a patch row's length
+  int step_q, step_r;   // quotient and remainder of the patch pixels per loading pass by a patch row's length
+  int pitch2;           // stride 2: LDS halves per patch row
   // reciprocals: ceil(2^31 / d) for quotients of scalars, ceil(2^23 / d) for those of lanes
-  uint32_t by_strip_w, by_h, by_batch;
+  uint32_t by_strip_w, by_h, by_batch, by_period;   // period: stride 2, patch rows of an image
   uint32_t by23_strip_w, by23_row, by23_h, by23_h1, by23_batch;
 };
 
@@ -87,6 +89,39 @@ __host__ __device__ __forceinline__ void run_pixel(const RunGeometry& g, const R
   m = x < (uint32_t)g.w ? (int)((img * (uint32_t)g.h + y) * (uint32_t)g.w + x) : -1;
 }
 
+// Stride 2 (pad 1).  An output row's taps read input rows 2 y - 1 .. 2 y + 1: an image has 2 h + 1 patch rows, the first
+// one zeros, the last one zeros too where hin is odd.  Strips are an even number of columns wide; a patch row holds
+// 2 strip_w + 1 pixels, in LDS the even ones first, so that the lanes of a tap read neighbours.
+__host__ __device__ __forceinline__ bool run2_patch_pixel(const RunGeometry& g, const RunOrigin& o, uint32_t row, uint32_t col,
+                                                          int& m) {
+  const uint32_t e = 2 * o.y + row, k = run_div31(e, g.by_period), f = e - k * (uint32_t)(2 * g.h + 1);
+  const uint32_t ds = run_div23(o.img + k, g.by23_batch), img = o.img + k - ds * (uint32_t)g.batch;
+  const int y = (int)f - 1, x = (int)(2 * (o.strip + ds) * (uint32_t)g.strip_w + col) - 1;
+  m = ((int)img * g.hin + y) * g.win + x;
+  return y >= 0 && y < g.hin && x >= 0 && x < g.win;
+}
+// The pixel's first tap: patch row `row`, even pixel `col` of it.
+__host__ __device__ __forceinline__ void run2_pixel(const RunGeometry& g, const RunOrigin& o, uint32_t i, uint32_t& row,
+                                                    uint32_t& col, int& m) {
+  run_pixel(g, o, i, row, col, m);       // row = d + k: d output rows and k images further
+  const uint32_t d = run_div23(o.rem + i, g.by23_strip_w);
+  row += d;
+}
+// LDS halves per patch row with u 16-byte units per pixel: two rows further, the next output row's first pixel lies in
+// the bank group behind its predecessor's.
+constexpr __host__ __device__ __forceinline__ int run2_row_pitch(int strip_w, int u) {
+  return 8 * (u * (2 * strip_w + 1) + ((u * strip_w / 2 - u * (2 * strip_w + 1)) % 8 + 8) % 8);
+}
+
+inline void run_finish_plan(RunGeometry& g, int px, int h, int w, int hin, int win, int batch, int row, int step) {
+  g.px = px; g.h = h; g.w = w; g.hin = hin; g.win = win; g.batch = batch;
+  g.step_q = step / row; g.step_r = step % row;
+  auto by = [](int bits, int d) { return (uint32_t)((((uint64_t)1 << bits) + (uint64_t)d - 1) / (uint64_t)d); };
+  g.by_strip_w = by(31, g.strip_w); g.by_h = by(31, h); g.by_batch = by(31, batch); g.by_period = by(31, 2 * h + 1);
+  g.by23_strip_w = by(23, g.strip_w); g.by23_row = by(23, row);
+  g.by23_h = by(23, h); g.by23_h1 = by(23, h + 1); g.by23_batch = by(23, batch);
+}
+
 // Plans runs of px pixels with patches of at most 32 * passes pixels and lds bytes: the strips as wide as gives the fewest
 // tiles and then the smallest patch.  Returns the number of tiles, 0 if no strip width fits.
 inline int run_plan(int h, int w, int batch, int px, int passes, int lds, RunGeometry& g) {
@@ -106,13 +141,31 @@ inline int run_plan(int h, int w, int batch, int px, int passes, int lds, RunGeo
     }
   }
   if (!best_tiles) return 0;
-  g.px = px; g.h = h; g.w = w; g.batch = batch;
-  const int row = g.strip_w + 2;
-  g.step_q = 32 / row; g.step_r = 32 % row;
-  auto by = [](int bits, int d) { return (uint32_t)((((uint64_t)1 << bits) + (uint64_t)d - 1) / (uint64_t)d); };
-  g.by_strip_w = by(31, g.strip_w); g.by_h = by(31, h); g.by_batch = by(31, batch);
-  g.by23_strip_w = by(23, g.strip_w); g.by23_row = by(23, row);
-  g.by23_h = by(23, h); g.by23_h1 = by(23, h + 1); g.by23_batch = by(23, batch);
+  g.pitch2 = 0;
+  run_finish_plan(g, px, h, w, h, w, batch, g.strip_w + 2, 32);
+  return best_tiles;
+}
+
+// The same at stride 2; a loading pass takes `step` patch pixels of u 16-byte units in LDS.
+inline int run2_plan(int hin, int win, int batch, int px, int passes, int lds, int step, int u, RunGeometry& g) {
+  const int h = (hin + 1) / 2, w = (win + 1) / 2;
+  const int64_t rows = (int64_t)batch * h;
+  if (h > 2500 || rows * (w + 64) >= (int64_t)1 << 23) return 0;
+  int best_tiles = 0, best_px = 0;
+  for (int sw = 2; sw <= w + 1 && sw <= 64; sw += 2) {
+    const int64_t strips = (w + sw - 1) / sw, tiles = (rows * strips * sw + px - 1) / px;
+    const int d = (px % sw == 0 ? px - 1 : px + sw - 2) / sw, k = (d + h - 1) / h, n_rows = 2 * d + k + 3;
+    const int n_px = n_rows * (2 * sw + 1);
+    if (n_px > step * passes || n_rows * run2_row_pitch(sw, u) * 2 + 128 > lds) continue;
+    if (tiles * px * sw >= (int64_t)1 << 31 || (rows * strips + px) * h >= (int64_t)1 << 31) continue;
+    if (!best_tiles || tiles < best_tiles || (tiles == best_tiles && n_px < best_px)) {
+      best_tiles = (int)tiles; best_px = n_px;
+      g.strip_w = sw; g.rows = n_rows;
+    }
+  }
+  if (!best_tiles) return 0;
+  g.pitch2 = run2_row_pitch(g.strip_w, u);
+  run_finish_plan(g, px, h, w, hin, win, batch, 2 * g.strip_w + 1, step);
   return best_tiles;
 }
 
