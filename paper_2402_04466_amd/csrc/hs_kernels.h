@@ -92,6 +92,7 @@ struct ConvParams {
   int variant;          // ConvVariant
   int kw_splits;        // CONV_DIRECT: K splits
   int tiles_x;          // spatial variants: tiles per output row
+  uint32_t tiles_img, by_tiles_img, by_tiles_x;   // CONV_BLOCK64: tiles per image; reciprocals (run_div31)
   int ntaps, kw, chunks_per_tap, nchunks, ktot;
   int stride, pad;
   int chunks_per_split; // K split z handles chunks [z*chunks_per_split, ...)
@@ -116,7 +117,7 @@ struct ConvParams {
   // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
   const f16* wt2_frag;
   f16* out2; int out2_pitch;
-  // CONV_KW: form (kRunForms, kRun2Forms), tiles; bytes of the input and of the weights; log2 of n_block, reciprocal of
+  // CONV_KW: form (kRunForms, kRun2Forms), tiles; bytes of the input (CONV_BLOCK64, too) and of the weights; log2 of n_block, reciprocal of
   // tiles_m * n_block (run_div31)
   int run_form;
   RunGeometry run;

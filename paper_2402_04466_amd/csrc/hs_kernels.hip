@@ -25,8 +25,12 @@ __device__ __forceinline__ uint32_t udiv_est(uint32_t num, uint32_t d, float rcp
 // load, and a lane whose offset lies behind the buffer reads zeros (kOutside: always).
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
 constexpr int kOutside = (int)0x80000000u;
+// (Both arguments are the same for the whole wavefront; unless told so the compiler may keep the descriptor in vector
+// registers, and then every load is a loop over the lanes' values.)
 __device__ __forceinline__ BufferRsrc buffer_of(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
+  const uint64_t b = (uint64_t)base;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00027000);
 }
 __device__ __forceinline__ u32x4 load16(BufferRsrc buf, int lane_offset, int offset) {
   return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, lane_offset, offset, 0));
@@ -570,49 +574,46 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
   constexpr int TH = 8, TW = 16, YH = TH + 2, YW = TW + 2, XH = TH + 4, XW = TW + 4;
   constexpr int PITCH = 64 + 8;
   constexpr int RPY = (YW * PITCH * 2 + ((128 - (YW * PITCH * 2) % 256 + 256) % 256)) / 2;
-  constexpr int RPX = (XW * PITCH * 2 + ((128 - (XW * PITCH * 2) % 256 + 256) % 256)) / 2;
-  static_assert((RPY * 2) % 256 == 128 && (RPX * 2) % 256 == 128, "row pitch must be 128 mod 256 bytes");
+  // input rows: the 18 pixels of an intermediate row end where, 16 bank groups of 16 bytes round, the next row's begin
+  constexpr int RPX = XW * PITCH + 8 * (((YW - XW) * 9 % 16 + 32) % 16);
+  static_assert((RPY * 2) % 256 == 128, "row pitch must be 128 mod 256 bytes");
+  static_assert(RPX / 8 % 16 == YW * 9 % 16 && RPX >= XW * PITCH, "phase A's lanes must not meet in a bank group");
   static_assert(XH * RPX >= YH * RPY, "the intermediate patch is written over the input patch");
   constexpr int NPY = YH * YW;                         // 180 intermediate pixels
   constexpr int XV = XH * XW * 8, XL = (XV + 255) / 256;   // input patch vectors, per thread
   constexpr int FR = 12, BD = 2;        // weight fragments and pixel K-steps in flight
   __shared__ __align__(16) f16 s_xy[XH * RPX];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  const int tm = (int)(blockIdx.x & 7u) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (tm >= p.tiles_m) return;
-  const int tiles_img = p.tiles_m / p.batch;
-  const int img = tm / tiles_img, ts = tm - img * tiles_img, ty = ts / p.tiles_x;
-  const int y0 = ty * TH, x0 = (ts - ty * p.tiles_x) * TW;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 31, h = lane >> 5;
+  const uint32_t tm = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
+  const uint32_t img_u = run_div31(tm, p.by_tiles_img), ts = tm - img_u * p.tiles_img, ty = run_div31(ts, p.by_tiles_x);
+  const int img = (int)img_u, y0 = (int)ty * TH, x0 = (int)(ts - ty * (uint32_t)p.tiles_x) * TW;
   const int wm = wave & 1, wn = wave >> 1;
 
   // ---- input patch: pixel (y0 - 2 + py, x0 - 2 + px), zeros outside the image
+  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), wa_buf = buffer_of(p.wt_frag, 72 * 1024),
+                   wb_buf = buffer_of(p.wt2_frag, 72 * 1024);
   u32x4 st_x[XL];
-  uint32_t x_inb = 0;
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int v = tid + 256 * i;
-    const int pix = min(v >> 3, XH * XW - 1), py = pix / XW, px = pix - py * XW;
+    const int pix = v >> 3, py = pix / XW, px = pix - py * XW;
     const int iy = y0 - 2 + py, ix = x0 - 2 + px;
     const bool in = v < XV && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
-    x_inb |= (in ? 1u : 0u) << i;
-    const int off = in ? ((img * p.hin + iy) * p.win + ix) * p.cin_pitch + (tid & 7) * 8 : 0;
-    st_x[i] = *reinterpret_cast<const u32x4*>(p.in + off);
+    st_x[i] = load16(in_buf, in ? (((img * p.hin + iy) * p.win + ix) * p.cin_pitch + (tid & 7) * 8) * 2 : kOutside, 0);
   }
   // ---- weight fragments of this wavefront's 32 channels: 36 of conv_a, then 36 of conv_b
-  const u32x4* const wa = reinterpret_cast<const u32x4*>(p.wt_frag) + wn * (36 * 64) + lane;
-  const u32x4* const wb = reinterpret_cast<const u32x4*>(p.wt2_frag) + wn * (36 * 64) + lane;
+  const int w0 = wn * 36 * 1024;
   u32x4 fa[FR];
 #pragma unroll
-  for (int q = 0; q < FR; ++q) fa[q] = wa[q * 64];
+  for (int q = 0; q < FR; ++q) fa[q] = load16(wa_buf, lane * 16, w0 + q * 1024);
+  if (tm >= (uint32_t)p.tiles_m) return;    // (only here: see k_conv3x3_run)
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int v = tid + 256 * i;
     if (v < XV) {
       const int pix = v >> 3, py = pix / XW, px = pix - py * XW;
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(&s_xy[py * RPX + px * PITCH + (v & 7) * 8]) =
-          ((x_inb >> i) & 1u) ? st_x[i] : zero;
+      *reinterpret_cast<u32x4*>(&s_xy[py * RPX + px * PITCH + (v & 7) * 8]) = st_x[i];
     }
   }
 
@@ -644,7 +645,7 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
 #pragma unroll
     for (int k = 0; k < 3; ++k)
       acc_a[k] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bf[q % (BD + 1)][k], acc_a[k], 0, 0, 0);
-    fa[q % FR] = q + FR < 36 ? wa[(q + FR) * 64] : wb[(q + FR - 36) * 64];
+    fa[q % FR] = q + FR < 36 ? load16(wa_buf, lane * 16, w0 + (q + FR) * 1024) : load16(wb_buf, lane * 16, w0 + (q + FR - 36) * 1024);
     __builtin_amdgcn_sched_barrier(0);
   }
 #undef HS_READ_A
@@ -699,7 +700,7 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
 #pragma unroll
     for (int g = 0; g < 2; ++g)
       acc_b[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bf[q % (BD + 1)][g], acc_b[g], 0, 0, 0);
-    if (q + FR < 36) fa[q % FR] = wb[(q + FR) * 64];
+    if (q + FR < 36) fa[q % FR] = load16(wb_buf, lane * 16, w0 + (q + FR) * 1024);
     __builtin_amdgcn_sched_barrier(0);
   }
 #undef HS_READ_B
@@ -998,14 +999,20 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = wave % KS, cw = wave / KS;
+  // the parameters of the prologue, all in one round trip
+  asm volatile("" ::"s"(p.in), "s"(p.wt_frag), "s"(p.run_in_bytes), "s"(p.run_w_bytes), "s"(p.cin_pitch), "s"(p.chunks_per_tap),
+               "s"(p.tiles_per_xcd), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.n_block), "s"(p.run_by_blk), "s"(p.run_nb_shift),
+               "s"(p.run.strip_w), "s"(p.run.rows), "s"(p.run.h), "s"(p.run.w), "s"(p.run.by_strip_w), "s"(p.run.by_h),
+               "s"(p.run.by_batch), "s"(p.run.by23_row));
   const uint32_t tile = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
-  if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
   const uint32_t nb = (uint32_t)p.n_block;                         // a power of two; tile order: see above
   const uint32_t t_blk = run_div31(tile, p.run_by_blk), in_blk = tile - t_blk * (uint32_t)p.tiles_m * nb;
   const int n0 = (int)(t_blk * nb + (in_blk & (nb - 1))) * C;
   const RunOrigin org = run_origin(p.run, in_blk >> p.run_nb_shift);
   const int rw = p.run.strip_w + 2, rp = run_row_pitch(p.run.strip_w);   // patch pixels, LDS halves per row
 
+  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes);
+  u32x4 first[PL];
   // ---- patch loader: pixel (tid + threads * i) / 8 of the patch: source offset in bytes (padding: reads as
   // zeros), LDS slot (beyond the patch: 128 bytes that nothing reads)
   int l_poff[PL], l_lds[PL];
@@ -1018,12 +1025,12 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
       const bool fits = prow < (uint32_t)p.run.rows, in = run_patch_pixel(p.run, org, prow, pcol, m) && fits;
       l_poff[i] = in ? (m * p.cin_pitch + (tid & 7) * 8) * 2 : kOutside;
       l_lds[i] = fits ? (int)prow * rp + (int)pcol * PITCH + (tid & 7) * 8 : LDS / 2 - 64 + (tid & 7) * 8;
+      first[i] = load16(in_buf, l_poff[i], 0);
       prow += (uint32_t)p.run.step_q;
       pcol += (uint32_t)p.run.step_r;
       if (pcol >= (uint32_t)rw) { pcol -= (uint32_t)rw; ++prow; }
     }
   }
-  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes);
   u32x4 st_p[PL];
 #define HS_LOAD_P(I_, CC_) st_p[I_] = load16(in_buf, l_poff[I_], (CC_) * 128);
 #define HS_HAND_P(V_, I_, B_) *reinterpret_cast<u32x4*>(&s_patch[(B_) * (LDS / 2) + l_lds[I_]]) = (V_);
@@ -1031,10 +1038,6 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
   // ---- prologue: loads of the first patch (and the second), of the weight ring, in the order of the loop below,
   // whose waits count the loads issued since
   const int n_cc = p.chunks_per_tap;                               // even
-  u32x4 first[PL];
-#pragma unroll
-  for (int i = 0; i < PL; ++i)
-    first[i] = load16(in_buf, l_poff[i], 0);
 #pragma unroll
   for (int i = 0; i < PL; ++i) HS_LOAD_P(i, 1)
   int wf = ((n0 / 32 + cw) * n_cc * 36 + ks * KK) * 1024;          // bytes from wt_frag on
@@ -1052,6 +1055,9 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
   int fpo[PG], o_m[PG];
 #pragma unroll
   for (int g = 0; g < PG; ++g) pixel(g, fpo[g], o_m[g]);
+  // (Only here: an exit further up would split the loads of the parameters into several round trips.  Beyond the last tile all
+  // of the above lies outside the buffers.)
+  if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
 #pragma unroll
   for (int i = 0; i < PL; ++i) HS_HAND_P(first[i], i, 0)
   __syncthreads();
@@ -1216,14 +1222,21 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = wave % KS, cw = wave / KS;
+  // the parameters of the prologue, all in one round trip
+  asm volatile("" ::"s"(p.in), "s"(p.wt_frag), "s"(p.run_in_bytes), "s"(p.run_w_bytes), "s"(p.cin_pitch), "s"(p.chunks_per_tap),
+               "s"(p.tiles_per_xcd), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.n_block), "s"(p.run_by_blk), "s"(p.run_nb_shift),
+               "s"(p.run.strip_w), "s"(p.run.rows), "s"(p.run.h), "s"(p.run.w), "s"(p.run.by_strip_w), "s"(p.run.by_h),
+               "s"(p.run.by_batch), "s"(p.run.by23_row), "s"(p.wt2_frag), "s"(p.run.pitch2), "s"(p.run.by_period), "s"(p.run.hin));
   const uint32_t tile = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
-  if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
   const uint32_t nb = (uint32_t)p.n_block;                         // a power of two; tile order: see above
   const uint32_t t_blk = run_div31(tile, p.run_by_blk), in_blk = tile - t_blk * (uint32_t)p.tiles_m * nb;
   const int n0 = (int)(t_blk * nb + (in_blk & (nb - 1))) * C;
   const RunOrigin org = run_origin(p.run, in_blk >> p.run_nb_shift);
   const int rw = 2 * p.run.strip_w + 1, rp = p.run.pitch2, odd = (p.run.strip_w + 1) * PITCH;   // odd: offset of a row's odd pixels
 
+  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes),
+                   w2_buf = buffer_of(p.wt2_frag, p.run_w_bytes / 9);
+  u32x4 first[PL];
   // ---- patch loader, as in k_conv3x3_run
   int l_poff[PL], l_lds[PL];
   {
@@ -1236,13 +1249,12 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
       const bool fits = prow < (uint32_t)p.run.rows, in = run2_patch_pixel(p.run, org, prow, pcol, m) && fits;
       l_poff[i] = in ? (m * p.cin_pitch + v) * 2 : kOutside;
       l_lds[i] = fits ? (int)prow * rp + (int)(pcol >> 1) * PITCH + (pcol & 1u ? odd : 0) + v : LDS / 2 - 64 + v;
+      first[i] = load16(in_buf, l_poff[i], 0);
       prow += (uint32_t)p.run.step_q;
       pcol += (uint32_t)p.run.step_r;
       if (pcol >= (uint32_t)rw) { pcol -= (uint32_t)rw; ++prow; }
     }
   }
-  const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes),
-                   w2_buf = buffer_of(p.wt2_frag, p.run_w_bytes / 9);
   u32x4 st_p[PL];
 #define HS_LOAD_P(I_, IT_) st_p[I_] = load16(in_buf, l_poff[I_], (IT_) * (VP * 16));
 #define HS_HAND_P(V_, I_, B_) *reinterpret_cast<u32x4*>(&s_patch[(B_) * (LDS / 2) + l_lds[I_]]) = (V_);
@@ -1254,9 +1266,6 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
   constexpr int WP = 36 * 1024 * KS / 2, WP2 = 4 * 1024 * KS / 2;                           // and from pair to pair
   int wf = (n0 / 32 + cw) * p.chunks_per_tap * 36 * 1024 + ks * 1024 - single * WI;
   int wf2 = (n0 / 32 + cw) * p.chunks_per_tap * 4 * 1024 + ks * 1024 - single * WI2;
-  u32x4 first[PL];
-#pragma unroll
-  for (int i = 0; i < PL; ++i) first[i] = load16(in_buf, l_poff[i], 0);
 #pragma unroll
   for (int i = 0; i < PL; ++i) HS_LOAD_P(i, min(1, n_it - 1))
   u32x4 fa[9], fb;
@@ -1270,6 +1279,9 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
     run2_pixel(p.run, org, 32 * g + r, row, col, o_m[g]);
     fpo[g] = (int)row * rp + (int)col * PITCH + h * 8 + ks * 16;
   }
+  // (Only here: an exit further up would split the loads of the parameters into several round trips.  Beyond the last tile all
+  // of the above lies outside the buffers.)
+  if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
 #pragma unroll
   for (int i = 0; i < PL; ++i) HS_HAND_P(first[i], i, single)
   __syncthreads();

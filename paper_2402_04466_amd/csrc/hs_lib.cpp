@@ -682,6 +682,10 @@ struct Builder {
     g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
     g.tiles_n = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
     g.tiles_per_xcd = (g.tiles_m + 7) / 8;
+    g.tiles_img = (uint32_t)(g.tiles_m / g.batch);
+    auto by = [](uint64_t d) { return (uint32_t)((((uint64_t)1 << 31) + d - 1) / d); };
+    g.by_tiles_img = by(g.tiles_img); g.by_tiles_x = by((uint64_t)g.tiles_x);
+    g.run_in_bytes = (uint32_t)(g.batch * g.hin * g.win * 128);
     g.wt_frag = d_w ? d_w + wa_off : nullptr;
     g.wt2_frag = d_w ? d_w + wb_off : nullptr;
     g.out = out->p; g.out_pitch = out->pitch;
