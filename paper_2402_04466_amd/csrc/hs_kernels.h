@@ -37,6 +37,7 @@ struct ResizeParams {
   const float* lut32;   // 256 entries
   const f16* lut16;     // 256 entries
   float rcp_dx, rcp_dy;         // 1/(2*wo), 1/(2*ho): division estimates
+  uint64_t* t_end;      // when the launch's last workgroup ended, on the device's constant-rate clock
   uint32_t d_magic, d_shift;    // floor(n / (4*wo*ho)) = mulhi(n, d_magic) >> d_shift for n < 2^31
 };
 KernelDesc describe(const ResizeParams& p);
@@ -166,6 +167,11 @@ struct PostRecord {           // written by the kernel into pinned host memory
   // (see PostParams) until then
   int32_t ticks[8];
 };
+// Ticks of the device's constant-rate clock from the ends of the first three stages (post: where stage 3 has a launch)
+// until the overlay's last workgroup, which writes them into pinned host memory.  (Events attached to the stages' last
+// kernels would say the same, but each of them leaves the queue idle for 4.6 us, since such a kernel ends with a release
+// to the host.)
+struct StageTicks { int64_t pre, infer, post; };
 // Stage 3.  Per cell (written by the kernel that computes the logits): heat = sigmoid(logit), mask =
 // logit > theta, both [batch][8][n], and kmap [batch][n] = the lowest channel whose mask is set, 0xff
 // if none (what the overlay draws).  Per channel (here, or in the overlay's launch): PostRecord.
@@ -179,6 +185,7 @@ struct PostParams {
   // the centre of tool k's argmax cell, cx = -1 when the tool is absent; NULL: not wanted
   int* marks;
   int wm, hm, wf, hf;            // map (n == wm*hm) and frame size, for the anchors
+  uint64_t* t_end;               // as in ResizeParams
 };
 KernelDesc describe(const PostParams& p);
 
@@ -196,7 +203,10 @@ struct OverlayLayer {
   float rcp_scale;                   // 1/scale
   // stage 3's channel maxima of this layer's network, found in the overlay's launch: logits
   // [batch][8][hm*wm] and the records [batch] (NULL: a launch of their own has found them)
-  const float* logits; PostRecord* rec; float theta; const uint64_t* t_stage2;
+  const float* logits; PostRecord* rec; float theta;
+  // ends of stages 1 to 3 on the device's clock (stage 3's where it has a launch), and where to put the ticks since
+  // (NULL: not wanted)
+  const uint64_t* t_stages; StageTicks* ticks;
   uint64_t glyph[9];                 // bit (5*row + col) of glyph g, col 0 = leftmost
 };
 struct OverlayParams {

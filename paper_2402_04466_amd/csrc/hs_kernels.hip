@@ -155,6 +155,7 @@ __global__ __launch_bounds__(512) void k_resize_norm(ResizeParams p) {
   }
 #undef HS_HAND_VEC
 #undef HS_FETCH_VEC
+  if (tid == 0 && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1) *p.t_end = wall_clock64();
 }
 
 static unsigned resize_block(const ResizeParams& p) {
@@ -1713,6 +1714,7 @@ __global__ __launch_bounds__(256) void k_postprocess(PostParams p) {
     mk[0] = bv > p.theta ? ((2 * ax + 1) * p.wf) / (2 * p.wm) : -1;
     mk[1] = bv > p.theta ? ((2 * ay + 1) * p.hf) / (2 * p.hm) : -1;
   }
+  if (threadIdx.x == 0 && k == 7 && img == p.batch - 1) *p.t_end = wall_clock64();
 }
 
 KernelDesc describe(const PostParams& p) {
@@ -1914,7 +1916,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
     const OverlayLayer& L = p.layer[LAYERS ? blockIdx.x >> 3 : 0];
     const int k = (int)(blockIdx.x & 7u), n = L.wm * L.hm;
     if (!L.rec) return;
-    const uint64_t t_stage2 = *L.t_stage2;
+    const uint64_t t_stage2 = L.t_stages[1];
     float bv;
     int bi;
     channel_maximum(L.logits + ((size_t)by * 8 + k) * n, n, L.theta, k, L.rec + by, bv, bi);
@@ -1924,7 +1926,18 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;          // groups per row, of the frame
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g_wave = ((int)blockIdx.x - p.n_max) * 256 + wave * 64;   // first group of the wavefront
-  if (g_wave >= total) return;
+  if (g_wave >= total) {
+    // The grid's last workgroup has no pixels: begun behind all others, it reads the clock for the stages' ends beside
+    // their work.  (At the end of the last workgroup that draws, the stores to the host put 1.8 us on a frame.)
+    const int l = (int)threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && l < nl && p.layer[LAYERS ? l : 0].ticks) {
+      const OverlayLayer& L = p.layer[LAYERS ? l : 0];
+      const uint64_t now = wall_clock64();
+      *L.ticks = StageTicks{(int64_t)(now - L.t_stages[0]), (int64_t)(now - L.t_stages[1]),
+                            (int64_t)(now - L.t_stages[2])};
+    }
+    return;
+  }
   const uint8_t* const src = p.src[by];
   uint8_t* const dst = p.dst[by];
   // rows of whole groups that butt against each other: the frame is one run of vectors
@@ -1996,7 +2009,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
 KernelDesc describe(const OverlayParams& p) {
   const unsigned groups = (unsigned)(((p.wf + 15) >> 4) * p.hf);
   const void* f = p.n_layers > 1 ? (const void*)k_overlay<true> : (const void*)k_overlay<false>;
-  return KernelDesc{f, dim3((groups + 255) / 256 + (unsigned)p.n_max, p.batch), dim3(256), 0};
+  return KernelDesc{f, dim3((groups + 255) / 256 + (unsigned)p.n_max + 1, p.batch), dim3(256), 0};   // 1: the clock
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -127,6 +127,10 @@ struct Slot {
   // the event that the overlay waits for: behind stage 3 where it has a launch of its own, else
   // behind stage 2
   hipEvent_t ev_stage3 = nullptr;
+  // Frames launched kernel by kernel take the stages' ends from `ticks`.  Their ev_infer / ev_stage3 only order streams,
+  // and are there (has_event) only where another stream waits for them at submit or is likely to later (order_behind).
+  bool stamped = false, has_event = true;
+  hipStream_t stream = nullptr;       // the frame's, up to stage 3
   // the event that says the frame has left the last stage: ev_overlay, or, for a member of a
   // group, the first member's (one overlay launch serves them all)
   hipEvent_t ev_done = nullptr;
@@ -140,6 +144,7 @@ struct Slot {
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   std::vector<hipGraphNode_t> resize_nodes;
+  StageTicks* ticks = nullptr; // pinned host memory, written by the overlay's kernel
   PostRecord* rec = nullptr;   // [batch], pinned host memory, written by the stage-3 kernel
   f16* d_netin = nullptr;      // [batch] padded images
   float* d_netin_f32 = nullptr;
@@ -1025,7 +1030,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
   const size_t n_map = (size_t)mh * mw;
   const int B = d->batch;
   struct SlotBuf { f16* netin; float* netin32; float* logits; float* heat; uint8_t* mask;
-                   uint8_t* kmap; int* marks; uint64_t* t_stage2; };
+                   uint8_t* kmap; int* marks; uint64_t* t_stages; };
   std::vector<SlotBuf> sb(depth);
   for (int i = 0; i < depth; ++i) {
     sb[i].netin = b.carve.take<f16>((size_t)B * ph * pw * 4);
@@ -1036,7 +1041,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     sb[i].mask = b.carve.take<uint8_t>(B * 8 * n_map);
     sb[i].kmap = b.carve.take<uint8_t>(B * n_map);
     sb[i].marks = d->annotate ? b.carve.take<int>((size_t)B * 16) : nullptr;
-    sb[i].t_stage2 = b.carve.take<uint64_t>(1);
+    sb[i].t_stages = b.carve.take<uint64_t>(3);
   }
   const size_t total = round_up_sz(b.carve.off, 256);
   if (bytes_out) *bytes_out = total;
@@ -1079,14 +1084,16 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
   const double theta_d = std::log((double)d->threshold / (1.0 - (double)d->threshold));
   int a_q8 = (int)lrint(256.0 * (double)d->alpha);
   a_q8 = std::max(0, std::min(256, a_q8));
-  HS_HIP(hipHostMalloc(&app->pinned, sizeof(PostRecord) * depth * B, hipHostMallocDefault));
-  std::memset(app->pinned, 0, sizeof(PostRecord) * depth * B);
+  const size_t pinned_bytes = (sizeof(PostRecord) * B + sizeof(StageTicks)) * depth;
+  HS_HIP(hipHostMalloc(&app->pinned, pinned_bytes, hipHostMallocDefault));
+  std::memset(app->pinned, 0, pinned_bytes);
   app->slots.resize(depth);
   for (int i = 0; i < depth; ++i) {
     Slot& s = app->slots[i];
     s.d_netin = sb[i].netin; s.d_netin_f32 = sb[i].netin32;
     s.d_logits = sb[i].logits; s.d_heat = sb[i].heat; s.d_mask = sb[i].mask;
     s.rec = (PostRecord*)app->pinned + (size_t)i * B;
+    s.ticks = (StageTicks*)((PostRecord*)app->pinned + (size_t)depth * B) + i;
     s.results.resize(B);
     {
       Op r;
@@ -1098,6 +1105,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       rp.dst32_img_stride = (size_t)3 * d->net_h * d->net_w;
       rp.wi = d->frame_w; rp.hi = d->frame_h; rp.wo = d->net_w; rp.ho = d->net_h;
       rp.dst = s.d_netin; rp.dst_w = pw; rp.pad_l = pad; rp.pad_t = pad;
+      rp.t_end = sb[i].t_stages;
       rp.dst_f32 = s.d_netin_f32; rp.lut32 = d_lut32; rp.lut16 = d_lut16;
       rp.rcp_dx = 1.0f / (2.0f * d->net_w); rp.rcp_dy = 1.0f / (2.0f * d->net_h);
       {
@@ -1126,7 +1134,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       logits = s.d_logits;
       w.theta = (float)theta_d;
       w.heat = s.d_heat; w.mask = s.d_mask; w.kmap = sb[i].kmap;
-      w.t_end = sb[i].t_stage2;
+      w.t_end = sb[i].t_stages + 1;
     };
     Op& lo = s.infer[b.logits_op];
     if (lo.fam == F_CONV) bind_logits(lo.conv, lo.conv.out_f32);
@@ -1157,7 +1165,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       Op p;
       p.fam = F_POST;
       p.post = PostParams{s.d_logits, (int)n_map, (float)theta_d, s.rec, B, sb[i].marks, mw, mh,
-                          d->frame_w, d->frame_h};
+                          d->frame_w, d->frame_h, sb[i].t_stages + 2};
       p.bytes = B * 8.0 * n_map * 4;
       s.post.push_back(p);
       s.maxima_with_overlay = !d->annotate;
@@ -1174,7 +1182,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       op.n_layers = 1;
       OverlayLayer& L = op.layer[0];
       L.kmap = sb[i].kmap; L.wm = mw; L.hm = mh;
-      L.logits = s.d_logits; L.theta = (float)theta_d; L.t_stage2 = sb[i].t_stage2;   // rec and n_max: per frame
+      L.logits = s.d_logits; L.theta = (float)theta_d; L.t_stages = sb[i].t_stages;   // rec, ticks and n_max: per frame
       L.rcp_wm = 1.0f / (float)mw;
       L.a = a_q8;
       L.marks = sb[i].marks;
@@ -1226,10 +1234,18 @@ static void completer_main(hs_app* app) {
     hipError_t e = hipEventSynchronize(s->ev_done);
     const uint64_t t_done = now_ns();
     float ms_pre = 0, ms_inf = 0, ms_post = 0;
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_done);
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_done);
-    if (s->maxima_rode) ms_post = std::max(0.0f, ms_inf - stage3_ms(*s, app->ctx->wall_clock_khz));
-    else if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_stage3, s->ev_done);
+    if (s->stamped) {
+      const float per_tick = 1.0f / (float)app->ctx->wall_clock_khz;
+      const float ms_max = s->maxima_rode ? stage3_ms(*s, app->ctx->wall_clock_khz) : 0.0f;
+      ms_inf = std::max((float)s->ticks->infer * per_tick, ms_max);   // (the drawing may end before the maxima)
+      ms_pre = ms_inf + (float)(s->ticks->pre - s->ticks->infer) * per_tick;
+      ms_post = s->maxima_rode ? ms_inf - ms_max : (float)s->ticks->post * per_tick;
+    } else {
+      if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_done);
+      if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_done);
+      if (s->maxima_rode) ms_post = std::max(0.0f, ms_inf - stage3_ms(*s, app->ctx->wall_clock_khz));
+      else if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_stage3, s->ev_done);
+    }
     auto back = [&](float ms) {
       const double ns = (double)ms * 1e6;
       return t_done - (uint64_t)std::max(0.0, ns);
@@ -1793,6 +1809,14 @@ static hs_status submit_stages(hs_app* app, const uint8_t* const* d_frames,
   return st;
 }
 
+// `stream` goes on behind `event` of frame `before`, which may be in flight; where that frame has no such event, behind
+// its overlay.
+static hs_status order_behind(hipStream_t stream, const Slot& before, hipEvent_t Slot::*event) {
+  if (before.stream == stream) return HS_OK;             // one queue: in order
+  HS_HIP(hipStreamWaitEvent(stream, before.has_event ? before.*event : before.ev_overlay, 0));
+  return HS_OK;
+}
+
 static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* const* d_frames,
                                 uint8_t* const* d_overlay_outs, uint64_t frame_id,
                                 uint64_t t_submit, bool own_overlay, Slot** slot_out,
@@ -1836,11 +1860,25 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   const bool maxima_here = s->maxima_with_overlay && !app->timing;
   s->overlay[0].overlay.layer[0].rec = maxima_here ? s->rec : nullptr;
   s->overlay[0].overlay.n_max = maxima_here ? 8 : 0;
+  hipStream_t ov_stream = app->s_overlay ? app->s_overlay : lane_stream;
+  s->stamped = !graph && !app->timing;
+  s->overlay[0].overlay.layer[0].ticks = s->stamped ? s->ticks : nullptr;
+  // An event on a stage's last kernel costs 4.6 us of its queue.  Whoever waits for this frame's stage 2 or 3: the overlay
+  // on another stream, a group's overlay, or the next frame in another lane if it comes while this one is in flight: at
+  // its recurrent cell, or where it follows a frame of its own lane in this stream.  A frame that comes alone has events
+  // for a recurrent cell only: for the next frame to wait for its overlay instead measured 2 to 4 % on twelve full-HD
+  // frames back to back, and an event recorded when that frame comes (4 us of host) 1.5 % on five applications.
+  const bool two_queues = app->lanes > 1 && app->s_lane[0] != app->s_lane[1];
+  const bool others_wait = !own_overlay || ov_stream != lane_stream || (two_queues && (!idle || s->wait_idx >= 0));
+  s->has_event = !s->stamped || others_wait;
+  s->stream = lane_stream;
+  auto event = [&](hipEvent_t e, bool wanted) { return !s->stamped || wanted ? e : nullptr; };
   if (!idle && app->lane_last_stream[s->lane] && app->lane_last_stream[s->lane] != lane_stream &&
       app->depth >= app->lanes) {
     Slot& same_lane =
         app->slots[(size_t)((s - app->slots.data()) + app->depth - app->lanes) % app->depth];
-    HS_HIP(hipStreamWaitEvent(lane_stream, same_lane.ev_stage3, 0));
+    st = order_behind(lane_stream, same_lane, &Slot::ev_stage3);
+    if (st != HS_OK) return st;
   }
   app->lane_last_stream[s->lane] = lane_stream;
   // the caller's producer (another stream) may still be writing the frames
@@ -1851,20 +1889,21 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
     HS_HIP(hipGraphExecKernelNodeSetParams(s->graph_exec, s->resize_nodes[0], &kp));
     HS_HIP(hipGraphLaunch(s->graph_exec, lane_stream));
   } else {
-    st = run_ops(app, s->pre, lane_stream, s->ev_pre);
+    st = run_ops(app, s->pre, lane_stream, event(s->ev_pre, false));
     if (st != HS_OK) return st;
-    if (s->wait_idx >= 0 && app->depth > 1) {
+    if (s->wait_idx >= 0 && app->depth > 1 && !idle) {
       // the recurrent cell waits for the previous frame's state update (other lane)
       Slot& before = app->slots[(size_t)((s - app->slots.data()) + app->depth - 1) % app->depth];
       st = run_ops(app, infer, lane_stream, nullptr, 0, (size_t)s->wait_idx);
       if (st != HS_OK) return st;
-      HS_HIP(hipStreamWaitEvent(lane_stream, before.ev_infer, 0));
-      st = run_ops(app, infer, lane_stream, s->ev_infer, (size_t)s->wait_idx);
+      st = order_behind(lane_stream, before, &Slot::ev_infer);
+      if (st != HS_OK) return st;
+      st = run_ops(app, infer, lane_stream, event(s->ev_infer, others_wait), (size_t)s->wait_idx);
     } else {
-      st = run_ops(app, infer, lane_stream, s->ev_infer);
+      st = run_ops(app, infer, lane_stream, event(s->ev_infer, others_wait));
     }
     if (st != HS_OK) return st;
-    if (!maxima_here) st = run_ops(app, s->post, lane_stream, s->ev_post);
+    if (!maxima_here) st = run_ops(app, s->post, lane_stream, event(s->ev_post, others_wait));
     if (st != HS_OK) return st;
   }
   if (graph) HS_HIP(hipEventRecord(s->ev_post, lane_stream));
@@ -1876,7 +1915,6 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
     *stream_out = lane_stream;
     return HS_OK;
   }
-  hipStream_t ov_stream = app->s_overlay ? app->s_overlay : lane_stream;
   if (ov_stream != lane_stream) HS_HIP(hipStreamWaitEvent(ov_stream, s->ev_stage3, 0));
   st = run_ops(app, s->overlay, ov_stream, s->ev_overlay);
   if (st != HS_OK) return st;

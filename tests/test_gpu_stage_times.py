@@ -68,3 +68,34 @@ def test_stage_three_of_a_group(hs, timed):
     finally:
         grp.close()
         hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("net,depth", [("tiny4", 2), ("resnet18_convlstm", 2), ("resnet18_convlstm", 3),
+                                       ("resnet18_convlstm", 4)])
+def test_frames_alone_and_in_flight(hs, net, depth):
+    """A frame that comes alone leaves the next one, in another lane, another event to wait for than a frame in flight
+    does: mixed, the stages end in order and the frames are those of a stream whose every frame comes alone."""
+    ctx = hs.hs_init(0)
+    mixed, alone = _app(hs, ctx, net, queue_depth=depth), _app(hs, ctx, net, queue_depth=depth)
+    runs = [1, 2, 1, min(3, depth), depth, 1, 2]
+    try:
+        frames = list(si.uniform_frames(sum(runs), 360, 640, 9))
+        d_in = [mixed.upload_frame(f) for f in frames]
+        got, want = [mixed.new_output() for _ in frames], [alone.new_output() for _ in frames]
+        for i, out in enumerate(want):
+            assert alone.submit_batch([d_in[i]], [out], i) == hs.HS_OK
+            alone.wait_batch()
+        i = 0
+        for n in runs:
+            print(f"[stage-times] {net} depth {depth}: {n} frames from {i}", flush=True)
+            for j in range(i, i + n):
+                assert mixed.submit_batch([d_in[j]], [got[j]], j) == hs.HS_OK
+            for _ in range(n):
+                _check(mixed.wait_batch())
+            i += n
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert (a == b).all(), i
+    finally:
+        mixed.close()
+        alone.close()
+        hs.hs_shutdown(ctx)
