@@ -55,9 +55,11 @@ __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
   return r;
 }
 
-// Block size: 256..512 threads, chosen by the host so that the passes over the output row are as
-// full as possible (854 pixels: two passes of 448 threads instead of four of 256) and that a
-// source row is at most kResizeVecs 16-byte vectors per thread.  The row loads are the first
+// Block size: 256..512 threads, chosen by the host so that a source row is at most kResizeVecs 16-byte vectors per
+// thread.  A launch of one round of workgroups takes the size whose passes over the output row are as full as possible
+// (one 854 x 480 frame: two passes of 448 threads 4.8 us, four of 256 5.1).  A longer one takes the smallest: what counts
+// there is how many rows a CU has under way while each waits for its source (sixteen 416 x 240 frames 11.5 -> 9.6 us,
+// twelve 854 x 480 24.2 -> 23.2; of 192 and 128 threads, 10.7 and 27 to 29).  The row loads are the first
 // thing a workgroup issues: the lookup tables and the row arithmetic are set up behind them.
 constexpr int kResizeVecs = 4;
 template <int NV>   // 16-byte vectors per thread and source row: 1, 2 or 4
@@ -161,9 +163,11 @@ __global__ __launch_bounds__(512) void k_resize_norm(ResizeParams p) {
 static unsigned resize_block(const ResizeParams& p) {
   const unsigned row_vecs = (unsigned)((3 * p.wi + 15) >> 4);
   const unsigned t_min = std::max(256u, (row_vecs + kResizeVecs - 1) / kResizeVecs);
+  const bool one_round = (unsigned)p.ho * (unsigned)p.batch <= 4 * 256;   // four workgroups of 448 threads on every CU
   unsigned best = 0;
   for (unsigned t = 256; t <= 512; t += 64) {
     if (t < t_min) continue;
+    if (!one_round) return t;
     if (!best || (p.wo + t - 1) / t * t < (p.wo + best - 1) / best * best) best = t;
   }
   return best ? best : 512;
