@@ -146,3 +146,32 @@ def test_small_network_of_many_tiles_matches_the_oracle(hs):
     finally:
         s.close()
         hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("frame_w,frame_h,net_w,net_h,batch", [
+    (64, 48, 130, 128, 8),       # 1024 rows: the longest launch of one round
+    (64, 48, 130, 129, 8),       # beyond it: 256 threads
+    (1367, 40, 300, 80, 13),     # rows of 257 vectors
+    (5466, 40, 70, 80, 13),      # 1025 vectors: more than four for each of 256 threads, 320 are taken
+])
+def test_resize_of_many_rows_matches_the_oracle(hs, frame_w, frame_h, net_w, net_h, batch):
+    from paper_2402_04466_amd.harness import AppStream
+    blob = si.he_normal_blob(si.TINY4_LAYERS, 12)
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=frame_w, frame_h=frame_h, net_w=net_w, net_h=net_h, blob=blob,
+                  palette=si.DEFAULT_PALETTE, queue_depth=2, batch=batch)
+    try:
+        print(f"[resize-rows] {frame_w}x{frame_h} -> {net_w}x{net_h} batch {batch}", flush=True)
+        host = [si.uniform_frames(1, frame_h, frame_w, 80 + j)[0] for j in range(batch)]
+        d_in, d_out = [s.upload_frame(f) for f in host], [s.new_output() for _ in host]
+        assert s.submit_batch(d_in, d_out, 0) == hs.HS_OK
+        rs = s.wait_batch()
+        lut = oracle.normalize_lut(0.5, 0.25, fp16=True)
+        for j in (0, batch - 1):
+            o32, _ = make_oracles("tiny4", blob, net_w, net_h, True, si.DEFAULT_PALETTE)
+            got = s.fetch(rs[j], d_out[j])["net_input"].astype(np.float32)
+            assert np.array_equal(got[..., :3], lut[o32.process(host[j])["resized"]]), j
+            assert np.all(got[..., 3] == 0), j
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
