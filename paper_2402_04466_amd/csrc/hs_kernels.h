@@ -37,7 +37,7 @@ struct ResizeParams {
   const float* lut32;   // 256 entries
   const f16* lut16;     // 256 entries
   float rcp_dx, rcp_dy;         // 1/(2*wo), 1/(2*ho): division estimates
-  uint64_t* t_end;      // when the launch's last workgroup ended, on the device's constant-rate clock
+  uint64_t* t_end;      // the launch's end, on the device's constant-rate clock, as its highest-numbered workgroup sees it
   uint32_t d_magic, d_shift;    // floor(n / (4*wo*ho)) = mulhi(n, d_magic) >> d_shift for n < 2^31
 };
 KernelDesc describe(const ResizeParams& p);
@@ -167,15 +167,17 @@ struct PostRecord {           // written by the kernel into pinned host memory
   // (see PostParams) until then
   int32_t ticks[8];
 };
-// Ticks of the device's constant-rate clock from the ends of the first three stages (post: where stage 3 has a launch)
-// until the overlay's last workgroup, which writes them into pinned host memory.  (Events attached to the stages' last
-// kernels would say the same, but each of them leaves the queue idle for 4.6 us, since such a kernel ends with a release
-// to the host.)
-struct StageTicks { int64_t pre, infer, post; };
+// The ends of the stages on the device's constant-rate clock, in pinned host memory, written by the overlay's launch
+// (post: where stage 3 has a launch; drawn: where wanted).  drawn is the launch's end as its highest-numbered workgroup
+// sees it ahead of its last stores.  (Events attached to the stages' last kernels would say the same, but each of them
+// leaves the queue idle for 4.6 us, since such a kernel ends with a release to the host; one for the overlay's begin, for
+// its length, leaves it idle for 14.)
+struct StageStamps { uint64_t pre, infer, post, drawn; };
 // Stage 3.  Per cell (written by the kernel that computes the logits): heat = sigmoid(logit), mask =
 // logit > theta, both [batch][8][n], and kmap [batch][n] = the lowest channel whose mask is set, 0xff
 // if none (what the overlay draws).  Per channel (here, or in the overlay's launch): PostRecord.
-// t_end: when that kernel's last workgroup ended, on the device's constant-rate clock (one for all XCDs).
+// t_end: that kernel's end, on the device's constant-rate clock (one for all XCDs), as its highest-numbered workgroup sees
+// it.
 struct PostParams {
   const float* logits; int n;    // [batch][8][n]
   float theta;                   // logit threshold
@@ -204,9 +206,9 @@ struct OverlayLayer {
   // stage 3's channel maxima of this layer's network, found in the overlay's launch: logits
   // [batch][8][hm*wm] and the records [batch] (NULL: a launch of their own has found them)
   const float* logits; PostRecord* rec; float theta;
-  // ends of stages 1 to 3 on the device's clock (stage 3's where it has a launch), and where to put the ticks since
-  // (NULL: not wanted)
-  const uint64_t* t_stages; StageTicks* ticks;
+  // ends of stages 1 to 3 on the device's clock (stage 3's where it has a launch), and where the host wants them (NULL:
+  // nowhere)
+  const uint64_t* t_stages; StageStamps* stamps;
   uint64_t glyph[9];                 // bit (5*row + col) of glyph g, col 0 = leftmost
 };
 struct OverlayParams {
@@ -214,8 +216,9 @@ struct OverlayParams {
   int batch; size_t pitch; int wf, hf;
   float rcp_gpr, rcp_hf, rcp_wf;     // 1/ceil(wf/16), 1/hf, 1/wf (ceil(wf/16)*hf below 2^31)
   int n_layers;                      // layers drawn in order, each over the one before
-  int n_max;                         // workgroups per image ahead of the drawing ones: 8 * n_layers
+  int n_max;                         // workgroups per image between the first and the drawing ones: 8 * n_layers
                                      // when some layer has a rec, else 0
+  int stamp_end;                     // layer[0].stamps->drawn is wanted
   OverlayLayer layer[kMaxLayers];
 };
 KernelDesc describe(const OverlayParams& p);

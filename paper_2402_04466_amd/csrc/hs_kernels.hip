@@ -1737,7 +1737,8 @@ KernelDesc describe(const PostParams& p) {
 // the pixels only their bytes are stored, so the padding between rows stays what it was.  (Those
 // groups used to go pixel by pixel: one such lane held up its wavefront for 45 byte loads, 54 us
 // instead of 11 for four 1279 x 719 frames with annotations.)
-// The first n_max workgroups of an image find stage 3's channel maxima (see channel_maximum).
+// Workgroup 0 of an image hands the host the stages' ends, the next n_max find stage 3's channel maxima (see
+// channel_maximum).
 // =============================================================================================
 // One layer of stage 4 applied to a group of 16 pixels held in registers (w[0..11], word j starts
 // with channel j mod 3): blend of the layer's channel map, then its annotations.
@@ -1916,9 +1917,20 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   __shared__ u32x4 s_x[4][192];
   const int by = (int)blockIdx.y;                                // image of the batch
   const int nl = LAYERS ? p.n_layers : 1;
-  if ((int)blockIdx.x < p.n_max) {                               // eight workgroups per layer
-    const OverlayLayer& L = p.layer[LAYERS ? blockIdx.x >> 3 : 0];
-    const int k = (int)(blockIdx.x & 7u), n = L.wm * L.hm;
+  const int b = (int)blockIdx.x - 1;
+  if (b < 0) {                                                   // (first, so that its stores to the host end beside the drawing)
+    const int l = (int)threadIdx.x;
+    if (by == 0 && l < nl && p.layer[LAYERS ? l : 0].stamps) {
+      const OverlayLayer& L = p.layer[LAYERS ? l : 0];
+      L.stamps->pre = L.t_stages[0];
+      L.stamps->infer = L.t_stages[1];
+      L.stamps->post = L.t_stages[2];
+    }
+    return;
+  }
+  if (b < p.n_max) {                                             // eight workgroups per layer
+    const OverlayLayer& L = p.layer[LAYERS ? b >> 3 : 0];
+    const int k = b & 7, n = L.wm * L.hm;
     if (!L.rec) return;
     const uint64_t t_stage2 = L.t_stages[1];
     float bv;
@@ -1929,19 +1941,8 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   }
   const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;          // groups per row, of the frame
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g_wave = ((int)blockIdx.x - p.n_max) * 256 + wave * 64;   // first group of the wavefront
-  if (g_wave >= total) {
-    // The grid's last workgroup has no pixels: begun behind all others, it reads the clock for the stages' ends beside
-    // their work.  (At the end of the last workgroup that draws, the stores to the host put 1.8 us on a frame.)
-    const int l = (int)threadIdx.x;
-    if (blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && l < nl && p.layer[LAYERS ? l : 0].ticks) {
-      const OverlayLayer& L = p.layer[LAYERS ? l : 0];
-      const uint64_t now = wall_clock64();
-      *L.ticks = StageTicks{(int64_t)(now - L.t_stages[0]), (int64_t)(now - L.t_stages[1]),
-                            (int64_t)(now - L.t_stages[2])};
-    }
-    return;
-  }
+  const int g_wave = (b - p.n_max) * 256 + wave * 64;            // first group of the wavefront
+  if (g_wave >= total) return;
   const uint8_t* const src = p.src[by];
   uint8_t* const dst = p.dst[by];
   // rows of whole groups that butt against each other: the frame is one run of vectors
@@ -1997,6 +1998,9 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // The launch's end as its last workgroup sees it, noted ahead of the pixels' stores, whose way to memory hides the
+  // stamp's to the host.  (Behind them it puts 1.8 us on a frame.)
+  if (p.stamp_end && blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && threadIdx.x == 0) p.layer[0].stamps->drawn = wall_clock64();
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     const u32x4 o = s_x[wave][64 * j + lane];
@@ -2013,7 +2017,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
 KernelDesc describe(const OverlayParams& p) {
   const unsigned groups = (unsigned)(((p.wf + 15) >> 4) * p.hf);
   const void* f = p.n_layers > 1 ? (const void*)k_overlay<true> : (const void*)k_overlay<false>;
-  return KernelDesc{f, dim3((groups + 255) / 256 + (unsigned)p.n_max + 1, p.batch), dim3(256), 0};   // 1: the clock
+  return KernelDesc{f, dim3(1 + (unsigned)p.n_max + (groups + 255) / 256, p.batch), dim3(256), 0};
 }
 
 // ---------------------------------------------------------------------------------------------

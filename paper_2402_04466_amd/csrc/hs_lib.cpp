@@ -127,8 +127,9 @@ struct Slot {
   // the event that the overlay waits for: behind stage 3 where it has a launch of its own, else
   // behind stage 2
   hipEvent_t ev_stage3 = nullptr;
-  // Frames launched kernel by kernel take the stages' ends from `ticks`.  Their ev_infer / ev_stage3 only order streams,
-  // and are there (has_event) only where another stream waits for them at submit or is likely to later (order_behind).
+  // Frames launched kernel by kernel take the stages' ends from `stamps`.  Their ev_infer / ev_stage3 order streams, and
+  // are there only where another stream waits for them at submit or is likely to later (order_behind); ev_stage3
+  // (has_event) also ties the device's clock to the frame's end.
   bool stamped = false, has_event = true;
   hipStream_t stream = nullptr;       // the frame's, up to stage 3
   // the event that says the frame has left the last stage: ev_overlay, or, for a member of a
@@ -144,7 +145,7 @@ struct Slot {
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   std::vector<hipGraphNode_t> resize_nodes;
-  StageTicks* ticks = nullptr; // pinned host memory, written by the overlay's kernel
+  StageStamps* stamps = nullptr; // pinned host memory, written by the overlay's kernel
   PostRecord* rec = nullptr;   // [batch], pinned host memory, written by the stage-3 kernel
   f16* d_netin = nullptr;      // [batch] padded images
   float* d_netin_f32 = nullptr;
@@ -1084,7 +1085,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
   const double theta_d = std::log((double)d->threshold / (1.0 - (double)d->threshold));
   int a_q8 = (int)lrint(256.0 * (double)d->alpha);
   a_q8 = std::max(0, std::min(256, a_q8));
-  const size_t pinned_bytes = (sizeof(PostRecord) * B + sizeof(StageTicks)) * depth;
+  const size_t pinned_bytes = (sizeof(PostRecord) * B + sizeof(StageStamps)) * depth;
   HS_HIP(hipHostMalloc(&app->pinned, pinned_bytes, hipHostMallocDefault));
   std::memset(app->pinned, 0, pinned_bytes);
   app->slots.resize(depth);
@@ -1093,7 +1094,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     s.d_netin = sb[i].netin; s.d_netin_f32 = sb[i].netin32;
     s.d_logits = sb[i].logits; s.d_heat = sb[i].heat; s.d_mask = sb[i].mask;
     s.rec = (PostRecord*)app->pinned + (size_t)i * B;
-    s.ticks = (StageTicks*)((PostRecord*)app->pinned + (size_t)depth * B) + i;
+    s.stamps = (StageStamps*)((PostRecord*)app->pinned + (size_t)depth * B) + i;
     s.results.resize(B);
     {
       Op r;
@@ -1182,7 +1183,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       op.n_layers = 1;
       OverlayLayer& L = op.layer[0];
       L.kmap = sb[i].kmap; L.wm = mw; L.hm = mh;
-      L.logits = s.d_logits; L.theta = (float)theta_d; L.t_stages = sb[i].t_stages;   // rec, ticks and n_max: per frame
+      L.logits = s.d_logits; L.theta = (float)theta_d; L.t_stages = sb[i].t_stages;   // rec, stamps and n_max: per frame
       L.rcp_wm = 1.0f / (float)mw;
       L.a = a_q8;
       L.marks = sb[i].marks;
@@ -1221,6 +1222,13 @@ static float stage3_ms(const Slot& s, int khz) {
   return (float)ticks / (float)khz;
 }
 
+// From a stage's stamp, in the workgroup that ends last, until the event on that launch: events see a launch 0.8 to 1.0 us
+// longer, at both ends together, than its workgroups' stamps do.
+constexpr float kStampToEventMs = 0.0005f;
+// From StageStamps::drawn until the overlay's end.  Against the event behind stage 2, in plain frames of 64 x 48 to
+// 1920 x 1080 pixels, sixteen of 320 x 180, two of 2048 x 1024: medians of 0.1 to 2.1 us.
+constexpr float kDrawnToEndMs = 0.001f;
+
 static void completer_main(hs_app* app) {
   (void)hipSetDevice(app->ctx->device);
   for (;;) {
@@ -1235,11 +1243,14 @@ static void completer_main(hs_app* app) {
     const uint64_t t_done = now_ns();
     float ms_pre = 0, ms_inf = 0, ms_post = 0;
     if (s->stamped) {
-      const float per_tick = 1.0f / (float)app->ctx->wall_clock_khz;
-      const float ms_max = s->maxima_rode ? stage3_ms(*s, app->ctx->wall_clock_khz) : 0.0f;
-      ms_inf = std::max((float)s->ticks->infer * per_tick, ms_max);   // (the drawing may end before the maxima)
-      ms_pre = ms_inf + (float)(s->ticks->pre - s->ticks->infer) * per_tick;
-      ms_post = s->maxima_rode ? ms_inf - ms_max : (float)s->ticks->post * per_tick;
+      const StageStamps& t = *s->stamps;
+      auto span = [&](uint64_t from, uint64_t to) { return (float)(int64_t)(to - from) / (float)app->ctx->wall_clock_khz; };
+      float ms = 0;                      // from the stamp of ev_stage3's stage on
+      if (s->has_event && e == hipSuccess) e = hipEventElapsedTime(&ms, s->ev_stage3, s->ev_done);
+      ms += s->has_event ? kStampToEventMs : span(t.infer, t.drawn) + kDrawnToEndMs;
+      ms_post = s->maxima_rode ? std::max(0.0f, ms - stage3_ms(*s, app->ctx->wall_clock_khz)) : ms;
+      ms_inf = s->maxima_rode ? ms : ms + span(t.infer, t.post);
+      ms_pre = ms_inf + span(t.pre, t.infer);
     } else {
       if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_done);
       if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_done);
@@ -1809,8 +1820,8 @@ static hs_status submit_stages(hs_app* app, const uint8_t* const* d_frames,
   return st;
 }
 
-// `stream` goes on behind `event` of frame `before`, which may be in flight; where that frame has no such event, behind
-// its overlay.
+// `stream` goes on behind `event` (ev_stage3, or at a recurrent cell ev_infer) of frame `before`, which may be in flight;
+// where that frame has no such event, behind its overlay.
 static hs_status order_behind(hipStream_t stream, const Slot& before, hipEvent_t Slot::*event) {
   if (before.stream == stream) return HS_OK;             // one queue: in order
   HS_HIP(hipStreamWaitEvent(stream, before.has_event ? before.*event : before.ev_overlay, 0));
@@ -1862,7 +1873,7 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   s->overlay[0].overlay.n_max = maxima_here ? 8 : 0;
   hipStream_t ov_stream = app->s_overlay ? app->s_overlay : lane_stream;
   s->stamped = !graph && !app->timing;
-  s->overlay[0].overlay.layer[0].ticks = s->stamped ? s->ticks : nullptr;
+  s->overlay[0].overlay.layer[0].stamps = s->stamped ? s->stamps : nullptr;
   // An event on a stage's last kernel costs 4.6 us of its queue.  Whoever waits for this frame's stage 2 or 3: the overlay
   // on another stream, a group's overlay, or the next frame in another lane if it comes while this one is in flight: at
   // its recurrent cell, or where it follows a frame of its own lane in this stream.  A frame that comes alone has events
@@ -1870,7 +1881,14 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   // frames back to back, and an event recorded when that frame comes (4 us of host) 1.5 % on five applications.
   const bool two_queues = app->lanes > 1 && app->s_lane[0] != app->s_lane[1];
   const bool others_wait = !own_overlay || ov_stream != lane_stream || (two_queues && (!idle || s->wait_idx >= 0));
-  s->has_event = !s->stamped || others_wait;
+  // The one behind stage 3 also ties the stages' stamps, on the device's clock, to the frame's end.  Without it they are
+  // tied to what the overlay's last workgroup sees of that end (kDrawnToEndMs), which serves while the workgroups (4096
+  // pixels each) run side by side on the whole device and take equally long.  With more of them it is up to 7 us early (a
+  // plain 7680 x 4320 frame), with annotations up to 11 (320 x 240): such frames have the event, and pay for it.
+  const bool even_drawing =
+      !app->desc.annotate && !app->partitioned && (double)B * app->desc.frame_w * app->desc.frame_h <= 1024 * 4096.0;
+  s->has_event = !s->stamped || others_wait || !even_drawing;
+  s->overlay[0].overlay.stamp_end = s->stamped && !s->has_event;
   s->stream = lane_stream;
   auto event = [&](hipEvent_t e, bool wanted) { return !s->stamped || wanted ? e : nullptr; };
   if (!idle && app->lane_last_stream[s->lane] && app->lane_last_stream[s->lane] != lane_stream &&
@@ -1898,12 +1916,12 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
       if (st != HS_OK) return st;
       st = order_behind(lane_stream, before, &Slot::ev_infer);
       if (st != HS_OK) return st;
-      st = run_ops(app, infer, lane_stream, event(s->ev_infer, others_wait), (size_t)s->wait_idx);
+      st = run_ops(app, infer, lane_stream, event(s->ev_infer, maxima_here ? s->has_event : others_wait), (size_t)s->wait_idx);
     } else {
-      st = run_ops(app, infer, lane_stream, event(s->ev_infer, others_wait));
+      st = run_ops(app, infer, lane_stream, event(s->ev_infer, maxima_here ? s->has_event : others_wait));
     }
     if (st != HS_OK) return st;
-    if (!maxima_here) st = run_ops(app, s->post, lane_stream, event(s->ev_post, others_wait));
+    if (!maxima_here) st = run_ops(app, s->post, lane_stream, event(s->ev_post, s->has_event));
     if (st != HS_OK) return st;
   }
   if (graph) HS_HIP(hipEventRecord(s->ev_post, lane_stream));
@@ -2208,6 +2226,7 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   };
   if (st0 != HS_OK) { set_error("%s", err0.text); return fail_all(st0); }
   op.n_max = 0;
+  op.stamp_end = 0;        // (members' stages have events)
   for (size_t i = 0; i < n; ++i) {
     op.layer[i] = slot[i]->overlay[0].overlay.layer[0];
     if (op.layer[i].rec) op.n_max = 8 * (int)n;

@@ -99,3 +99,59 @@ def test_frames_alone_and_in_flight(hs, net, depth):
         mixed.close()
         alone.close()
         hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("frame_w,frame_h,batch,depth,mode,annotate", [
+    (1920, 1080, 1, 2, "eager", False),    # drawn by workgroups that are all there at once
+    (1920, 1080, 2, 2, "eager", False),
+    (1920, 1080, 1, 2, "eager", True),
+    (320, 240, 1, 2, "eager", True),       # a few workgroups, of which those that paint take far longer
+    (7680, 4320, 1, 2, "eager", False),    # and in many rounds
+    (7680, 4320, 1, 2, "eager", True),
+    (7680, 4320, 1, 3, "eager", False),    # the overlay on a stream of its own
+    (3840, 2160, 4, 2, "eager", True),
+    (7680, 4320, 1, 2, "graph", True),
+])
+def test_the_last_stage_is_as_long_as_the_drawing(hs, frame_w, frame_h, batch, depth, mode, annotate):
+    """What lies between the ends of the stages before the overlay and the frame's end is the overlay kernel, as kernel
+    timing measures it.  Allowed: a fifth of it (clocks and bandwidth differ from run to run), 2 us for the stamps and, above
+    it, 12 us for the gaps between launches and events."""
+    from paper_2402_04466_amd.harness import AppStream
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=frame_w, frame_h=frame_h, net_w=128, net_h=96, batch=batch,
+                  queue_depth=depth, blob=si.he_normal_blob(si.TINY4_LAYERS, 5), palette=si.DEFAULT_PALETTE,
+                  glyphs=si.DEFAULT_GLYPHS if annotate else None)
+    try:
+        hs.hs_set_launch_mode(s.app, hs.HS_LAUNCH_GRAPH if mode == "graph" else hs.HS_LAUNCH_EAGER)
+        frames = list(si.uniform_frames(batch, frame_h, frame_w, 6))
+        d_in, d_out = [s.upload_frame(f) for f in frames], [s.new_output() for _ in frames]
+
+        def step(i):
+            assert s.submit_batch(d_in, d_out, i) == hs.HS_OK
+            return s.wait_batch()
+        for i in range(4):
+            step(i)
+        hs.hs_set_kernel_timing(s.app, True)
+        for i in range(8):
+            step(4 + i)
+        times = {k["name"]: 1e3 * k["total_ms"] / 8 for k in hs.hs_get_kernel_times(s.app)}
+        hs.hs_set_kernel_timing(s.app, False)
+        draw = times["overlay"]
+        after = {"pre": [], "infer": [], "post": []}
+        for i in range(9):
+            r = step(12 + i)[0]
+            _check([r])
+            for k, t in (("pre", r.t_pre_done_ns), ("infer", r.t_infer_done_ns), ("post", r.t_post_done_ns)):
+                after[k].append((r.t_overlay_done_ns - t) / 1e3)
+        after = {k: sorted(v)[4] for k, v in after.items()}
+        print(f"[stage-times] {frame_w}x{frame_h} {mode} batch {batch} depth {depth} annotate {annotate}: overlay kernel "
+              f"{draw:.1f} us, ends before the frame's {after}, kernels {times}", flush=True)
+        assert 0.8 * draw - 2 <= after["infer"] <= 1.2 * draw + times["postprocess"] + 12
+        assert after["pre"] - after["infer"] <= 1.2 * times["conv_mfma"] + 12
+        if annotate:                                      # stage 3 has a launch of its own, the drawing follows it
+            assert 0.8 * draw - 2 <= after["post"] <= 1.2 * draw + 12
+        elif draw > 25:                                   # the maxima are found by the launch's first workgroups
+            assert after["post"] >= 0.3 * draw
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
