@@ -612,7 +612,7 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
   u32x4 fa[FR];
 #pragma unroll
   for (int q = 0; q < FR; ++q) fa[q] = load16(wa_buf, lane * 16, w0 + q * 1024);
-  if (tm >= (uint32_t)p.tiles_m) return;    // (only here: see k_conv3x3_run)
+  if (tm >= (uint32_t)p.tiles_m) return;    // (only here: see k_conv3x3_run; its pixels lie behind the buffer, the weights are every tile's)
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int v = tid + 256 * i;
@@ -1010,10 +1010,9 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
                "s"(p.run.strip_w), "s"(p.run.rows), "s"(p.run.h), "s"(p.run.w), "s"(p.run.by_strip_w), "s"(p.run.by_h),
                "s"(p.run.by_batch), "s"(p.run.by23_row));
   const uint32_t tile = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
-  const uint32_t nb = (uint32_t)p.n_block;                         // a power of two; tile order: see above
-  const uint32_t t_blk = run_div31(tile, p.run_by_blk), in_blk = tile - t_blk * (uint32_t)p.tiles_m * nb;
-  const int n0 = (int)(t_blk * nb + (in_blk & (nb - 1))) * C;
-  const RunOrigin org = run_origin(p.run, in_blk >> p.run_nb_shift);
+  const RunTile rt = run_tile(tile, p.tiles_m, p.tiles_n, p.n_block, p.run_nb_shift, p.run_by_blk);   // tile order: see above
+  const int n0 = (int)rt.channels * C;
+  const RunOrigin org = run_origin(p.run, rt.run);
   const int rw = p.run.strip_w + 2, rp = run_row_pitch(p.run.strip_w);   // patch pixels, LDS halves per row
 
   const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes);
@@ -1061,7 +1060,7 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
 #pragma unroll
   for (int g = 0; g < PG; ++g) pixel(g, fpo[g], o_m[g]);
   // (Only here: an exit further up would split the loads of the parameters into several round trips.  Beyond the last tile all
-  // of the above lies outside the buffers.)
+  // of the above is the last tile's.)
   if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
 #pragma unroll
   for (int i = 0; i < PL; ++i) HS_HAND_P(first[i], i, 0)
@@ -1233,10 +1232,9 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
                "s"(p.run.strip_w), "s"(p.run.rows), "s"(p.run.h), "s"(p.run.w), "s"(p.run.by_strip_w), "s"(p.run.by_h),
                "s"(p.run.by_batch), "s"(p.run.by23_row), "s"(p.wt2_frag), "s"(p.run.pitch2), "s"(p.run.by_period), "s"(p.run.hin));
   const uint32_t tile = (blockIdx.x & 7u) * (uint32_t)p.tiles_per_xcd + (blockIdx.x >> 3);
-  const uint32_t nb = (uint32_t)p.n_block;                         // a power of two; tile order: see above
-  const uint32_t t_blk = run_div31(tile, p.run_by_blk), in_blk = tile - t_blk * (uint32_t)p.tiles_m * nb;
-  const int n0 = (int)(t_blk * nb + (in_blk & (nb - 1))) * C;
-  const RunOrigin org = run_origin(p.run, in_blk >> p.run_nb_shift);
+  const RunTile rt = run_tile(tile, p.tiles_m, p.tiles_n, p.n_block, p.run_nb_shift, p.run_by_blk);   // tile order: see above
+  const int n0 = (int)rt.channels * C;
+  const RunOrigin org = run_origin(p.run, rt.run);
   const int rw = 2 * p.run.strip_w + 1, rp = p.run.pitch2, odd = (p.run.strip_w + 1) * PITCH;   // odd: offset of a row's odd pixels
 
   const BufferRsrc in_buf = buffer_of(p.in, p.run_in_bytes), w_buf = buffer_of(p.wt_frag, p.run_w_bytes),
@@ -1285,7 +1283,7 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
     fpo[g] = (int)row * rp + (int)col * PITCH + h * 8 + ks * 16;
   }
   // (Only here: an exit further up would split the loads of the parameters into several round trips.  Beyond the last tile all
-  // of the above lies outside the buffers.)
+  // of the above is the last tile's.)
   if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
 #pragma unroll
   for (int i = 0; i < PL; ++i) HS_HAND_P(first[i], i, single)

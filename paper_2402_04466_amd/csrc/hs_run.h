@@ -50,6 +50,20 @@ __host__ __device__ __forceinline__ uint32_t run_div23(uint32_t n, uint32_t by) 
   return run_mul24(n, by) >> 23;
 }
 
+// Workgroup `tile` of a launch of tiles_m runs x tiles_n channel tiles, in blocks of n_block = 1 << nb_shift channel tiles
+// (by_blk: reciprocal of tiles_m * n_block): its run, its channel tile.  The surplus workgroups of a grid that is padded to
+// whole XCDs get the last tile, so that what they load before they leave lies inside the layer's tensors.
+struct RunTile {
+  uint32_t run, channels;
+};
+__host__ __device__ __forceinline__ RunTile run_tile(uint32_t tile, int tiles_m, int tiles_n, int n_block, int nb_shift,
+                                                     uint32_t by_blk) {
+  const uint32_t nb = (uint32_t)n_block, last = (uint32_t)(tiles_m * tiles_n) - 1;
+  tile = tile < last ? tile : last;
+  const uint32_t blk = run_div31(tile, by_blk), in_blk = tile - blk * (uint32_t)tiles_m * nb;
+  return RunTile{in_blk >> nb_shift, blk * nb + (in_blk & (nb - 1))};
+}
+
 // Where tile `tile` starts: row `y` of column `img` (image) of strip `strip`, `rem` pixels into the row.
 struct RunOrigin {
   uint32_t rem, y, strip, img;

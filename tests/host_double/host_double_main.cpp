@@ -27,11 +27,11 @@ struct Program {   // what a program has in hand before it creates an applicatio
   std::vector<float> weights;
   void* workspace = nullptr;
   std::vector<uint8_t> frame, out;
-  explicit Program(int net, int batch = 1) : frame(64 * 48 * 3 + 16), out(64 * 48 * 3 + 16) {
+  explicit Program(int net, int batch = 1, int net_w = 40, int net_h = 24) : frame(64 * 48 * 3 + 16), out(64 * 48 * 3 + 16) {
     CHECK(hs_init(0, &ctx) == HS_OK);
     memset(&d, 0, sizeof(d));
     d.frame_w = 64; d.frame_h = 48; d.frame_pitch = 192;
-    d.net_w = 40; d.net_h = 24; d.net = net;
+    d.net_w = net_w; d.net_h = net_h; d.net = net;
     d.mean = 0.5f; d.std = 0.25f; d.threshold = 0.5f; d.alpha = 0.5f;
     d.queue_depth = 2; d.batch = batch; d.glyph_scale = 1;
     size_t need = 0;
@@ -353,6 +353,46 @@ static void prefetched_weights() {
   }
 }
 
+// Of the grid of a layer in tiles of consecutive pixels every tile is one workgroup's, and what the surplus workgroups load
+// lies inside the layer's tensors as well.
+static void tile_grids() {
+  const int sizes[][3] = {{8, 8, 1}, {40, 24, 1}, {130, 66, 6}, {96, 64, 1}, {288, 160, 5}, {300, 170, 16}, {40, 520, 2}};
+  long surplus = 0;
+  for (const auto& z : sizes) {
+    Program p(HS_NET_RESNET18_CONVLSTM, z[2], z[0], z[1]);
+    hs_app* app = nullptr;
+    CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+    fake::n_conv_launches = 0;
+    std::vector<const uint8_t*> src((size_t)z[2], p.src());
+    std::vector<uint8_t*> dst((size_t)z[2], p.dst());
+    std::vector<hs_result> r((size_t)z[2]);
+    CHECK(hs_submit_batch(app, src.data(), dst.data(), 1) == HS_OK && hs_wait_batch(app, r.data(), 1000000000) == HS_OK);
+    int run = 0;
+    for (int i = 0; i < fake::n_conv_launches; ++i) {
+      const hs::ConvParams& c = fake::conv_launches[i];
+      if (c.variant != hs::CONV_KW) continue;
+      ++run;
+      std::vector<int> seen((size_t)(c.tiles_m * c.tiles_n));
+      const int channels = c.cout / c.tiles_n;
+      CHECK(8 * c.tiles_per_xcd >= c.tiles_m * c.tiles_n);
+      for (uint32_t t = 0; t < 8u * (uint32_t)c.tiles_per_xcd; ++t) {
+        const hs::RunTile at = hs::run_tile(t, c.tiles_m, c.tiles_n, c.n_block, c.run_nb_shift, c.run_by_blk);
+        CHECK(at.run < (uint32_t)c.tiles_m && at.channels < (uint32_t)c.tiles_n);
+        // the last byte of the tile's weights: chunks x 36 KB per 32 channels, and 4 KB of the projection's
+        const uint64_t groups = (uint64_t)(at.channels + 1) * (uint64_t)channels / 32;
+        CHECK(groups * (uint64_t)c.chunks_per_tap * 36 * 1024 <= c.run_w_bytes);
+        CHECK(groups * (uint64_t)c.chunks_per_tap * 4 * 1024 <= c.run_w_bytes / 9);
+        if (t < seen.size()) ++seen[(size_t)(at.run * (uint32_t)c.tiles_n + at.channels)];
+        else ++surplus;
+      }
+      for (int n : seen) CHECK(n == 1);
+    }
+    CHECK(run > 10);
+    CHECK(hs_destroy_app(app) == HS_OK);
+  }
+  CHECK(surplus > 0);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -365,6 +405,7 @@ int main(int argc, char** argv) {
   else if (check == "ready_result") ready_result();
   else if (check == "endless_wait") endless_wait();
   else if (check == "prefetched_weights") prefetched_weights();
+  else if (check == "tile_grids") tile_grids();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
