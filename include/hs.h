@@ -121,17 +121,17 @@ typedef struct {
  * The three intermediate stamps are t_overlay_done_ns minus the time on the GPU between that
  * stage's end and the overlay's end.  With kernel-by-kernel launches the kernels note the stages'
  * ends on the device's clock, and a GPU event behind stage 2 or 3 ties that clock to the overlay's
- * end (stamps within 1 us); a frame that needs no such event (submitted while the application is
- * idle, on one queue, without annotations, B * frame_w * frame_h at most 4194304) takes the
- * overlay's end from its last workgroup instead (within 2 us, some more where other applications
- * hold up that workgroup).  With graph launch, and while kernels are timed, GPU events give them
- * all (a few us, since every event is a packet of its own there).
- * Stage 3's per-cell outputs (heat, mask) are written by
- * stage 2's last kernel; stage 3 ends when its channel maxima (argmax, present, peak) have been
- * found.  Without the annotation layer that is done by the first workgroups of each image in the
- * overlay's launch, beside the drawing ones, and they stamp their end themselves.  On frames so
- * small that the drawing ends first, stage 3 and the overlay end together.  Stage 3 of a batch,
- * whose last image is drawn last, ends shortly before the overlay, and that of a group's member
+ * end (stamps within 1 us); a frame submitted while the application is idle, unpartitioned and
+ * without annotations, B * frame_w * frame_h at most 4194304, takes the overlay's end from its
+ * last workgroup instead (within 2 us, some more where other applications hold up that
+ * workgroup).  With graph launch, and while kernels are timed, GPU events give them all (a few
+ * us, since every event is a packet of its own there).
+ * Stage 3's per-cell outputs (heat, mask) are written by stage 2's last kernel; stage 3 ends when
+ * its channel maxima (argmax, present, peak) have been found.  Without the annotation layer that is
+ * done by the first workgroups of each image in the overlay's launch, beside the drawing ones, and
+ * they stamp their end themselves.  On frames so small that the drawing ends first, stage 3 and
+ * the overlay end together.  Stage 3 of a batch, whose last image is drawn last, ends shortly
+ * before the overlay, and that of a group's member
  * includes the wait for the other members' networks.
  * End-to-end latency = t_overlay_done_ns - t_submit_ns (Section II-C).
  *

@@ -218,7 +218,7 @@ struct OverlayParams {
   int n_layers;                      // layers drawn in order, each over the one before
   int n_max;                         // workgroups per image between the first and the drawing ones: 8 * n_layers
                                      // when some layer has a rec, else 0
-  int stamp_end;                     // layer[0].stamps->drawn is wanted
+  int stamp_end;                     // the layers' stamps->drawn is wanted
   OverlayLayer layer[kMaxLayers];
 };
 KernelDesc describe(const OverlayParams& p);

@@ -1998,7 +1998,10 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   // The launch's end as its last workgroup sees it, noted ahead of the pixels' stores, whose way to memory hides the
   // stamp's to the host.  (Behind them it puts 1.8 us on a frame.)
-  if (p.stamp_end && blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && threadIdx.x == 0) p.layer[0].stamps->drawn = wall_clock64();
+  if (p.stamp_end && blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && (int)threadIdx.x < nl) {
+    StageStamps* const st = p.layer[LAYERS ? threadIdx.x : 0].stamps;
+    if (st) st->drawn = wall_clock64();
+  }
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     const u32x4 o = s_x[wave][64 * j + lane];

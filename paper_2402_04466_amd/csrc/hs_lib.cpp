@@ -128,9 +128,9 @@ struct Slot {
   // behind stage 2
   hipEvent_t ev_stage3 = nullptr;
   // Frames launched kernel by kernel take the stages' ends from `stamps`.  Their ev_infer / ev_stage3 order streams, and
-  // are there only where another stream waits for them at submit or is likely to later (order_behind); ev_stage3
-  // (has_event) also ties the device's clock to the frame's end.
-  bool stamped = false, has_event = true;
+  // are there only where another stream waits for them at submit or is likely to later (order_behind).  What ties the
+  // device's clock to the frame's end is a stamp of the overlay's last workgroup (end_stamped), or else ev_stage3 (has_event).
+  bool stamped = false, end_stamped = false, has_event = true;
   hipStream_t stream = nullptr;       // the frame's, up to stage 3
   // the event that says the frame has left the last stage: ev_overlay, or, for a member of a
   // group, the first member's (one overlay launch serves them all)
@@ -1246,8 +1246,8 @@ static void completer_main(hs_app* app) {
       const StageStamps& t = *s->stamps;
       auto span = [&](uint64_t from, uint64_t to) { return (float)(int64_t)(to - from) / (float)app->ctx->wall_clock_khz; };
       float ms = 0;                      // from the stamp of ev_stage3's stage on
-      if (s->has_event && e == hipSuccess) e = hipEventElapsedTime(&ms, s->ev_stage3, s->ev_done);
-      ms += s->has_event ? kStampToEventMs : span(t.infer, t.drawn) + kDrawnToEndMs;
+      if (!s->end_stamped && e == hipSuccess) e = hipEventElapsedTime(&ms, s->ev_stage3, s->ev_done);
+      ms += s->end_stamped ? span(t.infer, t.drawn) + kDrawnToEndMs : kStampToEventMs;
       ms_post = s->maxima_rode ? std::max(0.0f, ms - stage3_ms(*s, app->ctx->wall_clock_khz)) : ms;
       ms_inf = s->maxima_rode ? ms : ms + span(t.infer, t.post);
       ms_pre = ms_inf + span(t.pre, t.infer);
@@ -1881,14 +1881,14 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   // frames back to back, and an event recorded when that frame comes (4 us of host) 1.5 % on five applications.
   const bool two_queues = app->lanes > 1 && app->s_lane[0] != app->s_lane[1];
   const bool others_wait = !own_overlay || ov_stream != lane_stream || (two_queues && (!idle || s->wait_idx >= 0));
-  // The one behind stage 3 also ties the stages' stamps, on the device's clock, to the frame's end.  Without it they are
-  // tied to what the overlay's last workgroup sees of that end (kDrawnToEndMs), which serves while the workgroups (4096
-  // pixels each) run side by side on the whole device and take equally long.  With more of them it is up to 7 us early (a
-  // plain 7680 x 4320 frame), with annotations up to 11 (320 x 240): such frames have the event, and pay for it.
-  const bool even_drawing =
-      !app->desc.annotate && !app->partitioned && (double)B * app->desc.frame_w * app->desc.frame_h <= 1024 * 4096.0;
-  s->has_event = !s->stamped || others_wait || !even_drawing;
-  s->overlay[0].overlay.stamp_end = s->stamped && !s->has_event;
+  // What the overlay's last workgroup sees of the frame's end (kDrawnToEndMs) serves to tie the stages' stamps to it while
+  // the workgroups (4096 pixels each) run side by side, not held up by another frame, and take equally long.  With more of
+  // them it is up to 7 us early (a plain 7680 x 4320 frame), with annotations up to 11 (320 x 240).  Such frames have the
+  // event behind stage 3 for it, and the completion thread spends 1 us (35 at an application's first frame) on its time.
+  s->end_stamped = s->stamped && idle && !app->desc.annotate && !app->partitioned &&
+                   (double)B * app->desc.frame_w * app->desc.frame_h <= 1024 * 4096.0;
+  s->has_event = !s->stamped || others_wait || !s->end_stamped;
+  s->overlay[0].overlay.stamp_end = s->end_stamped;
   s->stream = lane_stream;
   auto event = [&](hipEvent_t e, bool wanted) { return !s->stamped || wanted ? e : nullptr; };
   if (!idle && app->lane_last_stream[s->lane] && app->lane_last_stream[s->lane] != lane_stream &&
@@ -2226,8 +2226,12 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   };
   if (st0 != HS_OK) { set_error("%s", err0.text); return fail_all(st0); }
   op.n_max = 0;
-  op.stamp_end = 0;        // (members' stages have events)
+  bool even = true;        // no member's annotations are drawn
+  for (size_t i = 0; i < n; ++i) even = even && !group->members[i]->desc.annotate && !group->members[i]->partitioned;
+  op.stamp_end = 0;
   for (size_t i = 0; i < n; ++i) {
+    slot[i]->end_stamped = slot[i]->end_stamped && even;       // (else its event: a member's stage 3 has one)
+    if (slot[i]->end_stamped) op.stamp_end = 1;
     op.layer[i] = slot[i]->overlay[0].overlay.layer[0];
     if (op.layer[i].rec) op.n_max = 8 * (int)n;
   }
