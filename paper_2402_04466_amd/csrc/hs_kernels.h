@@ -60,12 +60,16 @@ enum ConvVariant {
   CONV_S2_DIRA,   // 3x3/2 layers (+ fused 1x1/2 projection) of one Cin chunk on large grids: tile 8 x 8 x 128, weights
                   // from wt_frag / wt2_frag, tile walking, no residual (k_conv3x3s2_dira)
   CONV_KW         // 3x3 layers with the K splits inside the workgroup, tiles of consecutive pixels, weights from wt_frag /
-                  // wt2_frag.  Stride 1, an even number of Cin chunks: k_conv3x3_run.  Stride 2 (+ fused projection):
-                  // k_conv3x3s2_run
+                  // wt2_frag.  Stride 1, an even number of Cin chunks: k_conv3x3_run.  Stride 2, always with its fused
+                  // projection: k_conv3x3s2_run
 };
 // The forms of k_conv3x3_run: channels and pixels of a tile, loading passes over a patch (32 pixels each), bytes of a patch
 // buffer; cost of a tile in us where its CU works on several, fixed and per Cin chunk (see Builder::choose_form).
-struct RunForm { int ch, px, passes, lds; double cost, chunk_cost; };
+struct RunForm {
+  int ch, px, passes, lds;
+  double cost, chunk_cost;
+  constexpr int splits() const { return 128 / ch; }   // K splits: four wavefronts of 32 channels each
+};
 constexpr RunForm kRunForms[] = {
     {32, 32, 3, 16384, 0.35, 0.47}, {32, 64, 4, 24576, 0.55, 0.57},  {64, 64, 4, 24576, 0.75, 1.03},
     {64, 96, 6, 26624, 1.3, 1.29},  {64, 128, 7, 36864, 1.9, 1.62}, {64, 160, 8, 40960, 2.3, 2.22},
@@ -73,7 +77,11 @@ constexpr RunForm kRunForms[] = {
 };
 constexpr int kRunFormCount = 7, kRunFormAnyMap = 6;
 // And of k_conv3x3s2_run: patch pixels per loading pass, 16-byte LDS units per patch pixel besides.
-struct Run2Form { int ch, px, passes, lds, step, units; double cost, chunk_cost; };
+struct Run2Form {
+  int ch, px, passes, lds, step, units;
+  double cost, chunk_cost;
+  constexpr int splits() const { return 128 / ch; }
+};
 constexpr Run2Form kRun2Forms[] = {
     {32, 32, 6, 28672, 32, 9, 1.2, 0.53}, {64, 32, 3, 16384, 64, 5, 0.4, 1.3}, {64, 64, 5, 28672, 64, 5, 1.4, 1.62},
     {64, 96, 8, 40960, 64, 5, 2.4, 2.0},

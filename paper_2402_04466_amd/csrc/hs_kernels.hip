@@ -1387,34 +1387,41 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
   }
   asm volatile("" ::"v"(touched));
 }
-// The instantiations of k_conv3x3s2_run: see kRun2Forms.
+// The instantiations of k_conv3x3s2_run and k_conv3x3_run: the host plans for the tiles, splits and patch buffers of
+// kRun2Forms and kRunForms, four wavefronts each; pixel (and weight) fragments in flight and workgroups per CU.
+template <int I, int BD, int OCC>
+static const void* run2_kernel() {
+  constexpr Run2Form f = kRun2Forms[I];
+  static_assert(f.step == f.ch && f.units == 2 * f.splits() + 1, "a patch pixel's vectors, and one more unit against bank conflicts");
+  return (const void*)k_conv3x3s2_run<f.px / 32, f.splits(), f.ch / 32, BD, f.passes, f.lds, OCC>;
+}
 static const void* run2_kernel_of(int form) {
   switch (form) {
-    case 0: return (const void*)k_conv3x3s2_run<1, 4, 1, 5, 6, 28672, 2>;
-    case 1: return (const void*)k_conv3x3s2_run<1, 2, 2, 5, 3, 16384, 3>;
-    case 2: return (const void*)k_conv3x3s2_run<2, 2, 2, 5, 5, 28672, 2>;
-    case 3: return (const void*)k_conv3x3s2_run<3, 2, 2, 5, 8, 40960, 2>;
-    case 4: return (const void*)k_conv3x3s2_run<1, 4, 1, 5, 8, 40960, 1>;
+    case 0: return run2_kernel<0, 5, 2>();
+    case 1: return run2_kernel<1, 5, 3>();
+    case 2: return run2_kernel<2, 5, 2>();
+    case 3: return run2_kernel<3, 5, 2>();
+    case 4: return run2_kernel<4, 5, 1>();
     default: return nullptr;
   }
 }
-// The instantiations of k_conv3x3_run: see kRunForms.
+template <int I, int FR, int BD, int OCC>
+static const void* run_kernel() {
+  constexpr RunForm f = kRunForms[I];
+  return (const void*)k_conv3x3_run<f.px / 32, f.splits(), f.ch / 32, FR, BD, f.passes, f.lds, OCC>;
+}
 static const void* run_kernel_of(int form) {
   switch (form) {
-    case 0: return (const void*)k_conv3x3_run<1, 4, 1, 9, 8, 3, 16384, 3>;
-    case 1: return (const void*)k_conv3x3_run<2, 4, 1, 9, 6, 4, 24576, 3>;
-    case 2: return (const void*)k_conv3x3_run<2, 2, 2, 9, 8, 4, 24576, 3>;
-    case 3: return (const void*)k_conv3x3_run<3, 2, 2, 9, 4, 6, 26624, 3>;
-    case 4: return (const void*)k_conv3x3_run<4, 2, 2, 9, 5, 7, 36864, 2>;
-    case 5: return (const void*)k_conv3x3_run<5, 2, 2, 12, 5, 8, 40960, 2>;
-    case 6: return (const void*)k_conv3x3_run<1, 4, 1, 9, 8, 7, 44032, 1>;
+    case 0: return run_kernel<0, 9, 8, 3>();
+    case 1: return run_kernel<1, 9, 6, 3>();
+    case 2: return run_kernel<2, 9, 8, 3>();
+    case 3: return run_kernel<3, 9, 4, 3>();
+    case 4: return run_kernel<4, 9, 5, 2>();
+    case 5: return run_kernel<5, 12, 5, 2>();
+    case 6: return run_kernel<6, 9, 8, 1>();
     default: return nullptr;
   }
 }
-static_assert(kRunForms[0].passes == 3 && kRunForms[0].lds == 16384 && kRunForms[1].passes == 4 && kRunForms[1].lds == 24576 &&
-              kRunForms[2].passes == 4 && kRunForms[2].lds == 24576 && kRunForms[3].passes == 6 && kRunForms[3].lds == 26624 &&
-              kRunForms[4].passes == 7 && kRunForms[4].lds == 36864 && kRunForms[5].passes == 8 && kRunForms[5].lds == 40960 &&
-              kRunForms[6].passes == 7 && kRunForms[6].lds == 44032, "the host plans for the kernels' patch buffers");
 
 KernelDesc describe(const ConvParams& p) {
   // 1-D grid, padded to a multiple of 8 so that every XCD owns tiles_per_xcd consecutive tiles

@@ -477,9 +477,11 @@ struct Builder {
     return c.tiles_m > 0 && (double)c.tiles_m * c.tiles_n * c.tiles_m * c.tiles_n < 2147483648.0;   // run_div31
   }
 
-  // k_conv3x3s2_run with a form of kRun2Forms.
+  // k_conv3x3s2_run with a form of kRun2Forms.  (Its items are chunks with four K splits, half chunks with two, and it takes
+  // them in pairs, or a single one.)
   static bool plan_run2(ConvParams& c, int form) {
     const Run2Form& f = kRun2Forms[form];
+    if (f.splits() == 4 && c.chunks_per_tap % 2 != 0 && c.chunks_per_tap != 1) return false;
     const double in_bytes = 2.0 * c.batch * c.hin * c.win * c.cin_pitch, w_bytes = 2.0 * c.cout_pad * c.ktot;
     if (c.cout % f.ch != 0 || in_bytes >= 2147483648.0 || w_bytes >= 2147483648.0) return false;
     c.variant = CONV_KW;
@@ -642,6 +644,7 @@ struct Builder {
     ConvParams probe = g;
     choose_split(probe);
     const bool direct = probe.variant == CONV_DIRECT, fuse = proj_out != nullptr;
+    if (probe.variant == CONV_KW && stride == 2 && !fuse) throw std::logic_error("k_conv3x3s2_run computes a projection too");
     const size_t wf_halves = (size_t)(direct ? 32 : g.cout_pad) * g.ktot, wf_off = reserve_w(wf_halves);
     size_t wf2_off = kNoWeights;
     if (!direct) {

@@ -1,0 +1,55 @@
+// The plans of layers that no network here has, from the library's own planning code: what its kernels do not do is refused.
+#include "hs_lib.cpp"
+
+#define CHECK(cond)                                   \
+  do {                                                \
+    if (!(cond)) {                                    \
+      printf("line %d: %s\n", __LINE__, #cond);       \
+      exit(1);                                        \
+    }                                                 \
+  } while (0)
+
+static hs_app_desc description() {
+  hs_app_desc d;
+  memset(&d, 0, sizeof(d));
+  d.batch = 2;
+  return d;
+}
+
+static Tensor tensor(int h, int w, int c, int batch) {
+  Tensor t;
+  t.h = h; t.w = w; t.c = t.pitch = c;
+  t.cap = (size_t)batch * h * w * c;
+  return t;
+}
+
+// A stride-2 layer of so many Cin chunks, planned with one form.
+static bool plans(int chunks, int form) {
+  ConvParams c;
+  memset(&c, 0, sizeof(c));
+  c.batch = 2; c.hin = 24; c.win = 40; c.cin_pitch = 64 * chunks;
+  c.hout = 12; c.wout = 20; c.img_m = 240; c.m = 480;
+  c.cout = c.cout_pad = 128; c.kc = 64; c.ntaps = 9; c.kw = 3; c.stride = 2; c.pad = 1;
+  c.chunks_per_tap = chunks; c.nchunks = 9 * chunks; c.ktot = 64 * c.nchunks;
+  return Builder::plan_run2(c, form);
+}
+
+int main() {
+  for (int form = 0; form < kRun2FormCount; ++form)
+    for (int chunks = 1; chunks <= 8; ++chunks)
+      // four K splits: whole chunks, in pairs or a single one; two: half chunks, always in pairs
+      CHECK(plans(chunks, form) == (kRun2Forms[form].splits() == 2 || chunks == 1 || chunks % 2 == 0));
+  const hs_app_desc d = description();
+  for (bool with_projection : {true, false}) {
+    Builder b(d, nullptr, false, false);
+    Tensor in = tensor(24, 40, 128, d.batch), out = tensor(12, 20, 128, d.batch), proj = out;
+    bool refused = false;
+    try {
+      b.conv_layer(in, 0, 128, 3, 2, 1, true, nullptr, &out, false, false, 0, with_projection ? &proj : nullptr);
+    } catch (const std::logic_error&) {
+      refused = true;
+    }
+    CHECK(refused == !with_projection);
+  }
+  return 0;
+}

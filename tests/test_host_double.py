@@ -33,6 +33,19 @@ def test_host_code(host_double, check):
     assert r.returncode == 0, (r.returncode, r.stdout[-500:], r.stderr[-500:])
 
 
+def test_refused_plans(tmp_path):
+    exe = str(tmp_path / "plan")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
+    src = [os.path.join(HERE, "plan_main.cpp"), os.path.join(HERE, "fake_hip.cpp")]
+    src += [os.path.join(build.CSRC, f) for f in ("hs_host.cpp", "hs_driver.cpp")]
+    subprocess.run([os.path.join(rocm, "llvm", "bin", "clang++"), "-std=c++17", "-O2", "-w",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"), "-I",
+                    os.path.join(ROOT, "include"), "-I", build.CSRC, *src, "-o", exe, "-lpthread", "-ldl"],
+                   check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-500:]
+
+
 def test_tiles_of_consecutive_pixels(tmp_path):
     exe = str(tmp_path / "run_geometry")
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
