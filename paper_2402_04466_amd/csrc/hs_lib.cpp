@@ -748,11 +748,15 @@ struct Builder {
     conv_layer(t3, at, 8, 3, 1, 1, false, nullptr, &lg, true, false);    at += 8 * 32 * 9;
     blob_off = at;
     map_h = lg.h; map_w = lg.w; stateful = false;
-    // One launch for all layers, but the layers one after the other while kernels are being timed, and where there are
-    // many tiles: the halos that k_tiny_net computes again then cost more than the launches and tensors it saves
-    // (network's launches in us, layers -> one: one 128 x 128 frame 16.8 -> 6.8, eight 320 x 320 28.2 -> 23.5, sixteen, 1600
-    // tiles, 43.7 -> 39.1, sixteen 640 x 640, 6400 tiles, 113 -> 131).
-    if (d.batch * ((map_h + 7) / 8) * ((map_w + 7) / 8) > 2048) return;
+    // One launch for all layers, but the layers one after the other while kernels are being timed, and where the halos that
+    // k_tiny_net computes again, and its tiles beyond the map's edges, cost more than the launches and tensors it saves.  It
+    // takes a round of 256 tiles at a time, the layers go by pixels: times in us, fitted to 35 sizes from one 128 x 128 frame
+    // to one of 1448 x 1448, thin ones among them.  Measured, layers / one launch: one 128 x 128 frame 15.6 / 6.8, eight 320 x 320
+    // 26.2 / 23.4, sixteen (1600 tiles) 41.5 / 39.9; sixteen 300 x 200 (1120 tiles, 84 % full) 27.6 / 28.9, eight 640 x 360
+    // (1920 tiles) 43.6 / 45.2, sixteen 4000 x 16 (2000 tiles, half full) 28.6 / 44.4.
+    const double pixels = (double)d.batch * map_h * map_w;
+    const int rounds = (d.batch * ((map_h + 7) / 8) * ((map_w + 7) / 8) + 255) / 256;
+    if (2.0 + 5.3 * rounds > std::max(15.6, 10.3 + 0.288e-3 * pixels)) return;
     layer_ops = ops;
     Op net;
     net.fam = F_CONV;

@@ -393,6 +393,26 @@ static void tile_grids() {
   CHECK(surplus > 0);
 }
 
+// The small network runs in one launch where that is the faster form, measured at these sizes, and else layer by layer.
+static void small_network_forms() {
+  const struct { int w, h, batch; bool one; } sizes[] = {
+      {128, 128, 1, true},   {320, 320, 8, true},   {320, 320, 16, true},  {1280, 720, 1, true}, {4000, 16, 4, true},
+      {300, 200, 16, false}, {640, 360, 8, false},  {4000, 16, 8, false},  {16, 4000, 16, false}, {1448, 1448, 1, false}};
+  for (const auto& z : sizes) {
+    Program p(HS_NET_TINY4, z.batch, z.w, z.h);
+    hs_app* app = nullptr;
+    CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+    fake::n_conv_launches = 0;
+    std::vector<const uint8_t*> src((size_t)z.batch, p.src());
+    std::vector<uint8_t*> dst((size_t)z.batch, p.dst());
+    std::vector<hs_result> r((size_t)z.batch);
+    CHECK(hs_submit_batch(app, src.data(), dst.data(), 1) == HS_OK && hs_wait_batch(app, r.data(), 1000000000) == HS_OK);
+    CHECK(fake::n_conv_launches == (z.one ? 1 : 4));
+    CHECK(fake::conv_launches[0].variant == (z.one ? hs::CONV_TINY_NET : hs::CONV_DIRECT));
+    CHECK(hs_destroy_app(app) == HS_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -406,6 +426,7 @@ int main(int argc, char** argv) {
   else if (check == "endless_wait") endless_wait();
   else if (check == "prefetched_weights") prefetched_weights();
   else if (check == "tile_grids") tile_grids();
+  else if (check == "small_network_forms") small_network_forms();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }
