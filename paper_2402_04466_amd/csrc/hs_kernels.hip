@@ -947,12 +947,18 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
 // Touches this workgroup's share of the next layer's weights (one 4-byte load per 128-byte line),
 // so that they are on their way into the last-level cache when that layer starts: streamed from
 // HBM by the layer itself, every ring of fragments in flight costs a full memory latency.  Called
-// behind the K loop; the loads complete during the epilogue (the value is consumed at its end).
-__device__ __forceinline__ uint32_t prefetch_next(const ConvParams& p, int block, int n_blocks) {
-  uint32_t x = 0;
-  for (int i = block * (int)blockDim.x + (int)threadIdx.x; i < p.next_lines; i += n_blocks * (int)blockDim.x)
-    x ^= *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(p.next_wt) + (size_t)i * 128);
-  return x;
+// behind the K loop; the loads complete during the epilogue (the values are consumed at its end).
+// At most four lines per thread, all in flight at once: a grid of few workgroups leaves the rest to the next layer (sixteen
+// 8 x 8 inputs, up to 27 lines per thread one after the other 150 us a pass, so 128; two 192 x 108 123, 114).
+constexpr int kTouched = 4;
+__device__ __forceinline__ void prefetch_next(const ConvParams& p, int block, int n_blocks, uint32_t (&x)[kTouched]) {
+  const BufferRsrc buf = buffer_of(p.next_wt, (uint32_t)p.next_lines * 128);
+  const uint32_t stride = (uint32_t)n_blocks * blockDim.x, first = (uint32_t)block * blockDim.x + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kTouched; ++k) {
+    const uint32_t i = first + k * stride;
+    x[k] = __builtin_amdgcn_raw_buffer_load_b32(buf, i < (uint32_t)p.next_lines ? (int)(i * 128) : kOutside, 0, 0);
+  }
 }
 
 // =============================================================================================
@@ -1137,7 +1143,8 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
 #undef HS_HAND_P
 #undef HS_LOAD_P
 
-  const uint32_t touched = prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n);
+  uint32_t touched[kTouched] = {};
+  if (p.next_lines) prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n, touched);
   if (KS > 1) __syncthreads();       // every wavefront is done with the patches
 #pragma unroll
   for (int ps = 0; ps < PASSES; ++ps) {
@@ -1196,7 +1203,7 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
         }
       }
   }
-  asm volatile("" ::"v"(touched));
+  asm volatile("" ::"v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
 }
 // =============================================================================================
 // 3x3 stride-2 pad-1 layers with the block's 1x1 stride-2 projection riding along: k_conv3x3_run's tiles, K splits and
@@ -1340,7 +1347,8 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
 #undef HS_HAND_P
 #undef HS_LOAD_P
 
-  const uint32_t touched = prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n);
+  uint32_t touched[kTouched] = {};
+  if (p.next_lines) prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n, touched);
   float4* const s_red = reinterpret_cast<float4*>(s_raw) + wave / KS * KS * UP * 128 + lane;
 #pragma unroll
   for (int ps = 0; ps < PASSES; ++ps) {
@@ -1385,7 +1393,7 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams 
         else store_half(p.out2, p.out2_pitch, false, o_m[g], cbase, h, v[0], v[1], none, false);   // no ReLU
       }
   }
-  asm volatile("" ::"v"(touched));
+  asm volatile("" ::"v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
 }
 // The instantiations of k_conv3x3s2_run and k_conv3x3_run: the host plans for the tiles, splits and patch buffers of
 // kRun2Forms and kRunForms, four wavefronts each; pixel (and weight) fragments in flight and workgroups per CU.
