@@ -963,7 +963,7 @@ __device__ __forceinline__ void prefetch_next(const ConvParams& p, int block, in
 
 // =============================================================================================
 // 3x3 stride-1 pad-1 layers with several Cin chunks (stages 2-4 and the ConvLSTM gates), at every size.
-// A tile is 32 * CW channels x a RUN of 32 * PG consecutive pixels: the map is cut into strips of run_w columns, and
+// A tile is 32 * CW channels x a RUN of 32 * PG consecutive pixels: the map is cut into strips of strip_w columns, and
 // the pixels of all strips of all images of the launch, row by row, are one list that the runs are cut from.  So no
 // tile but the last is partly empty, whatever the map (tiles of 8 x 16 pixels are to 79 % full on a 27 x 15 map), and
 // the host can pick the tile whose count fills the CUs (Builder::choose_form).
@@ -978,8 +978,7 @@ __device__ __forceinline__ void prefetch_next(const ConvParams& p, int block, in
 //     tile a tile's weights come in once (two wavefronts that share a channel group fetch them twice).
 //   - All loads have scalar offsets into buffers of known size: no address arithmetic in the loop, and padding reads
 //     as zeros (flat pointers and selects instead: 4 to 10 % of a launch).
-//   - The partial sums meet in LDS and are added in pairs, PASSES times a part of them; every wavefront finishes its share
-//     of the channels.
+//   - The partial sums meet in LDS and are added in pairs; every wavefront finishes its share of the channels.
 // Per output and K split: chunk, tap, K-step; then the splits in pairs.
 // PL: 16-byte vectors of a patch per thread; LDS: bytes of a patch buffer (128 of them taken by vectors beyond the
 // patch); FR, BD: weight and pixel fragments in flight; OCC: workgroups per CU.  The values are the fastest of those
@@ -1000,10 +999,10 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
   // accumulators are finished in pieces of 16 channels x 32 pixels (QU = 2 quads per lane), or 8 where there are fewer
   // such pieces than K splits
   constexpr int QU = 2 * PG < KS ? 1 : 2, UNITS = 4 / QU * PG, UB = QU * 1024;
-  // partial sums that meet in LDS at a time, and passes over them
-  constexpr int UP = KS == 1 || UNITS * NW * UB <= 2 * LDS || UNITS * NW * UB <= 65536 ? UNITS : KS, PASSES = UNITS / UP, UN = UP / KS;
-  static_assert(UNITS % UP == 0 && UP % KS == 0, "every K split finishes the same number of pieces");
-  constexpr int RED = KS == 1 ? 0 : (PASSES > 1 ? 2 : 1) * UP * NW * UB, SHM = RED > 2 * LDS ? RED : 2 * LDS;
+  constexpr int UN = UNITS / KS;                                   // pieces a wavefront finishes
+  static_assert(UNITS % KS == 0, "every K split finishes the same number of pieces");
+  constexpr int RED = UNITS * NW * UB, SHM = RED > 2 * LDS ? RED : 2 * LDS;
+  static_assert(RED <= 2 * LDS || RED <= 65536, "the partial sums take no more LDS than the patches, or 64 KB");
   __shared__ __align__(16) unsigned char s_raw[SHM];
   f16* const s_patch = reinterpret_cast<f16*>(s_raw);
 
@@ -1114,25 +1113,23 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
   }
   // residual of the pieces this wavefront finishes (without one: any address, so that the loads are
   // unconditional), fetched behind the last chunks
-  u32x4 res_raw[PASSES][UN];
+  u32x4 res_raw[UN];
   {
     const f16* const rsp = p.res ? p.res + n0 + cw * 32 + 4 * QU * h : p.in;
     const int pitch = p.res ? p.res_pitch : 0;
 #pragma unroll
-    for (int ps = 0; ps < PASSES; ++ps)
-#pragma unroll
-      for (int k = 0; k < UN; ++k) {
-        const int q = (ps * UP + ks * UN + k) * QU;
-        int lds, m;
-        pixel(q / 4, lds, m);
-        const f16* const at = rsp + (size_t)max(m, 0) * pitch + (p.res ? 8 * (q % 4) : 0);
-        if (QU == 2) {
-          res_raw[ps][k] = *reinterpret_cast<const u32x4*>(at);
-        } else {
-          const uint2 v = *reinterpret_cast<const uint2*>(at);
-          res_raw[ps][k] = {v.x, v.y, 0u, 0u};
-        }
+    for (int k = 0; k < UN; ++k) {
+      const int q = (ks * UN + k) * QU;
+      int lds, m;
+      pixel(q / 4, lds, m);
+      const f16* const at = rsp + (size_t)max(m, 0) * pitch + (p.res ? 8 * (q % 4) : 0);
+      if (QU == 2) {
+        res_raw[k] = *reinterpret_cast<const u32x4*>(at);
+      } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(at);
+        res_raw[k] = {v.x, v.y, 0u, 0u};
       }
+    }
   }
   HS_CHUNK(0, true)
   __syncthreads();
@@ -1145,64 +1142,56 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
 
   uint32_t touched[kTouched] = {};
   if (p.next_lines) prefetch_next(p, (int)tile, p.tiles_m * p.tiles_n, touched);
-  if (KS > 1) __syncthreads();       // every wavefront is done with the patches
+  __syncthreads();                   // every wavefront is done with the patches
+  float4* const s_red = reinterpret_cast<float4*>(s_raw) + (size_t)(wave / KS) * KS * UNITS * (UB / 16) + lane;
 #pragma unroll
-  for (int ps = 0; ps < PASSES; ++ps) {
-    // (the passes take the two halves of the LDS in turn: the barrier of one pass orders the next one's writes
-    // behind the reads of the one before)
-    float4* const s_red = reinterpret_cast<float4*>(s_raw) + (PASSES > 1 ? (ps & 1) * UP * NW * (UB / 16) : 0) +
-                          (size_t)(wave / KS) * KS * UP * (UB / 16) + lane;
-    if (KS > 1) {
+  for (int u = 0; u < UNITS; ++u)
+    if (u / UN != ks) {
+      const int q = u * QU;                                        // first quad of the piece
+      const floatx16& a = acc[q / 4];
 #pragma unroll
-      for (int u = 0; u < UP; ++u)
-        if (u / UN != ks) {
-          const int q = (ps * UP + u) * QU;                        // first quad of the piece
-          const floatx16& a = acc[q / 4];
-#pragma unroll
-          for (int j = 0; j < QU; ++j) {
-            const int o = 4 * (q % 4 + j);
-            s_red[(ks * UP + u) * (UB / 16) + 64 * j] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
-          }
-        }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < UP; ++u)
-      if (u / UN == ks) {
-        const int q = (ps * UP + u) * QU;
-        const floatx16& a = acc[q / 4];
-        float4 v[2];
-#pragma unroll
-        for (int j = 0; j < QU; ++j) {
-          const int o = 4 * (q % 4 + j);
-          float4 b[KS];
-#pragma unroll
-          for (int k = 0; k < KS; ++k) {
-            b[k] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
-            if (k != ks) b[k] = s_red[(k * UP + u) * (UB / 16) + 64 * j];
-          }
-#pragma unroll
-          for (int d = KS / 2; d >= 1; d /= 2)                     // in pairs
-#pragma unroll
-            for (int k = 0; k < d; ++k) {
-              b[k].x += b[k + d].x; b[k].y += b[k + d].y; b[k].z += b[k + d].z; b[k].w += b[k + d].w;
-            }
-          v[j] = b[0];
-        }
-        const int cbase = n0 + cw * 32 + 8 * (q % 4), m = o_m[q / 4];
-        if (p.use_partial) {
-          if (m >= 0) {
-            float* dst = p.partial + (size_t)m * p.cout_pad + cbase + 4 * h;
-#pragma unroll
-            for (int j = 0; j < QU; ++j) *reinterpret_cast<float4*>(dst + 8 * j) = v[j];
-          }
-        } else if (QU == 2) {
-          store_half(p.out, p.out_pitch, p.relu != 0, m, cbase, h, v[0], v[1], res_raw[ps][u % UN], p.res != nullptr);
-        } else {
-          store_quad(p, m, cbase, h, v[0], res_raw[ps][u % UN]);
-        }
+      for (int j = 0; j < QU; ++j) {
+        const int o = 4 * (q % 4 + j);
+        s_red[(ks * UNITS + u) * (UB / 16) + 64 * j] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
       }
-  }
+    }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < UNITS; ++u)
+    if (u / UN == ks) {
+      const int q = u * QU;
+      const floatx16& a = acc[q / 4];
+      float4 v[2];
+#pragma unroll
+      for (int j = 0; j < QU; ++j) {
+        const int o = 4 * (q % 4 + j);
+        float4 b[KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          b[k] = make_float4(a[o], a[o + 1], a[o + 2], a[o + 3]);
+          if (k != ks) b[k] = s_red[(k * UNITS + u) * (UB / 16) + 64 * j];
+        }
+#pragma unroll
+        for (int d = KS / 2; d >= 1; d /= 2)                       // in pairs
+#pragma unroll
+          for (int k = 0; k < d; ++k) {
+            b[k].x += b[k + d].x; b[k].y += b[k + d].y; b[k].z += b[k + d].z; b[k].w += b[k + d].w;
+          }
+        v[j] = b[0];
+      }
+      const int cbase = n0 + cw * 32 + 8 * (q % 4), m = o_m[q / 4];
+      if (p.use_partial) {
+        if (m >= 0) {
+          float* dst = p.partial + (size_t)m * p.cout_pad + cbase + 4 * h;
+#pragma unroll
+          for (int j = 0; j < QU; ++j) *reinterpret_cast<float4*>(dst + 8 * j) = v[j];
+        }
+      } else if (QU == 2) {
+        store_half(p.out, p.out_pitch, p.relu != 0, m, cbase, h, v[0], v[1], res_raw[u % UN], p.res != nullptr);
+      } else {
+        store_quad(p, m, cbase, h, v[0], res_raw[u % UN]);
+      }
+    }
   asm volatile("" ::"v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
 }
 // =============================================================================================
