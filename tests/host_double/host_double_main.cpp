@@ -323,7 +323,7 @@ static void endless_wait() {
   CHECK(hs_destroy_app(app) == HS_OK);
 }
 
-// A kernel is told to prefetch the next layer's weights only if it does so (k_conv3x3_kw), and then
+// A kernel is told to prefetch the next layer's weights only if it does so (k_conv3x3_run, k_conv3x3s2_run), and then
 // exactly those that the layer has.
 static void prefetched_weights() {
   for (int net : {(int)HS_NET_TINY4, (int)HS_NET_RESNET18_CONVLSTM}) {

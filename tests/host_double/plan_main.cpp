@@ -1,4 +1,5 @@
-// The plans of layers that no network here has, from the library's own planning code: what its kernels do not do is refused.
+// The library's own planning code.  Without arguments: plans of layers that no network here has; what the kernels do not do
+// is refused.  With arguments, "resnet18_convlstm" or "tiny4" and width, height, batch: prints each layer's kernel and form.
 #include "hs_lib.cpp"
 
 #define CHECK(cond)                                   \
@@ -34,7 +35,30 @@ static bool plans(int chunks, int form) {
   return Builder::plan_run2(c, form);
 }
 
-int main() {
+static int print_forms(const char* net, int w, int h, int batch) {
+  hs_app_desc d = description();
+  d.net = strcmp(net, "tiny4") == 0 ? HS_NET_TINY4 : HS_NET_RESNET18_CONVLSTM;
+  d.net_w = w; d.net_h = h; d.batch = batch;
+  int pw, ph, pad;
+  padded_input_geometry(w, h, d.net == HS_NET_TINY4 ? 3 : 7, &pw, &ph, &pad);
+  Builder b(d, nullptr, false, false);
+  b.walk(ph, pw);
+  for (const Op& op : b.ops) {
+    if (op.fam != F_CONV) continue;
+    const ConvParams& c = op.conv;
+    switch (c.variant) {
+      case CONV_DIRECT: printf("direct %d\n", c.kw_splits); break;
+      case CONV_TINY_NET: printf("tiny_net 0\n"); break;
+      case CONV_BLOCK64: printf("block64 0\n"); break;
+      case CONV_S2_DIRA: printf("s2_dira 0\n"); break;
+      default: printf("%s %d\n", c.stride == 1 ? "run" : "s2_run", c.run_form);
+    }
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc == 5) return print_forms(argv[1], atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
   for (int form = 0; form < kRun2FormCount; ++form)
     for (int chunks = 1; chunks <= 8; ++chunks)
       // four K splits: whole chunks, in pairs or a single one; two: half chunks, always in pairs

@@ -1,7 +1,7 @@
-"""The convolution kernels of small and middle grids: every instantiation of k_conv3x3_kw the
-host's rules choose, at maps smaller than one tile, one tile plus a remainder, and several ragged
-tiles, and k_conv_direct (the small network), against the CPU oracle.  The recurrent cell is checked
-alone on the GPU's own inputs."""
+"""The convolution kernels against the CPU oracle, at maps smaller than one tile, one tile plus a
+remainder, and many ragged tiles: every form of k_conv3x3_run and k_conv3x3s2_run, the walking stride-2
+kernel (a test of the host's planning holds that these sizes take them all), k_tiny_net and
+k_conv_direct (the small network).  The recurrent cell is checked alone on the GPU's own inputs."""
 import numpy as np
 import pytest
 
@@ -15,11 +15,11 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("nw,nh,batch", [
     (8, 8, 1),        # the smallest input: maps of 2 x 2 and 1 x 1 pixels, the last stage's the largest tensor
     (8, 8, 3),        # the same, several images in every tensor
-    (96, 64, 1),      # maps of 8 x 12, 4 x 6 and 2 x 3 pixels: less than a tile; 1, 2, 4 and 6 K splits
-    (130, 66, 6),     # three K splits (the last one shorter), grids beyond one round of workgroups
-    (130, 66, 16),    # one split, two and four channel groups per workgroup, both strides
-    (288, 160, 5),    # two splits with 8 x 8-pixel tiles
-    (288, 160, 12),   # one split with 8 x 8-pixel tiles, maps of 20 x 36, 10 x 18 and 5 x 9
+    (96, 64, 1),      # maps of 8 x 12, 4 x 6 and 2 x 3 pixels: tiles of 32 channels x 32 pixels, and those for tiny maps
+    (130, 66, 6),     # the former alone, grids beyond one round of workgroups
+    (130, 66, 16),    # runs that span several images
+    (288, 160, 5),    # four K splits at every layer but the first at stride 2
+    (288, 160, 12),   # tiles of 32 and 64 channels x 64 pixels, of 64 x 96; maps of 20 x 36, 10 x 18 and 5 x 9
 ])
 def test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch):
     from paper_2402_04466_amd.harness import AppStream
@@ -61,9 +61,9 @@ def test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch):
 
 @pytest.mark.parametrize("nw,nh,batch", [
     (40, 520, 2),     # maps of 2 x 17 pixels and wider: strips of a few columns, tiles over several images
-    (300, 170, 16),   # tiles of 32 and 64 channels x 64 pixels, of 64 x 96
-    (430, 250, 16),   # tiles of 64 channels x 128 pixels
-    (860, 500, 11),   # tiles of 64 channels x 160 pixels, maps no multiple of any strip
+    (300, 170, 16),   # tiles of 32 channels x 32 pixels, of 32 and 64 x 64, on several rounds of workgroups
+    (430, 250, 16),   # tiles of 64 channels x 64 and 128 pixels
+    (860, 500, 11),   # of 64 channels x 128 and 160 pixels, 96 at stride 2, maps no multiple of any strip; walking workgroups
 ])
 def test_tiles_of_consecutive_pixels_match_the_oracle(hs, nw, nh, batch):
     test_small_grid_convolutions_match_the_oracle(hs, nw, nh, batch)
@@ -72,7 +72,7 @@ def test_tiles_of_consecutive_pixels_match_the_oracle(hs, nw, nh, batch):
 @pytest.mark.parametrize("nw,nh,batch", [
     (8, 8, 1),        # a 2 x 2 map: one pixel tile, mostly beyond the layer's end
     (33, 17, 3),      # ragged maps, images that end inside a pixel tile, two K splits
-    (250, 190, 5),    # first layers without a split, the last ones at the line between one and two
+    (250, 190, 5),    # 240 tiles: nearly a round
 ])
 def test_small_network_layers_match_the_oracle(hs, nw, nh, batch):
     from paper_2402_04466_amd.harness import AppStream

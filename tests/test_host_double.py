@@ -33,8 +33,9 @@ def test_host_code(host_double, check):
     assert r.returncode == 0, (r.returncode, r.stdout[-500:], r.stderr[-500:])
 
 
-def test_refused_plans(tmp_path):
-    exe = str(tmp_path / "plan")
+@pytest.fixture(scope="session")
+def plan(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan")
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
     src = [os.path.join(HERE, "plan_main.cpp"), os.path.join(HERE, "fake_hip.cpp")]
     src += [os.path.join(build.CSRC, f) for f in ("hs_host.cpp", "hs_driver.cpp")]
@@ -42,8 +43,31 @@ def test_refused_plans(tmp_path):
                     "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"), "-I",
                     os.path.join(ROOT, "include"), "-I", build.CSRC, *src, "-o", exe, "-lpthread", "-ldl"],
                    check=True)
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    return exe
+
+
+def test_refused_plans(plan):
+    r = subprocess.run([plan], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-500:]
+
+
+def test_gpu_tests_run_every_convolution_kernel(plan):
+    """The sizes of the GPU tests against the oracle take every kernel and form that the planner can choose."""
+    import test_gpu_small_grids as t
+
+    def forms(net, *tests):
+        got = set()
+        for test in tests:
+            sizes = [m for m in test.pytestmark if m.name == "parametrize"][0].args[1]
+            for size in sizes:
+                r = subprocess.run([plan, net, *map(str, size)], capture_output=True, text=True, timeout=60)
+                assert r.returncode == 0
+                got |= set(r.stdout.split("\n")) - {""}
+        return got
+    big = forms("resnet18_convlstm", t.test_small_grid_convolutions_match_the_oracle,
+                t.test_tiles_of_consecutive_pixels_match_the_oracle)
+    assert big == {f"run {i}" for i in range(7)} | {f"s2_run {i}" for i in range(5)} | {"block64 0", "s2_dira 0"}, sorted(big)
+    assert forms("tiny4", t.test_small_network_layers_match_the_oracle) == {"tiny_net 0"}
 
 
 def test_tiles_of_consecutive_pixels(tmp_path):
