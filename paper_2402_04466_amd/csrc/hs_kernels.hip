@@ -57,9 +57,10 @@ __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
 
 // Block size: 256..512 threads, chosen by the host so that a source row is at most kResizeVecs 16-byte vectors per
 // thread.  A launch of one round of workgroups takes the size whose passes over the output row are as full as possible
-// (one 854 x 480 frame: two passes of 448 threads 4.8 us, four of 256 5.1).  A longer one takes the smallest: what counts
-// there is how many rows a CU has under way while each waits for its source (sixteen 416 x 240 frames 11.5 -> 9.6 us,
-// twelve 854 x 480 24.2 -> 23.2; of 192 and 128 threads, 10.7 and 27 to 29).  The row loads are the first
+// (two 854 x 480 frames of 3840 x 2160: two passes of 448 threads 6.9 us, four of 256 7.4).  A longer one takes the smallest:
+// what counts there is how many rows a CU has under way while each waits for its source (sixteen 416 x 240 frames: 256
+// threads 8.5 us, 448 10.1; eight 5.4, 6.6; six 854 x 480 11.5, 12.3; twelve of 192 and 128 threads 27 to 29).  Over 24
+// launches of 128 to 5760 rows that is the fastest of 256 to 512 threads or within 5 % of it.  The row loads are the first
 // thing a workgroup issues: the lookup tables and the row arithmetic are set up behind them.
 constexpr int kResizeVecs = 4;
 template <int NV>   // 16-byte vectors per thread and source row: 1, 2 or 4
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(512, 2) void k_tiny_net(ConvParams p) {
 // 11.3 -> 9.4 us, four 641x361 20.6 -> 18.1, sixteen 416x240 29.2 -> 24.5; twelve 854x480 frames as
 // two launches with the weights resident in LDS and registers 61.4 -> 58.9, which was the last
 // grid where two launches had been the faster form.)
-// FR and BD are the largest that leave three workgroups per CU (154 registers): with BD = 3 and two
+// FR and BD are the largest that leave three workgroups per CU (146 registers): with BD = 3 and two
 // workgroups 64 us at twelve frames; FR = 9 is equal, FR = 18 (two workgroups) 64.
 // Every output accumulates tap-major with four K-steps of 16 per tap, as in the other stride-1
 // kernels.

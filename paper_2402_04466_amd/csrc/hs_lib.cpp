@@ -495,9 +495,9 @@ struct Builder {
   // The form of k_conv3x3_run or k_conv3x3s2_run for a layer.  A tile's time is a fixed part and one per Cin chunk
   // (kRunForms, kRun2Forms, fitted to twelve 854 x 480 frames, where every CU works on several tiles); the launch lasts as
   // long as its busiest CU, which has ceil(tiles / 256) of them.  A CU with a single tile hides nothing of its latencies
-  // behind another one: 1 us more.  Over eleven sizes from one 192 x 110 to twelve 854 x 480 frames the form with the
-  // smallest sum is the fastest one or within 8 % of it (four 641 x 361 frames, 512 channels at stride 1: 9.6 us, the other
-  // forms 11.7 to 19.7).
+  // behind another one: 1 us more.  Over eleven sizes from one 192 x 110 to twelve 854 x 480 frames, all layers, the form with
+  // the smallest sum is the fastest one or within 8 % of it (four 641 x 361 frames, 512 channels at stride 1: 8.0 us, the
+  // other forms 10.5 to 17.3).
   template <class Form, class Plan>
   static void choose_form(ConvParams& c, const Form* forms, int n_forms, int any_map, Plan plan) {
     constexpr int kRound = 256;
@@ -525,8 +525,10 @@ struct Builder {
       const int n = c.batch * ((c.hout + 7) / 8) * ((c.wout + 7) / 8) * (c.cout / 128);   // tiles of 8 x 8 x 128
       if (c.chunks_per_tap == 1 && n > 1024) {
         // One chunk, more tiles than two rounds of workgroups: k_conv3x3s2_dira walks them, the next tile's patch fetched
-        // during the current one's products (two workgroups per CU are resident, so walk in one round).  Twelve 854 x 480
-        // frames (1344 tiles) 30.9 us, k_conv3x3s2_run 33.8; sixteen 416 x 240 frames (448 tiles) 17.7, 15.1.
+        // during the current one's products (two workgroups per CU are resident, so walk in one round), in steps of 10 us
+        // per 512 tiles; k_conv3x3s2_run goes by rounds of its own tiles.  Us at 854 x 480, the latter first: eight frames (896
+        // tiles) 23.7, 25.1, nine (1008) 27.0, 26.0, ten (1120) 28.7, 30.8, eleven (1232) 28.9, 30.0, twelve (1344) 33.1,
+        // 30.3, sixteen (1792) 43.3, 39.1; six 1280 x 720 (1440) 36.2, 31.5; sixteen 416 x 240 (448) 16.0, 17.3.
         c.variant = CONV_S2_DIRA;
         c.tiles_x = (c.wout + 7) / 8;
         c.tiles_m = c.batch * ((c.hout + 7) / 8) * c.tiles_x;
