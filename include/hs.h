@@ -131,8 +131,8 @@ typedef struct {
  * done by the first workgroups of each image in the overlay's launch, beside the drawing ones, and
  * they stamp their end themselves.  On frames so small that the drawing ends first, stage 3 and
  * the overlay end together.  Stage 3 of a batch, whose last image is drawn last, ends shortly
- * before the overlay, and that of a group's member
- * includes the wait for the other members' networks.
+ * before the overlay, and that of a group's member includes the wait for the other members'
+ * networks.
  * End-to-end latency = t_overlay_done_ns - t_submit_ns (Section II-C).
  *
  * Device pointers alias the queue slot the frame was given inside the application's

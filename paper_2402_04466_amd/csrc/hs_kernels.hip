@@ -613,7 +613,8 @@ __global__ __launch_bounds__(256, 3) void k_block64_fused(ConvParams p) {
   u32x4 fa[FR];
 #pragma unroll
   for (int q = 0; q < FR; ++q) fa[q] = load16(wa_buf, lane * 16, w0 + q * 1024);
-  if (tm >= (uint32_t)p.tiles_m) return;    // (only here: see k_conv3x3_run; its pixels lie behind the buffer, the weights are every tile's)
+  // (only here: see k_conv3x3_run; a surplus workgroup's pixels lie behind the buffer, and the weights are every tile's)
+  if (tm >= (uint32_t)p.tiles_m) return;
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int v = tid + 256 * i;
