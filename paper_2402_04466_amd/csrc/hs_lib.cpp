@@ -39,9 +39,9 @@ namespace hs {
   } while (0)
 
 // ---- kernel families (for timing) ----------------------------------------------------------
-enum Family { F_RESIZE, F_CONV, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_COUNT };
+enum Family { F_RESIZE, F_CONV, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_NET, F_COUNT };   // F_NET: the small network in one launch
 static const char* kFamilyName[F_COUNT] = {"resize_norm", "conv_mfma", "lstm_head",
-                                           "stem_pool_mfma", "postprocess", "overlay"};
+                                           "stem_pool_mfma", "postprocess", "overlay", "tiny_net_mfma"};
 
 struct Op {
   Family fam;
@@ -58,7 +58,7 @@ struct Op {
 static KernelDesc op_desc(const Op& op) {
   switch (op.fam) {
     case F_RESIZE: return describe(op.resize);
-    case F_CONV: return describe(op.conv);
+    case F_CONV: case F_NET: return describe(op.conv);
     case F_LSTM: return describe(op.lstm);
     case F_STEM: return describe(op.stem);
     case F_POST: return describe(op.post);
@@ -69,7 +69,7 @@ static KernelDesc op_desc(const Op& op) {
 static void* op_params(Op& op) {
   switch (op.fam) {
     case F_RESIZE: return &op.resize;
-    case F_CONV: return &op.conv;
+    case F_CONV: case F_NET: return &op.conv;
     case F_LSTM: return &op.lstm;
     case F_STEM: return &op.stem;
     case F_POST: return &op.post;
@@ -116,7 +116,7 @@ constexpr int kMaxLanes = 2;
 struct Slot {
   std::vector<Op> pre;     // stage 1: one launch, blockIdx.y = stream of the batch
   std::vector<Op> infer;   // stage 2: the network over the whole batch
-  std::vector<Op> infer_layers;   // the small network layer by layer, while kernels are being timed
+  std::vector<Op> infer_layers;   // the small network layer by layer, run as well while kernels are being timed
   std::vector<Op> infer_static;   // the same with the gate scratch in the library's fixed
                                   // device array (empty when the scratch needed exceeds it)
   std::vector<Op> post;    // stage 3: the channel maxima
@@ -750,8 +750,8 @@ struct Builder {
     conv_layer(t3, at, 8, 3, 1, 1, false, nullptr, &lg, true, false);    at += 8 * 32 * 9;
     blob_off = at;
     map_h = lg.h; map_w = lg.w; stateful = false;
-    // One launch for all layers, but the layers one after the other while kernels are being timed, and where the halos that
-    // k_tiny_net computes again, and its tiles beyond the map's edges, cost more than the launches and tensors it saves.  It
+    // One launch for all layers (and, while kernels are being timed, the layers one after the other behind it), unless the halos
+    // that k_tiny_net computes again, and its tiles beyond the map's edges, cost more than the launches and tensors it saves.  It
     // takes a round of 256 tiles at a time, the layers go by pixels: times in us, fitted to 35 sizes from one 128 x 128 frame
     // to one of 1448 x 1448, thin ones among them.  Measured, layers / one launch: one 128 x 128 frame 15.6 / 6.8, eight 320 x 320
     // 26.2 / 23.4, sixteen (1600 tiles) 41.5 / 39.9; sixteen 300 x 200 (1120 tiles, 84 % full) 27.6 / 28.9, eight 640 x 360
@@ -761,7 +761,7 @@ struct Builder {
     if (2.0 + 5.3 * rounds > std::max(15.6, 10.3 + 0.288e-3 * pixels)) return;
     layer_ops = ops;
     Op net;
-    net.fam = F_CONV;
+    net.fam = F_NET;
     net.conv = layer_ops[0].conv;
     const ConvParams& last = layer_ops[3].conv;
     net.conv.variant = CONV_TINY_NET;
@@ -1147,7 +1147,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       w.t_end = sb[i].t_stages + 1;
     };
     Op& lo = s.infer[b.logits_op];
-    if (lo.fam == F_CONV) bind_logits(lo.conv, lo.conv.out_f32);
+    if (lo.fam == F_CONV || lo.fam == F_NET) bind_logits(lo.conv, lo.conv.out_f32);
     else bind_logits(lo.lstm, lo.lstm.logits);
     if (!s.infer_layers.empty()) {
       s.infer_layers.front().conv.in = s.d_netin;
@@ -1843,8 +1843,7 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
                                 hipStream_t* stream_out, hipEvent_t frames_ready,
                                 bool static_scratch) {
   HS_HIP(hipSetDevice(app->ctx->device));
-  std::vector<Op>& infer = static_scratch ? s->infer_static
-                           : app->timing && !s->infer_layers.empty() ? s->infer_layers : s->infer;
+  std::vector<Op>& infer = static_scratch ? s->infer_static : s->infer;
   const int B = app->batch;
   const size_t n_map = (size_t)app->map_w * app->map_h;
   const size_t netin_img = (size_t)app->netin_h * app->netin_w * 4;
@@ -1929,6 +1928,9 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
     } else {
       st = run_ops(app, infer, lane_stream, event(s->ev_infer, maxima_here ? s->has_event : others_wait));
     }
+    if (st != HS_OK) return st;
+    // (to time them; what they leave is the same up to the order of fp32 sums)
+    if (app->timing && !s->infer_layers.empty()) st = run_ops(app, s->infer_layers, lane_stream, s->ev_infer);
     if (st != HS_OK) return st;
     if (!maxima_here) st = run_ops(app, s->post, lane_stream, event(s->ev_post, s->has_event));
     if (st != HS_OK) return st;

@@ -413,6 +413,25 @@ static void small_network_forms() {
   }
 }
 
+// While kernels are timed, the launch that every other frame makes of the small network is timed, too.
+static void timed_small_network() {
+  Program p(HS_NET_TINY4);
+  hs_app* app = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK && hs_set_kernel_timing(app, 1) == HS_OK);
+  hs_result r;
+  for (int i = 0; i < 2; ++i)
+    CHECK(hs_submit_frame(app, p.src(), p.dst(), (uint64_t)i) == HS_OK && hs_wait_result(app, &r, 1000000000) == HS_OK);
+  hs_kernel_time t[16];
+  int n = 0, net = 0, layers = 0;
+  CHECK(hs_get_kernel_times(app, t, 16, &n) == HS_OK && n <= 16);
+  for (int i = 0; i < n; ++i) {
+    if (!strcmp(t[i].name, "tiny_net_mfma")) net = (int)t[i].launches;
+    if (!strcmp(t[i].name, "conv_mfma")) layers = (int)t[i].launches;
+  }
+  CHECK(net == 2 && layers == 8);
+  CHECK(hs_destroy_app(app) == HS_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "packing_threads") packing_threads();
@@ -427,6 +446,7 @@ int main(int argc, char** argv) {
   else if (check == "prefetched_weights") prefetched_weights();
   else if (check == "tile_grids") tile_grids();
   else if (check == "small_network_forms") small_network_forms();
+  else if (check == "timed_small_network") timed_small_network();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
   return 0;
 }

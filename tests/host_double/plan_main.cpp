@@ -44,7 +44,7 @@ static int print_forms(const char* net, int w, int h, int batch) {
   Builder b(d, nullptr, false, false);
   b.walk(ph, pw);
   for (const Op& op : b.ops) {
-    if (op.fam != F_CONV) continue;
+    if (op.fam != F_CONV && op.fam != F_NET) continue;
     const ConvParams& c = op.conv;
     switch (c.variant) {
       case CONV_DIRECT: printf("direct %d\n", c.kw_splits); break;

@@ -112,7 +112,7 @@ def test_small_network_in_one_launch_equals_its_layers(hs, nw, nh, batch):
         host = [si.uniform_frames(1, fh, fw, 40 + j)[0] for j in range(batch)]
         d_in = [s.upload_frame(f) for f in host]
         got = []
-        for timed in (False, True):          # layer by layer while kernels are being timed
+        for timed in (False, True):          # layer by layer, behind the one launch, while kernels are being timed
             hs.hs_set_kernel_timing(s.app, timed)
             d_out = [s.new_output() for _ in host]
             assert s.submit_batch(d_in, d_out, 0) == hs.HS_OK
