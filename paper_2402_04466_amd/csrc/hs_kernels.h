@@ -210,7 +210,6 @@ struct OverlayLayer {
   // annotation layer: cross-hair and 'T'<k> label per present tool, opaque, in tool order
   const int* marks;                  // anchors written by the postprocess kernel, NULL: none
   int arm, half, scale;              // marker arm / half thickness, pixels per glyph cell
-  float rcp_scale;                   // 1/scale
   // stage 3's channel maxima of this layer's network, found in the overlay's launch: logits
   // [batch][8][hm*wm] and the records [batch] (NULL: a launch of their own has found them)
   const float* logits; PostRecord* rec; float theta;
@@ -222,7 +221,7 @@ struct OverlayLayer {
 struct OverlayParams {
   const uint8_t* src[kMaxBatch]; uint8_t* dst[kMaxBatch];   // per stream
   int batch; size_t pitch; int wf, hf;
-  float rcp_gpr, rcp_hf, rcp_wf;     // 1/ceil(wf/16), 1/hf, 1/wf (ceil(wf/16)*hf below 2^31)
+  float rcp_gpr, rcp_qpr, rcp_hf, rcp_wf;   // 1/ceil(wf/16), 1/ceil(wf/4), 1/hf, 1/wf (ceil(wf/4)*hf below 2^31)
   int n_layers;                      // layers drawn in order, each over the one before
   int n_max;                         // workgroups per image between the first and the drawing ones: 8 * n_layers
                                      // when some layer has a rec, else 0

@@ -11,6 +11,7 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // plain 16-byte register value
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3), aligned(4)));   // 12 bytes in memory, at any word
 
 // floor(num / d) for num, d < 2^31 where the quotient is < 2^22: float estimate, exact fix-up.
 __device__ __forceinline__ uint32_t udiv_est(uint32_t num, uint32_t d, float rcp_d) {
@@ -1730,22 +1731,32 @@ KernelDesc describe(const PostParams& p) {
 }
 
 // =============================================================================================
-// Stage 4: pure streaming.  A thread owns one group of 16 pixels (48 bytes, three 16-byte
-// accesses) of one frame row; groups are numbered row-major over the frame, 256 per workgroup,
-// so there is no per-row prologue and no barrier.  A group spans at most two cells of the
-// channel map when a cell is at least 16 pixels wide: both are fetched up front together with
-// the pixels (a third cell, on tiny frames, is fetched on demand).  A wavefront moves the 192
+// Stage 4: pure streaming, one read and one write of the frame, in two forms.
+//
+// Groups of 16 pixels (FINE == false).  A thread owns 48 bytes, three 16-byte accesses, of one frame
+// row; groups are numbered row-major over the frame, 256 per workgroup, so there is no per-row
+// prologue and no barrier.  A group sees at most two cells of the channel map (the host takes this
+// form only then): both are fetched up front together with the pixels.  A wavefront moves the 192
 // vectors of its 64 groups as consecutive 16-byte accesses and regroups them through LDS, instead
 // of every lane touching its own 48-byte span.  The last group of a row may hang over the row's
 // end: vectors that start beyond the pitch are not fetched, and of a vector that holds the end of
 // the pixels only their bytes are stored, so the padding between rows stays what it was.  (Those
 // groups used to go pixel by pixel: one such lane held up its wavefront for 45 byte loads, 54 us
 // instead of 11 for four 1279 x 719 frames with annotations.)
+//
+// Quads of 4 pixels (FINE == true).  A thread owns 12 bytes, which a wavefront reads and writes as
+// one run of 768, and fetches the channel byte of each pixel: any number of cells.  What bounds a
+// small frame is the chain of instructions of one thread, on a chip that it does not fill, so four
+// times the threads with a third of the chain each.
+//
 // Workgroup 0 of an image hands the host the stages' ends, the next n_max find stage 3's channel maxima (see
 // channel_maximum).
 // =============================================================================================
-// One layer of stage 4 applied to a group of 16 pixels held in registers (w[0..11], word j starts
-// with channel j mod 3): blend of the layer's channel map, then its annotations.
+// 0xffffffff where the condition holds, else 0.
+__device__ __forceinline__ uint32_t mask_of(bool c) { return c ? 0xffffffffu : 0u; }
+// Bits of a where m is set, else of b.
+__device__ __forceinline__ uint32_t pick_bits(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
+
 // Colour of channel k (0..7).  A select chain over the eight scalar palette words: indexing the
 // kernel-argument array with a per-lane k would be a vector load from memory, one more full
 // memory latency between the channel byte and the blend.
@@ -1756,28 +1767,80 @@ __device__ __forceinline__ uint32_t overlay_colour(const OverlayLayer& L, uint32
   return c;
 }
 
-// The channel-map cells a group of 16 pixels starting at (X0, Y) can see in layer L: its first
-// cell, and the two channel bytes fetched up front (a third cell, on tiny frames, on demand).
+// Where the annotation layer of L may draw on N pixels starting at (X0, Y), held as words w (N = 4 or 16; word j starts with
+// channel j mod 3).  A tool's drawing lies in one box; a wavefront visits only the tools whose box some lane meets, tools in
+// increasing order (later tools paint over earlier ones).  Lane i of every 16 fetches word i of the eight anchors: one memory
+// latency, and the loop reads them as scalars.  What a tool paints is a bit per pixel, spread to the bytes' masks.
+template <int N>
+__device__ __forceinline__ void overlay_marks(const OverlayLayer& L, uint32_t (&w)[3 * N / 4], int Y, int X0, int by) {
+  const int anchors = L.marks[(size_t)by * 16 + (threadIdx.x & 15)];
+  const int lab_w = 11 * L.scale, lab_h = 7 * L.scale;
+  // the cross-hair's bars are 2 * arm + 1 long and 2 * half + 1 thick; either may be the larger.  The
+  // label reaches further to the right than a bar (13 pixels past arm at least, half is at most 8)
+  const int ext = max(L.arm, L.half);
+#pragma unroll 1
+  for (int k = 0; k < 8; ++k) {
+    const int cx = __builtin_amdgcn_readlane(anchors, 2 * k), cy = __builtin_amdgcn_readlane(anchors, 2 * k + 1);
+    if (cx < 0) continue;
+    const int ox = cx + L.arm + 2, oy = cy - lab_h - 2;          // label origin
+    const bool met = Y >= min(cy - ext, oy) && Y <= cy + ext && X0 + N - 1 >= cx - ext && X0 < ox + lab_w;
+    if (!__any((int)met)) continue;
+    // |X - cx| <= reach: the wider of the two bars where the row meets both (-1: it meets neither)
+    const int dy = abs(Y - cy), reach = max(dy <= L.half ? L.arm : -1, dy <= L.arm ? L.half : -1);
+    uint32_t m[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) m[i] = mask_of(abs(X0 + i - cx) <= reach);
+    const bool label = Y >= oy && Y < oy + lab_h;
+    if (__any((int)label)) {
+      // this row's glyph cells as bits, cell 11 empty: what lies outside the label's pixels 0 .. lab_w - 1 takes that one.
+      // Pixel to cell: floor(x / scale) = x * ceil(65536 / scale) >> 16 for x <= 88, scale <= 8 (the excess x * scale / 65536
+      // stays below 1 / scale)
+      const uint32_t inv = (65536u + (uint32_t)L.scale - 1u) / (uint32_t)L.scale;
+      const int gy = (int)(mul24((uint32_t)max(0, min(Y - oy, lab_h - 1)), inv) >> 16);
+      const uint32_t row = (uint32_t)(L.glyph[0] >> (5 * gy)) & 31u, row_k = (uint32_t)(L.glyph[1 + k] >> (5 * gy)) & 31u;
+      const uint32_t cells = label ? row | row_k << 6 : 0u;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const uint32_t lx = min((uint32_t)(X0 + i - ox), (uint32_t)lab_w);
+        m[i] |= 0u - (cells >> (mul24(lx, inv) >> 16) & 1u);
+      }
+    }
+    const uint32_t col = L.pal[k], r = col & 0xffu, g = (col >> 8) & 0xffu, b = (col >> 16) & 0xffu;
+    const uint32_t c[3] = {r | g << 8 | b << 16 | r << 24, g | b << 8 | r << 16 | g << 24, b | r << 8 | g << 16 | b << 24};
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) {                            // four pixels are three words
+      w[3 * q] = pick_bits(pick_bits(0x00ffffffu, m[4 * q], m[4 * q + 1]), c[0], w[3 * q]);
+      w[3 * q + 1] = pick_bits(pick_bits(0x0000ffffu, m[4 * q + 1], m[4 * q + 2]), c[1], w[3 * q + 1]);
+      w[3 * q + 2] = pick_bits(pick_bits(0x000000ffu, m[4 * q + 2], m[4 * q + 3]), c[2], w[3 * q + 2]);
+    }
+  }
+}
+
+// The channel-map cells a group of 16 pixels starting at (X0, Y) sees in layer L: its first
+// cell, and the two channel bytes.
 struct OverlayCells {
-  const uint8_t* krow;
   int mx0;
   uint8_t k0, k1;
 };
+__device__ __forceinline__ const uint8_t* overlay_map_row(const OverlayParams& p, const OverlayLayer& L, int Y, int by) {
+  const int my = (int)udiv_est((uint32_t)(Y * L.hm), (uint32_t)p.hf, p.rcp_hf);
+  return L.kmap + ((size_t)by * L.hm + my) * L.wm;
+}
 __device__ __forceinline__ OverlayCells overlay_cells(const OverlayParams& p, const OverlayLayer& L,
                                                       int Y, int X0, int by) {
   OverlayCells c;
-  const int my = (int)udiv_est((uint32_t)(Y * L.hm), (uint32_t)p.hf, p.rcp_hf);
-  c.krow = L.kmap + ((size_t)by * L.hm + my) * L.wm;
+  const uint8_t* const krow = overlay_map_row(p, L, Y, by);
   c.mx0 = (int)udiv_est((uint32_t)(X0 * L.wm), (uint32_t)p.wf, p.rcp_wf);
-  c.k0 = c.krow[c.mx0];
-  c.k1 = c.krow[min(c.mx0 + 1, L.wm - 1)];
+  c.k0 = krow[c.mx0];
+  c.k1 = krow[min(c.mx0 + 1, L.wm - 1)];
   return c;
 }
 
+// One layer of stage 4 applied to a group of 16 pixels held in registers (w[0..11], word j starts
+// with channel j mod 3): blend of the layer's channel map, then its annotations.
 __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, const OverlayLayer& L,
                                                     const OverlayCells& cells, uint32_t (&w)[12],
                                                     int Y, int X0, int by) {
-  const uint8_t* krow = cells.krow;
   const int ia = 256 - L.a;
   const int mx0 = cells.mx0;
   const uint8_t k0 = cells.k0, k1 = cells.k1;
@@ -1787,8 +1850,7 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
   // its neighbour.  The field pair is below 2^24 and the factor at most 256: 24-bit multiplies
   // (full rate; the 32-bit ones run at a quarter of it) are exact.
   const int mx_last = (int)udiv_est((uint32_t)(min(X0 + 15, p.wf - 1) * L.wm), (uint32_t)p.wf, p.rcp_wf);
-  const bool one_cell = mx_last == mx0 || (mx_last == mx0 + 1 && k1 == k0);
-  if (one_cell) {
+  if (mx_last == mx0 || k1 == k0) {
     if (k0 != 0xff) {
       const uint32_t col = overlay_colour(L, k0);
       uint32_t t[3];
@@ -1803,7 +1865,7 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
                (mad24(o, (uint32_t)ia, co) & 0xff00ff00u);
       }
     }
-  } else if (mx_last == mx0 + 1) {
+  } else {
     // two cells: pixels [0, s) see k0, [s, 16) see k1.  Same packed blend with the colour
     // term chosen per byte (byte index < 3*s), then bytes of an undrawn cell are restored.
     const int rem = X0 * L.wm - mx0 * p.wf;
@@ -1831,94 +1893,52 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
       const uint32_t draw = (low & d0) | (~low & d1);
       w[j] = (blended & draw) | (w[j] & ~draw);
     }
-  } else {
-    int mx = mx0;
-    int rem = X0 * L.wm - mx0 * p.wf;
+  }
+  if (L.marks) overlay_marks<16>(L, w, Y, X0, by);
+}
+
+// The channel bytes of a quad of pixels starting at (X0, Y) in layer L, pixel i in byte i (0xff: nothing to draw).
+__device__ __forceinline__ uint32_t overlay_quad_cells(const OverlayParams& p, const OverlayLayer& L, int Y, int X0, int by) {
+  const uint8_t* const krow = overlay_map_row(p, L, Y, by);
+  uint32_t k[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint8_t k = mx == mx0 ? k0 : (mx == mx0 + 1 ? k1 : krow[min(mx, L.wm - 1)]);
-      if (k != 0xff) {
-        const uint32_t col = overlay_colour(L, k);
+  for (int i = 0; i < 4; ++i) k[i] = krow[udiv_est((uint32_t)(min(X0 + i, p.wf - 1) * L.wm), (uint32_t)p.wf, p.rcp_wf)];
+  return k[0] | k[1] << 8 | k[2] << 16 | k[3] << 24;
+}
+// One layer of stage 4 applied to a quad (three words): the same packed blend, every pixel with its own colour terms
+// (a * colour + 128; terms[k] = {red, green in the upper half}, {blue}), then the bytes of undrawn pixels are restored.
+__device__ __forceinline__ void overlay_layer_quad(const OverlayLayer& L, const uint2* terms, uint32_t cells, uint32_t (&w)[3],
+                                                   int Y, int X0, int by) {
+  if (__any((int)(cells != 0xffffffffu))) {
+    const uint32_t ia = 256u - (uint32_t)L.a;
+    uint2 t[4];
+    uint32_t d[4];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const int byte = 3 * i + c;                 // literal after unrolling
-          const uint32_t pc = (col >> (8 * c)) & 0xffu;
-          const uint32_t old = (w[byte >> 2] >> (8 * (byte & 3))) & 0xffu;
-          const uint32_t nw = mad24((uint32_t)L.a, pc, mad24((uint32_t)ia, old, 128u)) >> 8;
-          w[byte >> 2] = (w[byte >> 2] & ~(0xffu << (8 * (byte & 3)))) | (nw << (8 * (byte & 3)));
-        }
-      }
-      rem += L.wm;
-      while (rem >= p.wf) { rem -= p.wf; ++mx; }
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t k = (cells >> (8 * i)) & 0xffu;
+      d[i] = mask_of(k != 0xffu);
+      t[i] = terms[k & 7u];
+    }
+    // bytes: r0 g0 b0 r1 | g1 b1 r2 g2 | b2 r3 g3 b3; the terms of bytes 0 and 2, of bytes 1 and 3
+    const uint32_t te[3] = {(t[0].x & 0xffffu) | t[0].y << 16, t[1].x >> 16 | t[2].x << 16, t[2].y | (t[3].x & 0xffff0000u)};
+    const uint32_t to[3] = {t[0].x >> 16 | t[1].x << 16, t[1].y | (t[2].x & 0xffff0000u), (t[3].x & 0xffffu) | t[3].y << 16};
+    const uint32_t draw[3] = {pick_bits(0x00ffffffu, d[0], d[1]), pick_bits(0x0000ffffu, d[1], d[2]),
+                              pick_bits(0x000000ffu, d[2], d[3])};
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const uint32_t e = w[j] & 0x00ff00ffu, o = (w[j] >> 8) & 0x00ff00ffu;
+      const uint32_t blended = ((mad24(e, ia, te[j]) >> 8) & 0x00ff00ffu) | (mad24(o, ia, to[j]) & 0xff00ff00u);
+      w[j] = pick_bits(draw[j], blended, w[j]);
     }
   }
-  if (L.marks) {
-    // annotation layer: a tool's drawing lies in one box; only groups that meet a box look
-    // closer, pixel by pixel, tools in increasing order (later tools paint over earlier ones).
-    // The eight anchors are fetched together and tested first: one memory latency, and a wavefront
-    // visits only the tools that some lane meets.
-    const int* mk = L.marks + (size_t)by * 16;
-    const int lab_w = 11 * L.scale, lab_h = 7 * L.scale;
-    // the cross-hair's bars are 2 * arm + 1 long and 2 * half + 1 thick; either may be the larger.  The
-    // label reaches further to the right than a bar (13 pixels past arm at least, half is at most 8)
-    const int ext = max(L.arm, L.half);
-    uint32_t met = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int cx = mk[2 * k], cy = mk[2 * k + 1];
-      const int ox = cx + L.arm + 2, oy = cy - lab_h - 2;          // label origin
-      const bool in = cx >= 0 && Y >= min(cy - ext, oy) && Y <= cy + ext && X0 + 15 >= cx - ext &&
-                      X0 < ox + lab_w;
-      met |= in ? 1u << k : 0u;
-    }
-#pragma unroll 1
-    for (int k = 0; k < 8; ++k) {
-      if (!__any((int)((met >> k) & 1u))) continue;
-      if (!((met >> k) & 1u)) continue;
-      const int cx = mk[2 * k], cy = mk[2 * k + 1];
-      const int ox = cx + L.arm + 2, oy = cy - lab_h - 2;
-      const uint32_t col = L.pal[k];
-      // what this row paints, as pixel intervals around cx and a bit per label pixel
-      const int dy = abs(Y - cy);
-      // |X - cx| <= reach: the wider of the two bars where the row meets both
-      const int reach = max(dy <= L.half ? L.arm : -1, dy <= L.arm ? L.half : -1);
-      uint64_t lab_lo = 0, lab_hi = 0;       // label pixels lx = 0..63 and 64..87 of this row
-      if (Y >= oy && Y < oy + lab_h) {
-        const int gy = (int)udiv_est((uint32_t)(Y - oy), (uint32_t)L.scale, L.rcp_scale);
-        const uint32_t cells = (uint32_t)((L.glyph[0] >> (5 * gy)) & 31ull) |
-                               ((uint32_t)((L.glyph[1 + k] >> (5 * gy)) & 31ull) << 6);
-        const uint64_t run = (1ull << L.scale) - 1ull;               // scale <= 8 pixels per cell
-        for (int cell = 0; cell < 11; ++cell) {
-          if (!((cells >> cell) & 1u)) continue;
-          const int at = cell * L.scale;
-          if (at < 64) lab_lo |= run << at;
-          if (at + L.scale > 64) lab_hi |= at >= 64 ? run << (at - 64) : run >> (64 - at);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int X = X0 + i, lx = X - ox;
-        bool hit = abs(X - cx) <= reach;
-        if (lx >= 0 && lx < lab_w) hit = hit || (((lx < 64 ? lab_lo >> lx : lab_hi >> (lx - 64)) & 1ull) != 0);
-        if (hit) {
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const int byte = 3 * i + c;               // literal after unrolling
-            const uint32_t pc = (col >> (8 * c)) & 0xffu;
-            w[byte >> 2] = (w[byte >> 2] & ~(0xffu << (8 * (byte & 3)))) | (pc << (8 * (byte & 3)));
-          }
-        }
-      }
-    }
-  }
+  if (L.marks) overlay_marks<4>(L, w, Y, X0, by);
 }
 
 // LAYERS == false: exactly one layer (every single-network application).  LAYERS == true: the
 // n_layers layers of a multi-network application are applied in order, each on the result of
 // the one before, while the pixels sit in registers (one read and one write of the frame).
-template <bool LAYERS>
+template <bool LAYERS, bool FINE>
 __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
-  __shared__ u32x4 s_x[4][192];
   const int by = (int)blockIdx.y;                                // image of the batch
   const int nl = LAYERS ? p.n_layers : 1;
   const int b = (int)blockIdx.x - 1;
@@ -1943,88 +1963,156 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
     if (threadIdx.x == 0) L.rec[by].ticks[k] = (int32_t)(wall_clock64() - t_stage2);
     return;
   }
-  const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;          // groups per row, of the frame
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g_wave = (b - p.n_max) * 256 + wave * 64;            // first group of the wavefront
-  if (g_wave >= total) return;
   const uint8_t* const src = p.src[by];
   uint8_t* const dst = p.dst[by];
-  // rows of whole groups that butt against each other: the frame is one run of vectors
-  const bool flat = (p.wf & 15) == 0 && p.pitch == (size_t)48 * gpr;
-  // all quotients by float estimate + exact fix-up (operands < 2^31, quotients < 2^22)
-  const int g = min(g_wave + lane, total - 1);
-  const int Y = (int)udiv_est((uint32_t)g, (uint32_t)gpr, p.rcp_gpr), X0 = (g - Y * gpr) * 16;
-  // the first layer's map bytes are requested before the pixels, so the two fetches overlap
-  const OverlayCells first = overlay_cells(p, p.layer[0], Y, X0, by);
-  // vector 64 * j + lane of the wavefront: byte offset in the frame, and how many of its bytes are pixels
-  size_t v_off[3];
-  int v_bytes[3];
-  u32x4 t[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int v = 64 * j + lane;
-    const uint32_t gi = ((uint32_t)v * 171u) >> 9;               // v / 3 for v < 192
-    const int gv = g_wave + (int)gi;
-    if (flat) {
-      const bool in = gv < total;
-      v_off[j] = (size_t)(in ? g_wave * 3 + v : g_wave * 3) * 16;
-      v_bytes[j] = in ? 16 : 0;
-    } else {
-      const int yv = (int)udiv_est((uint32_t)min(gv, total - 1), (uint32_t)gpr, p.rcp_gpr);
-      const int in_row = (min(gv, total - 1) - yv * gpr) * 48 + (v - 3 * (int)gi) * 16;
-      v_bytes[j] = gv < total ? max(0, min(16, 3 * p.wf - in_row)) : 0;
-      v_off[j] = (size_t)yv * p.pitch + (v_bytes[j] > 0 ? in_row : 0);
-    }
-    t[j] = *reinterpret_cast<const u32x4*>(src + v_off[j]);
-  }
-  s_x[wave][lane] = t[0]; s_x[wave][64 + lane] = t[1]; s_x[wave][128 + lane] = t[2];
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  uint32_t w[12];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const u32x4 v = s_x[wave][3 * lane + j];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[4 * j + i] = v[i];
-  }
-  overlay_layer_group(p, p.layer[0], first, w, Y, X0, by);
-  if (LAYERS) {
-#pragma unroll 1
-    for (int l = 1; l < nl; ++l)
-      overlay_layer_group(p, p.layer[l], overlay_cells(p, p.layer[l], Y, X0, by), w, Y, X0, by);
-  }
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const u32x4 o = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-    s_x[wave][3 * lane + j] = o;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   // The launch's end as its last workgroup sees it, noted ahead of the pixels' stores, whose way to memory hides the
   // stamp's to the host.  (Behind them it puts 1.8 us on a frame.)
-  if (p.stamp_end && blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && (int)threadIdx.x < nl) {
-    StageStamps* const st = p.layer[LAYERS ? threadIdx.x : 0].stamps;
-    if (st) st->drawn = wall_clock64();
-  }
+  auto stamp_end = [&] {
+    if (p.stamp_end && blockIdx.x == gridDim.x - 1 && by == p.batch - 1 && (int)threadIdx.x < nl) {
+      StageStamps* const st = p.layer[LAYERS ? threadIdx.x : 0].stamps;
+      if (st) st->drawn = wall_clock64();
+    }
+  };
+  if constexpr (FINE) {
+    __shared__ uint2 s_terms[LAYERS ? kMaxLayers : 1][8];
+    const int qpr = (p.wf + 3) >> 2, total = qpr * p.hf;         // quads per row, of the frame
+    const int q_own = (b - p.n_max) * 256 + (int)threadIdx.x, q = min(q_own, total - 1);
+    const int Y = (int)udiv_est((uint32_t)q, (uint32_t)qpr, p.rcp_qpr), X0 = (q - Y * qpr) * 4;
+    const size_t at = (size_t)Y * p.pitch + (size_t)X0 * 3;
+    const int bytes = min(12, 3 * (p.wf - X0));                  // of the quad that are pixels
+    uint32_t cells[LAYERS ? kMaxLayers : 1];
+    cells[0] = overlay_quad_cells(p, p.layer[0], Y, X0, by);
+    uint32_t w[3];
+    if (bytes == 12) {
+      const u32x3 v = *reinterpret_cast<const u32x3*>(src + at);
+      w[0] = v[0]; w[1] = v[1]; w[2] = v[2];
+    } else {                                                     // words that hold pixels lie inside the row's pitch
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const u32x4 o = s_x[wave][64 * j + lane];
-    if (v_bytes[j] == 16) {
-      *reinterpret_cast<u32x4*>(dst + v_off[j]) = o;
-    } else if (v_bytes[j] > 0) {                                 // the end of a row inside this vector
+      for (int j = 0; j < 3; ++j) w[j] = 4 * j < bytes ? *reinterpret_cast<const uint32_t*>(src + at + 4 * j) : 0u;
+    }
+    if (LAYERS) {
 #pragma unroll
-      for (int i = 0; i < 15; ++i)
-        if (i < v_bytes[j]) dst[v_off[j] + i] = (uint8_t)(o[i >> 2] >> (8 * (i & 3)));
+      for (int l = 1; l < kMaxLayers; ++l)
+        if (l < nl) cells[l] = overlay_quad_cells(p, p.layer[l], Y, X0, by);
+    }
+    if (threadIdx.x < 8) {
+#pragma unroll
+      for (int l = 0; l < (LAYERS ? kMaxLayers : 1); ++l) {
+        const OverlayLayer& L = p.layer[l];
+        const uint32_t col = overlay_colour(L, threadIdx.x), a = (uint32_t)L.a;
+        s_terms[l][threadIdx.x] = make_uint2(mad24(a, col & 0xffu, 128u) | mad24(a, (col >> 8) & 0xffu, 128u) << 16,
+                                             mad24(a, (col >> 16) & 0xffu, 128u));
+      }
+    }
+    __syncthreads();
+    overlay_layer_quad(p.layer[0], s_terms[0], cells[0], w, Y, X0, by);
+    if (LAYERS) {
+#pragma unroll
+      for (int l = 1; l < kMaxLayers; ++l)
+        if (l < nl) overlay_layer_quad(p.layer[l], s_terms[l], cells[l], w, Y, X0, by);
+    }
+    stamp_end();
+    if (q_own < total) {
+      if (bytes == 12) {
+        *reinterpret_cast<u32x3*>(dst + at) = u32x3{w[0], w[1], w[2]};
+      } else {
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+          if (i < bytes) dst[at + i] = (uint8_t)(w[i >> 2] >> (8 * (i & 3)));
+      }
+    }
+  } else {
+    __shared__ u32x4 s_x[4][192];
+    const int gpr = (p.wf + 15) >> 4, total = gpr * p.hf;        // groups per row, of the frame
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g_wave = (b - p.n_max) * 256 + wave * 64;          // first group of the wavefront
+    if (g_wave >= total) return;
+    // rows of whole groups that butt against each other: the frame is one run of vectors
+    const bool flat = (p.wf & 15) == 0 && p.pitch == (size_t)48 * gpr;
+    // all quotients by float estimate + exact fix-up (operands < 2^31, quotients < 2^22)
+    const int g = min(g_wave + lane, total - 1);
+    const int Y = (int)udiv_est((uint32_t)g, (uint32_t)gpr, p.rcp_gpr), X0 = (g - Y * gpr) * 16;
+    // the first layer's map bytes are requested before the pixels, so the two fetches overlap
+    const OverlayCells first = overlay_cells(p, p.layer[0], Y, X0, by);
+    // vector 64 * j + lane of the wavefront: byte offset in the frame, and how many of its bytes are pixels
+    size_t v_off[3];
+    int v_bytes[3];
+    u32x4 t[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int v = 64 * j + lane;
+      const uint32_t gi = ((uint32_t)v * 171u) >> 9;             // v / 3 for v < 192
+      const int gv = g_wave + (int)gi;
+      if (flat) {
+        const bool in = gv < total;
+        v_off[j] = (size_t)(in ? g_wave * 3 + v : g_wave * 3) * 16;
+        v_bytes[j] = in ? 16 : 0;
+      } else {
+        const int yv = (int)udiv_est((uint32_t)min(gv, total - 1), (uint32_t)gpr, p.rcp_gpr);
+        const int in_row = (min(gv, total - 1) - yv * gpr) * 48 + (v - 3 * (int)gi) * 16;
+        v_bytes[j] = gv < total ? max(0, min(16, 3 * p.wf - in_row)) : 0;
+        v_off[j] = (size_t)yv * p.pitch + (v_bytes[j] > 0 ? in_row : 0);
+      }
+      t[j] = *reinterpret_cast<const u32x4*>(src + v_off[j]);
+    }
+    s_x[wave][lane] = t[0]; s_x[wave][64 + lane] = t[1]; s_x[wave][128 + lane] = t[2];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    uint32_t w[12];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const u32x4 v = s_x[wave][3 * lane + j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[4 * j + i] = v[i];
+    }
+    overlay_layer_group(p, p.layer[0], first, w, Y, X0, by);
+    if (LAYERS) {
+#pragma unroll 1
+      for (int l = 1; l < nl; ++l)
+        overlay_layer_group(p, p.layer[l], overlay_cells(p, p.layer[l], Y, X0, by), w, Y, X0, by);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const u32x4 o = {w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
+      s_x[wave][3 * lane + j] = o;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    stamp_end();
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const u32x4 o = s_x[wave][64 * j + lane];
+      if (v_bytes[j] == 16) {
+        *reinterpret_cast<u32x4*>(dst + v_off[j]) = o;
+      } else if (v_bytes[j] > 0) {                               // the end of a row inside this vector
+#pragma unroll
+        for (int i = 0; i < 15; ++i)
+          if (i < v_bytes[j]) dst[v_off[j] + i] = (uint8_t)(o[i >> 2] >> (8 * (i & 3)));
+      }
     }
   }
 }
 
+// Quads where a group of 16 pixels may see three cells of some layer's map, and for launches of fewer than 192 workgroups'
+// worth of such groups, which leave CUs idle.  Us, groups of 16 / quads (cells of 16 pixels and more): 640 x 360 6.5 / 4.3,
+// annotated 8.1 / 5.0; 960 x 540 (32 400 groups) 5.8 / 4.5; 1280 x 720 (57 600) 5.0 / 4.8; 1279 x 719 4.6 / 4.9; 1920 x 1080 6.1 / 5.3,
+// annotated 6.3 / 8.1; four 1279 x 719 (230 080) 6.7 / 8.1; twelve 1920 x 1080 24.1 / 30.9.  Before the quads and the annotations as
+// masks (a third cell fetched on demand, labels pixel by pixel): 320 x 240 with cells of 10 pixels 11.0 (4.8 now), annotated
+// 322 x 241 21.8 (4.8), four annotated 1279 x 719 15.3 (8.7), twelve annotated 1920 x 1080 37.4 (29.0).
+static bool overlay_fine(const OverlayParams& p) {
+  for (int l = 0; l < p.n_layers; ++l)
+    if (15 * p.layer[l].wm > p.wf) return true;
+  return (int64_t)((p.wf + 15) >> 4) * p.hf * p.batch < 192 * 256;
+}
+
 KernelDesc describe(const OverlayParams& p) {
-  const unsigned groups = (unsigned)(((p.wf + 15) >> 4) * p.hf);
-  const void* f = p.n_layers > 1 ? (const void*)k_overlay<true> : (const void*)k_overlay<false>;
-  return KernelDesc{f, dim3(1 + (unsigned)p.n_max + (groups + 255) / 256, p.batch), dim3(256), 0};
+  const bool fine = overlay_fine(p);
+  const unsigned threads = (unsigned)((fine ? (p.wf + 3) >> 2 : (p.wf + 15) >> 4) * p.hf);
+  const void* f = p.n_layers > 1 ? (fine ? (const void*)k_overlay<true, true> : (const void*)k_overlay<true, false>)
+                                 : (fine ? (const void*)k_overlay<false, true> : (const void*)k_overlay<false, false>);
+  return KernelDesc{f, dim3(1 + (unsigned)p.n_max + (threads + 255) / 256, p.batch), dim3(256), 0};
 }
 
 // ---------------------------------------------------------------------------------------------

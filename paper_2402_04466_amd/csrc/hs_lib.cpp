@@ -1187,7 +1187,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       std::memset(&op, 0, sizeof(op));
       op.batch = B; op.pitch = d->frame_pitch;
       op.wf = d->frame_w; op.hf = d->frame_h;
-      op.rcp_gpr = 1.0f / (float)((d->frame_w + 15) / 16);
+      op.rcp_gpr = 1.0f / (float)((d->frame_w + 15) / 16); op.rcp_qpr = 1.0f / (float)((d->frame_w + 3) / 4);
       op.rcp_hf = 1.0f / (float)d->frame_h; op.rcp_wf = 1.0f / (float)d->frame_w;
       op.n_layers = 1;
       OverlayLayer& L = op.layer[0];
@@ -1197,7 +1197,6 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
       L.a = a_q8;
       L.marks = sb[i].marks;
       L.arm = d->marker_arm; L.half = d->marker_half; L.scale = d->glyph_scale;
-      L.rcp_scale = 1.0f / (float)std::max(1, d->glyph_scale);
       for (int g = 0; g < 9; ++g) {
         uint64_t bits = 0;
         for (int r = 0; r < 7; ++r)

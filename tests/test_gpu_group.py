@@ -55,7 +55,7 @@ def _build(hs, ctx, specs, fw, fh, depth):
     return GroupStream(ctx, members), oracles
 
 
-@pytest.mark.parametrize("fw,fh", [(640, 360), (333, 187)])
+@pytest.mark.parametrize("fw,fh", [(640, 360), (333, 187), (1293, 760)])   # the last drawn by groups of 16 pixels
 def test_group_of_three_networks_matches_oracle(hs, ctx, fw, fh):
     specs = _specs(fw, fh)
     frames = si.tool_scene_frames(3, fh, fw, seed=40)

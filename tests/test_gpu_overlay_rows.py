@@ -86,3 +86,43 @@ def test_marker_shapes(hs, arm, half, scale):
     finally:
         s.close()
         hs.hs_shutdown(ctx)
+
+
+@pytest.mark.parametrize("fw,fh,extra_pitch,net_w,net_h,batch,annotate", [
+    (1023, 767, 0, 96, 64, 1, True),      # 49 088 groups of 16 pixels: quads
+    (1023, 768, 0, 96, 64, 1, True),      # 49 152: groups of 16
+    (1030, 378, 16, 64, 64, 2, True),     # 49 140, padded rows that end inside a word
+    (1021, 385, 16, 64, 64, 2, True),     # 49 280
+    (360, 67, 0, 96, 64, 1, False),       # 24 cells of 15 pixels
+    (359, 67, 0, 96, 64, 1, False),       # cells of less than 15: quads on any frame
+    (359, 460, 32, 96, 64, 5, True),
+    (361, 460, 32, 96, 64, 5, True),
+    (13, 7, 0, 96, 64, 2, False),         # more cells than pixels
+])
+def test_overlay_forms(hs, fw, fh, extra_pitch, net_w, net_h, batch, annotate):
+    """Both sides of the lines between the overlay's two forms, several images per launch; bit-exact as above."""
+    from paper_2402_04466_amd.harness import AppStream
+    pitch = (3 * fw + 15) // 16 * 16 + extra_pitch
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=fw, frame_h=fh, net_w=net_w, net_h=net_h, batch=batch,
+                  blob=si.he_normal_blob(si.TINY4_LAYERS, 11), palette=si.DEFAULT_PALETTE, frame_pitch=pitch, alpha=0.61,
+                  glyphs=si.DEFAULT_GLYPHS if annotate else None, marker_arm=9, marker_half=1, glyph_scale=3)
+    try:
+        frames = list(si.uniform_frames(batch, fh, fw, 21))
+        print(f"[overlay-forms] {fw}x{fh} pitch {pitch} batch {batch}", flush=True)
+        d_in, d_out = [s.upload_frame(f) for f in frames], [s.new_output() for _ in frames]
+        for o in d_out:
+            o.fill_(0xA5)
+        torch.cuda.synchronize()
+        assert s.submit_batch(d_in, d_out, 0) == hs.HS_OK
+        for f, r, o in zip(frames, s.wait_batch(), d_out):
+            g = s.fetch(r, o)
+            want = oracle.overlay(f, g["mask"], si.DEFAULT_PALETTE, 0.61)
+            if annotate:
+                want = oracle.annotate(want, g["argmax_idx"], g["present"], g["mask"].shape[2],
+                                       g["mask"].shape[1], si.DEFAULT_PALETTE, si.DEFAULT_GLYPHS, 9, 1, 3)
+            assert np.array_equal(g["overlay"], want)
+            assert bool((o[:, 3 * fw:] == 0xA5).all()), "row padding was written"
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
