@@ -441,7 +441,7 @@ typedef struct {
   int cpu;                   /* core the submitting thread pins itself to, -1: none        */
 } hs_feed;
 /* Drives n_feeds sources concurrently, one submitting thread each (the paper runs one
- * process per application, Section V-B), for n_frames frames per source, and returns when
+ * process per application, Section V-B; a single unpinned source back to back is driven by the caller's), for n_frames frames per source, and returns when
  * every result has been collected.  fps > 0: frame k of every source is submitted at
  * t0 + k / fps (absolute deadlines, clock_nanosleep on CLOCK_MONOTONIC); a frame that finds
  * its queue full is dropped and counted.  fps == 0: back to back, as fast as the queues take
