@@ -5,6 +5,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "hs_run.h"
@@ -88,53 +89,55 @@ constexpr Run2Form kRun2Forms[] = {
     {32, 32, 8, 40960, 32, 9, 1.2, 0.53},   // maps a few pixels wide or high
 };
 constexpr int kRun2FormCount = 5, kRun2FormAnyMap = 4;
-struct ConvParams {
+// What k_conv3x3_run and k_conv3x3s2_run read of a layer's parameters, and so all that their launches hand over.
+struct RunParams {
   const f16* in;
   const f16* wt_frag;   // weights in MFMA fragment order: [cout_pad / 32][Cin chunk][tap][K-step of 16][lane][8 halves], lane
                         // r + 32 h holding k = 16 * step + 8 * h .. + 7 of channel 32 * group + r
-  int hin, win, cin_pitch;
+  f16* out;             // out[m*out_pitch + n]
+  const f16* res;       // optional residual, res[m*res_pitch + n]
+  float* partial;       // [m][cout_pad] fp32
+  // CONV_BLOCK64: the second convolution's weights.  Stride 2: fused 1x1 stride-2 projection of the
+  // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
+  const f16* wt2_frag;
+  f16* out2;
+  // CONV_KW: weights of the layer that runs next, to be prefetched, in 128-byte lines (0: none)
+  const void* next_wt; int next_lines;
+  int cin_pitch, out_pitch, res_pitch, out2_pitch;
+  int cout_pad;         // multiple of the block's N tile
+  int chunks_per_tap;
+  int use_partial;      // 1: store the fp32 sums for the ConvLSTM epilogue, no epilogue here
+  int relu;
+  int tiles_m, tiles_n; // spatial x channel tiles; the grid is 8 * tiles_per_xcd workgroups
+  int tiles_per_xcd;    // ceil(workgroups / 8)
+  int n_block;          // channel tiles per block of the tile order (divides tiles_n;
+                        // 1: spatial tile fastest, tiles_n: channel tile fastest)
+  // bytes of the input (CONV_BLOCK64, too) and of the weights; log2 of n_block, reciprocal of tiles_m * n_block (run_div31); tiles
+  uint32_t run_in_bytes, run_w_bytes;
+  int run_nb_shift;
+  uint32_t run_by_blk;
+  RunGeometry run;
+};
+struct ConvParams : RunParams {
+  int hin, win;
   int mid_h, mid_w;     // CONV_TINY_NET
   int hout, wout, m;    // m = batch*hout*wout output pixels (images stacked along m)
   int batch, img_m;     // images per launch, pixels per image (hout*wout)
-  int cout, cout_pad;   // cout_pad: multiple of the block's N tile
+  int cout;
   int kc;               // 16, 32 or 64
   int variant;          // ConvVariant
   int kw_splits;        // CONV_DIRECT: K splits
   int tiles_x;          // spatial variants: tiles per output row
   uint32_t tiles_img, by_tiles_img, by_tiles_x;   // CONV_BLOCK64: tiles per image; reciprocals (run_div31)
-  int ntaps, kw, chunks_per_tap, nchunks, ktot;
+  int ntaps, kw, nchunks, ktot;
   int stride, pad;
   int chunks_per_split; // K split z handles chunks [z*chunks_per_split, ...)
-  int tiles_m, tiles_n; // spatial x channel tiles; the grid is 8 * tiles_per_xcd workgroups
   int tiles_per_wg;     // consecutive spatial tiles one workgroup walks (>= 1);
                         // workgroups = ceil(tiles_m / tiles_per_wg) * tiles_n
-  int tiles_per_xcd;    // ceil(workgroups / 8)
-  int n_block;          // channel tiles per block of the tile order (divides tiles_n;
-                        // 1: spatial tile fastest, tiles_n: channel tile fastest)
-  int use_partial;      // 1: store the fp32 sums for the ConvLSTM epilogue, no epilogue here
-  float* partial;       // [m][cout_pad] fp32
-  // fused epilogue (use_partial == 0)
-  f16* out;             // out[m*out_pitch + n]
-  int out_pitch;
-  const f16* res;       // optional residual, res[m*res_pitch + n]
-  int res_pitch;
-  int relu;
   float* out_f32;       // if set: the logits, planar fp32 out_f32[(image*8 + n)*img_m + pixel], instead of
                         // `out`; with them stage 3's per-cell outputs (see PostParams)
   float theta; float* heat; uint8_t* mask; uint8_t* kmap; uint64_t* t_end;
-  // CONV_BLOCK64: the second convolution's weights.  Stride 2: fused 1x1 stride-2 projection of the
-  // same input (no residual, no ReLU), or NULL: [cout_pad / 32][Cin chunk][K-step of 16][lane][8 halves]
-  const f16* wt2_frag;
-  f16* out2; int out2_pitch;
-  // CONV_KW: form (kRunForms, kRun2Forms), tiles; bytes of the input (CONV_BLOCK64, too) and of the weights; log2 of n_block, reciprocal of
-  // tiles_m * n_block (run_div31)
-  int run_form;
-  RunGeometry run;
-  uint32_t run_in_bytes, run_w_bytes;
-  int run_nb_shift;
-  uint32_t run_by_blk;
-  // CONV_KW: weights of the layer that runs next, to be prefetched, in 128-byte lines (0: none)
-  const void* next_wt; int next_lines;
+  int run_form;         // CONV_KW: form (kRunForms, kRun2Forms)
 };
 KernelDesc describe(const ConvParams& p);
 
@@ -218,7 +221,8 @@ struct OverlayLayer {
   const uint64_t* t_stages; StageStamps* stamps;
   uint64_t glyph[9];                 // bit (5*row + col) of glyph g, col 0 = leftmost
 };
-struct OverlayParams {
+template <int N>
+struct OverlayParamsOf {
   const uint8_t* src[kMaxBatch]; uint8_t* dst[kMaxBatch];   // per stream
   int batch; size_t pitch; int wf, hf;
   float rcp_gpr, rcp_qpr, rcp_hf, rcp_wf;   // 1/ceil(wf/16), 1/ceil(wf/4), 1/hf, 1/wf (ceil(wf/4)*hf below 2^31)
@@ -226,8 +230,10 @@ struct OverlayParams {
   int n_max;                         // workgroups per image between the first and the drawing ones: 8 * n_layers
                                      // when some layer has a rec, else 0
   int stamp_end;                     // the layers' stamps->drawn is wanted
-  OverlayLayer layer[kMaxLayers];
+  OverlayLayer layer[N];
 };
+typedef OverlayParamsOf<kMaxLayers> OverlayParams;   // begins like OverlayParamsOf<1>, all that a launch of one layer hands over
+static_assert(offsetof(OverlayParams, layer) == offsetof(OverlayParamsOf<1>, layer), "the same beginning");
 KernelDesc describe(const OverlayParams& p);
 
 // ---- scratch for callers that cannot allocate ---------------------------------------------

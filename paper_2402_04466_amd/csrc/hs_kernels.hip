@@ -301,7 +301,7 @@ __device__ __forceinline__ void store_half(f16* out, int pitch, bool relu, int m
   }
 }
 // And for one quad, channels cbase + 4h .. + 3; res: the lane's 8 bytes of the residual.
-__device__ __forceinline__ void store_quad(const ConvParams& p, int m, int cbase, int h, const float4& v0, const u32x4& res) {
+__device__ __forceinline__ void store_quad(const RunParams& p, int m, int cbase, int h, const float4& v0, const u32x4& res) {
   float v[4] = {v0.x, v0.y, v0.z, v0.w};
   const half4 rq = __builtin_bit_cast(half4, make_uint2(res[0], res[1]));
   half4 o;
@@ -954,7 +954,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3s2_dira(ConvParams p) {
 // At most four lines per thread, all in flight at once: a grid of few workgroups leaves the rest to the next layer (sixteen
 // 8 x 8 inputs, up to 27 lines per thread one after the other 150 us a pass, so 128; two 192 x 108 123, 114).
 constexpr int kTouched = 4;
-__device__ __forceinline__ void prefetch_next(const ConvParams& p, int block, int n_blocks, uint32_t (&x)[kTouched]) {
+__device__ __forceinline__ void prefetch_next(const RunParams& p, int block, int n_blocks, uint32_t (&x)[kTouched]) {
   const BufferRsrc buf = buffer_of(p.next_wt, (uint32_t)p.next_lines * 128);
   const uint32_t stride = (uint32_t)n_blocks * blockDim.x, first = (uint32_t)block * blockDim.x + threadIdx.x;
 #pragma unroll
@@ -995,7 +995,7 @@ __device__ __forceinline__ void prefetch_next(const ConvParams& p, int block, in
 // 12.9 / 12.0 / 12.2 / 27.2, twelve 854 x 480 frames 32.7 / 32.4 / 35.1 / 81 -> 29.6 / 25.8 / 26.3 / 62.
 // =============================================================================================
 template <int PG, int KS, int CW, int FR, int BD, int PL, int LDS, int OCC>
-__global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p) {
+__global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(RunParams p) {
   constexpr int NW = KS * CW, C = 32 * CW, PITCH = kRunPitch;
   constexpr int KK = 4 / KS, SPC = 9 * KK;        // K-steps of a tap, of a chunk, that a wavefront takes
   static_assert(2 * SPC % FR == 0, "the fragment ring must divide the K-steps of two chunks");
@@ -1213,7 +1213,7 @@ __global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3_run(ConvParams p)
 // 17.7 / 13.9 / 14.0 -> 15.1 / 12.3 / 12.1, twelve 854 x 480 frames 30.9 / 27.6 / 28.8 -> (k_conv3x3s2_dira) / 26.9 / 24.8.
 // =============================================================================================
 template <int PG, int KS, int CW, int BD, int PL, int LDS, int OCC>
-__global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(ConvParams p) {
+__global__ __launch_bounds__(64 * KS * CW, OCC) void k_conv3x3s2_run(RunParams p) {
   constexpr int NW = KS * CW, C = 32 * CW, VP = 2 * KS, U = VP + 1, PITCH = 8 * U;   // 16-byte vectors, LDS units per pixel
   constexpr int UNITS = 4 * PG;                                    // pieces of 16 channels x 32 pixels, the projection's too
   constexpr int UP = UNITS * NW * 2048 <= 2 * LDS || UNITS * NW * 2048 <= 65536 ? UNITS : UNITS / 2, PASSES = UNITS / UP, UN = UP / KS;
@@ -1822,11 +1822,13 @@ struct OverlayCells {
   int mx0;
   uint8_t k0, k1;
 };
-__device__ __forceinline__ const uint8_t* overlay_map_row(const OverlayParams& p, const OverlayLayer& L, int Y, int by) {
+template <int NL>
+__device__ __forceinline__ const uint8_t* overlay_map_row(const OverlayParamsOf<NL>& p, const OverlayLayer& L, int Y, int by) {
   const int my = (int)udiv_est((uint32_t)(Y * L.hm), (uint32_t)p.hf, p.rcp_hf);
   return L.kmap + ((size_t)by * L.hm + my) * L.wm;
 }
-__device__ __forceinline__ OverlayCells overlay_cells(const OverlayParams& p, const OverlayLayer& L,
+template <int NL>
+__device__ __forceinline__ OverlayCells overlay_cells(const OverlayParamsOf<NL>& p, const OverlayLayer& L,
                                                       int Y, int X0, int by) {
   OverlayCells c;
   const uint8_t* const krow = overlay_map_row(p, L, Y, by);
@@ -1838,7 +1840,8 @@ __device__ __forceinline__ OverlayCells overlay_cells(const OverlayParams& p, co
 
 // One layer of stage 4 applied to a group of 16 pixels held in registers (w[0..11], word j starts
 // with channel j mod 3): blend of the layer's channel map, then its annotations.
-__device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, const OverlayLayer& L,
+template <int NL>
+__device__ __forceinline__ void overlay_layer_group(const OverlayParamsOf<NL>& p, const OverlayLayer& L,
                                                     const OverlayCells& cells, uint32_t (&w)[12],
                                                     int Y, int X0, int by) {
   const int ia = 256 - L.a;
@@ -1898,7 +1901,8 @@ __device__ __forceinline__ void overlay_layer_group(const OverlayParams& p, cons
 }
 
 // The channel bytes of a quad of pixels starting at (X0, Y) in layer L, pixel i in byte i (0xff: nothing to draw).
-__device__ __forceinline__ uint32_t overlay_quad_cells(const OverlayParams& p, const OverlayLayer& L, int Y, int X0, int by) {
+template <int NL>
+__device__ __forceinline__ uint32_t overlay_quad_cells(const OverlayParamsOf<NL>& p, const OverlayLayer& L, int Y, int X0, int by) {
   const uint8_t* const krow = overlay_map_row(p, L, Y, by);
   uint32_t k[4];
 #pragma unroll
@@ -1938,7 +1942,7 @@ __device__ __forceinline__ void overlay_layer_quad(const OverlayLayer& L, const 
 // n_layers layers of a multi-network application are applied in order, each on the result of
 // the one before, while the pixels sit in registers (one read and one write of the frame).
 template <bool LAYERS, bool FINE>
-__global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
+__global__ __launch_bounds__(256) void k_overlay(OverlayParamsOf<LAYERS ? kMaxLayers : 1> p) {
   const int by = (int)blockIdx.y;                                // image of the batch
   const int nl = LAYERS ? p.n_layers : 1;
   const int b = (int)blockIdx.x - 1;
@@ -1990,7 +1994,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
 #pragma unroll
       for (int j = 0; j < 3; ++j) w[j] = 4 * j < bytes ? *reinterpret_cast<const uint32_t*>(src + at + 4 * j) : 0u;
     }
-    if (LAYERS) {
+    if constexpr (LAYERS) {
 #pragma unroll
       for (int l = 1; l < kMaxLayers; ++l)
         if (l < nl) cells[l] = overlay_quad_cells(p, p.layer[l], Y, X0, by);
@@ -2006,7 +2010,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
     }
     __syncthreads();
     overlay_layer_quad(p.layer[0], s_terms[0], cells[0], w, Y, X0, by);
-    if (LAYERS) {
+    if constexpr (LAYERS) {
 #pragma unroll
       for (int l = 1; l < kMaxLayers; ++l)
         if (l < nl) overlay_layer_quad(p.layer[l], s_terms[l], cells[l], w, Y, X0, by);
@@ -2067,7 +2071,7 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParams p) {
       for (int i = 0; i < 4; ++i) w[4 * j + i] = v[i];
     }
     overlay_layer_group(p, p.layer[0], first, w, Y, X0, by);
-    if (LAYERS) {
+    if constexpr (LAYERS) {
 #pragma unroll 1
       for (int l = 1; l < nl; ++l)
         overlay_layer_group(p, p.layer[l], overlay_cells(p, p.layer[l], Y, X0, by), w, Y, X0, by);
