@@ -141,6 +141,16 @@ struct ConvParams : RunParams {
 };
 KernelDesc describe(const ConvParams& p);
 
+// CONV_TINY_NET from the frame on: stage 1 in the same launch (r; its padded image is written, but not read).
+struct TinyFrameParams {
+  ResizeParams r;
+  const f16* wt_frag;
+  float* out_f32; float* heat; uint8_t* mask; uint8_t* kmap; uint64_t* t_end;   // as in ConvParams
+  float theta;
+  int mid_h, mid_w, hout, wout, m, img_m;
+};
+KernelDesc describe(const TinyFrameParams& p);
+
 // ConvLSTM gate non-linearities and state update from the gate pre-activations, plus the 1x1
 // head on the new h.  partial: [m][4*hid], channels ordered i, f, g, o (hid each);
 // hid must be 256.  c: fp32 [m][hid] updated in place; h: fp16 written to h_out[m*h_pitch + j];

@@ -64,6 +64,31 @@ __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
 // launches of 128 to 5760 rows that is the fastest of 256 to 512 threads or within 5 % of it.  The row loads are the first
 // thing a workgroup issues: the lookup tables and the row arithmetic are set up behind them.
 constexpr int kResizeVecs = 4;
+// The bilinear sum of the two source pixels that start in bytes 0 .. 5 of a (upper row) and c (lower row), rounded, per channel.
+__device__ __forceinline__ void resize_sum(const ResizeParams& p, uint32_t d, const uint32_t (&a)[2], const uint32_t (&c)[2], uint32_t wx0,
+                                           uint32_t wx1, uint32_t wy0, uint32_t wy1, uint32_t (&q)[3]) {
+  const uint64_t r0 = (uint64_t)a[1] << 32 | a[0], r1 = (uint64_t)c[1] << 32 | c[0];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint32_t p00 = (uint32_t)(r0 >> (8 * i)) & 0xffu, p01 = (uint32_t)(r0 >> (8 * i + 24)) & 0xffu;
+    const uint32_t p10 = (uint32_t)(r1 >> (8 * i)) & 0xffu, p11 = (uint32_t)(r1 >> (8 * i + 24)) & 0xffu;
+    // every factor is below 2^24 (weights <= 2*wo, 2*ho <= 2^15; a row sum <= 2*wo*255 < 2^24) and
+    // the sum below 2^31: 24-bit multiplies are exact here and run at four times the rate of
+    // the 32-bit ones
+    const uint32_t acc = mad24(wy0, mad24(wx0, p00, mul24(wx1, p01)),
+                               mul24(wy1, mad24(wx0, p10, mul24(wx1, p11))));
+    // floor((acc + d/2) / d) by multiplication: exact for numerators below 2^31
+    q[i] = __umulhi(acc + (d >> 1), p.d_magic) >> p.d_shift;
+  }
+}
+// First of the two source columns (rows) of output column (row) i of `out`, and the second one's weight out of 2 * out.
+__device__ __forceinline__ uint32_t resize_source(int i, int in, int out, float rcp, uint32_t& weight) {
+  const uint32_t span = 2u * (uint32_t)out;
+  const int n = max(0, min((2 * i + 1) * in - out, (in - 1) * (int)span));
+  const uint32_t first = udiv_est((uint32_t)n, span, rcp);
+  weight = (uint32_t)n - first * span;
+  return first;
+}
 template <int NV>   // 16-byte vectors per thread and source row: 1, 2 or 4
 __global__ __launch_bounds__(512) void k_resize_norm(ResizeParams p) {
   extern __shared__ __align__(16) uint8_t lds[];
@@ -75,10 +100,8 @@ __global__ __launch_bounds__(512) void k_resize_norm(ResizeParams p) {
   f16* const dst = p.dst + blockIdx.y * p.dst_img_stride;
   float* const dst_f32 = p.dst_f32 ? p.dst_f32 + blockIdx.y * p.dst32_img_stride : nullptr;
   const uint32_t dy = 2u * (uint32_t)p.ho, dx = 2u * (uint32_t)p.wo;
-  int ny = (2 * Y + 1) * p.hi - p.ho;
-  ny = max(0, min(ny, (p.hi - 1) * (int)dy));
-  const uint32_t y0 = udiv_est((uint32_t)ny, dy, p.rcp_dy);
-  const uint32_t fy = (uint32_t)ny - y0 * dy;
+  uint32_t fy;
+  const uint32_t y0 = resize_source(Y, p.hi, p.ho, p.rcp_dy, fy);
   const uint32_t y1 = min(y0 + 1u, (uint32_t)(p.hi - 1));
 
   // the two source rows: 16-byte loads into named registers (as arrays they end up in scratch
@@ -115,34 +138,20 @@ __global__ __launch_bounds__(512) void k_resize_norm(ResizeParams p) {
   __syncthreads();
   const uint32_t wy1 = fy, wy0 = dy - fy;
   for (int X = tid; X < p.wo; X += T) {
-    int nx = (2 * X + 1) * p.wi - p.wo;
-    nx = max(0, min(nx, (p.wi - 1) * (int)dx));
-    const uint32_t x0 = udiv_est((uint32_t)nx, dx, p.rcp_dx);
-    const uint32_t fx = (uint32_t)nx - x0 * dx;
+    uint32_t fx;
+    const uint32_t x0 = resize_source(X, p.wi, p.wo, p.rcp_dx, fx);
     const uint32_t wx1 = fx, wx0 = dx - fx;
     // The two source pixels x0, x0+1 are 6 consecutive bytes inside three aligned words: fetch
     // the words from each row and funnel-shift the bytes into place (v_alignbyte).  At the
     // right edge x0 + 1 is past the row, its weight fx is 0 there and the bytes read are the
     // next row or the padding behind the rows.
     const uint32_t b0 = 3u * x0, wi0 = b0 >> 2, sh = b0 & 3u;
-    const uint32_t a0 = __builtin_amdgcn_alignbyte(p0[wi0 + 1], p0[wi0], sh);      // bytes 0..3
-    const uint32_t a1 = __builtin_amdgcn_alignbyte(p0[wi0 + 2], p0[wi0 + 1], sh);  // bytes 4..7
-    const uint32_t c0 = __builtin_amdgcn_alignbyte(p1[wi0 + 1], p1[wi0], sh);
-    const uint32_t c1 = __builtin_amdgcn_alignbyte(p1[wi0 + 2], p1[wi0 + 1], sh);
-    const uint64_t r0 = (uint64_t)a1 << 32 | a0, r1 = (uint64_t)c1 << 32 | c0;
+    const uint32_t a[2] = {__builtin_amdgcn_alignbyte(p0[wi0 + 1], p0[wi0], sh),        // bytes 0..3
+                           __builtin_amdgcn_alignbyte(p0[wi0 + 2], p0[wi0 + 1], sh)};   // bytes 4..7
+    const uint32_t c[2] = {__builtin_amdgcn_alignbyte(p1[wi0 + 1], p1[wi0], sh),
+                           __builtin_amdgcn_alignbyte(p1[wi0 + 2], p1[wi0 + 1], sh)};
     uint32_t q[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const uint32_t p00 = (uint32_t)(r0 >> (8 * c)) & 0xffu, p01 = (uint32_t)(r0 >> (8 * c + 24)) & 0xffu;
-      const uint32_t p10 = (uint32_t)(r1 >> (8 * c)) & 0xffu, p11 = (uint32_t)(r1 >> (8 * c + 24)) & 0xffu;
-      // every factor is below 2^24 (weights <= 2*wo, 2*ho <= 2^15; a row sum <= 2*wo*255 < 2^24) and
-      // the sum below 2^31: 24-bit multiplies are exact here and run at four times the rate of
-      // the 32-bit ones
-      const uint32_t acc = mad24(wy0, mad24(wx0, p00, mul24(wx1, p01)),
-                                 mul24(wy1, mad24(wx0, p10, mul24(wx1, p11))));
-      // floor((acc + d/2) / d) by multiplication: exact for numerators below 2^31
-      q[c] = __umulhi(acc + (d >> 1), p.d_magic) >> p.d_shift;
-    }
+    resize_sum(p, d, a, c, wx0, wx1, wy0, wy1, q);
     half4 px;
     px[0] = s_lut16[q[0]];
     px[1] = s_lut16[q[1]];
@@ -316,7 +325,8 @@ __device__ __forceinline__ void store_quad(const RunParams& p, int m, int cbase,
 
 // The small network's last layer: logits of pixel ml of an image, eight channels, planar per image, and stage 3's per-cell
 // outputs (see PostParams).  Lane half h holds four of a pixel's channels; every lane of the wavefront must call it.
-__device__ __forceinline__ void store_logits(const ConvParams& p, bool valid, int img, int ml, int h, const floatx16& acc) {
+template <class P>   // ConvParams or TinyFrameParams
+__device__ __forceinline__ void store_logits(const P& p, bool valid, int img, int ml, int h, const floatx16& acc) {
   uint32_t set_channels = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -434,37 +444,118 @@ __global__ __launch_bounds__(256) void k_conv_direct(ConvParams p) {
 // before the first product by the wavefronts that need them.  LDS pixels are padded to 48 and 80 bytes against bank
 // conflicts.  Sums as in k_conv_direct with two K splits (first layer: one).
 // p.wt_frag: the four layers' weights in k_conv_direct's order, one after the other.
+//
+// FRAME: stage 1 is part of the launch.  The workgroup computes the 51 x 52 pixels of the network's input under its tile from
+// the frame (2.6 times as many as there are, with k_resize_norm's arithmetic), keeps them in LDS and stores its own 32 x 32.
+// What it saves is a launch, which is what bounds the host back to back, and a trip of the image through memory: sixteen annotated
+// 322 x 241 frames to 96 x 72 381 -> 316 us, one 320 x 240 frame to 128 x 128 29.3 -> 28.6.
 // =============================================================================================
-__global__ __launch_bounds__(512, 2) void k_tiny_net(ConvParams p) {
+template <bool FRAME> struct TinyNetArgs { typedef ConvParams type; };
+template <> struct TinyNetArgs<true> { typedef TinyFrameParams type; };
+template <bool FRAME>
+__global__ __launch_bounds__(512, 2) void k_tiny_net(typename TinyNetArgs<FRAME>::type p) {
   constexpr int N1 = 25, N2 = 12, N3 = 10, N4 = 8;                 // pixels per side of the layers' tiles
   constexpr int P1 = 24, P2 = 40;                                  // halves per LDS pixel of 16 and 32 channels
   constexpr int W2 = 3 * 1024, W3 = W2 + 9 * 1024, W4 = W3 + 18 * 1024, W_BYTES = W4 + 18 * 1024;
-  __shared__ __align__(16) f16 s1[N1 * N1 * P1], s2[N2 * N2 * P2], s3[N3 * N3 * P2];
+  constexpr int H0 = 2 * N1 + 1, W0 = 2 * N1 + 2, NP = (H0 * W0 + 511) / 512;   // FRAME: rows and pixels per row of the input, per thread
+  __shared__ __align__(16) f16 s1[N1 * N1 * P1], s2[N2 * N2 * P2], s3[N3 * N3 * P2], s0[FRAME ? H0 * W0 * 4 : 8];
 
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int x0 = N4 * (int)blockIdx.x, y0 = N4 * (int)blockIdx.y, img = (int)blockIdx.z;
-  const BufferRsrc in_buf = buffer_of(p.in, (uint32_t)(p.batch * p.hin * p.win * 8)), w_buf = buffer_of(p.wt_frag, W_BYTES);
+  const BufferRsrc w_buf = buffer_of(p.wt_frag, W_BYTES);
   const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
   // ---- operands: first layer's pixels (groups wave, wave + 8, wave + 16), then the weights
   u32x4 xb[3][3], w1[3], w2[9], w34[18];
+  u32x3 upper[NP], lower[NP];
+  f16 lut16 = (f16)0.0f;
+  float lut32 = 0.0f;
+  if constexpr (FRAME) {
+    lut16 = p.r.lut16[threadIdx.x & 255];
+    lut32 = p.r.lut32[threadIdx.x & 255];
+    // (rows are read in whole 16-byte vectors, no further: what lies behind the last one reads as zeros)
+    const BufferRsrc frame = buffer_of(p.r.src[img], (uint32_t)p.r.src_pitch * (uint32_t)(p.r.hi - 1) + (uint32_t)(3 * p.r.wi + 15) / 16 * 16);
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const int q = 32 * (wave + 8 * i) + r, ry = q / N1, rx = q - ry * N1, y = 2 * y0 - 5 + ry, x = 2 * x0 - 5 + rx;
-    const bool in = q < N1 * N1 && y >= 0 && y < p.mid_h && x >= 0 && x < p.mid_w;
-    const int off = in ? ((img * p.hin + 2 * y) * p.win + 2 * x + 2 * h) * 8 : kOutside;
+    for (int i = 0; i < NP; ++i) {
+      const int q = min((int)threadIdx.x + 512 * i, H0 * W0 - 1), Y = 4 * y0 - 11 + q / W0, X = 4 * x0 - 11 + q % W0;
+      uint32_t fx, fy;
+      const uint32_t sx = resize_source(X, p.r.wi, p.r.wo, p.r.rcp_dx, fx), sy = resize_source(Y, p.r.hi, p.r.ho, p.r.rcp_dy, fy);
+      const uint32_t at = sy * (uint32_t)p.r.src_pitch + (3 * sx & ~3u);
+      upper[i] = __builtin_bit_cast(u32x3, __builtin_amdgcn_raw_buffer_load_b96(frame, (int)at, 0, 0));
+      lower[i] = __builtin_bit_cast(u32x3, __builtin_amdgcn_raw_buffer_load_b96(
+          frame, (int)(at + (sy + 1 < (uint32_t)p.r.hi ? (uint32_t)p.r.src_pitch : 0u)), 0, 0));
+    }
+  } else {
+    const BufferRsrc in_buf = buffer_of(p.in, (uint32_t)(p.batch * p.hin * p.win * 8));
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky) xb[i][ky] = load16(in_buf, off, ky * p.win * 8);
+    for (int i = 0; i < 3; ++i) {
+      const int q = 32 * (wave + 8 * i) + r, ry = q / N1, rx = q - ry * N1, y = 2 * y0 - 5 + ry, x = 2 * x0 - 5 + rx;
+      const bool in = q < N1 * N1 && y >= 0 && y < p.mid_h && x >= 0 && x < p.mid_w;
+      const int off = in ? ((img * p.hin + 2 * y) * p.win + 2 * x + 2 * h) * 8 : kOutside;
+#pragma unroll
+      for (int ky = 0; ky < 3; ++ky) xb[i][ky] = load16(in_buf, off, ky * p.win * 8);
+    }
   }
 #pragma unroll
   for (int q = 0; q < 3; ++q) w1[q] = load16(w_buf, lane * 16, q * 1024);
+  // wavefronts 0-4 compute the second layer, 0-3 the third, 4 and 5 the last one (the others fetch nothing: 64 bytes a clock come in)
+  const int lane2 = wave < 5 ? lane * 16 : kOutside, lane34 = wave < 6 ? lane * 16 : kOutside;
 #pragma unroll
-  for (int q = 0; q < 9; ++q) w2[q] = load16(w_buf, lane * 16, W2 + q * 1024);
-  // wavefronts 0-3 compute the third layer, 4 and 5 the last one
+  for (int q = 0; q < 9; ++q) w2[q] = load16(w_buf, lane2, W2 + q * 1024);
 #pragma unroll
-  for (int q = 0; q < 18; ++q) w34[q] = load16(w_buf, lane * 16, (wave < 4 ? W3 : W4) + q * 1024);
+  for (int q = 0; q < 18; ++q) w34[q] = load16(w_buf, lane34, (wave < 4 ? W3 : W4) + q * 1024);
 
+  if constexpr (FRAME) {
+    // ---- stage 1: the image's pixels, zero outside it
+    __shared__ float s_lut32[256];
+    __shared__ f16 s_lut16[256];
+    if (threadIdx.x < 256) {
+      s_lut16[threadIdx.x] = lut16;
+      s_lut32[threadIdx.x] = lut32;
+    }
+    __syncthreads();
+    const uint32_t dx = 2u * (uint32_t)p.r.wo, dy = 2u * (uint32_t)p.r.ho;
+    f16* const dst = p.r.dst + (size_t)img * p.r.dst_img_stride;
+    float* const dst_f32 = p.r.dst_f32 ? p.r.dst_f32 + (size_t)img * p.r.dst32_img_stride : nullptr;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int q = (int)threadIdx.x + 512 * i, row = q / W0, col = q % W0, Y = 4 * y0 - 11 + row, X = 4 * x0 - 11 + col;
+      uint32_t fx, fy, v[3];
+      const uint32_t sh = 3 * resize_source(X, p.r.wi, p.r.wo, p.r.rcp_dx, fx) & 3u;
+      (void)resize_source(Y, p.r.hi, p.r.ho, p.r.rcp_dy, fy);
+      const uint32_t a[2] = {__builtin_amdgcn_alignbyte(upper[i][1], upper[i][0], sh), __builtin_amdgcn_alignbyte(upper[i][2], upper[i][1], sh)};
+      const uint32_t c[2] = {__builtin_amdgcn_alignbyte(lower[i][1], lower[i][0], sh), __builtin_amdgcn_alignbyte(lower[i][2], lower[i][1], sh)};
+      resize_sum(p.r, dx * dy, a, c, dx - fx, fx, dy - fy, fy, v);
+      const bool in = Y >= 0 && Y < p.r.ho && X >= 0 && X < p.r.wo;
+      half4 px = {s_lut16[v[0]], s_lut16[v[1]], s_lut16[v[2]], (f16)0.0f};
+      if (!in) px = half4{};
+      if (q < H0 * W0) *reinterpret_cast<half4*>(&s0[q * 4]) = px;
+      if (in && row >= 11 && row < 43 && col >= 11 && col < 43) {
+        *reinterpret_cast<half4*>(dst + ((size_t)(Y + p.r.pad_t) * p.r.dst_w + X + p.r.pad_l) * 4) = px;
+        if (dst_f32) {
+          const size_t plane = (size_t)p.r.ho * p.r.wo;
+          float* const o = dst_f32 + (size_t)Y * p.r.wo + X;
+          o[0] = s_lut32[v[0]];
+          o[plane] = s_lut32[v[1]];
+          o[2 * plane] = s_lut32[v[2]];
+        }
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && blockIdx.z == gridDim.z - 1)
+      *p.r.t_end = wall_clock64();
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int q = 32 * (wave + 8 * i) + r, ry = q / N1, rx = q - ry * N1, y = 2 * y0 - 5 + ry, x = 2 * x0 - 5 + rx;
+      const bool in = q < N1 * N1 && y >= 0 && y < p.mid_h && x >= 0 && x < p.mid_w;
+#pragma unroll
+      for (int ky = 0; ky < 3; ++ky) {
+        xb[i][ky] = u32x4{};
+        if (in) xb[i][ky] = *reinterpret_cast<const u32x4*>(&s0[((2 * ry + ky) * W0 + 2 * rx + 2 * h) * 4]);
+      }
+    }
+  }
   // ---- first layer: 3 -> 16 channels, stride 2.  Zero outside the layer's map, the next layer's padding
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -1433,7 +1524,7 @@ KernelDesc describe(const ConvParams& p) {
       return KernelDesc{f, grid, dim3(256), 0};
     }
     case CONV_TINY_NET:
-      return KernelDesc{(const void*)k_tiny_net, dim3((unsigned)(p.wout + 7) / 8, (unsigned)(p.hout + 7) / 8, (unsigned)p.batch),
+      return KernelDesc{(const void*)k_tiny_net<false>, dim3((unsigned)(p.wout + 7) / 8, (unsigned)(p.hout + 7) / 8, (unsigned)p.batch),
                         dim3(512), 0};
     case CONV_BLOCK64: return KernelDesc{(const void*)k_block64_fused, grid, dim3(256), 0};
     case CONV_S2_DIRA: return KernelDesc{(const void*)k_conv3x3s2_dira, grid, dim3(256), 0};
@@ -1441,6 +1532,10 @@ KernelDesc describe(const ConvParams& p) {
       return KernelDesc{p.stride == 1 ? run_kernel_of(p.run_form) : run2_kernel_of(p.run_form), grid, dim3(256), 0};
     default: return KernelDesc{nullptr, grid, dim3(256), 0};
   }
+}
+
+KernelDesc describe(const TinyFrameParams& p) {
+  return KernelDesc{(const void*)k_tiny_net<true>, dim3((unsigned)(p.wout + 7) / 8, (unsigned)(p.hout + 7) / 8, (unsigned)p.r.batch), dim3(512), 0};
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -39,9 +39,10 @@ namespace hs {
   } while (0)
 
 // ---- kernel families (for timing) ----------------------------------------------------------
-enum Family { F_RESIZE, F_CONV, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_NET, F_COUNT };   // F_NET: the small network in one launch
+enum Family { F_RESIZE, F_CONV, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_NET, F_FRAME_NET, F_COUNT };   // F_NET: the small network in one launch,
+// F_FRAME_NET: with stage 1 (never timed)
 static const char* kFamilyName[F_COUNT] = {"resize_norm", "conv_mfma", "lstm_head",
-                                           "stem_pool_mfma", "postprocess", "overlay", "tiny_net_mfma"};
+                                           "stem_pool_mfma", "postprocess", "overlay", "tiny_net_mfma", "frame_net_mfma"};
 
 struct Op {
   Family fam;
@@ -53,6 +54,7 @@ struct Op {
   StemPoolParams stem;
   PostParams post;
   OverlayParams overlay;
+  TinyFrameParams frame_net;
 };
 
 static KernelDesc op_desc(const Op& op) {
@@ -62,6 +64,7 @@ static KernelDesc op_desc(const Op& op) {
     case F_LSTM: return describe(op.lstm);
     case F_STEM: return describe(op.stem);
     case F_POST: return describe(op.post);
+    case F_FRAME_NET: return describe(op.frame_net);
     default: return describe(op.overlay);
   }
 }
@@ -73,6 +76,7 @@ static void* op_params(Op& op) {
     case F_LSTM: return &op.lstm;
     case F_STEM: return &op.stem;
     case F_POST: return &op.post;
+    case F_FRAME_NET: return &op.frame_net;
     default: return &op.overlay;
   }
 }
@@ -126,6 +130,7 @@ struct HalfBatch {
 struct Slot {
   std::vector<Op> pre;     // stage 1: one launch, blockIdx.y = stream of the batch
   std::vector<Op> infer;   // stage 2: the network over the whole batch
+  std::vector<Op> frame_net;      // stages 1 and 2 of the small network in one launch (empty: two are the better form)
   std::vector<Op> infer_layers;   // the small network layer by layer, run as well while kernels are being timed
   std::vector<Op> infer_static;   // the same with the gate scratch in the library's fixed
                                   // device array (empty when the scratch needed exceeds it)
@@ -1065,6 +1070,16 @@ static hs_status validate_desc(const hs_app_desc* d) {
 }
 
 // Builds the whole plan into `app`, or only sizes the workspace when app == NULL.
+// Whether stage 1 is part of the small network's launch: where that is one round of workgroups, 256 tiles.  A workgroup that
+// resizes 2.6 times its pixels takes 2 us longer, a launch of its own 4, and back to back the host waits for each launch.  Us, two
+// launches / one: 128 x 128 (16 tiles) 29.3 / 28.6, sixteen (256) 47 / 46.5; 320 x 320 (100) 35.2 / 34.5, three (300) 45 / 47,
+// sixteen 89 / 102; sixteen frames back to back 322 x 241 to 96 x 72 300 / 238, 1920 x 1080 to 320 x 200 340 / 270; four batches of
+// twelve 300 x 300 (1200) 250 / 292.
+static bool frame_net_pays(const hs_app_desc& d, int map_h, int map_w) {
+  return (double)d.frame_pitch * d.frame_h < 2147483648.0 &&             // 32-bit offsets
+         d.batch * ((map_h + 7) / 8) * ((map_w + 7) / 8) <= 256;
+}
+
 // A batch that finds the device idle runs as two halves side by side on the application's two streams: what a launch leaves
 // idle at its ends (boundary, first operands, the last round's sums and stores) goes to the other half's.  Every sum is
 // the whole batch's bit for bit (choose_split), so whether a batch is split shows in its time alone.
@@ -1280,6 +1295,18 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     if (!s.infer_layers.empty()) {
       s.infer_layers.front().conv.in = s.d_netin;
       bind_logits(s.infer_layers.back().conv, s.infer_layers.back().conv.out_f32);
+    }
+    if (lo.fam == F_NET && frame_net_pays(*d, mh, mw)) {
+      Op o;
+      o.fam = F_FRAME_NET;
+      TinyFrameParams& f = o.frame_net;
+      const ConvParams& c = lo.conv;
+      std::memset(&f, 0, sizeof(f));
+      f.r = s.pre[0].resize;
+      f.wt_frag = c.wt_frag;
+      f.out_f32 = c.out_f32; f.heat = c.heat; f.mask = c.mask; f.kmap = c.kmap; f.t_end = c.t_end; f.theta = c.theta;
+      f.mid_h = c.mid_h; f.mid_w = c.mid_w; f.hout = c.hout; f.wout = c.wout; f.m = c.m; f.img_m = c.img_m;
+      s.frame_net.push_back(o);
     }
     app->partial_bytes = b.partial_floats * sizeof(float);
     if (app->partial_bytes <= app->ctx->static_scratch_bytes && app->ctx->d_static_scratch) {
@@ -2113,9 +2140,13 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
     HS_HIP(hipGraphExecKernelNodeSetParams(s->graph_exec, s->resize_nodes[0], &kp));
     HS_HIP(hipGraphLaunch(s->graph_exec, lane_stream));
   } else {
-    st = run_ops(app, s->pre, lane_stream, event(s->ev_pre, false));
+    const bool frame_net = s->stamped && !static_scratch && !s->frame_net.empty();
+    if (frame_net) std::copy_n(s->pre[0].resize.src, B, s->frame_net[0].frame_net.r.src);
+    else st = run_ops(app, s->pre, lane_stream, event(s->ev_pre, false));
     if (st != HS_OK) return st;
-    if (s->wait_idx >= 0 && app->depth > 1 && !idle) {
+    if (frame_net) {
+      st = run_ops(app, s->frame_net, lane_stream, event(s->ev_infer, maxima_here ? s->has_event : others_wait));
+    } else if (s->wait_idx >= 0 && app->depth > 1 && !idle) {
       // the recurrent cell waits for the previous frame's state update (other lane)
       Slot& before = app->slots[(size_t)((s - app->slots.data()) + app->depth - 1) % app->depth];
       st = run_ops(app, infer, lane_stream, nullptr, 0, (size_t)s->wait_idx);

@@ -167,6 +167,12 @@ KernelDesc describe(const ConvParams& p) {
   if (p.wt_frag && fake::n_conv_launches < fake::kMaxConvLaunches) fake::conv_launches[fake::n_conv_launches++] = p;
   return some();
 }
+KernelDesc describe(const TinyFrameParams& p) {   // a launch of the small network as well
+  ConvParams c{};
+  c.variant = CONV_TINY_NET;
+  c.wt_frag = p.wt_frag;
+  return describe(c);
+}
 KernelDesc describe(const LstmEpilogueParams&) { return some(); }
 KernelDesc describe(const StemPoolParams&) { return some(); }
 KernelDesc describe(const PostParams&) { return some(); }
