@@ -75,8 +75,9 @@ constexpr RunForm kRunForms[] = {
     {32, 32, 3, 16384, 0.35, 0.47}, {32, 64, 4, 24576, 0.55, 0.57},  {64, 64, 4, 24576, 0.75, 1.03},
     {64, 96, 6, 26624, 1.3, 1.29},  {64, 128, 7, 36864, 1.9, 1.62}, {64, 160, 8, 40960, 2.3, 2.22},
     {32, 32, 7, 44032, 0.35, 0.47},   // patches of maps a few pixels wide or high, which hold mostly border
+    {32, 128, 7, 36864, 1.37, 0.745},   // partitions alone
 };
-constexpr int kRunFormCount = 7, kRunFormAnyMap = 6;
+constexpr int kRunFormCount = 8, kRunFormAnyMap = 6;
 // And of k_conv3x3s2_run: patch pixels per loading pass, 16-byte LDS units per patch pixel besides.
 struct Run2Form {
   int ch, px, passes, lds, step, units;

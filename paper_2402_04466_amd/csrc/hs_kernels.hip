@@ -1510,6 +1510,7 @@ static const void* run_kernel_of(int form) {
     case 4: return run_kernel<4, 9, 5, 2>();
     case 5: return run_kernel<5, 12, 5, 2>();
     case 6: return run_kernel<6, 9, 8, 1>();
+    case 7: return run_kernel<7, 9, 5, 2>();
     default: return nullptr;
   }
 }

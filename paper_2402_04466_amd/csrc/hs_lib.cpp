@@ -518,17 +518,21 @@ struct Builder {
   // the smallest sum is the fastest one or within 8 % of it (four 641 x 361 frames, 512 channels at stride 1: 8.0 us, the
   // other forms 10.5 to 17.3).
   // splits: only forms with that many K splits, whose sums are the same bit for bit (0: any).
+  // cus: the CUs that a round of tiles has, fewer in a partition (effective_cus), where wider forms then take fewer rounds.  Over 24
+  // layers on 40, 64, 80 and 128 CUs the form chosen is 1 % slower than the best one with as many K splits on average, at
+  // most 16 %.  (80 CUs, two 854 x 480 frames, us per layer, planned for 256 CUs / for their own: 512 channels 16.4 / 14.2, gates 37.0 / 31.6.)
+  static constexpr int kAllCus = 256;
   template <class Form, class Plan>
-  static void choose_form(ConvParams& c, const Form* forms, int n_forms, int any_map, int splits, Plan plan) {
-    constexpr int kRound = 256;
+  static void choose_form(ConvParams& c, const Form* forms, int n_forms, int any_map, int splits, int cus, Plan plan) {
     double best = 0;
     int form = -1;
     for (int i = 0; i < n_forms; ++i) {
-      if (i == any_map && form >= 0) break;
+      if ((i == any_map && form >= 0) || (i > any_map && cus >= kAllCus)) continue;
       ConvParams t = c;
       if ((splits && forms[i].splits() != splits) || !plan(t, i)) continue;
-      const int rounds = (t.tiles_m * t.tiles_n + kRound - 1) / kRound;
-      const double cost = rounds * (forms[i].cost + forms[i].chunk_cost * c.chunks_per_tap) + (rounds == 1 ? 1.0 : 0.0);
+      const int rounds = (t.tiles_m * t.tiles_n + cus - 1) / cus;
+      const double tile = forms[i].cost + forms[i].chunk_cost * c.chunks_per_tap;
+      const double cost = rounds * tile + (rounds == 1 ? 1.0 : 0.0);
       if (form < 0 || cost < best) { best = cost; form = i; }
     }
     if (form < 0) throw std::logic_error("no tile form for a layer of this network");
@@ -537,7 +541,7 @@ struct Builder {
 
   // Picks the kernel variant, the tile grid and the split along K.  like: the plan of the same layer over another number of
   // images, whose sums this one's are to be, bit for bit.
-  static void choose_split(ConvParams& c, const ConvParams* like = nullptr) {
+  static void choose_split(ConvParams& c, const ConvParams* like = nullptr, int cus = kAllCus) {
     // the shared-patch kernels address the input with 32-bit offsets (in halves)
     const bool fits32 = (double)c.batch * c.hin * c.win * c.cin_pitch < 2147483648.0;
     const bool s3x3 = c.ntaps == 9 && c.kw == 3 && c.pad == 1 && c.kc == 64 && c.cout % 128 == 0 && fits32;
@@ -556,10 +560,10 @@ struct Builder {
         c.tiles_n = c.cout / 128;
         c.tiles_per_wg = (n + 511) / 512;
       } else {
-        choose_form(c, kRun2Forms, kRun2FormCount, kRun2FormAnyMap, like ? kRun2Forms[like->run_form].splits() : 0, plan_run2);
+        choose_form(c, kRun2Forms, kRun2FormCount, kRun2FormAnyMap, like ? kRun2Forms[like->run_form].splits() : 0, cus, plan_run2);
       }
     } else if (s3x3 && c.stride == 1 && c.chunks_per_tap >= 2) {
-      choose_form(c, kRunForms, kRunFormCount, kRunFormAnyMap, like ? kRunForms[like->run_form].splits() : 0, plan_run);
+      choose_form(c, kRunForms, kRunFormCount, kRunFormAnyMap, like ? kRunForms[like->run_form].splits() : 0, cus, plan_run);
     } else if (c.cout <= 32 && c.kc <= 32 && c.chunks_per_tap == 1 && c.ntaps <= 9) {
       // two K splits, of at most five taps each, while tiles of 64 pixels would be fewer than 192
       c.variant = CONV_DIRECT;
@@ -1894,6 +1898,9 @@ hs_status hs_get_features(hs_app* app, int stream, float* x_out) {
   });
 }
 
+static void plan_for_cus(hs_app* app, int cus);
+static int effective_cus(const uint32_t* mask, int n_words, int device_cus);
+
 hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
                            const uint32_t* cu_mask_overlay, int n_words) {
   return guarded("hs_set_partition", [&]() -> hs_status {
@@ -1911,6 +1918,7 @@ hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
     if (st != HS_OK) return st;
     std::memset(app->claim, 0, sizeof(app->claim));
     app->partitioned = false;
+    plan_for_cus(app, Builder::kAllCus);
     return HS_OK;
   }
   uint32_t others[HS_MAX_CU_WORDS] = {0};
@@ -1924,8 +1932,38 @@ hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
   std::memset(app->claim, 0, sizeof(app->claim));
   for (int w = 0; w < n_words; ++w) app->claim[w] = cu_mask_infer[w] | cu_mask_overlay[w];
   app->partitioned = true;
+  plan_for_cus(app, effective_cus(cu_mask_infer, n_words, ctx->n_cus));
   return HS_OK;
   });
+}
+
+// Plans the convolutions anew for that many CUs.  (A slot's graph keeps the forms that it was built with.)
+static void plan_for_cus(hs_app* app, int cus) {
+  Slot& first = app->slots[0];
+  for (size_t i = 0; i < first.infer.size(); ++i) {
+    Op& op = first.infer[i];
+    if (op.fam != F_CONV || op.conv.variant != CONV_KW) continue;
+    const ConvParams before = op.conv;
+    Builder::choose_split(op.conv, &before, cus);
+    for (Slot& s : app->slots) {
+      if (&s != &first) s.infer[i] = Builder::part_of(s.infer[i], 0, app->batch, &op);
+      if (!s.infer_static.empty()) s.infer_static[i] = Builder::part_of(s.infer_static[i], 0, app->batch, &op);
+    }
+  }
+}
+// CUs that a launch under the mask keeps busy.  Bit i is a CU of XCD i mod 8, in its shader engine i / 8 mod 4, and workgroups
+// are dealt out evenly to the engines that have CUs: the one with the fewest sets the pace.  (Every layer timed on 80 CUs, two or
+// three per engine, takes as long as on 64: gates of two 854 x 480 frames 31.6 and 31.4 us; on 40 as on 32.)
+static int effective_cus(const uint32_t* mask, int n_words, int device_cus) {
+  const int xcds = xcd_count(device_cus);
+  constexpr int kEngines = 4;
+  std::vector<int> n((size_t)xcds * kEngines, 0);
+  for (int i = 0; i < device_cus && i < 32 * n_words; ++i)
+    if (mask[i / 32] >> (i % 32) & 1u) ++n[(size_t)(i % xcds * kEngines + i / xcds % kEngines)];
+  int engines = 0, fewest = device_cus;
+  for (int k : n)
+    if (k) { ++engines; fewest = std::min(fewest, k); }
+  return engines ? engines * fewest : device_cus;
 }
 
 // Marks the slot as in flight and wakes the completion thread (the last step of a submit).

@@ -63,6 +63,30 @@ int main(int argc, char** argv) {
     for (int chunks = 1; chunks <= 8; ++chunks)
       // four K splits: whole chunks, in pairs or a single one; two: half chunks, always in pairs
       CHECK(plans(chunks, form) == (kRun2Forms[form].splits() == 2 || chunks == 1 || chunks % 2 == 0));
+  // CUs that a mask keeps busy: engines with CUs times the fewest of one
+  auto busy = [](int from, int to) {
+    uint32_t mask[8] = {0};
+    for (int i = from; i < to; ++i) mask[i / 32] |= 1u << (i % 32);
+    return effective_cus(mask, 8, 256);
+  };
+  CHECK(busy(0, 256) == 256 && busy(0, 128) == 128 && busy(0, 80) == 64 && busy(80, 160) == 64 && busy(0, 40) == 32 && busy(0, 16) == 16);
+  // a layer planned for fewer CUs: as many K splits; for all of them again: the plan it had
+  for (int chunks : {2, 4, 8, 12})
+    for (int batch : {1, 2, 3}) {
+      ConvParams c;
+      memset(&c, 0, sizeof(c));
+      c.batch = batch; c.hin = c.hout = 15; c.win = c.wout = 27; c.img_m = 405; c.m = batch * 405; c.cin_pitch = 64 * chunks;
+      c.cout = c.cout_pad = 512; c.kc = 64; c.ntaps = 9; c.kw = 3; c.stride = 1; c.pad = 1;
+      c.chunks_per_tap = chunks; c.nchunks = 9 * chunks; c.ktot = 64 * c.nchunks;
+      Builder::choose_split(c);
+      const int form = c.run_form;
+      for (int cus : {16, 32, 64, 128, 256}) {
+        const ConvParams before = c;
+        Builder::choose_split(c, &before, cus);
+        CHECK(kRunForms[c.run_form].splits() == kRunForms[form].splits());
+      }
+      CHECK(c.run_form == form);
+    }
   const hs_app_desc d = description();
   for (bool with_projection : {true, false}) {
     Builder b(d, nullptr, false, false);
