@@ -1090,10 +1090,10 @@ static bool frame_net_pays(const hs_app_desc& d, int map_h, int map_w) {
 static hs_status build_halves(hs_app* app) {
   // Where 38 launches instead of 19 keep the host ahead of the GPU: 4 to 4.9 us each, depending on the process.  Us, whole / halves in
   // the slower and the faster kind: nine 416 x 240 frames (0.90 M pixels) 187 / 208, 187; seven 480 x 270 (0.91) 187 / 208, 190; four 641 x
-  // 361 (0.93) 199 / 202, 184; five 640 x 360 (1.15) 234 / 225, 212; three 854 x 480 (1.23) 235 / 230, 220; sixteen 416 x 240
+  // 361 (0.93) 199 / 202, 184; five 640 x 360 (1.15) 234 / 225, 212 (but smaller frames, more of them, 193 / 199); three 854 x 480 (1.23) 235 / 230, 220; sixteen 416 x 240
   // (1.60) 274 / 243, 235; four 854 x 480 (1.64) 271 / 242, 236; twelve (4.92) 580 / 528; sixteen 771 / 690.
   const int B = app->batch;
-  if (!app->stateful || app->lanes < 2 || B < 2 || (double)B * app->desc.net_w * app->desc.net_h < 1e6) return HS_OK;
+  if (!app->stateful || app->lanes < 2 || B < 2 || (double)B * app->desc.net_w * app->desc.net_h < 1.2e6) return HS_OK;
   for (Slot& s : app->slots)
     for (int k = 0; k < 2; ++k) {
       HalfBatch& h = s.halves[k];
@@ -1810,6 +1810,11 @@ hs_status hs_create_app(hs_ctx* ctx, const hs_app_desc* desc, hs_app** out) {
   }
   if (st == HS_OK) st = make_streams(app.get(), nullptr, nullptr, 0);
   if (st != HS_OK) return st;
+  if (app->slots[0].halves[1].n > 0) {   // the first batch needs both streams, and a stream's first launch takes 0.1 ms longer
+    for (int l = 0; l < app->lanes; ++l) launch_fill_zero(app->d_concat[l], 16, app->s_lane[l]);
+    HS_HIP(hipGetLastError());
+    for (int l = 0; l < app->lanes; ++l) HS_HIP(hipStreamSynchronize(app->s_lane[l]));
+  }
   app->completer = std::thread(completer_main, app.get());
   {
     std::lock_guard<std::mutex> lk(ctx->mu);

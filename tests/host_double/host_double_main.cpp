@@ -358,7 +358,7 @@ static void prefetched_weights() {
 static void halves_of_a_batch() {
   std::vector<hs::ConvParams> launched[2];
   for (int halves = 0; halves < 2; ++halves) {
-    Program p(HS_NET_RESNET18_CONVLSTM, 5, 700, 300);
+    Program p(HS_NET_RESNET18_CONVLSTM, 5, 820, 300);
     p.d.queue_depth = halves ? 2 : 1;
     size_t need = 0;
     CHECK(hs_query_workspace(&p.d, &need) == HS_OK);

@@ -9,11 +9,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("batch,nw,nh,depth,annotate", [
-    (2, 900, 560, 2, False),
+    (2, 1100, 560, 2, False),
     (3, 854, 480, 4, False),      # halves of two and one; the 64 -> 128-channel layer's tiles of consecutive pixels
-    (5, 640, 360, 2, True),       # stage 3 in launches of its own
+    (5, 680, 360, 2, True),       # stage 3 in launches of its own
     (12, 854, 480, 2, False),     # that layer as a walk over its tiles
-    (16, 300, 214, 4, False),
+    (16, 300, 256, 4, False),
 ])
 def test_halves_are_the_whole_batch(hs, batch, nw, nh, depth, annotate):
     from paper_2402_04466_amd.harness import AppStream
