@@ -229,7 +229,9 @@ hs_status hs_get_features(hs_app* app, int stream, float* x_out);
  * empty, names a CU the device does not have, or intersects CUs claimed by another
  * application of the context. On MI355X CU i belongs to XCD i mod 8 and every mask must
  * contain at least one CU of each XCD (HS_E_INVAL otherwise): build masks from whole groups
- * of 8 consecutive CUs. Passing NULL for both masks releases the claim and
+ * of 8 consecutive CUs, best of 32: workgroups go evenly to an XCD's four shader engines (CU i: engine i / 8
+ * mod 4), so 80 CUs are as fast as 64.  The network's layers are planned for the CUs that the inference mask
+ * keeps busy; results are the whole device's bit for bit.  Passing NULL for both masks releases the claim and
  * returns the application to the unpartitioned state (all CUs, claims nothing).
  * HS_E_STATE while frames are in flight. */
 hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
@@ -290,7 +292,8 @@ hs_status hs_wait_result(hs_app* app, hs_result* out, uint64_t timeout_ns);
 /* Batched applications (desc.batch = B > 1): one frame of each of the B streams per call.
  * d_frames / d_overlay_outs are HOST arrays of B device pointers (same rules per frame as
  * hs_submit_frame). The B frames share the time stamps of the call; results come back as B
- * consecutive hs_result entries (stream order) written to out[0..B-1]. The single-frame
+ * consecutive hs_result entries (stream order) written to out[0..B-1].  A large batch that finds the device idle
+ * runs as two halves side by side on the application's two streams, with the same results bit for bit.  The single-frame
  * calls above return HS_E_STATE on a batched application; with B = 1 both forms work. */
 hs_status hs_submit_batch(hs_app* app, const uint8_t* const* d_frames,
                           uint8_t* const* d_overlay_outs, uint64_t frame_id);
