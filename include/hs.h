@@ -292,8 +292,7 @@ hs_status hs_wait_result(hs_app* app, hs_result* out, uint64_t timeout_ns);
 /* Batched applications (desc.batch = B > 1): one frame of each of the B streams per call.
  * d_frames / d_overlay_outs are HOST arrays of B device pointers (same rules per frame as
  * hs_submit_frame). The B frames share the time stamps of the call; results come back as B
- * consecutive hs_result entries (stream order) written to out[0..B-1].  A large batch that finds the device idle
- * runs as two halves side by side on the application's two streams, with the same results bit for bit.  The single-frame
+ * consecutive hs_result entries (stream order) written to out[0..B-1].  The single-frame
  * calls above return HS_E_STATE on a batched application; with B = 1 both forms work. */
 hs_status hs_submit_batch(hs_app* app, const uint8_t* const* d_frames,
                           uint8_t* const* d_overlay_outs, uint64_t frame_id);

@@ -314,29 +314,6 @@ void worker_main(Worker* w) {
   }
 }
 
-// The applications that a run of these feeds drives, told while it lasts that their frames do not come alone.
-class Crowd {
- public:
-  Crowd(const hs_feed* feeds, int n_feeds, bool back_to_back) {
-    int others = 0;
-    for (int i = 0; i < n_feeds; ++i) {
-      hs_app* const a = feeds[i].mux ? feeds[i].mux->app : feeds[i].app;
-      if (feeds[i].group || !a) ++others;
-      else if (std::find(apps_.begin(), apps_.end(), a) == apps_.end()) apps_.push_back(a);
-    }
-    if (!back_to_back && apps_.size() + others < 2) apps_.clear();
-    for (hs_app* a : apps_) hs_internal_app_crowd(a, 1);
-  }
-  ~Crowd() {
-    for (hs_app* a : apps_) hs_internal_app_crowd(a, -1);
-  }
-  Crowd(const Crowd&) = delete;
-  Crowd& operator=(const Crowd&) = delete;
-
- private:
-  std::vector<hs_app*> apps_;
-};
-
 }  // namespace
 
 extern "C" hs_status hs_run_feeds(const hs_feed* feeds, int n_feeds, double fps, int n_frames,
@@ -369,9 +346,6 @@ extern "C" hs_status hs_run_feeds(const hs_feed* feeds, int n_feeds, double fps,
       w.t0 = t0;
       w.period = fps > 0.0 ? (uint64_t)(1e9 / fps) : 0;
     }
-    // Batches that have the device to themselves run as two halves side by side; those that share it with their feed's next ones or
-    // with other applications' must not: three applications of three 1080p streams, two batches each, 945 -> 1074 us.
-    Crowd crowd(feeds, n_feeds, fps == 0.0 && n_frames > 1);
     const uint64_t t_begin = now_ns();
     // A single feed runs on the caller's thread, which would only wait, unless the feed sets its thread's core or timer: a thread
     // started and joined costs 40 to 60 us (sixteen annotated 322 x 241 frames 434 -> 392 us, twelve 1920 x 1080 1047 -> 998, four batches of twelve 2065 -> 2000).

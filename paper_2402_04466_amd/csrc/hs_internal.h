@@ -68,5 +68,4 @@ hs_status guarded(const char* fn, F&& body) {
 // What the per-stream front (hs_mux) must know of the application it drives.
 int hs_internal_app_batch(const hs_app* app);      // streams per submit
 int hs_internal_app_grouped(const hs_app* app);    // 1 while a member of a group
-void hs_internal_app_crowd(hs_app* app, int calls);   // +1 / -1: a call brings more frames at once than this application's next one
 

@@ -117,16 +117,6 @@ enum SlotState { SLOT_FREE = 0, SLOT_INFLIGHT = 1, SLOT_DONE = 2 };
 // measured with one graph launch per frame, about 75 us: no gain.)
 constexpr int kMaxLanes = 2;
 
-// One half of a batch that comes alone: its own launches on a stream of its own, side by side with the other half's (see
-// build_halves).  The first half's events and stamps are the slot's.
-struct HalfBatch {
-  int first = 0, n = 0;    // images
-  std::vector<Op> pre, infer, post, overlay;
-  hipEvent_t ev_infer = nullptr, ev_post = nullptr, ev_overlay = nullptr, ev_stage3 = nullptr;
-  StageStamps* stamps = nullptr;
-  hipStream_t stream = nullptr;
-};
-
 struct Slot {
   std::vector<Op> pre;     // stage 1: one launch, blockIdx.y = stream of the batch
   std::vector<Op> infer;   // stage 2: the network over the whole batch
@@ -147,8 +137,6 @@ struct Slot {
   // device's clock to the frame's end is a stamp of the overlay's last workgroup (end_stamped), or else ev_stage3 (has_event).
   bool stamped = false, end_stamped = false, has_event = true;
   hipStream_t stream = nullptr;       // the frame's, up to stage 3
-  HalfBatch halves[2];                // both with n > 0 where the batch may run as two halves,
-  bool split = false;                 // and did so this time
   // the event that says the frame has left the last stage: ev_overlay, or, for a member of a
   // group, the first member's (one overlay launch serves them all)
   hipEvent_t ev_done = nullptr;
@@ -192,7 +180,6 @@ struct hs_ctx {
   std::mutex mu;
   std::vector<hs_app*> apps;
   unsigned n_created = 0;             // applications created so far
-  std::atomic<int> frames_in_flight{0};   // of all applications
   // Idle streams created with the context.  The runtime deals streams out to its four hardware
   // queues strictly in turn only once each queue exists: of the first four streams of a process whose
   // default stream has been used, two share a queue, and an application created first would have
@@ -243,7 +230,6 @@ struct hs_app {
   double acc_ms[F_COUNT] = {0}, acc_flops[F_COUNT] = {0}, acc_bytes[F_COUNT] = {0};
   uint64_t acc_n[F_COUNT] = {0};
   void* pinned = nullptr;
-  std::atomic<int> crowded{0};   // calls under way that bring more frames, beside this application's next one, at once
   hs_group* group = nullptr;   // set while the application is a member of a multi-network group
   size_t partial_bytes = 0;    // gate scratch (pre-activations, fp32) one frame needs
 };
@@ -539,8 +525,8 @@ struct Builder {
     plan(c, form);
   }
 
-  // Picks the kernel variant, the tile grid and the split along K.  like: the plan of the same layer over another number of
-  // images, whose sums this one's are to be, bit for bit.
+  // Picks the kernel variant, the tile grid and the split along K.  like: the plan that the layer has for other CUs, whose sums
+  // this one's are to be, bit for bit.
   static void choose_split(ConvParams& c, const ConvParams* like = nullptr, int cus = kAllCus) {
     // the shared-patch kernels address the input with 32-bit offsets (in halves)
     const bool fits32 = (double)c.batch * c.hin * c.win * c.cin_pitch < 2147483648.0;
@@ -548,7 +534,7 @@ struct Builder {
     c.tiles_per_wg = 1;
     if (s3x3 && c.stride == 2) {
       const int n = c.batch * ((c.hout + 7) / 8) * ((c.wout + 7) / 8) * (c.cout / 128);   // tiles of 8 x 8 x 128
-      if (like ? like->variant == CONV_S2_DIRA : c.chunks_per_tap == 1 && n > 1024) {
+      if (c.chunks_per_tap == 1 && n > 1024) {
         // One chunk, more tiles than two rounds of workgroups: k_conv3x3s2_dira walks them, the next tile's patch fetched
         // during the current one's products (two workgroups per CU are resident, so walk in one round), in steps of 10 us
         // per 512 tiles; k_conv3x3s2_run goes by rounds of its own tiles.  Us at 854 x 480, the latter first: eight frames (896
@@ -696,22 +682,6 @@ struct Builder {
     return idx;
   }
 
-  static void plan_block64(ConvParams& g) {
-    g.variant = CONV_BLOCK64;
-    g.tiles_x = (g.wout + 15) / 16;
-    g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
-    g.tiles_n = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
-    g.tiles_per_xcd = (g.tiles_m + 7) / 8;
-    g.tiles_img = (uint32_t)(g.tiles_m / g.batch);
-    auto by = [](uint64_t d) { return (uint32_t)((((uint64_t)1 << 31) + d - 1) / d); };
-    g.by_tiles_img = by(g.tiles_img); g.by_tiles_x = by((uint64_t)g.tiles_x);
-    g.run_in_bytes = (uint32_t)(g.batch * g.hin * g.win * 128);
-  }
-  static void plan_stem(StemPoolParams& sp) {
-    sp.tiles_x = (sp.wp + 14) / 15; sp.tiles_y = (sp.hp + 7) / 8;
-    sp.tiles_per_xcd = (sp.batch * sp.tiles_x * sp.tiles_y + 7) / 8;
-  }
-
   // A 64 -> 64 -> 64 channel BasicBlock without projection as ONE launch (k_block64_fused):
   // out = ReLU(conv_b(ReLU(conv_a(in))) + in).  Weights are reserved in blob order (conv a, conv b).
   void block64_layer(const Tensor& in, size_t at_a, size_t at_b, Tensor* out) {
@@ -729,7 +699,15 @@ struct Builder {
     pack_frag_at(at_b, 64, 64, 9, 64, wb_off);
     out->h = g.hout; out->w = g.wout; out->c = 64;
     check_room(*out, g.m);
-    plan_block64(g);
+    g.variant = CONV_BLOCK64;
+    g.tiles_x = (g.wout + 15) / 16;
+    g.tiles_m = g.batch * ((g.hout + 7) / 8) * g.tiles_x;
+    g.tiles_n = 1; g.chunks_per_split = 1; g.tiles_per_wg = 1; g.n_block = 1;
+    g.tiles_per_xcd = (g.tiles_m + 7) / 8;
+    g.tiles_img = (uint32_t)(g.tiles_m / g.batch);
+    auto by = [](uint64_t d) { return (uint32_t)((((uint64_t)1 << 31) + d - 1) / d); };
+    g.by_tiles_img = by(g.tiles_img); g.by_tiles_x = by((uint64_t)g.tiles_x);
+    g.run_in_bytes = (uint32_t)(g.batch * g.hin * g.win * 128);
     g.wt_frag = d_w ? d_w + wa_off : nullptr;
     g.wt2_frag = d_w ? d_w + wb_off : nullptr;
     g.out = out->p; g.out_pitch = out->pitch;
@@ -847,7 +825,8 @@ struct Builder {
       sp.out = buf[0].p;
       sp.hin = ph; sp.win = pw; sp.hc = hs_; sp.wc = ws_; sp.hp = hp; sp.wp = wp;
       sp.batch = d.batch;
-      plan_stem(sp);
+      sp.tiles_x = (wp + 14) / 15; sp.tiles_y = (hp + 7) / 8;
+      sp.tiles_per_xcd = (sp.batch * sp.tiles_x * sp.tiles_y + 7) / 8;
       op.flops = 2.0 * nb * hs_ * ws_ * 64.0 * 3 * 49;
       op.bytes = nb * ((double)d.net_h * d.net_w * 8 + (double)hp * wp * 64 * 2);
       ops.push_back(op);
@@ -922,71 +901,6 @@ struct Builder {
     blob_off = at;
     map_h = hf; map_w = wf; stateful = true;
     d_c = cstate; d_concat = concat;
-  }
-
-  // Part of a batch's launch: images first .. first + n - 1 of the tensors that the whole one reads and writes.
-  // planned: the same part of the same layer over other buffers.
-  static Op part_of(Op op, int first, int n, const Op* planned = nullptr) {
-    const size_t f = (size_t)first;
-    auto on = [](auto*& p, size_t by) { if (p) p += by; };
-    switch (op.fam) {
-      case F_RESIZE: {                   // (src: per frame)
-        ResizeParams& r = op.resize;
-        r.batch = n;
-        on(r.dst, f * r.dst_img_stride); on(r.dst_f32, f * r.dst32_img_stride);
-        break;
-      }
-      case F_STEM: {
-        StemPoolParams& p = op.stem;
-        p.batch = n;
-        on(p.in, f * p.hin * p.win * 4); on(p.out, f * p.hp * p.wp * 64);
-        plan_stem(p);
-        break;
-      }
-      case F_CONV: {
-        ConvParams& c = op.conv;
-        const ConvParams whole = c;
-        const size_t px = f * c.img_m;
-        c.batch = n; c.m = n * c.img_m;
-        on(c.in, f * c.hin * c.win * c.cin_pitch);
-        on(c.out, px * c.out_pitch); on(c.out2, px * c.out2_pitch); on(c.res, px * c.res_pitch); on(c.partial, px * c.cout_pad);
-        if (planned) {
-          ConvParams q = planned->conv;
-          q.in = c.in; q.out = c.out; q.out2 = c.out2; q.res = c.res; q.partial = c.partial;
-          c = q;
-        } else if (c.variant == CONV_BLOCK64) {
-          plan_block64(c);
-        } else {
-          choose_split(c, &whole);
-        }
-        if (first) c.next_lines = 0;     // the first part prefetches for both
-        break;
-      }
-      case F_LSTM: {
-        LstmEpilogueParams& l = op.lstm;
-        const size_t px = f * l.img_m;
-        l.m = n * l.img_m;
-        on(l.partial, px * 4 * l.hid); on(l.c, px * l.hid); on(l.h_out, px * l.h_pitch);
-        on(l.logits, 8 * px); on(l.heat, 8 * px); on(l.mask, 8 * px); on(l.kmap, px);
-        break;
-      }
-      case F_POST: {
-        PostParams& p = op.post;
-        p.batch = n;
-        on(p.logits, f * 8 * p.n); on(p.rec, f); on(p.marks, f * 16);
-        break;
-      }
-      case F_OVERLAY: {                  // (src, dst and rec: per frame)
-        OverlayParams& o = op.overlay;
-        o.batch = n;
-        OverlayLayer& l = o.layer[0];
-        const size_t px = f * l.wm * l.hm;
-        on(l.kmap, px); on(l.logits, 8 * px); on(l.marks, f * 16);
-        break;
-      }
-      default: throw std::logic_error("this launch has no parts");
-    }
-    return op;
   }
 
   void walk(int ph, int pw) {
@@ -1073,7 +987,6 @@ static hs_status validate_desc(const hs_app_desc* d) {
   return HS_OK;
 }
 
-// Builds the whole plan into `app`, or only sizes the workspace when app == NULL.
 // Whether stage 1 is part of the small network's launch: where that is one round of workgroups, 256 tiles.  A workgroup that
 // resizes 2.6 times its pixels takes 2 us longer, a launch of its own 4, and back to back the host waits for each launch.  Us, two
 // launches / one: 128 x 128 (16 tiles) 29.3 / 28.6, sixteen (256) 47 / 46.5; 320 x 320 (100) 35.2 / 34.5, three (300) 45 / 47,
@@ -1084,46 +997,7 @@ static bool frame_net_pays(const hs_app_desc& d, int map_h, int map_w) {
          d.batch * ((map_h + 7) / 8) * ((map_w + 7) / 8) <= 256;
 }
 
-// A batch that finds the device idle runs as two halves side by side on the application's two streams: what a launch leaves
-// idle at its ends (boundary, first operands, the last round's sums and stores) goes to the other half's.  Every sum is
-// the whole batch's bit for bit (choose_split), so whether a batch is split shows in its time alone.
-static hs_status build_halves(hs_app* app) {
-  // Where 38 launches instead of 19 keep the host ahead of the GPU: 4 to 4.9 us each, depending on the process.  Us, whole / halves in
-  // the slower and the faster kind: nine 416 x 240 frames (0.90 M pixels) 187 / 208, 187; seven 480 x 270 (0.91) 187 / 208, 190; four 641 x
-  // 361 (0.93) 199 / 202, 184; five 640 x 360 (1.15) 234 / 225, 212 (but smaller frames, more of them, 193 / 199); three 854 x 480 (1.23) 235 / 230, 220; sixteen 416 x 240
-  // (1.60) 274 / 243, 235; four 854 x 480 (1.64) 271 / 242, 236; twelve (4.92) 580 / 528; sixteen 771 / 690.
-  const int B = app->batch;
-  if (!app->stateful || app->lanes < 2 || B < 2 || (double)B * app->desc.net_w * app->desc.net_h < 1.2e6) return HS_OK;
-  for (Slot& s : app->slots)
-    for (int k = 0; k < 2; ++k) {
-      HalfBatch& h = s.halves[k];
-      const HalfBatch& planned = app->slots[0].halves[k];
-      const int first = k ? (B + 1) / 2 : 0, n = k ? B / 2 : (B + 1) / 2;
-      auto part = [&](const std::vector<Op>& whole, std::vector<Op>& out, const std::vector<Op>& like) {
-        for (size_t i = 0; i < whole.size(); ++i)
-          out.push_back(Builder::part_of(whole[i], first, n, &out != &like ? &like[i] : nullptr));
-      };
-      part(s.pre, h.pre, planned.pre);
-      part(s.infer, h.infer, planned.infer);
-      part(s.post, h.post, planned.post);
-      part(s.overlay, h.overlay, planned.overlay);
-      if (k) {
-        h.pre[0].resize.t_end += 3;
-        h.infer.back().lstm.t_end += 3;
-        h.post[0].post.t_end += 3;
-        h.overlay[0].overlay.layer[0].t_stages += 3;
-        HS_HIP(hipEventCreate(&h.ev_infer));
-        HS_HIP(hipEventCreate(&h.ev_post));
-        HS_HIP(hipEventCreate(&h.ev_overlay));
-      } else {
-        h.ev_infer = s.ev_infer; h.ev_post = s.ev_post; h.ev_overlay = s.ev_overlay;
-      }
-      h.stamps = s.stamps + k;
-      h.first = first; h.n = n;
-    }
-  return HS_OK;
-}
-
+// Builds the whole plan into `app`, or only sizes the workspace when app == NULL.
 static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out) {
   const bool create = app != nullptr;
   const int depth = d->queue_depth;
@@ -1198,7 +1072,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     sb[i].mask = b.carve.take<uint8_t>(B * 8 * n_map);
     sb[i].kmap = b.carve.take<uint8_t>(B * n_map);
     sb[i].marks = d->annotate ? b.carve.take<int>((size_t)B * 16) : nullptr;
-    sb[i].t_stages = b.carve.take<uint64_t>(6);   // (a second half's behind the first's)
+    sb[i].t_stages = b.carve.take<uint64_t>(3);
   }
   const size_t total = round_up_sz(b.carve.off, 256);
   if (bytes_out) *bytes_out = total;
@@ -1241,7 +1115,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
   const double theta_d = std::log((double)d->threshold / (1.0 - (double)d->threshold));
   int a_q8 = (int)lrint(256.0 * (double)d->alpha);
   a_q8 = std::max(0, std::min(256, a_q8));
-  const size_t pinned_bytes = (sizeof(PostRecord) * B + 2 * sizeof(StageStamps)) * depth;
+  const size_t pinned_bytes = (sizeof(PostRecord) * B + sizeof(StageStamps)) * depth;
   HS_HIP(hipHostMalloc(&app->pinned, pinned_bytes, hipHostMallocDefault));
   std::memset(app->pinned, 0, pinned_bytes);
   app->slots.resize(depth);
@@ -1250,7 +1124,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     s.d_netin = sb[i].netin; s.d_netin_f32 = sb[i].netin32;
     s.d_logits = sb[i].logits; s.d_heat = sb[i].heat; s.d_mask = sb[i].mask;
     s.rec = (PostRecord*)app->pinned + (size_t)i * B;
-    s.stamps = (StageStamps*)((PostRecord*)app->pinned + (size_t)depth * B) + 2 * i;
+    s.stamps = (StageStamps*)((PostRecord*)app->pinned + (size_t)depth * B) + i;
     s.results.resize(B);
     {
       Op r;
@@ -1376,17 +1250,17 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     s.ev_done = s.ev_overlay;
     s.ev_stage3 = s.ev_post;
   }
-  return build_halves(app);
+  return HS_OK;
 }
 
 // ---- completion thread ---------------------------------------------------------------------------
-// Ticks from the end of stage 2 until the last channel maximum of n images was found, where that
+// From the end of stage 2 until the last channel maximum of the frame (batch) was found, where that
 // happened in the overlay's launch.  Stamped by the kernels themselves: an event for the start of that
 // launch is a packet of its own in the queue (one 1080p frame 160 -> 167 us, twelve back to back 1189 -> 1256).
-static int32_t stage3_ticks(const PostRecord* rec, int n) {
+static float stage3_ms(const Slot& s, int khz) {
   int32_t ticks = 0;
-  for (int j = 0; j < n; ++j) ticks = std::max(ticks, *std::max_element(rec[j].ticks, rec[j].ticks + 8));
-  return ticks;
+  for (size_t j = 0; j < s.results.size(); ++j) ticks = std::max(ticks, *std::max_element(s.rec[j].ticks, s.rec[j].ticks + 8));
+  return (float)ticks / (float)khz;
 }
 
 // From a stage's stamp, in the workgroup that ends last, until the event on that launch: events see a launch 0.8 to 1.0 us
@@ -1407,36 +1281,21 @@ static void completer_main(hs_app* app) {
       s = &app->slots[app->n_completed % app->depth];
     }
     hipError_t e = hipEventSynchronize(s->ev_done);
-    if (s->split && e == hipSuccess) e = hipEventSynchronize(s->halves[1].ev_overlay);
     const uint64_t t_done = now_ns();
-    float ms_pre = 0, ms_inf = 0, ms_post = 0;     // from the stages' ends to the frame's
-    const int khz = app->ctx->wall_clock_khz;
+    float ms_pre = 0, ms_inf = 0, ms_post = 0;
     if (s->stamped) {
-      // On the device's clock, from the first launches' end of stage 2 on: of two halves the later end counts, stage by stage.
-      const uint64_t zero = s->stamps->infer;
-      double pre = -1e30, infer = -1e30, post = -1e30, end = -1e30;
-      auto later = [](double& t, double of) { t = std::max(t, of); };
-      auto add = [&](const StageStamps& t, const PostRecord* rec, int n, hipEvent_t stage3, hipEvent_t overlay) {
-        auto at = [&](uint64_t stamp) { return (double)(int64_t)(stamp - zero); };
-        float ms = 0;                    // from the stamp of stage3's stage on
-        if (!s->end_stamped && e == hipSuccess) e = hipEventElapsedTime(&ms, stage3, overlay);
-        later(pre, at(t.pre));
-        later(infer, at(t.infer));
-        later(post, s->maxima_rode ? at(t.infer) + stage3_ticks(rec, n) : at(t.post));
-        later(end, s->end_stamped ? at(t.drawn) + (double)kDrawnToEndMs * khz
-                                  : at(s->maxima_rode ? t.infer : t.post) + (double)(ms + kStampToEventMs) * khz);
-      };
-      if (s->split)
-        for (const HalfBatch& h : s->halves) add(*h.stamps, s->rec + h.first, h.n, h.ev_stage3, h.ev_overlay);
-      else
-        add(*s->stamps, s->rec, app->batch, s->ev_stage3, s->ev_done);
-      ms_pre = (float)((end - pre) / khz);
-      ms_inf = (float)((end - infer) / khz);
-      ms_post = (float)((end - post) / khz);
+      const StageStamps& t = *s->stamps;
+      auto span = [&](uint64_t from, uint64_t to) { return (float)(int64_t)(to - from) / (float)app->ctx->wall_clock_khz; };
+      float ms = 0;                      // from the stamp of ev_stage3's stage on
+      if (!s->end_stamped && e == hipSuccess) e = hipEventElapsedTime(&ms, s->ev_stage3, s->ev_done);
+      ms += s->end_stamped ? span(t.infer, t.drawn) + kDrawnToEndMs : kStampToEventMs;
+      ms_post = s->maxima_rode ? std::max(0.0f, ms - stage3_ms(*s, app->ctx->wall_clock_khz)) : ms;
+      ms_inf = s->maxima_rode ? ms : ms + span(t.infer, t.post);
+      ms_pre = ms_inf + span(t.pre, t.infer);
     } else {
       if (e == hipSuccess) e = hipEventElapsedTime(&ms_pre, s->ev_pre, s->ev_done);
       if (e == hipSuccess) e = hipEventElapsedTime(&ms_inf, s->ev_infer, s->ev_done);
-      if (s->maxima_rode) ms_post = ms_inf - (float)stage3_ticks(s->rec, app->batch) / (float)khz;
+      if (s->maxima_rode) ms_post = std::max(0.0f, ms_inf - stage3_ms(*s, app->ctx->wall_clock_khz));
       else if (e == hipSuccess) e = hipEventElapsedTime(&ms_post, s->ev_stage3, s->ev_done);
     }
     auto back = [&](float ms) {
@@ -1458,7 +1317,6 @@ static void completer_main(hs_app* app) {
       if (e != hipSuccess && app->completer_error.empty())
         app->completer_error.set(hipGetErrorString(e));
       s->state = SLOT_DONE;
-      app->ctx->frames_in_flight--;
       app->n_completed++;
       app->completed_pub.store(app->n_completed, std::memory_order_release);
     }
@@ -1557,8 +1415,7 @@ static void release_app(hs_app* app) {
   for (Slot& s : app->slots) {
     if (s.graph_exec) (void)hipGraphExecDestroy(s.graph_exec);
     if (s.graph) (void)hipGraphDestroy(s.graph);
-    const HalfBatch& h = s.halves[1];
-    for (hipEvent_t ev : {s.ev_pre, s.ev_infer, s.ev_post, s.ev_overlay, h.ev_infer, h.ev_post, h.ev_overlay})
+    for (hipEvent_t ev : {s.ev_pre, s.ev_infer, s.ev_post, s.ev_overlay})
       if (ev) (void)hipEventDestroy(ev);
   }
   destroy_streams(app);
@@ -1653,7 +1510,6 @@ static hs_status build_slot_graph(Slot& s, hipEvent_t wait_ev) {
 // ================================================================================================
 int hs_internal_app_batch(const hs_app* app) { return app->batch; }
 int hs_internal_app_grouped(const hs_app* app) { return app->group != nullptr; }
-void hs_internal_app_crowd(hs_app* app, int calls) { app->crowded += calls; }
 
 extern "C" {
 
@@ -1810,11 +1666,6 @@ hs_status hs_create_app(hs_ctx* ctx, const hs_app_desc* desc, hs_app** out) {
   }
   if (st == HS_OK) st = make_streams(app.get(), nullptr, nullptr, 0);
   if (st != HS_OK) return st;
-  if (app->slots[0].halves[1].n > 0) {   // the first batch needs both streams, and a stream's first launch takes 0.1 ms longer
-    for (int l = 0; l < app->lanes; ++l) launch_fill_zero(app->d_concat[l], 16, app->s_lane[l]);
-    HS_HIP(hipGetLastError());
-    for (int l = 0; l < app->lanes; ++l) HS_HIP(hipStreamSynchronize(app->s_lane[l]));
-  }
   app->completer = std::thread(completer_main, app.get());
   {
     std::lock_guard<std::mutex> lk(ctx->mu);
@@ -1950,9 +1801,14 @@ static void plan_for_cus(hs_app* app, int cus) {
     if (op.fam != F_CONV || op.conv.variant != CONV_KW) continue;
     const ConvParams before = op.conv;
     Builder::choose_split(op.conv, &before, cus);
+    auto take = [&](ConvParams& c) {       // the same layer over other buffers
+      ConvParams q = op.conv;
+      q.in = c.in; q.out = c.out; q.out2 = c.out2; q.res = c.res; q.partial = c.partial;
+      c = q;
+    };
     for (Slot& s : app->slots) {
-      if (&s != &first) s.infer[i] = Builder::part_of(s.infer[i], 0, app->batch, &op);
-      if (!s.infer_static.empty()) s.infer_static[i] = Builder::part_of(s.infer_static[i], 0, app->batch, &op);
+      if (&s != &first) take(s.infer[i].conv);
+      if (!s.infer_static.empty()) take(s.infer_static[i].conv);
     }
   }
 }
@@ -1978,7 +1834,6 @@ static void finish_submit(hs_app* app, Slot* s) {
   {
     std::lock_guard<std::mutex> lk(app->mu);
     s->state = SLOT_INFLIGHT;
-    app->ctx->frames_in_flight++;
     app->n_submitted++;
   }
   app->cv_work.notify_one();
@@ -2045,53 +1900,11 @@ static hs_status submit_stages(hs_app* app, const uint8_t* const* d_frames,
   return st;
 }
 
-// `stream` goes on behind stage 3 of frame `before`, which may be in flight, or at a recurrent cell behind its stage 2; where
-// that frame has no event there, behind its overlay.
-static hs_status order_behind(hipStream_t stream, const Slot& before, bool at_cell) {
-  auto order = [&](hipStream_t other, hipEvent_t infer, hipEvent_t stage3, hipEvent_t overlay) -> hs_status {
-    if (other == stream) return HS_OK;                   // one queue: in order
-    HS_HIP(hipStreamWaitEvent(stream, !before.has_event ? overlay : at_cell ? infer : stage3, 0));
-    return HS_OK;
-  };
-  if (!before.split) return order(before.stream, before.ev_infer, before.ev_stage3, before.ev_overlay);
-  for (const HalfBatch& h : before.halves) {
-    const hs_status st = order(h.stream, h.ev_infer, h.ev_stage3, h.ev_overlay);
-    if (st != HS_OK) return st;
-  }
-  return HS_OK;
-}
-
-// The halves of a batch that comes alone, layer by layer in turn, so that neither waits for the other's launches.
-static hs_status enqueue_halves(hs_app* app, Slot* s, const uint8_t* const* d_frames, uint8_t* const* d_overlay_outs,
-                                hipEvent_t frames_ready) {
-  const OverlayParams& whole = s->overlay[0].overlay;
-  for (HalfBatch& h : s->halves) {
-    OverlayParams& o = h.overlay[0].overlay;
-    for (int j = 0; j < h.n; ++j) {
-      h.pre[0].resize.src[j] = o.src[j] = d_frames[h.first + j];
-      o.dst[j] = d_overlay_outs[h.first + j];
-    }
-    o.n_max = whole.n_max; o.stamp_end = whole.stamp_end;
-    o.layer[0].rec = whole.layer[0].rec ? whole.layer[0].rec + h.first : nullptr;
-    o.layer[0].stamps = h.stamps;
-    h.ev_stage3 = s->maxima_rode ? h.ev_infer : h.ev_post;
-    if (frames_ready) HS_HIP(hipStreamWaitEvent(h.stream, frames_ready, 0));
-  }
-  for (HalfBatch& h : s->halves) {
-    const hs_status st = run_ops(app, h.pre, h.stream, nullptr);
-    if (st != HS_OK) return st;
-  }
-  for (size_t i = 0; i < s->infer.size(); ++i)
-    for (HalfBatch& h : s->halves) {
-      const hs_status st = run_ops(app, h.infer, h.stream, i + 1 == s->infer.size() ? h.ev_infer : nullptr, i, i + 1);
-      if (st != HS_OK) return st;
-    }
-  for (HalfBatch& h : s->halves) {
-    hs_status st = HS_OK;
-    if (!s->maxima_rode) st = run_ops(app, h.post, h.stream, h.ev_post);
-    if (st == HS_OK) st = run_ops(app, h.overlay, h.stream, h.ev_overlay);
-    if (st != HS_OK) return st;
-  }
+// `stream` goes on behind `event` (ev_stage3, or at a recurrent cell ev_infer) of frame `before`, which may be in flight;
+// where that frame has no such event, behind its overlay.
+static hs_status order_behind(hipStream_t stream, const Slot& before, hipEvent_t Slot::*event) {
+  if (before.stream == stream) return HS_OK;             // one queue: in order
+  HS_HIP(hipStreamWaitEvent(stream, before.has_event ? before.*event : before.ev_overlay, 0));
   return HS_OK;
 }
 
@@ -2156,25 +1969,15 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   s->has_event = !s->stamped || others_wait || !s->end_stamped;
   s->overlay[0].overlay.stamp_end = s->end_stamped;
   s->stream = lane_stream;
-  s->split = false;
   auto event = [&](hipEvent_t e, bool wanted) { return !s->stamped || wanted ? e : nullptr; };
-  Slot& same_lane = app->slots[(size_t)((s - app->slots.data()) + app->depth - app->lanes) % app->depth];
-  if (!idle && app->lane_last_stream[s->lane] && (same_lane.split || app->lane_last_stream[s->lane] != lane_stream)) {
-    st = order_behind(lane_stream, same_lane, false);
+  if (!idle && app->lane_last_stream[s->lane] && app->lane_last_stream[s->lane] != lane_stream &&
+      app->depth >= app->lanes) {
+    Slot& same_lane =
+        app->slots[(size_t)((s - app->slots.data()) + app->depth - app->lanes) % app->depth];
+    st = order_behind(lane_stream, same_lane, &Slot::ev_stage3);
     if (st != HS_OK) return st;
   }
   app->lane_last_stream[s->lane] = lane_stream;
-  s->maxima_rode = maxima_here;
-  s->ev_done = s->ev_overlay;
-  s->split = s->halves[1].n > 0 && s->stamped && s->has_event && idle && own_overlay && two_queues && !static_scratch &&
-             app->ctx->frames_in_flight == 0 && app->crowded == 0;
-  if (s->split) {
-    s->halves[0].stream = lane_stream;
-    s->halves[1].stream = app->s_lane[(app->last_stream + 1) % app->lanes];
-    st = enqueue_halves(app, s, d_frames, d_overlay_outs, frames_ready);
-    if (st == HS_OK) finish_submit(app, s);
-    return st;
-  }
   // the caller's producer (another stream) may still be writing the frames
   if (frames_ready) HS_HIP(hipStreamWaitEvent(lane_stream, frames_ready, 0));
   if (graph) {
@@ -2194,7 +1997,7 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
       Slot& before = app->slots[(size_t)((s - app->slots.data()) + app->depth - 1) % app->depth];
       st = run_ops(app, infer, lane_stream, nullptr, 0, (size_t)s->wait_idx);
       if (st != HS_OK) return st;
-      st = order_behind(lane_stream, before, true);
+      st = order_behind(lane_stream, before, &Slot::ev_infer);
       if (st != HS_OK) return st;
       st = run_ops(app, infer, lane_stream, event(s->ev_infer, maxima_here ? s->has_event : others_wait), (size_t)s->wait_idx);
     } else {
@@ -2209,6 +2012,8 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   }
   if (graph) HS_HIP(hipEventRecord(s->ev_post, lane_stream));
   s->ev_stage3 = !graph && maxima_here ? s->ev_infer : s->ev_post;
+  s->maxima_rode = maxima_here;
+  s->ev_done = s->ev_overlay;
   if (!own_overlay) {
     *slot_out = s;
     *stream_out = lane_stream;

@@ -28,6 +28,13 @@ std::atomic<bool> fail_block_after_thread_start{false};
 static thread_local bool fail_next_block = false;
 hs::ConvParams conv_launches[kMaxConvLaunches];
 std::atomic<int> n_conv_launches{0};
+void* launch_streams[kMaxLaunches];
+std::atomic<int> n_launches{0};
+static hipError_t launched(hipStream_t s) {
+  const int n = n_launches++;
+  if (n < kMaxLaunches) launch_streams[n] = s;
+  return hipSuccess;
+}
 void reset_failures() {
   blocks_until_failure = threads_until_failure = -1;
   fail_block_after_thread_start = false;
@@ -134,9 +141,9 @@ hipError_t hipExtStreamCreateWithCUMask(hipStream_t* s, uint32_t, const uint32_t
 hipError_t hipStreamDestroy(hipStream_t s) { return drop(s); }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
-hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) {
-  return hipSuccess;
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t s) { return launched(s); }
+hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t s, hipEvent_t, hipEvent_t, int) {
+  return launched(s);
 }
 hipError_t hipGraphCreate(hipGraph_t* g, unsigned) { return make(g); }
 hipError_t hipGraphDestroy(hipGraph_t g) { return drop(g); }

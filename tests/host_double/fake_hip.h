@@ -16,5 +16,9 @@ extern std::atomic<bool> fail_block_after_thread_start;   // the thread's starte
 constexpr int kMaxConvLaunches = 128;
 extern hs::ConvParams conv_launches[kMaxConvLaunches];
 extern std::atomic<int> n_conv_launches;
+// kernels launched so far, and the streams that the first of them went to
+constexpr int kMaxLaunches = 256;
+extern void* launch_streams[kMaxLaunches];
+extern std::atomic<int> n_launches;
 void reset_failures();
 }  // namespace fake
