@@ -1266,8 +1266,10 @@ static float stage3_ms(const Slot& s, int khz) {
 // From a stage's stamp, in the workgroup that ends last, until the event on that launch: events see a launch 0.8 to 1.0 us
 // longer, at both ends together, than its workgroups' stamps do.
 constexpr float kStampToEventMs = 0.0005f;
-// From StageStamps::drawn until the overlay's end.  Against the event behind stage 2, in plain frames of 64 x 48 to
-// 1920 x 1080 pixels, sixteen of 320 x 180, two of 2048 x 1024: medians of 0.1 to 2.1 us.
+// From StageStamps::drawn until the overlay's end, unless the search for a channel's maximum, one workgroup's on a map of any size, takes
+// longer: a frame ends with the later of the two.  Against the event behind stage 2, in plain frames of 64 x 48 to 4000 x 1000
+// pixels and batches of 4 to 16, groups and quads, both networks: medians of -0.4 to 2.5 us after drawn, or -0.4 to 0.4 after the maxima
+// where they are the later ones (1920 x 1080 pixels, a map of 160 x 90: 13.8 us after drawn).
 constexpr float kDrawnToEndMs = 0.001f;
 
 static void completer_main(hs_app* app) {
@@ -1288,8 +1290,9 @@ static void completer_main(hs_app* app) {
       auto span = [&](uint64_t from, uint64_t to) { return (float)(int64_t)(to - from) / (float)app->ctx->wall_clock_khz; };
       float ms = 0;                      // from the stamp of ev_stage3's stage on
       if (!s->end_stamped && e == hipSuccess) e = hipEventElapsedTime(&ms, s->ev_stage3, s->ev_done);
-      ms += s->end_stamped ? span(t.infer, t.drawn) + kDrawnToEndMs : kStampToEventMs;
-      ms_post = s->maxima_rode ? std::max(0.0f, ms - stage3_ms(*s, app->ctx->wall_clock_khz)) : ms;
+      const float maxima_ms = s->maxima_rode ? stage3_ms(*s, app->ctx->wall_clock_khz) : 0.0f;
+      ms = s->end_stamped ? std::max(span(t.infer, t.drawn) + kDrawnToEndMs, maxima_ms) : ms + kStampToEventMs;
+      ms_post = s->maxima_rode ? std::max(0.0f, ms - maxima_ms) : ms;
       ms_inf = s->maxima_rode ? ms : ms + span(t.infer, t.post);
       ms_pre = ms_inf + span(t.pre, t.infer);
     } else {
@@ -1961,8 +1964,8 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
   const bool two_queues = app->lanes > 1 && app->s_lane[0] != app->s_lane[1];
   const bool others_wait = !own_overlay || ov_stream != lane_stream || (two_queues && (!idle || s->wait_idx >= 0));
   // What the overlay's last workgroup sees of the frame's end (kDrawnToEndMs) serves to tie the stages' stamps to it while
-  // the workgroups (4096 pixels each) run side by side, not held up by another frame, and take equally long.  With more of
-  // them it is up to 7 us early (a plain 7680 x 4320 frame), with annotations up to 11 (320 x 240).  Such frames have the
+  // the workgroups run side by side, not held up by another frame, and take equally long: up to 1024 of 4096 pixels, or four times as
+  // many of a quarter of the work.  With more of them it is up to 7 us early (a plain 7680 x 4320 frame), with annotations up to 11 (320 x 240).  Such frames have the
   // event behind stage 3 for it, and the completion thread spends 1 us (35 at an application's first frame) on its time.
   s->end_stamped = s->stamped && idle && !app->desc.annotate && !app->partitioned &&
                    (double)B * app->desc.frame_w * app->desc.frame_h <= 1024 * 4096.0;
@@ -2312,8 +2315,9 @@ hs_status hs_submit_group(hs_group* group, const uint8_t* d_frame, uint8_t* d_ov
   };
   if (st0 != HS_OK) { set_error("%s", err0.text); return fail_all(st0); }
   op.n_max = 0;
-  bool even = true;        // no member's annotations are drawn
-  for (size_t i = 0; i < n; ++i) even = even && !group->members[i]->desc.annotate && !group->members[i]->partitioned;
+  bool even = true;        // no member's annotations are drawn, and its maxima take as long to find as the others'
+  for (const hs_app* a : group->members)
+    even = even && !a->desc.annotate && !a->partitioned && a->map_w * a->map_h == group->members[0]->map_w * group->members[0]->map_h;
   op.stamp_end = 0;
   for (size_t i = 0; i < n; ++i) {
     slot[i]->end_stamped = slot[i]->end_stamped && even;       // (else its event: a member's stage 3 has one)

@@ -30,6 +30,8 @@ hs::ConvParams conv_launches[kMaxConvLaunches];
 std::atomic<int> n_conv_launches{0};
 void* launch_streams[kMaxLaunches];
 std::atomic<int> n_launches{0};
+uint64_t overlay_drawn = 500;
+int32_t overlay_maxima = 300;
 static hipError_t launched(hipStream_t s) {
   const int n = n_launches++;
   if (n < kMaxLaunches) launch_streams[n] = s;
@@ -183,7 +185,14 @@ KernelDesc describe(const TinyFrameParams& p) {   // a launch of the small netwo
 KernelDesc describe(const LstmEpilogueParams&) { return some(); }
 KernelDesc describe(const StemPoolParams&) { return some(); }
 KernelDesc describe(const PostParams&) { return some(); }
-KernelDesc describe(const OverlayParams&) { return some(); }
+KernelDesc describe(const OverlayParams& p) {
+  for (int l = 0; l < p.n_layers; ++l) {
+    const OverlayLayer& L = p.layer[l];
+    if (L.stamps) *L.stamps = StageStamps{100000, 200000, 0, 200000 + fake::overlay_drawn};
+    for (int j = 0; L.rec && j < p.batch; ++j) L.rec[j].ticks[j % 8] = fake::overlay_maxima;
+  }
+  return some();
+}
 hipError_t static_scratch_address(void** p, size_t* n) {
   static char scratch[256];
   *p = scratch;

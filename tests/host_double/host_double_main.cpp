@@ -1,5 +1,6 @@
 // Host code of the library against the stand-in runtime: `host_double_main <check>` exits 0 when the
 // check holds, prints what does not and exits 1 otherwise.
+#include <math.h>
 #include <sched.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -440,6 +441,23 @@ static void small_network_forms() {
   }
 }
 
+// A frame that comes alone ends with the drawing or, on a large map, with the last channel maximum: whichever is later.
+static void end_of_a_frame() {
+  Program p(HS_NET_TINY4);
+  hs_app* app = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &app) == HS_OK);
+  const struct { uint64_t drawn; int32_t maxima; double infer_us, post_us; } ends[] = {{500, 300, 6, 3}, {500, 2000, 20, 0}, {500, 550, 6, 0.5}};
+  for (const auto& z : ends) {
+    fake::overlay_drawn = z.drawn; fake::overlay_maxima = z.maxima;
+    hs_result r;
+    CHECK(hs_submit_frame(app, p.src(), p.dst(), 1) == HS_OK && hs_wait_result(app, &r, 1000000000) == HS_OK);
+    auto from_end = [&](uint64_t t) { return 1e-3 * (double)(r.t_overlay_done_ns - t); };
+    CHECK(fabs(from_end(r.t_infer_done_ns) - z.infer_us) < 0.1 && fabs(from_end(r.t_post_done_ns) - z.post_us) < 0.1);
+    CHECK(fabs(from_end(r.t_pre_done_ns) - from_end(r.t_infer_done_ns) - 1000) < 0.1);
+  }
+  CHECK(hs_destroy_app(app) == HS_OK);
+}
+
 // While kernels are timed, the launch that every other frame makes of the small network is timed, too.
 static void timed_small_network() {
   Program p(HS_NET_TINY4);
@@ -473,6 +491,7 @@ int main(int argc, char** argv) {
   else if (check == "prefetched_weights") prefetched_weights();
   else if (check == "tile_grids") tile_grids();
   else if (check == "one_queue_alone") one_queue_alone();
+  else if (check == "end_of_a_frame") end_of_a_frame();
   else if (check == "small_network_forms") small_network_forms();
   else if (check == "timed_small_network") timed_small_network();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }

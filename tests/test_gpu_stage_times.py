@@ -101,6 +101,38 @@ def test_frames_alone_and_in_flight(hs, net, depth):
         hs.hs_shutdown(ctx)
 
 
+@pytest.mark.parametrize("frame_w,frame_h,net_w,net_h", [(1920, 1080, 640, 360), (1920, 1080, 480, 270)])   # drawn in quads, in groups of 16
+def test_the_last_stage_waits_for_the_maxima(hs, frame_w, frame_h, net_w, net_h):
+    """On a large map the search for the channels' maxima, in the overlay's launch, takes longer than the drawing, as long as it does in
+    a launch of its own while kernels are timed.  Allowed: a fifth of that, and 2 us for the stamps and that launch's boundary."""
+    from paper_2402_04466_amd.harness import AppStream
+    ctx = hs.hs_init(0)
+    s = AppStream(ctx, net=hs.HS_NET_TINY4, frame_w=frame_w, frame_h=frame_h, net_w=net_w, net_h=net_h, queue_depth=2,
+                  blob=si.he_normal_blob(si.TINY4_LAYERS, 5), palette=si.DEFAULT_PALETTE)
+    try:
+        d_in, d_out = s.upload_frame(next(iter(si.uniform_frames(1, frame_h, frame_w, 6)))), s.new_output()
+
+        def steps(n):
+            after = []
+            for i in range(n):
+                assert s.submit(d_in, d_out, i) == hs.HS_OK
+                r = s.wait()
+                _check([r])
+                after.append((r.t_overlay_done_ns - r.t_infer_done_ns) / 1e3)
+            return sorted(after)[n // 2]
+        steps(4)
+        hs.hs_set_kernel_timing(s.app, True)
+        steps(8)
+        times = {k["name"]: 1e3 * k["total_ms"] / 8 for k in hs.hs_get_kernel_times(s.app)}
+        hs.hs_set_kernel_timing(s.app, False)
+        after = steps(9)
+        print(f"[stage-times] {frame_w}x{frame_h}, net {net_w}x{net_h}: kernels {times}, stage 2 ends {after:.1f} us before the frame", flush=True)
+        assert after >= 0.8 * max(times["overlay"], times["postprocess"]) - 2
+    finally:
+        s.close()
+        hs.hs_shutdown(ctx)
+
+
 @pytest.mark.parametrize("frame_w,frame_h,batch,depth,mode,annotate", [
     (1920, 1080, 1, 2, "eager", False),    # drawn by workgroups that are all there at once
     (1920, 1080, 2, 2, "eager", False),
