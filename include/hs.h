@@ -388,8 +388,9 @@ hs_status hs_set_cpu_affinity(hs_app* app, int cpu);
  * meant for roofline measurements, off by default). Switching resets the accumulators.
  * While it is on, stage 3's channel maxima have a launch of their own ("postprocess"), so that
  * they and the overlay are timed apart; otherwise only the annotation layer makes it one. The
- * small network, where it is one launch ("tiny_net_mfma"), then runs again layer by layer
- * ("conv_mfma"), with the same results up to the order of fp32 sums.
+ * small network, where it is one launch ("tiny_net_mfma"), runs with stage 1 in that launch as well, where that is
+ * what other frames do ("frame_net_mfma"), and then again layer by layer ("conv_mfma"), with the same results up to
+ * the order of fp32 sums.
  * HS_E_STATE while frames are in flight. */
 hs_status hs_set_kernel_timing(hs_app* app, int enable);
 /* Copy up to max_entries accumulated entries; *n_entries receives the count available.

@@ -40,7 +40,7 @@ namespace hs {
 
 // ---- kernel families (for timing) ----------------------------------------------------------
 enum Family { F_RESIZE, F_CONV, F_LSTM, F_STEM, F_POST, F_OVERLAY, F_NET, F_FRAME_NET, F_COUNT };   // F_NET: the small network in one launch,
-// F_FRAME_NET: with stage 1 (never timed)
+// F_FRAME_NET: with stage 1
 static const char* kFamilyName[F_COUNT] = {"resize_norm", "conv_mfma", "lstm_head",
                                            "stem_pool_mfma", "postprocess", "overlay", "tiny_net_mfma", "frame_net_mfma"};
 
@@ -121,7 +121,7 @@ struct Slot {
   std::vector<Op> pre;     // stage 1: one launch, blockIdx.y = stream of the batch
   std::vector<Op> infer;   // stage 2: the network over the whole batch
   std::vector<Op> frame_net;      // stages 1 and 2 of the small network in one launch (empty: two are the better form)
-  std::vector<Op> infer_layers;   // the small network layer by layer, run as well while kernels are being timed
+  std::vector<Op> infer_layers;   // the small network layer by layer; all its forms are run while kernels are being timed
   std::vector<Op> infer_static;   // the same with the gate scratch in the library's fixed
                                   // device array (empty when the scratch needed exceeds it)
   std::vector<Op> post;    // stage 3: the channel maxima
@@ -1177,6 +1177,7 @@ static hs_status build_plan(const hs_app_desc* d, hs_app* app, size_t* bytes_out
     if (lo.fam == F_NET && frame_net_pays(*d, mh, mw)) {
       Op o;
       o.fam = F_FRAME_NET;
+      o.flops = lo.flops; o.bytes = s.pre[0].bytes;
       TinyFrameParams& f = o.frame_net;
       const ConvParams& c = lo.conv;
       std::memset(&f, 0, sizeof(f));
@@ -2008,6 +2009,11 @@ static hs_status enqueue_stages(hs_app* app, Slot* s, bool idle, const uint8_t* 
     }
     if (st != HS_OK) return st;
     // (to time them; what they leave is the same up to the order of fp32 sums)
+    if (app->timing && !s->frame_net.empty()) {
+      std::copy_n(s->pre[0].resize.src, B, s->frame_net[0].frame_net.r.src);
+      st = run_ops(app, s->frame_net, lane_stream, nullptr);
+      if (st != HS_OK) return st;
+    }
     if (app->timing && !s->infer_layers.empty()) st = run_ops(app, s->infer_layers, lane_stream, s->ev_infer);
     if (st != HS_OK) return st;
     if (!maxima_here) st = run_ops(app, s->post, lane_stream, event(s->ev_post, s->has_event));
