@@ -1758,8 +1758,45 @@ hs_status hs_get_features(hs_app* app, int stream, float* x_out) {
   });
 }
 
-static void plan_for_cus(hs_app* app, int cus);
-static int effective_cus(const uint32_t* mask, int n_words, int device_cus);
+// CUs that a launch under the mask keeps busy.  Bit i is a CU of XCD i mod 8, in its shader engine i / 8 mod 4, and workgroups
+// are dealt out evenly to the engines that have CUs: the one with the fewest sets the pace.  (Every layer timed on 80 CUs, two or
+// three per engine, takes as long as on 64: gates of two 854 x 480 frames 31.6 and 31.4 us; on 40 as on 32.)
+static int effective_cus(const uint32_t* mask, int n_words, int device_cus) {
+  const int xcds = xcd_count(device_cus);
+  constexpr int kEngines = 4;
+  std::vector<int> n((size_t)xcds * kEngines, 0);
+  for (int i = 0; i < device_cus && i < 32 * n_words; ++i)
+    if (mask[i / 32] >> (i % 32) & 1u) ++n[(size_t)(i % xcds * kEngines + i / xcds % kEngines)];
+  int engines = 0, fewest = device_cus;
+  for (int k : n)
+    if (k) { ++engines; fewest = std::min(fewest, k); }
+  return engines ? engines * fewest : device_cus;
+}
+
+// The plans of the network's layers for that many CUs (of those that k_conv3x3_run and k_conv3x3s2_run compute).  Made before
+// anything changes: planning allocates.
+static std::vector<ConvParams> plans_for_cus(const hs_app* app, int cus) {
+  std::vector<ConvParams> plans;
+  for (const Op& op : app->slots[0].infer)
+    if (op.fam == F_CONV && op.conv.variant == CONV_KW) {
+      plans.push_back(op.conv);
+      Builder::choose_split(plans.back(), &op.conv, cus);
+    }
+  return plans;
+}
+// Every slot's launches take them, each with its own buffers.  (A slot's graph keeps the forms that it was built with.)
+static void take_plans(hs_app* app, const std::vector<ConvParams>& plans) {
+  for (Slot& s : app->slots)
+    for (std::vector<Op>* ops : {&s.infer, &s.infer_static}) {
+      size_t n = 0;
+      for (Op& op : *ops) {
+        if (op.fam != F_CONV || op.conv.variant != CONV_KW) continue;
+        const ConvParams own = op.conv;
+        op.conv = plans[n++];
+        op.conv.in = own.in; op.conv.out = own.out; op.conv.out2 = own.out2; op.conv.res = own.res; op.conv.partial = own.partial;
+      }
+    }
+}
 
 hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
                            const uint32_t* cu_mask_overlay, int n_words) {
@@ -1774,11 +1811,12 @@ hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
   HS_HIP(hipSetDevice(ctx->device));
   std::lock_guard<std::mutex> lk(ctx->mu);
   if (!cu_mask_infer) {
+    const std::vector<ConvParams> plans = plans_for_cus(app, Builder::kAllCus);
     hs_status st = make_streams(app, nullptr, nullptr, 0);
     if (st != HS_OK) return st;
     std::memset(app->claim, 0, sizeof(app->claim));
     app->partitioned = false;
-    plan_for_cus(app, Builder::kAllCus);
+    take_plans(app, plans);
     return HS_OK;
   }
   uint32_t others[HS_MAX_CU_WORDS] = {0};
@@ -1787,48 +1825,15 @@ hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,
       for (int w = 0; w < HS_MAX_CU_WORDS; ++w) others[w] |= o->claim[w];
   hs_status st = admission_check(others, cu_mask_infer, cu_mask_overlay, n_words, ctx->n_cus);
   if (st != HS_OK) return st;
+  const std::vector<ConvParams> plans = plans_for_cus(app, effective_cus(cu_mask_infer, n_words, ctx->n_cus));
   st = make_streams(app, cu_mask_infer, cu_mask_overlay, n_words);
   if (st != HS_OK) return st;
   std::memset(app->claim, 0, sizeof(app->claim));
   for (int w = 0; w < n_words; ++w) app->claim[w] = cu_mask_infer[w] | cu_mask_overlay[w];
   app->partitioned = true;
-  plan_for_cus(app, effective_cus(cu_mask_infer, n_words, ctx->n_cus));
+  take_plans(app, plans);
   return HS_OK;
   });
-}
-
-// Plans the convolutions anew for that many CUs.  (A slot's graph keeps the forms that it was built with.)
-static void plan_for_cus(hs_app* app, int cus) {
-  Slot& first = app->slots[0];
-  for (size_t i = 0; i < first.infer.size(); ++i) {
-    Op& op = first.infer[i];
-    if (op.fam != F_CONV || op.conv.variant != CONV_KW) continue;
-    const ConvParams before = op.conv;
-    Builder::choose_split(op.conv, &before, cus);
-    auto take = [&](ConvParams& c) {       // the same layer over other buffers
-      ConvParams q = op.conv;
-      q.in = c.in; q.out = c.out; q.out2 = c.out2; q.res = c.res; q.partial = c.partial;
-      c = q;
-    };
-    for (Slot& s : app->slots) {
-      if (&s != &first) take(s.infer[i].conv);
-      if (!s.infer_static.empty()) take(s.infer_static[i].conv);
-    }
-  }
-}
-// CUs that a launch under the mask keeps busy.  Bit i is a CU of XCD i mod 8, in its shader engine i / 8 mod 4, and workgroups
-// are dealt out evenly to the engines that have CUs: the one with the fewest sets the pace.  (Every layer timed on 80 CUs, two or
-// three per engine, takes as long as on 64: gates of two 854 x 480 frames 31.6 and 31.4 us; on 40 as on 32.)
-static int effective_cus(const uint32_t* mask, int n_words, int device_cus) {
-  const int xcds = xcd_count(device_cus);
-  constexpr int kEngines = 4;
-  std::vector<int> n((size_t)xcds * kEngines, 0);
-  for (int i = 0; i < device_cus && i < 32 * n_words; ++i)
-    if (mask[i / 32] >> (i % 32) & 1u) ++n[(size_t)(i % xcds * kEngines + i / xcds % kEngines)];
-  int engines = 0, fewest = device_cus;
-  for (int k : n)
-    if (k) { ++engines; fewest = std::min(fewest, k); }
-  return engines ? engines * fewest : device_cus;
 }
 
 // Marks the slot as in flight and wakes the completion thread (the last step of a submit).

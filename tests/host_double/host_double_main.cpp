@@ -188,6 +188,52 @@ static void call_failures() {
   CHECK(hs_destroy_app(b) == HS_OK && hs_destroy_app(a) == HS_OK);
 }
 
+// Every allocation of a call that sets or releases a partition fails once: nothing has changed then, neither claims nor the plan
+// of any layer.
+static void partition_failures() {
+  Program p(HS_NET_RESNET18_CONVLSTM, 2, 427, 240), p2(HS_NET_TINY4);
+  p.d.queue_depth = 2;
+  hs_app *a = nullptr, *b = nullptr;
+  CHECK(hs_create_app(p.ctx, &p.d, &a) == HS_OK && hs_create_app(p.ctx, &p2.d, &b) == HS_OK);
+  uint32_t mask[8] = {0xffffffffu, 0xffffffffu, 0xffffu};     // 80 CUs
+  const uint8_t* src[2] = {p.src(), p.src()};
+  uint8_t* dst[2] = {p.dst(), p.dst()};
+  hs_result r[2];
+  auto plan = [&] {                          // of the launches of one batch in each lane
+    fake::n_conv_launches = 0;
+    for (int i = 0; i < 2; ++i) CHECK(hs_submit_batch(a, src, dst, 1) == HS_OK && hs_wait_batch(a, r, 1000000000) == HS_OK);
+    std::vector<int> v;
+    for (int i = 0; i < fake::n_conv_launches; ++i) {
+      const hs::ConvParams& c = fake::conv_launches[i];
+      for (int x : {c.run_form, c.tiles_m, c.tiles_n, c.tiles_per_xcd, c.n_block, c.run_nb_shift, (int)c.run_by_blk}) v.push_back(x);
+    }
+    return v;
+  };
+  const std::vector<int> whole = plan();
+  std::vector<int> part;
+  for (int release = 0; release < 2; ++release)
+    for (long n = 0;; ++n) {
+      fake::blocks_until_failure = n;
+      const hs_status st = release ? hs_set_partition(a, nullptr, nullptr, 0) : hs_set_partition(a, mask, mask, 8);
+      const bool reached = fake::blocks_until_failure < 0;
+      fake::reset_failures();
+      if (!reached) {
+        CHECK(st == HS_OK && n > 10);
+        break;
+      }
+      CHECK(st == HS_E_NOMEM && plan() == (release ? part : whole));
+      CHECK(hs_set_partition(b, mask, mask, 8) == (release ? HS_E_OVERSUBSCRIBED : HS_OK));
+      CHECK(hs_set_partition(b, nullptr, nullptr, 0) == HS_OK);
+      if (!release && n == 0) {
+        CHECK(hs_set_partition(a, mask, mask, 8) == HS_OK);
+        part = plan();
+        CHECK(part != whole && hs_set_partition(a, nullptr, nullptr, 0) == HS_OK && plan() == whole);
+      }
+    }
+  CHECK(plan() == whole);
+  CHECK(hs_destroy_app(b) == HS_OK && hs_destroy_app(a) == HS_OK);
+}
+
 // A mux whose allocations are refused, one after the other: a frame that is not taken can be handed
 // over again, a result that cannot be fetched is still there at the next call, and every stream gets
 // its own ids, in order.
@@ -497,6 +543,7 @@ int main(int argc, char** argv) {
   else if (check == "tile_grids") tile_grids();
   else if (check == "one_queue_alone") one_queue_alone();
   else if (check == "end_of_a_frame") end_of_a_frame();
+  else if (check == "partition_failures") partition_failures();
   else if (check == "small_network_forms") small_network_forms();
   else if (check == "timed_small_network") timed_small_network();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }
