@@ -230,8 +230,8 @@ hs_status hs_get_features(hs_app* app, int stream, float* x_out);
  * application of the context. On MI355X CU i belongs to XCD i mod 8 and every mask must
  * contain at least one CU of each XCD (HS_E_INVAL otherwise): build masks from whole groups
  * of 8 consecutive CUs, best of 32: workgroups go evenly to an XCD's four shader engines (CU i: engine i / 8
- * mod 4), so 80 CUs are as fast as 64.  The network's layers are planned for the CUs that the inference mask
- * keeps busy; results are the whole device's bit for bit.  Passing NULL for both masks releases the claim and
+ * mod 4), so 80 CUs are as fast as 64.  Launched kernel by kernel, the network's layers are planned for the CUs that the inference mask
+ * keeps busy; a HIP graph (HS_LAUNCH_GRAPH) keeps the whole device's plans.  Results are the whole device's bit for bit.  Passing NULL for both masks releases the claim and
  * returns the application to the unpartitioned state (all CUs, claims nothing).
  * HS_E_STATE while frames are in flight. */
 hs_status hs_set_partition(hs_app* app, const uint32_t* cu_mask_infer,

@@ -2198,7 +2198,8 @@ __global__ __launch_bounds__(256) void k_overlay(OverlayParamsOf<LAYERS ? kMaxLa
 // Quads where a group of 16 pixels may see three cells of some layer's map, and for launches of fewer than 192 workgroups'
 // worth of such groups, which leave CUs idle.  Us, groups of 16 / quads (cells of 16 pixels and more): 640 x 360 6.5 / 4.3,
 // annotated 8.1 / 5.0; 960 x 540 (32 400 groups) 5.8 / 4.5; 1280 x 720 (57 600) 5.0 / 4.8; 1279 x 719 4.6 / 4.9; 1920 x 1080 6.1 / 5.3,
-// annotated 6.3 / 8.1; four 1279 x 719 (230 080) 6.7 / 8.1; twelve 1920 x 1080 24.1 / 30.9.  Before the quads and the annotations as
+// annotated 6.3 / 8.1; four 1279 x 719 (230 080) 6.7 / 8.1; twelve 1920 x 1080 24.1 / 30.9.  (One line for all: between it and
+// about 130 000 groups a plain frame would be up to 0.8 us faster in quads, an annotated one 1.8 slower.)  Before the quads and the annotations as
 // masks (a third cell fetched on demand, labels pixel by pixel): 320 x 240 with cells of 10 pixels 11.0 (4.8 now), annotated
 // 322 x 241 21.8 (4.8), four annotated 1279 x 719 15.3 (8.7), twelve annotated 1920 x 1080 37.4 (29.0).
 static bool overlay_fine(const OverlayParams& p) {

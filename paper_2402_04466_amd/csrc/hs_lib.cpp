@@ -991,7 +991,8 @@ static hs_status validate_desc(const hs_app_desc* d) {
 // resizes 2.6 times its pixels takes 2 us longer, a launch of its own 4, and back to back the host waits for each launch.  Us, two
 // launches / one: 128 x 128 (16 tiles) 29.3 / 28.6, sixteen (256) 47 / 46.5; 320 x 320 (100) 35.2 / 34.5, three (300) 45 / 47,
 // sixteen 89 / 102; sixteen frames back to back 322 x 241 to 96 x 72 300 / 238, 1920 x 1080 to 320 x 200 340 / 270; four batches of
-// twelve 300 x 300 (1200) 250 / 292.
+// twelve 300 x 300 (1200) 250 / 292.  Frames that are large beside the network's input gain back to back only: 3840 x 2160 to 128 x 128
+// alone 39.0 / 40.6, twelve 260 / 221; fifteen 1920 x 1080 to 128 x 128 in a batch 81.1 / 82.2, twelve batches 767 / 680.
 static bool frame_net_pays(const hs_app_desc& d, int map_h, int map_w) {
   return (double)d.frame_pitch * d.frame_h < 2147483648.0 &&             // 32-bit offsets
          d.batch * ((map_h + 7) / 8) * ((map_w + 7) / 8) <= 256;

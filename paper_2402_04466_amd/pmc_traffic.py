@@ -55,7 +55,7 @@ def main(argv):
         fb = f_scale * sum(fv) / max(len(fv), 1)
         wb = w_scale * sum(wv) / max(len(wv), 1)
         rows.append((name, len(fv), fb, wb))
-        if "conv" in name:
+        if "conv" in name or "block64" in name:      # (the convolutions' family as bench.py counts it)
             conv_f += f_scale * sum(fv)
             conv_w += w_scale * sum(wv)
             conv_n += len(fv)
