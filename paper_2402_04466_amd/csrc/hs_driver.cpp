@@ -358,7 +358,14 @@ extern "C" hs_status hs_run_feeds(const hs_feed* feeds, int n_feeds, double fps,
     } catch (const std::exception& e) {
       not_started.set(e.what());
     }
-    if (here) worker_main(&workers[0]);
+    if (here) {                  // and leaves no trace there: current device, last failure
+      const int device = hs_internal_current_device();
+      hs::Message last;
+      last.set(hs_last_error());
+      worker_main(&workers[0]);
+      hs_internal_use_device(device);
+      set_error("%s", last.text);
+    }
     for (std::thread& t : threads) t.join();
     if (threads.size() < n_threads) {
       set_error("hs_run_feeds: no thread for feed %zu: %s", threads.size(), not_started.text);

@@ -68,4 +68,7 @@ hs_status guarded(const char* fn, F&& body) {
 // What the per-stream front (hs_mux) must know of the application it drives.
 int hs_internal_app_batch(const hs_app* app);      // streams per submit
 int hs_internal_app_grouped(const hs_app* app);    // 1 while a member of a group
+// The calling thread's current device (-1: unknown), which every call here may change.
+int hs_internal_current_device();
+void hs_internal_use_device(int device);
 

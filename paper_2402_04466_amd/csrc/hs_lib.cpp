@@ -1515,6 +1515,13 @@ static hs_status build_slot_graph(Slot& s, hipEvent_t wait_ev) {
 // ================================================================================================
 int hs_internal_app_batch(const hs_app* app) { return app->batch; }
 int hs_internal_app_grouped(const hs_app* app) { return app->group != nullptr; }
+int hs_internal_current_device() {
+  int device = -1;
+  return hipGetDevice(&device) == hipSuccess ? device : -1;
+}
+void hs_internal_use_device(int device) {
+  if (device >= 0) (void)hipSetDevice(device);
+}
 
 extern "C" {
 

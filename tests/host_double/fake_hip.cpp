@@ -30,6 +30,7 @@ hs::ConvParams conv_launches[kMaxConvLaunches];
 std::atomic<int> n_conv_launches{0};
 void* launch_streams[kMaxLaunches];
 std::atomic<int> n_launches{0};
+thread_local int device = 0;
 uint64_t overlay_drawn = 500;
 int32_t overlay_maxima = 300;
 static hipError_t launched(hipStream_t s) {
@@ -109,7 +110,8 @@ template <class T> static hipError_t drop(T x) {
 }
 extern "C" {
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int d) { fake::device = d; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = fake::device; return hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   memset(p, 0, sizeof(*p));
   strcpy(p->gcnArchName, "gfx950");

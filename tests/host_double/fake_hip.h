@@ -23,5 +23,6 @@ extern std::atomic<int> n_launches;
 // what an overlay's launch leaves in the stamps and records that it is given, in ticks of 10 ns
 extern uint64_t overlay_drawn;             // from the end of stage 2 to StageStamps::drawn
 extern int32_t overlay_maxima;             // to the last channel maximum
+extern thread_local int device;            // the calling thread's current device
 void reset_failures();
 }  // namespace fake

@@ -150,6 +150,31 @@ static void feed_failures() {
   for (hs_feed& f : feeds) CHECK(hs_destroy_app(f.app) == HS_OK);
 }
 
+// A feed that the caller's own thread drives leaves that thread as it was: its current device, and what its last failure was.
+static void callers_thread() {
+  Program p(HS_NET_TINY4);
+  hs_feed feed;
+  memset(&feed, 0, sizeof(feed));
+  const uint8_t* src = p.src();
+  uint8_t* dst = p.dst();
+  hs_result out[4], *results = out;
+  CHECK(hs_create_app(p.ctx, &p.d, &feed.app) == HS_OK);
+  feed.d_frames = &src; feed.d_outs = &dst;
+  feed.n_frames = feed.n_outs = feed.batch = feed.results_per_frame = 1;
+  feed.cpu = -1;
+  CHECK(hs_get_state(nullptr, 0, nullptr, nullptr) == HS_E_INVAL);
+  const std::string before = hs_last_error();
+  fake::device = 3;
+  CHECK(hs_run_feeds(&feed, 1, 0.0, 4, &results, nullptr, nullptr, nullptr) == HS_OK);
+  CHECK(before == hs_last_error() && fake::device == 3);
+  feed.batch = 2;                            // more than the application takes: its submits fail
+  const uint8_t* two[2] = {nullptr, nullptr};
+  feed.d_frames = two;
+  CHECK(hs_run_feeds(&feed, 1, 0.0, 4, &results, nullptr, nullptr, nullptr) == HS_E_INVAL);
+  CHECK(strstr(hs_last_error(), "feed 0: hs_submit_batch: NULL frame pointer") && fake::device == 3);
+  CHECK(hs_destroy_app(feed.app) == HS_OK);
+}
+
 // Every other call that allocates: a refused allocation is an error code.  A submit that fails after
 // work has been handed over leaves an application that says so.
 static void call_failures() {
@@ -544,6 +569,7 @@ int main(int argc, char** argv) {
   else if (check == "one_queue_alone") one_queue_alone();
   else if (check == "end_of_a_frame") end_of_a_frame();
   else if (check == "partition_failures") partition_failures();
+  else if (check == "callers_thread") callers_thread();
   else if (check == "small_network_forms") small_network_forms();
   else if (check == "timed_small_network") timed_small_network();
   else { printf("no check named '%s'\n", check.c_str()); return 2; }

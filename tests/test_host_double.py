@@ -27,7 +27,7 @@ def host_double(tmp_path_factory):
 
 @pytest.mark.parametrize("check", ["packing_threads", "create_failures", "group_failures", "feed_failures",
                                    "call_failures", "mux_failures", "pinned_wait", "ready_result", "endless_wait",
-                                   "prefetched_weights", "tile_grids", "one_queue_alone", "end_of_a_frame", "partition_failures", "small_network_forms",
+                                   "prefetched_weights", "tile_grids", "one_queue_alone", "end_of_a_frame", "partition_failures", "callers_thread", "small_network_forms",
                                    "timed_small_network"])
 def test_host_code(host_double, check):
     r = subprocess.run([host_double, check], capture_output=True, text=True, timeout=120)
