@@ -123,8 +123,9 @@ typedef struct {
  * ends on the device's clock, and a GPU event behind stage 2 or 3 ties that clock to the overlay's
  * end (stamps within 1 us); a frame submitted while the application is idle, unpartitioned and
  * without annotations, B * frame_w * frame_h at most 4194304, takes the overlay's end from its
- * last workgroup instead (within 2 us, some more where other applications hold up that
- * workgroup).  With graph launch, and while kernels are timed, GPU events give them all (a few
+ * last workgroup, or from its search for the channel maxima if that takes longer, instead (within 2.5 us, some
+ * more where other applications hold up that workgroup).  Members of a group do so where their maps have
+ * equally many cells.  With graph launch, and while kernels are timed, GPU events give them all (a few
  * us, since every event is a packet of its own there).
  * Stage 3's per-cell outputs (heat, mask) are written by stage 2's last kernel; stage 3 ends when
  * its channel maxima (argmax, present, peak) have been found.  Without the annotation layer that is
